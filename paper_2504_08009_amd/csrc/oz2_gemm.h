@@ -1,0 +1,131 @@
+// Device and host helpers shared by the INT8 GEMM kernels (oz2_stage2.hip, oz2_stage2_tiles.hip).
+#ifndef OZ2_GEMM_H
+#define OZ2_GEMM_H
+
+#include "oz2_internal.h"
+
+// Division of numbers below 2^31 by one that the host knows: with s = 31 + ceil(log2 d) and m = ceil(2^s / d),
+// n m / 2^s exceeds n / d by less than 1 / d.  On the device a scalar multiplication and a shift; the compiler's own
+// division goes through the vector units' FP32 reciprocal, some thirty instructions per quotient that a workgroup
+// would wait for between two tiles.
+struct FastDiv {
+  unsigned m, s;
+};
+inline FastDiv fast_div(unsigned d) {
+  unsigned log = 0;
+  while (((uint64_t)1 << log) < d) ++log;
+  return {(unsigned)((((uint64_t)1 << (31 + log)) + d - 1) / d), 31 + log};
+}
+__device__ __forceinline__ int operator/(int n, const FastDiv& d) {
+  return (int)(((uint64_t)(unsigned)n * d.m) >> d.s);
+}
+
+// 16-byte-per-lane direct load global -> LDS.  The wave writes 1024 contiguous bytes starting at the
+// LDS byte address in M0; lane l's 16 bytes come from base + its own 32-bit byte offset.  Written as
+// inline assembly so that completion is tracked by the kernels' explicit vmcnt waits (one per k-tile)
+// instead of a conservative wait after every load.
+__device__ __forceinline__ void load_to_lds_16(const int8_t* base, unsigned voff, unsigned lds_addr) {
+  asm volatile(
+      "s_mov_b32 m0, %2\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %0, %1"
+      :
+      : "v"(voff), "s"(base), "s"(lds_addr)
+      : "memory", "m0");
+}
+
+// s_waitcnt vmcnt(N) only (gfx9 encoding: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8)
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  static_assert(N >= 0 && N < 64, "six bits");
+  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+}
+
+// wait_vmcnt<STRICT>, or wait_vmcnt<LOOSE> while i is below `below` (both uniform): one scalar branch, where the compiler
+// makes three of the two-sided form.
+template <int STRICT, int LOOSE>
+__device__ __forceinline__ void wait_vmcnt_unless_below(int i, int below) {
+  static_assert(0 <= STRICT && STRICT <= LOOSE && LOOSE < 64, "six bits");
+  asm volatile(
+      "s_cmp_lt_i32 %0, %1\n\t"
+      "s_cbranch_scc1 .Loose%=\n\t"
+      "s_waitcnt vmcnt(%2)\n"
+      ".Loose%=:\n\t"
+      "s_waitcnt vmcnt(%3)"
+      :
+      : "s"(i), "s"(below), "n"(STRICT), "n"(LOOSE)
+      : "memory", "scc");
+}
+
+// ---------------------------------------------------------------------------------------------------
+// Algorithm 1 line 7 in the epilogue of the products: the residue in [0, p) of an INT32 c', as a byte.
+//   acc = c' + OZ2_ACC_START modulo 2^32 (the accumulators start there).  As an unsigned word with bytes b3..b0,
+//   x = sum_i b_i (2^(8 i) mod p) + ((-OZ2_ACC_START) mod p) is congruent to c' and at most 2^18; one byte dot product
+//   forms it on top of the bits of the float 2^23 + e, so that its result read as a float is 2^23 + e + x exactly.
+//   With e chosen so that (2^23 + e) / p lies (p + 1) / (2 p) above an integer, the one rounding of
+//   fma(2^23 + e + x, 1/p, K) gives 2^23 + floor(x / p) + j (j a constant): the exact quotient plus one half stays
+//   1/(2p) away from every tie, further than 1/p's rounding moves it.  j is what makes e + x - (quotient bits) p congruent to
+//   x - floor(x / p) p modulo 256, i.e. the low byte of one 16-bit multiply-add is the residue.
+//   256 needs no quotient (the low byte of x is the residue, and 256 times anything leaves it alone).
+//   OZ2_ACC_START is an inline constant of the MFMA (the bits of 1 / (2 pi)) whose lower 22 bits lie near their middle:
+//   sums of |c'| < 2^20.8, which is nearly all of them, agree in their upper ten bits whatever their sign, and the
+//   matrix cores switch that much less (they run at the card's power limit; against a start at 2^31, GEMM of 26
+//   moduli at 8192^3: 10.61 -> 10.47 ms).  It must exceed every |c'|: terms of at most 2^14, so blocks of the inner
+//   dimension of at most OZ2_ACC_BLOCK, plus what a reduction between blocks leaves (below 3 p).
+// ---------------------------------------------------------------------------------------------------
+#define OZ2_ACC_START 0x3e22f983u
+#define OZ2_ACC_BLOCK 61440
+static_assert((uint64_t)OZ2_ACC_BLOCK * (1 << 14) + 3 * 256 < OZ2_ACC_START, "sums stay positive");
+
+inline Oz2FoldConsts oz2_fold_consts(int p) {
+  Oz2FoldConsts c;
+  const unsigned u = (unsigned)p, k1 = 256u % u, k2 = k1 * k1 % u, k3 = k2 * k1 % u;
+  c.p = p;
+  c.inv_p = 1.0f / (float)p;
+  c.kpack = (1u % u) | (k1 << 8) | (k2 << 16) | (k3 << 24);
+  c.neg_p = (1u << 16) - u;
+  const unsigned start = (u - OZ2_ACC_START % u) % u;
+  unsigned e = 0, j = 0, above = 0;
+  if (u & 1u) {
+    const unsigned half = (u + 1u) / 2u;
+    e = (half + u - (1u << 23) % u) % u;
+    above = ((1u << 23) + e - half) / u;
+    unsigned inv = u;  // 1/p modulo 256: each step doubles the number of right bits (p p = 1 modulo 8)
+    for (int i = 0; i < 3; ++i) inv *= 2u - u * inv;
+    j = (e * inv) & 255u;
+  }
+  c.base = 0x4b000000u + e + start;
+  c.offset = (float)((1u << 23) - above - 1u + j);
+  return c;
+}
+
+// Four byte sums x (the results of the dot product) -> four residues, one per byte: two of the 16-bit multiply-adds write
+// the upper half of a register whose lower half the other two have written, and one byte permutation collects all four.
+__device__ __forceinline__ unsigned oz2_fold_residues4(const unsigned* x, const Oz2FoldConsts& c) {
+  unsigned t[4], lo, hi;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) t[i] = __float_as_uint(fmaf(__uint_as_float(x[i]), c.inv_p, c.offset));
+  asm("v_mad_u16 %0, %1, %2, %3" : "=v"(lo) : "v"(t[0]), "v"(c.neg_p), "v"(x[0]));
+  asm("v_mad_u16 %0, %1, %2, %3" : "=v"(hi) : "v"(t[2]), "v"(c.neg_p), "v"(x[2]));
+  asm("v_mad_u16 %0, %1, %2, %3 op_sel:[0,0,0,1]" : "+v"(lo) : "v"(t[1]), "v"(c.neg_p), "v"(x[1]));
+  asm("v_mad_u16 %0, %1, %2, %3 op_sel:[0,0,0,1]" : "+v"(hi) : "v"(t[3]), "v"(c.neg_p), "v"(x[3]));
+  return __builtin_amdgcn_perm(hi, lo, 0x06040200u);
+}
+
+// The constants in vector registers: an operand from a scalar register costs an instruction a cycle.
+__device__ __forceinline__ unsigned to_vector(unsigned v) {
+  unsigned r;
+  asm volatile("v_mov_b32 %0, %1" : "=v"(r) : "s"(v));
+  return r;
+}
+__device__ __forceinline__ Oz2FoldConsts in_vector_registers(const Oz2FoldConsts& c) {
+  Oz2FoldConsts v = c;
+  v.kpack = to_vector(c.kpack);
+  v.base = to_vector(c.base);
+  v.neg_p = to_vector(c.neg_p);
+  v.inv_p = __uint_as_float(to_vector(__float_as_uint(c.inv_p)));
+  v.offset = __uint_as_float(to_vector(__float_as_uint(c.offset)));
+  return v;
+}
+
+#endif

@@ -55,6 +55,16 @@ struct Oz2CrtDigits {
                         // of the L in use): added after the MFMA, whose accumulator then starts at the inline zero
 };
 
+// Constants of line 7 in the epilogue of the products for one modulus (oz2_fold_consts in oz2_gemm.h).
+struct Oz2FoldConsts {
+  int p;
+  float inv_p;       // RN(1/p)
+  unsigned kpack;    // 2^(8 i) mod p in byte i
+  unsigned base;     // bits of the float 2^23, plus what the byte sums start from
+  float offset;
+  unsigned neg_p;    // 2^16 - p
+};
+
 struct Oz2Plan {
   int N;
   int kappa;

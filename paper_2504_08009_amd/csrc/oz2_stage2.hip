@@ -18,8 +18,8 @@
 // ds_read_b128 fall on 16 different bank groups (measured: no bank conflicts).
 //
 // Schedule of one k-tile (two MFMA k-steps of 16 MFMAs): during step 0 the fragments of step 1 are read
-// from LDS; then one vmcnt wait + barrier makes the NEXT k-tile visible to all waves; during step 1 the
-// first fragments of that next tile are read and the 8 direct loads that refill the stage freed by the
+// from LDS; two MFMAs into step 1 one vmcnt wait + barrier makes the NEXT k-tile visible to all waves; during the rest
+// of step 1 the first fragments of that next tile are read and the 8 direct loads that refill the stage freed by the
 // barrier are issued, one LDS read per two MFMAs and one global load per two MFMAs, so that no queue
 // fills up and stalls MFMA issue.
 //
@@ -43,15 +43,14 @@
 // end of the tile it fetches the first k-tiles of the workgroup's next tile, so the copies of a new tile cost no
 // time of their own at the tile boundary (measured against issuing them after the main loop, before the
 // epilogue: GEMM -9 % at k = 1024, -5 % at 4096^3, -1 % at 8192^3, even at 16384^3 where the power cap decides).
-// The loop has one body for every iteration and the same number of copies in flight at every wait: with 256
-// accumulator registers per lane, a second variant of the loop body costs register moves between the variants.
+// The loop has one body for every iteration and the same number of copies in flight at every wait.
 //
 // Structured products: for the symmetric product op(A) op(A)^T both operands are A's planes and the
 // workgroups of the other triangle of tiles return at once; for a triangular operand a tile walks only the
 // k-tiles up to or from its diagonal block.
 #include <type_traits>
 
-#include "oz2_internal.h"
+#include "oz2_gemm.h"
 
 namespace {
 
@@ -66,6 +65,13 @@ constexpr int kStageBytes = (BM + BN) * BK;      // 32 KiB: A tile then B tile
 constexpr int kLdsBytes = NS * kStageBytes;
 constexpr int kLoads = 8;                        // direct loads per wave per k-tile
 constexpr int kGroupM = 8;
+// Products of step 1 in front of the barrier: they and the last two of step 0 cover the arrival of the last fragments
+// read, which the barrier waits for.
+constexpr int kSyncAt = 1;
+// The tile orders below are written for the eight accelerator dies (XCDs) of the MI355X, on which the hardware
+// places workgroup i of a launch on die i % 8.
+constexpr int kXcds = 8;
+constexpr int kStores = 16;                      // stores per wave of an epilogue (UINT8; the INT32 one has more)
 
 struct GemmArgs {
   const int8_t* a;
@@ -82,36 +88,107 @@ struct GemmArgs {
   const unsigned long long* skip_flag;  // if not null and nonzero on the device: the products are not needed
   unsigned long long* xcd_sync;         // one counter per XCD (zero at launch), or null: no round sync
   int full_rounds;                      // rounds in which every workgroup slot has a tile
-  int xcds;                             // accelerator dies of the chip: workgroup i of a launch runs on die i % xcds
   int sync_spins;                       // bound of one wait of the round synchronisation, in polls of the counter
-  float p[OZ2_MAX_PLANES];             // modulus of every plane
+  FastDiv per_modulus;                  // planes per modulus: plane u is reduced modulo number u / per_modulus
+  FastDiv div_plane;                    // tiles, sub-blocks or super-blocks of a plane
+  FastDiv div_rows, div_cols;           // sub-blocks or super-blocks down a column and along a row of them
+  FastDiv div_group, div_last;          // tiles of a group of kGroupM tile rows, tile rows of the last group
+  Oz2FoldConsts fold[OZ2_MAX_N];        // residue epilogue and reduction between k-blocks, per modulus
 };
-
-// 16-byte-per-lane direct load global -> LDS.  The wave writes 1024 contiguous bytes starting at the
-// LDS byte address in M0; lane l's 16 bytes come from base + its own 32-bit byte offset.  Written as
-// inline assembly so that completion is tracked by this file's explicit vmcnt waits (one per k-tile)
-// instead of a conservative wait after every load.
-__device__ __forceinline__ void load_to_lds_16(const int8_t* base, unsigned voff, unsigned lds_addr) {
-  asm volatile(
-      "s_mov_b32 m0, %2\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %0, %1"
-      :
-      : "v"(voff), "s"(base), "s"(lds_addr)
-      : "memory", "m0");
-}
-
-// s_waitcnt vmcnt(N) only (gfx9 encoding: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8)
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-}
 
 // Any representative of c modulo p with |result| <= 3p is enough between k-blocks: the final residue is
 // taken in stage 3.  The quotient is estimated in FP32 (error below two units).
 __device__ __forceinline__ int reduce_mod(int c, int p, float inv_p) {
   int q = (int)rintf((float)c * inv_p);
   return c - q * p;
+}
+
+// ---- The 256 accumulators of a lane live in registers by name: MFMA tile (x, y) of the wave's 4 x 4, T = x + 4 y, in
+// the ordinary registers v[112 + 16 T ...] for T < kVgprTiles and in the accumulation registers a[16 T ...] for the
+// others.  An ordinary instruction reads the former directly, the latter only through a move of eight cycles, and
+// of the 256 ordinary registers the kernel's own code needs fewer than 112 (amdgpu_num_vgpr keeps the compiler to
+// them); every statement below names what it writes.  (As variables the accumulators were copied through ordinary
+// registers and scratch memory wherever the main loop meets the code around it: up to 256 moves per tile and 20 to 1200
+// bytes of scratch per lane, depending on the form of the loop.)
+// What the compiler does not see is the distance an MFMA needs to a reader of its result (settle_acc).  Operands come
+// from LDS reads, whose arrival it waits for, and the next MFMA on the same accumulators is fifteen others away.
+constexpr int kVgprTiles = 8;
+template <int T>
+struct Acc;
+#define OZ2_ACC_TILE(T, R, LO, HI, FOLD, READ, WRITE, ...)                                                      \
+  template <>                                                                                                   \
+  struct Acc<T> {                                                                                               \
+    /* acc := acc + a b */                                                                                      \
+    static __device__ __forceinline__ void add(const v4i& a, const v4i& b) {                                    \
+      asm volatile("v_mfma_i32_32x32x32_i8 " R "[" #LO ":" #HI "], %0, %1, " R "[" #LO ":" #HI "]"              \
+                   :                                                                                            \
+                   : "v"(a), "v"(b)                                                                             \
+                   : __VA_ARGS__);                                                                              \
+    }                                                                                                           \
+    /* acc := start + a b */                                                                                    \
+    template <bool RESIDUE_U8>                                                                                  \
+    static __device__ __forceinline__ void start(const v4i& a, const v4i& b) {                                  \
+      if constexpr (RESIDUE_U8)                                                                                 \
+        asm volatile("v_mfma_i32_32x32x32_i8 " R "[" #LO ":" #HI "], %0, %1, 0.15915494" : : "v"(a), "v"(b) : __VA_ARGS__); \
+      else                                                                                                      \
+        asm volatile("v_mfma_i32_32x32x32_i8 " R "[" #LO ":" #HI "], %0, %1, 0" : : "v"(a), "v"(b) : __VA_ARGS__); \
+    }                                                                                                           \
+    static __device__ __forceinline__ unsigned read(int e) {                                                    \
+      unsigned v;                                                                                               \
+      asm volatile(READ " %0, " R "[" #LO "+%1]" : "=v"(v) : "n"(e));                                           \
+      return v;                                                                                                 \
+    }                                                                                                           \
+    static __device__ __forceinline__ void write(int e, unsigned v) {                                           \
+      asm volatile(WRITE " " R "[" #LO "+%1], %0" : : "v"(v), "n"(e) : __VA_ARGS__);                            \
+    }                                                                                                           \
+    /* oz2_fold_sum; its result can be read three instructions later (settle_sums) */                          \
+    static __device__ __forceinline__ unsigned fold_sum(int e, unsigned kpack, unsigned base) {                 \
+      unsigned v;                                                                                               \
+      asm volatile(FOLD(LO) : "=&v"(v) : "v"(kpack), "v"(base), "n"(e));                                        \
+      return v;                                                                                                 \
+    }                                                                                                           \
+  };
+#define OZ2_FOLD_V(LO) "v_dot4_u32_u8 %0, v[" #LO "+%3], %1, %2"
+#define OZ2_FOLD_A(LO) "v_accvgpr_read_b32 %0, a[" #LO "+%3]\n\tv_dot4_u32_u8 %0, %0, %1, %2"
+OZ2_ACC_TILE(0, "v", 112, 127, OZ2_FOLD_V, "v_mov_b32", "v_mov_b32", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119", "v120", "v121", "v122", "v123", "v124", "v125", "v126", "v127")
+OZ2_ACC_TILE(1, "v", 128, 143, OZ2_FOLD_V, "v_mov_b32", "v_mov_b32", "v128", "v129", "v130", "v131", "v132", "v133", "v134", "v135", "v136", "v137", "v138", "v139", "v140", "v141", "v142", "v143")
+OZ2_ACC_TILE(2, "v", 144, 159, OZ2_FOLD_V, "v_mov_b32", "v_mov_b32", "v144", "v145", "v146", "v147", "v148", "v149", "v150", "v151", "v152", "v153", "v154", "v155", "v156", "v157", "v158", "v159")
+OZ2_ACC_TILE(3, "v", 160, 175, OZ2_FOLD_V, "v_mov_b32", "v_mov_b32", "v160", "v161", "v162", "v163", "v164", "v165", "v166", "v167", "v168", "v169", "v170", "v171", "v172", "v173", "v174", "v175")
+OZ2_ACC_TILE(4, "v", 176, 191, OZ2_FOLD_V, "v_mov_b32", "v_mov_b32", "v176", "v177", "v178", "v179", "v180", "v181", "v182", "v183", "v184", "v185", "v186", "v187", "v188", "v189", "v190", "v191")
+OZ2_ACC_TILE(5, "v", 192, 207, OZ2_FOLD_V, "v_mov_b32", "v_mov_b32", "v192", "v193", "v194", "v195", "v196", "v197", "v198", "v199", "v200", "v201", "v202", "v203", "v204", "v205", "v206", "v207")
+OZ2_ACC_TILE(6, "v", 208, 223, OZ2_FOLD_V, "v_mov_b32", "v_mov_b32", "v208", "v209", "v210", "v211", "v212", "v213", "v214", "v215", "v216", "v217", "v218", "v219", "v220", "v221", "v222", "v223")
+OZ2_ACC_TILE(7, "v", 224, 239, OZ2_FOLD_V, "v_mov_b32", "v_mov_b32", "v224", "v225", "v226", "v227", "v228", "v229", "v230", "v231", "v232", "v233", "v234", "v235", "v236", "v237", "v238", "v239")
+OZ2_ACC_TILE(8, "a", 128, 143, OZ2_FOLD_A, "v_accvgpr_read_b32", "v_accvgpr_write_b32", "a128", "a129", "a130", "a131", "a132", "a133", "a134", "a135", "a136", "a137", "a138", "a139", "a140", "a141", "a142", "a143")
+OZ2_ACC_TILE(9, "a", 144, 159, OZ2_FOLD_A, "v_accvgpr_read_b32", "v_accvgpr_write_b32", "a144", "a145", "a146", "a147", "a148", "a149", "a150", "a151", "a152", "a153", "a154", "a155", "a156", "a157", "a158", "a159")
+OZ2_ACC_TILE(10, "a", 160, 175, OZ2_FOLD_A, "v_accvgpr_read_b32", "v_accvgpr_write_b32", "a160", "a161", "a162", "a163", "a164", "a165", "a166", "a167", "a168", "a169", "a170", "a171", "a172", "a173", "a174", "a175")
+OZ2_ACC_TILE(11, "a", 176, 191, OZ2_FOLD_A, "v_accvgpr_read_b32", "v_accvgpr_write_b32", "a176", "a177", "a178", "a179", "a180", "a181", "a182", "a183", "a184", "a185", "a186", "a187", "a188", "a189", "a190", "a191")
+OZ2_ACC_TILE(12, "a", 192, 207, OZ2_FOLD_A, "v_accvgpr_read_b32", "v_accvgpr_write_b32", "a192", "a193", "a194", "a195", "a196", "a197", "a198", "a199", "a200", "a201", "a202", "a203", "a204", "a205", "a206", "a207")
+OZ2_ACC_TILE(13, "a", 208, 223, OZ2_FOLD_A, "v_accvgpr_read_b32", "v_accvgpr_write_b32", "a208", "a209", "a210", "a211", "a212", "a213", "a214", "a215", "a216", "a217", "a218", "a219", "a220", "a221", "a222", "a223")
+OZ2_ACC_TILE(14, "a", 224, 239, OZ2_FOLD_A, "v_accvgpr_read_b32", "v_accvgpr_write_b32", "a224", "a225", "a226", "a227", "a228", "a229", "a230", "a231", "a232", "a233", "a234", "a235", "a236", "a237", "a238", "a239")
+OZ2_ACC_TILE(15, "a", 240, 255, OZ2_FOLD_A, "v_accvgpr_read_b32", "v_accvgpr_write_b32", "a240", "a241", "a242", "a243", "a244", "a245", "a246", "a247", "a248", "a249", "a250", "a251", "a252", "a253", "a254", "a255")
+#undef OZ2_FOLD_V
+#undef OZ2_FOLD_A
+#undef OZ2_ACC_TILE
+static_assert(OZ2_ACC_START == 0x3e22f983u, "the bits of 1 / (2 pi), an inline constant of the instruction");
+
+// The wait between the last MFMA of sixteen passes and the first use of a result by another instruction (19 states),
+// and between a write by another instruction and the next MFMA.
+__device__ __forceinline__ void settle_acc() { asm volatile("s_nop 15\n\ts_nop 3"); }
+// The wait between a byte dot product and the first use of its result by another kind of instruction.
+__device__ __forceinline__ void settle_sums(unsigned (&x)[16]) {
+  asm volatile("s_nop 2"
+               : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]), "+v"(x[8]),
+                 "+v"(x[9]), "+v"(x[10]), "+v"(x[11]), "+v"(x[12]), "+v"(x[13]), "+v"(x[14]));
+  asm volatile("" : "+v"(x[15]));
+}
+
+// Calls f(integral_constant<int, 0>) .. f(integral_constant<int, COUNT - 1>).
+template <int COUNT, int I = 0, class F>
+__device__ __forceinline__ void unrolled(F&& f) {
+  if constexpr (I < COUNT) {
+    f(std::integral_constant<int, I>());
+    unrolled<COUNT, I + 1>(f);
+  }
 }
 
 struct Frag {
@@ -121,7 +198,7 @@ struct Frag {
 // What one workgroup needs to know about a unit of work.
 struct Tile {
   int t, tm, tn;
-  int ktiles;            // k-tiles this tile walks (may be 0: the tile is then all zeros)
+  int ktiles;            // k-tiles this tile walks, at least 1
   const int8_t* a_wave;  // first byte this wave copies of the tile's first k-tile of A'
   const int8_t* b_wave;  // same for B'
   bool valid;            // false: nothing to compute for this work index
@@ -146,10 +223,10 @@ __device__ __forceinline__ Tile decode_tile(const GemmArgs& g, int slot, int wv)
     const int rnd = idx >> 5, within = idx & 31;
     const int sub_m = g.tiles_m >> 3, per_plane = sub_m * (g.tiles_n >> 2);
     const int entry = rnd * 8 + x;
-    t = entry / per_plane;
+    t = entry / g.div_plane;
     if (t >= g.num_moduli) return T;
     const int r = entry - t * per_plane;
-    const int sn = r / sub_m, sm = r - sn * sub_m;
+    const int sn = r / g.div_rows, sm = r - sn * sub_m;
     tm = sm * 8 + (within & 7);
     tn = sn * 4 + (within >> 3);
   } else if (g.superblock) {
@@ -158,7 +235,7 @@ __device__ __forceinline__ Tile decode_tile(const GemmArgs& g, int slot, int wv)
     const int x = slot & 7, idx = slot >> 3;
     const int sb = idx >> 5, within = idx & 31;
     const int sbs_m = g.tiles_m >> 4, sbs_n = g.tiles_n >> 4;
-    t = sb / (sbs_m * sbs_n);
+    t = sb / g.div_plane;
     const int sr = sb - t * (sbs_m * sbs_n);
     // Structured products: the eight sub-blocks of a super-block hold different amounts of work (tiles beyond
     // the diagonal are skipped, tiles of a triangular operand differ in length), so the sub-block an XCD takes
@@ -166,10 +243,11 @@ __device__ __forceinline__ Tile decode_tile(const GemmArgs& g, int slot, int wv)
     const int xp = (g.triangle | g.krange) ? ((x + sr + t) & 7) : x;
     // super-block coordinates; with a triangular operand the super-blocks with the longest tiles go first
     // (measured at 16384: 32.0 -> 30.1 ms for the product with a lower triangular first operand)
-    int sm = sr % sbs_m, sn = sr / sbs_m;
-    if (g.krange == OZ2_KRANGE_UPTO_ROW) { sm = sbs_m - 1 - sr / sbs_n; sn = sr % sbs_n; }
-    if (g.krange == OZ2_KRANGE_FROM_ROW) { sm = sr / sbs_n; sn = sr % sbs_n; }
-    if (g.krange == OZ2_KRANGE_UPTO_COL) { sn = sbs_n - 1 - sr / sbs_m; }
+    const int by_rows = sr / g.div_rows, by_cols = sr / g.div_cols;
+    int sm = sr - by_rows * sbs_m, sn = by_rows;
+    if (g.krange == OZ2_KRANGE_UPTO_ROW) { sm = sbs_m - 1 - by_cols; sn = sr - by_cols * sbs_n; }
+    if (g.krange == OZ2_KRANGE_FROM_ROW) { sm = by_cols; sn = sr - by_cols * sbs_n; }
+    if (g.krange == OZ2_KRANGE_UPTO_COL) { sn = sbs_n - 1 - by_rows; }
     tm = sm * 16 + (xp & 1) * 8 + (within & 7);
     tn = sn * 16 + (xp >> 1) * 4 + (within >> 3);
     if (t >= g.num_moduli) return T;
@@ -177,15 +255,19 @@ __device__ __forceinline__ Tile decode_tile(const GemmArgs& g, int slot, int wv)
     const int item = (slot & 7) * g.chunk + (slot >> 3);
     if (item >= g.total) return T;
     const int per_t = g.tiles_m * g.tiles_n;
-    t = item / per_t;
+    t = item / g.div_plane;
     const int r = item - t * per_t;
     const int per_group = kGroupM * g.tiles_n;
-    const int gid = r / per_group;
+    const int gid = r / g.div_group;
     const int first_m = gid * kGroupM;
-    const int gsize = g.tiles_m - first_m < kGroupM ? g.tiles_m - first_m : kGroupM;
     const int rr = r - gid * per_group;
-    tm = first_m + rr % gsize;
-    tn = rr / gsize;
+    if (g.tiles_m - first_m < kGroupM) {
+      tn = rr / g.div_last;
+      tm = first_m + rr - tn * (g.tiles_m - first_m);
+    } else {
+      tn = rr / kGroupM;
+      tm = first_m + rr % kGroupM;
+    }
   }
   // symmetric product: the other triangle of tiles is never needed
   if ((g.triangle == 1 && tm < tn) || (g.triangle == 2 && tm > tn)) return T;
@@ -217,7 +299,7 @@ __device__ __forceinline__ Tile decode_tile(const GemmArgs& g, int slot, int wv)
 // A kernel of its own: the reduction's 256 x 8 instructions need so many registers at once that the compiler parks
 // 48 accumulators in scratch memory around it, on the path of every tile, and the instantiation without it does not.
 template <bool RESIDUE_U8, bool LIST_ORDER, bool EARLY_ARRIVAL, bool KBLOCKED>
-__global__ void __launch_bounds__(kThreads) gemm_i8_kernel(const GemmArgs g) {
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))) gemm_i8_kernel(const GemmArgs g) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
 
   // stage 1 found an infinity or a NaN: the FP64 fallback forms C, these products would be thrown away
@@ -281,7 +363,6 @@ __global__ void __launch_bounds__(kThreads) gemm_i8_kernel(const GemmArgs g) {
       F.b[q - 4] = *reinterpret_cast<const v4i*>(base + b_row_off + (q - 4) * 32 * BK + coff);
   };
 
-  v16i acc[4][4];
 
 // Operand roles of v_mfma_i32_32x32x32_i8: the rows of the first operand run over the result registers
 // (lane l, register e: row 8 (e / 4) + 4 (l / 32) + e % 4), the rows of the second over the lanes (row l % 32).
@@ -289,16 +370,28 @@ __global__ void __launch_bounds__(kThreads) gemm_i8_kernel(const GemmArgs g) {
 //   stored as 2 x 128 contiguous bytes of a column of C'.
 //   UINT8 export: first = A', second = B': each group of four registers holds four consecutive rows i of
 //   one column, i.e. the four bytes of one 32-bit store.
-#define OZ2_MFMA(F, q)                                                                                        \
-  acc[(q)&3][(q) >> 2] =                                                                                      \
-      RESIDUE_U8 ? __builtin_amdgcn_mfma_i32_32x32x32_i8(F.a[(q)&3], F.b[(q) >> 2], acc[(q)&3][(q) >> 2], 0, 0, 0) \
-                 : __builtin_amdgcn_mfma_i32_32x32x32_i8(F.b[(q) >> 2], F.a[(q)&3], acc[(q)&3][(q) >> 2], 0, 0, 0)
+  // The sixteen products of a k-step go back and forth over the rows, so that every one shares an operand with the
+  // one before it: product q is tile (q % 4 or 3 - q % 4, q / 4).
+  auto mfma = [&](const Frag& F, auto qc) {
+    constexpr int q = decltype(qc)::value, x = (q & 4) ? 3 - (q & 3) : q & 3, y = q >> 2;
+    if constexpr (RESIDUE_U8)
+      Acc<4 * y + x>::add(F.a[x], F.b[y]);
+    else
+      Acc<4 * y + x>::add(F.b[y], F.a[x]);
+  };
+  auto mfma_start = [&](const Frag& F, auto qc) {
+    constexpr int q = decltype(qc)::value, x = (q & 4) ? 3 - (q & 3) : q & 3, y = q >> 2;
+    if constexpr (RESIDUE_U8)
+      Acc<4 * y + x>::template start<true>(F.a[x], F.b[y]);
+    else
+      Acc<4 * y + x>::template start<false>(F.b[y], F.a[x]);
+  };
 
   prologue_loads(cur, 0);
   bool first = true;
   int round = 0;
   int stage = 0;  // stage that holds k-tile 0 of the current tile
-  const int xcd = blockIdx.x % g.xcds;
+  const int xcd = blockIdx.x % kXcds;
   for (;;) {
   const int ktiles = cur.ktiles;
   const int t = cur.t, tm = cur.tm, tn = cur.tn;
@@ -316,22 +409,15 @@ __global__ void __launch_bounds__(kThreads) gemm_i8_kernel(const GemmArgs g) {
   const bool across = nxt.valid && ktiles >= NS - 1 && nxt.ktiles >= NS - 1;
   const int8_t* const over_a = across ? nxt.a_wave : cur.a_wave;
   const int8_t* const over_b = across ? nxt.b_wave : cur.b_wave;
-#pragma unroll
-  for (int x = 0; x < 4; ++x)
-#pragma unroll
-    for (int y = 0; y < 4; ++y)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[x][y][e] = RESIDUE_U8 ? (int)0x80000000 : 0;
-  // (the residue epilogue works on c' + 2^31 as an unsigned word: the accumulators start there, modulo 2^32)
 
-  // ---- k-tiles 0 .. NS-2 are in flight: make tile 0 visible, its first fragments in registers.  After the
-  // first tile of the loop the previous epilogue's stores are outstanding as well and cannot be told apart
-  // from loads by the counter, so everything is waited for (the loads were issued before that epilogue).
+  // ---- k-tiles 0 .. NS-2 are in flight: make tile 0 visible, its first fragments in registers.  After the first
+  // tile of the loop the kStores stores of the previous epilogue were issued behind those copies; the counter goes
+  // down in issue order, so a wait that leaves that many more operations outstanding covers the copies alone and the
+  // stores drain during the first k-tiles.
   if (first)
     wait_vmcnt<(NS - 2) * kLoads>();
   else
-    wait_vmcnt<0>();
-  first = false;
+    wait_vmcnt<(NS - 2) * kLoads + kStores>();
   if (g.xcd_sync != nullptr && round < g.full_rounds && threadIdx.x == 0) {
     // The workgroups of an XCD start their tiles of a round together.  The wait is bounded (about a millisecond).
     // If it runs to its bound, the workgroups of this XCD are not all resident at once (another kernel holds
@@ -340,7 +426,7 @@ __global__ void __launch_bounds__(kThreads) gemm_i8_kernel(const GemmArgs g) {
     // (A flag kept in a register instead would live across the main loop, where no register is free.)
     unsigned long long* c = g.xcd_sync + xcd;
     if (!EARLY_ARRIVAL || round == 0) atomicAdd(c, 1ull);
-    const unsigned long long target = (unsigned long long)(gridDim.x / g.xcds) * (unsigned long long)(round + 1);
+    const unsigned long long target = (unsigned long long)(gridDim.x / kXcds) * (unsigned long long)(round + 1);
     bool arrived = false;
     for (int spins = 0; spins < g.sync_spins; ++spins) {
       if (__hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= target) {
@@ -355,6 +441,8 @@ __global__ void __launch_bounds__(kThreads) gemm_i8_kernel(const GemmArgs g) {
     }
   }
   ++round;
+  const int store_window = first ? 0 : NS - 2;
+  first = false;
   __syncthreads();
   Frag F0, F1;
 #pragma unroll
@@ -363,62 +451,83 @@ __global__ void __launch_bounds__(kThreads) gemm_i8_kernel(const GemmArgs g) {
   // fa, fb: where the next fetch reads (k-tile kt + NS - 1 of this tile while that exists)
   const int8_t* fa = NS - 1 < ktiles ? cur.a_wave + (size_t)(NS - 1) * (BM * BK) : cur.a_wave;
   const int8_t* fb = NS - 1 < ktiles ? cur.b_wave + (size_t)(NS - 1) * (BN * BK) : cur.b_wave;
-  auto body = [&](int kt) {
-    const char* base = lds + stage * kStageBytes;
+  // step 0 of k-tile kt: MFMAs on F0, fetch F1 = (tile kt, step 1)
+  auto fetch_f1 = [&](int kt, int q) {
+    if (q == 0 || ((q & 1) && q < 15)) rd(F1, lds + stage * kStageBytes, off_s1, (q + 1) >> 1);
+    if (q == 1 && kt + NS - 1 == ktiles) {  // the fetches run past the end of this tile from here on
+      fa = over_a;
+      fb = over_b;
+    }
+  };
+  auto step0 = [&](int kt) {
+    unrolled<16>([&](auto q) {
+      mfma(F0, q);
+      fetch_f1(kt, q);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  // step 1 of k-tile kt: MFMAs on F1, fetch F0 = (tile kt+1, step 0), issue the loads of tile kt+NS-1
+  auto step1 = [&](int kt) {
     const int nstage = stage + 1 == NS ? 0 : stage + 1;
     const char* nbase = lds + nstage * kStageBytes;
     const int lstage = stage == 0 ? NS - 1 : stage - 1;  // stage of tile kt-1 == stage of tile kt+NS-1
-    // step 0: MFMAs on F0, fetch F1 = (tile kt, step 1)
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      OZ2_MFMA(F0, q);
-      if ((q & 1) == 0) rd(F1, base, off_s1, q >> 1);
-      if (q == 1 && kt + NS - 1 == ktiles) {  // the fetches run past the end of this tile from here on
-        fa = over_a;
-        fb = over_b;
+    unrolled<16>([&](auto q) {
+      mfma(F1, q);
+      if constexpr (q == kSyncAt) {
+        // k-tile kt+1 must be complete in LDS for every wave before anyone reads it; passing this barrier
+        // also means every wave has finished reading k-tile kt-1, whose stage is refilled below.  In the first NS - 2
+        // iterations the previous epilogue's stores lie between the copies waited for and the newest operation.
+        wait_vmcnt_unless_below<(NS - 3) * kLoads, (NS - 3) * kLoads + kStores>(kt, store_window);
+        __syncthreads();
       }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    // k-tile kt+1 must be complete in LDS for every wave before anyone reads it; passing this barrier
-    // also means every wave has finished reading k-tile kt-1, whose stage is refilled below
-    wait_vmcnt<(NS - 3) * kLoads>();
-    __syncthreads();
-    // step 1: MFMAs on F1, fetch F0 = (tile kt+1, step 0), issue the loads of tile kt+NS-1
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      OZ2_MFMA(F1, q);
-      if ((q & 1) == 0) rd(F0, nbase, off_s0, q >> 1);
-      if ((q & 1) == 1) gl(fa, fb, lstage, q >> 1);
+      if constexpr (q > kSyncAt) {
+        constexpr int left = 15 - kSyncAt;  // read r and load r stand at this distance from the barrier
+        unrolled<8>([&](auto r) {
+          if constexpr (decltype(r)::value * (left - 1) / 7 + 1 == q - kSyncAt) rd(F0, nbase, off_s0, r);
+          if constexpr ((decltype(r)::value * (left - 1) + 6) / 7 + 1 == q - kSyncAt) gl(fa, fb, lstage, r);
+        });
+      }
       if (q == 15 && (kt + NS - 1 < ktiles || across)) {
         fa += BM * BK;
         fb += BN * BK;
       }
       __builtin_amdgcn_sched_barrier(0);
-    }
+    });
     stage = nstage;
   };
 
-  const int p_int = (int)g.p[t];
-  const float inv_pf = 1.0f / g.p[t];
-  if constexpr (KBLOCKED) {
-    for (int kt0 = 0; kt0 < ktiles; kt0 += g.ktiles_per_block) {
-      const int kt1 = kt0 + g.ktiles_per_block < ktiles ? kt0 + g.ktiles_per_block : ktiles;
-      int kt = kt0;
-      for (; kt < kt1; ++kt) body(kt);
-      if (kt1 < ktiles) {  // between k-blocks: bring the accumulators back near zero
-#pragma unroll
-        for (int x = 0; x < 4; ++x)
-#pragma unroll
-          for (int y = 0; y < 4; ++y)
-#pragma unroll
-            for (int e = 0; e < 16; ++e)
-              acc[x][y][e] = RESIDUE_U8 ? (reduce_mod(acc[x][y][e] ^ (int)0x80000000, p_int, inv_pf) ^ (int)0x80000000)
-                                        : reduce_mod(acc[x][y][e], p_int, inv_pf);
+  const Oz2FoldConsts& fc = g.fold[t / g.per_modulus];
+  const Oz2FoldConsts fv = in_vector_registers(fc);  // ahead of the main loop, which hides their loads
+  // The first products of a tile start from an inline constant of the instruction (clearing 256 accumulators takes
+  // 8 cycles each, 2000 of the tile's 30000 at k = 1024), so step 0 of k-tile 0 stands before the loop and the loop
+  // goes from step 1 to step 0 of the next k-tile.
+  unrolled<16>([&](auto q) {
+    mfma_start(F0, q);
+    fetch_f1(0, q);
+    __builtin_amdgcn_sched_barrier(0);
+  });
+  int kt = 0;
+  int block_end = KBLOCKED ? g.ktiles_per_block : 0;
+  while (kt + 1 < ktiles) {
+    step1(kt);
+    ++kt;
+    if constexpr (KBLOCKED) {
+      if (kt == block_end) {  // between k-blocks: bring the accumulators back near zero
+        block_end += g.ktiles_per_block;
+        settle_acc();
+        unrolled<16>([&](auto tile) {
+          constexpr int T = decltype(tile)::value;
+          constexpr int start = RESIDUE_U8 ? (int)OZ2_ACC_START : 0;
+          unrolled<16>([&](auto e) {
+            Acc<T>::write(decltype(e)::value, (unsigned)(reduce_mod((int)Acc<T>::read(decltype(e)::value) - start, fc.p, fc.inv_p) + start));
+          });
+        });
+        settle_acc();
       }
     }
-  } else {
-    for (int kt = 0; kt < ktiles; ++kt) body(kt);
+    step0(kt);
   }
+  step1(kt);
 
   // ---- a next tile whose first copies were not fetched by the main loop above: they fly during the epilogue
   // below.  The barrier makes sure that every wave has left the main loop (all LDS reads of this tile issued) before
@@ -437,19 +546,15 @@ __global__ void __launch_bounds__(kThreads) gemm_i8_kernel(const GemmArgs g) {
   }
 
   // ---- epilogue
+  settle_acc();
   if (RESIDUE_U8) {
-    // Algorithm 1 line 7 here: c'' = c' mod p in [0, p), four residues per 32-bit store.  Lane holds column
+    // Algorithm 1 line 7 here: c'' = c' mod p in [0, p), four residues per 32-bit word.  Lane holds column
     // j = lane % 32 of a 32 x 32 tile, each group of four registers four consecutive rows i.
-    //   u = c' + 2^31 as an unsigned word with bytes b3..b0;  r1 = sum_i b_i (2^(8i) mod p) + ((-2^31) mod p)
-    //   is congruent to c' and below 2^18 (one v_dot4_u32_u8), hence exact in FP32.  floor((r1 + 1/2)/p)
-    //   == floor(r1/p), and (r1 + 1/2)/p stays 2^-9 away from every integer while the FP32 evaluation errs
-    //   by less than 2^-12 (quotient below 2^11), so the floor and the remainder are exact.
-    const unsigned pu = (unsigned)p_int;
-    const unsigned k1 = 256u % pu, k2 = (k1 * k1) % pu, k3 = (k2 * k1) % pu;
-    const unsigned kpack = 1u | (k1 << 8) | (k2 << 16) | (k3 << 24);
-    const unsigned two31 = (((k3 * 128u) % pu));            // 2^31 = 2^24 * 2^7
-    const unsigned bias = (pu - two31) % pu;
-    const float pf = g.p[t], ipf = 1.0f / pf, hipf = 0.5f / pf;
+    // Bound by instruction issue, one wave per SIMD: 3.25 instructions of 5 cycles per element, and the 8-cycle move for
+    // the half that sits in accumulation registers (before: seven, the move for all, and 2000 cycles to clear the
+    // accumulators for the next tile).  With the stores left to drain and the tile decoding on the scalar unit the
+    // work between two main loops went from 13000 to 7500 cycles: GEMM of 18 moduli at 8192 x 8192 x 1024 1.31 -> 1.19 ms
+    // (2.08 POP/s), of 16 at 4096^3 0.87 -> 0.85, of 14 at 2048^3 0.115 -> 0.108, of 26 at 8192^3 10.67 -> 10.50.
     // the wave's corner of the tile (uniform over the wave) and the lane's own offset from it (column lane % 32,
     // rows 16 half ..: below 2^32, m_pad is below 2^27)
     uint8_t* const corner = reinterpret_cast<uint8_t*>(g.c) + (size_t)t * g.n_pad * g.m_pad +
@@ -460,24 +565,20 @@ __global__ void __launch_bounds__(kThreads) gemm_i8_kernel(const GemmArgs g) {
     asm volatile("" : "+s"(start));  // opaque zero: the count below is taken here, in every tile
     const unsigned lane_now = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, start));
     const unsigned lane_off = (lane_now & 31u) * (unsigned)g.m_pad + 16u * (lane_now >> 5);
-#pragma unroll
-    for (int tj = 0; tj < 4; ++tj) {
+    unrolled<4>([&](auto tjc) {
+      constexpr int tj = decltype(tjc)::value;
       // w[ti][a]: rows ti*32 + 8a + 4*half + (0..3) of column j, one byte each
       unsigned w[4][4];
+      unrolled<4>([&](auto tic) {
+        constexpr int ti = decltype(tic)::value;
+        // sixteen elements step by step: a byte dot product's result can only be read three instructions later
+        unsigned x[16];
+        unrolled<16>([&](auto e) { x[e] = Acc<4 * tj + ti>::fold_sum(decltype(e)::value, fv.kpack, fv.base); });
+        settle_sums(x);
 #pragma unroll
-      for (int ti = 0; ti < 4; ++ti)
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          unsigned v = 0;
-#pragma unroll
-          for (int b = 0; b < 4; ++b) {
-            const unsigned u = (unsigned)acc[ti][tj][4 * a + b];
-            const float x = (float)__builtin_amdgcn_udot4(u, kpack, bias, false);
-            const float q = floorf(fmaf(x, ipf, hipf));
-            v = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(-q, pf, x), b, v);
-          }
-          w[ti][a] = v;
-        }
+        for (int a = 0; a < 4; ++a) w[ti][a] = oz2_fold_residues4(x + 4 * a, fv);
+        __builtin_amdgcn_sched_barrier(0);
+      });
       // Lanes l and l + 32 hold the two interleaved halves of the same 32 rows.  Swapping the upper half
       // of w[ti][a] with the lower half of w[ti][a+2] leaves lane l with rows 0..15 and lane l + 32 with
       // rows 16..31 of the 32-row group, 16 contiguous bytes each: one 16-byte store per lane and group,
@@ -490,19 +591,21 @@ __global__ void __launch_bounds__(kThreads) gemm_i8_kernel(const GemmArgs g) {
         v4i o = {(int)s0[0], (int)s0[1], (int)s1[0], (int)s1[1]};
         *reinterpret_cast<v4i*>(cj + ti * 32 + lane_off) = o;
       }
-    }
+      __builtin_amdgcn_sched_barrier(0);
+    });
   } else {
     // lane holds row i = lane % 32 of a 32 x 32 tile, register e column 8 (e / 4) + 4 (lane / 32) + e % 4
     const size_t row = (size_t)tm * BM + wm * 128 + (lane & 31);       // + ti*32
     const size_t col0 = (size_t)tn * BN + wn * 128 + 4 * half;         // + tj*32 + 8*(e/4) + e%4
     int* plane = g.c + (size_t)t * g.n_pad * g.m_pad + row;
-#pragma unroll
-    for (int tj = 0; tj < 4; ++tj)
-#pragma unroll
-      for (int ti = 0; ti < 4; ++ti)
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-          plane[(col0 + tj * 32 + 8 * (e >> 2) + (e & 3)) * g.m_pad + ti * 32] = acc[ti][tj][e];
+    unrolled<4>([&](auto tjc) {
+      unrolled<4>([&](auto tic) {
+        unrolled<16>([&](auto ec) {
+          constexpr int tj = decltype(tjc)::value, ti = decltype(tic)::value, e = decltype(ec)::value;
+          plane[(col0 + tj * 32 + 8 * (e >> 2) + (e & 3)) * g.m_pad + ti * 32] = (int)Acc<4 * tj + ti>::read(e);
+        });
+      });
+    });
   }
   if (!nxt.valid) {
     wait_vmcnt<0>();  // the copies fetched beyond the end of the last tile must have landed before the LDS is given back
@@ -510,7 +613,6 @@ __global__ void __launch_bounds__(kThreads) gemm_i8_kernel(const GemmArgs g) {
   }
   cur = nxt;
   }  // loop over this workgroup's tiles
-#undef OZ2_MFMA
 }
 
 __global__ void clear_sync_kernel(unsigned long long* counters, int count) {
@@ -524,9 +626,6 @@ namespace {
 // Once per process: the kernels' dynamic LDS limit and the number of compute units (a multiple of 8, one
 // workgroup slot each).  Callers hold the library's lock.
 int g_cus = 0;
-// The tile orders above are written for the eight accelerator dies (XCDs) of the MI355X, on which the hardware
-// places workgroup i of a launch on die i % 8.
-constexpr int kXcds = 8;
 int g_sync_spins = 4096;  // polls per wait of the round synchronisation (each followed by a short sleep); 0: off
 hipError_t gemm_setup() {
   if (g_cus) return hipSuccess;
@@ -547,10 +646,11 @@ hipError_t gemm_setup() {
   return hipSuccess;
 }
 
-// num_moduli planes of A' (off_a) times planes of B' (off_b) -> planes of C' (off_c); moduli[t] = modulus of plane t
+// num_moduli planes of A' (off_a) times planes of B' (off_b) -> planes of C' (off_c); plane t is reduced
 // b_is_a: the second operand's planes are the first operand's (symmetric product; m_pad == n_pad)
-hipError_t launch_gemm(const Oz2Layout& lay, char* ws, int num_moduli, const int* moduli, int64_t kblock, int residue_u8,
-                       int triangle, int krange, bool b_is_a, bool check_flag, hipStream_t st) {
+// (moduli: one per per_modulus consecutive planes)
+hipError_t launch_gemm(const Oz2Layout& lay, char* ws, int num_moduli, const int* moduli, int per_modulus, int64_t kblock,
+                       int residue_u8, int triangle, int krange, bool b_is_a, bool check_flag, hipStream_t st) {
   hipError_t e = gemm_setup();
   if (e != hipSuccess) return e;
   if (num_moduli < 1 || num_moduli > OZ2_MAX_PLANES) return hipErrorInvalidValue;
@@ -579,16 +679,30 @@ hipError_t launch_gemm(const Oz2Layout& lay, char* ws, int num_moduli, const int
   const bool list_order = !g.superblock && triangle == 0 && krange == OZ2_KRANGE_ALL && g.tiles_m % 8 == 0 &&
                           g.tiles_n % 4 == 0 && total / 32 >= 64;
   if (list_order) g.chunk = (int)((total / 32 + 7) / 8) * 32;  // whole rounds of 32 tiles per XCD
+  if (list_order) {
+    g.div_rows = fast_div((unsigned)(g.tiles_m / 8));
+    g.div_plane = fast_div((unsigned)(g.tiles_m / 8 * (g.tiles_n / 4)));
+  } else if (g.superblock) {
+    g.div_rows = fast_div((unsigned)(g.tiles_m / 16));
+    g.div_plane = fast_div((unsigned)(g.tiles_m / 16 * (g.tiles_n / 16)));
+  } else {
+    g.div_rows = fast_div(1);
+    g.div_plane = fast_div((unsigned)(g.tiles_m * g.tiles_n));
+  }
+  g.div_cols = fast_div((unsigned)(g.superblock ? g.tiles_n / 16 : 1));
+  g.div_group = fast_div((unsigned)(kGroupM * g.tiles_n));
+  g.div_last = fast_div((unsigned)(g.tiles_m % kGroupM ? g.tiles_m % kGroupM : 1));
   g.ktiles = (int)(lay.k_pad / BK);
-  g.ktiles_per_block = (int)(kblock / BK);
-  for (int t = 0; t < OZ2_MAX_PLANES; ++t) g.p[t] = t < num_moduli ? (float)moduli[t] : 1.0f;
+  // (UINT8: a little below what INT32 holds, see OZ2_ACC_START; the residues do not depend on the blocks)
+  g.ktiles_per_block = (int)((residue_u8 && kblock > OZ2_ACC_BLOCK ? OZ2_ACC_BLOCK : kblock) / BK);
+  g.per_modulus = fast_div((unsigned)per_modulus);
+  for (int t = 0; t < num_moduli / per_modulus; ++t) g.fold[t] = oz2_fold_consts(moduli[t]);
   // General products: one workgroup per compute unit (each holds one: 128 KiB of LDS, 512 registers per lane),
   // every workgroup walks the work indices of its slot in launch order.  Structured products have tiles of
   // unequal length (or none): there the hardware's dynamic placement of one workgroup per index balances better.
   unsigned grid = (unsigned)(g.chunk * 8);
   g.xcd_sync = nullptr;
   g.full_rounds = 0;
-  g.xcds = kXcds;
   g.sync_spins = g_sync_spins;
   if (triangle == 0 && krange == OZ2_KRANGE_ALL) {
     if (grid > (unsigned)g_cus) grid = (unsigned)g_cus;
@@ -656,7 +770,7 @@ hipError_t oz2_launch_clear_sync(const Oz2Layout& lay, char* ws, hipStream_t st)
 
 hipError_t oz2_launch_stage2(const Oz2Plan& plan, const Oz2Layout& lay, char* ws, int64_t kblock, int residue_u8,
                              int triangle, int krange, int check_flag, hipStream_t st) {
-  return launch_gemm(lay, ws, plan.N, plan.moduli, kblock, residue_u8, triangle, krange, triangle != 0, check_flag != 0, st);
+  return launch_gemm(lay, ws, plan.N, plan.moduli, 1, kblock, residue_u8, triangle, krange, triangle != 0, check_flag != 0, st);
 }
 
 // The seven products per modulus of the Strassen form: 7 N planes of half the extents of lay, plane 7 t + s
@@ -668,15 +782,12 @@ hipError_t oz2_launch_strassen_gemm(const Oz2Plan& plan, const Oz2Layout& lay, c
   half.n_pad = lay.n_pad / 2;
   half.k_pad = lay.k_pad / 2;
   if (half.m_pad % BM || half.n_pad % BN || half.k_pad % BK) return hipErrorInvalidValue;
-  int moduli[OZ2_MAX_PLANES];
-  for (int t = 0; t < plan.N; ++t)
-    for (int s = 0; s < 7; ++s) moduli[7 * t + s] = plan.moduli[t];
-  return launch_gemm(half, ws, 7 * plan.N, moduli, kblock, 1, 0, OZ2_KRANGE_ALL, false, check_flag != 0, st);
+  return launch_gemm(half, ws, 7 * plan.N, plan.moduli, 7, kblock, 1, 0, OZ2_KRANGE_ALL, false, check_flag != 0, st);
 }
 
 // One plain INT8 product with INT32 output and no modular reduction between k-blocks: the caller guarantees
 // k_pad * 64 * 64 < 2^31.
 hipError_t oz2_launch_bound_gemm(const Oz2Layout& lay, char* ws, bool symmetric, hipStream_t st) {
   const int one = 1;
-  return launch_gemm(lay, ws, 1, &one, lay.k_pad, 0, 0, OZ2_KRANGE_ALL, symmetric, false, st);
+  return launch_gemm(lay, ws, 1, &one, 1, lay.k_pad, 0, 0, OZ2_KRANGE_ALL, symmetric, false, st);
 }
