@@ -171,10 +171,9 @@ int oz2_build_plan(int N, int64_t k, Oz2Plan* plan) {
   cv.two_level = plan->kappa > 75;
   for (int t = 0; t < N; ++t) {
     int p = plan->moduli[t];
-    cv.p[t] = (double)p;
-    cv.inv_p[t] = 1.0 / (double)p;
-    cv.c32[t] = (double)pow2_sym(32, p);
-    cv.c64[t] = (double)pow2_sym(64, p);
+    const int c32 = pow2_sym(32, p), c64 = pow2_sym(64, p);
+    const auto halves = [](int v) { return ((unsigned)v & 0xffffu) * 0x10001u; };
+    cv.mod[t] = {1.0 / (double)p, (double)c32, (double)c64, halves(c32), halves(c64), halves(-p), (unsigned)p};
   }
 
   Oz2CrtConsts& cc = plan->crt;

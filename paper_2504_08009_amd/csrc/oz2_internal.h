@@ -20,13 +20,17 @@
 #define OZ2_TILE_K 64
 
 // Constants of the conversion kernels (Algorithm 1 lines 2-5), passed by value as a kernel argument.
+struct Oz2ConvMod {
+  double inv_p;              // RN(1/p)
+  double c32, c64;           // 2^32 and 2^64 reduced to the symmetric range modulo p
+  unsigned c32_h, c64_h;     // the same modulo 2^16, in both halves of a word
+  unsigned neg_p_h;          // -p likewise
+  unsigned p;
+};
 struct Oz2ConvConsts {
   int N;
   int two_level;             // 1 when kappa is too large for the one-level 2^32 split
-  double p[OZ2_MAX_N];       // moduli as doubles
-  double inv_p[OZ2_MAX_N];   // RN(1/p)
-  double c32[OZ2_MAX_N];     // 2^32 reduced to the symmetric range modulo p
-  double c64[OZ2_MAX_N];     // 2^64 likewise
+  Oz2ConvMod mod[OZ2_MAX_N];
 };
 
 // Constants of the CRT kernel (Algorithm 1 lines 7-10).

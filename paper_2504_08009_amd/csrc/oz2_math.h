@@ -41,13 +41,74 @@ OZ2_HD Oz2Split oz2_scale_trunc_split(double a, int shift) {
   return s;
 }
 
+// Two elements side by side.  The quotient q = rint(y/p) is read off the low bits of y/p + 1.5 * 2^52, and the residue
+// y - q p, of which only the last 16 bits matter (it lies in [-128, 128]), is formed from the last 16 bits of x0, x1,
+// x2 and q, both elements in one register.  Per element and modulus two FP64 instructions and 1.5 others (the rounding,
+// the FP64 remainder and its conversion to an integer took five and more to pack the byte: 33 cycles against 18).
+typedef unsigned short oz2_u16x2 __attribute__((ext_vector_type(2)));
+#define OZ2_ROUND 0x1.8p52  // added to |v| < 2^51, its sum with v ends in the bits of the integer nearest to v
+
+OZ2_HD unsigned oz2_low_word(double v) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return (unsigned)__double2loint(v);
+#else
+  return (unsigned)__builtin_bit_cast(unsigned long long, v);
+#endif
+}
+OZ2_HD unsigned oz2_low_halves(unsigned hi, unsigned lo) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+#else
+  return (lo & 0xffffu) | (hi << 16);
+#endif
+}
+// byte 0 and byte 2 of two words -> one word
+OZ2_HD unsigned oz2_even_bytes(unsigned hi, unsigned lo) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_perm(hi, lo, 0x06040200u);
+#else
+  return (lo & 0xffu) | ((lo >> 8) & 0xff00u) | ((hi & 0xffu) << 16) | ((hi << 8) & 0xff000000u);
+#endif
+}
+OZ2_HD oz2_u16x2 oz2_halves(double a, double b) {  // last 16 bits of two integer-valued doubles below 2^51
+  return __builtin_bit_cast(oz2_u16x2, oz2_low_halves(oz2_low_word(b + OZ2_ROUND), oz2_low_word(a + OZ2_ROUND)));
+}
+
 template <bool TWO_LEVEL>
-OZ2_HD int oz2_sym_residue(const Oz2Split& s, double p, double inv_p, double c32, double c64) {
-  double y = fma(s.x1, c32, s.x0);
-  if (TWO_LEVEL) y = fma(s.x2, c64, y);
-  double q = rint(y * inv_p);
-  double r = fma(-q, p, y);
-  return (int)r;
+struct Oz2SplitPair {
+  Oz2Split a, b;
+  oz2_u16x2 x0, x1, x2;
+};
+template <bool TWO_LEVEL>
+OZ2_HD Oz2SplitPair<TWO_LEVEL> oz2_split_pair(double a, double b, int shift) {
+  Oz2SplitPair<TWO_LEVEL> s;
+  s.a = oz2_scale_trunc_split<TWO_LEVEL>(a, shift);
+  s.b = oz2_scale_trunc_split<TWO_LEVEL>(b, shift);
+  s.x0 = oz2_halves(s.a.x0, s.b.x0);
+  s.x1 = oz2_halves(s.a.x1, s.b.x1);
+  s.x2 = TWO_LEVEL ? oz2_halves(s.a.x2, s.b.x2) : oz2_u16x2{0, 0};
+  return s;
+}
+
+template <bool TWO_LEVEL>
+OZ2_HD double oz2_rounded_quotient(const Oz2Split& s, const Oz2ConvMod& m) {
+  double y = fma(s.x1, m.c32, s.x0);
+  if (TWO_LEVEL) y = fma(s.x2, m.c64, y);
+  return fma(y, m.inv_p, OZ2_ROUND);
+}
+
+// symmetric residues of both elements as 16-bit integers
+template <bool TWO_LEVEL>
+OZ2_HD oz2_u16x2 oz2_residue_pair(const Oz2SplitPair<TWO_LEVEL>& s, const Oz2ConvMod& m) {
+  const oz2_u16x2 q =
+      __builtin_bit_cast(oz2_u16x2, oz2_low_halves(oz2_low_word(oz2_rounded_quotient<TWO_LEVEL>(s.b, m)),
+                                                   oz2_low_word(oz2_rounded_quotient<TWO_LEVEL>(s.a, m))));
+  oz2_u16x2 r = s.x1 * __builtin_bit_cast(oz2_u16x2, m.c32_h) + s.x0;
+  if (TWO_LEVEL) r = s.x2 * __builtin_bit_cast(oz2_u16x2, m.c64_h) + r;
+  return q * __builtin_bit_cast(oz2_u16x2, m.neg_p_h) + r;
+}
+OZ2_HD unsigned oz2_pack_pairs(oz2_u16x2 lo, oz2_u16x2 hi) {  // low bytes of four 16-bit values
+  return oz2_even_bytes(__builtin_bit_cast(unsigned, hi), __builtin_bit_cast(unsigned, lo));
 }
 
 // ---------------------------------------------------------------------------------------------------

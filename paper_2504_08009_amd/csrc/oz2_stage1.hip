@@ -457,21 +457,18 @@ __device__ __forceinline__ void convert_strided(const double* __restrict__ A, in
     return;
   }
   constexpr bool TWO_LEVEL = KIND == 1;
-  Oz2Split xs[16];
+  Oz2SplitPair<TWO_LEVEL> xs[8];
 #pragma unroll
-  for (int u = 0; u < 16; ++u) xs[u] = oz2_scale_trunc_split<TWO_LEVEL>(mine[u], shift);
+  for (int u = 0; u < 8; ++u) xs[u] = oz2_split_pair<TWO_LEVEL>(mine[2 * u], mine[2 * u + 1], shift);
   for (int t = 0; t < cc.N; ++t) {
-    const double p = cc.p[t], ip = cc.inv_p[t], c32 = cc.c32[t], c64 = cc.c64[t];
-    int r[16];
+    const Oz2ConvMod mod = cc.mod[t];
+    unsigned v[4];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) r[u] = oz2_sym_residue<TWO_LEVEL>(xs[u], p, ip, c32, c64);
-    uint4 v;
-    v.x = pack4(r[0], r[1], r[2], r[3]);
-    v.y = pack4(r[4], r[5], r[6], r[7]);
-    v.z = pack4(r[8], r[9], r[10], r[11]);
-    v.w = pack4(r[12], r[13], r[14], r[15]);
+    for (int u = 0; u < 4; ++u)
+      v[u] = oz2_pack_pairs(oz2_residue_pair<TWO_LEVEL>(xs[2 * u], mod),
+                            oz2_residue_pair<TWO_LEVEL>(xs[2 * u + 1], mod));
     // written once, read by a later kernel: non-temporal store
-    __builtin_nontemporal_store(v4u{v.x, v.y, v.z, v.w}, reinterpret_cast<v4u*>(dst + (size_t)t * plane_stride));
+    __builtin_nontemporal_store(v4u{v[0], v[1], v[2], v[3]}, reinterpret_cast<v4u*>(dst + (size_t)t * plane_stride));
   }
 }
 
@@ -516,21 +513,18 @@ __device__ __forceinline__ void convert_contig(const double* __restrict__ B, int
     return;
   }
   constexpr bool TWO_LEVEL = KIND == 1;
-  Oz2Split xs[16];
+  Oz2SplitPair<TWO_LEVEL> xs[8];
 #pragma unroll
-  for (int u = 0; u < 16; ++u) xs[u] = oz2_scale_trunc_split<TWO_LEVEL>(mine[u], shift);
+  for (int u = 0; u < 8; ++u) xs[u] = oz2_split_pair<TWO_LEVEL>(mine[2 * u], mine[2 * u + 1], shift);
   for (int t = 0; t < cc.N; ++t) {
-    const double p = cc.p[t], ip = cc.inv_p[t], c32 = cc.c32[t], c64 = cc.c64[t];
-    int r[16];
+    const Oz2ConvMod mod = cc.mod[t];
+    unsigned v[4];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) r[u] = oz2_sym_residue<TWO_LEVEL>(xs[u], p, ip, c32, c64);
-    uint4 v;
-    v.x = pack4(r[0], r[1], r[2], r[3]);
-    v.y = pack4(r[4], r[5], r[6], r[7]);
-    v.z = pack4(r[8], r[9], r[10], r[11]);
-    v.w = pack4(r[12], r[13], r[14], r[15]);
+    for (int u = 0; u < 4; ++u)
+      v[u] = oz2_pack_pairs(oz2_residue_pair<TWO_LEVEL>(xs[2 * u], mod),
+                            oz2_residue_pair<TWO_LEVEL>(xs[2 * u + 1], mod));
     // written once, read by a later kernel: non-temporal store
-    __builtin_nontemporal_store(v4u{v.x, v.y, v.z, v.w}, reinterpret_cast<v4u*>(dst + (size_t)t * plane_stride));
+    __builtin_nontemporal_store(v4u{v[0], v[1], v[2], v[3]}, reinterpret_cast<v4u*>(dst + (size_t)t * plane_stride));
   }
 }
 
@@ -764,12 +758,17 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
   return hipGetLastError();
 }
 
-void oz2_host_residues_impl(const Oz2ConvConsts& c, double a, int shift, int8_t* out) {
-  if (c.two_level) {
-    Oz2Split s = oz2_scale_trunc_split<true>(a, shift);
-    for (int t = 0; t < c.N; ++t) out[t] = (int8_t)(oz2_sym_residue<true>(s, c.p[t], c.inv_p[t], c.c32[t], c.c64[t]) & 0xff);
-  } else {
-    Oz2Split s = oz2_scale_trunc_split<false>(a, shift);
-    for (int t = 0; t < c.N; ++t) out[t] = (int8_t)(oz2_sym_residue<false>(s, c.p[t], c.inv_p[t], c.c32[t], c.c64[t]) & 0xff);
+template <bool TWO_LEVEL>
+static void host_residues(const Oz2ConvConsts& c, double a, int shift, int8_t* out) {
+  const Oz2SplitPair<TWO_LEVEL> s = oz2_split_pair<TWO_LEVEL>(a, a, shift);
+  for (int t = 0; t < c.N; ++t) {
+    const oz2_u16x2 r = oz2_residue_pair<TWO_LEVEL>(s, c.mod[t]);
+    out[t] = (int8_t)(oz2_pack_pairs(r, r) & 0xff);
   }
+}
+void oz2_host_residues_impl(const Oz2ConvConsts& c, double a, int shift, int8_t* out) {
+  if (c.two_level)
+    host_residues<true>(c, a, shift, out);
+  else
+    host_residues<false>(c, a, shift, out);
 }

@@ -105,7 +105,7 @@ __device__ __forceinline__ void strassen_convert(const StrassenJob& j, const Oz2
   constexpr bool TWO_LEVEL = KIND == 1;
   const int vv = threadIdx.x >> 4, g = threadIdx.x & 15;
   const int64_t rq = r0 + vv;
-  Oz2Split xs[2][2][4];
+  Oz2SplitPair<TWO_LEVEL> xs[2][2][2];
 #pragma unroll
   for (int a = 0; a < 2; ++a) {
     const int64_t v = rq + a * j.vh;
@@ -114,7 +114,7 @@ __device__ __forceinline__ void strassen_convert(const StrassenJob& j, const Oz2
     for (int b = 0; b < 2; ++b) {
       const double* mine = tile + ((2 * a + b) * kVecs + vv) * kPitch + 4 * g;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) xs[a][b][u] = oz2_scale_trunc_split<TWO_LEVEL>(mine[u], shift);
+      for (int h = 0; h < 2; ++h) xs[a][b][h] = oz2_split_pair<TWO_LEVEL>(mine[2 * h], mine[2 * h + 1], shift);
     }
   }
   const size_t plane_stride = (size_t)j.vh * j.kh;
@@ -125,8 +125,8 @@ __device__ __forceinline__ void strassen_convert(const StrassenJob& j, const Oz2
   int8_t* plane = j.planes;
   const int side = j.side;
   for (int t = 0; t < cc.N; ++t) {
-    const double p = cc.p[t], ip = cc.inv_p[t], c32 = cc.c32[t], c64 = cc.c64[t];
-    const unsigned short ps = (unsigned short)(int)p;
+    const Oz2ConvMod mod = cc.mod[t];
+    const unsigned short ps = (unsigned short)mod.p;
     const u16x2 P = {ps, ps};
     // residues in [0, p) as pairs: x[a][b][h] = inner positions 2h, 2h + 1 of block (a, b)
     u16x2 x[2][2][2];
@@ -136,9 +136,7 @@ __device__ __forceinline__ void strassen_convert(const StrassenJob& j, const Oz2
       for (int b = 0; b < 2; ++b)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const int re = oz2_sym_residue<TWO_LEVEL>(xs[a][b][2 * h], p, ip, c32, c64);
-          const int ro = oz2_sym_residue<TWO_LEVEL>(xs[a][b][2 * h + 1], p, ip, c32, c64);
-          const u16x2 s = as_pair(((unsigned)re & 0xffffu) | ((unsigned)ro << 16));  // symmetric, wrapped when negative
+          const u16x2 s = oz2_residue_pair<TWO_LEVEL>(xs[a][b][h], mod);  // symmetric, wrapped when negative
           x[a][b][h] = __builtin_elementwise_min(s, (u16x2)(s + P));
         }
     u16x2 c[7][2];
@@ -165,7 +163,7 @@ __device__ __forceinline__ void strassen_convert(const StrassenJob& j, const Oz2
         c[6][h] = add_mod(x01, x11, P);
       }
     }
-    const unsigned short adj = (unsigned short)(256 - (int)p);
+    const unsigned short adj = (unsigned short)(256 - mod.p);
     const u16x2 ADJ = {adj, adj};
 #pragma unroll
     for (int s = 0; s < 7; ++s) {
