@@ -55,7 +55,7 @@ std::mutex g_setup_mu;
 bool g_setup_done = false;
 bool ensure_setup() {
   std::lock_guard<std::mutex> lock(g_setup_mu);
-  if (!g_setup_done) g_setup_done = oz2_gemm_setup() == hipSuccess;
+  if (!g_setup_done) g_setup_done = oz2_gemm_setup() == hipSuccess && oz2_stage1_setup() == hipSuccess;
   return g_setup_done;
 }
 
@@ -336,7 +336,7 @@ int oz2_stage1_convert(int64_t m, int64_t n, int64_t k, const double* A, int64_t
   int rc = prepare(s, m, n, k, num_moduli, &plan, &lay);
   if (rc) return rc;
   hipError_t e = oz2_launch_stage1(0, 0, m, n, k, A, lda, B, ldb, 0, 0, *plan, s.shift_mode, s.bit_split, 0, lay, s.ws,
-                                   static_cast<hipStream_t>(stream));
+                                   static_cast<hipStream_t>(stream), nullptr);
   return e == hipSuccess ? OZ2_OK : OZ2_ERR_HIP;
 }
 
@@ -356,7 +356,8 @@ int oz2_stage2_gemm(int64_t m, int64_t n, int64_t k, int num_moduli, void* strea
   // the counters of the round synchronisation must be zero at launch; in oz2_dgemm stage 1 has cleared them
   hipError_t e = oz2_launch_clear_sync(lay, s.ws, static_cast<hipStream_t>(stream));
   if (e == hipSuccess)
-    e = oz2_launch_stage2(*plan, lay, s.ws, s.kblock, s.product_format, 0, OZ2_KRANGE_ALL, 0, static_cast<hipStream_t>(stream));
+    e = oz2_launch_stage2(*plan, lay, s.ws, s.kblock, s.product_format, 0, OZ2_KRANGE_ALL, 0, Oz2ScanFinish{nullptr, 0u, nullptr},
+                          static_cast<hipStream_t>(stream));
   return e == hipSuccess ? OZ2_OK : OZ2_ERR_HIP;
 }
 
@@ -432,9 +433,10 @@ int dgemm_ex_impl(bool static_ws, char transa, char transb, int64_t m, int64_t n
   if (rc) return rc;
   char* const ws = w.p;
   auto mark = [&](int i) { return !s.ev_on || hipEventRecord(s.ev[i], st) == hipSuccess; };
+  Oz2ScanFinish fin;
   if (!mark(0)) return OZ2_ERR_HIP;
   if (oz2_launch_stage1(ta, tb, m, n, k, A, lda, B, ldb, 0, 0, *plan, s.shift_mode, s.bit_split, strassen ? 1 : 0, lay, ws,
-                        st) != hipSuccess ||
+                        st, &fin) != hipSuccess ||
       !mark(1))
     return OZ2_ERR_HIP;
   if (strassen) {
@@ -443,7 +445,7 @@ int dgemm_ex_impl(bool static_ws, char transa, char transb, int64_t m, int64_t n
     if (oz2_launch_strassen_crt(m, n, alpha, beta, C, ldc, *plan, lay, ws, s.nonfinite_check, st) != hipSuccess || !mark(3))
       return OZ2_ERR_HIP;
   } else {
-    if (oz2_launch_stage2(*plan, lay, ws, s.kblock, s.product_format, 0, OZ2_KRANGE_ALL, s.nonfinite_check, st) !=
+    if (oz2_launch_stage2(*plan, lay, ws, s.kblock, s.product_format, 0, OZ2_KRANGE_ALL, s.nonfinite_check, fin, st) !=
             hipSuccess ||
         !mark(2))
       return OZ2_ERR_HIP;
@@ -519,13 +521,14 @@ int oz2_dsyrk(char uplo, char trans, int64_t n, int64_t k, double alpha, const d
   int rc = prepare(s, n, n, k, num_moduli, &plan, &lay);
   if (rc) return rc;
   auto mark = [&](int i) { return !s.ev_on || hipEventRecord(s.ev[i], st) == hipSuccess; };
+  Oz2ScanFinish fin;
   if (!mark(0)) return OZ2_ERR_HIP;
   // op(A) op(A)^T: the columns of the second operand are the rows of the first, so A is converted once and
   // its planes serve as both operands
-  if (oz2_launch_stage1(ta, 0, n, n, k, A, lda, nullptr, 0, 0, 0, *plan, s.shift_mode, 0, 0, lay, s.ws, st) != hipSuccess ||
+  if (oz2_launch_stage1(ta, 0, n, n, k, A, lda, nullptr, 0, 0, 0, *plan, s.shift_mode, 0, 0, lay, s.ws, st, &fin) != hipSuccess ||
       !mark(1))
     return OZ2_ERR_HIP;
-  if (oz2_launch_stage2(*plan, lay, s.ws, s.kblock, s.product_format, tri, OZ2_KRANGE_ALL, s.nonfinite_check, st) != hipSuccess ||
+  if (oz2_launch_stage2(*plan, lay, s.ws, s.kblock, s.product_format, tri, OZ2_KRANGE_ALL, s.nonfinite_check, fin, st) != hipSuccess ||
       !mark(2))
     return OZ2_ERR_HIP;
   if (oz2_launch_stage3(n, n, alpha, beta, C, ldc, *plan, lay, s.ws, s.product_format, s.nonfinite_check, tri, st) !=
@@ -579,11 +582,12 @@ int oz2_dtrmm(char side, char uplo, char transa, char diag, int64_t m, int64_t n
   const int krange = left ? (op_lower ? OZ2_KRANGE_UPTO_ROW : OZ2_KRANGE_FROM_ROW)
                           : (op_lower ? OZ2_KRANGE_FROM_COL : OZ2_KRANGE_UPTO_COL);
   auto mark = [&](int i) { return !s.ev_on || hipEventRecord(s.ev[i], st) == hipSuccess; };
+  Oz2ScanFinish fin;
   if (!mark(0)) return OZ2_ERR_HIP;
-  if (oz2_launch_stage1(tx, ty, m, n, ka, X, ldx, Y, ldy, trix, triy, *plan, s.shift_mode, 0, 0, lay, s.ws, st) != hipSuccess ||
+  if (oz2_launch_stage1(tx, ty, m, n, ka, X, ldx, Y, ldy, trix, triy, *plan, s.shift_mode, 0, 0, lay, s.ws, st, &fin) != hipSuccess ||
       !mark(1))
     return OZ2_ERR_HIP;
-  if (oz2_launch_stage2(*plan, lay, s.ws, s.kblock, s.product_format, 0, krange, s.nonfinite_check, st) != hipSuccess || !mark(2))
+  if (oz2_launch_stage2(*plan, lay, s.ws, s.kblock, s.product_format, 0, krange, s.nonfinite_check, fin, st) != hipSuccess || !mark(2))
     return OZ2_ERR_HIP;
   // B is overwritten: stage 1 has read all of it by now (stream order)
   if (oz2_launch_stage3(m, n, alpha, 0.0, B, ldb, *plan, lay, s.ws, s.product_format, s.nonfinite_check, 0, st) !=

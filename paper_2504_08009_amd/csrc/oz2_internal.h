@@ -96,10 +96,21 @@ void oz2_make_layout(int64_t m, int64_t n, int64_t k, int N, int c_elem_bytes, O
 // 256 and 64), and each plane region holds 7 N planes of a quarter of the padded area.
 void oz2_make_layout_strassen(int64_t m, int64_t n, int64_t k, int N, Oz2Layout* lay);
 
+// Reports of a stage 1 that found its maxima without atomics: one word per workgroup, nonzero where it saw an infinity or
+// a NaN.  A workgroup of the next launch turns them into the 32 flag words (finish_scan).
+struct Oz2ScanFinish {
+  const unsigned long long* slots;  // null: nothing to do
+  unsigned count;
+  unsigned long long* flags;
+};
+
 // Kernel launchers.  Each returns hipSuccess or the launch error.
+// deferred: if not null, stage 1 may leave the flag words to the launch after it, which then gets what it needs here
+// (slots == nullptr: they are complete).
 hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
                              const double* B, int64_t ldb, int tri_a, int tri_b, const Oz2Plan& plan, int shift_mode,
-                             int bit_split, int strassen, const Oz2Layout& lay, char* ws, hipStream_t st);
+                             int bit_split, int strassen, const Oz2Layout& lay, char* ws, hipStream_t st,
+                             Oz2ScanFinish* deferred);
 // Strassen form of line 6 (oz2_strassen.hip, oz2_stage2.hip): operand planes, the 7 N products, CRT pass
 hipError_t oz2_launch_strassen_convert(int transa, int transb, int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
                                        const double* B, int64_t ldb, const Oz2Plan& plan, const int* kinds,
@@ -111,6 +122,8 @@ hipError_t oz2_launch_strassen_crt(int64_t m, int64_t n, double alpha, double be
 // One-time device set-up of the GEMM kernels (function attributes, compute-unit count); also done lazily by the
 // first launch.
 hipError_t oz2_gemm_setup();
+hipError_t oz2_stage1_setup();
+int oz2_gemm_cus();  // compute units, after the set-up
 // Bound of one wait of the GEMM's round synchronisation in polls (0 switches the synchronisation off), and the
 // clearing of its counters for a GEMM that no stage 1 precedes.
 void oz2_gemm_set_sync_spins(int spins);
@@ -128,8 +141,9 @@ hipError_t oz2_launch_clear_sync(const Oz2Layout& lay, char* ws, hipStream_t st)
 // check_flag != 0: return at once on the device when stage 1 found a non-finite input.
 // triangle: 0 = general product; 1 / 2 = symmetric product op(A) op(A)^T (B's planes are A's), only the tiles of
 // the lower / upper triangle are computed
+// fin: what stage 1 left to this launch (see Oz2ScanFinish); the products are then formed whatever the flag will be.
 hipError_t oz2_launch_stage2(const Oz2Plan& plan, const Oz2Layout& lay, char* ws, int64_t kblock, int residue_u8,
-                             int triangle, int krange, int check_flag, hipStream_t st);
+                             int triangle, int krange, int check_flag, const Oz2ScanFinish& fin, hipStream_t st);
 // P = A''B'' of the INT8-product shift mode: bound planes in the slots of residue plane 0 -> INT32 in the slot of
 // product plane 0.  Exact for k_pad * 64 * 64 < 2^31.
 hipError_t oz2_launch_bound_gemm(const Oz2Layout& lay, char* ws, bool symmetric, hipStream_t st);

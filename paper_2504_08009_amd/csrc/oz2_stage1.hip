@@ -15,11 +15,13 @@
 // The maxima of both operands share one launch and so do their conversions (small problems are bound by the
 // number of launches); a block picks its operand and its kernel body by its index.
 #include "oz2_math.h"
+#include "oz2_scan_finish.h"
 
 namespace {
 
 constexpr int kThreads = 256;
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
 
 __global__ void __launch_bounds__(kThreads) fill_u64_kernel(unsigned long long* p, int64_t count) {
   int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
@@ -348,20 +350,6 @@ __global__ void __launch_bounds__(kThreads) vector_scan_kernel(const ScanJob ja,
   if (threadIdx.x == 0) slots[blockIdx.x] = any ? 1ull : 0ull;
 }
 
-// What the first workgroup of the conversion launch does for the launch above: the flag word (1 when any slot
-// is set) and, cleared, the counters of the GEMM's round synchronisation.
-struct ScanFinish {
-  const unsigned long long* slots;  // null: nothing to do (the maxima came from the atomic kernels)
-  unsigned count;
-  unsigned long long* flags;        // 32 words
-};
-__device__ __forceinline__ void finish_scan(const ScanFinish& f) {
-  int bad = 0;
-  for (unsigned i = threadIdx.x; i < f.count; i += kThreads) bad |= f.slots[i] != 0ull;
-  bad = __syncthreads_or(bad);
-  if (threadIdx.x < 32) f.flags[threadIdx.x] = (threadIdx.x == 0 && bad) ? 1ull : 0ull;
-}
-
 __device__ __forceinline__ unsigned pack4(int r0, int r1, int r2, int r3) {
   return (unsigned)(r0 & 0xff) | ((unsigned)(r1 & 0xff) << 8) | ((unsigned)(r2 & 0xff) << 16) | ((unsigned)r3 << 24);
 }
@@ -542,7 +530,7 @@ constexpr int kConvTileDoubles =
     kConvARows * kConvAPitch > kConvBCols * kConvBColPitch ? kConvARows * kConvAPitch : kConvBCols * kConvBColPitch;
 template <int KA, int KB>
 __global__ void __launch_bounds__(kThreads) operand_convert_kernel(const ConvJob ja, const ConvJob jb,
-                                                                   const Oz2ConvConsts cc, const ScanFinish fin) {
+                                                                   const Oz2ConvConsts cc, const Oz2ScanFinish fin) {
   __shared__ __attribute__((aligned(16))) double tile[kConvTileDoubles];
   if (fin.slots != nullptr && blockIdx.x == 0) finish_scan(fin);  // uniform over the workgroup
   if (blockIdx.x < ja.nblk) {
@@ -559,6 +547,123 @@ __global__ void __launch_bounds__(kThreads) operand_convert_kernel(const ConvJob
     else
       convert_contig<KB>(jb.X, jb.ld, jb.k, jb.nvec, jb.nvec_pad, jb.k_pad, jb.shifts, jb.planes, jb.tri, cc, tile, bx, by);
   }
+}
+
+// ---- Short vectors (inner dimension up to 1024): lines 1-5 in ONE pass.  A workgroup holds eight whole vectors in LDS
+// (up to 64 KiB, two workgroups per compute unit), so the operand is read once instead of twice and the maxima, the shifts
+// and the residues of both operands take one launch.  Bound by HBM at large sizes (8 bytes read, N written per
+// element), by the launch and the chain of a thread's elements at small ones.  Whole calls against the two launches (us): 14
+// moduli 256^3 32.3 -> 24.8, 512^3 36.4 -> 30.1, 1024^3 60.2 -> 53.8, 300 x 3000 x 1000 92 -> 73, 2048 x 2048 x 512
+// 98 -> 92; 16 moduli 4096 x 4096 x 1024 and 18 moduli 8192 x 8192 x 1024 even.
+// Eight vectors of a column-major operand read by rows are 64-byte pieces of its columns: the workgroups of neighbouring
+// groups, which read the other halves of the same cache lines, are placed on the same die.
+constexpr int kShortVecs = 8;
+constexpr int kShortThreads = 512;
+constexpr int kShortK = 1024;
+struct ShortJob {
+  const double* X;
+  int64_t ld, nvec, nvec_pad, k, k_pad;
+  unsigned long long* vmax;
+  int* shifts;
+  int8_t* planes;
+  int param;  // kappa of this operand
+  int tri, strided;
+  unsigned nblk;  // workgroups that have vectors
+  unsigned chunk; // workgroups per die (a multiple of nblk / 8, rounded up)
+};
+template <int KIND>
+__device__ __forceinline__ void convert_short(const ShortJob& j, const Oz2ConvConsts& cc, double* tile, unsigned id,
+                                              unsigned long long* slot) {
+  constexpr int V = kShortVecs;
+  __shared__ unsigned long long part[kShortThreads / 64][V];
+  const int64_t v0 = (int64_t)id * V;
+  const int pitch = (int)j.k_pad + 4;  // doubles per vector: four banks of 32 bytes apart
+  if (j.strided) {
+    const int v = threadIdx.x % V;
+    const bool in = v0 + v < j.nvec;
+    const double* src = j.X + v0 + v;
+#pragma unroll 4
+    for (int l = threadIdx.x / V; l < j.k_pad; l += kShortThreads / V)
+      tile[v * pitch + l] = (in && l < j.k) ? tri_value(src[(int64_t)l * j.ld], v0 + v, l, j.tri) : 0.0;
+  } else {
+    // a wave takes one vector, its lanes run down the vector
+    const int v = threadIdx.x >> 6;
+    static_assert(kShortThreads / 64 == V, "one wave per vector");
+    const bool in = v0 + v < j.nvec;
+    const double* src = j.X + (v0 + v) * j.ld;
+#pragma unroll 4
+    for (int l = threadIdx.x & 63; l < j.k_pad; l += 64)
+      tile[v * pitch + l] = (in && l < j.k) ? tri_value(src[l], l, v0 + v, j.tri) : 0.0;
+  }
+  __syncthreads();
+  // lane: vector lane / 8, inner positions 8 (lane % 8) .. + 7 of a k-tile; wave w takes the k-tiles w, w + 8, ...
+  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, v = lane >> 3;
+  const double* mine = tile + v * pitch + 8 * (lane & 7);
+  const int ktiles = (int)(j.k_pad / kBlkK);
+  unsigned long long mx = 0ull;
+  for (int kt = wv; kt < ktiles; kt += kShortThreads / 64)
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const unsigned long long b = abs_bits(mine[kt * kBlkK + u]);
+      mx = b > mx ? b : mx;
+    }
+#pragma unroll
+  for (int off = 4; off >= 1; off >>= 1) {
+    const unsigned long long o = __shfl_xor(mx, off, 64);
+    mx = o > mx ? o : mx;
+  }
+  if ((lane & 7) == 0) part[wv][v] = mx;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kShortThreads / 64; ++w) mx = part[w][v] > mx ? part[w][v] : mx;
+  const int shift = mx ? j.param - 1 - exponent_of_bits(mx) : 0;
+  if (wv == 0 && (lane & 7) == 0) {
+    j.vmax[v0 + v] = mx;
+    j.shifts[v0 + v] = shift;
+  }
+  const bool bad = mx >= kInfBits;
+  if (wv == 0) {
+    const bool any = __any(bad);
+    if (lane == 0) *slot = any ? 1ull : 0ull;
+  }
+  constexpr bool TWO_LEVEL = KIND == 1;
+  const size_t plane_stride = (size_t)j.nvec_pad * j.k_pad;
+  int8_t* const base = j.planes + (size_t)(v0 / kBlkRows) * kBlkRows * j.k_pad + ((v0 % kBlkRows) + v) * kBlkK + 8 * (lane & 7);
+  for (int kt = wv; kt < ktiles; kt += kShortThreads / 64) {
+    Oz2SplitPair<TWO_LEVEL> xs[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      xs[u] = oz2_split_pair<TWO_LEVEL>(mine[kt * kBlkK + 2 * u], mine[kt * kBlkK + 2 * u + 1], shift);
+    int8_t* dst = base + (size_t)kt * (kBlkRows * kBlkK);
+    for (int t = 0; t < cc.N; ++t) {
+      const Oz2ConvMod mod = cc.mod[t];
+      v2u w;
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        w[h] = oz2_pack_pairs(oz2_residue_pair<TWO_LEVEL>(xs[2 * h], mod), oz2_residue_pair<TWO_LEVEL>(xs[2 * h + 1], mod));
+      __builtin_nontemporal_store(w, reinterpret_cast<v2u*>(dst));
+      dst += plane_stride;
+    }
+  }
+}
+
+template <int KA, int KB>
+__global__ void __launch_bounds__(kShortThreads) short_convert_kernel(const ShortJob ja, const ShortJob jb, const Oz2ConvConsts cc,
+                                                                      unsigned long long* __restrict__ slots) {
+  extern __shared__ __attribute__((aligned(16))) double short_tile[];
+  // workgroup i of a launch runs on die i % 8: consecutive groups of vectors for each die
+  const unsigned x = blockIdx.x & 7u;
+  unsigned y = blockIdx.x >> 3;
+  const bool first = y < ja.chunk;
+  const ShortJob& j = first ? ja : jb;
+  if (!first) y -= ja.chunk;
+  const unsigned id = x * j.chunk + y;
+  if (id >= j.nblk) return;
+  unsigned long long* slot = slots + (first ? id : ja.nblk + id);
+  if (first)
+    convert_short<KA>(ja, cc, short_tile, id, slot);
+  else
+    convert_short<KB>(jb, cc, short_tile, id, slot);
 }
 
 }  // namespace
@@ -612,7 +717,7 @@ void launch_norm(const Operand& o, hipStream_t st) {
 
 // planes of one or two operands in one launch; kind 0 / 1: residue planes with the one- / two-level split,
 // kind 2: the bound plane
-hipError_t launch_convert(const Operand* ops, int nops, const int* kind, const Oz2ConvConsts& conv, const ScanFinish& fin,
+hipError_t launch_convert(const Operand* ops, int nops, const int* kind, const Oz2ConvConsts& conv, const Oz2ScanFinish& fin,
                           hipStream_t st) {
   ConvJob job[2] = {};
   int64_t total = 0;
@@ -645,6 +750,18 @@ hipError_t launch_convert(const Operand* ops, int nops, const int* kind, const O
 
 }  // namespace
 
+// Once per process, before any launch: the dynamic LDS limit of the one-pass conversion.
+hipError_t oz2_stage1_setup() {
+  const void* kernels[4] = {
+      reinterpret_cast<const void*>(short_convert_kernel<0, 0>), reinterpret_cast<const void*>(short_convert_kernel<0, 1>),
+      reinterpret_cast<const void*>(short_convert_kernel<1, 0>), reinterpret_cast<const void*>(short_convert_kernel<1, 1>)};
+  hipError_t e = hipSuccess;
+  for (int i = 0; i < 4 && e == hipSuccess; ++i)
+    e = hipFuncSetAttribute(kernels[i], hipFuncAttributeMaxDynamicSharedMemorySize,
+                            kShortVecs * (kShortK + 4) * (int)sizeof(double));
+  return e;
+}
+
 // transa / transb: 0 = the operand is stored as op(X) (column-major), 1 = it is stored transposed.
 // B == nullptr: the symmetric product op(A) op(A)^T (n == m); only A's vectors, shifts and planes are produced.
 // tri_a / tri_b: triangular structure of the stored arrays (0 = full; see tri_value).
@@ -652,7 +769,8 @@ hipError_t launch_convert(const Operand* ops, int nops, const int* kind, const O
 // formed as usual on its padded extents, only the residue planes differ.
 hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
                              const double* B, int64_t ldb, int tri_a, int tri_b, const Oz2Plan& plan, int shift_mode,
-                             int bit_split, int strassen, const Oz2Layout& lay, char* ws, hipStream_t st) {
+                             int bit_split, int strassen, const Oz2Layout& lay, char* ws, hipStream_t st,
+                             Oz2ScanFinish* deferred) {
   // rows of op(A): strided in a stored m x k matrix, contiguous in a stored k x m matrix;
   // columns of op(B): contiguous in a stored k x n matrix, strided in a stored n x k matrix
   // Row maxima, flag words and column maxima are adjacent, and so are the two auxiliary vectors: one fill
@@ -685,7 +803,40 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
   // the odd bit of the sum (bit_split == 0: the equal split; the symmetric product always uses it).
   const int d = bit_split;
   int xbits[2];  // |x'| < 2^xbits decides how deep the conversion kernels split an element
-  ScanFinish fin = {nullptr, 0u, nullptr};
+  Oz2ScanFinish fin = {nullptr, 0u, nullptr};
+  // Short vectors under the simple bound: everything in one launch, whose reports the caller's GEMM launch turns into
+  // the flag word (deferred != nullptr: the caller sees to that).
+  if (deferred) *deferred = {nullptr, 0u, nullptr};
+  if (deferred && shift_mode == OZ2_SHIFT_MAX && !strassen && lay.k_pad <= kShortK) {
+    const int kappa_a = plan.kappa - d, kappa_b = d == 0 ? plan.kappa : plan.kappa_sum - kappa_a;
+    ShortJob sj[2] = {};
+    int64_t groups = 0;
+    for (int x = 0; x < nops; ++x) {
+      const Operand& o = ops[x];
+      const unsigned nblk = (unsigned)(o.nvec_pad / kShortVecs);
+      sj[x] = {o.X, o.ld, o.nvec, o.nvec_pad, o.k, o.k_pad, o.vmax, o.shifts, o.planes, x == 0 ? kappa_a : kappa_b, o.tri,
+               o.strided ? 1 : 0, nblk, (nblk + 7) / 8};
+      groups += nblk;
+    }
+    // the slots live in the auxiliary vectors, which this shift mode does not use (one word per 8 vectors)
+    unsigned long long* slots = ops[0].vaux;
+    *deferred = {slots, (unsigned)groups, flag};
+    const dim3 grid(8 * (sj[0].chunk + sj[1].chunk)), thr(kShortThreads);
+    const size_t lds = (size_t)kShortVecs * (lay.k_pad + 4) * sizeof(double);
+#define OZ2_SHORT(KA, KB) \
+  hipLaunchKernelGGL((short_convert_kernel<KA, KB>), grid, thr, lds, st, sj[0], sj[1], conv, slots)
+    const bool two_a = kappa_a > 75, two_b = kappa_b > 75;
+    if (two_a && two_b)
+      OZ2_SHORT(1, 1);
+    else if (two_a)
+      OZ2_SHORT(1, 0);
+    else if (two_b)
+      OZ2_SHORT(0, 1);
+    else
+      OZ2_SHORT(0, 0);
+#undef OZ2_SHORT
+    return hipGetLastError();
+  }
   // Small operands under the simple bound: maxima and shifts in one launch without atomics (nothing to clear
   // first); its per-workgroup reports become the flag word in the conversion launch.  "Small": at most 2^25 elements
   // in both operands together (4096 x 4096 twice), where 16 vectors per workgroup are work enough for the chip
@@ -722,7 +873,7 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
     shifts(0, 6, 6, 0, 0);  // exponents 5 - e of the bounds
     {
       const int bound[2] = {2, 2};
-      if (hipError_t e = launch_convert(ops, nops, bound, conv, ScanFinish{nullptr, 0u, nullptr}, st); e != hipSuccess) return e;
+      if (hipError_t e = launch_convert(ops, nops, bound, conv, Oz2ScanFinish{nullptr, 0u, nullptr}, st); e != hipSuccess) return e;
     }
     fill(ops[0].vaux, n_aux);
     hipError_t e = oz2_launch_bound_gemm(lay, ws, B == nullptr, st);

@@ -51,6 +51,7 @@
 #include <type_traits>
 
 #include "oz2_gemm.h"
+#include "oz2_scan_finish.h"
 
 namespace {
 
@@ -86,6 +87,7 @@ struct GemmArgs {
   int triangle;            // 0: all tiles; 1: only tiles with tm >= tn (lower); 2: only tm <= tn (upper)
   int krange;              // triangular operand: which k-tiles of a tile can be nonzero (see OZ2_KRANGE_*)
   const unsigned long long* skip_flag;  // if not null and nonzero on the device: the products are not needed
+  Oz2ScanFinish fin;                    // reports of stage 1 that workgroup 0 turns into the flag word
   unsigned long long* xcd_sync;         // one counter per XCD (zero at launch), or null: no round sync
   int full_rounds;                      // rounds in which every workgroup slot has a tile
   int sync_spins;                       // bound of one wait of the round synchronisation, in polls of the counter
@@ -304,6 +306,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
 
   // stage 1 found an infinity or a NaN: the FP64 fallback forms C, these products would be thrown away
   if (g.skip_flag != nullptr && *g.skip_flag != 0ull) return;
+  if (g.fin.slots != nullptr && blockIdx.x == 0) finish_scan(g.fin);
 
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -650,7 +653,8 @@ hipError_t gemm_setup() {
 // b_is_a: the second operand's planes are the first operand's (symmetric product; m_pad == n_pad)
 // (moduli: one per per_modulus consecutive planes)
 hipError_t launch_gemm(const Oz2Layout& lay, char* ws, int num_moduli, const int* moduli, int per_modulus, int64_t kblock,
-                       int residue_u8, int triangle, int krange, bool b_is_a, bool check_flag, hipStream_t st) {
+                       int residue_u8, int triangle, int krange, bool b_is_a, bool check_flag, const Oz2ScanFinish& fin,
+                       hipStream_t st) {
   hipError_t e = gemm_setup();
   if (e != hipSuccess) return e;
   if (num_moduli < 1 || num_moduli > OZ2_MAX_PLANES) return hipErrorInvalidValue;
@@ -660,7 +664,9 @@ hipError_t launch_gemm(const Oz2Layout& lay, char* ws, int num_moduli, const int
   if (b_is_a && lay.m_pad != lay.n_pad) return hipErrorInvalidValue;
   g.triangle = triangle;
   g.krange = krange;
-  g.skip_flag = check_flag ? reinterpret_cast<const unsigned long long*>(ws + lay.off_flags) : nullptr;
+  // (with reports still to be turned into the flag by this launch, nobody can look at the flag yet)
+  g.skip_flag = check_flag && !fin.slots ? reinterpret_cast<const unsigned long long*>(ws + lay.off_flags) : nullptr;
+  g.fin = fin;
   g.c = reinterpret_cast<int*>(ws + lay.off_c);
   g.m_pad = lay.m_pad;
   g.n_pad = lay.n_pad;
@@ -758,6 +764,10 @@ hipError_t launch_gemm(const Oz2Layout& lay, char* ws, int num_moduli, const int
 
 hipError_t oz2_gemm_setup() { return gemm_setup(); }
 
+int oz2_gemm_cus() { return g_cus; }
+
+static constexpr Oz2ScanFinish kNothing = {nullptr, 0u, nullptr};
+
 void oz2_gemm_set_sync_spins(int spins) { g_sync_spins = spins; }
 
 // The round synchronisation counts on counters that are zero at launch.  Stage 1 clears them with the row
@@ -769,8 +779,9 @@ hipError_t oz2_launch_clear_sync(const Oz2Layout& lay, char* ws, hipStream_t st)
 }
 
 hipError_t oz2_launch_stage2(const Oz2Plan& plan, const Oz2Layout& lay, char* ws, int64_t kblock, int residue_u8,
-                             int triangle, int krange, int check_flag, hipStream_t st) {
-  return launch_gemm(lay, ws, plan.N, plan.moduli, 1, kblock, residue_u8, triangle, krange, triangle != 0, check_flag != 0, st);
+                             int triangle, int krange, int check_flag, const Oz2ScanFinish& fin, hipStream_t st) {
+  return launch_gemm(lay, ws, plan.N, plan.moduli, 1, kblock, residue_u8, triangle, krange, triangle != 0, check_flag != 0, fin,
+                     st);
 }
 
 // The seven products per modulus of the Strassen form: 7 N planes of half the extents of lay, plane 7 t + s
@@ -782,12 +793,12 @@ hipError_t oz2_launch_strassen_gemm(const Oz2Plan& plan, const Oz2Layout& lay, c
   half.n_pad = lay.n_pad / 2;
   half.k_pad = lay.k_pad / 2;
   if (half.m_pad % BM || half.n_pad % BN || half.k_pad % BK) return hipErrorInvalidValue;
-  return launch_gemm(half, ws, 7 * plan.N, plan.moduli, 7, kblock, 1, 0, OZ2_KRANGE_ALL, false, check_flag != 0, st);
+  return launch_gemm(half, ws, 7 * plan.N, plan.moduli, 7, kblock, 1, 0, OZ2_KRANGE_ALL, false, check_flag != 0, kNothing, st);
 }
 
 // One plain INT8 product with INT32 output and no modular reduction between k-blocks: the caller guarantees
 // k_pad * 64 * 64 < 2^31.
 hipError_t oz2_launch_bound_gemm(const Oz2Layout& lay, char* ws, bool symmetric, hipStream_t st) {
   const int one = 1;
-  return launch_gemm(lay, ws, 1, &one, 1, lay.k_pad, 0, 0, OZ2_KRANGE_ALL, symmetric, false, st);
+  return launch_gemm(lay, ws, 1, &one, 1, lay.k_pad, 0, 0, OZ2_KRANGE_ALL, symmetric, false, kNothing, st);
 }

@@ -1,0 +1,115 @@
+"""Small products against the oracle, every bit of C: sizes at the edges of the 64 x 64, 128 x 128 and 256 x 256 tiles of
+the products, inner dimensions at the edges of a k-tile and of the one-pass conversion (1024), both orientations of either
+operand, operands split one and two levels deep, and infinities / NaNs in the last vector of the last workgroup."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import paper_2504_08009_amd as oz
+from oracle import oracle as orc
+
+
+def _dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x.T)).cuda().t()
+
+
+def _gemm(ta, tb, A, B, N, beta=0.0):
+    opA, opB = (A.T if ta == "T" else A), (B.T if tb == "T" else B)
+    m, k = opA.shape
+    n = opB.shape[1]
+    rng = np.random.default_rng(m + n)
+    C0 = np.asfortranarray(rng.standard_normal((m, n)))
+    dA, dB, dC = _dev(A), _dev(B), _dev(C0)
+    ws = oz.Workspace(m, n, k, N)
+    oz.oz2_dgemm_ex(ta, tb, m, n, k, 1.0, dA.data_ptr(), A.shape[0], dB.data_ptr(), B.shape[0], beta, dC.data_ptr(), m, N)
+    torch.cuda.synchronize()
+    flag = int(ws.view(oz.workspace_layout(m, n, k, N)["flags"], 1, torch.int64).item())
+    return dC.cpu().numpy(), orc.dgemm_ex(ta, tb, 1.0, A, B, beta, C0, N), flag
+
+
+def _mat(rng, r, c):
+    return np.asfortranarray((rng.random((r, c)) - 0.5) * np.exp(rng.standard_normal((r, c))))
+
+
+@pytest.mark.parametrize("m,n", [(1, 1), (63, 64), (65, 127), (128, 129), (191, 257), (256, 7), (9, 520), (300, 385), (640, 600)])
+@pytest.mark.parametrize("k", [1, 64, 65, 200, 1024, 1025])
+def test_edges_of_the_tiles_and_of_the_one_pass_conversion(m, n, k):
+    rng = np.random.default_rng(m * 1000 + n + k)
+    ta, tb = [("N", "N"), ("T", "N"), ("N", "T"), ("T", "T")][(m + k) % 4]
+    N = [14, 9, 16, 22][(n + k) % 4]  # 22: elements of more than 75 bits, split two levels deep
+    print("small: m=%d n=%d k=%d N=%d op=%s%s" % (m, n, k, N, ta, tb), flush=True)
+    A = _mat(rng, *((m, k) if ta == "N" else (k, m)))
+    B = _mat(rng, *((k, n) if tb == "N" else (n, k)))
+    got, ref, flag = _gemm(ta, tb, A, B, N, beta=float(k % 2))
+    assert flag == 0 and np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("delta", [30, -30])
+def test_one_operand_split_deeper_than_the_other(delta):
+    """21 moduli and a bit split of 30: one operand needs the two-level split, the other does not."""
+    rng = np.random.default_rng(5)
+    m, n, k, N = 130, 70, 300, 21
+    A, B = _mat(rng, m, k), _mat(rng, k, n)
+    oz.oz2_set_bit_split(delta)
+    try:
+        dA, dB, dC = _dev(A), _dev(B), _dev(np.zeros((m, n), order="F"))
+        ws = oz.Workspace(m, n, k, N)
+        oz.oz2_dgemm(m, n, k, dA.data_ptr(), m, dB.data_ptr(), k, dC.data_ptr(), m, N)
+        torch.cuda.synchronize()
+    finally:
+        oz.oz2_set_bit_split(0)
+    assert np.array_equal(dC.cpu().numpy(), orc.dgemm(A, B, N, delta=delta).C)
+    del ws
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("where", ["first of A", "last of A", "last of B"])
+@pytest.mark.parametrize("m,n,k", [(300, 131, 200), (1400, 1300, 70), (2100, 2000, 64)])
+def test_nonfinite_inputs_reach_the_fallback(m, n, k, where, bad):
+    """The reports of the one-pass conversion become the flag in the launch of the products; the fallback's blocks ride with
+    stage 3 up to 2^22 elements of C and have a launch of their own above."""
+    rng = np.random.default_rng(7)
+    A, B = _mat(rng, m, k), _mat(rng, k, n)
+    if where == "first of A":
+        A[0, 0] = bad
+    elif where == "last of A":
+        A[m - 1, k - 1] = bad
+    else:
+        B[k - 1, n - 1] = bad
+    got, ref, flag = _gemm("N", "N", A, B, 14)
+    assert flag == 1
+    finite = np.isfinite(ref)
+    assert np.array_equal(got[~finite], ref[~finite], equal_nan=True) and np.all(np.isfinite(got[finite]))
+    # finite elements are FP64 sums of k products in both, the oracle's with one rounding per product and sum, the kernel's
+    # with one per fused multiply-add: each within (k + 1) 2^-53 |A||B| of the exact sum
+    A0, B0 = np.where(np.isfinite(A), A, 0.0), np.where(np.isfinite(B), B, 0.0)
+    bound = 2 * (k + 1) * 2.0**-53 * (np.abs(A0) @ np.abs(B0))
+    assert np.all(np.abs(got[finite] - ref[finite]) <= bound[finite])
+    # the next call on the same shape starts from a clear flag
+    A[0, 0] = A[m - 1, k - 1] = B[k - 1, n - 1] = 1.0
+    got, ref, flag = _gemm("N", "N", A, B, 14)
+    assert flag == 0 and np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("uplo", ["L", "U"])
+def test_symmetric_update_with_more_than_2_24_elements(uplo):
+    """The matrix-core kernel of stage 3 skips what lies in the other triangle: rows and columns around its 256 x 16 blocks."""
+    n, k, N = 4200, 64, 6
+    rng = np.random.default_rng(3)
+    A = _mat(rng, n, k)
+    dA = _dev(A)
+    dC = torch.full((n, n), 7.0, dtype=torch.float64, device="cuda")
+    ws = oz.Workspace(n, n, k, N)
+    oz.oz2_dsyrk(uplo, "N", n, k, 1.0, dA.data_ptr(), n, 0.0, dC.data_ptr(), n, N)
+    torch.cuda.synchronize()
+    got = dC.t().cpu().numpy()
+    inside = np.tril(np.ones((n, n), bool)) if uplo == "L" else np.triu(np.ones((n, n), bool))
+    assert np.all(got[~inside] == 7.0)
+    rows = np.concatenate([np.arange(0, 40), np.arange(240, 280), np.arange(2030, 2070), np.arange(4080, 4200)])
+    ref = orc.dgemm(A, np.asfortranarray(A.T), N, rows=rows, cols=np.arange(n)).C
+    mine = inside[rows]
+    assert np.array_equal(got[rows][mine], ref[mine])
+    del ws
