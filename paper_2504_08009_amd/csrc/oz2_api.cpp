@@ -55,7 +55,7 @@ std::mutex g_setup_mu;
 bool g_setup_done = false;
 bool ensure_setup() {
   std::lock_guard<std::mutex> lock(g_setup_mu);
-  if (!g_setup_done) g_setup_done = oz2_gemm_setup() == hipSuccess && oz2_stage1_setup() == hipSuccess;
+  if (!g_setup_done) g_setup_done = oz2_gemm_setup() == hipSuccess && oz2_gemm_tiles_setup() == hipSuccess && oz2_stage1_setup() == hipSuccess;
   return g_setup_done;
 }
 
@@ -356,7 +356,7 @@ int oz2_stage2_gemm(int64_t m, int64_t n, int64_t k, int num_moduli, void* strea
   // the counters of the round synchronisation must be zero at launch; in oz2_dgemm stage 1 has cleared them
   hipError_t e = oz2_launch_clear_sync(lay, s.ws, static_cast<hipStream_t>(stream));
   if (e == hipSuccess)
-    e = oz2_launch_stage2(*plan, lay, s.ws, s.kblock, s.product_format, 0, OZ2_KRANGE_ALL, 0, Oz2ScanFinish{nullptr, 0u, nullptr},
+    e = oz2_launch_products(*plan, lay, s.ws, m, n, s.kblock, s.product_format, 0, OZ2_KRANGE_ALL, 0, Oz2ScanFinish{nullptr, 0u, nullptr},
                           static_cast<hipStream_t>(stream));
   return e == hipSuccess ? OZ2_OK : OZ2_ERR_HIP;
 }
@@ -445,7 +445,7 @@ int dgemm_ex_impl(bool static_ws, char transa, char transb, int64_t m, int64_t n
     if (oz2_launch_strassen_crt(m, n, alpha, beta, C, ldc, *plan, lay, ws, s.nonfinite_check, st) != hipSuccess || !mark(3))
       return OZ2_ERR_HIP;
   } else {
-    if (oz2_launch_stage2(*plan, lay, ws, s.kblock, s.product_format, 0, OZ2_KRANGE_ALL, s.nonfinite_check, fin, st) !=
+    if (oz2_launch_products(*plan, lay, ws, m, n, s.kblock, s.product_format, 0, OZ2_KRANGE_ALL, s.nonfinite_check, fin, st) !=
             hipSuccess ||
         !mark(2))
       return OZ2_ERR_HIP;
@@ -528,7 +528,7 @@ int oz2_dsyrk(char uplo, char trans, int64_t n, int64_t k, double alpha, const d
   if (oz2_launch_stage1(ta, 0, n, n, k, A, lda, nullptr, 0, 0, 0, *plan, s.shift_mode, 0, 0, lay, s.ws, st, &fin) != hipSuccess ||
       !mark(1))
     return OZ2_ERR_HIP;
-  if (oz2_launch_stage2(*plan, lay, s.ws, s.kblock, s.product_format, tri, OZ2_KRANGE_ALL, s.nonfinite_check, fin, st) != hipSuccess ||
+  if (oz2_launch_products(*plan, lay, s.ws, n, n, s.kblock, s.product_format, tri, OZ2_KRANGE_ALL, s.nonfinite_check, fin, st) != hipSuccess ||
       !mark(2))
     return OZ2_ERR_HIP;
   if (oz2_launch_stage3(n, n, alpha, beta, C, ldc, *plan, lay, s.ws, s.product_format, s.nonfinite_check, tri, st) !=
@@ -587,7 +587,7 @@ int oz2_dtrmm(char side, char uplo, char transa, char diag, int64_t m, int64_t n
   if (oz2_launch_stage1(tx, ty, m, n, ka, X, ldx, Y, ldy, trix, triy, *plan, s.shift_mode, 0, 0, lay, s.ws, st, &fin) != hipSuccess ||
       !mark(1))
     return OZ2_ERR_HIP;
-  if (oz2_launch_stage2(*plan, lay, s.ws, s.kblock, s.product_format, 0, krange, s.nonfinite_check, fin, st) != hipSuccess || !mark(2))
+  if (oz2_launch_products(*plan, lay, s.ws, m, n, s.kblock, s.product_format, 0, krange, s.nonfinite_check, fin, st) != hipSuccess || !mark(2))
     return OZ2_ERR_HIP;
   // B is overwritten: stage 1 has read all of it by now (stream order)
   if (oz2_launch_stage3(m, n, alpha, 0.0, B, ldb, *plan, lay, s.ws, s.product_format, s.nonfinite_check, 0, st) !=

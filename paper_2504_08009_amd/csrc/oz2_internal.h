@@ -144,6 +144,12 @@ hipError_t oz2_launch_clear_sync(const Oz2Layout& lay, char* ws, hipStream_t st)
 // fin: what stage 1 left to this launch (see Oz2ScanFinish); the products are then formed whatever the flag will be.
 hipError_t oz2_launch_stage2(const Oz2Plan& plan, const Oz2Layout& lay, char* ws, int64_t kblock, int residue_u8,
                              int triangle, int krange, int check_flag, const Oz2ScanFinish& fin, hipStream_t st);
+// The same for an m x n result with the tiles that fit its size (oz2_stage2_tiles.hip): the large kernel above, or one with
+// small tiles.
+hipError_t oz2_gemm_tiles_setup();
+hipError_t oz2_launch_products(const Oz2Plan& plan, const Oz2Layout& lay, char* ws, int64_t m, int64_t n, int64_t kblock,
+                               int residue_u8, int triangle, int krange, int check_flag, const Oz2ScanFinish& fin,
+                               hipStream_t st);
 // P = A''B'' of the INT8-product shift mode: bound planes in the slots of residue plane 0 -> INT32 in the slot of
 // product plane 0.  Exact for k_pad * 64 * 64 < 2^31.
 hipError_t oz2_launch_bound_gemm(const Oz2Layout& lay, char* ws, bool symmetric, hipStream_t st);

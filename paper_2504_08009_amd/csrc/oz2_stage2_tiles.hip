@@ -1,0 +1,245 @@
+// Stage 2 for small products (Algorithm 1 lines 6-7, UINT8 residues): the same operand planes, MFMA instruction, LDS
+// layout and residue arithmetic as gemm_i8_kernel (oz2_stage2.hip), with tiles of 128 x 128 or 64 x 64 and several
+// workgroups per compute unit in the place of one persistent workgroup with a 256 x 256 tile.
+//
+// A product of a few 256 x 256 tiles per modulus leaves most of the chip idle (14 workgroups for 256 x 256 x 256 with 14
+// moduli) and computes the padding of its last tiles (60 % of the work at 333 x 517); the time is that of one tile from
+// launch to last store.  Smaller tiles cost more L2 -> LDS bytes per operation (twice as many at 128 x 128, four times at
+// 64 x 64) but there is bandwidth to spare at these sizes, and rows and columns beyond the matrices are not touched.
+// Which sizes come here, with both sides' times: tile_size below.
+//
+// One workgroup of four waves (2 x 2) per tile, the k-tiles of 64 bytes in a ring of NS LDS stages filled by direct
+// loads NS - 1 ahead; the other workgroups of the compute unit work while one waits for its first copies or stores its
+// residues.  256 registers per lane or less: the accumulators are ordinary registers (build.py builds this file with
+// -amdgpu-mfma-vgpr-form), so the epilogue reads them directly.
+#include "oz2_gemm.h"
+#include "oz2_scan_finish.h"
+
+namespace {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v16i __attribute__((ext_vector_type(16)));
+
+constexpr int BK = OZ2_TILE_K;
+constexpr int kThreads = 256;
+constexpr int kBlk = OZ2_TILE_M;  // rows of a block of the plane layout
+static_assert(OZ2_TILE_M == 256 && OZ2_TILE_N == 256 && OZ2_TILE_K == 64, "plane layout is 256 x 64 blocks");
+constexpr int kGroup = 8;         // tile rows of a column group
+
+struct TileArgs {
+  const int8_t* a;
+  const int8_t* b;
+  uint8_t* c;
+  int64_t m_pad, n_pad, k_pad;
+  int tiles_m, tiles_n, total, chunk;  // tiles, and tiles per die
+  int ktiles, triangle, krange;        // as in the large kernel
+  const unsigned long long* skip_flag;
+  Oz2ScanFinish fin;
+  FastDiv div_plane, div_group, div_last;
+  Oz2FoldConsts fold[OZ2_MAX_N];
+};
+
+// MI x NI MFMA tiles of 32 x 32 per wave, NS stages, WGS workgroups per compute unit
+template <int MI, int NI, int NS, int WGS>
+__global__ void __launch_bounds__(kThreads, WGS) gemm_i8_tile_kernel(const TileArgs g) {
+  constexpr int TM = 64 * MI, TN = 64 * NI;
+  constexpr int kStage = (TM + TN) * BK;
+  constexpr int kLoadsA = MI, kLoadsB = NI, kLoads = kLoadsA + kLoadsB;  // direct loads of 1 KiB per wave and k-tile
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+
+  if (g.skip_flag != nullptr && *g.skip_flag != 0ull) return;
+  if (g.fin.slots != nullptr && blockIdx.x == 0) finish_scan(g.fin);
+
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wv >> 1, wn = wv & 1;
+
+  // workgroup i of a launch runs on die i % 8: each die takes a contiguous range of tiles, in column groups of kGroup rows
+  const int item = (int)(blockIdx.x & 7) * g.chunk + (int)(blockIdx.x >> 3);
+  if (item >= g.total) return;
+  const int t = item / g.div_plane;
+  const int r = item - t * (g.tiles_m * g.tiles_n);
+  const int gid = r / g.div_group;
+  const int first_m = gid * kGroup, rr = r - gid * (kGroup * g.tiles_n);
+  int tm, tn;
+  if (g.tiles_m - first_m < kGroup) {
+    tn = rr / g.div_last;
+    tm = first_m + rr - tn * (g.tiles_m - first_m);
+  } else {
+    tn = rr / kGroup;
+    tm = first_m + rr % kGroup;
+  }
+  if (g.triangle == 1 && (tm + 1) * TM <= tn * TN) return;
+  if (g.triangle == 2 && (tn + 1) * TN <= tm * TM) return;
+  int kt_begin = 0, kt_end = g.ktiles;
+  if (g.krange == OZ2_KRANGE_UPTO_ROW) kt_end = min(g.ktiles, (tm + 1) * (TM / BK));
+  if (g.krange == OZ2_KRANGE_FROM_ROW) kt_begin = tm * (TM / BK);
+  if (g.krange == OZ2_KRANGE_UPTO_COL) kt_end = min(g.ktiles, (tn + 1) * (TN / BK));
+  if (g.krange == OZ2_KRANGE_FROM_COL) kt_begin = tn * (TN / BK);
+  const int ktiles = kt_end - kt_begin;
+
+  const size_t kp = (size_t)g.k_pad;
+  // first byte this wave copies of the tile's first k-tile: tile row r lies in block r / kBlk, TM / 4 rows per wave
+  const int8_t* pa = g.a + ((size_t)t * g.m_pad + (size_t)(tm * TM / kBlk) * kBlk) * kp + (size_t)(tm * TM % kBlk) * BK +
+                     (size_t)kt_begin * (kBlk * BK) + wv * (TM / 4) * BK;
+  const int8_t* pb = g.b + ((size_t)t * g.n_pad + (size_t)(tn * TN / kBlk) * kBlk) * kp + (size_t)(tn * TN % kBlk) * BK +
+                     (size_t)kt_begin * (kBlk * BK) + wv * (TN / 4) * BK;
+  const unsigned voff = (unsigned)((lane >> 2) * BK) + (((lane & 3) ^ (lane >> 4)) << 4);
+  const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)lds;
+  const unsigned lds_a = __builtin_amdgcn_readfirstlane(lds_base + wv * (TM / 4 * BK));
+  const unsigned lds_b = __builtin_amdgcn_readfirstlane(lds_base + TM * BK + wv * (TN / 4 * BK));
+  auto load = [&](int kt, int st) {
+    const size_t off = (size_t)kt * (kBlk * BK);
+#pragma unroll
+    for (int q = 0; q < kLoadsA; ++q) load_to_lds_16(pa + off + q * 1024, voff, lds_a + st * kStage + q * 1024);
+#pragma unroll
+    for (int q = 0; q < kLoadsB; ++q) load_to_lds_16(pb + off + q * 1024, voff, lds_b + st * kStage + q * 1024);
+  };
+  const int swz = (lane >> 2) & 3, half = lane >> 5;
+  const int a_off = (wm * (TM / 2) + (lane & 31)) * BK, b_off = TM * BK + (wn * (TN / 2) + (lane & 31)) * BK;
+  const int off_s[2] = {((0 + half) ^ swz) << 4, ((2 + half) ^ swz) << 4};
+
+  v16i acc[MI][NI];
+#pragma unroll
+  for (int x = 0; x < MI; ++x)
+#pragma unroll
+    for (int y = 0; y < NI; ++y)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[x][y][e] = (int)OZ2_ACC_START;
+  // (beyond the last k-tile the first one is fetched again: every wait counts on the same number of copies in flight)
+#pragma unroll
+  for (int p = 0; p < NS - 1; ++p) load(p < ktiles ? p : 0, p);
+  const Oz2FoldConsts fc = in_vector_registers(g.fold[t]);
+  int stage = 0;
+  for (int kt = 0; kt < ktiles; ++kt) {
+    wait_vmcnt<(NS - 2) * kLoads>();
+    __syncthreads();  // k-tile kt is complete, and nobody reads the stage of kt - 1 any more, which is refilled below
+    const char* base = lds + stage * kStage;
+    v4i fa[2][MI], fb[2][NI];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+#pragma unroll
+      for (int x = 0; x < MI; ++x) fa[s][x] = *reinterpret_cast<const v4i*>(base + a_off + x * 32 * BK + off_s[s]);
+#pragma unroll
+      for (int y = 0; y < NI; ++y) fb[s][y] = *reinterpret_cast<const v4i*>(base + b_off + y * 32 * BK + off_s[s]);
+    }
+    load(kt + NS - 1 < ktiles ? kt + NS - 1 : 0, stage == 0 ? NS - 1 : stage - 1);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int y = 0; y < NI; ++y)
+#pragma unroll
+        for (int x = 0; x < MI; ++x)
+          acc[x][y] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[s][x], fb[s][y], acc[x][y], 0, 0, 0);
+    stage = stage + 1 == NS ? 0 : stage + 1;
+  }
+
+  // Algorithm 1 line 7 (see the large kernel): four consecutive registers are four consecutive rows of a column
+  uint8_t* const corner = g.c + ((size_t)t * g.n_pad + (size_t)tn * TN + wn * (TN / 2)) * g.m_pad + (size_t)tm * TM + wm * (TM / 2);
+  const unsigned lane_off = (lane & 31u) * (unsigned)g.m_pad + 16u * (lane >> 5);
+#pragma unroll
+  for (int y = 0; y < NI; ++y) {
+    uint8_t* cj = corner + (size_t)(y * 32) * g.m_pad;
+    v4i o[MI];
+#pragma unroll
+    for (int x = 0; x < MI; ++x) {
+      unsigned s[16], w[4];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) s[e] = __builtin_amdgcn_udot4((unsigned)acc[x][y][e], fc.kpack, fc.base, false);
+#pragma unroll
+      for (int a = 0; a < 4; ++a) w[a] = oz2_fold_residues4(s + 4 * a, fc);
+      const auto s0 = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
+      const auto s1 = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+      o[x] = v4i{(int)s0[0], (int)s0[1], (int)s1[0], (int)s1[1]};
+    }
+#pragma unroll
+    for (int x = 0; x < MI; ++x) *reinterpret_cast<v4i*>(cj + x * 32 + lane_off) = o[x];
+  }
+  wait_vmcnt<0>();  // the copies fetched beyond the last k-tile must have landed before the LDS is given back
+}
+
+template <int MI, int NI, int NS, int WGS>
+constexpr int kTileLds = NS * 64 * (MI + NI) * BK;
+
+template <int MI, int NI, int NS, int WGS>
+hipError_t set_lds() {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_i8_tile_kernel<MI, NI, NS, WGS>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, kTileLds<MI, NI, NS, WGS>);
+}
+
+template <int MI, int NI, int NS, int WGS>
+hipError_t launch(TileArgs& g, int64_t m, int64_t n, int planes, hipStream_t st) {
+  constexpr int TM = 64 * MI, TN = 64 * NI;
+  g.tiles_m = (int)((m + TM - 1) / TM);
+  g.tiles_n = (int)((n + TN - 1) / TN);
+  const int64_t total = (int64_t)g.tiles_m * g.tiles_n * planes;
+  if (total > (int64_t)1 << 30) return hipErrorInvalidValue;
+  g.total = (int)total;
+  g.chunk = (int)((total + 7) / 8);
+  g.div_plane = fast_div((unsigned)(g.tiles_m * g.tiles_n));
+  g.div_group = fast_div((unsigned)(kGroup * g.tiles_n));
+  g.div_last = fast_div((unsigned)(g.tiles_m % kGroup ? g.tiles_m % kGroup : 1));
+  hipLaunchKernelGGL((gemm_i8_tile_kernel<MI, NI, NS, WGS>), dim3((unsigned)g.chunk * 8), dim3(kThreads),
+                     (kTileLds<MI, NI, NS, WGS>), st, g);
+  return hipGetLastError();
+}
+
+#define OZ2_TILE_128 2, 2, 3, 3
+#define OZ2_TILE_64 1, 1, 4, 4
+
+}  // namespace
+
+hipError_t oz2_gemm_tiles_setup() {
+  hipError_t e = set_lds<OZ2_TILE_128>();
+  return e == hipSuccess ? set_lds<OZ2_TILE_64>() : e;
+}
+
+static hipError_t launch_tiles(int tile, const Oz2Plan& plan, const Oz2Layout& lay, char* ws, int64_t m, int64_t n, int triangle,
+                               int krange, bool check_flag, const Oz2ScanFinish& fin, hipStream_t st) {
+  const bool b_is_a = triangle != 0;  // symmetric product
+  if (b_is_a && lay.m_pad != lay.n_pad) return hipErrorInvalidValue;
+  if (lay.m_pad >= ((int64_t)1 << 27)) return hipErrorInvalidValue;  // the epilogue's lane offsets
+  TileArgs g;
+  g.a = reinterpret_cast<const int8_t*>(ws + lay.off_a);
+  g.b = reinterpret_cast<const int8_t*>(ws + (b_is_a ? lay.off_a : lay.off_b));
+  g.c = reinterpret_cast<uint8_t*>(ws + lay.off_c);
+  g.m_pad = lay.m_pad;
+  g.n_pad = lay.n_pad;
+  g.k_pad = lay.k_pad;
+  g.ktiles = (int)(lay.k_pad / BK);
+  g.triangle = triangle;
+  g.krange = krange;
+  g.skip_flag = check_flag && !fin.slots ? reinterpret_cast<const unsigned long long*>(ws + lay.off_flags) : nullptr;
+  g.fin = fin;
+  for (int t = 0; t < plan.N; ++t) g.fold[t] = oz2_fold_consts(plan.moduli[t]);
+  return tile == 64 ? launch<OZ2_TILE_64>(g, m, n, plan.N, st) : launch<OZ2_TILE_128>(g, m, n, plan.N, st);
+}
+
+// Which kernel's tiles: 64 or 128 (this file) or 256 (oz2_stage2.hip).  64 x 64 when every tile gets a compute unit
+// of its own.  Otherwise the smaller of two estimates in nanoseconds, whose coefficients are measured times per tile and
+// compute unit (a k-tile, and the rest): rounds of the chip with 256 x 256 tiles, which compute the padding, against
+// 128 x 128 tiles, of which a compute unit holds three.  Whole calls, 128 against 256 (us): 14 moduli 512^3 24 / 29,
+// 700^3 34 / 37, 1024^3 51 / 49, 1024 x 1024 x 2048 87 / 80, 2048^3 212 / 200, 300 x 3000 x 1000 57 / 67, 16 moduli
+// 96 x 8192 x 8192 700 / 736, 4096 x 4096 x 1024 469 / 441; 64 against 128: 128^3 16.8 / 17.7, 256^3 18.4 / 19.4, 512^3
+// 25.1 / 24.4, 700^3 36 / 34.
+static int tile_size(int64_t m, int64_t n, int64_t k_pad, int num_moduli, int triangle, int krange) {
+  const int64_t cus = oz2_gemm_cus();
+  auto rounds = [&](int64_t tile) {
+    const int64_t tm = (m + tile - 1) / tile, tn = (n + tile - 1) / tile;
+    const int64_t tiles = (triangle ? tm * (tn + 1) / 2 : tm * tn) * num_moduli;
+    return (tiles + cus - 1) / cus;
+  };
+  if (rounds(64) <= 1) return 64;
+  const int64_t ktiles = krange == OZ2_KRANGE_ALL ? k_pad / BK : (k_pad / BK + 1) / 2;
+  return rounds(128) * (270 * ktiles + 600) + 3000 < rounds(256) * (720 * ktiles + 4500) ? 128 : 256;
+}
+
+hipError_t oz2_launch_products(const Oz2Plan& plan, const Oz2Layout& lay, char* ws, int64_t m, int64_t n, int64_t kblock,
+                               int residue_u8, int triangle, int krange, int check_flag, const Oz2ScanFinish& fin,
+                               hipStream_t st) {
+  // (the small tiles take UINT8 residues and one block of the inner dimension only)
+  const bool fits = residue_u8 && kblock >= lay.k_pad && lay.k_pad <= OZ2_ACC_BLOCK;
+  const int tile = fits ? tile_size(m, n, lay.k_pad, plan.N, triangle, krange) : 256;
+  if (tile == 256) return oz2_launch_stage2(plan, lay, ws, kblock, residue_u8, triangle, krange, check_flag, fin, st);
+  return launch_tiles(tile, plan, lay, ws, m, n, triangle, krange, check_flag != 0, fin, st);
+}
