@@ -449,9 +449,11 @@ int dgemm_ex_impl(bool static_ws, char transa, char transb, int64_t m, int64_t n
             hipSuccess ||
         !mark(2))
       return OZ2_ERR_HIP;
-    // up to 2^18 elements of C the blocks of the fallback ride in the launch of stage 3: one launch less where
-    // launches are what the call costs (from 1024 x 1024 on the wider kernel's lower occupancy costs as much)
-    if (s.nonfinite_check && s.product_format == OZ2_PRODUCT_RESIDUE_U8 && m * n <= ((int64_t)1 << 18)) {
+    // below 2^24 elements of C (where the matrix-core kernel takes over) the blocks of the fallback ride in the launch of
+    // stage 3: one launch less (whole calls, us: 2200 x 2200 x 500 103 -> 98, 3000 x 3000 x 1000 224 -> 220, 18 moduli
+    // 3001 x 2777 x 3500 674 -> 667), and with its smaller tiles the fallback itself is the faster one (1024^3 612 -> 277,
+    // 4000^3 7770 -> 5430)
+    if (s.nonfinite_check && s.product_format == OZ2_PRODUCT_RESIDUE_U8 && m * n < ((int64_t)1 << 24)) {
       if (oz2_launch_stage3_or_fallback(ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, *plan, lay, ws, st) !=
               hipSuccess ||
           !mark(3))

@@ -2,23 +2,8 @@
 #ifndef OZ2_GEMM_H
 #define OZ2_GEMM_H
 
+#include "oz2_fast_div.h"
 #include "oz2_internal.h"
-
-// Division of numbers below 2^31 by one that the host knows: with s = 31 + ceil(log2 d) and m = ceil(2^s / d),
-// n m / 2^s exceeds n / d by less than 1 / d.  On the device a scalar multiplication and a shift; the compiler's own
-// division goes through the vector units' FP32 reciprocal, some thirty instructions per quotient that a workgroup
-// would wait for between two tiles.
-struct FastDiv {
-  unsigned m, s;
-};
-inline FastDiv fast_div(unsigned d) {
-  unsigned log = 0;
-  while (((uint64_t)1 << log) < d) ++log;
-  return {(unsigned)((((uint64_t)1 << (31 + log)) + d - 1) / d), 31 + log};
-}
-__device__ __forceinline__ int operator/(int n, const FastDiv& d) {
-  return (int)(((uint64_t)(unsigned)n * d.m) >> d.s);
-}
 
 // 16-byte-per-lane direct load global -> LDS.  The wave writes 1024 contiguous bytes starting at the
 // LDS byte address in M0; lane l's 16 bytes come from base + its own 32-bit byte offset.  Written as

@@ -5,6 +5,7 @@
 // 4N (INT32 planes) or N (UINT8 residue planes, line 7 already taken by the GEMM epilogue) bytes read and 8
 // written per element: bound by HBM traffic with INT32 planes, by FP64 instruction issue with UINT8 planes.
 #include "oz2_fallback_tile.h"
+#include "oz2_fast_div.h"
 #include "oz2_math.h"
 
 namespace {
@@ -13,12 +14,11 @@ constexpr int kThreads = 256;
 static_assert(kThreads == kFallbackThreads, "the small-problem kernel runs both bodies with one block size");
 
 // One plane's values for R consecutive rows: INT32 products (16-byte loads, R = 4) or UINT8 residues that
-// the GEMM epilogue already reduced (8-byte loads, R = 8).
-template <bool U8>
+// the GEMM epilogue already reduced (R bytes: 8, 4 or 2).
+template <bool U8, int R>
 struct PlaneLoad;
 template <>
-struct PlaneLoad<false> {
-  static constexpr int R = 4;
+struct PlaneLoad<false, 4> {
   typedef int Raw __attribute__((ext_vector_type(4)));
   static __device__ __forceinline__ void residues(const Raw& c, double p, double ip, double hip_, double* res) {
     res[0] = oz2_floor_mod(c.x, p, ip, hip_);
@@ -28,8 +28,7 @@ struct PlaneLoad<false> {
   }
 };
 template <>
-struct PlaneLoad<true> {
-  static constexpr int R = 8;
+struct PlaneLoad<true, 8> {
   typedef unsigned Raw __attribute__((ext_vector_type(2)));
   static __device__ __forceinline__ void residues(const Raw& c, double, double, double, double* res) {
 #pragma unroll
@@ -39,18 +38,31 @@ struct PlaneLoad<true> {
     }
   }
 };
+template <>
+struct PlaneLoad<true, 4> {
+  typedef unsigned Raw;
+  static __device__ __forceinline__ void residues(Raw c, double, double, double, double* res) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) res[r] = (double)((c >> (8 * r)) & 0xffu);
+  }
+};
+template <>
+struct PlaneLoad<true, 2> {
+  typedef unsigned short Raw;
+  static __device__ __forceinline__ void residues(Raw c, double, double, double, double* res) {
+    res[0] = (double)(c & 0xffu);
+    res[1] = (double)(c >> 8);
+  }
+};
 
-// One thread: R consecutive rows i of one column j (chunk: which kThreads * R rows of the column the block takes).
-template <int L, bool U8>
+// One thread: the R consecutive rows i0 .. of one column j.
+template <int L, bool U8, int R>
 __device__ __forceinline__ void crt_rows(const void* __restrict__ cplanes, int64_t m_pad, int64_t n_pad,
                                          const int* __restrict__ sa, const int* __restrict__ sb, double* __restrict__ C,
                                          int64_t ldc, int64_t m, int64_t n, const double alpha, const double beta,
-                                         const int triangle, const Oz2CrtConsts& cc, const int64_t j, const int64_t chunk) {
-  typedef PlaneLoad<U8> PL;
+                                         const int triangle, const Oz2CrtConsts& cc, const int64_t j, const int64_t i0) {
+  typedef PlaneLoad<U8, R> PL;
   typedef typename PL::Raw Raw;
-  constexpr int R = PL::R;
-  const int64_t i0 = (chunk * kThreads + threadIdx.x) * R;
-  if (i0 >= m) return;
   // symmetric product: only the lower (1: i >= j) or upper (2: i <= j) triangle of C exists and is written
   if ((triangle == 1 && i0 + R - 1 < j) || (triangle == 2 && i0 > j)) return;
   // element (i, j) of plane t sits at index (t*n_pad + j)*m_pad + i, in units of int32 or of bytes
@@ -128,36 +140,43 @@ __device__ __forceinline__ void crt_rows(const void* __restrict__ cplanes, int64
   }
 }
 
-template <int L, bool U8>
+// The work of a launch is the columns' pieces of R rows, one after the other (per_col of them in a column), so that
+// short and ragged columns leave no lanes idle (a block per 2048 rows of a column before: one lane in eight worked at 256
+// rows, two thirds of them at 2777).
+template <int L, bool U8, int R>
 __global__ void __launch_bounds__(kThreads) crt_kernel(const void* __restrict__ cplanes, int64_t m_pad, int64_t n_pad,
                                                        const int* __restrict__ sa, const int* __restrict__ sb,
                                                        double* __restrict__ C, int64_t ldc, int64_t m, int64_t n,
                                                        const double alpha, const double beta,
                                                        const unsigned long long* __restrict__ skip_flag,
-                                                       const int triangle, const Oz2CrtConsts cc) {
+                                                       const int triangle, const int per_col, const FastDiv by_col,
+                                                       const Oz2CrtConsts cc) {
   // a non-finite input was found in stage 1: C is left to the FP64 fallback (uniform over the grid)
   if (skip_flag != nullptr && *skip_flag != 0ull) return;
-  crt_rows<L, U8>(cplanes, m_pad, n_pad, sa, sb, C, ldc, m, n, alpha, beta, triangle, cc, blockIdx.x, blockIdx.y);
+  const int g = (int)(blockIdx.x * kThreads + threadIdx.x), j = g / by_col;
+  if (j >= n) return;
+  crt_rows<L, U8, R>(cplanes, m_pad, n_pad, sa, sb, C, ldc, m, n, alpha, beta, triangle, cc, j, (int64_t)(g - j * per_col) * R);
 }
 
-// Small problems, where every launch counts: the blocks of the FP64 fallback ride in the same launch.  Rows of
-// blocks below crt_chunks are the kernel above; the rows after them are the fallback's tiles, numbered along x
-// first.  Which of the two sets works is decided by the flag of stage 1, the other returns at once.
-template <int L>
-__global__ void __launch_bounds__(kThreads, 2) crt_or_fallback_kernel(const void* __restrict__ cplanes, int64_t m_pad,
+// Products below 2^24 elements, where every launch counts: the blocks of the FP64 fallback ride in the same launch, behind those of
+// the kernel above.  Which of the two sets works is decided by the flag of stage 1, the other returns at once.
+template <int L, int R>
+__global__ void __launch_bounds__(kThreads, 4) crt_or_fallback_kernel(const void* __restrict__ cplanes, int64_t m_pad,
                                                                    int64_t n_pad, const int* __restrict__ sa,
                                                                    const int* __restrict__ sb,
                                                                    const unsigned long long* __restrict__ flag,
-                                                                   const unsigned crt_chunks, const int64_t tiles,
-                                                                   const Oz2FallbackArgs f, const Oz2CrtConsts cc) {
+                                                                   const unsigned crt_blocks, const int per_col,
+                                                                   const FastDiv by_col, const Oz2FallbackArgs f,
+                                                                   const Oz2CrtConsts cc) {
   const bool nonfinite = *flag != 0ull;
-  if (blockIdx.y < crt_chunks) {
+  if (blockIdx.x < crt_blocks) {
     if (nonfinite) return;
-    crt_rows<L, true>(cplanes, m_pad, n_pad, sa, sb, f.C, f.ldc, f.m, f.n, f.alpha, f.beta, 0, cc, blockIdx.x, blockIdx.y);
-  } else {
-    const int64_t tile = (int64_t)(blockIdx.y - crt_chunks) * gridDim.x + blockIdx.x;
-    if (!nonfinite || tile >= tiles) return;
-    oz2_fallback_tile(f, tile);
+    const int g = (int)(blockIdx.x * kThreads + threadIdx.x), j = g / by_col;
+    if (j >= f.n) return;
+    crt_rows<L, true, R>(cplanes, m_pad, n_pad, sa, sb, f.C, f.ldc, f.m, f.n, f.alpha, f.beta, 0, cc, j,
+                         (int64_t)(g - j * per_col) * R);
+  } else if (nonfinite) {
+    oz2_fallback_tile<kFallbackSmallTile>(f, blockIdx.x - crt_blocks);
   }
 }
 
@@ -197,6 +216,9 @@ __global__ void __launch_bounds__(kThreads) crt_mfma_kernel(const uint8_t* __res
   const int64_t i0 = ((int64_t)blockIdx.y * (kThreads / 64) + wv) * 256 + 4 * lane;  // this thread's four rows
   if (i0 - 4 * lane >= m) return;  // the whole wave (planes are padded to multiples of 256 rows: what it reads exists)
   const int64_t j0 = (int64_t)blockIdx.x * kCrtCols;
+  // symmetric product: nothing to do for a wave whose 256 rows x 16 columns lie in the other triangle (dsyrk of order
+  // 5000 with inner dimension 1024, whole call: 499 -> 430 us)
+  if ((triangle == 1 && i0 - 4 * lane + 255 < j0) || (triangle == 2 && i0 - 4 * lane > j0 + kCrtCols - 1)) return;
   const int N = cc.N;
 
   // first operand: row lane % 32, inner positions 16 (lane / 32) .. + 15; nonzero where the row's block is the half
@@ -315,8 +337,6 @@ hipError_t oz2_launch_stage3(int64_t m, int64_t n, double alpha, double beta, do
   const unsigned long long* skip = check_flag ? reinterpret_cast<const unsigned long long*>(ws + lay.off_flags) : nullptr;
   const int* sa = reinterpret_cast<const int*>(ws + lay.off_sa);
   const int* sb = triangle ? sa : reinterpret_cast<const int*>(ws + lay.off_sb);  // symmetric: columns are A's rows
-  const int64_t per_block = (int64_t)kThreads * (residue_u8 ? PlaneLoad<true>::R : PlaneLoad<false>::R);
-  dim3 grid((unsigned)n, (unsigned)((m + per_block - 1) / per_block));
   // (from 2^24 elements on: below, a thread's 64 elements leave too few threads for the chip and the other kernel wins)
   if (residue_u8 && plan.digits.valid && m * n >= ((int64_t)1 << 24)) {
     // at most 16 moduli: the accumulation of line 9 on the matrix cores
@@ -338,15 +358,20 @@ hipError_t oz2_launch_stage3(int64_t m, int64_t n, double alpha, double beta, do
     }
     return hipGetLastError();
   }
+  const int rows = residue_u8 ? 8 : 4;
+  const int64_t per_col = (m + rows - 1) / rows, threads = per_col * n;
+  if (threads >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+  const FastDiv by_col = fast_div((unsigned)per_col);
+  const dim3 grid((unsigned)((threads + kThreads - 1) / kThreads));
   switch (plan.crt.L) {
-#define OZ2_CASE(LL)                                                                                              \
-  case LL:                                                                                                        \
-    if (residue_u8)                                                                                               \
-      hipLaunchKernelGGL((crt_kernel<LL, true>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa,  \
-                         sb, C, ldc, m, n, alpha, beta, skip, triangle, plan.crt);                                \
-    else                                                                                                          \
-      hipLaunchKernelGGL((crt_kernel<LL, false>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa, \
-                         sb, C, ldc, m, n, alpha, beta, skip, triangle, plan.crt);                                \
+#define OZ2_CASE(LL)                                                                                                    \
+  case LL:                                                                                                              \
+    if (residue_u8)                                                                                                     \
+      hipLaunchKernelGGL((crt_kernel<LL, true, 8>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa, sb, \
+                         C, ldc, m, n, alpha, beta, skip, triangle, (int)per_col, by_col, plan.crt);                    \
+    else                                                                                                                \
+      hipLaunchKernelGGL((crt_kernel<LL, false, 4>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa,    \
+                         sb, C, ldc, m, n, alpha, beta, skip, triangle, (int)per_col, by_col, plan.crt);                \
     break;
     OZ2_CASE(1)
     OZ2_CASE(2)
@@ -368,18 +393,25 @@ hipError_t oz2_launch_stage3_or_fallback(int transa, int transb, int64_t m, int6
   const unsigned long long* flag = reinterpret_cast<const unsigned long long*>(ws + lay.off_flags);
   const int* sa = reinterpret_cast<const int*>(ws + lay.off_sa);
   const int* sb = reinterpret_cast<const int*>(ws + lay.off_sb);
-  const int64_t per_block = (int64_t)kThreads * PlaneLoad<true>::R;
-  const int64_t chunks = (m + per_block - 1) / per_block;
-  const int64_t tiles_m = (m + kFallbackTile - 1) / kFallbackTile, tiles_n = (n + kFallbackTile - 1) / kFallbackTile;
-  const int64_t tiles = tiles_m * tiles_n, tile_rows = (tiles + n - 1) / n;
-  if (chunks + tile_rows > 65535) return hipErrorInvalidValue;
+  // two rows per thread up to 2^18 elements, four above: enough threads for the chip, and a short chain in each
+  const int rows = m * n <= ((int64_t)1 << 18) ? 2 : 4;
+  const int64_t per_col = (m + rows - 1) / rows, threads = per_col * n;
+  constexpr int FT = kFallbackSmallTile;
+  const int64_t tiles_m = (m + FT - 1) / FT, tiles_n = (n + FT - 1) / FT;
+  const int64_t crt_blocks = (threads + kThreads - 1) / kThreads;
+  if (threads >= ((int64_t)1 << 31) || crt_blocks + tiles_m * tiles_n >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+  const FastDiv by_col = fast_div((unsigned)per_col);
   const Oz2FallbackArgs f = {transa, transb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, tiles_m, 0, 0, 0};
-  dim3 grid((unsigned)n, (unsigned)(chunks + tile_rows));
+  const dim3 grid((unsigned)(crt_blocks + tiles_m * tiles_n));
   switch (plan.crt.L) {
-#define OZ2_CASE(LL)                                                                                                 \
-  case LL:                                                                                                           \
-    hipLaunchKernelGGL((crt_or_fallback_kernel<LL>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa, \
-                       sb, flag, (unsigned)chunks, tiles, f, plan.crt);                                              \
+#define OZ2_CASE(LL)                                                                                                     \
+  case LL:                                                                                                               \
+    if (rows == 2)                                                                                                       \
+      hipLaunchKernelGGL((crt_or_fallback_kernel<LL, 2>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa, \
+                         sb, flag, (unsigned)crt_blocks, (int)per_col, by_col, f, plan.crt);                             \
+    else                                                                                                                 \
+      hipLaunchKernelGGL((crt_or_fallback_kernel<LL, 4>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa, \
+                         sb, flag, (unsigned)crt_blocks, (int)per_col, by_col, f, plan.crt);                             \
     break;
     OZ2_CASE(1)
     OZ2_CASE(2)

@@ -70,7 +70,7 @@ def test_one_operand_split_deeper_than_the_other(delta):
 @pytest.mark.parametrize("m,n,k", [(300, 131, 200), (1400, 1300, 70), (2100, 2000, 64)])
 def test_nonfinite_inputs_reach_the_fallback(m, n, k, where, bad):
     """The reports of the one-pass conversion become the flag in the launch of the products; the fallback's blocks ride with
-    stage 3 up to 2^22 elements of C and have a launch of their own above."""
+    stage 3 (below 2^24 elements of C)."""
     rng = np.random.default_rng(7)
     A, B = _mat(rng, m, k), _mat(rng, k, n)
     if where == "first of A":
