@@ -15,12 +15,13 @@ HIP_FLAGS = [
 
 
 # Per-file additions.  The CRT kernels use the matrix cores for a few instructions among vector arithmetic on their
-# results, and the small-tile GEMM needs fewer than 256 registers in all: there the MFMA results belong in ordinary
+# results, and the small-tile and thin GEMMs need fewer than 256 registers in all: there the MFMA results belong in ordinary
 # vector registers (otherwise every result is copied out of the accumulation registers, and the accumulator start copied
 # in, one instruction per register).
 EXTRA_FLAGS = {
     "oz2_stage3.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "oz2_stage2_tiles.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "oz2_thin.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
 
 

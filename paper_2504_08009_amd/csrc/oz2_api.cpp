@@ -336,7 +336,7 @@ int oz2_stage1_convert(int64_t m, int64_t n, int64_t k, const double* A, int64_t
   int rc = prepare(s, m, n, k, num_moduli, &plan, &lay);
   if (rc) return rc;
   hipError_t e = oz2_launch_stage1(0, 0, m, n, k, A, lda, B, ldb, 0, 0, *plan, s.shift_mode, s.bit_split, 0, lay, s.ws,
-                                   static_cast<hipStream_t>(stream), nullptr);
+                                   static_cast<hipStream_t>(stream), 0, nullptr, nullptr);
   return e == hipSuccess ? OZ2_OK : OZ2_ERR_HIP;
 }
 
@@ -434,9 +434,12 @@ int dgemm_ex_impl(bool static_ws, char transa, char transb, int64_t m, int64_t n
   char* const ws = w.p;
   auto mark = [&](int i) { return !s.ev_on || hipEventRecord(s.ev[i], st) == hipSuccess; };
   Oz2ScanFinish fin;
+  const int thin =
+      !strassen && s.product_format == OZ2_PRODUCT_RESIDUE_U8 ? oz2_thin_applies(m, n, *plan, lay, s.kblock) : 0;
+  int two_level = 0;
   if (!mark(0)) return OZ2_ERR_HIP;
   if (oz2_launch_stage1(ta, tb, m, n, k, A, lda, B, ldb, 0, 0, *plan, s.shift_mode, s.bit_split, strassen ? 1 : 0, lay, ws,
-                        st, &fin) != hipSuccess ||
+                        st, thin, &two_level, &fin) != hipSuccess ||
       !mark(1))
     return OZ2_ERR_HIP;
   if (strassen) {
@@ -445,10 +448,12 @@ int dgemm_ex_impl(bool static_ws, char transa, char transb, int64_t m, int64_t n
     if (oz2_launch_strassen_crt(m, n, alpha, beta, C, ldc, *plan, lay, ws, s.nonfinite_check, st) != hipSuccess || !mark(3))
       return OZ2_ERR_HIP;
   } else {
-    if (oz2_launch_products(*plan, lay, ws, m, n, s.kblock, s.product_format, 0, OZ2_KRANGE_ALL, s.nonfinite_check, fin, st) !=
-            hipSuccess ||
-        !mark(2))
-      return OZ2_ERR_HIP;
+    const hipError_t e =
+        thin == 1 ? oz2_launch_thin_products(1, ta == 0, A, lda, m, n, k, two_level, *plan, lay, ws, s.nonfinite_check, st)
+        : thin == 2 ? oz2_launch_thin_products(2, tb != 0, B, ldb, n, m, k, two_level, *plan, lay, ws, s.nonfinite_check, st)
+                    : oz2_launch_products(*plan, lay, ws, m, n, s.kblock, s.product_format, 0, OZ2_KRANGE_ALL,
+                                          s.nonfinite_check, fin, st);
+    if (e != hipSuccess || !mark(2)) return OZ2_ERR_HIP;
     // below 2^24 elements of C (where the matrix-core kernel takes over) the blocks of the fallback ride in the launch of
     // stage 3: one launch less (whole calls, us: 2200 x 2200 x 500 103 -> 98, 3000 x 3000 x 1000 224 -> 220, 18 moduli
     // 3001 x 2777 x 3500 674 -> 667), and with its smaller tiles the fallback itself is the faster one (1024^3 612 -> 277,
@@ -527,7 +532,7 @@ int oz2_dsyrk(char uplo, char trans, int64_t n, int64_t k, double alpha, const d
   if (!mark(0)) return OZ2_ERR_HIP;
   // op(A) op(A)^T: the columns of the second operand are the rows of the first, so A is converted once and
   // its planes serve as both operands
-  if (oz2_launch_stage1(ta, 0, n, n, k, A, lda, nullptr, 0, 0, 0, *plan, s.shift_mode, 0, 0, lay, s.ws, st, &fin) != hipSuccess ||
+  if (oz2_launch_stage1(ta, 0, n, n, k, A, lda, nullptr, 0, 0, 0, *plan, s.shift_mode, 0, 0, lay, s.ws, st, 0, nullptr, &fin) != hipSuccess ||
       !mark(1))
     return OZ2_ERR_HIP;
   if (oz2_launch_products(*plan, lay, s.ws, n, n, s.kblock, s.product_format, tri, OZ2_KRANGE_ALL, s.nonfinite_check, fin, st) != hipSuccess ||
@@ -586,7 +591,7 @@ int oz2_dtrmm(char side, char uplo, char transa, char diag, int64_t m, int64_t n
   auto mark = [&](int i) { return !s.ev_on || hipEventRecord(s.ev[i], st) == hipSuccess; };
   Oz2ScanFinish fin;
   if (!mark(0)) return OZ2_ERR_HIP;
-  if (oz2_launch_stage1(tx, ty, m, n, ka, X, ldx, Y, ldy, trix, triy, *plan, s.shift_mode, 0, 0, lay, s.ws, st, &fin) != hipSuccess ||
+  if (oz2_launch_stage1(tx, ty, m, n, ka, X, ldx, Y, ldy, trix, triy, *plan, s.shift_mode, 0, 0, lay, s.ws, st, 0, nullptr, &fin) != hipSuccess ||
       !mark(1))
     return OZ2_ERR_HIP;
   if (oz2_launch_products(*plan, lay, s.ws, m, n, s.kblock, s.product_format, 0, krange, s.nonfinite_check, fin, st) != hipSuccess || !mark(2))

@@ -105,12 +105,14 @@ struct Oz2ScanFinish {
 };
 
 // Kernel launchers.  Each returns hipSuccess or the launch error.
+// thin: 1 / 2 = only the second / first operand's planes are wanted (oz2_launch_thin_products converts the other one
+// itself); *large_two_level then tells how deep that one's elements are to be split.
 // deferred: if not null, stage 1 may leave the flag words to the launch after it, which then gets what it needs here
 // (slots == nullptr: they are complete).
 hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
                              const double* B, int64_t ldb, int tri_a, int tri_b, const Oz2Plan& plan, int shift_mode,
                              int bit_split, int strassen, const Oz2Layout& lay, char* ws, hipStream_t st,
-                             Oz2ScanFinish* deferred);
+                             int thin, int* large_two_level, Oz2ScanFinish* deferred);
 // Strassen form of line 6 (oz2_strassen.hip, oz2_stage2.hip): operand planes, the 7 N products, CRT pass
 hipError_t oz2_launch_strassen_convert(int transa, int transb, int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
                                        const double* B, int64_t ldb, const Oz2Plan& plan, const int* kinds,
@@ -150,6 +152,12 @@ hipError_t oz2_gemm_tiles_setup();
 hipError_t oz2_launch_products(const Oz2Plan& plan, const Oz2Layout& lay, char* ws, int64_t m, int64_t n, int64_t kblock,
                                int residue_u8, int triangle, int krange, int check_flag, const Oz2ScanFinish& fin,
                                hipStream_t st);
+// Thin general products (oz2_thin.hip): conversion of the large operand and products in one kernel.  oz2_thin_applies: 0 no,
+// 1 the first operand is the large one, 2 the second.
+int oz2_thin_applies(int64_t m, int64_t n, const Oz2Plan& plan, const Oz2Layout& lay, int64_t kblock);
+hipError_t oz2_launch_thin_products(int which, int strided, const double* X, int64_t ld, int64_t nvec, int64_t nthin, int64_t k,
+                                    int two_level, const Oz2Plan& plan, const Oz2Layout& lay, char* ws, int check_flag,
+                                    hipStream_t st);
 // P = A''B'' of the INT8-product shift mode: bound planes in the slots of residue plane 0 -> INT32 in the slot of
 // product plane 0.  Exact for k_pad * 64 * 64 < 2^31.
 hipError_t oz2_launch_bound_gemm(const Oz2Layout& lay, char* ws, bool symmetric, hipStream_t st);

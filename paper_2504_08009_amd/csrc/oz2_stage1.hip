@@ -769,8 +769,8 @@ hipError_t oz2_stage1_setup() {
 // formed as usual on its padded extents, only the residue planes differ.
 hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
                              const double* B, int64_t ldb, int tri_a, int tri_b, const Oz2Plan& plan, int shift_mode,
-                             int bit_split, int strassen, const Oz2Layout& lay, char* ws, hipStream_t st,
-                             Oz2ScanFinish* deferred) {
+                             int bit_split, int strassen, const Oz2Layout& lay, char* ws, hipStream_t st, int thin,
+                             int* large_two_level, Oz2ScanFinish* deferred) {
   // rows of op(A): strided in a stored m x k matrix, contiguous in a stored k x m matrix;
   // columns of op(B): contiguous in a stored k x n matrix, strided in a stored n x k matrix
   // Row maxima, flag words and column maxima are adjacent, and so are the two auxiliary vectors: one fill
@@ -807,7 +807,7 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
   // Short vectors under the simple bound: everything in one launch, whose reports the caller's GEMM launch turns into
   // the flag word (deferred != nullptr: the caller sees to that).
   if (deferred) *deferred = {nullptr, 0u, nullptr};
-  if (deferred && shift_mode == OZ2_SHIFT_MAX && !strassen && lay.k_pad <= kShortK) {
+  if (deferred && !thin && shift_mode == OZ2_SHIFT_MAX && !strassen && lay.k_pad <= kShortK) {
     const int kappa_a = plan.kappa - d, kappa_b = d == 0 ? plan.kappa : plan.kappa_sum - kappa_a;
     ShortJob sj[2] = {};
     int64_t groups = 0;
@@ -904,6 +904,12 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
     // general products only: the planes are the seven block combinations per modulus of the Strassen form
     if (!B || tri_a || tri_b) return hipErrorInvalidValue;
     return oz2_launch_strassen_convert(transa, transb, m, n, k, A, lda, B, ldb, plan, kinds, lay, ws, st);
+  }
+  if (thin) {
+    const int small = thin == 1 ? 1 : 0;
+    *large_two_level = kinds[1 - small];
+    if (hipError_t e = launch_convert(ops + small, 1, kinds + small, conv, fin, st); e != hipSuccess) return e;
+    return hipGetLastError();
   }
   if (hipError_t e = launch_convert(ops, nops, kinds, conv, fin, st); e != hipSuccess) return e;
   return hipGetLastError();

@@ -1,0 +1,254 @@
+// Stage 1b and stage 2 in one kernel for thin products (Algorithm 1 lines 2-7): a large operand against at most 128 vectors
+// of the other one.
+//
+// The residue planes of the large operand are N bytes per element that the conversion writes and the products read once:
+// at 8192 x 96 x 8192 with 16 moduli the 1.1 GB of planes cost two thirds of the call.  Here a workgroup takes 64 vectors
+// of the large operand and a group of up to eight moduli, converts a k-tile of 64 inner positions at a time in registers,
+// passes the residues through LDS (64 rows x 64 bytes per modulus, double buffered) and multiplies them with the planes
+// of the thin operand, which come straight from the L2 in the layout an MFMA operand has: wave w works for modulus w of the
+// group and nobody else needs those bytes.  The large operand is read once per group (the groups of the same 64 vectors
+// run on the same die at the same time and find it in the L2); its planes do not exist.
+// Bound by the conversion's vector instructions (some 50 per element and group of eight moduli: 3700 of the 5200 cycles of
+// a k-tile).
+//
+// 512 threads, eight waves, two per SIMD: 32 NI accumulators per lane (NI = 32-vector tiles of the thin operand), ordinary
+// registers (build.py builds this file with -amdgpu-mfma-vgpr-form).
+#include "oz2_gemm.h"
+#include "oz2_math.h"
+
+namespace {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v16i __attribute__((ext_vector_type(16)));
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
+
+constexpr int kThreads = 512;
+constexpr int kRows = 64;               // vectors of the large operand per workgroup
+constexpr int kGroup = kThreads / 64;   // moduli per group: one per wave
+constexpr int BK = OZ2_TILE_K;
+constexpr int kBlk = OZ2_TILE_M;        // plane layout: blocks of 256 rows x 64 bytes
+constexpr int kTileBytes = kRows * BK;  // one modulus in LDS
+constexpr int kMaxThin = 128;
+
+struct ThinArgs {
+  const double* X;        // large operand: element (v, l) at X[v + l ld] (strided) or X[l + v ld]
+  int64_t ld, nvec, k;
+  const int* shifts;
+  int strided;
+  const int8_t* thin;     // planes of the thin operand
+  int64_t thin_pad, k_pad;
+  uint8_t* c;
+  int64_t m_pad, n_pad;
+  int groups, per_group;  // groups of moduli
+  int total, chunk;       // workgroups, and workgroups per die
+  FastDiv div_groups;
+  const unsigned long long* skip_flag;
+  Oz2ConvConsts conv;
+  Oz2FoldConsts fold[OZ2_MAX_N];
+};
+
+template <int KIND, int NI, bool BIG_A>
+__global__ void __launch_bounds__(kThreads) thin_products_kernel(const ThinArgs g) {
+  constexpr bool TWO_LEVEL = KIND == 1;
+  __shared__ __attribute__((aligned(1024))) char lds[2][kGroup][kTileBytes];
+  if (g.skip_flag != nullptr && *g.skip_flag != 0ull) return;
+  const int item = (int)(blockIdx.x & 7) * g.chunk + (int)(blockIdx.x >> 3);  // workgroup i of a launch runs on die i % 8
+  if (item >= g.total) return;
+  const int rg = item / g.div_groups, group = item - rg * g.groups;
+  const int64_t r0 = (int64_t)rg * kRows;
+  const int t0 = group * g.per_group;
+  const int count = min(g.per_group, g.conv.N - t0);
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+
+  // ---- conversion: this thread's vector and its eight inner positions of a k-tile
+  const int row = g.strided ? lane : 8 * wv + (lane >> 3);
+  const int pos = g.strided ? 8 * wv : 8 * (lane & 7);
+  // (a workgroup's last rows may lie beyond the operand: they repeat its last vector, and nobody reads their results)
+  const int64_t v = r0 + row < g.nvec ? r0 + row : g.nvec - 1;
+  const int shift = g.shifts[v];
+  const double* const src = g.strided ? g.X + v + (int64_t)pos * g.ld : g.X + v * g.ld + pos;
+  const int64_t step = g.strided ? g.ld : 1;
+  const int ktiles = (int)(g.k_pad / BK);
+  auto fetch = [&](int kt, double (&d)[8]) {
+    const double* p = src + (int64_t)kt * BK * step;
+    if ((int64_t)(kt + 1) * BK <= g.k) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) d[u] = p[u * step];
+    } else {  // the last k-tile, or beyond it: zeros where there is nothing to read
+      const int64_t left = g.k - ((int64_t)kt * BK + pos);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) d[u] = u < left ? p[u * step] : 0.0;
+    }
+  };
+  // 16-byte chunks of a row are swizzled as in the GEMM's stages (fragments of 16 rows fall on 16 bank groups)
+  const int put = row * BK + ((((pos >> 4) ^ (row >> 2)) & 3) << 4) + (pos & 8);
+  Oz2ConvMod mods[kGroup];  // in scalar registers throughout (loaded per k-tile, every modulus waited for its constants)
+#pragma unroll
+  for (int tt = 0; tt < kGroup; ++tt) mods[tt] = g.conv.mod[tt < count ? t0 + tt : t0];
+  auto convert = [&](const double (&d)[8], int buf) {
+    Oz2SplitPair<TWO_LEVEL> xs[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) xs[u] = oz2_split_pair<TWO_LEVEL>(d[2 * u], d[2 * u + 1], shift);
+#pragma unroll
+    for (int tt = 0; tt < kGroup; ++tt)
+      if (tt < count) {
+        v2u w;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          w[h] = oz2_pack_pairs(oz2_residue_pair<TWO_LEVEL>(xs[2 * h], mods[tt]),
+                                oz2_residue_pair<TWO_LEVEL>(xs[2 * h + 1], mods[tt]));
+        *reinterpret_cast<v2u*>(&lds[buf][tt][put]) = w;
+      }
+  };
+
+  // ---- products: wave w for modulus t0 + w
+  const bool works = wv < count;
+  const int t = works ? t0 + wv : t0;
+  const int half = lane >> 5, swz = (lane >> 2) & 3;
+  const int8_t* const thin = g.thin + (size_t)t * g.thin_pad * g.k_pad + (lane & 31) * BK + half * 16;
+  v4i ft[2][NI];
+  auto fetch_thin = [&](int kt) {
+    const int8_t* p = thin + (size_t)kt * (kBlk * BK);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int y = 0; y < NI; ++y) ft[s][y] = *reinterpret_cast<const v4i*>(p + y * 32 * BK + s * 32);
+  };
+  v16i acc[2][NI];
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < NI; ++y)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[x][y][e] = (int)OZ2_ACC_START;
+
+  // k-tile kt is multiplied while kt + 1 is converted and kt + 2 is on its way from memory
+  auto iteration = [&](int kt, const double (&now)[8], double (&later)[8]) {
+    const int buf = kt & 1;
+    fetch(kt + 2, later);
+    if (works) {
+      const char* base = lds[buf][wv] + (lane & 31) * BK;
+      v4i fb[2][2];
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+          fb[s][x] = *reinterpret_cast<const v4i*>(base + x * 32 * BK + (((2 * s + half) ^ swz) << 4));
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int y = 0; y < NI; ++y)
+#pragma unroll
+          for (int x = 0; x < 2; ++x)
+            acc[x][y] = BIG_A ? __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[s][x], ft[s][y], acc[x][y], 0, 0, 0)
+                              : __builtin_amdgcn_mfma_i32_32x32x32_i8(ft[s][y], fb[s][x], acc[x][y], 0, 0, 0);
+      fetch_thin(kt + 1 < ktiles ? kt + 1 : kt);
+    }
+    if (kt + 1 < ktiles) convert(now, buf ^ 1);
+    __syncthreads();  // the next k-tile is complete, and nobody reads this one's buffer any more
+  };
+  double d0[8], d1[8];
+  fetch(0, d0);
+  fetch(1, d1);
+  if (works) fetch_thin(0);
+  convert(d0, 0);
+  __syncthreads();
+  for (int kt = 0; kt < ktiles; kt += 2) {
+    iteration(kt, d1, d0);
+    if (kt + 1 < ktiles) iteration(kt + 1, d0, d1);
+  }
+  if (!works) return;
+
+  // ---- residues (Algorithm 1 line 7, see the GEMM's epilogue): a lane holds column lane % 32 of a 32 x 32 tile
+  const Oz2FoldConsts fc = in_vector_registers(g.fold[t]);
+  uint8_t* const plane = g.c + (size_t)t * g.n_pad * g.m_pad + (size_t)(lane & 31) * g.m_pad + 16 * half;
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < NI; ++y) {
+      unsigned s[16], w[4];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) s[e] = __builtin_amdgcn_udot4((unsigned)acc[x][y][e], fc.kpack, fc.base, false);
+#pragma unroll
+      for (int a = 0; a < 4; ++a) w[a] = oz2_fold_residues4(s + 4 * a, fc);
+      const auto s0 = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
+      const auto s1 = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+      const int64_t i = BIG_A ? r0 + x * 32 : y * 32, j = BIG_A ? y * 32 : r0 + x * 32;
+      *reinterpret_cast<v4i*>(plane + j * g.m_pad + i) = v4i{(int)s0[0], (int)s0[1], (int)s1[0], (int)s1[1]};
+    }
+}
+
+}  // namespace
+
+// The smaller of two estimates in nanoseconds, measured times per k-tile of a workgroup (one per compute unit) and per
+// byte that conversion and products move between them otherwise (8 read, N written, N read per element of the large
+// operand, 4.3 TB/s).  Whole calls, with planes against without (us): 16 moduli 8192 x 96 x 8192 680 / 474, 96 x 8192 x 8192
+// 698 / 536, 8192 x 32 x 8192 671 / 436, 16384 x 64 x 2048 374 / 244, 4096 x 64 x 4096 172 / 193; 14 moduli 64 x 15484 x
+// 9445 1391 / 1034; 22 moduli 8192 x 96 x 8192 906 / 864.
+int oz2_thin_applies(int64_t m, int64_t n, const Oz2Plan& plan, const Oz2Layout& lay, int64_t kblock) {
+  const int64_t thin = m < n ? m : n, large = m < n ? n : m;
+  // (up to 1024 the one-pass conversion reads the operand once, which is the better half of this)
+  if (thin > kMaxThin || lay.k_pad <= 1024 || lay.k_pad > OZ2_ACC_BLOCK || kblock < lay.k_pad) return 0;
+  const int64_t groups = (plan.N + kGroup - 1) / kGroup, cus = oz2_gemm_cus();
+  const int64_t rounds = ((large + kRows - 1) / kRows * groups + cus - 1) / cus;
+  const int64_t here = rounds * (lay.k_pad / BK) * 2700, planes = large * lay.k_pad / 10 * (8 + 2 * plan.N) / 430;
+  return here < planes - planes / 10 ? (m < n ? 2 : 1) : 0;
+}
+
+hipError_t oz2_launch_thin_products(int which, int strided, const double* X, int64_t ld, int64_t nvec, int64_t nthin, int64_t k,
+                                    int two_level, const Oz2Plan& plan, const Oz2Layout& lay, char* ws, int check_flag,
+                                    hipStream_t st) {
+  if (nthin > kMaxThin) return hipErrorInvalidValue;
+  const bool big_a = which == 1;
+  ThinArgs g;
+  g.X = X;
+  g.ld = ld;
+  g.nvec = nvec;
+  g.k = k;
+  g.shifts = reinterpret_cast<const int*>(ws + (big_a ? lay.off_sa : lay.off_sb));
+  g.strided = strided;
+  g.thin = reinterpret_cast<const int8_t*>(ws + (big_a ? lay.off_b : lay.off_a));
+  g.thin_pad = big_a ? lay.n_pad : lay.m_pad;
+  g.k_pad = lay.k_pad;
+  g.c = reinterpret_cast<uint8_t*>(ws + lay.off_c);
+  g.m_pad = lay.m_pad;
+  g.n_pad = lay.n_pad;
+  g.groups = (plan.N + kGroup - 1) / kGroup;
+  g.per_group = (plan.N + g.groups - 1) / g.groups;
+  const int64_t total = (nvec + kRows - 1) / kRows * g.groups;
+  if (total > (int64_t)1 << 30) return hipErrorInvalidValue;
+  g.total = (int)total;
+  g.chunk = (int)((total + 7) / 8);
+  g.div_groups = fast_div((unsigned)g.groups);
+  g.skip_flag = check_flag ? reinterpret_cast<const unsigned long long*>(ws + lay.off_flags) : nullptr;
+  g.conv = plan.conv;
+  for (int t = 0; t < plan.N; ++t) g.fold[t] = oz2_fold_consts(plan.moduli[t]);
+  const dim3 grid((unsigned)g.chunk * 8), thr(kThreads);
+  const int ni = (int)((nthin + 31) / 32);
+#define OZ2_THIN(KIND, NI)                                                                   \
+  do {                                                                                       \
+    if (big_a)                                                                               \
+      hipLaunchKernelGGL((thin_products_kernel<KIND, NI, true>), grid, thr, 0, st, g);       \
+    else                                                                                     \
+      hipLaunchKernelGGL((thin_products_kernel<KIND, NI, false>), grid, thr, 0, st, g);      \
+  } while (0)
+#define OZ2_THIN_NI(KIND)                                                                    \
+  do {                                                                                       \
+    if (ni == 1)                                                                             \
+      OZ2_THIN(KIND, 1);                                                                     \
+    else if (ni == 2)                                                                        \
+      OZ2_THIN(KIND, 2);                                                                     \
+    else if (ni == 3)                                                                        \
+      OZ2_THIN(KIND, 3);                                                                     \
+    else                                                                                     \
+      OZ2_THIN(KIND, 4);                                                                     \
+  } while (0)
+  if (two_level)
+    OZ2_THIN_NI(1);
+  else
+    OZ2_THIN_NI(0);
+#undef OZ2_THIN_NI
+#undef OZ2_THIN
+  return hipGetLastError();
+}

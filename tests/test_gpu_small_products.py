@@ -113,3 +113,45 @@ def test_symmetric_update_with_more_than_2_24_elements(uplo):
     mine = inside[rows]
     assert np.array_equal(got[rows][mine], ref[mine])
     del ws
+
+
+@pytest.mark.parametrize("thin", [1, 32, 33, 97, 128])
+@pytest.mark.parametrize("ta,tb,first", [("N", "N", True), ("T", "N", True), ("N", "N", False), ("N", "T", False)])
+def test_thin_products_convert_the_large_operand_on_the_way(thin, ta, tb, first):
+    """A large operand of ragged extents against few vectors of the other one (oz2_thin.hip), either side, either orientation,
+    whole and partial groups of moduli, elements split one and two levels deep."""
+    large, k = 12337, 1101
+    N = {1: 16, 32: 15, 33: 24, 97: 8, 128: 23}[thin]
+    m, n = (large, thin) if first else (thin, large)
+    rng = np.random.default_rng(thin)
+    A = _mat(rng, *((m, k) if ta == "N" else (k, m)))
+    B = _mat(rng, *((k, n) if tb == "N" else (n, k)))
+    print("thin: m=%d n=%d k=%d N=%d op=%s%s" % (m, n, k, N, ta, tb), flush=True)
+    dA, dB = _dev(A), _dev(B)
+    dC = torch.full((n, m), 5.0, dtype=torch.float64, device="cuda")
+    ws = oz.Workspace(m, n, k, N)
+    oz.oz2_dgemm_ex(ta, tb, m, n, k, 1.0, dA.data_ptr(), A.shape[0], dB.data_ptr(), B.shape[0], 0.0, dC.data_ptr(), m, N)
+    torch.cuda.synchronize()
+    got = dC.t().cpu().numpy()
+    opA, opB = np.asfortranarray(A.T if ta == "T" else A), np.asfortranarray(B.T if tb == "T" else B)
+    pick = np.unique(np.concatenate([np.arange(70), np.arange(large - 90, large), rng.integers(0, large, 60)]))
+    rows, cols = (pick, np.arange(n)) if first else (np.arange(m), pick)
+    ref = orc.dgemm(opA, opB, N, rows=rows, cols=cols).C
+    assert np.array_equal(got[np.ix_(rows, cols)], ref)
+    # and every element against the products formed through planes (the staged calls)
+    dD = torch.empty((n, m), dtype=torch.float64, device="cuda")
+    if ta == "N" and tb == "N":
+        oz.oz2_stage1_convert(m, n, k, dA.data_ptr(), m, dB.data_ptr(), k, N)
+        oz.oz2_stage2_gemm(m, n, k, N)
+        oz.oz2_stage3_crt(m, n, k, dD.data_ptr(), m, N)
+        torch.cuda.synchronize()
+        assert torch.equal(dC, dD)
+    # an infinity in the large operand's last vector reaches the fallback
+    if first and ta == "N":
+        A[m - 1, k - 1] = np.inf
+        dA = _dev(A)
+        oz.oz2_dgemm_ex(ta, tb, m, n, k, 1.0, dA.data_ptr(), A.shape[0], dB.data_ptr(), B.shape[0], 0.0, dC.data_ptr(), m, N)
+        torch.cuda.synchronize()
+        got = dC.t().cpu().numpy()
+        assert np.all(np.isinf(got[m - 1])) and np.all(np.isfinite(got[:m - 1]))
+    del ws
