@@ -210,6 +210,19 @@ __global__ void __launch_bounds__(kThreads) colnorm_kernel(const double* __restr
 // An all-zero vector gets shift 0.
 // With unequal bit budgets (Section 3: k_A != k_B when the operands differ in precision) each operand has its
 // own param (modes 0, 1) or an offset added at the end (mode 2).
+__device__ __forceinline__ int shift_of(unsigned long long b, unsigned long long v, int mode, int param, int offset) {
+  if (!b) return 0;
+  const int e = exponent_of_bits(b);
+  if (mode == 0) return param - 1 - e;
+  if (mode == 1) {
+    const int bits = 64 - __clzll((long long)(v - 1));  // ceil(log2 S)
+    return param - (e - 19 + ((bits + 1) >> 1));
+  }
+  if (!v) return 0;
+  const int t = v <= 1 ? 0 : 64 - __clzll((long long)(v - 1));
+  const int d = param - t;
+  return (d >= 0 ? d / 2 : -((1 - d) / 2)) + offset - (e - 5);
+}
 struct ShiftJob {
   const unsigned long long* mx;
   const unsigned long long* aux;
@@ -224,125 +237,129 @@ __global__ void __launch_bounds__(kThreads) shifts_kernel(const ShiftJob ja, con
   const ShiftJob& j = first ? ja : jb;
   if (!first) i -= ja.count;
   if (i >= j.count) return;
-  const unsigned long long b = j.mx[i];
-  const int param = j.param;
-  int out = 0;
-  if (b) {
-    const int e = exponent_of_bits(b);
-    if (mode == 0) {
-      out = param - 1 - e;
-    } else if (mode == 1) {
-      const unsigned long long S = j.aux[i];
-      const int bits = 64 - __clzll((long long)(S - 1));  // ceil(log2 S)
-      out = param - (e - 19 + ((bits + 1) >> 1));
-    } else {
-      const unsigned long long R = j.aux[i];
-      if (R) {
-        const int t = R <= 1 ? 0 : 64 - __clzll((long long)(R - 1));
-        const int d = param - t;
-        out = (d >= 0 ? d / 2 : -((1 - d) / 2)) + j.offset - (e - 5);
-      }
-    }
-  }
-  j.s[i] = out;
+  j.s[i] = shift_of(j.mx[i], mode == 0 ? 0ull : j.aux[i], mode, j.param, j.offset);
 }
 
-// ---- Small operands: maxima and shifts (Section 3, the simple bound) of both operands in ONE launch and without
-// atomics, so that nothing has to be cleared first: a workgroup owns 16 whole vectors, forms their maxima, writes
-// them and the shifts kappa - 1 - floor(log2 max), and reports in a slot of its own whether it saw an infinity or
-// a NaN.  The conversion launch that follows folds the slots into the flag word.  Three launches fewer than
-// fill + maxima + shifts; used while the operands are small enough that 16 vectors per workgroup still fill the chip.
+// ---- Small operands: maxima, in the Cauchy-Schwarz mode the norm bounds, and shifts of both operands in ONE launch and
+// without atomics, so that nothing has to be cleared first: a workgroup owns 16 whole vectors, forms their maxima (and
+// from them, reading the vectors once more out of the caches, the sums of squares), writes them and the shifts, and reports
+// in a slot of its own whether it saw an infinity or a NaN.  The conversion launch that follows folds the slots into the
+// flag word.  Three launches fewer than fill + maxima + shifts, six with the norms; used while the operands are small
+// enough that 16 vectors per workgroup still fill the chip.
+// A triangular operand is read over the inner positions its 16 vectors can have, half of the array.
+// Bound by the latency of the loads in flight.  Whole calls against separate launches (us): Cauchy-Schwarz mode, 14 moduli,
+// 500^3 51 -> 40, 2048^3 212 -> 190, INT8-product mode 2048^3 277 -> 262; triangular product 4096 x 2048 of order 4096
+// (with the conversion below, which leaves out the same half) 590 -> 480.
 constexpr int kScanVecs = 16;
 struct ScanJob {
   const double* X;
   int64_t ld, nvec, nvec_pad, k;
   unsigned long long* vmax;
+  unsigned long long* vnorm;  // norm bounds (mode 1)
   int* shifts;
-  int param;  // kappa of this operand
+  int param;  // as in ShiftJob
   int tri, strided;
   unsigned nblk;
 };
-__global__ void __launch_bounds__(kThreads) vector_scan_kernel(const ScanJob ja, const ScanJob jb,
+
+// f(value) over this thread's share of vector v, element (v, l) at p[l * step], l = l0 .. l1 - 1 in strides; (r, c) of an
+// element in the stored array: (v, l) or, when swapped, (l, v)
+template <int STRIDE, class F>
+__device__ __forceinline__ void walk_vector(const double* p, int64_t step, int64_t v, int64_t l0, int64_t l1, int tri, bool swapped,
+                                            F&& f) {
+  int64_t l = l0;
+  for (; l + 7 * STRIDE < l1; l += 8 * STRIDE) {
+    double x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = p[(l + u * STRIDE) * step];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int64_t lu = l + u * STRIDE;
+      f(swapped ? tri_value(x[u], lu, v, tri) : tri_value(x[u], v, lu, tri));
+    }
+  }
+  for (; l < l1; l += STRIDE) f(swapped ? tri_value(p[l * step], l, v, tri) : tri_value(p[l * step], v, l, tri));
+}
+
+__global__ void __launch_bounds__(kThreads) vector_scan_kernel(const ScanJob ja, const ScanJob jb, const int mode,
                                                                unsigned long long* __restrict__ slots) {
+  constexpr int kPhases = kThreads / kScanVecs;
   __shared__ unsigned long long part[kThreads];
+  __shared__ unsigned long long top[kScanVecs];
   const bool first = blockIdx.x < ja.nblk;
   const ScanJob& j = first ? ja : jb;
   const unsigned id = first ? blockIdx.x : blockIdx.x - ja.nblk;
   const int64_t v0 = (int64_t)id * kScanVecs;
-  unsigned long long mx = 0ull;
-  int vv;  // which of the 16 vectors this thread's partial maximum belongs to
-  if (j.strided) {
-    // element (v, l) at X[v + l ld]: 16 lanes along the vectors (128 contiguous bytes), 16 column phases
-    vv = threadIdx.x & (kScanVecs - 1);
-    const int64_t v = v0 + vv;
-    if (v < j.nvec) {
-      const double* p = j.X + v;
-      int64_t l = threadIdx.x / kScanVecs;
-      for (; l + 7 * (kThreads / kScanVecs) < j.k; l += 8 * (kThreads / kScanVecs)) {
-        unsigned long long b[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int64_t lu = l + u * (kThreads / kScanVecs);
-          b[u] = abs_bits(tri_value(p[lu * j.ld], v, lu, j.tri));
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) mx = b[u] > mx ? b[u] : mx;
-      }
-      for (; l < j.k; l += kThreads / kScanVecs) {
-        const unsigned long long b = abs_bits(tri_value(p[l * j.ld], v, l, j.tri));
-        mx = b > mx ? b : mx;
-      }
-    }
-    part[threadIdx.x] = mx;
-    __syncthreads();
-    if (threadIdx.x < kScanVecs) {
-#pragma unroll
-      for (int ph = 1; ph < kThreads / kScanVecs; ++ph) {
-        const unsigned long long o = part[threadIdx.x + ph * kScanVecs];
-        mx = o > mx ? o : mx;
-      }
-    }
-  } else {
-    // element (v, l) at X[l + v ld]: a wave takes four vectors in turn, its lanes run down the vector
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    unsigned long long mine = 0ull;
-#pragma unroll 1
-    for (int q = 0; q < kScanVecs / 4; ++q) {
-      const int64_t v = v0 + wv * (kScanVecs / 4) + q;
-      unsigned long long m = 0ull;
-      if (v < j.nvec) {
-        const double* p = j.X + v * j.ld;
-        int64_t l = lane;
-        for (; l + 7 * 64 < j.k; l += 8 * 64) {
-          unsigned long long b[8];
-#pragma unroll
-          for (int u = 0; u < 8; ++u) b[u] = abs_bits(tri_value(p[l + u * 64], l + u * 64, v, j.tri));
-#pragma unroll
-          for (int u = 0; u < 8; ++u) m = b[u] > m ? b[u] : m;
-        }
-        for (; l < j.k; l += 64) {
-          const unsigned long long b = abs_bits(tri_value(p[l], l, v, j.tri));
-          m = b > m ? b : m;
-        }
-      }
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) {
-        const unsigned long long o = __shfl_xor(m, off, 64);
-        m = o > m ? o : m;
-      }
-      if (lane == q) mine = m;
-    }
-    if (lane < kScanVecs / 4) part[wv * (kScanVecs / 4) + lane] = mine;
-    __syncthreads();
-    if (threadIdx.x < kScanVecs) mx = part[threadIdx.x];
+  // inner positions a stored element of these vectors can have
+  const bool swapped = !j.strided;  // the vectors are columns of the stored array
+  int64_t lo = 0, hi = j.k;
+  if (j.tri & 3) {
+    const bool upto = ((j.tri & 3) == 1) != swapped;
+    if (upto)
+      hi = v0 + kScanVecs < hi ? v0 + kScanVecs : hi;
+    else
+      lo = v0 < hi ? v0 : hi;
   }
-  // threads 0 .. 15 hold the maxima of the 16 vectors
+  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  // strided: element (v, l) at X[v + l ld]; 16 lanes along the vectors (128 contiguous bytes), 16 phases along them.
+  // otherwise: element (v, l) at X[l + v ld]; a wave takes four vectors in turn, its lanes run down the vector.
+  const int vv = threadIdx.x & (kScanVecs - 1);
+  // one value per vector in top[]: f(element, partial, vector) over a thread's share, then the partials joined
+  auto reduce = [&](auto zero, auto&& f, auto&& join) {
+    if (j.strided) {
+      auto own = zero;
+      const int64_t v = v0 + vv;
+      if (v < j.nvec)
+        walk_vector<kPhases>(j.X + v, j.ld, v, lo + threadIdx.x / kScanVecs, hi, j.tri, false, [&](double x) { own = f(x, own, vv); });
+      unsigned long long acc = (unsigned long long)own;
+      part[threadIdx.x] = acc;
+      __syncthreads();
+      if (threadIdx.x < kScanVecs) {
+#pragma unroll
+        for (int ph = 1; ph < kPhases; ++ph) acc = join(acc, part[threadIdx.x + ph * kScanVecs]);
+        top[threadIdx.x] = acc;
+      }
+    } else {
+#pragma unroll 1
+      for (int q = 0; q < kScanVecs / 4; ++q) {
+        const int w = wv * (kScanVecs / 4) + q;
+        const int64_t v = v0 + w;
+        auto own = zero;
+        if (v < j.nvec) walk_vector<64>(j.X + v * j.ld, 1, v, lo + lane, hi, j.tri, true, [&](double x) { own = f(x, own, w); });
+        unsigned long long acc = (unsigned long long)own;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) acc = join(acc, __shfl_xor(acc, off, 64));
+        if (lane == 0) top[w] = acc;
+      }
+    }
+    __syncthreads();
+  };
+  reduce(
+      0ull,
+      [](double x, unsigned long long own, int) {
+        const unsigned long long b = abs_bits(x);
+        return b > own ? b : own;
+      },
+      [](unsigned long long a, unsigned long long b) { return a > b ? a : b; });
+  const unsigned long long mx = threadIdx.x < kScanVecs ? top[threadIdx.x] : 0ull;
+  unsigned long long norm = 0ull;
+  if (mode == 1) {
+    __shared__ int scale[kScanVecs];
+    if (threadIdx.x < kScanVecs) scale[threadIdx.x] = mx ? 19 - exponent_of_bits(mx) : 0;
+    __syncthreads();
+    // (a thread's sum is exact: vectors of at most 2^16 elements here, at most 2^12 terms of at most 2^40)
+    reduce(0.0, [&](double x, double own, int w) { return own + scaled_ceil_sq(x, scale[w]); },
+           [](unsigned long long a, unsigned long long b) { return a + b; });
+    norm = threadIdx.x < kScanVecs ? top[threadIdx.x] : 0ull;
+  }
+  // threads 0 .. 15 hold the values of the 16 vectors
   bool bad = false;
   if (threadIdx.x < kScanVecs) {
     const int64_t v = v0 + threadIdx.x;
     if (v < j.nvec_pad) {
       j.vmax[v] = mx;
-      j.shifts[v] = mx ? j.param - 1 - exponent_of_bits(mx) : 0;
+      if (mode == 1) j.vnorm[v] = norm;
+      j.shifts[v] = shift_of(mx, norm, mode, j.param, 0);
     }
     bad = mx >= kInfBits;
   }
@@ -368,33 +385,42 @@ __device__ __forceinline__ void store_bounds(const double* mine, int shift, int8
 }
 
 // ---- INT8-product shift mode (Section 4.1): row and column maxima of P = A''B'' (INT32, element (i,j) at
-// j*m_pad + i).  One block: 256 rows x 64 columns; lanes run along the rows.
+// j*m_pad + i).  A wave takes 256 rows (four per lane, 16-byte loads) x 64 columns; the four rows of a lane are joined
+// before the wave's reduction, which is what the kernel spends its time on (3001 x 2777: 38 -> 27 us).
 constexpr int kProdCols = 64;
+constexpr int kProdRows = kThreads / 64 * 256;
 __global__ void __launch_bounds__(kThreads) prodmax_kernel(const int* __restrict__ P, int64_t m_pad, int64_t m, int64_t n,
                                                            int64_t row_blocks, unsigned long long* __restrict__ rowtop,
                                                            unsigned long long* __restrict__ coltop) {
+  typedef int v4s __attribute__((ext_vector_type(4)));
   const int64_t rb = blockIdx.x % row_blocks, cb = blockIdx.x / row_blocks;
-  const int64_t i = rb * kThreads + threadIdx.x;  // < m_pad
+  const int lane = threadIdx.x & 63;
+  const int64_t i = rb * kProdRows + (threadIdx.x >> 6) * 256 + 4 * lane;
+  if (i - 4 * lane >= m_pad) return;  // the whole wave; m_pad is a multiple of 256
   const int64_t j0 = cb * kProdCols;
   const int* src = P + i + j0 * m_pad;
-  int rmax = 0;
+  v4s rmax = {0, 0, 0, 0};
   for (int jj = 0; jj < kProdCols; jj += 8) {
-    int v[8];
+    v4s v[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = (i < m && j0 + jj + u < n) ? src[(int64_t)(jj + u) * m_pad] : 0;
+    for (int u = 0; u < 8; ++u)
+      v[u] = j0 + jj + u < n ? __builtin_nontemporal_load(reinterpret_cast<const v4s*>(src + (int64_t)(jj + u) * m_pad)) : v4s{0, 0, 0, 0};
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      rmax = v[u] > rmax ? v[u] : rmax;
-      int c = v[u];
+      // (rows beyond m are padding: zero operands, zero products)
+      rmax = __builtin_elementwise_max(rmax, v[u]);
+      int c = max(max(v[u].x, v[u].y), max(v[u].z, v[u].w));
 #pragma unroll
       for (int off = 32; off >= 1; off >>= 1) {
         int o = __shfl_xor(c, off, 64);
         c = o > c ? o : c;
       }
-      if ((threadIdx.x & 63) == 0 && c > 0) atomicMax(coltop + j0 + jj + u, (unsigned long long)c);
+      if (lane == 0 && c > 0) atomicMax(coltop + j0 + jj + u, (unsigned long long)c);
     }
   }
-  if (rmax > 0) atomicMax(rowtop + i, (unsigned long long)rmax);
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    if (i + r < m && rmax[r] > 0) atomicMax(rowtop + i + r, (unsigned long long)rmax[r]);
 }
 
 // Plane layout (shared with the GEMM kernel): blocks of 256 rows x 64 bytes of the inner dimension, each
@@ -403,6 +429,13 @@ __global__ void __launch_bounds__(kThreads) prodmax_kernel(const int* __restrict
 constexpr int kBlkRows = OZ2_TILE_M;   // 256
 constexpr int kBlkK = OZ2_TILE_K;      // 64
 static_assert(OZ2_TILE_M == 256 && OZ2_TILE_N == 256 && OZ2_TILE_K == 64, "plane layout is 256 x 64 blocks");
+
+// A triangular operand (TRMM shape): do the products read inner positions l0 .. l1 - 1 of the block of 256 vectors that
+// vector v0 belongs to?  They walk the k-tiles up to (upto) or from the diagonal block; what they leave out is not written.
+__device__ __forceinline__ bool tile_used(int64_t v0, int64_t l0, int64_t l1, bool upto, int tri) {
+  const int64_t d0 = v0 / kBlkRows * kBlkRows;
+  return (tri & 3) == 0 || (upto ? l0 < d0 + kBlkRows : l1 > d0);
+}
 
 // A (m x k column-major) -> planes.  Block: 64 rows x 64 columns.  Every column segment (64 rows, 512
 // bytes) is read coalesced with lanes along the rows, transposed through LDS so that a thread holds 16
@@ -419,6 +452,7 @@ __device__ __forceinline__ void convert_strided(const double* __restrict__ A, in
                                                 double* tile, unsigned bx, unsigned by) {
   const int64_t r0 = (int64_t)bx * kConvARows;  // < m_pad
   const int64_t kb = by;
+  if (KIND != 2 && !tile_used(r0, kb * kBlkK, kb * kBlkK + kBlkK, (tri & 3) == 1, tri)) return;
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
   {
     const int64_t i = r0 + lane;
@@ -475,6 +509,7 @@ __device__ __forceinline__ void convert_contig(const double* __restrict__ B, int
                                                double* tile, unsigned bx, unsigned by) {
   const int64_t j0 = (int64_t)bx * kConvBCols;  // < n_pad, multiple of 16
   const int64_t lbase = (int64_t)by * kConvBKC;
+  if (KIND != 2 && !tile_used(j0, lbase, lbase + kConvBKC, (tri & 3) == 2, tri)) return;
   {
     const int64_t l = lbase + threadIdx.x;
     const int slot = (threadIdx.x >> 4) * kConvBGroup + (threadIdx.x & 15);
@@ -837,48 +872,60 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
 #undef OZ2_SHORT
     return hipGetLastError();
   }
-  // Small operands under the simple bound: maxima and shifts in one launch without atomics (nothing to clear
+  // Small operands: maxima, norm bounds and shifts in one launch without atomics (nothing to clear
   // first); its per-workgroup reports become the flag word in the conversion launch.  "Small": at most 2^25 elements
   // in both operands together (4096 x 4096 twice), where 16 vectors per workgroup are work enough for the chip
   // and the launches saved still count.
-  const bool scan = shift_mode == OZ2_SHIFT_MAX && !strassen &&
-                    (lay.m_pad + (nops == 2 ? lay.n_pad : 0)) * lay.k_pad <= ((int64_t)1 << 25);
+  const bool scan = !strassen && (lay.m_pad + (nops == 2 ? lay.n_pad : 0)) * lay.k_pad <= ((int64_t)1 << 25);
+  // what the shifts are formed from: the budgets of the operands, or (INT8-product mode) first the exponents 5 - e of the
+  // 6-bit bounds
+  int param[2];
+  if (shift_mode == OZ2_SHIFT_INT8_PRODUCT) {
+    param[0] = param[1] = 6;
+  } else if (shift_mode == OZ2_SHIFT_CAUCHY_SCHWARZ) {
+    param[0] = plan.beta - d;
+    param[1] = d == 0 ? plan.beta : plan.budget2 - param[0];
+  } else {
+    param[0] = plan.kappa - d;
+    param[1] = d == 0 ? plan.kappa : plan.kappa_sum - param[0];
+  }
+  const int base_mode = shift_mode == OZ2_SHIFT_CAUCHY_SCHWARZ ? 1 : 0;  // as shift_of counts them
   if (scan) {
-    const int kappa_a = plan.kappa - d, kappa_b = d == 0 ? plan.kappa : plan.kappa_sum - kappa_a;
     ScanJob sj[2] = {};
     unsigned total = 0;
     for (int x = 0; x < nops; ++x) {
       const Operand& o = ops[x];
-      sj[x] = {o.X, o.ld, o.nvec, o.nvec_pad, o.k, o.vmax, o.shifts, x == 0 ? kappa_a : kappa_b, o.tri, o.strided ? 1 : 0,
+      sj[x] = {o.X, o.ld, o.nvec, o.nvec_pad, o.k, o.vmax, o.vaux, o.shifts, param[x], o.tri, o.strided ? 1 : 0,
                (unsigned)(o.nvec_pad / kScanVecs)};
       total += sj[x].nblk;
     }
     if (nops == 1) sj[1] = sj[0], sj[1].nblk = 0;
-    // the slots live in the auxiliary vectors, which this shift mode does not use (one word per 16 vectors)
-    unsigned long long* slots = ops[0].vaux;
-    hipLaunchKernelGGL(vector_scan_kernel, dim3(total), thr, 0, st, sj[0], sj[1], slots);
+    // the slots live in the product region, which nothing else uses before the products (one word per 16 vectors)
+    unsigned long long* slots = reinterpret_cast<unsigned long long*>(ws + lay.off_c);
+    hipLaunchKernelGGL(vector_scan_kernel, dim3(total), thr, 0, st, sj[0], sj[1], base_mode, slots);
     fin = {slots, total, flag};
-    xbits[0] = kappa_a;
-    xbits[1] = kappa_b;
   } else {
-  fill(ops[0].vmax, n_max);
-  if (hipError_t e = launch_max(ops, nops, st); e != hipSuccess) return e;
+    fill(ops[0].vmax, n_max);
+    if (hipError_t e = launch_max(ops, nops, st); e != hipSuccess) return e;
+    if (base_mode == 1) {
+      fill(ops[0].vaux, n_aux);
+      for (int x = 0; x < nops; ++x) launch_norm(ops[x], st);
+    }
+    shifts(base_mode, param[0], param[1], 0, 0);
   }
-  if (scan) {
-    // shifts are written
-  } else if (shift_mode == OZ2_SHIFT_INT8_PRODUCT) {
+  if (shift_mode == OZ2_SHIFT_INT8_PRODUCT) {
     // bound planes (in the slots of residue plane 0), their INT8 product (in the slot of product plane 0),
     // its row and column maxima, then the shifts.  In the symmetric case the product is A''A''^T and its
     // row maxima are its column maxima (those land in the unused column array).
-    shifts(0, 6, 6, 0, 0);  // exponents 5 - e of the bounds
     {
       const int bound[2] = {2, 2};
-      if (hipError_t e = launch_convert(ops, nops, bound, conv, Oz2ScanFinish{nullptr, 0u, nullptr}, st); e != hipSuccess) return e;
+      if (hipError_t e = launch_convert(ops, nops, bound, conv, fin, st); e != hipSuccess) return e;
+      fin = {nullptr, 0u, nullptr};
     }
     fill(ops[0].vaux, n_aux);
     hipError_t e = oz2_launch_bound_gemm(lay, ws, B == nullptr, st);
     if (e != hipSuccess) return e;
-    const int64_t row_blocks = lay.m_pad / kThreads;
+    const int64_t row_blocks = (lay.m_pad + kProdRows - 1) / kProdRows;
     const int64_t nblk = row_blocks * (int64_t)blocks_of(n, kProdCols);
     if (nblk >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
     hipLaunchKernelGGL(prodmax_kernel, dim3((unsigned)nblk), thr, 0, st, reinterpret_cast<const int*>(ws + lay.off_c),
@@ -886,18 +933,9 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
     shifts(2, plan.budget2, plan.budget2, -d, d);
     xbits[0] = plan.budget2 / 2 + 7 - d;  // |x'| < 2^(e + 1 + sa) <= 2^(floor(b/2) + 6 -+ d)
     xbits[1] = plan.budget2 / 2 + 7 + d;
-  } else if (shift_mode == OZ2_SHIFT_CAUCHY_SCHWARZ) {
-    fill(ops[0].vaux, n_aux);
-    for (int x = 0; x < nops; ++x) launch_norm(ops[x], st);
-    const int beta_a = plan.beta - d, beta_b = d == 0 ? plan.beta : plan.budget2 - beta_a;
-    shifts(1, beta_a, beta_b, 0, 0);
-    xbits[0] = beta_a + 1;
-    xbits[1] = beta_b + 1;
   } else {
-    const int kappa_a = plan.kappa - d, kappa_b = d == 0 ? plan.kappa : plan.kappa_sum - kappa_a;
-    shifts(0, kappa_a, kappa_b, 0, 0);
-    xbits[0] = kappa_a;
-    xbits[1] = kappa_b;
+    xbits[0] = param[0] + base_mode;
+    xbits[1] = param[1] + base_mode;
   }
   const int kinds[2] = {xbits[0] > 75 ? 1 : 0, xbits[1] > 75 ? 1 : 0};
   if (strassen) {

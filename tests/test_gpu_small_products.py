@@ -155,3 +155,23 @@ def test_thin_products_convert_the_large_operand_on_the_way(thin, ta, tb, first)
         got = dC.t().cpu().numpy()
         assert np.all(np.isinf(got[m - 1])) and np.all(np.isfinite(got[:m - 1]))
     del ws
+
+
+@pytest.mark.parametrize("side,uplo,ta", [(s, u, t) for s in "LR" for u in "LU" for t in "NT"])
+def test_triangular_operand_of_which_only_the_used_half_is_converted(side, uplo, ta):
+    """Orders above the one-pass conversion's 1024: scan and conversion walk only the blocks that the products read.  The
+    workspace is full of other bytes beforehand, and the array's other triangle of NaNs."""
+    order, other, N = 1300, 70, 9
+    m, n = (order, other) if side == "L" else (other, order)
+    rng = np.random.default_rng(order + len(side + uplo + ta) + ord(side) + ord(uplo) + ord(ta))
+    A, B = _mat(rng, order, order), _mat(rng, m, n)
+    keep = np.tril(np.ones((order, order), bool)) if uplo == "L" else np.triu(np.ones((order, order), bool))
+    A[~keep] = np.nan
+    print("dtrmm: %s%s%s order %d" % (side, uplo, ta, order), flush=True)
+    dA, dB = _dev(A), _dev(B)
+    ws = oz.Workspace(m, n, order, N)
+    ws.buf.fill_(0x7f)
+    oz.oz2_dtrmm(side, uplo, ta, "N", m, n, 1.0, dA.data_ptr(), order, dB.data_ptr(), m, N)
+    torch.cuda.synchronize()
+    assert np.array_equal(dB.cpu().numpy(), orc.dtrmm(side, uplo, ta, "N", 1.0, A, B, N))
+    del ws
