@@ -45,9 +45,9 @@
 // epilogue: GEMM -9 % at k = 1024, -5 % at 4096^3, -1 % at 8192^3, even at 16384^3 where the power cap decides).
 // The loop has one body for every iteration and the same number of copies in flight at every wait.
 //
-// Structured products: for the symmetric product op(A) op(A)^T both operands are A's planes and the
-// workgroups of the other triangle of tiles return at once; for a triangular operand a tile walks only the
-// k-tiles up to or from its diagonal block.
+// Structured products: for the symmetric product op(A) op(A)^T both operands are A's planes and only the tiles of one
+// triangle are launched (in the super-block order: those of the other one return at once); for a triangular operand a tile
+// walks only the k-tiles up to or from its diagonal block.
 #include <type_traits>
 
 #include "oz2_gemm.h"
@@ -85,6 +85,7 @@ struct GemmArgs {
   int ktiles;              // k_pad / BK
   int ktiles_per_block;    // k-tiles between modular reductions of the accumulators
   int triangle;            // 0: all tiles; 1: only tiles with tm >= tn (lower); 2: only tm <= tn (upper)
+  int folded;              // tile rows of the triangle when tiles_m x tiles_n is its rectangle (see decode_tile), else 0
   int krange;              // triangular operand: which k-tiles of a tile can be nonzero (see OZ2_KRANGE_*)
   const unsigned long long* skip_flag;  // if not null and nonzero on the device: the products are not needed
   Oz2ScanFinish fin;                    // reports of stage 1 that workgroup 0 turns into the flag word
@@ -269,6 +270,18 @@ __device__ __forceinline__ Tile decode_tile(const GemmArgs& g, int slot, int wv)
     } else {
       tn = rr / kGroupM;
       tm = first_m + rr % kGroupM;
+    }
+    if (g.folded != 0) {
+      // the triangle of g.folded rows of tiles laid out as a rectangle: row y holds the triangle's row g.folded - 1 - y and,
+      // behind it, the short row that fills it up
+      const int y = tm, x = tn, len = g.folded - y;
+      tm = x < len ? g.folded - 1 - y : ((g.folded & 1) ? y - 1 : y);
+      tn = x < len ? x : x - len;
+      if (g.triangle == 2) {
+        const int swap = tm;
+        tm = tn;
+        tn = swap;
+      }
     }
   }
   // symmetric product: the other triangle of tiles is never needed
@@ -675,11 +688,19 @@ hipError_t launch_gemm(const Oz2Layout& lay, char* ws, int num_moduli, const int
   g.tiles_m = (int)(lay.m_pad / BM);
   g.tiles_n = (int)(lay.n_pad / BN);
   g.num_moduli = num_moduli;
+  g.superblock = (g.tiles_m % 16 == 0 && g.tiles_n % 16 == 0) ? 1 : 0;
+  // Symmetric product outside the super-block order: only the tiles of the triangle are counted, so that they are launched
+  // like those of a general product, one workgroup per compute unit (16 moduli, inner dimension 1024, whole calls: dsyrk of
+  // order 5000 425 -> 393 us, of order 10000 1447 -> 1333).
+  g.folded = triangle != 0 && !g.superblock ? g.tiles_m : 0;
+  if (g.folded) {
+    g.tiles_n = g.folded % 2 ? g.folded : g.folded + 1;
+    g.tiles_m = (g.folded + 1) / 2;
+  }
   const int64_t total = (int64_t)g.tiles_m * g.tiles_n * num_moduli;
   if (total > (int64_t)1 << 30) return hipErrorInvalidValue;
   g.total = (int)total;
   g.chunk = (int)((total + 7) / 8);
-  g.superblock = (g.tiles_m % 16 == 0 && g.tiles_n % 16 == 0) ? 1 : 0;
   // list order of the 8 x 4 sub-blocks: general products whose tile grid is a multiple of 8 x 4 but not of 16 x 16
   // (and at least eight rounds of them: with a handful of sub-blocks the range order spreads the tiles better)
   const bool list_order = !g.superblock && triangle == 0 && krange == OZ2_KRANGE_ALL && g.tiles_m % 8 == 0 &&
@@ -710,7 +731,7 @@ hipError_t launch_gemm(const Oz2Layout& lay, char* ws, int num_moduli, const int
   g.xcd_sync = nullptr;
   g.full_rounds = 0;
   g.sync_spins = g_sync_spins;
-  if (triangle == 0 && krange == OZ2_KRANGE_ALL) {
+  if ((triangle == 0 || g.folded) && krange == OZ2_KRANGE_ALL) {
     if (grid > (unsigned)g_cus) grid = (unsigned)g_cus;
     // General products: the workgroups of an XCD start the tiles of a round together, which keeps them
     // on the same k-tiles of their shared panels (measured: L2 misses 48.7 GiB per launch every time instead of

@@ -94,10 +94,12 @@ def test_nonfinite_inputs_reach_the_fallback(m, n, k, where, bad):
     assert flag == 0 and np.array_equal(got, ref)
 
 
+@pytest.mark.parametrize("n,k", [(4200, 64), (4200, 520), (4400, 520)])
 @pytest.mark.parametrize("uplo", ["L", "U"])
-def test_symmetric_update_with_more_than_2_24_elements(uplo):
-    """The matrix-core kernel of stage 3 skips what lies in the other triangle: rows and columns around its 256 x 16 blocks."""
-    n, k, N = 4200, 64, 6
+def test_symmetric_update_with_more_than_2_24_elements(uplo, n, k):
+    """The matrix-core kernel of stage 3 skips what lies in the other triangle: rows and columns around its 256 x 16 blocks;
+    with the longer inner dimension the products take 256 x 256 tiles, 17 or 18 rows of them, of one triangle only."""
+    N = 6
     rng = np.random.default_rng(3)
     A = _mat(rng, n, k)
     dA = _dev(A)
@@ -108,7 +110,7 @@ def test_symmetric_update_with_more_than_2_24_elements(uplo):
     got = dC.t().cpu().numpy()
     inside = np.tril(np.ones((n, n), bool)) if uplo == "L" else np.triu(np.ones((n, n), bool))
     assert np.all(got[~inside] == 7.0)
-    rows = np.concatenate([np.arange(0, 40), np.arange(240, 280), np.arange(2030, 2070), np.arange(4080, 4200)])
+    rows = np.concatenate([np.arange(0, 40), np.arange(240, 280), np.arange(2030, 2070), np.arange(n - 150, n)])
     ref = orc.dgemm(A, np.asfortranarray(A.T), N, rows=rows, cols=np.arange(n)).C
     mine = inside[rows]
     assert np.array_equal(got[rows][mine], ref[mine])
