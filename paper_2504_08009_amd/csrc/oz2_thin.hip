@@ -8,11 +8,15 @@
 // of the thin operand, which come straight from the L2 in the layout an MFMA operand has: wave w works for modulus w of the
 // group and nobody else needs those bytes.  The large operand is read once per group (the groups of the same 64 vectors
 // run on the same die at the same time and find it in the L2); its planes do not exist.
-// Bound by the conversion's vector instructions (some 50 per element and group of eight moduli: 3700 of the 5200 cycles of
-// a k-tile).
+// Bound by the conversion's vector instructions (some 50 per element and group of eight moduli: 3700 of the 4500 cycles of
+// a k-tile).  The loop has no branch that loads, and its loads stay where they are written: left to itself the compiler moves
+// them down to their use, where their latency shows (16 moduli 8192 x 96 x 8192 475 -> 406 us, 96 x 8192 x 8192 537 -> 429,
+// 22 moduli 8192 x 128 x 8192 1479 -> 824).
 //
 // 512 threads, eight waves, two per SIMD: 32 NI accumulators per lane (NI = 32-vector tiles of the thin operand), ordinary
 // registers (build.py builds this file with -amdgpu-mfma-vgpr-form).
+#include <type_traits>
+
 #include "oz2_gemm.h"
 #include "oz2_math.h"
 
@@ -70,15 +74,18 @@ __global__ void __launch_bounds__(kThreads) thin_products_kernel(const ThinArgs 
   const double* const src = g.strided ? g.X + v + (int64_t)pos * g.ld : g.X + v * g.ld + pos;
   const int64_t step = g.strided ? g.ld : 1;
   const int ktiles = (int)(g.k_pad / BK);
-  auto fetch = [&](int kt, double (&d)[8]) {
+  auto fetch = [&](int kt, auto whole, double (&d)[8]) {
     const double* p = src + (int64_t)kt * BK * step;
-    if ((int64_t)(kt + 1) * BK <= g.k) {
+    if constexpr (decltype(whole)::value) {
 #pragma unroll
       for (int u = 0; u < 8; ++u) d[u] = p[u * step];
-    } else {  // the last k-tile, or beyond it: zeros where there is nothing to read
-      const int64_t left = g.k - ((int64_t)kt * BK + pos);
+    } else {  // the last k-tile, or beyond it: the last element where there is nothing to read, then zero instead
+      const int last = (int)(g.k - ((int64_t)kt * BK + pos)) - 1;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) d[u] = u < left ? p[u * step] : 0.0;
+      for (int u = 0; u < 8; ++u) {
+        const double x = p[min(u, last) * step];
+        d[u] = u <= last ? x : 0.0;
+      }
     }
   };
   // 16-byte chunks of a row are swizzled as in the GEMM's stages (fragments of 16 rows fall on 16 bank groups)
@@ -123,40 +130,48 @@ __global__ void __launch_bounds__(kThreads) thin_products_kernel(const ThinArgs 
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[x][y][e] = (int)OZ2_ACC_START;
 
-  // k-tile kt is multiplied while kt + 1 is converted and kt + 2 is on its way from memory
-  auto iteration = [&](int kt, const double (&now)[8], double (&later)[8]) {
-    const int buf = kt & 1;
-    fetch(kt + 2, later);
-    if (works) {
-      const char* base = lds[buf][wv] + (lane & 31) * BK;
-      v4i fb[2][2];
+  // k-tile kt is multiplied while kt + 1 is converted and kt + 2 is on its way from memory.  No branches: where paths that
+  // load join, or a loop-carried value is copied, the loads in flight are waited for.
+  auto iteration = [&](int kt, int buf, auto whole, const double (&now)[8], double (&later)[8]) {
+    fetch(kt + 2, whole, later);
+    asm volatile("" ::: "memory");  // (the compiler would move the loads down to where their results are needed)
+    const char* base = lds[buf][works ? wv : 0] + (lane & 31) * BK;
+    v4i fb[2][2];
 #pragma unroll
-      for (int s = 0; s < 2; ++s)
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+        fb[s][x] = *reinterpret_cast<const v4i*>(base + x * 32 * BK + (((2 * s + half) ^ swz) << 4));
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int y = 0; y < NI; ++y)
 #pragma unroll
         for (int x = 0; x < 2; ++x)
-          fb[s][x] = *reinterpret_cast<const v4i*>(base + x * 32 * BK + (((2 * s + half) ^ swz) << 4));
-#pragma unroll
-      for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int y = 0; y < NI; ++y)
-#pragma unroll
-          for (int x = 0; x < 2; ++x)
-            acc[x][y] = BIG_A ? __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[s][x], ft[s][y], acc[x][y], 0, 0, 0)
-                              : __builtin_amdgcn_mfma_i32_32x32x32_i8(ft[s][y], fb[s][x], acc[x][y], 0, 0, 0);
-      fetch_thin(kt + 1 < ktiles ? kt + 1 : kt);
-    }
-    if (kt + 1 < ktiles) convert(now, buf ^ 1);
+          acc[x][y] = BIG_A ? __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[s][x], ft[s][y], acc[x][y], 0, 0, 0)
+                            : __builtin_amdgcn_mfma_i32_32x32x32_i8(ft[s][y], fb[s][x], acc[x][y], 0, 0, 0);
+    fetch_thin(kt + 1 < ktiles ? kt + 1 : ktiles - 1);
+    asm volatile("" ::: "memory");
+    convert(now, buf ^ 1);
     __syncthreads();  // the next k-tile is complete, and nobody reads this one's buffer any more
   };
+  const std::true_type whole;
+  const std::false_type part;
   double d0[8], d1[8];
-  fetch(0, d0);
-  fetch(1, d1);
-  if (works) fetch_thin(0);
+  fetch(0, whole, d0);  // (the inner dimension is above 1024)
+  fetch(1, whole, d1);
+  fetch_thin(0);
   convert(d0, 0);
   __syncthreads();
-  for (int kt = 0; kt < ktiles; kt += 2) {
-    iteration(kt, d1, d0);
-    if (kt + 1 < ktiles) iteration(kt + 1, d0, d1);
+  __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): what is pending here would be waited for in every round of the loop
+  int kt = 0;  // two at a time; what lies beyond the last k-tile is zero
+  for (; (int64_t)(kt + 4) * BK <= g.k; kt += 2) {
+    iteration(kt, 0, whole, d1, d0);
+    iteration(kt + 1, 1, whole, d0, d1);
+  }
+  for (; kt < ktiles; kt += 2) {
+    iteration(kt, 0, part, d1, d0);
+    iteration(kt + 1, 1, part, d0, d1);
   }
   if (!works) return;
 
@@ -183,16 +198,16 @@ __global__ void __launch_bounds__(kThreads) thin_products_kernel(const ThinArgs 
 
 // The smaller of two estimates in nanoseconds, measured times per k-tile of a workgroup (one per compute unit) and per
 // byte that conversion and products move between them otherwise (8 read, N written, N read per element of the large
-// operand, 4.3 TB/s).  Whole calls, with planes against without (us): 16 moduli 8192 x 96 x 8192 680 / 474, 96 x 8192 x 8192
-// 698 / 536, 8192 x 32 x 8192 671 / 436, 16384 x 64 x 2048 374 / 244, 4096 x 64 x 4096 172 / 193; 14 moduli 64 x 15484 x
-// 9445 1391 / 1034; 22 moduli 8192 x 96 x 8192 906 / 864.
+// operand, 4.3 TB/s).  Whole calls, with planes against without (us): 16 moduli 8192 x 96 x 8192 680 / 406, 96 x 8192 x 8192
+// 698 / 429, 8192 x 32 x 8192 671 / 353, 16384 x 64 x 2048 374 / 208; 14 moduli 64 x 15484 x 9445 1391 / 910; 18 moduli
+// 8192 x 96 x 8192 739 / 632; 22 moduli 8192 x 96 x 8192 906 / 739.
 int oz2_thin_applies(int64_t m, int64_t n, const Oz2Plan& plan, const Oz2Layout& lay, int64_t kblock) {
   const int64_t thin = m < n ? m : n, large = m < n ? n : m;
   // (up to 1024 the one-pass conversion reads the operand once, which is the better half of this)
   if (thin > kMaxThin || lay.k_pad <= 1024 || lay.k_pad > OZ2_ACC_BLOCK || kblock < lay.k_pad) return 0;
   const int64_t groups = (plan.N + kGroup - 1) / kGroup, cus = oz2_gemm_cus();
   const int64_t rounds = ((large + kRows - 1) / kRows * groups + cus - 1) / cus;
-  const int64_t here = rounds * (lay.k_pad / BK) * 2700, planes = large * lay.k_pad / 10 * (8 + 2 * plan.N) / 430;
+  const int64_t here = rounds * (lay.k_pad / BK) * 2400, planes = large * lay.k_pad / 10 * (8 + 2 * plan.N) / 430;
   return here < planes - planes / 10 ? (m < n ? 2 : 1) : 0;
 }
 

@@ -177,3 +177,23 @@ def test_triangular_operand_of_which_only_the_used_half_is_converted(side, uplo,
     torch.cuda.synchronize()
     assert np.array_equal(dB.cpu().numpy(), orc.dtrmm(side, uplo, ta, "N", 1.0, A, B, N))
     del ws
+
+
+@pytest.mark.parametrize("k", [1025, 1088, 1120, 1152, 1153, 1216, 1279])
+@pytest.mark.parametrize("ta", ["N", "T"])
+def test_thin_products_at_the_ends_of_the_inner_dimension(k, ta):
+    """Even and odd numbers of k-tiles, the last one whole or not: the loop takes two at a time."""
+    m, n, N = 12337, 40, 16
+    rng = np.random.default_rng(k)
+    A = _mat(rng, *((m, k) if ta == "N" else (k, m)))
+    B = _mat(rng, k, n)
+    print("thin: m=%d n=%d k=%d N=%d op=%s" % (m, n, k, N, ta), flush=True)
+    dA, dB = _dev(A), _dev(B)
+    dC = torch.full((n, m), 5.0, dtype=torch.float64, device="cuda")
+    ws = oz.Workspace(m, n, k, N)
+    oz.oz2_dgemm_ex(ta, "N", m, n, k, 1.0, dA.data_ptr(), A.shape[0], dB.data_ptr(), k, 0.0, dC.data_ptr(), m, N)
+    torch.cuda.synchronize()
+    rows = np.unique(np.concatenate([np.arange(70), np.arange(m - 70, m), rng.integers(0, m, 40)]))
+    opA = np.asfortranarray(A.T if ta == "T" else A)
+    assert np.array_equal(dC.t().cpu().numpy()[rows], orc.dgemm(opA, B, N, rows=rows, cols=np.arange(n)).C)
+    del ws
