@@ -250,7 +250,11 @@ __global__ void __launch_bounds__(kThreads) shifts_kernel(const ShiftJob ja, con
 // Bound by the latency of the loads in flight.  Whole calls against separate launches (us): Cauchy-Schwarz mode, 14 moduli,
 // 500^3 51 -> 40, 2048^3 212 -> 190, INT8-product mode 2048^3 277 -> 262; triangular product 4096 x 2048 of order 4096
 // (with the conversion below, which leaves out the same half) 590 -> 480.
+// 512 threads for the 16 vectors: twice the loads in flight where the workgroups are few (256 / 512 / 1024 threads, us: 500^3
+// Cauchy-Schwarz 39.9 / 36.0 / 34.0, 1000 x 1000 x 2000 86.2 / 78.3 / 78.7, 256 x 256 x 4096 64.3 / 56.5 / 57.6, 300 x 3000 x 5000
+// 258 / 246 / 251, 4096^3 1153 / 1151 / 1150).
 constexpr int kScanVecs = 16;
+constexpr int kScanThreads = 512;
 struct ScanJob {
   const double* X;
   int64_t ld, nvec, nvec_pad, k;
@@ -281,10 +285,11 @@ __device__ __forceinline__ void walk_vector(const double* p, int64_t step, int64
   for (; l < l1; l += STRIDE) f(swapped ? tri_value(p[l * step], l, v, tri) : tri_value(p[l * step], v, l, tri));
 }
 
-__global__ void __launch_bounds__(kThreads) vector_scan_kernel(const ScanJob ja, const ScanJob jb, const int mode,
+__global__ void __launch_bounds__(kScanThreads) vector_scan_kernel(const ScanJob ja, const ScanJob jb, const int mode,
                                                                unsigned long long* __restrict__ slots) {
-  constexpr int kPhases = kThreads / kScanVecs;
-  __shared__ unsigned long long part[kThreads];
+  constexpr int kEach = kScanVecs / (kScanThreads / 64);  // vectors a wave takes when they are columns
+  constexpr int kPhases = kScanThreads / kScanVecs;
+  __shared__ unsigned long long part[kScanThreads];
   __shared__ unsigned long long top[kScanVecs];
   const bool first = blockIdx.x < ja.nblk;
   const ScanJob& j = first ? ja : jb;
@@ -321,8 +326,8 @@ __global__ void __launch_bounds__(kThreads) vector_scan_kernel(const ScanJob ja,
       }
     } else {
 #pragma unroll 1
-      for (int q = 0; q < kScanVecs / 4; ++q) {
-        const int w = wv * (kScanVecs / 4) + q;
+      for (int q = 0; q < kEach; ++q) {
+        const int w = wv * kEach + q;
         const int64_t v = v0 + w;
         auto own = zero;
         if (v < j.nvec) walk_vector<64>(j.X + v * j.ld, 1, v, lo + lane, hi, j.tri, true, [&](double x) { own = f(x, own, w); });
@@ -902,7 +907,7 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
     if (nops == 1) sj[1] = sj[0], sj[1].nblk = 0;
     // the slots live in the product region, which nothing else uses before the products (one word per 16 vectors)
     unsigned long long* slots = reinterpret_cast<unsigned long long*>(ws + lay.off_c);
-    hipLaunchKernelGGL(vector_scan_kernel, dim3(total), thr, 0, st, sj[0], sj[1], base_mode, slots);
+    hipLaunchKernelGGL(vector_scan_kernel, dim3(total), dim3(kScanThreads), 0, st, sj[0], sj[1], base_mode, slots);
     fin = {slots, total, flag};
   } else {
     fill(ops[0].vmax, n_max);
