@@ -338,6 +338,12 @@ int oz2_host_crt_element_digits(int num_moduli, const uint8_t* residues, double*
  * two splitting depths to use, as the kernels do.  No GPU is touched. */
 int oz2_host_residues(int num_moduli, int kappa, double a, int shift, int8_t* res_out);
 
+/* Host-side evaluation of line 7 as the epilogues of stage 2 take it (UINT8 residue planes): the residues in
+ * [0, p) of `count` INT32 products modulo moduli table entry `index` (0 .. oz2_max_moduli() - 1), with the constants
+ * and the steps of the kernels.  The products are sums that one block of the inner dimension can have
+ * (|product| <= 61440 * 2^14).  No GPU is touched.  Returns 0 or a negative argument code. */
+int oz2_host_product_residues(int index, int64_t count, const int32_t* products, uint8_t* res_out);
+
 const char* oz2_status_string(int status);
 
 #ifdef __cplusplus

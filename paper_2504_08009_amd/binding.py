@@ -12,7 +12,7 @@ SYMBOLS = [
     "oz2_set_gemm_algorithm", "oz2_gemm_algorithm_for", "oz2_workspace_bytes_strassen", "oz2_workspace_bytes_preferred",
     "oz2_context_create", "oz2_context_destroy", "oz2_context_set_workspace", "oz2_context_set", "oz2_context_get",
     "oz2_context_workspace_bytes", "oz2_context_dgemm", "oz2_context_dsyrk", "oz2_context_dtrmm",
-    "oz2_set_kblock", "oz2_set_round_sync", "oz2_set_shift_mode", "oz2_set_product_format", "oz2_set_bit_split", "oz2_set_nonfinite_check", "oz2_set_stage_events", "oz2_calibrate_mfma", "oz2_host_crt_element", "oz2_host_crt_element_digits", "oz2_host_residues", "oz2_status_string",
+    "oz2_set_kblock", "oz2_set_round_sync", "oz2_set_shift_mode", "oz2_set_product_format", "oz2_set_bit_split", "oz2_set_nonfinite_check", "oz2_set_stage_events", "oz2_calibrate_mfma", "oz2_host_crt_element", "oz2_host_crt_element_digits", "oz2_host_residues", "oz2_host_product_residues", "oz2_status_string",
 ]
 
 
@@ -75,6 +75,7 @@ def lib():
         L.oz2_host_crt_element.argtypes = [ci, vp, vp]
         L.oz2_host_crt_element_digits.argtypes = [ci, vp, vp]
         L.oz2_host_residues.argtypes = [ci, ci, ctypes.c_double, ci, vp]
+        L.oz2_host_product_residues.argtypes = [ci, i64, vp, vp]
         L.oz2_status_string.restype = ctypes.c_char_p
         L.oz2_status_string.argtypes = [ci]
         _lib = L
@@ -280,6 +281,16 @@ def host_residues(num_moduli, kappa, a, shift):
     out = (ctypes.c_int8 * num_moduli)()
     _check(lib().oz2_host_residues(num_moduli, kappa, float(a), int(shift), out), "oz2_host_residues")
     return list(out)
+
+
+def host_product_residues(index, products):
+    """products: contiguous int32 numpy array -> uint8 array of the same shape"""
+    import numpy as np
+    assert products.dtype == np.int32 and products.flags.c_contiguous
+    out = np.empty(products.shape, dtype=np.uint8)
+    _check(lib().oz2_host_product_residues(index, products.size, products.ctypes.data, out.ctypes.data),
+           "oz2_host_product_residues")
+    return out
 
 
 OZ2_OPT_SHIFT_MODE, OZ2_OPT_PRODUCT_FORMAT, OZ2_OPT_GEMM_ALGORITHM, OZ2_OPT_KBLOCK, OZ2_OPT_BIT_SPLIT, OZ2_OPT_NONFINITE_CHECK = range(6)

@@ -745,6 +745,18 @@ int oz2_host_residues(int num_moduli, int kappa, double a, int shift, int8_t* re
   return OZ2_OK;
 }
 
+int oz2_host_product_residues(int index, int64_t count, const int32_t* products, uint8_t* res_out) {
+  if (index < 0 || index >= OZ2_MAX_N) return -1;
+  if (count < 0) return -2;
+  if (count == 0) return OZ2_OK;
+  if (!products) return -3;
+  if (!res_out) return -4;
+  int moduli[OZ2_MAX_N];
+  oz2_table_moduli(OZ2_MAX_N, moduli);
+  oz2_host_product_residues_impl(moduli[index], count, products, res_out);
+  return OZ2_OK;
+}
+
 const char* oz2_status_string(int status) {
   switch (status) {
     case OZ2_OK: return "success";

@@ -50,7 +50,9 @@ __device__ __forceinline__ void wait_vmcnt_unless_below(int i, int below) {
 //   With e chosen so that (2^23 + e) / p lies (p + 1) / (2 p) above an integer, the one rounding of
 //   fma(2^23 + e + x, 1/p, K) gives 2^23 + floor(x / p) + j (j a constant): the exact quotient plus one half stays
 //   1/(2p) away from every tie, further than 1/p's rounding moves it.  j is what makes e + x - (quotient bits) p congruent to
-//   x - floor(x / p) p modulo 256, i.e. the low byte of one 16-bit multiply-add is the residue.
+//   x - floor(x / p) p modulo 256, i.e. the low byte of one 16-bit multiply-add is the residue.  j is at least 1 (256 in the
+//   place of 0, which only 255 and 241 ask for): the exact sum may lie half a unit below 2^23 + floor(x / p) + j, and below
+//   2^23 floats are spaced by halves, so that j = 0 would leave 2^23 - 1/2 there and a residue of x < p one too small.
 //   256 needs no quotient (the low byte of x is the residue, and 256 times anything leaves it alone).
 //   OZ2_ACC_START is an inline constant of the MFMA (the bits of 1 / (2 pi)) whose lower 22 bits lie near their middle:
 //   sums of |c'| < 2^20.8, which is nearly all of them, agree in their upper ten bits whatever their sign, and the
@@ -78,10 +80,20 @@ inline Oz2FoldConsts oz2_fold_consts(int p) {
     unsigned inv = u;  // 1/p modulo 256: each step doubles the number of right bits (p p = 1 modulo 8)
     for (int i = 0; i < 3; ++i) inv *= 2u - u * inv;
     j = (e * inv) & 255u;
+    if (j == 0) j = 256;
   }
   c.base = 0x4b000000u + e + start;
   c.offset = (float)((1u << 23) - above - 1u + j);
   return c;
+}
+
+// The same for one value on the host, step by step (the 16-bit multiply-add of the device keeps the same low byte).
+inline uint8_t oz2_host_fold_residue(int32_t product, const Oz2FoldConsts& c) {
+  const unsigned acc = (unsigned)product + OZ2_ACC_START;
+  unsigned x = c.base;
+  for (int i = 0; i < 4; ++i) x += ((acc >> (8 * i)) & 255u) * ((c.kpack >> (8 * i)) & 255u);
+  const unsigned t = __builtin_bit_cast(unsigned, fmaf(__builtin_bit_cast(float, x), c.inv_p, c.offset));
+  return (uint8_t)(t * c.neg_p + x);
 }
 
 // Four byte sums x (the results of the dot product) -> four residues, one per byte: two of the 16-bit multiply-adds write

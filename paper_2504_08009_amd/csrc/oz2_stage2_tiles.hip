@@ -243,3 +243,8 @@ hipError_t oz2_launch_products(const Oz2Plan& plan, const Oz2Layout& lay, char* 
   if (tile == 256) return oz2_launch_stage2(plan, lay, ws, kblock, residue_u8, triangle, krange, check_flag, fin, st);
   return launch_tiles(tile, plan, lay, ws, m, n, triangle, krange, check_flag != 0, fin, st);
 }
+
+void oz2_host_product_residues_impl(int p, int64_t count, const int32_t* products, uint8_t* out) {
+  const Oz2FoldConsts c = oz2_fold_consts(p);
+  for (int64_t i = 0; i < count; ++i) out[i] = oz2_host_fold_residue(products[i], c);
+}

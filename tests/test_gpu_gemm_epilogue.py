@@ -54,3 +54,69 @@ def test_residues_of_products_over_the_int32_range(k, kblock):
     for t, p in enumerate(mods):
         ref = (k * b[t].astype(np.int64)[:, None] * a[t].astype(np.int64)[None, :]) % p
         assert np.array_equal(got[t], ref), "modulus %d" % p
+
+
+@pytest.mark.parametrize("k", [34960, 49416, 61440])
+@pytest.mark.parametrize("m,n", [(128, 128), (256, 512), (768, 768)])
+def test_residues_of_the_longest_sums_without_a_reduction(m, n, k):
+    """Up to 61440 terms reach the epilogue as one sum (up to 2^30 - 2^26).  The three results take the 64 x 64, the 128 x 128
+    and the 256 x 256 tiles of the products."""
+    mods, _ = oz.get_moduli(N)
+    print("longest sums: m=%d n=%d k=%d" % (m, n, k), flush=True)
+    ws = oz.Workspace(m, n, k, N, product_format=oz.OZ2_PRODUCT_RESIDUE_U8)
+    lay = oz.workspace_layout(m, n, k, N)
+    lo = np.array([-(p // 2) for p in mods])
+    hi = np.array([(p - 1) // 2 for p in mods])
+    rng = np.random.default_rng(k + m)
+
+    def vectors(count):
+        # (120 x -122 over 49416 terms modulo 255: one of the smallest byte sums there is)
+        v = np.concatenate([[120, -122, 127, -127, -128, 126, -126, 1], rng.permutation(256) - 128, rng.integers(-128, 128, count)])
+        return np.clip(v[None, :count], lo[:, None], hi[:, None]).astype(np.int8)
+
+    a, b = vectors(lay["m_pad"]), vectors(lay["n_pad"])
+    _fill(ws, lay, "a_planes", lay["m_pad"], a, k)
+    _fill(ws, lay, "b_planes", lay["n_pad"], b, k)
+    oz.oz2_stage2_gemm(m, n, k, N)
+    torch.cuda.synchronize()
+    got = ws.view(lay["c_planes"], N * lay["n_pad"] * lay["m_pad"], torch.uint8).view(N, lay["n_pad"], lay["m_pad"])
+    got = got[:, :n, :m].cpu().numpy()
+    for t, p in enumerate(mods):
+        ref = (k * b[t, :n].astype(np.int64)[:, None] * a[t, :m].astype(np.int64)[None, :]) % p
+        assert np.array_equal(got[t], ref), "modulus %d" % p
+    del ws
+
+
+@pytest.mark.parametrize("first", [True, False])
+def test_thin_products_of_the_longest_sums(first):
+    """Constant vectors of whole numbers with the residues 120, -122 ... modulo 255, long enough for sums near the INT32 limit, a
+    large operand against few vectors (oz2_thin.hip).  Every product is k a b, known as a Python integer."""
+    large, thin, k, moduli = 8192, 20, 49416, 14
+    _, kappa = oz.get_moduli(moduli, k)
+    rng = np.random.default_rng(11)
+    wanted = [120, -122, 127, -127, 126, -126, 1, 0]
+
+    def numbers(count):  # kappa bits each: the shifts are zero and nothing is truncated
+        v = 2 ** (kappa - 1) + 255 + rng.integers(0, 2 ** (kappa - 2), count)
+        r = np.array([wanted[i % 8] for i in range(count)])
+        return [int(x) for x in v - (v - r) % 255]
+
+    va, vb = numbers(large), numbers(thin)
+    assert all(2 ** (kappa - 1) <= x < 2**kappa for x in va + vb)
+    print("thin longest sums: first=%s" % first, flush=True)
+    dl = torch.tensor(va, dtype=torch.float64, device="cuda")
+    dt = torch.tensor(vb, dtype=torch.float64, device="cuda")
+    if first:  # A: large x k column-major, B: k x thin
+        A, B = dl.expand(k, large).contiguous(), dt[:, None].expand(thin, k).contiguous()
+        m, n = large, thin
+    else:
+        A, B = dt.expand(k, thin).contiguous(), dl[:, None].expand(large, k).contiguous()
+        m, n = thin, large
+    dC = torch.empty((n, m), dtype=torch.float64, device="cuda")
+    ws = oz.Workspace(m, n, k, moduli)
+    oz.oz2_dgemm(m, n, k, A.data_ptr(), m, B.data_ptr(), k, dC.data_ptr(), m, moduli)
+    torch.cuda.synchronize()
+    got = dC.cpu().numpy()
+    ref = np.array([[float(k * x * y) for x in va] for y in vb])
+    assert np.array_equal(got if first else got.T, ref)
+    del ws

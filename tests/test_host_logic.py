@@ -229,6 +229,30 @@ def test_host_residues_match_exact_integers(N, kappa):
 
 
 # ----------------------------------------------------------------------------------------------
+# Algorithm 1 line 7 in the epilogues of the products: the fold of an INT32 sum to its residue
+# ----------------------------------------------------------------------------------------------
+@pytest.mark.parametrize("index", range(26))
+def test_host_product_residues_over_all_legal_sums(index):
+    """Sums of up to 61440 products of two INT8 values.  The fold looks at the four bytes of the sum plus the accumulators'
+    start, so the cases are all words of such bytes at both ends of their range (which make the smallest and the largest
+    byte sums), random sums, and every sum near zero and near both extremes."""
+    p = orc.moduli(26)[index]
+    limit = 61440 * 2**14
+    ends = np.array(sorted(set(range(0, 34)) | {63, 64, 127, 128, 129, 191, 192} | set(range(222, 256))), dtype=np.int64)
+    top = ends[:, None] * 256 + ends[None, :]
+    words = (top.reshape(-1, 1) * 65536 + top.reshape(1, -1)[:, :: 7]).reshape(-1)
+    start = 0x3e22f983
+    rng = np.random.default_rng(index)
+    near = np.arange(-70000, 70001)
+    c = np.concatenate([words - start, rng.integers(-limit, limit + 1, 1 << 20), near, limit - 70000 + near, -limit + 70000 + near,
+                        [49416 * 120 * -122]])
+    c = np.ascontiguousarray(c[np.abs(c) <= limit].astype(np.int32))
+    got = oz.host_product_residues(index, c)
+    wrong = c[got != c.astype(np.int64) % p]
+    assert wrong.size == 0, (p, wrong.size, wrong[:5])
+
+
+# ----------------------------------------------------------------------------------------------
 # Algorithm 1 lines 7-11 on one element: residues of INT32 products -> double nearest to X
 # ----------------------------------------------------------------------------------------------
 def _crt_cases(N, rng):
