@@ -142,20 +142,21 @@ __device__ __forceinline__ void crt_rows(const void* __restrict__ cplanes, int64
 
 // The work of a launch is the columns' pieces of R rows, one after the other (per_col of them in a column), so that
 // short and ragged columns leave no lanes idle (a block per 2048 rows of a column before: one lane in eight worked at 256
-// rows, two thirds of them at 2777).
+// rows, two thirds of them at 2777).  A launch takes the columns j0 .. n - 1.
 template <int L, bool U8, int R>
 __global__ void __launch_bounds__(kThreads) crt_kernel(const void* __restrict__ cplanes, int64_t m_pad, int64_t n_pad,
                                                        const int* __restrict__ sa, const int* __restrict__ sb,
-                                                       double* __restrict__ C, int64_t ldc, int64_t m, int64_t n,
-                                                       const double alpha, const double beta,
+                                                       double* __restrict__ C, int64_t ldc, int64_t m, int64_t j0,
+                                                       int64_t n, const double alpha, const double beta,
                                                        const unsigned long long* __restrict__ skip_flag,
                                                        const int triangle, const int per_col, const FastDiv by_col,
                                                        const Oz2CrtConsts cc) {
   // a non-finite input was found in stage 1: C is left to the FP64 fallback (uniform over the grid)
   if (skip_flag != nullptr && *skip_flag != 0ull) return;
-  const int g = (int)(blockIdx.x * kThreads + threadIdx.x), j = g / by_col;
+  const int g = (int)(blockIdx.x * kThreads + threadIdx.x), q = g / by_col;
+  const int64_t j = j0 + q;
   if (j >= n) return;
-  crt_rows<L, U8, R>(cplanes, m_pad, n_pad, sa, sb, C, ldc, m, n, alpha, beta, triangle, cc, j, (int64_t)(g - j * per_col) * R);
+  crt_rows<L, U8, R>(cplanes, m_pad, n_pad, sa, sb, C, ldc, m, n, alpha, beta, triangle, cc, j, (int64_t)(g - q * per_col) * R);
 }
 
 // Products below 2^24 elements, where every launch counts: the blocks of the FP64 fallback ride in the same launch, behind those of
@@ -359,28 +360,32 @@ hipError_t oz2_launch_stage3(int64_t m, int64_t n, double alpha, double beta, do
     return hipGetLastError();
   }
   const int rows = residue_u8 ? 8 : 4;
-  const int64_t per_col = (m + rows - 1) / rows, threads = per_col * n;
-  if (threads >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+  const int64_t per_col = (m + rows - 1) / rows;
   const FastDiv by_col = fast_div((unsigned)per_col);
-  const dim3 grid((unsigned)((threads + kThreads - 1) / kThreads));
-  switch (plan.crt.L) {
+  // the pieces of a launch are counted below 2^31: results of 2^33 elements and more take several
+  const int64_t cols = (((int64_t)1 << 31) - kThreads) / per_col;
+  for (int64_t j0 = 0; j0 < n; j0 += cols) {
+    const int64_t j1 = n - j0 < cols ? n : j0 + cols;
+    const dim3 grid((unsigned)((per_col * (j1 - j0) + kThreads - 1) / kThreads));
+    switch (plan.crt.L) {
 #define OZ2_CASE(LL)                                                                                                    \
-  case LL:                                                                                                              \
-    if (residue_u8)                                                                                                     \
-      hipLaunchKernelGGL((crt_kernel<LL, true, 8>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa, sb, \
-                         C, ldc, m, n, alpha, beta, skip, triangle, (int)per_col, by_col, plan.crt);                    \
-    else                                                                                                                \
-      hipLaunchKernelGGL((crt_kernel<LL, false, 4>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa,    \
-                         sb, C, ldc, m, n, alpha, beta, skip, triangle, (int)per_col, by_col, plan.crt);                \
-    break;
-    OZ2_CASE(1)
-    OZ2_CASE(2)
-    OZ2_CASE(3)
-    OZ2_CASE(4)
-    OZ2_CASE(5)
+    case LL:                                                                                                              \
+      if (residue_u8)                                                                                                     \
+        hipLaunchKernelGGL((crt_kernel<LL, true, 8>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa, sb, \
+                           C, ldc, m, j0, j1, alpha, beta, skip, triangle, (int)per_col, by_col, plan.crt);               \
+      else                                                                                                                \
+        hipLaunchKernelGGL((crt_kernel<LL, false, 4>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa,    \
+                           sb, C, ldc, m, j0, j1, alpha, beta, skip, triangle, (int)per_col, by_col, plan.crt);           \
+      break;
+      OZ2_CASE(1)
+      OZ2_CASE(2)
+      OZ2_CASE(3)
+      OZ2_CASE(4)
+      OZ2_CASE(5)
 #undef OZ2_CASE
-    default:
-      return hipErrorInvalidValue;
+      default:
+        return hipErrorInvalidValue;
+    }
   }
   return hipGetLastError();
 }

@@ -340,6 +340,28 @@ def test_more_than_2_to_the_32_elements_of_c(N, algorithm):
     assert np.array_equal(got, ref)
 
 
+@pytest.mark.parametrize("beta", [0.0, 1.0])
+def test_more_than_2_to_the_33_elements_of_c_from_int32_planes(beta):
+    """2^31 threads of four rows each do not fit one launch of the CRT kernel: 2^20 x 8200 with INT32 planes.  Vectors of small
+    whole numbers, so every element of the outer product (added once to what C held, or replacing it) is known exactly."""
+    m, n, N = 1 << 20, 8200, 2
+    assert m // 4 * n > 1 << 31
+    a = (torch.arange(m, device="cuda") % 15 - 7).to(torch.float64)
+    b = (torch.arange(n, device="cuda") % 13 - 6).to(torch.float64)
+    C = torch.full((n, m), 3.0, dtype=torch.float64, device="cuda")
+    ws = oz.Workspace(m, n, 1, N, product_format=oz.OZ2_PRODUCT_INT32)
+    print("C of %d x %d = %.3f * 2^33 elements, INT32 planes, beta %g" % (m, n, m * n / 2.0**33, beta), flush=True)
+    oz.oz2_set_product_format(oz.OZ2_PRODUCT_INT32)
+    try:
+        oz.oz2_dgemm_ex("N", "N", m, n, 1, 1.0, a.data_ptr(), m, b.data_ptr(), 1, beta, C.data_ptr(), m, N)
+        torch.cuda.synchronize()
+    finally:
+        oz.oz2_set_product_format(oz.OZ2_PRODUCT_RESIDUE_U8)
+    del ws
+    for j in range(0, n, 1024):
+        assert torch.equal(C[j:j + 1024], b[j:j + 1024, None] * a[None, :] + 3.0 * beta), j
+
+
 def test_operand_planes_beyond_2_to_the_32_bytes():
     """An operand whose every residue plane is larger than 2^32 bytes (A: 66000 x 66000, 35 GB of FP64), so that a
     byte offset inside one plane does not fit 32 bits, against a narrow B.  A is drawn on the device with torch's
