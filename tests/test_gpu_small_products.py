@@ -117,6 +117,36 @@ def test_symmetric_update_with_more_than_2_24_elements(uplo, n, k):
     del ws
 
 
+@pytest.mark.parametrize("mode", [1, 2])
+@pytest.mark.parametrize("m,n,k", [(5, 300, 12288), (5, 300, 12289), (300, 200, 12353), (700, 300, 12300), (17, 700, 12345), (33, 40, 70001)])
+def test_few_long_vectors_in_the_other_shift_modes(m, n, k, mode):
+    """Inner dimensions around the line from which few vectors take separate launches for maxima, norms and shifts, an
+    infinity in the last place included."""
+    rng = np.random.default_rng(k + m)
+    ta, tb = [("N", "N"), ("T", "N"), ("N", "T"), ("T", "T")][(m + k) % 4]
+    print("few long vectors: mode %d m=%d n=%d k=%d op=%s%s" % (mode, m, n, k, ta, tb), flush=True)
+    A = _mat(rng, *((m, k) if ta == "N" else (k, m)))
+    B = _mat(rng, *((k, n) if tb == "N" else (n, k)))
+    opA, opB = np.asfortranarray(A.T if ta == "T" else A), np.asfortranarray(B.T if tb == "T" else B)
+    dA, dB, dC = _dev(A), _dev(B), _dev(np.zeros((m, n), order="F"))
+    ws = oz.Workspace(m, n, k, 14)
+    flags = ws.view(oz.workspace_layout(m, n, k, 14)["flags"], 1, torch.int64)
+    oz.oz2_set_shift_mode(mode)
+    try:
+        args = (ta, tb, m, n, k, 1.0, dA.data_ptr(), A.shape[0], dB.data_ptr(), B.shape[0], 0.0, dC.data_ptr(), m, 14)
+        oz.oz2_dgemm_ex(*args)
+        torch.cuda.synchronize()
+        assert int(flags.item()) == 0
+        assert np.array_equal(dC.cpu().numpy(), orc.dgemm(opA, opB, 14, mode=mode).C)
+        dB[-1, -1] = float("inf")
+        oz.oz2_dgemm_ex(*args)
+        torch.cuda.synchronize()
+        assert int(flags.item()) == 1 and not torch.isfinite(dC).all()
+    finally:
+        oz.oz2_set_shift_mode(0)
+    del ws
+
+
 @pytest.mark.parametrize("thin", [1, 32, 33, 97, 128])
 @pytest.mark.parametrize("ta,tb,first", [("N", "N", True), ("T", "N", True), ("N", "N", False), ("N", "T", False)])
 def test_thin_products_convert_the_large_operand_on_the_way(thin, ta, tb, first):
