@@ -104,6 +104,11 @@ struct Oz2ScanFinish {
   unsigned long long* flags;
 };
 
+// Products that take this many nanoseconds or more wait for the flag word, so that inputs with an infinity or a NaN skip
+// them: one launch of 2 to 4 us (whole calls with 16 moduli, finite inputs, with / without it, us: dtrmm 1024 x 16384 523 / 518,
+// dsyrk of order 4000, inner dimension 1000 273 / 270; with an infinity 2296 / 2666 and 1762 / 1951).
+#define OZ2_FINISH_FIRST_NS 100000
+
 // Kernel launchers.  Each returns hipSuccess or the launch error.
 // thin: 1 / 2 = only the second / first operand's planes are wanted (oz2_launch_thin_products converts the other one
 // itself); *large_two_level then tells how deep that one's elements are to be split.
@@ -125,6 +130,7 @@ hipError_t oz2_launch_strassen_crt(int64_t m, int64_t n, double alpha, double be
 // first launch.
 hipError_t oz2_gemm_setup();
 hipError_t oz2_stage1_setup();
+hipError_t oz2_launch_finish_scan(const Oz2ScanFinish& f, hipStream_t st);  // the flag word, in a launch of its own
 int oz2_gemm_cus();  // compute units, after the set-up
 // Bound of one wait of the GEMM's round synchronisation in polls (0 switches the synchronisation off), and the
 // clearing of its counters for a GEMM that no stage 1 precedes.
@@ -143,7 +149,8 @@ hipError_t oz2_launch_clear_sync(const Oz2Layout& lay, char* ws, hipStream_t st)
 // check_flag != 0: return at once on the device when stage 1 found a non-finite input.
 // triangle: 0 = general product; 1 / 2 = symmetric product op(A) op(A)^T (B's planes are A's), only the tiles of
 // the lower / upper triangle are computed
-// fin: what stage 1 left to this launch (see Oz2ScanFinish); the products are then formed whatever the flag will be.
+// fin: what stage 1 left to this launch (see Oz2ScanFinish).  With check_flag, short products are then formed whatever the
+// flag will be; long ones find out first.
 hipError_t oz2_launch_stage2(const Oz2Plan& plan, const Oz2Layout& lay, char* ws, int64_t kblock, int residue_u8,
                              int triangle, int krange, int check_flag, const Oz2ScanFinish& fin, hipStream_t st);
 // The same for an m x n result with the tiles that fit its size (oz2_stage2_tiles.hip): the large kernel above, or one with

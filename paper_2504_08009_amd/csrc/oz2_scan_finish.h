@@ -1,16 +1,29 @@
 // Shared by the kernels that follow a stage 1 without atomics (oz2_stage1.hip): each of its workgroups reports in a slot
 // of its own whether it saw an infinity or a NaN, and one workgroup of the next launch forms the flag word (1 when any
-// slot is set) and clears the counters of the GEMM's round synchronisation.
+// slot is set) and clears the counters of the GEMM's round synchronisation.  The other workgroups of that launch cannot
+// look at the flag word yet; where it pays (oz2_stage2.hip) they look at the slots.
 #ifndef OZ2_SCAN_FINISH_H
 #define OZ2_SCAN_FINISH_H
 
 #include "oz2_internal.h"
 
+// all threads of the workgroup: is any slot set?
+__device__ __forceinline__ int scan_found(const Oz2ScanFinish& f) {
+  unsigned long long any = 0ull;
+  unsigned i = threadIdx.x;
+  for (; i + 3 * blockDim.x < f.count; i += 4 * blockDim.x) {
+    unsigned long long v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = f.slots[i + u * blockDim.x];
+    any |= v[0] | v[1] | v[2] | v[3];
+  }
+  for (; i < f.count; i += blockDim.x) any |= f.slots[i];
+  return __syncthreads_or(any != 0ull);
+}
+
 // all threads of the workgroup
 __device__ __forceinline__ void finish_scan(const Oz2ScanFinish& f) {
-  int bad = 0;
-  for (unsigned i = threadIdx.x; i < f.count; i += blockDim.x) bad |= f.slots[i] != 0ull;
-  bad = __syncthreads_or(bad);
+  const int bad = scan_found(f);
   if (threadIdx.x < 32) f.flags[threadIdx.x] = (threadIdx.x == 0 && bad) ? 1ull : 0ull;
 }
 

@@ -687,6 +687,10 @@ __device__ __forceinline__ void convert_short(const ShortJob& j, const Oz2ConvCo
   }
 }
 
+// the flag word of the launch below, where the products are long enough to wait for it (OZ2_FINISH_FIRST_NS)
+constexpr int kFinishThreads = 1024;
+__global__ void __launch_bounds__(kFinishThreads) finish_scan_kernel(const Oz2ScanFinish f) { finish_scan(f); }
+
 template <int KA, int KB>
 __global__ void __launch_bounds__(kShortThreads) short_convert_kernel(const ShortJob ja, const ShortJob jb, const Oz2ConvConsts cc,
                                                                       unsigned long long* __restrict__ slots) {
@@ -789,6 +793,11 @@ hipError_t launch_convert(const Operand* ops, int nops, const int* kind, const O
 }
 
 }  // namespace
+
+hipError_t oz2_launch_finish_scan(const Oz2ScanFinish& f, hipStream_t st) {
+  hipLaunchKernelGGL(finish_scan_kernel, dim3(1), dim3(kFinishThreads), 0, st, f);
+  return hipGetLastError();
+}
 
 // Once per process, before any launch: the dynamic LDS limit of the one-pass conversion.
 hipError_t oz2_stage1_setup() {

@@ -89,6 +89,7 @@ struct GemmArgs {
   int krange;              // triangular operand: which k-tiles of a tile can be nonzero (see OZ2_KRANGE_*)
   const unsigned long long* skip_flag;  // if not null and nonzero on the device: the products are not needed
   Oz2ScanFinish fin;                    // reports of stage 1 that workgroup 0 turns into the flag word
+  int fin_stops;                        // 1: every workgroup looks at the reports and stops when there is one
   unsigned long long* xcd_sync;         // one counter per XCD (zero at launch), or null: no round sync
   int full_rounds;                      // rounds in which every workgroup slot has a tile
   int sync_spins;                       // bound of one wait of the round synchronisation, in polls of the counter
@@ -404,6 +405,10 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
   };
 
   prologue_loads(cur, 0);
+  if (g.fin_stops && scan_found(g.fin)) {  // (the reports arrive with the first copies)
+    wait_vmcnt<0>();
+    return;
+  }
   bool first = true;
   int round = 0;
   int stage = 0;  // stage that holds k-tile 0 of the current tile
@@ -680,6 +685,7 @@ hipError_t launch_gemm(const Oz2Layout& lay, char* ws, int num_moduli, const int
   // (with reports still to be turned into the flag by this launch, nobody can look at the flag yet)
   g.skip_flag = check_flag && !fin.slots ? reinterpret_cast<const unsigned long long*>(ws + lay.off_flags) : nullptr;
   g.fin = fin;
+  g.fin_stops = 0;
   g.c = reinterpret_cast<int*>(ws + lay.off_c);
   g.m_pad = lay.m_pad;
   g.n_pad = lay.n_pad;
@@ -755,6 +761,21 @@ hipError_t launch_gemm(const Oz2Layout& lay, char* ws, int num_moduli, const int
   // GEMM time with 448 rounds, -1.5 % with 64); with longer tiles the tighter form keeps the workgroups closer
   // together on their panels and is the faster one.  UINT8 epilogue only.
   const bool early = residue_u8 && g.xcd_sync != nullptr && g.ktiles <= 128;
+  // Stage 1 left the flag to this launch and non-finite inputs do not need these products (1.2 ms of 9 at 8192 x 8192 x 1024
+  // with 16 moduli).  A launch whose workgroups walk five tiles or more has each of them look at the reports first (16 moduli,
+  // finite inputs, whole calls with / without it, us: dsyrk of order 5000 378 / 376, 4096 x 4096 x 1024 440 / 440), but not
+  // more than 4096 of them; with one workgroup per tile (dtrmm 1024 x 16384 527 / 511) or more reports than that the flag word
+  // is formed ahead of the launch.
+  if (check_flag && fin.slots) {
+    const int64_t each = 720 * (krange == OZ2_KRANGE_ALL ? g.ktiles : (g.ktiles + 1) / 2) + 4500;
+    if (grid <= (unsigned)g_cus && total > 4 * (int64_t)g_cus && fin.count <= 4096) {
+      g.fin_stops = 1;
+    } else if ((triangle && !g.folded ? total / 2 : total) / g_cus * each >= OZ2_FINISH_FIRST_NS) {
+      if ((e = oz2_launch_finish_scan(fin, st)) != hipSuccess) return e;
+      g.fin = {nullptr, 0u, nullptr};
+      g.skip_flag = reinterpret_cast<const unsigned long long*>(ws + lay.off_flags);
+    }
+  }
   const dim3 grd(grid), thr(kThreads);
   // tiles walked in one k-block (the usual case) take the instantiation without the reduction between k-blocks
   const bool kblocked = g.ktiles_per_block < g.ktiles;

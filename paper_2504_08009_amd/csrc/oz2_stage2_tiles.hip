@@ -167,8 +167,9 @@ hipError_t set_lds() {
                              hipFuncAttributeMaxDynamicSharedMemorySize, kTileLds<MI, NI, NS, WGS>);
 }
 
+// flag: the flag word when the products are not needed once it is set, else null
 template <int MI, int NI, int NS, int WGS>
-hipError_t launch(TileArgs& g, int64_t m, int64_t n, int planes, hipStream_t st) {
+hipError_t launch(TileArgs& g, int64_t m, int64_t n, int planes, const unsigned long long* flag, hipStream_t st) {
   constexpr int TM = 64 * MI, TN = 64 * NI;
   g.tiles_m = (int)((m + TM - 1) / TM);
   g.tiles_n = (int)((n + TN - 1) / TN);
@@ -179,6 +180,14 @@ hipError_t launch(TileArgs& g, int64_t m, int64_t n, int planes, hipStream_t st)
   g.div_plane = fast_div((unsigned)(g.tiles_m * g.tiles_n));
   g.div_group = fast_div((unsigned)(kGroup * g.tiles_n));
   g.div_last = fast_div((unsigned)(g.tiles_m % kGroup ? g.tiles_m % kGroup : 1));
+  g.skip_flag = g.fin.slots ? nullptr : flag;
+  // (with reports still to be turned into the flag by this launch, nobody can look at the flag yet)
+  const int64_t each = 270 * (g.krange == OZ2_KRANGE_ALL ? g.ktiles : (g.ktiles + 1) / 2) + 600;
+  if (flag && g.fin.slots && (g.triangle ? total / 2 : total) / oz2_gemm_cus() * each >= OZ2_FINISH_FIRST_NS) {
+    if (hipError_t e = oz2_launch_finish_scan(g.fin, st); e != hipSuccess) return e;
+    g.fin = {nullptr, 0u, nullptr};
+    g.skip_flag = flag;
+  }
   hipLaunchKernelGGL((gemm_i8_tile_kernel<MI, NI, NS, WGS>), dim3((unsigned)g.chunk * 8), dim3(kThreads),
                      (kTileLds<MI, NI, NS, WGS>), st, g);
   return hipGetLastError();
@@ -209,10 +218,10 @@ static hipError_t launch_tiles(int tile, const Oz2Plan& plan, const Oz2Layout& l
   g.ktiles = (int)(lay.k_pad / BK);
   g.triangle = triangle;
   g.krange = krange;
-  g.skip_flag = check_flag && !fin.slots ? reinterpret_cast<const unsigned long long*>(ws + lay.off_flags) : nullptr;
   g.fin = fin;
+  const unsigned long long* flag = check_flag ? reinterpret_cast<const unsigned long long*>(ws + lay.off_flags) : nullptr;
   for (int t = 0; t < plan.N; ++t) g.fold[t] = oz2_fold_consts(plan.moduli[t]);
-  return tile == 64 ? launch<OZ2_TILE_64>(g, m, n, plan.N, st) : launch<OZ2_TILE_128>(g, m, n, plan.N, st);
+  return tile == 64 ? launch<OZ2_TILE_64>(g, m, n, plan.N, flag, st) : launch<OZ2_TILE_128>(g, m, n, plan.N, flag, st);
 }
 
 // Which kernel's tiles: 64 or 128 (this file) or 256 (oz2_stage2.hip).  64 x 64 when every tile gets a compute unit

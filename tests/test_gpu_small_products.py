@@ -94,6 +94,56 @@ def test_nonfinite_inputs_reach_the_fallback(m, n, k, where, bad):
     assert flag == 0 and np.array_equal(got, ref)
 
 
+@pytest.mark.parametrize("call,m,n,k", [("dgemm", 3000, 3000, 1000), ("dgemm", 8192, 8192, 64), ("dgemm", 30000, 3000, 1000),
+                                        ("dsyrk", 5000, 5000, 1000), ("dsyrk", 4096, 4096, 1000), ("dtrmm", 1000, 16384, 1000)])
+def test_long_products_are_not_formed_for_nonfinite_inputs(call, m, n, k):
+    """The one-pass conversion leaves the flag word to the launch after it.  Long products (walked by one workgroup per compute
+    unit, small tiles, more reports than every workgroup reads, one triangle, a triangular operand) find out before they start:
+    nothing is written over the product planes.  The next call, on finite values, forms them."""
+    N = 16
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(m + k)
+    A = torch.randn((k, m), dtype=torch.float64, device="cuda", generator=gen)  # m x k column-major
+    B = torch.randn((n, k), dtype=torch.float64, device="cuda", generator=gen)
+    print("%s: m=%d n=%d k=%d" % (call, m, n, k), flush=True)
+    ws = oz.Workspace(m, n, k, N)
+    lay = oz.workspace_layout(m, n, k, N)
+    planes = ws.view(lay["c_planes"], N * lay["n_pad"] * lay["m_pad"], torch.uint8)
+    flags = ws.view(lay["flags"], 1, torch.int64)
+
+    def run():
+        if call == "dtrmm":
+            C = B.clone()
+            oz.oz2_dtrmm("L", "L", "N", "N", m, n, 1.0, A.data_ptr(), m, C.data_ptr(), m, N)
+            ref = torch.matmul(B, torch.tril(A.t()).t().contiguous())
+        elif call == "dsyrk":
+            C = torch.zeros((n, n), dtype=torch.float64, device="cuda")
+            oz.oz2_dsyrk("L", "N", n, k, 1.0, A.data_ptr(), n, 0.0, C.data_ptr(), n, N)
+            ref = torch.triu(torch.matmul(A.t().contiguous(), A))
+        else:
+            C = torch.zeros((n, m), dtype=torch.float64, device="cuda")
+            oz.oz2_dgemm(m, n, k, A.data_ptr(), m, B.data_ptr(), k, C.data_ptr(), m, N)
+            ref = torch.matmul(B, A)
+        torch.cuda.synchronize()
+        return C, ref
+
+    kept = A[k - 1, m - 1].item()
+    A[k - 1, m - 1] = float("inf")  # last row of op(A)
+    planes.fill_(0x7f)
+    C, ref = run()
+    free = 8 * m * n if call == "dtrmm" else 0  # (the triangular product's fallback keeps its result at the region's front)
+    flag, untouched, last = int(flags.item()), bool((planes[free:] == 0x7f).all()), float(C[0, m - 1])
+    assert flag == 1 and untouched and not np.isfinite(last)
+    # (FP64 sums of k terms of order one on both sides: k (k + 1) 2^-53 < 1e-9 at most)
+    error = float((C[:, :m - 1] - ref[:, :m - 1]).abs().max())
+    assert error < 1e-9
+    A[k - 1, m - 1] = kept
+    C, ref = run()
+    flag, untouched, error = int(flags.item()), bool((planes[-planes.numel() // N:][:m] == 0x7f).all()), float((C - ref).abs().max())
+    assert flag == 0 and not untouched and error < 1e-9
+    del ws
+
+
 @pytest.mark.parametrize("n,k", [(4200, 64), (4200, 520), (4400, 520)])
 @pytest.mark.parametrize("uplo", ["L", "U"])
 def test_symmetric_update_with_more_than_2_24_elements(uplo, n, k):
