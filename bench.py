@@ -26,9 +26,21 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "gemm_hbm_traffic.txt")
 
 
 def gemm_source_hash():
+    """Of the GEMM's source file and of the repository's headers that it includes, each once, in the order met."""
     import hashlib
-    with open(GEMM_SOURCE, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    import re
+    digest, todo, seen = hashlib.sha256(), [GEMM_SOURCE], set()
+    while todo:
+        path = todo.pop(0)
+        if path in seen:
+            continue
+        seen.add(path)
+        with open(path, "rb") as f:
+            text = f.read()
+        digest.update(text)
+        for name in re.findall(rb'^\s*#include "([^"]+)"', text, flags=re.M):
+            todo.append(os.path.normpath(os.path.join(os.path.dirname(path), name.decode())))
+    return digest.hexdigest()[:16]
 
 
 def measured_traffic(key):

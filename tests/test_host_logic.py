@@ -152,8 +152,25 @@ def test_traffic_profile_belongs_to_the_gemm_source_in_the_tree():
     it was measured on; this fails when the kernel was edited and the counters were not taken again."""
     import bench
     tr = bench.measured_traffic("c4.strassen.u8")
-    assert tr is not None, "profiles/gemm_hbm_traffic.txt was taken on another oz2_stage2.hip: profile again"
+    assert tr is not None, "profiles/gemm_hbm_traffic.txt was taken on another oz2_stage2.hip or on other headers of it: profile again"
     assert tr["bytes"] > tr["algorithmic_GiB"] * 2**30 and bench.measured_traffic("no.such.entry") is None
+
+
+def test_traffic_profile_is_tied_to_the_headers_of_the_gemm_too(tmp_path, monkeypatch):
+    import shutil
+
+    import bench
+    src = tmp_path / "csrc"
+    shutil.copytree(os.path.dirname(bench.GEMM_SOURCE), src)
+    monkeypatch.setattr(bench, "GEMM_SOURCE", str(src / "oz2_stage2.hip"))
+    was = bench.gemm_source_hash()
+    for name, counts in [("oz2_stage2.hip", True), ("oz2_gemm.h", True), ("oz2_fast_div.h", True), ("oz2_scan_finish.h", True),
+                         ("oz2_internal.h", True), ("oz2_stage3.hip", False)]:
+        kept = (src / name).read_text()
+        (src / name).write_text(kept + "// edited\n")
+        assert (bench.gemm_source_hash() != was) == counts, name
+        (src / name).write_text(kept)
+    assert bench.gemm_source_hash() == was
 
 
 def test_workspace_layout_is_consistent():
