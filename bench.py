@@ -26,7 +26,8 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "gemm_hbm_traffic.txt")
 
 
 def gemm_source_hash():
-    """Of the GEMM's source file and of the repository's headers that it includes, each once, in the order met."""
+    """Of the GEMM's source file and of the headers beside it that it includes, each once, in the order met (the C interface,
+    which is elsewhere, holds declarations only)."""
     import hashlib
     import re
     digest, todo, seen = hashlib.sha256(), [GEMM_SOURCE], set()
@@ -38,8 +39,8 @@ def gemm_source_hash():
         with open(path, "rb") as f:
             text = f.read()
         digest.update(text)
-        for name in re.findall(rb'^\s*#include "([^"]+)"', text, flags=re.M):
-            todo.append(os.path.normpath(os.path.join(os.path.dirname(path), name.decode())))
+        for name in re.findall(rb'^\s*#include "([^"/]+)"', text, flags=re.M):
+            todo.append(os.path.join(os.path.dirname(path), name.decode()))
     return digest.hexdigest()[:16]
 
 
