@@ -1,6 +1,7 @@
 """Compile liboz2.so (HIP kernels + C ABI) for gfx950, in-tree."""
 import glob
 import os
+import re
 import subprocess
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -29,8 +30,59 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")) + glob.glob(os.path.join(CSRC, "*.cpp")))
 
 
+# The large GEMM keeps its accumulators in registers that its inline assembly names (oz2_stage2.hip): v112..v239 and
+# a128..a255.  That is sound only while the compiler keeps everything of its own out of them, which no language rule says.
+GEMM_SOURCE = "oz2_stage2.hip"
+GEMM_KERNEL = "gemm_i8_kernel"
+NAMED_VGPR, NAMED_AGPR = 112, 128
+
+
+def named_register_faults(assembly):
+    """Lines of the GEMM kernels' assembly in which the compiler has put a value of its own into an accumulator register or
+    into scratch memory, as (kernel, line) pairs; an empty list when all is well."""
+    faults, kernel, inside, kernels = [], None, False, 0
+    for line in assembly.splitlines():
+        label = re.match(r"(\w+):", line)
+        if label and GEMM_KERNEL in label.group(1):
+            kernel, kernels = label.group(1), kernels + 1
+        if kernel is None:
+            continue
+        if line.startswith(".Lfunc_end"):
+            kernel = None
+            continue
+        if "#ASMSTART" in line or "#ASMEND" in line:
+            inside = "#ASMSTART" in line
+            continue
+        code = line.split(";")[0].split("//")[0].strip()
+        if not code or code.startswith("."):
+            continue
+        if code.startswith(("scratch_", "buffer_load", "buffer_store")):
+            faults.append((kernel, code))
+        for kind, single, low, offset, high in re.findall(r"\b([va])(?:(\d+)\b|\[(\d+)(\+\d+)?(?::(\d+))?\])", code):
+            first = int(single or low)
+            last = int(high or first)
+            if kind == "v" and last < NAMED_VGPR:
+                continue
+            # a statement of the source: one whole tile of sixteen, or one register counted from a tile's first
+            base = NAMED_VGPR if kind == "v" else NAMED_AGPR
+            tile = first >= base and (first - base) % 16 == 0
+            if inside and tile and (offset or last == first + 15):
+                continue
+            faults.append((kernel, code))
+    if not kernels:
+        faults.append((GEMM_KERNEL, "not found"))
+    return faults
+
+
+def start_gemm_listing():
+    cmd = ["hipcc"] + HIP_FLAGS + EXTRA_FLAGS.get(GEMM_SOURCE, []) + ["--offload-device-only", "-S", os.path.join(CSRC, GEMM_SOURCE),
+                                                                     "-o", "-"]
+    return subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.DEVNULL), cmd
+
+
 def build(verbose=False):
     objs = []
+    listing, listing_cmd = start_gemm_listing()
     bdir = os.path.join(HERE, "_build")
     os.makedirs(bdir, exist_ok=True)
     procs = []
@@ -48,6 +100,13 @@ def build(verbose=False):
             raise RuntimeError("compile failed: %s\n%s" % (" ".join(cmd), text))
         if verbose and text.strip():
             print(text)
+    assembly = listing.communicate()[0].decode()
+    if listing.returncode:
+        raise RuntimeError("compile failed: %s" % " ".join(listing_cmd))
+    faults = named_register_faults(assembly)
+    if faults:
+        raise RuntimeError("%s: the compiler uses registers that the accumulators live in, or scratch memory:\n%s"
+                           % (GEMM_SOURCE, "\n".join("%s: %s" % f for f in faults[:20])))
     subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs)
     return LIB
 
