@@ -42,6 +42,24 @@ __device__ __forceinline__ void wait_vmcnt_unless_below(int i, int below) {
       : "memory", "scc");
 }
 
+// The triangle of `rows` rows of tiles (triangle 1: lower, 2: upper) laid out as a rectangle of half as many rows (rounded up)
+// and one column more (for an even number of them): row y holds the triangle's row rows - 1 - y and, behind it, the
+// short row that fills it up.  In: a tile of the rectangle; out: the tile of the triangle.
+__device__ __forceinline__ void unfold_triangle(int rows, int triangle, int& tm, int& tn) {
+  const int y = tm, x = tn, len = rows - y;
+  tm = x < len ? rows - 1 - y : ((rows & 1) ? y - 1 : y);
+  tn = x < len ? x : x - len;
+  if (triangle == 2) {
+    const int swap = tm;
+    tm = tn;
+    tn = swap;
+  }
+}
+inline void fold_triangle(int rows, int* tiles_m, int* tiles_n) {
+  *tiles_n = rows % 2 ? rows : rows + 1;
+  *tiles_m = (rows + 1) / 2;
+}
+
 // ---------------------------------------------------------------------------------------------------
 // Algorithm 1 line 7 in the epilogue of the products: the residue in [0, p) of an INT32 c', as a byte.
 //   acc = c' + OZ2_ACC_START modulo 2^32 (the accumulators start there).  As an unsigned word with bytes b3..b0,

@@ -85,7 +85,7 @@ struct GemmArgs {
   int ktiles;              // k_pad / BK
   int ktiles_per_block;    // k-tiles between modular reductions of the accumulators
   int triangle;            // 0: all tiles; 1: only tiles with tm >= tn (lower); 2: only tm <= tn (upper)
-  int folded;              // tile rows of the triangle when tiles_m x tiles_n is its rectangle (see decode_tile), else 0
+  int folded;              // tile rows of the triangle when tiles_m x tiles_n is its rectangle (unfold_triangle), else 0
   int krange;              // triangular operand: which k-tiles of a tile can be nonzero (see OZ2_KRANGE_*)
   const unsigned long long* skip_flag;  // if not null and nonzero on the device: the products are not needed
   Oz2ScanFinish fin;                    // reports of stage 1 that workgroup 0 turns into the flag word
@@ -272,18 +272,7 @@ __device__ __forceinline__ Tile decode_tile(const GemmArgs& g, int slot, int wv)
       tn = rr / kGroupM;
       tm = first_m + rr % kGroupM;
     }
-    if (g.folded != 0) {
-      // the triangle of g.folded rows of tiles laid out as a rectangle: row y holds the triangle's row g.folded - 1 - y and,
-      // behind it, the short row that fills it up
-      const int y = tm, x = tn, len = g.folded - y;
-      tm = x < len ? g.folded - 1 - y : ((g.folded & 1) ? y - 1 : y);
-      tn = x < len ? x : x - len;
-      if (g.triangle == 2) {
-        const int swap = tm;
-        tm = tn;
-        tn = swap;
-      }
-    }
+    if (g.folded != 0) unfold_triangle(g.folded, g.triangle, tm, tn);
   }
   // symmetric product: the other triangle of tiles is never needed
   if ((g.triangle == 1 && tm < tn) || (g.triangle == 2 && tm > tn)) return T;
@@ -699,10 +688,7 @@ hipError_t launch_gemm(const Oz2Layout& lay, char* ws, int num_moduli, const int
   // like those of a general product, one workgroup per compute unit (16 moduli, inner dimension 1024, whole calls: dsyrk of
   // order 5000 425 -> 393 us, of order 10000 1447 -> 1333).
   g.folded = triangle != 0 && !g.superblock ? g.tiles_m : 0;
-  if (g.folded) {
-    g.tiles_n = g.folded % 2 ? g.folded : g.folded + 1;
-    g.tiles_m = (g.folded + 1) / 2;
-  }
+  if (g.folded) fold_triangle(g.folded, &g.tiles_m, &g.tiles_n);
   const int64_t total = (int64_t)g.tiles_m * g.tiles_n * num_moduli;
   if (total > (int64_t)1 << 30) return hipErrorInvalidValue;
   g.total = (int)total;

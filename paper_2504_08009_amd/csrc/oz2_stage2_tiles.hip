@@ -32,7 +32,7 @@ struct TileArgs {
   uint8_t* c;
   int64_t m_pad, n_pad, k_pad;
   int tiles_m, tiles_n, total, chunk;  // tiles, and tiles per die
-  int ktiles, triangle, krange;        // as in the large kernel
+  int ktiles, triangle, folded, krange;  // as in the large kernel
   const unsigned long long* skip_flag;
   Oz2ScanFinish fin;
   FastDiv div_plane, div_group, div_last;
@@ -69,8 +69,7 @@ __global__ void __launch_bounds__(kThreads, WGS) gemm_i8_tile_kernel(const TileA
     tn = rr / kGroup;
     tm = first_m + rr % kGroup;
   }
-  if (g.triangle == 1 && (tm + 1) * TM <= tn * TN) return;
-  if (g.triangle == 2 && (tn + 1) * TN <= tm * TM) return;
+  if (g.folded != 0) unfold_triangle(g.folded, g.triangle, tm, tn);
   int kt_begin = 0, kt_end = g.ktiles;
   if (g.krange == OZ2_KRANGE_UPTO_ROW) kt_end = min(g.ktiles, (tm + 1) * (TM / BK));
   if (g.krange == OZ2_KRANGE_FROM_ROW) kt_begin = tm * (TM / BK);
@@ -173,6 +172,12 @@ hipError_t launch(TileArgs& g, int64_t m, int64_t n, int planes, const unsigned 
   constexpr int TM = 64 * MI, TN = 64 * NI;
   g.tiles_m = (int)((m + TM - 1) / TM);
   g.tiles_n = (int)((n + TN - 1) / TN);
+  // Symmetric product: only the tiles of the triangle are launched.  (With the other triangle's among them, returning at
+  // once, dies and compute units got uneven shares: dsyrk, whole calls, us, 14 moduli, order 900, inner dimension 8192
+  // 195 -> 169, 12000 264 -> 227; 16 moduli, order 1837, inner dimension 19821 1084 -> 939.)
+  static_assert(TM == TN, "the triangle of a square of tiles");
+  g.folded = g.triangle != 0 ? g.tiles_m : 0;
+  if (g.folded) fold_triangle(g.folded, &g.tiles_m, &g.tiles_n);
   const int64_t total = (int64_t)g.tiles_m * g.tiles_n * planes;
   if (total > (int64_t)1 << 30) return hipErrorInvalidValue;
   g.total = (int)total;
@@ -183,7 +188,7 @@ hipError_t launch(TileArgs& g, int64_t m, int64_t n, int planes, const unsigned 
   g.skip_flag = g.fin.slots ? nullptr : flag;
   // (with reports still to be turned into the flag by this launch, nobody can look at the flag yet)
   const int64_t each = 270 * (g.krange == OZ2_KRANGE_ALL ? g.ktiles : (g.ktiles + 1) / 2) + 600;
-  if (flag && g.fin.slots && (g.triangle ? total / 2 : total) / oz2_gemm_cus() * each >= OZ2_FINISH_FIRST_NS) {
+  if (flag && g.fin.slots && total / oz2_gemm_cus() * each >= OZ2_FINISH_FIRST_NS) {
     if (hipError_t e = oz2_launch_finish_scan(g.fin, st); e != hipSuccess) return e;
     g.fin = {nullptr, 0u, nullptr};
     g.skip_flag = flag;

@@ -167,6 +167,25 @@ def test_symmetric_update_with_more_than_2_24_elements(uplo, n, k):
     del ws
 
 
+@pytest.mark.parametrize("n", [1, 64, 65, 128, 129, 200, 256, 257, 320, 385, 600, 700])
+@pytest.mark.parametrize("uplo", ["L", "U"])
+def test_symmetric_update_by_small_tiles_of_one_triangle(uplo, n):
+    """Even and odd numbers of rows of 64 x 64 and 128 x 128 tiles, whose triangle is launched as a rectangle."""
+    k, N = 1101, 14
+    rng = np.random.default_rng(n)
+    A = _mat(rng, n, k)
+    C0 = np.asfortranarray(rng.standard_normal((n, n)))
+    dA, dC = _dev(A), _dev(C0)
+    ws = oz.Workspace(n, n, k, N)
+    ws.buf.fill_(0x5a)
+    print("dsyrk: n=%d k=%d uplo=%s" % (n, k, uplo), flush=True)
+    oz.oz2_dsyrk(uplo, "N", n, k, -1.0, dA.data_ptr(), n, 1.0, dC.data_ptr(), n, N)
+    torch.cuda.synchronize()
+    got = dC.cpu().numpy()
+    assert np.array_equal(got, orc.dsyrk(uplo, "N", -1.0, A, 1.0, C0, N))
+    del ws
+
+
 @pytest.mark.parametrize("mode", [1, 2])
 @pytest.mark.parametrize("m,n,k", [(5, 300, 12288), (5, 300, 12289), (300, 200, 12353), (700, 300, 12300), (17, 700, 12345), (33, 40, 70001)])
 def test_few_long_vectors_in_the_other_shift_modes(m, n, k, mode):
