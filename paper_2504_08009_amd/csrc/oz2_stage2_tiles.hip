@@ -235,7 +235,10 @@ static hipError_t launch_tiles(int tile, const Oz2Plan& plan, const Oz2Layout& l
 // 128 x 128 tiles, of which a compute unit holds three.  Whole calls, 128 against 256 (us): 14 moduli 512^3 24 / 29,
 // 700^3 34 / 37, 1024^3 51 / 49, 1024 x 1024 x 2048 87 / 80, 2048^3 212 / 200, 300 x 3000 x 1000 57 / 67, 16 moduli
 // 96 x 8192 x 8192 700 / 736, 4096 x 4096 x 1024 469 / 441; 64 against 128: 128^3 16.8 / 17.7, 256^3 18.4 / 19.4, 512^3
-// 25.1 / 24.4, 700^3 36 / 34.
+// 25.1 / 24.4, 700^3 36 / 34.  The time per k-tile of the small tiles grows from 200 k-tiles on, where their workgroups, which
+// nothing keeps on the same k-tiles, read twice the panels from beyond the L2 (whole calls, 128 against 256, us: 8 moduli
+// 2048 x 1147 x 9952 376 / 396, 20 moduli 376 x 3560 x 35718 2208 / 2237, 15 moduli 2948 x 270 x 22898 1078 / 1021, 8 moduli
+// 1030 x 3420 x 38226 2375 / 2236, 17 moduli 1509 x 700 x 53536 2129 / 1981).
 static int tile_size(int64_t m, int64_t n, int64_t k_pad, int num_moduli, int triangle, int krange) {
   const int64_t cus = oz2_gemm_cus();
   auto rounds = [&](int64_t tile) {
@@ -245,7 +248,8 @@ static int tile_size(int64_t m, int64_t n, int64_t k_pad, int num_moduli, int tr
   };
   if (rounds(64) <= 1) return 64;
   const int64_t ktiles = krange == OZ2_KRANGE_ALL ? k_pad / BK : (k_pad / BK + 1) / 2;
-  return rounds(128) * (270 * ktiles + 600) + 3000 < rounds(256) * (720 * ktiles + 4500) ? 128 : 256;
+  const int64_t per_ktile = 270 + (ktiles < 200 ? 0 : ktiles > 445 ? 35 : (ktiles - 200) / 7);
+  return rounds(128) * (per_ktile * ktiles + 600) + 3000 < rounds(256) * (720 * ktiles + 4500) ? 128 : 256;
 }
 
 hipError_t oz2_launch_products(const Oz2Plan& plan, const Oz2Layout& lay, char* ws, int64_t m, int64_t n, int64_t kblock,
