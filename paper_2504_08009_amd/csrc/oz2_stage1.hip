@@ -890,15 +890,18 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
   // first); its per-workgroup reports become the flag word in the conversion launch.  "Small": at most 2^25 elements
   // in both operands together (4096 x 4096 twice), where 16 vectors per workgroup are work enough for the chip
   // and the launches saved still count.  In the modes of Section 4.1 few long vectors keep the separate launches, which give a
-  // vector several workgroups: where their number is below an eighth (mode 1) or a tenth (mode 2) of their length, and that above
-  // 12288, the scan's workgroups are too few and too long (whole calls, 14 moduli, scan / separate launches, us, plain operands
-  // and with the first one transposed: mode 1 256 x 256 x 8192 103 / 102 and 85 / 99, x 12000 151 / 125 and 134 / 119, x 32768
-  // 378 / 265 and 344 / 253, 64 x 64 x 10300 130 / 119 and 105 / 114, 500 x 500 x 16384 293 / 254, 1000 x 1000 x 8192 252 / 258,
-  // x 16384 500 / 469 and 432 / 442; mode 2 256 x 256 x 4096 131 / 144 and 121 / 139, x 16384 340 / 308 and 325 / 306,
-  // 500 x 500 x 12000 353 / 328 and 328 / 328, 1000 x 1000 x 16384 692 / 696 and 659 / 678).
+  // vector several workgroups: where their number is below an eighth (mode 2 with two operands: a tenth) of their length, and that
+  // above a line, the scan's workgroups are too few and too long (whole calls, 14 moduli, scan / separate launches, us, plain
+  // operands and with the first one transposed: mode 1 256 x 256 x 8192 103 / 102 and 85 / 99, x 12000 151 / 125 and 134 / 119,
+  // x 32768 378 / 265 and 344 / 253, 64 x 64 x 10300 130 / 119 and 105 / 114, 500 x 500 x 16384 293 / 254, 1000 x 1000 x 8192
+  // 252 / 258, x 16384 500 / 469 and 432 / 442; mode 2 256 x 256 x 4096 131 / 144 and 121 / 139, x 10300 246 / 231 and 230 / 226,
+  // 500 x 500 x 10300 315 / 298 and 295 / 296, 1000 x 1000 x 16384 692 / 696 and 659 / 678; dsyrk, mode 1 order 500, 8192
+  // 138 / 121 and 109 / 116, 10000 169 / 141 and 144 / 130, order 900, 10000 218 / 194, mode 2 order 500, 10000 277 / 260 and
+  // 254 / 253, order 900, 12000 384 / 358).
   const int64_t vectors = lay.m_pad + (nops == 2 ? lay.n_pad : 0);
-  const bool few_and_long = shift_mode != OZ2_SHIFT_MAX && lay.k_pad > 12288 &&
-                            lay.k_pad >= vectors * (shift_mode == OZ2_SHIFT_CAUCHY_SCHWARZ ? 8 : 10);
+  const int line = nops == 1 ? 8192 : shift_mode == OZ2_SHIFT_CAUCHY_SCHWARZ ? 12288 : 10240;
+  const int64_t few = lay.k_pad / (nops == 2 && shift_mode == OZ2_SHIFT_INT8_PRODUCT ? 10 : 8);
+  const bool few_and_long = shift_mode != OZ2_SHIFT_MAX && lay.k_pad > line && vectors <= few;
   const bool scan = !strassen && vectors * lay.k_pad <= ((int64_t)1 << 25) && !few_and_long;
   // what the shifts are formed from: the budgets of the operands, or (INT8-product mode) first the exponents 5 - e of the
   // 6-bit bounds

@@ -187,7 +187,8 @@ def test_symmetric_update_by_small_tiles_of_one_triangle(uplo, n):
 
 
 @pytest.mark.parametrize("mode", [1, 2])
-@pytest.mark.parametrize("m,n,k", [(5, 300, 12288), (5, 300, 12289), (300, 200, 12353), (700, 300, 12300), (17, 700, 12345), (33, 40, 70001)])
+@pytest.mark.parametrize("m,n,k", [(5, 300, 12288), (5, 300, 12289), (300, 200, 12353), (700, 300, 12300), (17, 700, 12345), (33, 40, 70001),
+                                   (9, 200, 10240), (9, 200, 10241)])
 def test_few_long_vectors_in_the_other_shift_modes(m, n, k, mode):
     """Inner dimensions around the line from which few vectors take separate launches for maxima, norms and shifts, an
     infinity in the last place included."""
@@ -213,6 +214,25 @@ def test_few_long_vectors_in_the_other_shift_modes(m, n, k, mode):
         assert int(flags.item()) == 1 and not torch.isfinite(dC).all()
     finally:
         oz.oz2_set_shift_mode(0)
+    del ws
+
+
+@pytest.mark.parametrize("mode", [1, 2])
+@pytest.mark.parametrize("n,k,trans", [(70, 8192, "N"), (70, 8193, "T"), (300, 8200, "N"), (300, 12001, "T")])
+def test_symmetric_update_of_few_long_vectors_in_the_other_shift_modes(n, k, trans, mode):
+    rng = np.random.default_rng(k + n)
+    A = _mat(rng, *((n, k) if trans == "N" else (k, n)))
+    C0 = np.asfortranarray(rng.standard_normal((n, n)))
+    print("few long vectors: dsyrk mode %d n=%d k=%d %s" % (mode, n, k, trans), flush=True)
+    dA, dC = _dev(A), _dev(C0)
+    ws = oz.Workspace(n, n, k, 14)
+    oz.oz2_set_shift_mode(mode)
+    try:
+        oz.oz2_dsyrk("L", trans, n, k, 1.0, dA.data_ptr(), A.shape[0], 1.0, dC.data_ptr(), n, 14)
+        torch.cuda.synchronize()
+    finally:
+        oz.oz2_set_shift_mode(0)
+    assert np.array_equal(dC.cpu().numpy(), orc.dsyrk("L", trans, 1.0, A, 1.0, C0, 14, mode=mode))
     del ws
 
 
