@@ -518,6 +518,11 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
   });
   int kt = 0;
   int block_end = KBLOCKED ? g.ktiles_per_block : 0;
+  // The loop below starts 16 bytes past a multiple of 32.  Where it starts at one the same instructions take up to 4 % longer, in
+  // whole launches (stage 2 in the Strassen form, 16384 x 8192 x 12288, 24 moduli, ms, start modulo 64 = 0 / 16 / 32 / 48 / 56:
+  // 27.6 / 26.5 / 27.2 / 26.6 / 26.5; 8192 x 8192 x 12288, 18 moduli 9.78 / 9.51 / 9.72 / 9.50 / 9.52).  The 16 bytes are the
+  // instructions that the compiler puts between this statement and the loop.
+  asm volatile(".p2align 5");
   while (kt + 1 < ktiles) {
     step1(kt);
     ++kt;
