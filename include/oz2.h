@@ -335,7 +335,8 @@ int oz2_host_crt_element_digits(int num_moduli, const uint8_t* residues, double*
 
 /* Host-side evaluation of the device routine for lines 2-5 on one element: residues of
  * trunc(a * 2^shift) for all moduli (int8, num_moduli entries).  kappa tells the routine which of its
- * two splitting depths to use, as the kernels do.  No GPU is touched. */
+ * two splitting depths to use, as the kernels do.  Returns 0, a negative argument code, or -6 when the forms in which the
+ * kernels take the deeper split disagree.  No GPU is touched. */
 int oz2_host_residues(int num_moduli, int kappa, double a, int shift, int8_t* res_out);
 
 /* Host-side evaluation of line 7 as the epilogues of stage 2 take it (UINT8 residue planes): the residues in

@@ -741,8 +741,7 @@ int oz2_host_residues(int num_moduli, int kappa, double a, int shift, int8_t* re
   Oz2Plan plan;
   if (oz2_build_plan(num_moduli, 1, &plan) < 0) return -1;
   plan.conv.two_level = kappa > 75;  // same rule as the launcher: |x| < 2^kappa
-  oz2_host_residues_impl(plan.conv, a, shift, res_out);
-  return OZ2_OK;
+  return oz2_host_residues_impl(plan.conv, a, shift, res_out) ? OZ2_OK : -6;
 }
 
 int oz2_host_product_residues(int index, int64_t count, const int32_t* products, uint8_t* res_out) {

@@ -195,7 +195,7 @@ hipError_t oz2_launch_mfma_calibration(int workgroups, int iters, int random_ope
 hipError_t oz2_static_scratch(char** ptr, size_t* bytes);
 
 // Host instantiations of the device math (oz2_stage1.hip / oz2_stage3.hip), for unit tests.
-void oz2_host_residues_impl(const Oz2ConvConsts& c, double a, int shift, int8_t* out);
+bool oz2_host_residues_impl(const Oz2ConvConsts& c, double a, int shift, int8_t* out);
 void oz2_host_product_residues_impl(int p, int64_t count, const int32_t* products, uint8_t* out);
 double oz2_host_crt_impl(const Oz2CrtConsts& c, const int32_t* cprod);
 // the same element by the digit route of the matrix-core CRT kernel (res: num_moduli residues in [0, p_t))

@@ -107,6 +107,27 @@ OZ2_HD oz2_u16x2 oz2_residue_pair(const Oz2SplitPair<TWO_LEVEL>& s, const Oz2Con
   if (TWO_LEVEL) r = s.x2 * __builtin_bit_cast(oz2_u16x2, m.c64_h) + r;
   return q * __builtin_bit_cast(oz2_u16x2, m.neg_p_h) + r;
 }
+
+// The same of a two-level split for kernels that hold many elements per thread: the last 16 bits of x0 + x1 c32 are read off
+// that sum, modulus by modulus, in the place of those of x0 and x1 kept in registers; without KEEP_X2 those of x2 are
+// formed anew too.  One or two FP64 instructions more per element and modulus, 16 to 24 registers less: what decides whether four
+// waves share a SIMD or three.
+template <bool KEEP_X2>
+OZ2_HD oz2_u16x2 oz2_residue_pair_lean(const Oz2SplitPair<true>& s, const Oz2ConvMod& m) {
+  const double ta = fma(s.a.x1, m.c32, s.a.x0), tb = fma(s.b.x1, m.c32, s.b.x0);  // below 2^40
+  const double qa = fma(fma(s.a.x2, m.c64, ta), m.inv_p, OZ2_ROUND), qb = fma(fma(s.b.x2, m.c64, tb), m.inv_p, OZ2_ROUND);
+  oz2_u16x2 x2 = s.x2;
+  if (!KEEP_X2) {
+    double round = OZ2_ROUND;
+#ifdef __HIP_DEVICE_COMPILE__
+    asm volatile("" : "+s"(round));  // (otherwise the compiler forms them once and keeps them)
+#endif
+    x2 = __builtin_bit_cast(oz2_u16x2, oz2_low_halves(oz2_low_word(s.b.x2 + round), oz2_low_word(s.a.x2 + round)));
+  }
+  const oz2_u16x2 q = __builtin_bit_cast(oz2_u16x2, oz2_low_halves(oz2_low_word(qb), oz2_low_word(qa)));
+  const oz2_u16x2 r = x2 * __builtin_bit_cast(oz2_u16x2, m.c64_h) + oz2_halves(ta, tb);
+  return q * __builtin_bit_cast(oz2_u16x2, m.neg_p_h) + r;
+}
 OZ2_HD unsigned oz2_pack_pairs(oz2_u16x2 lo, oz2_u16x2 hi) {  // low bytes of four 16-bit values
   return oz2_even_bytes(__builtin_bit_cast(unsigned, hi), __builtin_bit_cast(unsigned, lo));
 }

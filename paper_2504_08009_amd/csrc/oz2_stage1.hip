@@ -450,6 +450,15 @@ constexpr int kConvARows = 64;
 constexpr int kConvAPitch = 65;  // doubles per row in LDS
 // KIND 0 / 1: residues of trunc(a 2^shift) with the one- / two-level split; KIND 2: the single plane of 6-bit
 // upper bounds ceil(|a| 2^shift) of Section 4.1 (written where plane 0 goes).
+// Sixteen elements per thread: with the two-level split 165 registers and three waves per SIMD in the usual form, 122 and four in
+// the lean one (stage 1, us, 22 moduli 176 x 10067 x 24807 2340 -> 2087, 24 moduli
+// 2653 x 6427 x 30545 2747 -> 2434, 22 moduli 4096^3 226 -> 233).
+__device__ __forceinline__ oz2_u16x2 conversion_residues(const Oz2SplitPair<false>& s, const Oz2ConvMod& m) {
+  return oz2_residue_pair<false>(s, m);
+}
+__device__ __forceinline__ oz2_u16x2 conversion_residues(const Oz2SplitPair<true>& s, const Oz2ConvMod& m) {
+  return oz2_residue_pair_lean<true>(s, m);
+}
 template <int KIND>
 __device__ __forceinline__ void convert_strided(const double* __restrict__ A, int64_t lda, int64_t m, int64_t k,
                                                 int64_t m_pad, int64_t k_pad, const int* __restrict__ sa,
@@ -492,8 +501,7 @@ __device__ __forceinline__ void convert_strided(const double* __restrict__ A, in
     unsigned v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-      v[u] = oz2_pack_pairs(oz2_residue_pair<TWO_LEVEL>(xs[2 * u], mod),
-                            oz2_residue_pair<TWO_LEVEL>(xs[2 * u + 1], mod));
+      v[u] = oz2_pack_pairs(conversion_residues(xs[2 * u], mod), conversion_residues(xs[2 * u + 1], mod));
     // written once, read by a later kernel: non-temporal store
     __builtin_nontemporal_store(v4u{v[0], v[1], v[2], v[3]}, reinterpret_cast<v4u*>(dst + (size_t)t * plane_stride));
   }
@@ -549,8 +557,7 @@ __device__ __forceinline__ void convert_contig(const double* __restrict__ B, int
     unsigned v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-      v[u] = oz2_pack_pairs(oz2_residue_pair<TWO_LEVEL>(xs[2 * u], mod),
-                            oz2_residue_pair<TWO_LEVEL>(xs[2 * u + 1], mod));
+      v[u] = oz2_pack_pairs(conversion_residues(xs[2 * u], mod), conversion_residues(xs[2 * u + 1], mod));
     // written once, read by a later kernel: non-temporal store
     __builtin_nontemporal_store(v4u{v[0], v[1], v[2], v[3]}, reinterpret_cast<v4u*>(dst + (size_t)t * plane_stride));
   }
@@ -980,16 +987,19 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
 }
 
 template <bool TWO_LEVEL>
-static void host_residues(const Oz2ConvConsts& c, double a, int shift, int8_t* out) {
+static bool host_residues(const Oz2ConvConsts& c, double a, int shift, int8_t* out) {
   const Oz2SplitPair<TWO_LEVEL> s = oz2_split_pair<TWO_LEVEL>(a, a, shift);
+  bool same = true;
   for (int t = 0; t < c.N; ++t) {
     const oz2_u16x2 r = oz2_residue_pair<TWO_LEVEL>(s, c.mod[t]);
     out[t] = (int8_t)(oz2_pack_pairs(r, r) & 0xff);
+    if constexpr (TWO_LEVEL) {
+      const oz2_u16x2 l = oz2_residue_pair_lean<true>(s, c.mod[t]), m = oz2_residue_pair_lean<false>(s, c.mod[t]);
+      same = same && l[0] == r[0] && l[1] == r[1] && m[0] == r[0] && m[1] == r[1];
+    }
   }
+  return same;
 }
-void oz2_host_residues_impl(const Oz2ConvConsts& c, double a, int shift, int8_t* out) {
-  if (c.two_level)
-    host_residues<true>(c, a, shift, out);
-  else
-    host_residues<false>(c, a, shift, out);
+bool oz2_host_residues_impl(const Oz2ConvConsts& c, double a, int shift, int8_t* out) {
+  return c.two_level ? host_residues<true>(c, a, shift, out) : host_residues<false>(c, a, shift, out);
 }
