@@ -450,14 +450,16 @@ constexpr int kConvARows = 64;
 constexpr int kConvAPitch = 65;  // doubles per row in LDS
 // KIND 0 / 1: residues of trunc(a 2^shift) with the one- / two-level split; KIND 2: the single plane of 6-bit
 // upper bounds ceil(|a| 2^shift) of Section 4.1 (written where plane 0 goes).
-// Sixteen elements per thread: with the two-level split 165 registers and three waves per SIMD in the usual form, 122 and four in
-// the lean one (stage 1, us, 22 moduli 176 x 10067 x 24807 2340 -> 2087, 24 moduli
-// 2653 x 6427 x 30545 2747 -> 2434, 22 moduli 4096^3 226 -> 233).
-__device__ __forceinline__ oz2_u16x2 conversion_residues(const Oz2SplitPair<false>& s, const Oz2ConvMod& m) {
-  return oz2_residue_pair<false>(s, m);
-}
-__device__ __forceinline__ oz2_u16x2 conversion_residues(const Oz2SplitPair<true>& s, const Oz2ConvMod& m) {
-  return oz2_residue_pair_lean<true>(s, m);
+// KIND 3: the two-level split, its residues in the lean form.  Sixteen elements per thread take 165 registers and three waves per
+// SIMD in the usual form, 122 and four in the lean one, which has two FP64 instructions more: the better one where the
+// operands stream from memory, not where a call is a chain of latencies (stage 1, us, usual / lean: 22 moduli 176 x 10067 x 24807
+// 2340 / 2087, 24 moduli 2653 x 6427 x 30545 2747 / 2434, 96 x 8192 x 8192 658 / 584, 22 moduli 4096^3 226 / 233, 2048^3 64 / 67).
+template <int KIND>
+__device__ __forceinline__ oz2_u16x2 conversion_residues(const Oz2SplitPair<(KIND & 1) != 0>& s, const Oz2ConvMod& m) {
+  if constexpr (KIND == 3)
+    return oz2_residue_pair_lean<true>(s, m);
+  else
+    return oz2_residue_pair<KIND == 1>(s, m);
 }
 template <int KIND>
 __device__ __forceinline__ void convert_strided(const double* __restrict__ A, int64_t lda, int64_t m, int64_t k,
@@ -492,7 +494,7 @@ __device__ __forceinline__ void convert_strided(const double* __restrict__ A, in
     store_bounds(mine, shift, dst);
     return;
   }
-  constexpr bool TWO_LEVEL = KIND == 1;
+  constexpr bool TWO_LEVEL = (KIND & 1) != 0;
   Oz2SplitPair<TWO_LEVEL> xs[8];
 #pragma unroll
   for (int u = 0; u < 8; ++u) xs[u] = oz2_split_pair<TWO_LEVEL>(mine[2 * u], mine[2 * u + 1], shift);
@@ -501,7 +503,7 @@ __device__ __forceinline__ void convert_strided(const double* __restrict__ A, in
     unsigned v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-      v[u] = oz2_pack_pairs(conversion_residues(xs[2 * u], mod), conversion_residues(xs[2 * u + 1], mod));
+      v[u] = oz2_pack_pairs(conversion_residues<KIND>(xs[2 * u], mod), conversion_residues<KIND>(xs[2 * u + 1], mod));
     // written once, read by a later kernel: non-temporal store
     __builtin_nontemporal_store(v4u{v[0], v[1], v[2], v[3]}, reinterpret_cast<v4u*>(dst + (size_t)t * plane_stride));
   }
@@ -548,7 +550,7 @@ __device__ __forceinline__ void convert_contig(const double* __restrict__ B, int
     store_bounds(mine, shift, dst);
     return;
   }
-  constexpr bool TWO_LEVEL = KIND == 1;
+  constexpr bool TWO_LEVEL = (KIND & 1) != 0;
   Oz2SplitPair<TWO_LEVEL> xs[8];
 #pragma unroll
   for (int u = 0; u < 8; ++u) xs[u] = oz2_split_pair<TWO_LEVEL>(mine[2 * u], mine[2 * u + 1], shift);
@@ -557,7 +559,7 @@ __device__ __forceinline__ void convert_contig(const double* __restrict__ B, int
     unsigned v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-      v[u] = oz2_pack_pairs(conversion_residues(xs[2 * u], mod), conversion_residues(xs[2 * u + 1], mod));
+      v[u] = oz2_pack_pairs(conversion_residues<KIND>(xs[2 * u], mod), conversion_residues<KIND>(xs[2 * u + 1], mod));
     // written once, read by a later kernel: non-temporal store
     __builtin_nontemporal_store(v4u{v[0], v[1], v[2], v[3]}, reinterpret_cast<v4u*>(dst + (size_t)t * plane_stride));
   }
@@ -767,9 +769,9 @@ void launch_norm(const Operand& o, hipStream_t st) {
 }
 
 // planes of one or two operands in one launch; kind 0 / 1: residue planes with the one- / two-level split,
-// kind 2: the bound plane
-hipError_t launch_convert(const Operand* ops, int nops, const int* kind, const Oz2ConvConsts& conv, const Oz2ScanFinish& fin,
-                          hipStream_t st) {
+// kind 2: the bound plane; large: operands that stream from memory (KIND 3 in the place of 1)
+hipError_t launch_convert(const Operand* ops, int nops, const int* kind, bool large, const Oz2ConvConsts& conv,
+                          const Oz2ScanFinish& fin, hipStream_t st) {
   ConvJob job[2] = {};
   int64_t total = 0;
   for (int x = 0; x < nops; ++x) {
@@ -789,10 +791,16 @@ hipError_t launch_convert(const Operand* ops, int nops, const int* kind, const O
     OZ2_CONV(2, 2);
   else if (ka == 0 && kb == 0)
     OZ2_CONV(0, 0);
+  else if (ka == 0 && large)
+    OZ2_CONV(0, 3);
   else if (ka == 0)
     OZ2_CONV(0, 1);
+  else if (kb == 0 && large)
+    OZ2_CONV(3, 0);
   else if (kb == 0)
     OZ2_CONV(1, 0);
+  else if (large)
+    OZ2_CONV(3, 3);
   else
     OZ2_CONV(1, 1);
 #undef OZ2_CONV
@@ -909,7 +917,8 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
   const int line = nops == 1 ? 8192 : shift_mode == OZ2_SHIFT_CAUCHY_SCHWARZ ? 12288 : 10240;
   const int64_t few = lay.k_pad / (nops == 2 && shift_mode == OZ2_SHIFT_INT8_PRODUCT ? 10 : 8);
   const bool few_and_long = shift_mode != OZ2_SHIFT_MAX && lay.k_pad > line && vectors <= few;
-  const bool scan = !strassen && vectors * lay.k_pad <= ((int64_t)1 << 25) && !few_and_long;
+  const bool large = vectors * lay.k_pad > ((int64_t)1 << 25);
+  const bool scan = !strassen && !large && !few_and_long;
   // what the shifts are formed from: the budgets of the operands, or (INT8-product mode) first the exponents 5 - e of the
   // 6-bit bounds
   int param[2];
@@ -952,7 +961,7 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
     // row maxima are its column maxima (those land in the unused column array).
     {
       const int bound[2] = {2, 2};
-      if (hipError_t e = launch_convert(ops, nops, bound, conv, fin, st); e != hipSuccess) return e;
+      if (hipError_t e = launch_convert(ops, nops, bound, false, conv, fin, st); e != hipSuccess) return e;
       fin = {nullptr, 0u, nullptr};
     }
     fill(ops[0].vaux, n_aux);
@@ -979,10 +988,10 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
   if (thin) {
     const int small = thin == 1 ? 1 : 0;
     *large_two_level = kinds[1 - small];
-    if (hipError_t e = launch_convert(ops + small, 1, kinds + small, conv, fin, st); e != hipSuccess) return e;
+    if (hipError_t e = launch_convert(ops + small, 1, kinds + small, large, conv, fin, st); e != hipSuccess) return e;
     return hipGetLastError();
   }
-  if (hipError_t e = launch_convert(ops, nops, kinds, conv, fin, st); e != hipSuccess) return e;
+  if (hipError_t e = launch_convert(ops, nops, kinds, large, conv, fin, st); e != hipSuccess) return e;
   return hipGetLastError();
 }
 
