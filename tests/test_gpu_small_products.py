@@ -316,3 +316,52 @@ def test_thin_products_at_the_ends_of_the_inner_dimension(k, ta):
     opA = np.asfortranarray(A.T if ta == "T" else A)
     assert np.array_equal(dC.t().cpu().numpy()[rows], orc.dgemm(opA, B, N, rows=rows, cols=np.arange(n)).C)
     del ws
+
+
+@pytest.mark.parametrize("first", [True, False])
+@pytest.mark.parametrize("mode,delta,N,k,ta,tb", [(1, 0, 16, 1101, "N", "T"), (2, 0, 16, 1101, "T", "N"), (1, 0, 16, 3000, "T", "T"),
+                                                  (2, 0, 15, 3000, "N", "N"), (0, 30, 21, 1101, "N", "N"), (0, -30, 21, 3000, "T", "N"),
+                                                  (1, 25, 21, 3000, "N", "N"), (2, -25, 21, 1101, "N", "T"), (0, 0, 16, 3000, "N", "T")])
+def test_thin_products_under_the_other_settings(mode, delta, N, k, ta, tb, first):
+    """The shift modes of Section 4.1, bit splits of which one operand needs the two-level split and the other does not, an update
+    of C with leading dimensions of its own, and operands beyond the 2^25 elements up to which one launch finds the shifts."""
+    large, thin = 12337, 40
+    m, n = (large, thin) if first else (thin, large)
+    rng = np.random.default_rng(100 * N + mode + k)
+    A = _mat(rng, *((m, k) if ta == "N" else (k, m)))
+    B = _mat(rng, *((k, n) if tb == "N" else (n, k)))
+    print("thin: mode %d split %d m=%d n=%d k=%d N=%d op=%s%s" % (mode, delta, m, n, k, N, ta, tb), flush=True)
+
+    def padded(x, more):  # column-major with `more` unused rows of NaN below each column
+        buf = torch.full((x.shape[1], x.shape[0] + more), float("nan"), dtype=torch.float64, device="cuda")
+        buf[:, :x.shape[0]] = torch.from_numpy(np.ascontiguousarray(x.T)).cuda()
+        return buf
+
+    dA, dB = padded(A, 3), padded(B, 2)
+    C0 = np.asfortranarray(rng.standard_normal((m, n)))
+    dC = padded(C0, 1)
+    ws = oz.Workspace(m, n, k, N)
+    lay = oz.workspace_layout(m, n, k, N)
+    ws.buf.fill_(0x7f)
+    pad = lay["m_pad"] if first else lay["n_pad"]
+    second_plane = ws.view(lay["a_planes" if first else "b_planes"] + pad * lay["k_pad"], pad * lay["k_pad"], torch.uint8)
+    oz.oz2_set_shift_mode(mode)
+    oz.oz2_set_bit_split(delta)
+    try:
+        oz.oz2_dgemm_ex(ta, tb, m, n, k, -0.5, dA.data_ptr(), dA.shape[1], dB.data_ptr(), dB.shape[1], 2.0, dC.data_ptr(), m + 1, N)
+        torch.cuda.synchronize()
+    finally:
+        oz.oz2_set_bit_split(0)
+        oz.oz2_set_shift_mode(0)
+    untouched = bool((second_plane == 0x7f).all())
+    assert untouched  # the large operand was converted on the way, its planes were not written
+    got = dC[:, :m].t().cpu().numpy()
+    assert bool(torch.isnan(dC[:, m]).all())
+    opA, opB = np.asfortranarray(A.T if ta == "T" else A), np.asfortranarray(B.T if tb == "T" else B)
+    pick = np.unique(np.concatenate([np.arange(66), np.arange(large - 70, large), rng.integers(0, large, 40)]))
+    rows, cols = (pick, np.arange(n)) if first else (np.arange(m), pick)
+    P = orc.dgemm(opA, opB, N, rows=rows, cols=cols, mode=mode, delta=delta).C
+    sub = C0[np.ix_(rows, cols)]
+    # alpha is a power of two and beta doubles: fma(alpha, P, beta C) rounds alpha P + beta C once, as this sum does
+    assert np.array_equal(got[np.ix_(rows, cols)], -0.5 * P + 2.0 * sub)
+    del ws
