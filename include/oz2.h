@@ -223,7 +223,8 @@ int oz2_context_dtrmm(oz2_context* ctx, char side, char uplo, char transa, char 
 /* Exceptional values (Section 3.1, closing remark: the emulation covers products of finite matrices; NaNs
  * and infinities need detection and a fallback to ordinary FP64 arithmetic).  With the check on (default),
  * stage 1 of oz2_dgemm / oz2_dgemm_ex records in the workspace whether A or B holds an infinity or a NaN
- * (free: the row / column maxima are taken on bit patterns); stage 3 then leaves C alone and an FP64 kernel
+ * (free: the row / column maxima are taken on bit patterns); the INT8 products are then left out (short ones with an
+ * inner dimension up to 1024 are formed all the same), stage 3 leaves C alone and an FP64 kernel
  * launched behind it forms C := alpha op(A) op(B) + beta C by the IEEE rules.  The decision is taken on the
  * device, the call does not synchronise; the workspace flag (oz2_workspace_layout, entry 9) tells afterwards
  * which way it went.  Signed zeros are not tracked: an emulated result that is zero is +0.  With the check
@@ -306,7 +307,10 @@ int oz2_calibrate_mfma(int workgroups, int iters, int random_operands, int* sink
 
 /* Inner-dimension block length for line 6.  INT32 accumulation is exact for fewer than 2^17 terms
  * (Section 3.1); longer inner dimensions are processed in blocks and the accumulators are reduced
- * modulo p_t between blocks.  kblock must be a positive multiple of 64 and at most 65536 (the default).
+ * modulo p_t between blocks.  kblock must be a positive multiple of 64 and at most 65536 (the default);
+ * with UINT8 residue planes a block is at most 61440 long whatever is set (the accumulators start at a
+ * constant there), so inner dimensions above 61440 -- in the Strassen form halves above it -- are reduced once or
+ * more.  C is the same for every block length.
  * With blocking active the INT32 planes hold a value congruent to the exact product modulo p_t.
  * Returns 0 or -1. */
 int oz2_set_kblock(int64_t kblock);

@@ -306,8 +306,8 @@ __global__ void __launch_bounds__(kScanThreads) vector_scan_kernel(const ScanJob
       lo = v0 < hi ? v0 : hi;
   }
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  // strided: element (v, l) at X[v + l ld]; 16 lanes along the vectors (128 contiguous bytes), 16 phases along them.
-  // otherwise: element (v, l) at X[l + v ld]; a wave takes four vectors in turn, its lanes run down the vector.
+  // strided: element (v, l) at X[v + l ld]; 16 lanes along the vectors (128 contiguous bytes), kPhases along them.
+  // otherwise: element (v, l) at X[l + v ld]; a wave takes kEach vectors in turn, its lanes run down the vector.
   const int vv = threadIdx.x & (kScanVecs - 1);
   // one value per vector in top[]: f(element, partial, vector) over a thread's share, then the partials joined
   auto reduce = [&](auto zero, auto&& f, auto&& join) {
@@ -352,7 +352,9 @@ __global__ void __launch_bounds__(kScanThreads) vector_scan_kernel(const ScanJob
     __shared__ int scale[kScanVecs];
     if (threadIdx.x < kScanVecs) scale[threadIdx.x] = mx ? 19 - exponent_of_bits(mx) : 0;
     __syncthreads();
-    // (a thread's sum is exact: vectors of at most 2^16 elements here, at most 2^12 terms of at most 2^40)
+    // (a thread's sum is exact: at most 2^25 elements in at least 256 padded vectors, so vectors of at most 2^17 elements, of which a
+    // thread adds at most 2^17 / kPhases = 2^12 terms of at most 2^40)
+    static_assert(kPhases >= 32, "2^12 terms of a vector of 2^17 elements");
     reduce(0.0, [&](double x, double own, int w) { return own + scaled_ceil_sq(x, scale[w]); },
            [](unsigned long long a, unsigned long long b) { return a + b; });
     norm = threadIdx.x < kScanVecs ? top[threadIdx.x] : 0ull;

@@ -24,7 +24,7 @@
 // fills up and stalls MFMA issue.
 //
 // INT32 accumulation is exact for fewer than 2^17 terms (Section 3.1).  For longer inner dimensions the
-// accumulators are reduced modulo p_t every `kblock` bytes of k (kblock <= 65536), which keeps them below
+// accumulators are reduced modulo p_t every `kblock` bytes of k (kblock <= 65536, UINT8 residues: 61440), which keeps them below
 // 2^31 and leaves the residue of the product unchanged.
 //
 // The 1-D grid is remapped so that the 32 workgroups resident on an XCD (workgroup id mod 8) form an
@@ -110,7 +110,8 @@ __device__ __forceinline__ int reduce_mod(int c, int p, float inv_p) {
 // ---- The 256 accumulators of a lane live in registers by name: MFMA tile (x, y) of the wave's 4 x 4, T = x + 4 y, in
 // the ordinary registers v[112 + 16 T ...] for T < kVgprTiles and in the accumulation registers a[16 T ...] for the
 // others.  An ordinary instruction reads the former directly, the latter only through a move of eight cycles, and
-// of the 256 ordinary registers the kernel's own code needs fewer than 112 (amdgpu_num_vgpr keeps the compiler to
+// of the 256 ordinary registers the kernel's own code needs fewer than 112 (build.py refuses a build in which the compiler
+// uses a register named here, or scratch memory; amdgpu_num_vgpr keeps it to
 // them); every statement below names what it writes.  (As variables the accumulators were copied through ordinary
 // registers and scratch memory wherever the main loop meets the code around it: up to 256 moves per tile and 20 to 1200
 // bytes of scratch per lane, depending on the form of the loop.)
@@ -568,7 +569,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
     // Bound by instruction issue, one wave per SIMD: 3.25 instructions of 5 cycles per element, and the 8-cycle move for
     // the half that sits in accumulation registers (before: seven, the move for all, and 2000 cycles to clear the
     // accumulators for the next tile).  With the stores left to drain and the tile decoding on the scalar unit the
-    // work between two main loops went from 13000 to 7500 cycles: GEMM of 18 moduli at 8192 x 8192 x 1024 1.31 -> 1.19 ms
+    // work between two main loops went from 13000 to 7500 cycles: GEMM of 18 moduli at 8192 x 8192 x 1024 1.31 -> 1.20 ms
     // (2.08 POP/s), of 16 at 4096^3 0.87 -> 0.85, of 14 at 2048^3 0.115 -> 0.108, of 26 at 8192^3 10.67 -> 10.50.
     // the wave's corner of the tile (uniform over the wave) and the lane's own offset from it (column lane % 32,
     // rows 16 half ..: below 2^32, m_pad is below 2^27)

@@ -200,7 +200,7 @@ __global__ void __launch_bounds__(kThreads) thin_products_kernel(const ThinArgs 
 // byte that conversion and products move between them otherwise (8 read, N written, N read per element of the large
 // operand, 4.3 TB/s).  Whole calls, with planes against without (us): 16 moduli 8192 x 96 x 8192 680 / 406, 96 x 8192 x 8192
 // 698 / 429, 8192 x 32 x 8192 671 / 353, 16384 x 64 x 2048 374 / 208; 14 moduli 64 x 15484 x 9445 1391 / 910; 18 moduli
-// 8192 x 96 x 8192 739 / 632; 22 moduli 8192 x 96 x 8192 906 / 739.
+// 8192 x 96 x 8192 739 / 605; 22 moduli 8192 x 96 x 8192 906 / 764.
 int oz2_thin_applies(int64_t m, int64_t n, const Oz2Plan& plan, const Oz2Layout& lay, int64_t kblock) {
   const int64_t thin = m < n ? m : n, large = m < n ? n : m;
   // (up to 1024 the one-pass conversion reads the operand once, which is the better half of this)

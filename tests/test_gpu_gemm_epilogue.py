@@ -1,7 +1,9 @@
-"""Residues that the GEMM epilogue leaves (Algorithm 1 lines 6-7) for products over the whole INT32 range, all moduli.
+"""Residues that the GEMM epilogues leave (Algorithm 1 lines 6-7), all moduli.
 
-Rows of A' and columns of B' are constant, so element (i, j) of C' is k a_i b_j exactly: from 0 to the extremes of
-65536 terms of 128 * 128 and -128 * 127.  Planes are written into the workspace directly; whole numbers, no tolerance."""
+Rows of A' and columns of B' are constant, so element (i, j) of C' is k a_i b_j exactly.  The first test covers one to five k-tiles,
+reductions between blocks of one k-tile, and an inner dimension of 65536, of which the epilogue sees what a reduction after
+61440 terms leaves and 4096 terms more; the others the longest sums that an epilogue can see, 61440 terms of 128 * 128 and
+-128 * 127, in each of the kernels.  Planes are written into the workspace directly; whole numbers, no tolerance."""
 import numpy as np
 import pytest
 
