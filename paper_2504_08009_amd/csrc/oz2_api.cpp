@@ -55,7 +55,9 @@ std::mutex g_setup_mu;
 bool g_setup_done = false;
 bool ensure_setup() {
   std::lock_guard<std::mutex> lock(g_setup_mu);
-  if (!g_setup_done) g_setup_done = oz2_gemm_setup() == hipSuccess && oz2_gemm_tiles_setup() == hipSuccess && oz2_stage1_setup() == hipSuccess;
+  if (!g_setup_done)
+    g_setup_done = oz2_gemm_setup() == hipSuccess && oz2_gemm_tiles_setup() == hipSuccess && oz2_stage1_setup() == hipSuccess &&
+                   oz2_thin_setup() == hipSuccess;
   return g_setup_done;
 }
 

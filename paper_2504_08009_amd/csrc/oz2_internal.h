@@ -159,6 +159,7 @@ hipError_t oz2_gemm_tiles_setup();
 hipError_t oz2_launch_products(const Oz2Plan& plan, const Oz2Layout& lay, char* ws, int64_t m, int64_t n, int64_t kblock,
                                int residue_u8, int triangle, int krange, int check_flag, const Oz2ScanFinish& fin,
                                hipStream_t st);
+hipError_t oz2_thin_setup();
 // Thin general products (oz2_thin.hip): conversion of the large operand and products in one kernel.  oz2_thin_applies: 0 no,
 // 1 the first operand is the large one, 2 the second.
 int oz2_thin_applies(int64_t m, int64_t n, const Oz2Plan& plan, const Oz2Layout& lay, int64_t kblock);

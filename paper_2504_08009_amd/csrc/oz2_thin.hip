@@ -4,14 +4,18 @@
 // The residue planes of the large operand are N bytes per element that the conversion writes and the products read once:
 // at 8192 x 96 x 8192 with 16 moduli the 1.1 GB of planes cost two thirds of the call.  Here a workgroup takes 64 vectors
 // of the large operand and a group of up to eight moduli, converts a k-tile of 64 inner positions at a time in registers,
-// passes the residues through LDS (64 rows x 64 bytes per modulus, double buffered) and multiplies them with the planes
+// passes the residues through LDS (64 rows x 64 bytes per modulus) and multiplies them with the planes
 // of the thin operand, which come straight from the L2 in the layout an MFMA operand has: wave w works for modulus w of the
 // group and nobody else needs those bytes.  The large operand is read once per group (the groups of the same 64 vectors
 // run on the same die at the same time and find it in the L2); its planes do not exist.
-// Bound by the conversion's vector instructions (some 50 per element and group of eight moduli: 3700 of the 4500 cycles of
-// a k-tile).  The loop has no branch that loads, and its loads stay where they are written: left to itself the compiler moves
-// them down to their use, where their latency shows (16 moduli 8192 x 96 x 8192 475 -> 406 us, 96 x 8192 x 8192 537 -> 429,
-// 22 moduli 8192 x 128 x 8192 1479 -> 824).
+// Bound by the conversion's vector instructions and by waits: 336 instructions of 4.5 cycles per wave and k-tile, two waves per
+// SIMD, are 3000 of its 4400 cycles (16 moduli 8192 x 96 x 8192).  The loop has no branch that loads, and its loads stay where
+// they are written: left to itself the compiler moves them down to their use, where their latency shows (475 -> 406 us a call
+// there).  Two k-tiles share a barrier, the large operand is fetched two k-tiles ahead into the registers just split, and the
+// products stand between the steps of the conversion, which the matrix cores work beside (a k-tile per barrier, products ahead of the
+// conversion / this, us: 16 moduli 8192 x 96 x 8192 389 / 366, 96 x 8192 x 8192 419 / 399, 8192 x 32 x 8192 348 / 327, 18 moduli
+// 8192 x 96 x 8192 575 / 520, 14 moduli 64 x 15484 x 9445 905 / 818).  The order of the two fetches matters: with the large operand's
+// behind the thin one's 96 x 8192 x 8192 takes 450.
 //
 // 512 threads, eight waves, two per SIMD: 32 NI accumulators per lane (NI = 32-vector tiles of the thin operand), ordinary
 // registers (build.py builds this file with -amdgpu-mfma-vgpr-form).
@@ -33,6 +37,8 @@ constexpr int BK = OZ2_TILE_K;
 constexpr int kBlk = OZ2_TILE_M;        // plane layout: blocks of 256 rows x 64 bytes
 constexpr int kTileBytes = kRows * BK;  // one modulus in LDS
 constexpr int kMaxThin = 128;
+constexpr int thin_lds_bytes(bool paired) { return (paired ? 4 : 2) * kGroup * kTileBytes; }  // k-tiles in LDS
+constexpr int kMfmaSteps = 8;           // steps of a k-tile's conversion that carry its products
 
 struct ThinArgs {
   const double* X;        // large operand: element (v, l) at X[v + l ld] (strided) or X[l + v ld]
@@ -51,10 +57,11 @@ struct ThinArgs {
   Oz2FoldConsts fold[OZ2_MAX_N];
 };
 
-template <int KIND, int NI, bool BIG_A>
+template <int KIND, int NI, bool BIG_A, bool PAIRED>
 __global__ void __launch_bounds__(kThreads) thin_products_kernel(const ThinArgs g) {
   constexpr bool TWO_LEVEL = KIND == 1;
-  __shared__ __attribute__((aligned(1024))) char lds[2][kGroup][kTileBytes];
+  extern __shared__ __attribute__((aligned(1024))) char thin_lds[];
+  auto lds = reinterpret_cast<char(*)[kGroup][kTileBytes]>(thin_lds);
   if (g.skip_flag != nullptr && *g.skip_flag != 0ull) return;
   const int item = (int)(blockIdx.x & 7) * g.chunk + (int)(blockIdx.x >> 3);  // workgroup i of a launch runs on die i % 8
   if (item >= g.total) return;
@@ -93,12 +100,16 @@ __global__ void __launch_bounds__(kThreads) thin_products_kernel(const ThinArgs 
   Oz2ConvMod mods[kGroup];  // in scalar registers throughout (loaded per k-tile, every modulus waited for its constants)
 #pragma unroll
   for (int tt = 0; tt < kGroup; ++tt) mods[tt] = g.conv.mod[tt < count ? t0 + tt : t0];
-  auto convert = [&](const double (&d)[8], int buf) {
+  // one k-tile in twelve steps: four that split two elements each, one per modulus; after(step) is called between them
+  auto convert = [&](const double (&d)[8], int buf, auto&& after) {
     Oz2SplitPair<TWO_LEVEL> xs[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) xs[u] = oz2_split_pair<TWO_LEVEL>(d[2 * u], d[2 * u + 1], shift);
+    for (int u = 0; u < 4; ++u) {
+      xs[u] = oz2_split_pair<TWO_LEVEL>(d[2 * u], d[2 * u + 1], shift);
+      after(u);
+    }
 #pragma unroll
-    for (int tt = 0; tt < kGroup; ++tt)
+    for (int tt = 0; tt < kGroup; ++tt) {
       if (tt < count) {
         v2u w;
 #pragma unroll
@@ -107,6 +118,8 @@ __global__ void __launch_bounds__(kThreads) thin_products_kernel(const ThinArgs 
                                 oz2_residue_pair<TWO_LEVEL>(xs[2 * h + 1], mods[tt]));
         *reinterpret_cast<v2u*>(&lds[buf][tt][put]) = w;
       }
+      after(4 + tt);
+    }
   };
 
   // ---- products: wave w for modulus t0 + w
@@ -130,30 +143,21 @@ __global__ void __launch_bounds__(kThreads) thin_products_kernel(const ThinArgs 
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[x][y][e] = (int)OZ2_ACC_START;
 
-  // k-tile kt is multiplied while kt + 1 is converted and kt + 2 is on its way from memory.  No branches: where paths that
-  // load join, or a loop-carried value is copied, the loads in flight are waited for.
-  auto iteration = [&](int kt, int buf, auto whole, const double (&now)[8], double (&later)[8]) {
-    fetch(kt + 2, whole, later);
-    asm volatile("" ::: "memory");  // (the compiler would move the loads down to where their results are needed)
-    const char* base = lds[buf][works ? wv : 0] + (lane & 31) * BK;
-    v4i fb[2][2];
+  auto fragments = [&](int slot, v4i (&fb)[2][2]) {
+    const char* base = lds[slot][works ? wv : 0] + (lane & 31) * BK;
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
       for (int x = 0; x < 2; ++x)
         fb[s][x] = *reinterpret_cast<const v4i*>(base + x * 32 * BK + (((2 * s + half) ^ swz) << 4));
+  };
+  auto multiply = [&](const v4i (&fb)[2][2], int from, int to) {
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int y = 0; y < NI; ++y)
-#pragma unroll
-        for (int x = 0; x < 2; ++x)
-          acc[x][y] = BIG_A ? __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[s][x], ft[s][y], acc[x][y], 0, 0, 0)
-                            : __builtin_amdgcn_mfma_i32_32x32x32_i8(ft[s][y], fb[s][x], acc[x][y], 0, 0, 0);
-    fetch_thin(kt + 1 < ktiles ? kt + 1 : ktiles - 1);
-    asm volatile("" ::: "memory");
-    convert(now, buf ^ 1);
-    __syncthreads();  // the next k-tile is complete, and nobody reads this one's buffer any more
+    for (int q = from; q < to; ++q) {
+      const int s = q / (2 * NI), y = q / 2 % NI, x = q % 2;
+      acc[x][y] = BIG_A ? __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[s][x], ft[s][y], acc[x][y], 0, 0, 0)
+                        : __builtin_amdgcn_mfma_i32_32x32x32_i8(ft[s][y], fb[s][x], acc[x][y], 0, 0, 0);
+    }
   };
   const std::true_type whole;
   const std::false_type part;
@@ -161,17 +165,69 @@ __global__ void __launch_bounds__(kThreads) thin_products_kernel(const ThinArgs 
   fetch(0, whole, d0);  // (the inner dimension is above 1024)
   fetch(1, whole, d1);
   fetch_thin(0);
-  convert(d0, 0);
-  __syncthreads();
-  __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): what is pending here would be waited for in every round of the loop
-  int kt = 0;  // two at a time; what lies beyond the last k-tile is zero
-  for (; (int64_t)(kt + 4) * BK <= g.k; kt += 2) {
-    iteration(kt, 0, whole, d1, d0);
-    iteration(kt + 1, 1, whole, d0, d1);
-  }
-  for (; kt < ktiles; kt += 2) {
-    iteration(kt, 0, part, d1, d0);
-    iteration(kt + 1, 1, part, d0, d1);
+  convert(d0, 0, [](int) {});
+  int kt = 0;  // two k-tiles in a round; what lies beyond the last one is zero
+  if constexpr (PAIRED) {
+    // k-tiles kt and kt + 1 are multiplied while kt + 2 and kt + 3 are converted and kt + 4 and kt + 5 are on their way from
+    // memory, one barrier for the two.  No branches: where paths that load join, or a loop-carried value is copied, the loads
+    // in flight are waited for.
+    auto iteration = [&](int kt, auto whole, double (&d)[8]) {
+      v4i fb[2][2];
+      fragments(kt & 3, fb);
+      convert(d, (kt + 2) & 3, [&](int step) {
+        if (step < kMfmaSteps) {
+          __builtin_amdgcn_sched_barrier(0);
+          multiply(fb, 4 * NI * step / kMfmaSteps, 4 * NI * (step + 1) / kMfmaSteps);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if (step == 3) {  // the elements are split: their registers take the next ones
+          fetch(kt + 4, whole, d);
+          asm volatile("" ::: "memory");  // (the compiler would move the loads down to where their results are needed)
+        }
+        if (step == kMfmaSteps - 1) {
+          fetch_thin(kt + 1 < ktiles ? kt + 1 : ktiles - 1);
+          asm volatile("" ::: "memory");
+        }
+      });
+    };
+    fetch(2, whole, d0);
+    convert(d1, 1, [](int) {});
+    fetch(3, whole, d1);
+    __syncthreads();
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): what is pending here would be waited for in every round of the loop
+    for (; (int64_t)(kt + 6) * BK <= g.k; kt += 2) {
+      iteration(kt, whole, d0);
+      iteration(kt + 1, whole, d1);
+      __syncthreads();  // the next two k-tiles are complete, and nobody reads these two any more
+    }
+    for (; kt < ktiles; kt += 2) {
+      iteration(kt, part, d0);
+      iteration(kt + 1, part, d1);
+      __syncthreads();
+    }
+  } else {
+    // k-tile kt is multiplied, then kt + 1 is converted, while kt + 2 is on its way from memory: 16 registers less
+    auto iteration = [&](int kt, int slot, auto whole, const double (&now)[8], double (&later)[8]) {
+      fetch(kt + 2, whole, later);
+      asm volatile("" ::: "memory");
+      v4i fb[2][2];
+      fragments(slot, fb);
+      multiply(fb, 0, 4 * NI);
+      fetch_thin(kt + 1 < ktiles ? kt + 1 : ktiles - 1);
+      asm volatile("" ::: "memory");
+      convert(now, slot ^ 1, [](int) {});
+      __syncthreads();  // the next k-tile is complete, and nobody reads this one's slot any more
+    };
+    __syncthreads();
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+    for (; (int64_t)(kt + 4) * BK <= g.k; kt += 2) {
+      iteration(kt, 0, whole, d1, d0);
+      iteration(kt + 1, 1, whole, d0, d1);
+    }
+    for (; kt < ktiles; kt += 2) {
+      iteration(kt, 0, part, d1, d0);
+      iteration(kt + 1, 1, part, d0, d1);
+    }
   }
   if (!works) return;
 
@@ -194,13 +250,64 @@ __global__ void __launch_bounds__(kThreads) thin_products_kernel(const ThinArgs 
     }
 }
 
+// Which form: pairs of k-tiles where their registers and 128 KiB of LDS cost nothing, one at a time for four tiles of the thin
+// operand (the pairs would keep 84 to 270 bytes per lane in scratch memory: 8192 x 128 x 8192 with 16 moduli 426 -> 527 us) and
+// for one tile with the one-level split when there are workgroups for two on a compute unit, which fit then (16384 x 32 x 4096
+// 315 us, in pairs 331).
+template <int KIND, int NI>
+constexpr bool kPairs = NI < 4;
+template <int KIND, int NI>
+constexpr bool kSingles = NI == 4 || (NI == 1 && KIND == 0);
+
+template <int KIND, int NI, bool PAIRED>
+hipError_t set_thin_lds() {
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(thin_products_kernel<KIND, NI, true, PAIRED>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, thin_lds_bytes(PAIRED));
+  if (e != hipSuccess) return e;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(thin_products_kernel<KIND, NI, false, PAIRED>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, thin_lds_bytes(PAIRED));
+}
+template <int KIND, int NI>
+hipError_t set_thin() {
+  hipError_t e = hipSuccess;
+  if constexpr (kPairs<KIND, NI>) e = set_thin_lds<KIND, NI, true>();
+  if constexpr (kSingles<KIND, NI>) e = e == hipSuccess ? set_thin_lds<KIND, NI, false>() : e;
+  return e;
+}
+template <int KIND>
+hipError_t set_thin_kind() {
+  hipError_t e = set_thin<KIND, 1>();
+  if (e == hipSuccess) e = set_thin<KIND, 2>();
+  if (e == hipSuccess) e = set_thin<KIND, 3>();
+  return e == hipSuccess ? set_thin<KIND, 4>() : e;
+}
+
+template <int KIND, int NI, bool BIG_A>
+void launch_thin(const ThinArgs& g, hipStream_t st) {
+  const dim3 grid((unsigned)g.chunk * 8), thr(kThreads);
+  const bool two_fit = g.total > oz2_gemm_cus();
+  if constexpr (kPairs<KIND, NI> && kSingles<KIND, NI>) {
+    if (two_fit) {
+      hipLaunchKernelGGL((thin_products_kernel<KIND, NI, BIG_A, false>), grid, thr, thin_lds_bytes(false), st, g);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((thin_products_kernel<KIND, NI, BIG_A, kPairs<KIND, NI>>), grid, thr, thin_lds_bytes(kPairs<KIND, NI>), st, g);
+}
+
 }  // namespace
+
+// Once per process, before any launch: the dynamic LDS limits.
+hipError_t oz2_thin_setup() {
+  const hipError_t e = set_thin_kind<0>();
+  return e == hipSuccess ? set_thin_kind<1>() : e;
+}
 
 // The smaller of two estimates in nanoseconds, measured times per k-tile of a workgroup (one per compute unit) and per
 // byte that conversion and products move between them otherwise (8 read, N written, N read per element of the large
-// operand, 4.3 TB/s).  Whole calls, with planes against without (us): 16 moduli 8192 x 96 x 8192 680 / 406, 96 x 8192 x 8192
-// 698 / 429, 8192 x 32 x 8192 671 / 353, 16384 x 64 x 2048 374 / 208; 14 moduli 64 x 15484 x 9445 1391 / 910; 18 moduli
-// 8192 x 96 x 8192 739 / 605; 22 moduli 8192 x 96 x 8192 906 / 764.
+// operand, 4.3 TB/s).  Whole calls, with planes against without (us): 16 moduli 8192 x 96 x 8192 680 / 366, 96 x 8192 x 8192
+// 698 / 399, 8192 x 32 x 8192 671 / 327, 16384 x 64 x 2048 374 / 195; 14 moduli 64 x 15484 x 9445 1391 / 818; 18 moduli
+// 8192 x 96 x 8192 739 / 520; 22 moduli 8192 x 96 x 8192 906 / 702.
 int oz2_thin_applies(int64_t m, int64_t n, const Oz2Plan& plan, const Oz2Layout& lay, int64_t kblock) {
   const int64_t thin = m < n ? m : n, large = m < n ? n : m;
   // (up to 1024 the one-pass conversion reads the operand once, which is the better half of this)
@@ -239,15 +346,8 @@ hipError_t oz2_launch_thin_products(int which, int strided, const double* X, int
   g.skip_flag = check_flag ? reinterpret_cast<const unsigned long long*>(ws + lay.off_flags) : nullptr;
   g.conv = plan.conv;
   for (int t = 0; t < plan.N; ++t) g.fold[t] = oz2_fold_consts(plan.moduli[t]);
-  const dim3 grid((unsigned)g.chunk * 8), thr(kThreads);
   const int ni = (int)((nthin + 31) / 32);
-#define OZ2_THIN(KIND, NI)                                                                   \
-  do {                                                                                       \
-    if (big_a)                                                                               \
-      hipLaunchKernelGGL((thin_products_kernel<KIND, NI, true>), grid, thr, 0, st, g);       \
-    else                                                                                     \
-      hipLaunchKernelGGL((thin_products_kernel<KIND, NI, false>), grid, thr, 0, st, g);      \
-  } while (0)
+#define OZ2_THIN(KIND, NI) (big_a ? launch_thin<KIND, NI, true>(g, st) : launch_thin<KIND, NI, false>(g, st))
 #define OZ2_THIN_NI(KIND)                                                                    \
   do {                                                                                       \
     if (ni == 1)                                                                             \

@@ -318,6 +318,27 @@ def test_thin_products_at_the_ends_of_the_inner_dimension(k, ta):
     del ws
 
 
+@pytest.mark.parametrize("k", [1025, 1089, 1153, 1217, 1281, 1344])
+@pytest.mark.parametrize("thin,N,first", [(20, 16, True), (32, 15, False), (96, 16, True), (70, 13, False), (31, 23, True), (90, 24, False)])
+def test_thin_products_two_k_tiles_at_a_time(thin, N, first, k):
+    """One and three 32-vector tiles of the thin operand with at most one workgroup per compute unit, elements split one and two levels
+    deep, every remainder of the number of k-tiles that the loop's rounds and its last fetches can meet."""
+    large = 5003
+    m, n = (large, thin) if first else (thin, large)
+    rng = np.random.default_rng(thin + k)
+    A, B = _mat(rng, m, k), _mat(rng, k, n)
+    print("thin pairs: m=%d n=%d k=%d N=%d" % (m, n, k, N), flush=True)
+    dA, dB = _dev(A), _dev(B)
+    dC = torch.full((n, m), 5.0, dtype=torch.float64, device="cuda")
+    ws = oz.Workspace(m, n, k, N)
+    oz.oz2_dgemm(m, n, k, dA.data_ptr(), m, dB.data_ptr(), k, dC.data_ptr(), m, N)
+    torch.cuda.synchronize()
+    pick = np.unique(np.concatenate([np.arange(66), np.arange(large - 70, large), rng.integers(0, large, 40)]))
+    rows, cols = (pick, np.arange(n)) if first else (np.arange(m), pick)
+    assert np.array_equal(dC.t().cpu().numpy()[np.ix_(rows, cols)], orc.dgemm(A, B, N, rows=rows, cols=cols).C)
+    del ws
+
+
 @pytest.mark.parametrize("first", [True, False])
 @pytest.mark.parametrize("mode,delta,N,k,ta,tb", [(1, 0, 16, 1101, "N", "T"), (2, 0, 16, 1101, "T", "N"), (1, 0, 16, 3000, "T", "T"),
                                                   (2, 0, 15, 3000, "N", "N"), (0, 30, 21, 1101, "N", "N"), (0, -30, 21, 3000, "T", "N"),
