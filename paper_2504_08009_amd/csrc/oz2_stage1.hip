@@ -16,6 +16,7 @@
 // number of launches); a block picks its operand and its kernel body by its index.
 #include "oz2_math.h"
 #include "oz2_scan_finish.h"
+#include "oz2_warm.h"
 
 namespace {
 
@@ -706,6 +707,7 @@ template <int KA, int KB>
 __global__ void __launch_bounds__(kShortThreads) short_convert_kernel(const ShortJob ja, const ShortJob jb, const Oz2ConvConsts cc,
                                                                       unsigned long long* __restrict__ slots) {
   extern __shared__ __attribute__((aligned(16))) double short_tile[];
+  warm_arguments(cc);
   // workgroup i of a launch runs on die i % 8: consecutive groups of vectors for each die
   const unsigned x = blockIdx.x & 7u;
   unsigned y = blockIdx.x >> 3;

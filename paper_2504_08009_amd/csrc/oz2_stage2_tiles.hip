@@ -14,6 +14,7 @@
 // -amdgpu-mfma-vgpr-form), so the epilogue reads them directly.
 #include "oz2_gemm.h"
 #include "oz2_scan_finish.h"
+#include "oz2_warm.h"
 
 namespace {
 
@@ -46,6 +47,7 @@ __global__ void __launch_bounds__(kThreads, WGS) gemm_i8_tile_kernel(const TileA
   constexpr int kStage = (TM + TN) * BK;
   constexpr int kLoadsA = MI, kLoadsB = NI, kLoads = kLoadsA + kLoadsB;  // direct loads of 1 KiB per wave and k-tile
   extern __shared__ __attribute__((aligned(1024))) char lds[];
+  warm_arguments(g);
 
   if (g.skip_flag != nullptr && *g.skip_flag != 0ull) return;
   if (g.fin.slots != nullptr && blockIdx.x == 0) finish_scan(g.fin);

@@ -7,6 +7,7 @@
 #include "oz2_fallback_tile.h"
 #include "oz2_fast_div.h"
 #include "oz2_math.h"
+#include "oz2_warm.h"
 
 namespace {
 
@@ -169,6 +170,7 @@ __global__ void __launch_bounds__(kThreads, 4) crt_or_fallback_kernel(const void
                                                                    const unsigned crt_blocks, const int per_col,
                                                                    const FastDiv by_col, const Oz2FallbackArgs f,
                                                                    const Oz2CrtConsts cc) {
+  warm_arguments(cc);
   const bool nonfinite = *flag != 0ull;
   if (blockIdx.x < crt_blocks) {
     if (nonfinite) return;
