@@ -14,6 +14,8 @@
 // a flag word of the workspace.  Triangular operands (TRMM shape) are masked while they are read.
 // The maxima of both operands share one launch and so do their conversions (small problems are bound by the
 // number of launches); a block picks its operand and its kernel body by its index.
+#include <type_traits>
+
 #include "oz2_math.h"
 #include "oz2_scan_finish.h"
 #include "oz2_warm.h"
@@ -601,15 +603,20 @@ __global__ void __launch_bounds__(kThreads) operand_convert_kernel(const ConvJob
   }
 }
 
-// ---- Short vectors (inner dimension up to 1024): lines 1-5 in ONE pass.  A workgroup holds eight whole vectors in LDS
-// (up to 64 KiB, two workgroups per compute unit), so the operand is read once instead of twice and the maxima, the shifts
+// ---- Short vectors (inner dimension up to 1024): lines 1-5 in ONE pass.  A workgroup holds eight or four whole vectors in LDS
+// (up to 64 KiB, two workgroups per compute unit or more), so the operand is read once instead of twice and the maxima, the shifts
 // and the residues of both operands take one launch.  Bound by HBM at large sizes (8 bytes read, N written per
 // element), by the launch and the chain of a thread's elements at small ones.  Whole calls against the two launches (us): 14
 // moduli 256^3 32.3 -> 24.8, 512^3 36.4 -> 30.1, 1024^3 60.2 -> 53.8, 300 x 3000 x 1000 92 -> 73, 2048 x 2048 x 512
 // 98 -> 92; 16 moduli 4096 x 4096 x 1024 and 18 moduli 8192 x 8192 x 1024 even.
 // Eight vectors of a column-major operand read by rows are 64-byte pieces of its columns: the workgroups of neighbouring
 // groups, which read the other halves of the same cache lines, are placed on the same die.
-constexpr int kShortVecs = 8;
+// At small sizes a thread's loads are all in flight at once and its maximum is formed on the way; four vectors per workgroup
+// where eight would leave compute units idle, and up to four k-tiles several waves share one, each with some of the moduli
+// (against loads behind a branch each, eight vectors and a k-tile per wave, whole calls, us: 14 moduli 256^3 15.3 / 14.0, 512^3 22.7 / 21.2,
+// 700^3 31.5 / 29.9, 1024^3 43.2 / 39.9, 13 moduli 80 x 4000 x 700 36.4 / 35.1, 16 moduli 150 x 2500 x 900 45.3 / 41.2; with the
+// changes to stage 3 that came along).
+constexpr int kShortVecs = 8, kShortFew = 4;  // vectors per workgroup
 constexpr int kShortThreads = 512;
 constexpr int kShortK = 1024;
 struct ShortJob {
@@ -623,71 +630,109 @@ struct ShortJob {
   unsigned nblk;  // workgroups that have vectors
   unsigned chunk; // workgroups per die (a multiple of nblk / 8, rounded up)
 };
-template <int KIND>
+template <int KIND, int V>
 __device__ __forceinline__ void convert_short(const ShortJob& j, const Oz2ConvConsts& cc, double* tile, unsigned id,
                                               unsigned long long* slot) {
-  constexpr int V = kShortVecs;
-  __shared__ unsigned long long part[kShortThreads / 64][V];
+  constexpr int kWaves = kShortThreads / 64;
+  __shared__ unsigned long long part[kWaves][V];  // largest magnitude of a vector among what a wave has read
   const int64_t v0 = (int64_t)id * V;
   const int pitch = (int)j.k_pad + 4;  // doubles per vector: four banks of 32 bytes apart
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  unsigned long long mx = 0ull;
+  // This thread's elements of vector v0 + v, positions l0, l0 + STEP, ...: B loads in flight at a time, none of them behind a
+  // branch (beyond the operand the last element is read and zero taken).
+  auto read = [&](auto batch, auto step, int v, int l0, const double* src, int64_t ld, bool swapped) {
+    constexpr int B = decltype(batch)::value, STEP = decltype(step)::value;
+    const bool in = v0 + v < j.nvec;
+    const int last = (int)j.k - 1;
+    for (int l = l0; l < (int)j.k_pad; l += B * STEP) {
+      double x[B];
+#pragma unroll
+      for (int u = 0; u < B; ++u) x[u] = src[(int64_t)min(l + u * STEP, last) * ld];
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const int lu = l + u * STEP;
+        const double y = !in || lu > last ? 0.0 : swapped ? tri_value(x[u], lu, v0 + v, j.tri) : tri_value(x[u], v0 + v, lu, j.tri);
+        if (lu < (int)j.k_pad) tile[v * pitch + lu] = y;
+        const unsigned long long b = abs_bits(y);
+        mx = b > mx ? b : mx;
+      }
+    }
+  };
+  auto join = [&](int from, int to) {
+#pragma unroll
+    for (int off = from; off >= to; off >>= 1) {
+      const unsigned long long o = __shfl_xor(mx, off, 64);
+      mx = o > mx ? o : mx;
+    }
+  };
+  const std::integral_constant<int, 2> two;
+  const std::integral_constant<int, 4> few;
+  const std::integral_constant<int, V == 4 ? 8 : 4> many;  // (V = 8: eight would cost a workgroup per compute unit)
   if (j.strided) {
     const int v = threadIdx.x % V;
-    const bool in = v0 + v < j.nvec;
-    const double* src = j.X + v0 + v;
-#pragma unroll 4
-    for (int l = threadIdx.x / V; l < j.k_pad; l += kShortThreads / V)
-      tile[v * pitch + l] = (in && l < j.k) ? tri_value(src[(int64_t)l * j.ld], v0 + v, l, j.tri) : 0.0;
+    const std::integral_constant<int, kShortThreads / V> step;
+    const double* src = j.X + (v0 + v < j.nvec ? v0 + v : j.nvec - 1);
+    if (j.k_pad <= 2 * step.value)
+      read(two, step, v, threadIdx.x / V, src, j.ld, false);
+    else if (j.k_pad <= 4 * step.value)
+      read(few, step, v, threadIdx.x / V, src, j.ld, false);
+    else
+      read(many, step, v, threadIdx.x / V, src, j.ld, false);
+    join(32, V);
+    if (lane < V) part[wv][lane] = mx;
   } else {
-    // a wave takes one vector, its lanes run down the vector
-    const int v = threadIdx.x >> 6;
-    static_assert(kShortThreads / 64 == V, "one wave per vector");
-    const bool in = v0 + v < j.nvec;
-    const double* src = j.X + (v0 + v) * j.ld;
-#pragma unroll 4
-    for (int l = threadIdx.x & 63; l < j.k_pad; l += 64)
-      tile[v * pitch + l] = (in && l < j.k) ? tri_value(src[l], l, v0 + v, j.tri) : 0.0;
+    // kWaves / V waves take a vector, their lanes run down the vector
+    const int v = wv % V;
+    const std::integral_constant<int, 64 * (kWaves / V)> step;
+    const double* src = j.X + (v0 + v < j.nvec ? v0 + v : j.nvec - 1) * j.ld;
+    const int l0 = (wv / V) * 64 + lane;
+    if (j.k_pad <= 2 * step.value)
+      read(two, step, v, l0, src, 1, true);
+    else if (j.k_pad <= 4 * step.value)
+      read(few, step, v, l0, src, 1, true);
+    else
+      read(many, step, v, l0, src, 1, true);
+    join(32, 1);
+    if (lane < V) part[wv][lane] = lane == v ? mx : 0ull;
   }
   __syncthreads();
-  // lane: vector lane / 8, inner positions 8 (lane % 8) .. + 7 of a k-tile; wave w takes the k-tiles w, w + 8, ...
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, v = lane >> 3;
-  const double* mine = tile + v * pitch + 8 * (lane & 7);
-  const int ktiles = (int)(j.k_pad / kBlkK);
-  unsigned long long mx = 0ull;
-  for (int kt = wv; kt < ktiles; kt += kShortThreads / 64)
+  // lane: inner positions 8 (lane % 8) .. + 7 of one of the V vectors in one of the 8 / V k-tiles that a wave takes at a time
+  constexpr int kSide = 8 / V;
+  const int v = (lane >> 3) % V, side = lane / (8 * V);
+  mx = 0ull;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const unsigned long long b = abs_bits(mine[kt * kBlkK + u]);
-      mx = b > mx ? b : mx;
-    }
-#pragma unroll
-  for (int off = 4; off >= 1; off >>= 1) {
-    const unsigned long long o = __shfl_xor(mx, off, 64);
-    mx = o > mx ? o : mx;
-  }
-  if ((lane & 7) == 0) part[wv][v] = mx;
-  __syncthreads();
-#pragma unroll
-  for (int w = 0; w < kShortThreads / 64; ++w) mx = part[w][v] > mx ? part[w][v] : mx;
+  for (int w = 0; w < kWaves; ++w) mx = part[w][v] > mx ? part[w][v] : mx;
   const int shift = mx ? j.param - 1 - exponent_of_bits(mx) : 0;
-  if (wv == 0 && (lane & 7) == 0) {
+  if (wv == 0 && side == 0 && (lane & 7) == 0) {
     j.vmax[v0 + v] = mx;
     j.shifts[v0 + v] = shift;
   }
-  const bool bad = mx >= kInfBits;
   if (wv == 0) {
-    const bool any = __any(bad);
+    const bool any = __any(mx >= kInfBits);
     if (lane == 0) *slot = any ? 1ull : 0ull;
   }
+  // Wave w takes the k-tiles w, w + 8, ... (in units of kSide); where there are four units or less, several waves take the
+  // same one with a share of the moduli each.
+  const int ktiles = (int)(j.k_pad / kBlkK), units = (ktiles + kSide - 1) / kSide;
+  static_assert(kWaves == 8, "the shares below");
+  const int parts = units > 4 ? 1 : units > 2 ? 2 : units == 2 ? 4 : 8;
+  const int share = units > 4 ? 0 : units == 3 ? (wv * 11) >> 5 : units == 4 ? wv >> 2 : units == 2 ? wv >> 1 : wv;  // wv / units
+  if (share >= parts) return;
+  const int t0 = cc.N * share / parts, t1 = cc.N * (share + 1) / parts;
   constexpr bool TWO_LEVEL = KIND == 1;
   const size_t plane_stride = (size_t)j.nvec_pad * j.k_pad;
-  int8_t* const base = j.planes + (size_t)(v0 / kBlkRows) * kBlkRows * j.k_pad + ((v0 % kBlkRows) + v) * kBlkK + 8 * (lane & 7);
-  for (int kt = wv; kt < ktiles; kt += kShortThreads / 64) {
+  int8_t* const base = j.planes + (size_t)t0 * plane_stride + (size_t)(v0 / kBlkRows) * kBlkRows * j.k_pad +
+                       ((v0 % kBlkRows) + v) * kBlkK + 8 * (lane & 7);
+  for (int unit = wv - share * units; unit < units; unit += parts == 1 ? kWaves : units) {
+    const int kt = unit * kSide + side;
+    if (kt >= ktiles) break;
+    const double* mine = tile + v * pitch + 8 * (lane & 7) + kt * kBlkK;
     Oz2SplitPair<TWO_LEVEL> xs[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-      xs[u] = oz2_split_pair<TWO_LEVEL>(mine[kt * kBlkK + 2 * u], mine[kt * kBlkK + 2 * u + 1], shift);
+    for (int u = 0; u < 4; ++u) xs[u] = oz2_split_pair<TWO_LEVEL>(mine[2 * u], mine[2 * u + 1], shift);
     int8_t* dst = base + (size_t)kt * (kBlkRows * kBlkK);
-    for (int t = 0; t < cc.N; ++t) {
+    for (int t = t0; t < t1; ++t) {
       const Oz2ConvMod mod = cc.mod[t];
       v2u w;
 #pragma unroll
@@ -703,8 +748,8 @@ __device__ __forceinline__ void convert_short(const ShortJob& j, const Oz2ConvCo
 constexpr int kFinishThreads = 1024;
 __global__ void __launch_bounds__(kFinishThreads) finish_scan_kernel(const Oz2ScanFinish f) { finish_scan(f); }
 
-template <int KA, int KB>
-__global__ void __launch_bounds__(kShortThreads) short_convert_kernel(const ShortJob ja, const ShortJob jb, const Oz2ConvConsts cc,
+template <int KA, int KB, int V>
+__global__ void __launch_bounds__(kShortThreads, KA == 0 && KB == 0 ? 6 : 4) short_convert_kernel(const ShortJob ja, const ShortJob jb, const Oz2ConvConsts cc,
                                                                       unsigned long long* __restrict__ slots) {
   extern __shared__ __attribute__((aligned(16))) double short_tile[];
   warm_arguments(cc);
@@ -718,9 +763,9 @@ __global__ void __launch_bounds__(kShortThreads) short_convert_kernel(const Shor
   if (id >= j.nblk) return;
   unsigned long long* slot = slots + (first ? id : ja.nblk + id);
   if (first)
-    convert_short<KA>(ja, cc, short_tile, id, slot);
+    convert_short<KA, V>(ja, cc, short_tile, id, slot);
   else
-    convert_short<KB>(jb, cc, short_tile, id, slot);
+    convert_short<KB, V>(jb, cc, short_tile, id, slot);
 }
 
 }  // namespace
@@ -820,11 +865,13 @@ hipError_t oz2_launch_finish_scan(const Oz2ScanFinish& f, hipStream_t st) {
 
 // Once per process, before any launch: the dynamic LDS limit of the one-pass conversion.
 hipError_t oz2_stage1_setup() {
-  const void* kernels[4] = {
-      reinterpret_cast<const void*>(short_convert_kernel<0, 0>), reinterpret_cast<const void*>(short_convert_kernel<0, 1>),
-      reinterpret_cast<const void*>(short_convert_kernel<1, 0>), reinterpret_cast<const void*>(short_convert_kernel<1, 1>)};
+#define OZ2_BOTH(KA, KB)                                                    \
+  reinterpret_cast<const void*>(short_convert_kernel<KA, KB, kShortVecs>),  \
+      reinterpret_cast<const void*>(short_convert_kernel<KA, KB, kShortFew>)
+  const void* kernels[8] = {OZ2_BOTH(0, 0), OZ2_BOTH(0, 1), OZ2_BOTH(1, 0), OZ2_BOTH(1, 1)};
+#undef OZ2_BOTH
   hipError_t e = hipSuccess;
-  for (int i = 0; i < 4 && e == hipSuccess; ++i)
+  for (int i = 0; i < 8 && e == hipSuccess; ++i)
     e = hipFuncSetAttribute(kernels[i], hipFuncAttributeMaxDynamicSharedMemorySize,
                             kShortVecs * (kShortK + 4) * (int)sizeof(double));
   return e;
@@ -877,11 +924,17 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
   if (deferred) *deferred = {nullptr, 0u, nullptr};
   if (deferred && !thin && shift_mode == OZ2_SHIFT_MAX && !strassen && lay.k_pad <= kShortK) {
     const int kappa_a = plan.kappa - d, kappa_b = d == 0 ? plan.kappa : plan.kappa_sum - kappa_a;
+    const int64_t vectors = lay.m_pad + (nops == 2 ? lay.n_pad : 0);
+    // Four vectors per workgroup, of which a compute unit takes several, up to this many vectors per compute unit (whole calls, four / eight,
+    // us: 14 moduli 512^3 21.2 / 22.2, 700^3 29.9 / 30.6, 16 moduli 150 x 2500 x 900 41.2 / 42.9, 1000 x 1000 x 200 37.0 / 36.3, 12
+    // moduli 2000 x 2000 x 100 57.3 / 54.5).
+    const int64_t per_cu = lay.k_pad <= 256 ? 4 : lay.k_pad <= 512 ? 8 : 16;
+    const int vecs = vectors <= per_cu * oz2_gemm_cus() ? kShortFew : kShortVecs;
     ShortJob sj[2] = {};
     int64_t groups = 0;
     for (int x = 0; x < nops; ++x) {
       const Operand& o = ops[x];
-      const unsigned nblk = (unsigned)(o.nvec_pad / kShortVecs);
+      const unsigned nblk = (unsigned)(o.nvec_pad / vecs);
       sj[x] = {o.X, o.ld, o.nvec, o.nvec_pad, o.k, o.k_pad, o.vmax, o.shifts, o.planes, x == 0 ? kappa_a : kappa_b, o.tri,
                o.strided ? 1 : 0, nblk, (nblk + 7) / 8};
       groups += nblk;
@@ -890,9 +943,14 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
     unsigned long long* slots = ops[0].vaux;
     *deferred = {slots, (unsigned)groups, flag};
     const dim3 grid(8 * (sj[0].chunk + sj[1].chunk)), thr(kShortThreads);
-    const size_t lds = (size_t)kShortVecs * (lay.k_pad + 4) * sizeof(double);
-#define OZ2_SHORT(KA, KB) \
-  hipLaunchKernelGGL((short_convert_kernel<KA, KB>), grid, thr, lds, st, sj[0], sj[1], conv, slots)
+    const size_t lds = (size_t)vecs * (lay.k_pad + 4) * sizeof(double);
+#define OZ2_SHORT(KA, KB)                                                                                                     \
+  do {                                                                                                                        \
+    if (vecs == kShortFew)                                                                                                    \
+      hipLaunchKernelGGL((short_convert_kernel<KA, KB, kShortFew>), grid, thr, lds, st, sj[0], sj[1], conv, slots);           \
+    else                                                                                                                      \
+      hipLaunchKernelGGL((short_convert_kernel<KA, KB, kShortVecs>), grid, thr, lds, st, sj[0], sj[1], conv, slots);          \
+  } while (0)
     const bool two_a = kappa_a > 75, two_b = kappa_b > 75;
     if (two_a && two_b)
       OZ2_SHORT(1, 1);

@@ -56,12 +56,16 @@ struct PlaneLoad<true, 2> {
   }
 };
 
-// One thread: the R consecutive rows i0 .. of one column j.
-template <int L, bool U8, int R>
+// One thread: the R consecutive rows i0 .. of one column j.  kBatch planes' values are fetched at a time, one batch ahead of
+// the arithmetic.  SMALL (a launch at its own latency): the shifts and C, where it is updated, are fetched with the first ones,
+// and so is *flag, which leaves C alone where it is set: one wait for memory in the place of four (256^3, inside the launch, 3.3
+// us before; in large launches the registers cost a wave per SIMD).
+template <int L, bool U8, int R, int kBatch, bool SMALL>
 __device__ __forceinline__ void crt_rows(const void* __restrict__ cplanes, int64_t m_pad, int64_t n_pad,
                                          const int* __restrict__ sa, const int* __restrict__ sb, double* __restrict__ C,
                                          int64_t ldc, int64_t m, int64_t n, const double alpha, const double beta,
-                                         const int triangle, const Oz2CrtConsts& cc, const int64_t j, const int64_t i0) {
+                                         const int triangle, const Oz2CrtConsts& cc, const int64_t j, const int64_t i0,
+                                         const unsigned long long* __restrict__ flag) {
   typedef PlaneLoad<U8, R> PL;
   typedef typename PL::Raw Raw;
   // symmetric product: only the lower (1: i >= j) or upper (2: i <= j) triangle of C exists and is written
@@ -79,11 +83,23 @@ __device__ __forceinline__ void crt_rows(const void* __restrict__ cplanes, int64
 
   // Planes are read once (non-temporal loads), a batch ahead of the arithmetic: kBatch loads per thread in flight keep enough bytes
   // moving per CU to cover the memory latency (one load ahead does not).
-  constexpr int kBatch = 4;
   const int N = cc.N;
   Raw nxt[kBatch];
 #pragma unroll
   for (int d = 0; d < kBatch; ++d) nxt[d] = __builtin_nontemporal_load(src + (size_t)(d < N ? d : N - 1) * stride);
+  double* dst = C + i0 + j * ldc;
+  int shift[R];
+  double old[R];
+  auto mine = [&](int r) { return i0 + r < m && !(triangle == 1 && i0 + r < j) && !(triangle == 2 && i0 + r > j); };
+  if constexpr (SMALL) {
+    const int sbj = sb[j];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      shift[r] = sa[i0 + r] + sbj;
+      old[r] = beta == 0.0 || !mine(r) ? 0.0 : dst[r];
+    }
+    if (*flag != 0ull) return;
+  }
   for (int t0 = 0; t0 < N; t0 += kBatch) {
     Raw cur[kBatch];
 #pragma unroll
@@ -110,23 +126,24 @@ __device__ __forceinline__ void crt_rows(const void* __restrict__ cplanes, int64
       }
     }
   }
-  const int sbj = sb[j];
-  double* dst = C + i0 + j * ldc;
+  const int sbj = SMALL ? 0 : sb[j];
   double out[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     int e2;
     const double x = oz2_crt_reduce<L>(S[r], cc, &e2);
-    out[r] = ldexp(x, e2 - sa[i0 + r] - sbj);  // sa is padded to m_pad (a multiple of 256): readable
+    if constexpr (SMALL)
+      out[r] = ldexp(x, e2 - shift[r]);
+    else
+      out[r] = ldexp(x, e2 - sa[i0 + r] - sbj);  // sa is padded to m_pad (a multiple of 256): readable
   }
   if (alpha != 1.0 || beta != 0.0) {
     // C := alpha * P + beta * C with one rounding of beta * C and one fused multiply-add; C is not read when
     // beta is zero (BLAS convention)
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const bool mine = i0 + r < m && !(triangle == 1 && i0 + r < j) && !(triangle == 2 && i0 + r > j);
-      const double tt = (beta == 0.0 || !mine) ? 0.0 : beta * dst[r];
-      out[r] = fma(alpha, out[r], tt);
+      const double c = SMALL ? old[r] : (beta == 0.0 || !mine(r)) ? 0.0 : dst[r];
+      out[r] = fma(alpha, out[r], beta == 0.0 ? 0.0 : beta * c);
     }
   }
   // all R results of the thread leave together: its 8 R contiguous bytes complete their cache lines at once
@@ -157,7 +174,8 @@ __global__ void __launch_bounds__(kThreads) crt_kernel(const void* __restrict__ 
   const int g = (int)(blockIdx.x * kThreads + threadIdx.x), q = g / by_col;
   const int64_t j = j0 + q;
   if (j >= n) return;
-  crt_rows<L, U8, R>(cplanes, m_pad, n_pad, sa, sb, C, ldc, m, n, alpha, beta, triangle, cc, j, (int64_t)(g - q * per_col) * R);
+  crt_rows<L, U8, R, 4, false>(cplanes, m_pad, n_pad, sa, sb, C, ldc, m, n, alpha, beta, triangle, cc, j, (int64_t)(g - q * per_col) * R,
+                        nullptr);
 }
 
 // Products below 2^24 elements, where every launch counts: the blocks of the FP64 fallback ride in the same launch, behind those of
@@ -171,14 +189,12 @@ __global__ void __launch_bounds__(kThreads, 4) crt_or_fallback_kernel(const void
                                                                    const FastDiv by_col, const Oz2FallbackArgs f,
                                                                    const Oz2CrtConsts cc) {
   warm_arguments(cc);
-  const bool nonfinite = *flag != 0ull;
   if (blockIdx.x < crt_blocks) {
-    if (nonfinite) return;
     const int g = (int)(blockIdx.x * kThreads + threadIdx.x), j = g / by_col;
     if (j >= f.n) return;
-    crt_rows<L, true, R>(cplanes, m_pad, n_pad, sa, sb, f.C, f.ldc, f.m, f.n, f.alpha, f.beta, 0, cc, j,
-                         (int64_t)(g - j * per_col) * R);
-  } else if (nonfinite) {
+    crt_rows<L, true, R, 8, true>(cplanes, m_pad, n_pad, sa, sb, f.C, f.ldc, f.m, f.n, f.alpha, f.beta, 0, cc, j,
+                            (int64_t)(g - j * per_col) * R, flag);
+  } else if (*flag != 0ull) {
     oz2_fallback_tile<kFallbackSmallTile>(f, blockIdx.x - crt_blocks);
   }
 }

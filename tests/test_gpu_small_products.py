@@ -47,6 +47,20 @@ def test_edges_of_the_tiles_and_of_the_one_pass_conversion(m, n, k):
     assert flag == 0 and np.array_equal(got, ref)
 
 
+@pytest.mark.parametrize("k", [1, 63, 65, 129, 193, 256, 257, 320, 449, 512, 513, 577, 960, 1000])
+@pytest.mark.parametrize("m,n,N", [(70, 45, 3), (300, 500, 15), (40, 4200, 5), (3900, 30, 22)])
+def test_one_pass_conversion_by_four_and_by_eight_vectors(m, n, N, k):
+    """Every number of k-tiles up to eight and beyond (waves that share a k-tile, with fewer moduli than waves among them), vectors
+    enough for workgroups of eight at every length and few enough for four, loads in flight that end inside a batch."""
+    rng = np.random.default_rng(m + 7 * n + k)
+    ta, tb = [("N", "N"), ("T", "T")][k % 2]
+    print("one pass: m=%d n=%d k=%d N=%d op=%s%s" % (m, n, k, N, ta, tb), flush=True)
+    A = _mat(rng, *((m, k) if ta == "N" else (k, m)))
+    B = _mat(rng, *((k, n) if tb == "N" else (n, k)))
+    got, ref, flag = _gemm(ta, tb, A, B, N, beta=float(m % 4 == 0))
+    assert flag == 0 and np.array_equal(got, ref)
+
+
 @pytest.mark.parametrize("delta", [30, -30])
 def test_one_operand_split_deeper_than_the_other(delta):
     """21 moduli and a bit split of 30: one operand needs the two-level split, the other does not."""
