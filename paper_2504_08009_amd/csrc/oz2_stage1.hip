@@ -26,7 +26,8 @@ constexpr int kThreads = 256;
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
 
-__global__ void __launch_bounds__(kThreads) fill_u64_kernel(unsigned long long* p, int64_t count) {
+__global__ void __launch_bounds__(kThreads) fill_u64_kernel(unsigned long long* p, int64_t count, const Oz2ScanFinish fin) {
+  if (fin.slots != nullptr && blockIdx.x == 0) finish_scan(fin);
   int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (i < count) p[i] = 0ull;
 }
@@ -243,7 +244,7 @@ __global__ void __launch_bounds__(kThreads) shifts_kernel(const ShiftJob ja, con
   j.s[i] = shift_of(j.mx[i], mode == 0 ? 0ull : j.aux[i], mode, j.param, j.offset);
 }
 
-// ---- Small operands: maxima, in the Cauchy-Schwarz mode the norm bounds, and shifts of both operands in ONE launch and
+// ---- Operands whose vectors are too long for that: maxima, in the Cauchy-Schwarz mode the norm bounds, and shifts of both in ONE launch and
 // without atomics, so that nothing has to be cleared first: a workgroup owns 16 whole vectors, forms their maxima (and
 // from them, reading the vectors once more out of the caches, the sums of squares), writes them and the shifts, and reports
 // in a slot of its own whether it saw an infinity or a NaN.  The conversion launch that follows folds the slots into the
@@ -395,22 +396,23 @@ __device__ __forceinline__ void store_bounds(const double* mine, int shift, int8
 }
 
 // ---- INT8-product shift mode (Section 4.1): row and column maxima of P = A''B'' (INT32, element (i,j) at
-// j*m_pad + i).  A wave takes 256 rows (four per lane, 16-byte loads) x 64 columns; the four rows of a lane are joined
-// before the wave's reduction, which is what the kernel spends its time on (3001 x 2777: 38 -> 27 us).
-constexpr int kProdCols = 64;
+// j*m_pad + i).  A wave takes 256 rows (four per lane, 16-byte loads) x 8 to 64 columns; the four rows of a lane are joined
+// before the wave's reduction, which is what the kernel spends its time on (3001 x 2777: 38 -> 27 us).  Few columns per wave are a
+// short chain (64 against 8, whole calls with 16 moduli, us: 64^3 53.0 / 35.8, 200 x 300 x 700 68.3 / 51.0, 1000 x 1000 x 2000 136.4 / 125.8)
+// but many waves that meet at a row's word (300 x 5000 x 700 134 / 157).
 constexpr int kProdRows = kThreads / 64 * 256;
 __global__ void __launch_bounds__(kThreads) prodmax_kernel(const int* __restrict__ P, int64_t m_pad, int64_t m, int64_t n,
-                                                           int64_t row_blocks, unsigned long long* __restrict__ rowtop,
+                                                           int64_t row_blocks, int cols, unsigned long long* __restrict__ rowtop,
                                                            unsigned long long* __restrict__ coltop) {
   typedef int v4s __attribute__((ext_vector_type(4)));
   const int64_t rb = blockIdx.x % row_blocks, cb = blockIdx.x / row_blocks;
   const int lane = threadIdx.x & 63;
   const int64_t i = rb * kProdRows + (threadIdx.x >> 6) * 256 + 4 * lane;
   if (i - 4 * lane >= m_pad) return;  // the whole wave; m_pad is a multiple of 256
-  const int64_t j0 = cb * kProdCols;
+  const int64_t j0 = cb * cols;
   const int* src = P + i + j0 * m_pad;
   v4s rmax = {0, 0, 0, 0};
-  for (int jj = 0; jj < kProdCols; jj += 8) {
+  for (int jj = 0; jj < cols; jj += 8) {
     v4s v[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u)
@@ -603,41 +605,48 @@ __global__ void __launch_bounds__(kThreads) operand_convert_kernel(const ConvJob
   }
 }
 
-// ---- Short vectors (inner dimension up to 1024): lines 1-5 in ONE pass.  A workgroup holds eight or four whole vectors in LDS
-// (up to 64 KiB, two workgroups per compute unit or more), so the operand is read once instead of twice and the maxima, the shifts
-// and the residues of both operands take one launch.  Bound by HBM at large sizes (8 bytes read, N written per
-// element), by the launch and the chain of a thread's elements at small ones.  Whole calls against the two launches (us): 14
-// moduli 256^3 32.3 -> 24.8, 512^3 36.4 -> 30.1, 1024^3 60.2 -> 53.8, 300 x 3000 x 1000 92 -> 73, 2048 x 2048 x 512
-// 98 -> 92; 16 moduli 4096 x 4096 x 1024 and 18 moduli 8192 x 8192 x 1024 even.
-// Eight vectors of a column-major operand read by rows are 64-byte pieces of its columns: the workgroups of neighbouring
-// groups, which read the other halves of the same cache lines, are placed on the same die.
-// At small sizes a thread's loads are all in flight at once and its maximum is formed on the way; four vectors per workgroup
-// where eight would leave compute units idle, and up to four k-tiles several waves share one, each with some of the moduli
-// (against loads behind a branch each, eight vectors and a k-tile per wave, whole calls, us: 14 moduli 256^3 15.3 / 14.0, 512^3 22.7 / 21.2,
-// 700^3 31.5 / 29.9, 1024^3 43.2 / 39.9, 13 moduli 80 x 4000 x 700 36.4 / 35.1, 16 moduli 150 x 2500 x 900 45.3 / 41.2; with the
-// changes to stage 3 that came along).
-constexpr int kShortVecs = 8, kShortFew = 4;  // vectors per workgroup
+// ---- Vectors that fit into LDS: lines 1-5 in ONE pass, in every shift mode (in the INT8-product mode: maxima and bound planes).
+// A workgroup holds eight, four or two whole vectors in LDS, so the operand is read once instead of twice and the maxima, the norms of
+// the Cauchy-Schwarz mode, the shifts and the residues of both operands take one launch.  Bound by HBM at large sizes (8 bytes read, N
+// written per element), by the launch and the chain of a thread's elements at small ones.  How many vectors, where not, and both sides'
+// times: short_vectors.  A thread's loads are in flight together and its maximum is formed on the way; up to four k-tiles several
+// waves share one, each with some of the moduli (against loads behind a branch each, eight vectors and a k-tile per wave, whole calls, us:
+// 14 moduli 256^3 15.3 / 14.0, 512^3 22.7 / 21.2, 700^3 31.5 / 29.9, 1024^3 43.2 / 39.9, 13 moduli 80 x 4000 x 700 36.4 / 35.1, 16 moduli
+// 150 x 2500 x 900 45.3 / 41.2; with the changes to stage 3 that came along).
+// A few vectors of a column-major operand read by rows are 16- to 64-byte pieces of its columns: the workgroups of neighbouring
+// groups, which read the other parts of the same cache lines, are placed on the same die.
 constexpr int kShortThreads = 512;
-constexpr int kShortK = 1024;
+constexpr int kShortLds = 156 * 1024;  // of 160 KiB, what a workgroup's vectors may take
 struct ShortJob {
   const double* X;
   int64_t ld, nvec, nvec_pad, k, k_pad;
   unsigned long long* vmax;
   int* shifts;
   int8_t* planes;
-  int param;  // kappa of this operand
+  int param;  // as in ShiftJob
   int tri, strided;
-  unsigned nblk;  // workgroups that have vectors
-  unsigned chunk; // workgroups per die (a multiple of nblk / 8, rounded up)
+  unsigned nblk;   // workgroups
+  unsigned chunk;  // workgroups per die: nblk / 8, there are 256 / V or a multiple of that
 };
+// KIND 0, 1: residue planes as in the conversion above; 2: the plane of 6-bit bounds.  mode: as shift_of counts them (0 or 1)
 template <int KIND, int V>
-__device__ __forceinline__ void convert_short(const ShortJob& j, const Oz2ConvConsts& cc, double* tile, unsigned id,
+__device__ __forceinline__ void convert_short(const ShortJob& j, const Oz2ConvConsts& cc, const int mode, double* tile, unsigned id,
                                               unsigned long long* slot) {
   constexpr int kWaves = kShortThreads / 64;
-  __shared__ unsigned long long part[kWaves][V];  // largest magnitude of a vector among what a wave has read
+  __shared__ unsigned long long part[kWaves][V];  // a wave's share of a vector's maximum, then of its norm
   const int64_t v0 = (int64_t)id * V;
   const int pitch = (int)j.k_pad + 4;  // doubles per vector: four banks of 32 bytes apart
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  // the k-tiles that are wanted: all, or of a triangular operand's residues those that the products read (see tile_used)
+  int kt_begin = 0, kt_end = (int)(j.k_pad / kBlkK);
+  if (KIND != 2 && (j.tri & 3)) {
+    const int64_t d0 = v0 / kBlkRows * kBlkRows;
+    if (((j.tri & 3) == 1) == (j.strided != 0))
+      kt_end = (int)min((int64_t)kt_end, (d0 + kBlkRows) / kBlkK);
+    else
+      kt_begin = (int)min((int64_t)kt_end, d0 / kBlkK);
+  }
+  const int begin = kt_begin * kBlkK, end = kt_end * kBlkK;
   unsigned long long mx = 0ull;
   // This thread's elements of vector v0 + v, positions l0, l0 + STEP, ...: B loads in flight at a time, none of them behind a
   // branch (beyond the operand the last element is read and zero taken).
@@ -645,7 +654,7 @@ __device__ __forceinline__ void convert_short(const ShortJob& j, const Oz2ConvCo
     constexpr int B = decltype(batch)::value, STEP = decltype(step)::value;
     const bool in = v0 + v < j.nvec;
     const int last = (int)j.k - 1;
-    for (int l = l0; l < (int)j.k_pad; l += B * STEP) {
+    for (int l = begin + l0; l < end; l += B * STEP) {
       double x[B];
 #pragma unroll
       for (int u = 0; u < B; ++u) x[u] = src[(int64_t)min(l + u * STEP, last) * ld];
@@ -653,11 +662,20 @@ __device__ __forceinline__ void convert_short(const ShortJob& j, const Oz2ConvCo
       for (int u = 0; u < B; ++u) {
         const int lu = l + u * STEP;
         const double y = !in || lu > last ? 0.0 : swapped ? tri_value(x[u], lu, v0 + v, j.tri) : tri_value(x[u], v0 + v, lu, j.tri);
-        if (lu < (int)j.k_pad) tile[v * pitch + lu] = y;
+        if (lu < end) tile[v * pitch + lu] = y;
         const unsigned long long b = abs_bits(y);
         mx = b > mx ? b : mx;
       }
     }
+  };
+  auto read_all = [&](auto step, int v, int l0, const double* src, int64_t ld, bool swapped) {
+    constexpr int STEP = decltype(step)::value;
+    if (end - begin <= 2 * STEP)
+      read(std::integral_constant<int, 2>(), step, v, l0, src, ld, swapped);
+    else if (V == 8 || end - begin <= 4 * STEP)  // (V = 8: eight would cost a workgroup per compute unit)
+      read(std::integral_constant<int, 4>(), step, v, l0, src, ld, swapped);
+    else
+      read(std::integral_constant<int, 8>(), step, v, l0, src, ld, swapped);
   };
   auto join = [&](int from, int to) {
 #pragma unroll
@@ -666,44 +684,51 @@ __device__ __forceinline__ void convert_short(const ShortJob& j, const Oz2ConvCo
       mx = o > mx ? o : mx;
     }
   };
-  const std::integral_constant<int, 2> two;
-  const std::integral_constant<int, 4> few;
-  const std::integral_constant<int, V == 4 ? 8 : 4> many;  // (V = 8: eight would cost a workgroup per compute unit)
   if (j.strided) {
     const int v = threadIdx.x % V;
-    const std::integral_constant<int, kShortThreads / V> step;
-    const double* src = j.X + (v0 + v < j.nvec ? v0 + v : j.nvec - 1);
-    if (j.k_pad <= 2 * step.value)
-      read(two, step, v, threadIdx.x / V, src, j.ld, false);
-    else if (j.k_pad <= 4 * step.value)
-      read(few, step, v, threadIdx.x / V, src, j.ld, false);
-    else
-      read(many, step, v, threadIdx.x / V, src, j.ld, false);
+    read_all(std::integral_constant<int, kShortThreads / V>(), v, threadIdx.x / V, j.X + (v0 + v < j.nvec ? v0 + v : j.nvec - 1), j.ld,
+             false);
     join(32, V);
     if (lane < V) part[wv][lane] = mx;
   } else {
     // kWaves / V waves take a vector, their lanes run down the vector
     const int v = wv % V;
-    const std::integral_constant<int, 64 * (kWaves / V)> step;
-    const double* src = j.X + (v0 + v < j.nvec ? v0 + v : j.nvec - 1) * j.ld;
-    const int l0 = (wv / V) * 64 + lane;
-    if (j.k_pad <= 2 * step.value)
-      read(two, step, v, l0, src, 1, true);
-    else if (j.k_pad <= 4 * step.value)
-      read(few, step, v, l0, src, 1, true);
-    else
-      read(many, step, v, l0, src, 1, true);
+    read_all(std::integral_constant<int, 64 * (kWaves / V)>(), v, (wv / V) * 64 + lane,
+             j.X + (v0 + v < j.nvec ? v0 + v : j.nvec - 1) * j.ld, 1, true);
     join(32, 1);
     if (lane < V) part[wv][lane] = lane == v ? mx : 0ull;
   }
   __syncthreads();
-  // lane: inner positions 8 (lane % 8) .. + 7 of one of the V vectors in one of the 8 / V k-tiles that a wave takes at a time
+  // lane: inner positions 8 (lane % 8) .. + 7 of one of the V vectors in one of the 8 / V k-tiles that a wave takes at a time;
+  // wave w takes the k-tiles w, w + 8, ... (in units of kSide)
   constexpr int kSide = 8 / V;
   const int v = (lane >> 3) % V, side = lane / (8 * V);
+  const int ktiles = kt_end - kt_begin, units = (ktiles + kSide - 1) / kSide;
+  const double* const mine = tile + v * pitch + 8 * (lane & 7) + begin;
   mx = 0ull;
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) mx = part[w][v] > mx ? part[w][v] : mx;
-  const int shift = mx ? j.param - 1 - exponent_of_bits(mx) : 0;
+  unsigned long long norm = 0ull;
+  if (KIND != 2 && mode == 1) {
+    // (a thread's sum is exact: at most 2^11 terms of at most 2^40)
+    static_assert(kShortLds / 8 / 64 <= 1 << 11, "terms of a thread");
+    const int scale = mx ? 19 - exponent_of_bits(mx) : 0;
+    double own = 0.0;
+    for (int kt = wv * kSide + side; kt < ktiles; kt += kWaves * kSide)
+#pragma unroll
+      for (int u = 0; u < 8; ++u) own += scaled_ceil_sq(mine[kt * kBlkK + u], scale);
+    unsigned long long sum = (unsigned long long)own;
+#pragma unroll
+    for (int off = 4; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
+#pragma unroll
+    for (int off = 32; off >= 8 * V; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    __syncthreads();  // the maxima have been read
+    if (side == 0 && (lane & 7) == 0) part[wv][v] = sum;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) norm += part[w][v];
+  }
+  const int shift = shift_of(mx, norm, KIND == 2 ? 0 : mode, j.param, 0);
   if (wv == 0 && side == 0 && (lane & 7) == 0) {
     j.vmax[v0 + v] = mx;
     j.shifts[v0 + v] = shift;
@@ -712,34 +737,40 @@ __device__ __forceinline__ void convert_short(const ShortJob& j, const Oz2ConvCo
     const bool any = __any(mx >= kInfBits);
     if (lane == 0) *slot = any ? 1ull : 0ull;
   }
-  // Wave w takes the k-tiles w, w + 8, ... (in units of kSide); where there are four units or less, several waves take the
-  // same one with a share of the moduli each.
-  const int ktiles = (int)(j.k_pad / kBlkK), units = (ktiles + kSide - 1) / kSide;
-  static_assert(kWaves == 8, "the shares below");
-  const int parts = units > 4 ? 1 : units > 2 ? 2 : units == 2 ? 4 : 8;
-  const int share = units > 4 ? 0 : units == 3 ? (wv * 11) >> 5 : units == 4 ? wv >> 2 : units == 2 ? wv >> 1 : wv;  // wv / units
-  if (share >= parts) return;
-  const int t0 = cc.N * share / parts, t1 = cc.N * (share + 1) / parts;
-  constexpr bool TWO_LEVEL = KIND == 1;
-  const size_t plane_stride = (size_t)j.nvec_pad * j.k_pad;
-  int8_t* const base = j.planes + (size_t)t0 * plane_stride + (size_t)(v0 / kBlkRows) * kBlkRows * j.k_pad +
-                       ((v0 % kBlkRows) + v) * kBlkK + 8 * (lane & 7);
-  for (int unit = wv - share * units; unit < units; unit += parts == 1 ? kWaves : units) {
-    const int kt = unit * kSide + side;
-    if (kt >= ktiles) break;
-    const double* mine = tile + v * pitch + 8 * (lane & 7) + kt * kBlkK;
-    Oz2SplitPair<TWO_LEVEL> xs[4];
+  int8_t* const base = j.planes + (size_t)(v0 / kBlkRows) * kBlkRows * j.k_pad + ((v0 % kBlkRows) + v) * kBlkK + 8 * (lane & 7) +
+                       (size_t)kt_begin * (kBlkRows * kBlkK);
+  if constexpr (KIND == 2) {
+    for (int kt = wv * kSide + side; kt < ktiles; kt += kWaves * kSide) {
+      int r[8];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) xs[u] = oz2_split_pair<TWO_LEVEL>(mine[2 * u], mine[2 * u + 1], shift);
-    int8_t* dst = base + (size_t)kt * (kBlkRows * kBlkK);
-    for (int t = t0; t < t1; ++t) {
-      const Oz2ConvMod mod = cc.mod[t];
-      v2u w;
+      for (int u = 0; u < 8; ++u) r[u] = oz2_bound6(mine[kt * kBlkK + u], shift);
+      *reinterpret_cast<v2u*>(base + (size_t)kt * (kBlkRows * kBlkK)) = v2u{pack4(r[0], r[1], r[2], r[3]), pack4(r[4], r[5], r[6], r[7])};
+    }
+  } else {
+    // (where there are four units or less, several waves take the same one with a share of the moduli each)
+    static_assert(kWaves == 8, "the shares below");
+    const int parts = units > 4 ? 1 : units > 2 ? 2 : units == 2 ? 4 : 8;
+    const int share = units > 4 ? 0 : units == 3 ? (wv * 11) >> 5 : units == 4 ? wv >> 2 : units == 2 ? wv >> 1 : wv;  // wv / units
+    if (share >= parts) return;
+    const int t0 = cc.N * share / parts, t1 = cc.N * (share + 1) / parts;
+    constexpr bool TWO_LEVEL = KIND == 1;
+    const size_t plane_stride = (size_t)j.nvec_pad * j.k_pad;
+    for (int unit = wv - share * units; unit < units; unit += parts == 1 ? kWaves : units) {
+      const int kt = unit * kSide + side;
+      if (kt >= ktiles) break;
+      Oz2SplitPair<TWO_LEVEL> xs[4];
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
-        w[h] = oz2_pack_pairs(oz2_residue_pair<TWO_LEVEL>(xs[2 * h], mod), oz2_residue_pair<TWO_LEVEL>(xs[2 * h + 1], mod));
-      __builtin_nontemporal_store(w, reinterpret_cast<v2u*>(dst));
-      dst += plane_stride;
+      for (int u = 0; u < 4; ++u) xs[u] = oz2_split_pair<TWO_LEVEL>(mine[kt * kBlkK + 2 * u], mine[kt * kBlkK + 2 * u + 1], shift);
+      int8_t* dst = base + (size_t)t0 * plane_stride + (size_t)kt * (kBlkRows * kBlkK);
+      for (int t = t0; t < t1; ++t) {
+        const Oz2ConvMod mod = cc.mod[t];
+        v2u w;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          w[h] = oz2_pack_pairs(oz2_residue_pair<TWO_LEVEL>(xs[2 * h], mod), oz2_residue_pair<TWO_LEVEL>(xs[2 * h + 1], mod));
+        __builtin_nontemporal_store(w, reinterpret_cast<v2u*>(dst));
+        dst += plane_stride;
+      }
     }
   }
 }
@@ -749,23 +780,25 @@ constexpr int kFinishThreads = 1024;
 __global__ void __launch_bounds__(kFinishThreads) finish_scan_kernel(const Oz2ScanFinish f) { finish_scan(f); }
 
 template <int KA, int KB, int V>
-__global__ void __launch_bounds__(kShortThreads, KA == 0 && KB == 0 ? 6 : 4) short_convert_kernel(const ShortJob ja, const ShortJob jb, const Oz2ConvConsts cc,
+__global__ void __launch_bounds__(kShortThreads, KA == 1 || KB == 1 ? 4 : 6) short_convert_kernel(const ShortJob ja, const ShortJob jb,
+                                                                      const Oz2ConvConsts cc, const int mode,
                                                                       unsigned long long* __restrict__ slots) {
   extern __shared__ __attribute__((aligned(16))) double short_tile[];
-  warm_arguments(cc);
-  // workgroup i of a launch runs on die i % 8: consecutive groups of vectors for each die
+  if (KA != 2) warm_arguments(cc);
+  // workgroup i of a launch runs on die i % 8: consecutive vectors for each die; of a triangular operand, whose vectors grow from one
+  // end to the other, 16 at a time, the next 16 for the next die
   const unsigned x = blockIdx.x & 7u;
   unsigned y = blockIdx.x >> 3;
   const bool first = y < ja.chunk;
   const ShortJob& j = first ? ja : jb;
   if (!first) y -= ja.chunk;
-  const unsigned id = x * j.chunk + y;
-  if (id >= j.nblk) return;
+  constexpr unsigned kNear = 16 / V;  // workgroups that share the cache lines of strided vectors
+  const unsigned id = j.tri ? (y / kNear * 8 + x) * kNear + y % kNear : x * j.chunk + y;
   unsigned long long* slot = slots + (first ? id : ja.nblk + id);
   if (first)
-    convert_short<KA, V>(ja, cc, short_tile, id, slot);
+    convert_short<KA, V>(ja, cc, mode, short_tile, id, slot);
   else
-    convert_short<KB, V>(jb, cc, short_tile, id, slot);
+    convert_short<KB, V>(jb, cc, mode, short_tile, id, slot);
 }
 
 }  // namespace
@@ -858,6 +891,26 @@ hipError_t launch_convert(const Operand* ops, int nops, const int* kind, bool la
 
 }  // namespace
 
+// Vectors per workgroup of the one-pass conversion, or 0: the separate launches.  A workgroup's vectors have to fit its LDS, and
+// several workgroups should share a compute unit, so that some read while others convert; strided vectors ask for whole cache lines, i.e.
+// for many vectors.  Whole calls, us, two / four / eight vectors and separate launches, 14 moduli where not said: up to an inner dimension of
+// 1024, four / eight: 512^3 21.2 / 22.2, 700^3 29.9 / 30.6, 16 moduli 150 x 2500 x 900 41.2 / 42.9, 1000 x 1000 x 200 37.0 / 36.3, 12
+// moduli 2000 x 2000 x 100 57.3 / 54.5.  Up to 2496: 12 moduli 150 x 150 x 1100 20.1 / 21.2 / 23.3, 27.1 separately, 16 moduli
+// 1000 x 1000 x 1500 62.2 / 59.7 / 60.3, 73.9, 2048^3 183.7 / 181.0 / 182.6, 190.5, 8000 x 8000 x 2400 2390 / 2359 / 2383, 2406, dsyrk
+// 3000 x 2000 214 / 210 / 219, 231.  Up to 4992: 2000 x 200 x 3000 with 15 77.5 / 84.9, 88.3, 3000^3 482 / 482, 512, 1500 x 1500 x 4500
+// 229 / 213, 240, 16 moduli 4096^3 1169 / 1159, 1157, dtrmm of order 4096 with 2048 columns 522 / 525, 496.  Up to 9984: 300 x 300 x 5000
+// with 16 64.2, 96.6, 500 x 500 x 8000 103, 139, 1000 x 1000 x 8000 208, 214, 2000 x 2000 x 8000 628, 607.  Elements split two levels
+// deep, 22 moduli: 700 x 3000 x 4000 341 / 347, 345, 4096 x 4096 x 2048 892 / 889 / 882, 886.
+static int short_vectors(int64_t vectors, int64_t k_pad, bool two_level) {
+  const int64_t cus = oz2_gemm_cus(), elements = vectors * k_pad;
+  const auto fits = [&](int v) { return v * (k_pad + 4) * (int64_t)sizeof(double) <= kShortLds; };
+  if (k_pad <= 1024) return vectors <= (k_pad <= 256 ? 4 : k_pad <= 512 ? 8 : 16) * cus ? 4 : 8;
+  if (two_level && elements > (int64_t)3 << 22) return 0;
+  if (fits(8)) return vectors <= 4 * cus ? 2 : 4;
+  if (fits(4)) return elements > (int64_t)21 << 20 ? 0 : vectors <= 4 * cus || k_pad <= 3392 || two_level ? 2 : 4;
+  return fits(2) && vectors <= 8 * cus ? 2 : 0;
+}
+
 hipError_t oz2_launch_finish_scan(const Oz2ScanFinish& f, hipStream_t st) {
   hipLaunchKernelGGL(finish_scan_kernel, dim3(1), dim3(kFinishThreads), 0, st, f);
   return hipGetLastError();
@@ -865,15 +918,14 @@ hipError_t oz2_launch_finish_scan(const Oz2ScanFinish& f, hipStream_t st) {
 
 // Once per process, before any launch: the dynamic LDS limit of the one-pass conversion.
 hipError_t oz2_stage1_setup() {
-#define OZ2_BOTH(KA, KB)                                                    \
-  reinterpret_cast<const void*>(short_convert_kernel<KA, KB, kShortVecs>),  \
-      reinterpret_cast<const void*>(short_convert_kernel<KA, KB, kShortFew>)
-  const void* kernels[8] = {OZ2_BOTH(0, 0), OZ2_BOTH(0, 1), OZ2_BOTH(1, 0), OZ2_BOTH(1, 1)};
-#undef OZ2_BOTH
+#define OZ2_ALL(KA, KB)                                           \
+  reinterpret_cast<const void*>(short_convert_kernel<KA, KB, 8>), \
+      reinterpret_cast<const void*>(short_convert_kernel<KA, KB, 4>), reinterpret_cast<const void*>(short_convert_kernel<KA, KB, 2>)
+  const void* kernels[15] = {OZ2_ALL(0, 0), OZ2_ALL(0, 1), OZ2_ALL(1, 0), OZ2_ALL(1, 1), OZ2_ALL(2, 2)};
+#undef OZ2_ALL
   hipError_t e = hipSuccess;
-  for (int i = 0; i < 8 && e == hipSuccess; ++i)
-    e = hipFuncSetAttribute(kernels[i], hipFuncAttributeMaxDynamicSharedMemorySize,
-                            kShortVecs * (kShortK + 4) * (int)sizeof(double));
+  for (int i = 0; i < 15 && e == hipSuccess; ++i)
+    e = hipFuncSetAttribute(kernels[i], hipFuncAttributeMaxDynamicSharedMemorySize, kShortLds);
   return e;
 }
 
@@ -905,8 +957,9 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
   const int nops = B ? 2 : 1;
   const int64_t n_max = nops == 2 ? lay.m_pad + 32 + lay.n_pad : lay.m_pad + 32;
   const int64_t n_aux = nops == 2 ? lay.m_pad + lay.n_pad : lay.m_pad;
-  auto fill = [&](unsigned long long* p, int64_t count) {
-    hipLaunchKernelGGL(fill_u64_kernel, dim3(blocks_of(count, kThreads)), thr, 0, st, p, count);
+  const Oz2ScanFinish nothing = {nullptr, 0u, nullptr};
+  auto fill = [&](unsigned long long* p, int64_t count, const Oz2ScanFinish& f) {
+    hipLaunchKernelGGL(fill_u64_kernel, dim3(blocks_of(count, kThreads)), thr, 0, st, p, count, f);
   };
   auto shifts = [&](int mode, int param_a, int param_b, int off_a, int off_b) {
     const ShiftJob ja = {ops[0].vmax, ops[0].vaux, ops[0].shifts, ops[0].nvec_pad, param_a, off_a};
@@ -918,69 +971,9 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
   // the odd bit of the sum (bit_split == 0: the equal split; the symmetric product always uses it).
   const int d = bit_split;
   int xbits[2];  // |x'| < 2^xbits decides how deep the conversion kernels split an element
-  Oz2ScanFinish fin = {nullptr, 0u, nullptr};
-  // Short vectors under the simple bound: everything in one launch, whose reports the caller's GEMM launch turns into
-  // the flag word (deferred != nullptr: the caller sees to that).
+  Oz2ScanFinish fin = nothing;
   if (deferred) *deferred = {nullptr, 0u, nullptr};
-  if (deferred && !thin && shift_mode == OZ2_SHIFT_MAX && !strassen && lay.k_pad <= kShortK) {
-    const int kappa_a = plan.kappa - d, kappa_b = d == 0 ? plan.kappa : plan.kappa_sum - kappa_a;
-    const int64_t vectors = lay.m_pad + (nops == 2 ? lay.n_pad : 0);
-    // Four vectors per workgroup, of which a compute unit takes several, up to this many vectors per compute unit (whole calls, four / eight,
-    // us: 14 moduli 512^3 21.2 / 22.2, 700^3 29.9 / 30.6, 16 moduli 150 x 2500 x 900 41.2 / 42.9, 1000 x 1000 x 200 37.0 / 36.3, 12
-    // moduli 2000 x 2000 x 100 57.3 / 54.5).
-    const int64_t per_cu = lay.k_pad <= 256 ? 4 : lay.k_pad <= 512 ? 8 : 16;
-    const int vecs = vectors <= per_cu * oz2_gemm_cus() ? kShortFew : kShortVecs;
-    ShortJob sj[2] = {};
-    int64_t groups = 0;
-    for (int x = 0; x < nops; ++x) {
-      const Operand& o = ops[x];
-      const unsigned nblk = (unsigned)(o.nvec_pad / vecs);
-      sj[x] = {o.X, o.ld, o.nvec, o.nvec_pad, o.k, o.k_pad, o.vmax, o.shifts, o.planes, x == 0 ? kappa_a : kappa_b, o.tri,
-               o.strided ? 1 : 0, nblk, (nblk + 7) / 8};
-      groups += nblk;
-    }
-    // the slots live in the auxiliary vectors, which this shift mode does not use (one word per 8 vectors)
-    unsigned long long* slots = ops[0].vaux;
-    *deferred = {slots, (unsigned)groups, flag};
-    const dim3 grid(8 * (sj[0].chunk + sj[1].chunk)), thr(kShortThreads);
-    const size_t lds = (size_t)vecs * (lay.k_pad + 4) * sizeof(double);
-#define OZ2_SHORT(KA, KB)                                                                                                     \
-  do {                                                                                                                        \
-    if (vecs == kShortFew)                                                                                                    \
-      hipLaunchKernelGGL((short_convert_kernel<KA, KB, kShortFew>), grid, thr, lds, st, sj[0], sj[1], conv, slots);           \
-    else                                                                                                                      \
-      hipLaunchKernelGGL((short_convert_kernel<KA, KB, kShortVecs>), grid, thr, lds, st, sj[0], sj[1], conv, slots);          \
-  } while (0)
-    const bool two_a = kappa_a > 75, two_b = kappa_b > 75;
-    if (two_a && two_b)
-      OZ2_SHORT(1, 1);
-    else if (two_a)
-      OZ2_SHORT(1, 0);
-    else if (two_b)
-      OZ2_SHORT(0, 1);
-    else
-      OZ2_SHORT(0, 0);
-#undef OZ2_SHORT
-    return hipGetLastError();
-  }
-  // Small operands: maxima, norm bounds and shifts in one launch without atomics (nothing to clear
-  // first); its per-workgroup reports become the flag word in the conversion launch.  "Small": at most 2^25 elements
-  // in both operands together (4096 x 4096 twice), where 16 vectors per workgroup are work enough for the chip
-  // and the launches saved still count.  In the modes of Section 4.1 few long vectors keep the separate launches, which give a
-  // vector several workgroups: where their number is below an eighth (mode 2 with two operands: a tenth) of their length, and that
-  // above a line, the scan's workgroups are too few and too long (whole calls, 14 moduli, scan / separate launches, us, plain
-  // operands and with the first one transposed: mode 1 256 x 256 x 8192 103 / 102 and 85 / 99, x 12000 151 / 125 and 134 / 119,
-  // x 32768 378 / 265 and 344 / 253, 64 x 64 x 10300 130 / 119 and 105 / 114, 500 x 500 x 16384 293 / 254, 1000 x 1000 x 8192
-  // 252 / 258, x 16384 500 / 469 and 432 / 442; mode 2 256 x 256 x 4096 131 / 144 and 121 / 139, x 10300 246 / 231 and 230 / 226,
-  // 500 x 500 x 10300 315 / 298 and 295 / 296, 1000 x 1000 x 16384 692 / 696 and 659 / 678; dsyrk, mode 1 order 500, 8192
-  // 138 / 121 and 109 / 116, 10000 169 / 141 and 144 / 130, order 900, 10000 218 / 194, mode 2 order 500, 10000 277 / 260 and
-  // 254 / 253, order 900, 12000 384 / 358).
   const int64_t vectors = lay.m_pad + (nops == 2 ? lay.n_pad : 0);
-  const int line = nops == 1 ? 8192 : shift_mode == OZ2_SHIFT_CAUCHY_SCHWARZ ? 12288 : 10240;
-  const int64_t few = lay.k_pad / (nops == 2 && shift_mode == OZ2_SHIFT_INT8_PRODUCT ? 10 : 8);
-  const bool few_and_long = shift_mode != OZ2_SHIFT_MAX && lay.k_pad > line && vectors <= few;
-  const bool large = vectors * lay.k_pad > ((int64_t)1 << 25);
-  const bool scan = !strassen && !large && !few_and_long;
   // what the shifts are formed from: the budgets of the operands, or (INT8-product mode) first the exponents 5 - e of the
   // 6-bit bounds
   int param[2];
@@ -994,7 +987,75 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
     param[1] = d == 0 ? plan.kappa : plan.kappa_sum - param[0];
   }
   const int base_mode = shift_mode == OZ2_SHIFT_CAUCHY_SCHWARZ ? 1 : 0;  // as shift_of counts them
-  if (scan) {
+  // Short vectors: everything in one launch (in the INT8-product mode: maxima and bound planes), whose reports the caller's
+  // GEMM launch turns into the flag word (deferred != nullptr: the caller sees to that).
+  const bool two_a = param[0] + base_mode > 75, two_b = param[1] + base_mode > 75;
+  const int short_vecs = deferred && !thin && !strassen ? short_vectors(vectors, lay.k_pad, two_a || two_b) : 0;
+  if (short_vecs) {
+    ShortJob sj[2] = {};
+    unsigned groups = 0;
+    for (int x = 0; x < nops; ++x) {
+      const Operand& o = ops[x];
+      const unsigned nblk = (unsigned)(o.nvec_pad / short_vecs);
+      sj[x] = {o.X, o.ld, o.nvec, o.nvec_pad, o.k, o.k_pad, o.vmax, o.shifts, o.planes, param[x], o.tri,
+               o.strided ? 1 : 0, nblk, nblk / 8};
+      groups += nblk;
+    }
+    // The reports live in the auxiliary vectors (a word per two vectors or more), which nothing else needs when this launch ends
+    // stage 1; in the INT8-product mode in the product region until the next launch has folded them.
+    const bool bounds = shift_mode == OZ2_SHIFT_INT8_PRODUCT;
+    unsigned long long* slots = bounds ? reinterpret_cast<unsigned long long*>(ws + lay.off_c) : ops[0].vaux;
+    fin = {slots, groups, flag};
+    const dim3 grid(8 * (sj[0].chunk + sj[1].chunk)), thr(kShortThreads);
+    const size_t lds = (size_t)short_vecs * (lay.k_pad + 4) * sizeof(double);
+#define OZ2_SHORT_V(KA, KB, V) \
+  hipLaunchKernelGGL((short_convert_kernel<KA, KB, V>), grid, thr, lds, st, sj[0], sj[1], conv, base_mode, slots)
+#define OZ2_SHORT(KA, KB)        \
+  do {                           \
+    if (short_vecs == 8)         \
+      OZ2_SHORT_V(KA, KB, 8);    \
+    else if (short_vecs == 4)    \
+      OZ2_SHORT_V(KA, KB, 4);    \
+    else                         \
+      OZ2_SHORT_V(KA, KB, 2);    \
+  } while (0)
+    if (bounds)
+      OZ2_SHORT(2, 2);
+    else if (two_a && two_b)
+      OZ2_SHORT(1, 1);
+    else if (two_a)
+      OZ2_SHORT(1, 0);
+    else if (two_b)
+      OZ2_SHORT(0, 1);
+    else
+      OZ2_SHORT(0, 0);
+#undef OZ2_SHORT
+#undef OZ2_SHORT_V
+    if (!bounds) {
+      *deferred = fin;
+      return hipGetLastError();
+    }
+  }
+  // Small operands: maxima, norm bounds and shifts in one launch without atomics (nothing to clear
+  // first); its per-workgroup reports become the flag word in the conversion launch.  "Small": at most 2^25 elements
+  // in both operands together (4096 x 4096 twice), where 16 vectors per workgroup are work enough for the chip
+  // and the launches saved still count.  In the modes of Section 4.1 few long vectors keep the separate launches, which give a
+  // vector several workgroups: where their number is below an eighth (mode 2 with two operands: a tenth) of their length, and that
+  // above a line, the scan's workgroups are too few and too long (whole calls, 14 moduli, scan / separate launches, us, plain
+  // operands and with the first one transposed: mode 1 256 x 256 x 8192 103 / 102 and 85 / 99, x 12000 151 / 125 and 134 / 119,
+  // x 32768 378 / 265 and 344 / 253, 64 x 64 x 10300 130 / 119 and 105 / 114, 500 x 500 x 16384 293 / 254, 1000 x 1000 x 8192
+  // 252 / 258, x 16384 500 / 469 and 432 / 442; mode 2 256 x 256 x 4096 131 / 144 and 121 / 139, x 10300 246 / 231 and 230 / 226,
+  // 500 x 500 x 10300 315 / 298 and 295 / 296, 1000 x 1000 x 16384 692 / 696 and 659 / 678; dsyrk, mode 1 order 500, 8192
+  // 138 / 121 and 109 / 116, 10000 169 / 141 and 144 / 130, order 900, 10000 218 / 194, mode 2 order 500, 10000 277 / 260 and
+  // 254 / 253, order 900, 12000 384 / 358).
+  const int line = nops == 1 ? 8192 : shift_mode == OZ2_SHIFT_CAUCHY_SCHWARZ ? 12288 : 10240;
+  const int64_t few = lay.k_pad / (nops == 2 && shift_mode == OZ2_SHIFT_INT8_PRODUCT ? 10 : 8);
+  const bool few_and_long = shift_mode != OZ2_SHIFT_MAX && lay.k_pad > line && vectors <= few;
+  const bool large = vectors * lay.k_pad > ((int64_t)1 << 25);
+  const bool scan = !strassen && !large && !few_and_long;
+  if (short_vecs) {
+    // (the bound planes exist)
+  } else if (scan) {
     ScanJob sj[2] = {};
     unsigned total = 0;
     for (int x = 0; x < nops; ++x) {
@@ -1009,10 +1070,10 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
     hipLaunchKernelGGL(vector_scan_kernel, dim3(total), dim3(kScanThreads), 0, st, sj[0], sj[1], base_mode, slots);
     fin = {slots, total, flag};
   } else {
-    fill(ops[0].vmax, n_max);
+    fill(ops[0].vmax, n_max, nothing);
     if (hipError_t e = launch_max(ops, nops, st); e != hipSuccess) return e;
     if (base_mode == 1) {
-      fill(ops[0].vaux, n_aux);
+      fill(ops[0].vaux, n_aux, nothing);
       for (int x = 0; x < nops; ++x) launch_norm(ops[x], st);
     }
     shifts(base_mode, param[0], param[1], 0, 0);
@@ -1021,19 +1082,22 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
     // bound planes (in the slots of residue plane 0), their INT8 product (in the slot of product plane 0),
     // its row and column maxima, then the shifts.  In the symmetric case the product is A''A''^T and its
     // row maxima are its column maxima (those land in the unused column array).
-    {
+    if (!short_vecs) {
       const int bound[2] = {2, 2};
       if (hipError_t e = launch_convert(ops, nops, bound, false, conv, fin, st); e != hipSuccess) return e;
       fin = {nullptr, 0u, nullptr};
     }
-    fill(ops[0].vaux, n_aux);
+    fill(ops[0].vaux, n_aux, fin);
+    fin = {nullptr, 0u, nullptr};
     hipError_t e = oz2_launch_bound_gemm(lay, ws, B == nullptr, st);
     if (e != hipSuccess) return e;
     const int64_t row_blocks = (lay.m_pad + kProdRows - 1) / kProdRows;
-    const int64_t nblk = row_blocks * (int64_t)blocks_of(n, kProdCols);
+    int cols = 8;  // as few as leave a row 128 atomic maxima or fewer
+    while (cols < 64 && (n + cols - 1) / cols > 128) cols *= 2;
+    const int64_t nblk = row_blocks * (int64_t)blocks_of(n, cols);
     if (nblk >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
     hipLaunchKernelGGL(prodmax_kernel, dim3((unsigned)nblk), thr, 0, st, reinterpret_cast<const int*>(ws + lay.off_c),
-                       lay.m_pad, m, n, row_blocks, ops[0].vaux, ops[1].vaux);
+                       lay.m_pad, m, n, row_blocks, cols, ops[0].vaux, ops[1].vaux);
     shifts(2, plan.budget2, plan.budget2, -d, d);
     xbits[0] = plan.budget2 / 2 + 7 - d;  // |x'| < 2^(e + 1 + sa) <= 2^(floor(b/2) + 6 -+ d)
     xbits[1] = plan.budget2 / 2 + 7 + d;

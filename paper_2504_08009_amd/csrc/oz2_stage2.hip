@@ -768,6 +768,13 @@ hipError_t launch_gemm(const Oz2Layout& lay, char* ws, int num_moduli, const int
       g.skip_flag = reinterpret_cast<const unsigned long long*>(ws + lay.off_flags);
     }
   }
+  // The round synchronisation needs its counters cleared before the launch, which comes with forming the flag word.
+  if (g.xcd_sync != nullptr && g.fin.slots) {
+    if ((e = oz2_launch_finish_scan(fin, st)) != hipSuccess) return e;
+    g.fin = {nullptr, 0u, nullptr};
+    g.fin_stops = 0;
+    if (check_flag) g.skip_flag = reinterpret_cast<const unsigned long long*>(ws + lay.off_flags);
+  }
   const dim3 grd(grid), thr(kThreads);
   // tiles walked in one k-block (the usual case) take the instantiation without the reduction between k-blocks
   const bool kblocked = g.ktiles_per_block < g.ktiles;

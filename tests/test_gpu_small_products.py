@@ -61,6 +61,63 @@ def test_one_pass_conversion_by_four_and_by_eight_vectors(m, n, N, k):
     assert flag == 0 and np.array_equal(got, ref)
 
 
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("m,n,k,N", [(60, 40, 1025, 3), (300, 200, 1999, 14), (700, 500, 2496, 9), (1200, 100, 2497, 5), (40, 700, 3393, 15),
+                                     (2000, 100, 4992, 4), (70, 300, 4993, 16), (256, 130, 6209, 22), (30, 20, 9984, 21), (30, 20, 9985, 21)])
+def test_one_pass_conversion_of_long_vectors(m, n, k, N, mode):
+    """Two, four and eight vectors per workgroup, the longest that fit and one more, in every shift mode; inner dimensions at which the
+    large tiles' round synchronisation needs its counters cleared ahead."""
+    rng = np.random.default_rng(3 * m + n + k)
+    ta, tb = [("N", "N"), ("T", "T"), ("N", "T")][(k + mode) % 3]
+    print("long: m=%d n=%d k=%d N=%d mode=%d op=%s%s" % (m, n, k, N, mode, ta, tb), flush=True)
+    A = _mat(rng, *((m, k) if ta == "N" else (k, m)))
+    B = _mat(rng, *((k, n) if tb == "N" else (n, k)))
+    A[(m // 2, slice(None)) if ta == "N" else (slice(None), m // 2)] = 0.0  # an all-zero vector
+    opA, opB = np.asfortranarray(A.T if ta == "T" else A), np.asfortranarray(B.T if tb == "T" else B)
+    dA, dB, dC = _dev(A), _dev(B), _dev(np.ones((m, n), order="F"))
+    ws = oz.Workspace(m, n, k, N)
+    flags = ws.view(oz.workspace_layout(m, n, k, N)["flags"], 1, torch.int64)
+    oz.oz2_set_shift_mode(mode)
+    try:
+        args = (ta, tb, m, n, k, 1.0, dA.data_ptr(), A.shape[0], dB.data_ptr(), B.shape[0], 0.0, dC.data_ptr(), m, N)
+        oz.oz2_dgemm_ex(*args)
+        torch.cuda.synchronize()
+        assert int(flags.item()) == 0
+        assert np.array_equal(dC.cpu().numpy(), orc.dgemm(opA, opB, N, mode=mode).C)
+        dA[-1, -1] = float("nan")
+        oz.oz2_dgemm_ex(*args)
+        torch.cuda.synchronize()
+        assert int(flags.item()) == 1 and bool(torch.isnan(dC[m - 1]).all()) and bool(torch.isfinite(dC[: m - 1]).all())
+    finally:
+        oz.oz2_set_shift_mode(0)
+
+
+@pytest.mark.parametrize("k,n", [(1100, 40), (2500, 30), (3500, 20)])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("side,uplo,ta", [("L", "L", "N"), ("L", "U", "T"), ("R", "U", "N"), ("R", "L", "T"), ("L", "U", "N")])
+def test_one_pass_conversion_of_a_triangular_operand(side, uplo, ta, mode, k, n):
+    """Triangular operands whose vectors fit into LDS: NaNs in the half that is not referenced, every element against the oracle
+    on the matrix that the convention defines."""
+    rng = np.random.default_rng(k + n + mode)
+    m_, n_, N = (k, n, 12) if side == "L" else (n, k, 12)
+    A = _mat(rng, k, k)
+    T = np.tril(A) if uplo == "L" else np.triu(A)
+    A[np.triu_indices(k, 1) if uplo == "L" else np.tril_indices(k, -1)] = np.nan
+    X = _mat(rng, m_, n_)
+    opT = np.asfortranarray(T.T if ta == "T" else T)
+    ref = orc.dgemm(opT, X, N, mode=mode).C if side == "L" else orc.dgemm(X, opT, N, mode=mode).C
+    dA, dX = _dev(A), _dev(X)
+    ws = oz.Workspace(m_, n_, k, N)
+    oz.oz2_set_shift_mode(mode)
+    try:
+        oz.oz2_dtrmm(side, uplo, ta, "N", m_, n_, 1.0, dA.data_ptr(), k, dX.data_ptr(), m_, N)
+        torch.cuda.synchronize()
+    finally:
+        oz.oz2_set_shift_mode(0)
+    assert np.array_equal(dX.cpu().numpy(), ref)
+    del ws
+
+
 @pytest.mark.parametrize("delta", [30, -30])
 def test_one_operand_split_deeper_than_the_other(delta):
     """21 moduli and a bit split of 30: one operand needs the two-level split, the other does not."""
