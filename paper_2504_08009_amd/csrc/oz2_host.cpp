@@ -179,6 +179,7 @@ int oz2_build_plan(int N, int64_t k, Oz2Plan* plan) {
   Oz2CrtConsts& cc = plan->crt;
   cc.N = N;
   cc.L = L;
+  cc.joined = L == 4 && mbits <= 146 ? 1 : 0;
   Wide half = M;
   wide_divmod(half, 2);
   const double Md = wide_to_double(M);

@@ -37,6 +37,7 @@ struct Oz2ConvConsts {
 struct Oz2CrtConsts {
   int N;
   int L;                               // number of 40-bit limbs: 40*L >= bit length of M
+  int joined;                          // 1: L == 4 and M < 2^146 (up to 18 moduli), see oz2_crt_reduce
   double p[OZ2_MAX_N];
   double inv_p[OZ2_MAX_N];             // RN(1/p)
   double half_inv_p[OZ2_MAX_N];        // 0.5 * inv_p

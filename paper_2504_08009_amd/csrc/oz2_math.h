@@ -185,9 +185,10 @@ OZ2_HD void oz2_digits_to_limbs(const int* D, const double* start, double* S) {
 #pragma unroll
   for (int l = 0; l < L; ++l) {
     const int first = 5 * l, last = l + 1 < L ? 5 * l + 4 : 15;
-    double v = (double)D[last];
+    // (two digits at a time as an integer below 2^29: a shift and add in the place of a conversion and an FP64 instruction)
+    double v = (last - first) % 2 == 0 ? (double)D[last] : (double)(D[last] * 256 + D[last - 1]);
 #pragma unroll
-    for (int i = last - 1; i >= first; --i) v = fma(v, 256.0, (double)D[i]);
+    for (int i = last - 1 - (last - first) % 2; i > first; i -= 2) v = fma(v, 65536.0, (double)(D[i] * 256 + D[i - 1]));
     S[l] = v + start[l];  // the digit sums were formed on c'' - 128: start holds 128 sum_t dig in limb form
   }
 }
@@ -223,35 +224,40 @@ OZ2_HD double oz2_crt_reduce(const double* S, const Oz2CrtConsts& cc, int* e2) {
   }
   oz2_carry<L>(D);
 
-  // window of three digits led by the highest nonzero one (or the lowest three)
-  double dh = D[2], dm = D[1], dl = D[0], rest = 0.0;
+  double dh = D[2], dm = D[1], lo = D[0];
   int shift = 0;
+  if (L == 4 && cc.joined) {
+    // |X| < 2^146: the top two digits joined, dh 2^80 + dm 2^40 + lo = X with integers dh and dm.  What rounding dh loses is below
+    // 2^13 and goes to the digit below, where it is exact.
+    const double u = D[LP - 1] * 0x1p40;
+    dh = u + D[2];                             // |u| >= 2^40 > |D[2]| or u == 0: Fast2Sum
+    dm = fma(D[2] - (dh - u), 0x1p40, D[1]);
+  } else if (L > 3) {
+    // window of three digits led by the highest nonzero one (or the lowest three)
+    double rest = 0.0;
 #pragma unroll
-  for (int w = 3; w < LP; ++w) {
-    if (D[w] != 0.0) {
-      dh = D[w];
-      dm = D[w - 1];
-      dl = D[w - 2];
-      double rr = 0.0;
+    for (int w = 3; w < LP; ++w) {
+      if (D[w] != 0.0) {
+        dh = D[w];
+        dm = D[w - 1];
+        lo = D[w - 2];
+        double rr = 0.0;
 #pragma unroll
-      for (int i = 0; i <= w - 3; ++i)
-        if (D[i] != 0.0) rr = D[i];
-      rest = rr;
-      shift = OZ2_LIMB_BITS * (w - 2);
+        for (int i = 0; i <= w - 3; ++i)
+          if (D[i] != 0.0) rr = D[i];
+        rest = rr;
+        shift = OZ2_LIMB_BITS * (w - 2);
+      }
     }
+    // the digits below the window only matter through their sign: move its last one by a quarter unit
+    lo += rest > 0.0 ? 0.25 : (rest < 0.0 ? -0.25 : 0.0);
   }
-  // the digits below the window only matter through their sign: move dl by a quarter unit
-  double lo = dl + (rest > 0.0 ? 0.25 : (rest < 0.0 ? -0.25 : 0.0));
-  double hi = dh * 0x1p80, mid = dm * 0x1p40;
-  double a = hi + mid;          // |hi| >= 2^80 > |mid| or hi == 0: Fast2Sum is exact
-  double b = mid - (a - hi);
-  double tail;
-  if (b != 0.0) {
-    // |b| >= 2^40 > 2|lo|: lo can only break an exact tie of a + b; nudge b by one part in 2^52
-    tail = lo != 0.0 ? fma(fabs(b), copysign(0x1p-52, lo), b) : b;
-  } else {
-    tail = lo;
-  }
+  const double hi = dh * 0x1p80, mid = dm * 0x1p40;
+  const double a = hi + mid;          // |hi| >= |mid| (2^80 > 2^79, or dh >= 2^53 where dm is above 2^39) or hi == 0: Fast2Sum
+  const double b = mid - (a - hi);
+  // b != 0: |b| >= 2^40 > 2|lo|, so lo can only break an exact tie of a + b; nudge b by one part in 2^52
+  const double nudged = fma(fabs(b), copysign(lo != 0.0 ? 0x1p-52 : 0.0, lo), b);
+  const double tail = b != 0.0 ? nudged : lo;
   *e2 = shift;
   return a + tail;
 }

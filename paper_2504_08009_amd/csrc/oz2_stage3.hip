@@ -261,14 +261,42 @@ __global__ void __launch_bounds__(kThreads) crt_mfma_kernel(const uint8_t* __res
     for (int t = 0; t < 16; ++t)
       nx[t] = (t < N && j0 + jj < n) ? __builtin_nontemporal_load(src + (size_t)t * plane_words + (size_t)jj * (m_pad / 4)) : 0x80808080u;
   };
+  // the shifts of these rows and columns, and C where it is updated, one column ahead like the residues
+  int row_shift[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) row_shift[r] = sa[i0 + r];  // sa is padded to m_pad
+  const int col_shifts = sb[j0 + (lane & (kCrtCols - 1)) < n ? j0 + (lane & (kCrtCols - 1)) : n - 1];
+  auto mine = [&](int r, int64_t j) { return i0 + r < m && !(triangle == 1 && i0 + r < j) && !(triangle == 2 && i0 + r > j); };
+  auto all_mine = [&](int64_t j) { return i0 + 4 <= m && (triangle == 0 || (triangle == 1 && i0 >= j) || (triangle == 2 && i0 + 3 <= j)); };
+  double old[4] = {0.0, 0.0, 0.0, 0.0};
+  auto fetch_c = [&](int jj) {
+    const int64_t j = j0 + jj;
+    if (beta == 0.0 || j >= n) return;  // C is not read when beta is zero (BLAS convention)
+    const double* p = C + i0 + j * ldc;
+    if (all_mine(j) && (reinterpret_cast<uintptr_t>(p) & 15) == 0) {
+      const double2 lo = *reinterpret_cast<const double2*>(p), hi = *reinterpret_cast<const double2*>(p + 2);
+      old[0] = lo.x, old[1] = lo.y, old[2] = hi.x, old[3] = hi.y;
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (mine(r, j)) old[r] = p[r];
+    }
+  };
   fetch(0);
+  fetch_c(0);
   for (int jj = 0; jj < kCrtCols; ++jj) {
     const int64_t j = j0 + jj;
     if (j >= n) break;  // uniform
     unsigned x[16];
 #pragma unroll
     for (int t = 0; t < 16; ++t) x[t] = nx[t] ^ 0x80808080u;  // c'' - 128 as signed bytes
-    if (jj + 1 < kCrtCols) fetch(jj + 1);
+    double now[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) now[r] = old[r];
+    if (jj + 1 < kCrtCols) {
+      fetch(jj + 1);
+      fetch_c(jj + 1);
+    }
     // 16 words [modulus](4 rows) -> 4 operands [row](16 moduli)
     v4i_t y[4];
 #pragma unroll
@@ -282,7 +310,7 @@ __global__ void __launch_bounds__(kThreads) crt_mfma_kernel(const uint8_t* __res
       y[2][g] = (int)__builtin_amdgcn_perm(d, b, 0x05040100u);
       y[3][g] = (int)__builtin_amdgcn_perm(d, b, 0x07060302u);
     }
-    const int sbj = sb[j];
+    const int sbj = __builtin_amdgcn_readlane(col_shifts, jj);
     double out[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -300,25 +328,20 @@ __global__ void __launch_bounds__(kThreads) crt_mfma_kernel(const uint8_t* __res
       oz2_digits_to_limbs<L>(D, dg.sinit, S);
       int e2;
       const double xv = oz2_crt_reduce<L>(S, cc, &e2);
-      out[r] = ldexp(xv, e2 - sa[i0 + r] - sbj);
+      out[r] = ldexp(xv, e2 - row_shift[r] - sbj);
     }
     double* dst = C + i0 + j * ldc;
     if (alpha != 1.0 || beta != 0.0) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const bool mine = i0 + r < m && !(triangle == 1 && i0 + r < j) && !(triangle == 2 && i0 + r > j);
-        const double tt = (beta == 0.0 || !mine) ? 0.0 : beta * dst[r];
-        out[r] = fma(alpha, out[r], tt);
-      }
+      for (int r = 0; r < 4; ++r) out[r] = fma(alpha, out[r], beta == 0.0 ? 0.0 : beta * now[r]);
     }
-    const bool whole = triangle == 0 || (triangle == 1 && i0 >= j) || (triangle == 2 && i0 + 3 <= j);
-    if (whole && i0 + 4 <= m && ((reinterpret_cast<uintptr_t>(dst) & 15) == 0)) {
+    if (all_mine(j) && ((reinterpret_cast<uintptr_t>(dst) & 15) == 0)) {
       *reinterpret_cast<double2*>(dst) = make_double2(out[0], out[1]);
       *reinterpret_cast<double2*>(dst + 2) = make_double2(out[2], out[3]);
     } else {
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        if (i0 + r < m && !(triangle == 1 && i0 + r < j) && !(triangle == 2 && i0 + r > j)) dst[r] = out[r];
+        if (mine(r, j)) dst[r] = out[r];
     }
   }
 }
