@@ -202,12 +202,26 @@ hipError_t launch(TileArgs& g, int64_t m, int64_t n, int planes, const unsigned 
 
 #define OZ2_TILE_128 2, 2, 3, 3
 #define OZ2_TILE_64 1, 1, 4, 4
+// few workgroups per compute unit, long inner dimensions (launch_tiles)
+#define OZ2_TILE_128_ONE 2, 2, 9, 1
+#define OZ2_TILE_64_ONE 1, 1, 16, 1
+#define OZ2_TILE_64_TWO 1, 1, 9, 2
+constexpr int kDeepKtiles = 24;
+
+// tiles of a plane
+int64_t tiles_of(int64_t tile, int64_t m, int64_t n, int triangle) {
+  const int64_t tm = (m + tile - 1) / tile, tn = (n + tile - 1) / tile;
+  return triangle ? tm * (tn + 1) / 2 : tm * tn;
+}
 
 }  // namespace
 
 hipError_t oz2_gemm_tiles_setup() {
   hipError_t e = set_lds<OZ2_TILE_128>();
-  return e == hipSuccess ? set_lds<OZ2_TILE_64>() : e;
+  if (e == hipSuccess) e = set_lds<OZ2_TILE_64>();
+  if (e == hipSuccess) e = set_lds<OZ2_TILE_64_ONE>();
+  if (e == hipSuccess) e = set_lds<OZ2_TILE_64_TWO>();
+  return e == hipSuccess ? set_lds<OZ2_TILE_128_ONE>() : e;
 }
 
 static hipError_t launch_tiles(int tile, const Oz2Plan& plan, const Oz2Layout& lay, char* ws, int64_t m, int64_t n, int triangle,
@@ -228,11 +242,22 @@ static hipError_t launch_tiles(int tile, const Oz2Plan& plan, const Oz2Layout& l
   g.fin = fin;
   const unsigned long long* flag = check_flag ? reinterpret_cast<const unsigned long long*>(ws + lay.off_flags) : nullptr;
   for (int t = 0; t < plan.N; ++t) g.fold[t] = oz2_fold_consts(plan.moduli[t]);
-  return tile == 64 ? launch<OZ2_TILE_64>(g, m, n, plan.N, flag, st) : launch<OZ2_TILE_128>(g, m, n, plan.N, flag, st);
+  // Where a compute unit gets one or two workgroups, the copies of a long inner dimension go as far ahead as the LDS allows: with two
+  // k-tiles in flight the loop waits for them (whole calls, us: 14 moduli 200 x 200 x 10000 106.3 -> 96.5, 16 moduli 300 x 300 x 2000
+  // 38.3 -> 33.3 and x 5000 64.1 -> 53.9, with the smaller tiles in part, dsyrk 500 x 3000 49.5 -> 43.5).
+  const int64_t total = tiles_of(tile, m, n, triangle) * plan.N, cus = oz2_gemm_cus();
+  const bool deep = g.ktiles >= kDeepKtiles;
+  if (tile == 64) {
+    if (deep && total <= cus) return launch<OZ2_TILE_64_ONE>(g, m, n, plan.N, flag, st);
+    if (deep && total <= 2 * cus) return launch<OZ2_TILE_64_TWO>(g, m, n, plan.N, flag, st);
+    return launch<OZ2_TILE_64>(g, m, n, plan.N, flag, st);
+  }
+  if (deep && total <= cus) return launch<OZ2_TILE_128_ONE>(g, m, n, plan.N, flag, st);
+  return launch<OZ2_TILE_128>(g, m, n, plan.N, flag, st);
 }
 
 // Which kernel's tiles: 64 or 128 (this file) or 256 (oz2_stage2.hip).  64 x 64 when every tile gets a compute unit
-// of its own.  Otherwise the smaller of two estimates in nanoseconds, whose coefficients are measured times per tile and
+// of its own, or half of one where the inner dimension is long.  Otherwise the smaller of two estimates in nanoseconds, whose coefficients are measured times per tile and
 // compute unit (a k-tile, and the rest): rounds of the chip with 256 x 256 tiles, which compute the padding, against
 // 128 x 128 tiles, of which a compute unit holds three.  Whole calls, 128 against 256 (us): 14 moduli 512^3 24 / 29,
 // 700^3 34 / 37, 1024^3 51 / 49, 1024 x 1024 x 2048 87 / 80, 2048^3 212 / 200, 300 x 3000 x 1000 57 / 67, 16 moduli
@@ -243,12 +268,8 @@ static hipError_t launch_tiles(int tile, const Oz2Plan& plan, const Oz2Layout& l
 // 1030 x 3420 x 38226 2375 / 2236, 17 moduli 1509 x 700 x 53536 2129 / 1981).
 static int tile_size(int64_t m, int64_t n, int64_t k_pad, int num_moduli, int triangle, int krange) {
   const int64_t cus = oz2_gemm_cus();
-  auto rounds = [&](int64_t tile) {
-    const int64_t tm = (m + tile - 1) / tile, tn = (n + tile - 1) / tile;
-    const int64_t tiles = (triangle ? tm * (tn + 1) / 2 : tm * tn) * num_moduli;
-    return (tiles + cus - 1) / cus;
-  };
-  if (rounds(64) <= 1) return 64;
+  auto rounds = [&](int64_t tile) { return (tiles_of(tile, m, n, triangle) * num_moduli + cus - 1) / cus; };
+  if (rounds(64) <= (k_pad / BK >= kDeepKtiles ? 2 : 1)) return 64;
   const int64_t ktiles = krange == OZ2_KRANGE_ALL ? k_pad / BK : (k_pad / BK + 1) / 2;
   const int64_t per_ktile = 270 + (ktiles < 200 ? 0 : ktiles > 445 ? 35 : (ktiles - 200) / 7);
   return rounds(128) * (per_ktile * ktiles + 600) + 3000 < rounds(256) * (720 * ktiles + 4500) ? 128 : 256;
