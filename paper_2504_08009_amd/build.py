@@ -58,15 +58,18 @@ def named_register_faults(assembly):
             continue
         if code.startswith(("scratch_", "buffer_load", "buffer_store")):
             faults.append((kernel, code))
-        for kind, single, low, offset, high in re.findall(r"\b([va])(?:(\d+)\b|\[(\d+)(\+\d+)?(?::(\d+))?\])", code):
-            first = int(single or low)
-            last = int(high or first)
+        for found in re.finditer(r"\b([va])(?:(\d+)\b|\[(0x[0-9a-f]+|\d+)(\+\d+)?(?::(0x[0-9a-f]+|\d+))?\])", code):
+            kind, single, low, offset, high = found.groups()
+            first = int(single or low, 0)
+            last = int(high, 0) if high else first
             if kind == "v" and last < NAMED_VGPR:
                 continue
-            # a statement of the source: one whole tile of sixteen, or one register counted from a tile's first
+            # a statement of the source: a whole tile, as the result or the accumulator of a product, or one register counted from
+            # a tile's first
             base = NAMED_VGPR if kind == "v" else NAMED_AGPR
-            tile = first >= base and (first - base) % 16 == 0
-            if inside and tile and (offset or last == first + 15):
+            count = last - first + 1
+            tile = count in (4, 16) and (first - base) % count == 0 and code[:found.start()].count(",") in (0, 3)
+            if inside and first >= base and (tile or (offset and (first - base) % 4 == 0)):
                 continue
             faults.append((kernel, code))
     if not kernels:

@@ -1,5 +1,5 @@
 // Stage 2 of Ozaki scheme II on gfx950: Algorithm 1 line 6, C'_t = A'_t B'_t for every modulus t with
-// INT8 operands and INT32 accumulation on the matrix cores (v_mfma_i32_32x32x32_i8).
+// INT8 operands and INT32 accumulation on the matrix cores (v_mfma_i32_16x16x64_i8).
 //
 // Operand layout (written by stage 1): each residue plane is stored in blocks of 256 rows x 64 bytes of
 // the inner dimension, every block contiguous (16 KiB): element (row, l) of plane t lives at
@@ -11,16 +11,21 @@
 // one byte (Algorithm 1 line 7 taken in the epilogue; four times less to write here and to read in stage 3).
 //
 // One workgroup (4 waves, one per SIMD) computes a 256 x 256 tile of one modulus.  Each wave owns a
-// 128 x 128 sub-tile = 4 x 4 MFMA tiles of 32 x 32 (256 accumulator registers).  The inner dimension is
+// 128 x 128 sub-tile = 8 x 8 MFMA tiles of 16 x 16 (256 accumulator registers).  The inner dimension is
 // walked in k-tiles of 64 bytes through a ring of four LDS stages (32 KiB each).  Both operands of a
 // k-tile are copied global -> LDS with 16-byte direct loads (no VGPR staging).  LDS rows are 64 bytes; the
 // 16-byte chunk index is XOR-swizzled with bits 2..3 of the row so that the 16 rows read together by a
 // ds_read_b128 fall on 16 different bank groups (measured: no bank conflicts).
 //
-// Schedule of one k-tile (two MFMA k-steps of 16 MFMAs): during step 0 the fragments of step 1 are read
-// from LDS; two MFMAs into step 1 one vmcnt wait + barrier makes the NEXT k-tile visible to all waves; during the rest
-// of step 1 the first fragments of that next tile are read and the 8 direct loads that refill the stage freed by the
-// barrier are issued, one LDS read per two MFMAs and one global load per two MFMAs, so that no queue
+// Which matrix instruction: under the card's power cap the products of 16 x 16 x 64 run at 4.0 POP/s on random operands with no
+// memory traffic, those of 32 x 32 x 32 at 3.5 (the larger tile moves twice the accumulator bytes per operation through the
+// register file): stage 2 of 16384^3 with 16 moduli in the Strassen form, whole calls 56.97 -> 51.8 ms, 8192^3 7.84 -> 7.40, 18 moduli
+// 8192 x 8192 x 1024 1.795 -> 1.69, 4096^3 1.167 -> 1.08; clock 1.55 -> 1.79 GHz at 8192^3.
+//
+// Schedule of one k-tile (64 MFMAs: tile rows 0-3 against all eight columns, then rows 4-7): there is one set of fragments, each
+// read again for the next k-tile after its last product.  During the first half rows 4-7 and the last column arrive; at
+// the start of the second one vmcnt wait + barrier makes the NEXT k-tile visible to all waves; during the rest its rows 0-3 and columns
+// 0-6 are read and the 8 direct loads that refill the stage freed by the barrier are issued, spread out so that no queue
 // fills up and stalls MFMA issue.
 //
 // INT32 accumulation is exact for fewer than 2^17 terms (Section 3.1).  For longer inner dimensions the
@@ -56,7 +61,6 @@
 namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int BM = OZ2_TILE_M, BN = OZ2_TILE_N, BK = OZ2_TILE_K;
 static_assert(BM == 256 && BN == 256 && BK == 64, "the kernel below is written for 256 x 256 x 64 tiles");
@@ -66,9 +70,8 @@ constexpr int kStageBytes = (BM + BN) * BK;      // 32 KiB: A tile then B tile
 constexpr int kLdsBytes = NS * kStageBytes;
 constexpr int kLoads = 8;                        // direct loads per wave per k-tile
 constexpr int kGroupM = 8;
-// Products of step 1 in front of the barrier: they and the last two of step 0 cover the arrival of the last fragments
-// read, which the barrier waits for.
-constexpr int kSyncAt = 1;
+// The product behind which the barrier stands: the first ones of the second half cover the arrival of the last fragments.
+constexpr int kSyncAt = 33;
 // The tile orders below are written for the eight accelerator dies (XCDs) of the MI355X, on which the hardware
 // places workgroup i of a launch on die i % 8.
 constexpr int kXcds = 8;
@@ -107,76 +110,77 @@ __device__ __forceinline__ int reduce_mod(int c, int p, float inv_p) {
   return c - q * p;
 }
 
-// ---- The 256 accumulators of a lane live in registers by name: MFMA tile (x, y) of the wave's 4 x 4, T = x + 4 y, in
-// the ordinary registers v[112 + 16 T ...] for T < kVgprTiles and in the accumulation registers a[16 T ...] for the
+// ---- The 256 accumulators of a lane live in registers by name: MFMA tile (x, y) of the wave's 8 x 8, T = x + 8 y, in
+// the ordinary registers v[112 + 4 T ...] for T < kVgprTiles and in the accumulation registers a[4 T ...] for the
 // others.  An ordinary instruction reads the former directly, the latter only through a move of eight cycles, and
 // of the 256 ordinary registers the kernel's own code needs fewer than 112 (build.py refuses a build in which the compiler
-// uses a register named here, or scratch memory; amdgpu_num_vgpr keeps it to
-// them); every statement below names what it writes.  (As variables the accumulators were copied through ordinary
+// uses a register named here, or scratch memory; amdgpu_num_vgpr keeps it to them, and named_accumulators tells it that the kernel
+// has them).  (As variables the accumulators were copied through ordinary
 // registers and scratch memory wherever the main loop meets the code around it: up to 256 moves per tile and 20 to 1200
 // bytes of scratch per lane, depending on the form of the loop.)
 // What the compiler does not see is the distance an MFMA needs to a reader of its result (settle_acc).  Operands come
-// from LDS reads, whose arrival it waits for, and the next MFMA on the same accumulators is fifteen others away.
-constexpr int kVgprTiles = 8;
+// from LDS reads, whose arrival it waits for, and the next MFMA on the same accumulators is 63 others away.
+constexpr int kVgprTiles = 32;
 template <int T>
-struct Acc;
-#define OZ2_ACC_TILE(T, R, LO, HI, FOLD, READ, WRITE, ...)                                                      \
-  template <>                                                                                                   \
-  struct Acc<T> {                                                                                               \
-    /* acc := acc + a b */                                                                                      \
-    static __device__ __forceinline__ void add(const v4i& a, const v4i& b) {                                    \
-      asm volatile("v_mfma_i32_32x32x32_i8 " R "[" #LO ":" #HI "], %0, %1, " R "[" #LO ":" #HI "]"              \
-                   :                                                                                            \
-                   : "v"(a), "v"(b)                                                                             \
-                   : __VA_ARGS__);                                                                              \
-    }                                                                                                           \
-    /* acc := start + a b */                                                                                    \
-    template <bool RESIDUE_U8>                                                                                  \
-    static __device__ __forceinline__ void start(const v4i& a, const v4i& b) {                                  \
-      if constexpr (RESIDUE_U8)                                                                                 \
-        asm volatile("v_mfma_i32_32x32x32_i8 " R "[" #LO ":" #HI "], %0, %1, 0.15915494" : : "v"(a), "v"(b) : __VA_ARGS__); \
-      else                                                                                                      \
-        asm volatile("v_mfma_i32_32x32x32_i8 " R "[" #LO ":" #HI "], %0, %1, 0" : : "v"(a), "v"(b) : __VA_ARGS__); \
-    }                                                                                                           \
-    static __device__ __forceinline__ unsigned read(int e) {                                                    \
-      unsigned v;                                                                                               \
-      asm volatile(READ " %0, " R "[" #LO "+%1]" : "=v"(v) : "n"(e));                                           \
-      return v;                                                                                                 \
-    }                                                                                                           \
-    static __device__ __forceinline__ void write(int e, unsigned v) {                                           \
-      asm volatile(WRITE " " R "[" #LO "+%1], %0" : : "v"(v), "n"(e) : __VA_ARGS__);                            \
-    }                                                                                                           \
-    /* oz2_fold_sum; its result can be read three instructions later (settle_sums) */                          \
-    static __device__ __forceinline__ unsigned fold_sum(int e, unsigned kpack, unsigned base) {                 \
-      unsigned v;                                                                                               \
-      asm volatile(FOLD(LO) : "=&v"(v) : "v"(kpack), "v"(base), "n"(e));                                        \
-      return v;                                                                                                 \
-    }                                                                                                           \
-  };
-#define OZ2_FOLD_V(LO) "v_dot4_u32_u8 %0, v[" #LO "+%3], %1, %2"
-#define OZ2_FOLD_A(LO) "v_accvgpr_read_b32 %0, a[" #LO "+%3]\n\tv_dot4_u32_u8 %0, %0, %1, %2"
-OZ2_ACC_TILE(0, "v", 112, 127, OZ2_FOLD_V, "v_mov_b32", "v_mov_b32", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119", "v120", "v121", "v122", "v123", "v124", "v125", "v126", "v127")
-OZ2_ACC_TILE(1, "v", 128, 143, OZ2_FOLD_V, "v_mov_b32", "v_mov_b32", "v128", "v129", "v130", "v131", "v132", "v133", "v134", "v135", "v136", "v137", "v138", "v139", "v140", "v141", "v142", "v143")
-OZ2_ACC_TILE(2, "v", 144, 159, OZ2_FOLD_V, "v_mov_b32", "v_mov_b32", "v144", "v145", "v146", "v147", "v148", "v149", "v150", "v151", "v152", "v153", "v154", "v155", "v156", "v157", "v158", "v159")
-OZ2_ACC_TILE(3, "v", 160, 175, OZ2_FOLD_V, "v_mov_b32", "v_mov_b32", "v160", "v161", "v162", "v163", "v164", "v165", "v166", "v167", "v168", "v169", "v170", "v171", "v172", "v173", "v174", "v175")
-OZ2_ACC_TILE(4, "v", 176, 191, OZ2_FOLD_V, "v_mov_b32", "v_mov_b32", "v176", "v177", "v178", "v179", "v180", "v181", "v182", "v183", "v184", "v185", "v186", "v187", "v188", "v189", "v190", "v191")
-OZ2_ACC_TILE(5, "v", 192, 207, OZ2_FOLD_V, "v_mov_b32", "v_mov_b32", "v192", "v193", "v194", "v195", "v196", "v197", "v198", "v199", "v200", "v201", "v202", "v203", "v204", "v205", "v206", "v207")
-OZ2_ACC_TILE(6, "v", 208, 223, OZ2_FOLD_V, "v_mov_b32", "v_mov_b32", "v208", "v209", "v210", "v211", "v212", "v213", "v214", "v215", "v216", "v217", "v218", "v219", "v220", "v221", "v222", "v223")
-OZ2_ACC_TILE(7, "v", 224, 239, OZ2_FOLD_V, "v_mov_b32", "v_mov_b32", "v224", "v225", "v226", "v227", "v228", "v229", "v230", "v231", "v232", "v233", "v234", "v235", "v236", "v237", "v238", "v239")
-OZ2_ACC_TILE(8, "a", 128, 143, OZ2_FOLD_A, "v_accvgpr_read_b32", "v_accvgpr_write_b32", "a128", "a129", "a130", "a131", "a132", "a133", "a134", "a135", "a136", "a137", "a138", "a139", "a140", "a141", "a142", "a143")
-OZ2_ACC_TILE(9, "a", 144, 159, OZ2_FOLD_A, "v_accvgpr_read_b32", "v_accvgpr_write_b32", "a144", "a145", "a146", "a147", "a148", "a149", "a150", "a151", "a152", "a153", "a154", "a155", "a156", "a157", "a158", "a159")
-OZ2_ACC_TILE(10, "a", 160, 175, OZ2_FOLD_A, "v_accvgpr_read_b32", "v_accvgpr_write_b32", "a160", "a161", "a162", "a163", "a164", "a165", "a166", "a167", "a168", "a169", "a170", "a171", "a172", "a173", "a174", "a175")
-OZ2_ACC_TILE(11, "a", 176, 191, OZ2_FOLD_A, "v_accvgpr_read_b32", "v_accvgpr_write_b32", "a176", "a177", "a178", "a179", "a180", "a181", "a182", "a183", "a184", "a185", "a186", "a187", "a188", "a189", "a190", "a191")
-OZ2_ACC_TILE(12, "a", 192, 207, OZ2_FOLD_A, "v_accvgpr_read_b32", "v_accvgpr_write_b32", "a192", "a193", "a194", "a195", "a196", "a197", "a198", "a199", "a200", "a201", "a202", "a203", "a204", "a205", "a206", "a207")
-OZ2_ACC_TILE(13, "a", 208, 223, OZ2_FOLD_A, "v_accvgpr_read_b32", "v_accvgpr_write_b32", "a208", "a209", "a210", "a211", "a212", "a213", "a214", "a215", "a216", "a217", "a218", "a219", "a220", "a221", "a222", "a223")
-OZ2_ACC_TILE(14, "a", 224, 239, OZ2_FOLD_A, "v_accvgpr_read_b32", "v_accvgpr_write_b32", "a224", "a225", "a226", "a227", "a228", "a229", "a230", "a231", "a232", "a233", "a234", "a235", "a236", "a237", "a238", "a239")
-OZ2_ACC_TILE(15, "a", 240, 255, OZ2_FOLD_A, "v_accvgpr_read_b32", "v_accvgpr_write_b32", "a240", "a241", "a242", "a243", "a244", "a245", "a246", "a247", "a248", "a249", "a250", "a251", "a252", "a253", "a254", "a255")
-#undef OZ2_FOLD_V
-#undef OZ2_FOLD_A
-#undef OZ2_ACC_TILE
+struct Acc {
+  static constexpr bool kV = T < kVgprTiles;
+  static constexpr int kReg = kV ? 112 + 4 * T : 4 * T;
+  /* acc := acc + a b */
+  static __device__ __forceinline__ void add(const v4i& a, const v4i& b) {
+    if constexpr (kV)
+      asm volatile("v_mfma_i32_16x16x64_i8 v[%2:%3], %0, %1, v[%2:%3]" : : "v"(a), "v"(b), "n"(kReg), "n"(kReg + 3));
+    else
+      asm volatile("v_mfma_i32_16x16x64_i8 a[%2:%3], %0, %1, a[%2:%3]" : : "v"(a), "v"(b), "n"(kReg), "n"(kReg + 3));
+  }
+  /* acc := start + a b */
+  template <bool RESIDUE_U8>
+  static __device__ __forceinline__ void start(const v4i& a, const v4i& b) {
+    if constexpr (kV && RESIDUE_U8)
+      asm volatile("v_mfma_i32_16x16x64_i8 v[%2:%3], %0, %1, 0.15915494" : : "v"(a), "v"(b), "n"(kReg), "n"(kReg + 3));
+    else if constexpr (kV)
+      asm volatile("v_mfma_i32_16x16x64_i8 v[%2:%3], %0, %1, 0" : : "v"(a), "v"(b), "n"(kReg), "n"(kReg + 3));
+    else if constexpr (RESIDUE_U8)
+      asm volatile("v_mfma_i32_16x16x64_i8 a[%2:%3], %0, %1, 0.15915494" : : "v"(a), "v"(b), "n"(kReg), "n"(kReg + 3));
+    else
+      asm volatile("v_mfma_i32_16x16x64_i8 a[%2:%3], %0, %1, 0" : : "v"(a), "v"(b), "n"(kReg), "n"(kReg + 3));
+  }
+  static __device__ __forceinline__ unsigned read(int e) {
+    unsigned v;
+    if constexpr (kV)
+      asm volatile("v_mov_b32 %0, v[%1+%2]" : "=v"(v) : "n"(kReg), "n"(e));
+    else
+      asm volatile("v_accvgpr_read_b32 %0, a[%1+%2]" : "=v"(v) : "n"(kReg), "n"(e));
+    return v;
+  }
+  static __device__ __forceinline__ void write(int e, unsigned v) {
+    if constexpr (kV)
+      asm volatile("v_mov_b32 v[%1+%2], %0" : : "v"(v), "n"(kReg), "n"(e));
+    else
+      asm volatile("v_accvgpr_write_b32 a[%1+%2], %0" : : "v"(v), "n"(kReg), "n"(e));
+  }
+  /* oz2_fold_sum; its result can be read three instructions later (settle_sums) */
+  static __device__ __forceinline__ unsigned fold_sum(int e, unsigned kpack, unsigned base) {
+    unsigned v;
+    if constexpr (kV)
+      asm volatile("v_dot4_u32_u8 %0, v[%3+%4], %1, %2" : "=&v"(v) : "v"(kpack), "v"(base), "n"(kReg), "n"(e));
+    else
+      asm volatile("v_accvgpr_read_b32 %0, a[%3+%4]\n\tv_dot4_u32_u8 %0, %0, %1, %2" : "=&v"(v) : "v"(kpack), "v"(base), "n"(kReg), "n"(e));
+    return v;
+  }
+};
+#define OZ2_TEN(R, N) R #N "0", R #N "1", R #N "2", R #N "3", R #N "4", R #N "5", R #N "6", R #N "7", R #N "8", R #N "9"
+__device__ __forceinline__ void named_accumulators() {
+  asm volatile("" : : : "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119", OZ2_TEN("v", 12), OZ2_TEN("v", 13),
+               OZ2_TEN("v", 14), OZ2_TEN("v", 15), OZ2_TEN("v", 16), OZ2_TEN("v", 17), OZ2_TEN("v", 18), OZ2_TEN("v", 19),
+               OZ2_TEN("v", 20), OZ2_TEN("v", 21), OZ2_TEN("v", 22), "v230", "v231", "v232", "v233", "v234", "v235", "v236", "v237",
+               "v238", "v239", "a128", "a129", OZ2_TEN("a", 13), OZ2_TEN("a", 14), OZ2_TEN("a", 15), OZ2_TEN("a", 16),
+               OZ2_TEN("a", 17), OZ2_TEN("a", 18), OZ2_TEN("a", 19), OZ2_TEN("a", 20), OZ2_TEN("a", 21), OZ2_TEN("a", 22),
+               OZ2_TEN("a", 23), OZ2_TEN("a", 24), "a250", "a251", "a252", "a253", "a254", "a255");
+}
+#undef OZ2_TEN
 static_assert(OZ2_ACC_START == 0x3e22f983u, "the bits of 1 / (2 pi), an inline constant of the instruction");
 
-// The wait between the last MFMA of sixteen passes and the first use of a result by another instruction (19 states),
+// The wait between the last MFMA and the first use of a result by another instruction (19 states are enough for the longest ones),
 // and between a write by another instruction and the next MFMA.
 __device__ __forceinline__ void settle_acc() { asm volatile("s_nop 15\n\ts_nop 3"); }
 // The wait between a byte dot product and the first use of its result by another kind of instruction.
@@ -196,8 +200,9 @@ __device__ __forceinline__ void unrolled(F&& f) {
   }
 }
 
+// Operands of a k-tile: sixteen rows x 64 bytes each, lane l holds 16 bytes (inner positions 16 (l / 16) ..) of row l % 16.
 struct Frag {
-  v4i a[4], b[4];
+  v4i a[8], b[8];
 };
 
 // What one workgroup needs to know about a unit of work.
@@ -355,45 +360,26 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
     }
   };
 
-  // ---- LDS -> fragments: lane reads row (lane & 31) of a 32-row group, k-chunk (2 s + lane/32)
-  const int swz = (lane >> 2) & 3;
-  const int half = lane >> 5;
-  const int a_row_off = (wm * 128 + (lane & 31)) * BK;
-  const int b_row_off = BM * BK + (wn * 128 + (lane & 31)) * BK;
-  const int off_s0 = ((0 + half) ^ swz) << 4, off_s1 = ((2 + half) ^ swz) << 4;
-  auto rd = [&](Frag& F, const char* base, int coff, int q) {  // read q in 0..7, ordered by first use
-    if (q == 0)
-      F.b[0] = *reinterpret_cast<const v4i*>(base + b_row_off + coff);
-    else if (q <= 4)
-      F.a[q - 1] = *reinterpret_cast<const v4i*>(base + a_row_off + (q - 1) * 32 * BK + coff);
+  // ---- LDS -> fragments: lane reads row (lane & 15) of a 16-row group, k-chunk lane / 16
+  const int frag_off = (lane & 15) * BK + (((lane >> 4) ^ ((lane >> 2) & 3)) << 4);
+  const int a_off = wm * 128 * BK + frag_off, b_off = BM * BK + wn * 128 * BK + frag_off;
+  auto rd_a = [&](Frag& F, const char* base, int x) { F.a[x] = *reinterpret_cast<const v4i*>(base + a_off + x * 16 * BK); };
+  auto rd_b = [&](Frag& F, const char* base, int y) { F.b[y] = *reinterpret_cast<const v4i*>(base + b_off + y * 16 * BK); };
+
+  // Operand roles of v_mfma_i32_16x16x64_i8: the rows of the first operand run over the result registers
+  // (lane l, register e: row 4 (l / 16) + e), the rows of the second over the lanes (row l % 16).  First = A', second = B': the
+  // four registers of a tile hold four consecutive rows i of one column.
+  // The 64 products of a k-tile: rows of tiles 0-3 against all eight columns, then rows 4-7; within a column back and forth, so
+  // that every product shares an operand with the one before it.
+  auto mfma = [&](const Frag& F, auto qc, auto first) {
+    constexpr int q = decltype(qc)::value, y = (q >> 2) & 7, x = (q >> 5) * 4 + ((y & 1) ? 3 - (q & 3) : q & 3);
+    if constexpr (decltype(first)::value)
+      Acc<8 * y + x>::template start<RESIDUE_U8>(F.a[x], F.b[y]);
     else
-      F.b[q - 4] = *reinterpret_cast<const v4i*>(base + b_row_off + (q - 4) * 32 * BK + coff);
+      Acc<8 * y + x>::add(F.a[x], F.b[y]);
   };
 
-
-// Operand roles of v_mfma_i32_32x32x32_i8: the rows of the first operand run over the result registers
-// (lane l, register e: row 8 (e / 4) + 4 (l / 32) + e % 4), the rows of the second over the lanes (row l % 32).
-//   INT32 export: first = B' (columns j over registers), second = A' (rows i over lanes): every register is
-//   stored as 2 x 128 contiguous bytes of a column of C'.
-//   UINT8 export: first = A', second = B': each group of four registers holds four consecutive rows i of
-//   one column, i.e. the four bytes of one 32-bit store.
-  // The sixteen products of a k-step go back and forth over the rows, so that every one shares an operand with the
-  // one before it: product q is tile (q % 4 or 3 - q % 4, q / 4).
-  auto mfma = [&](const Frag& F, auto qc) {
-    constexpr int q = decltype(qc)::value, x = (q & 4) ? 3 - (q & 3) : q & 3, y = q >> 2;
-    if constexpr (RESIDUE_U8)
-      Acc<4 * y + x>::add(F.a[x], F.b[y]);
-    else
-      Acc<4 * y + x>::add(F.b[y], F.a[x]);
-  };
-  auto mfma_start = [&](const Frag& F, auto qc) {
-    constexpr int q = decltype(qc)::value, x = (q & 4) ? 3 - (q & 3) : q & 3, y = q >> 2;
-    if constexpr (RESIDUE_U8)
-      Acc<4 * y + x>::template start<true>(F.a[x], F.b[y]);
-    else
-      Acc<4 * y + x>::template start<false>(F.b[y], F.a[x]);
-  };
-
+  named_accumulators();
   prologue_loads(cur, 0);
   if (g.fin_stops && scan_found(g.fin)) {  // (the reports arrive with the first copies)
     wait_vmcnt<0>();
@@ -455,35 +441,34 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
   const int store_window = first ? 0 : NS - 2;
   first = false;
   __syncthreads();
-  Frag F0, F1;
+  // One set of fragments: each is read again for the next k-tile after its last product and, two hundred cycles or more, before its
+  // first one there.  Rows 4-7 and the last column of a k-tile arrive during its own first half.
+  Frag F;
 #pragma unroll
-  for (int q = 0; q < 8; ++q) rd(F0, lds + stage * kStageBytes, off_s0, q);
+  for (int x = 0; x < 4; ++x) rd_a(F, lds + stage * kStageBytes, x);
+#pragma unroll
+  for (int y = 0; y < 7; ++y) rd_b(F, lds + stage * kStageBytes, y);
 
   // fa, fb: where the next fetch reads (k-tile kt + NS - 1 of this tile while that exists)
   const int8_t* fa = NS - 1 < ktiles ? cur.a_wave + (size_t)(NS - 1) * (BM * BK) : cur.a_wave;
   const int8_t* fb = NS - 1 < ktiles ? cur.b_wave + (size_t)(NS - 1) * (BN * BK) : cur.b_wave;
-  // step 0 of k-tile kt: MFMAs on F0, fetch F1 = (tile kt, step 1)
-  auto fetch_f1 = [&](int kt, int q) {
-    if (q == 0 || ((q & 1) && q < 15)) rd(F1, lds + stage * kStageBytes, off_s1, (q + 1) >> 1);
-    if (q == 1 && kt + NS - 1 == ktiles) {  // the fetches run past the end of this tile from here on
-      fa = over_a;
-      fb = over_b;
-    }
-  };
-  auto step0 = [&](int kt) {
-    unrolled<16>([&](auto q) {
-      mfma(F0, q);
-      fetch_f1(kt, q);
-      __builtin_amdgcn_sched_barrier(0);
-    });
-  };
-  // step 1 of k-tile kt: MFMAs on F1, fetch F0 = (tile kt+1, step 0), issue the loads of tile kt+NS-1
-  auto step1 = [&](int kt) {
+  // k-tile kt: its products; the fragments of k-tile kt + 1; the loads of k-tile kt + NS - 1
+  auto ktile = [&](int kt, auto first) {
+    const char* base = lds + stage * kStageBytes;
     const int nstage = stage + 1 == NS ? 0 : stage + 1;
     const char* nbase = lds + nstage * kStageBytes;
     const int lstage = stage == 0 ? NS - 1 : stage - 1;  // stage of tile kt-1 == stage of tile kt+NS-1
-    unrolled<16>([&](auto q) {
-      mfma(F1, q);
+    unrolled<64>([&](auto qc) {
+      constexpr int q = decltype(qc)::value;
+      mfma(F, qc, first);
+      if constexpr (q == 1) rd_b(F, base, 7);
+      if constexpr (q >= 4 && q < 20 && q % 4 == 0) rd_a(F, base, 4 + (q - 4) / 4);
+      if constexpr (q == 22) {
+        if (kt + NS - 1 == ktiles) {  // the fetches run past the end of this tile from here on
+          fa = over_a;
+          fb = over_b;
+        }
+      }
       if constexpr (q == kSyncAt) {
         // k-tile kt+1 must be complete in LDS for every wave before anyone reads it; passing this barrier
         // also means every wave has finished reading k-tile kt-1, whose stage is refilled below.  In the first NS - 2
@@ -492,15 +477,17 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
         __syncthreads();
       }
       if constexpr (q > kSyncAt) {
-        constexpr int left = 15 - kSyncAt;  // read r and load r stand at this distance from the barrier
-        unrolled<8>([&](auto r) {
-          if constexpr (decltype(r)::value * (left - 1) / 7 + 1 == q - kSyncAt) rd(F0, nbase, off_s0, r);
-          if constexpr ((decltype(r)::value * (left - 1) + 6) / 7 + 1 == q - kSyncAt) gl(fa, fb, lstage, r);
-        });
+        constexpr int d = q - kSyncAt;  // 1 .. 30
+        // row r of the next k-tile's first half at 2, 4, 6, 8, column c (last used at product 35 + 4 c) at 10, 13 .. 28
+        if constexpr (d % 2 == 0 && d <= 8) rd_a(F, nbase, d / 2 - 1);
+        if constexpr (d >= 10 && (d - 10) % 3 == 0 && d <= 28) rd_b(F, nbase, (d - 10) / 3);
+        if constexpr (d % 3 == 0 && d <= 24) gl(fa, fb, lstage, d / 3 - 1);
       }
-      if (q == 15 && (kt + NS - 1 < ktiles || across)) {
-        fa += BM * BK;
-        fb += BN * BK;
+      if constexpr (q == 63) {
+        if (kt + NS - 1 < ktiles || across) {
+          fa += BM * BK;
+          fb += BN * BK;
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
     });
@@ -510,40 +497,31 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
   const Oz2FoldConsts& fc = g.fold[t / g.per_modulus];
   const Oz2FoldConsts fv = in_vector_registers(fc);  // ahead of the main loop, which hides their loads
   // The first products of a tile start from an inline constant of the instruction (clearing 256 accumulators takes
-  // 8 cycles each, 2000 of the tile's 30000 at k = 1024), so step 0 of k-tile 0 stands before the loop and the loop
-  // goes from step 1 to step 0 of the next k-tile.
-  unrolled<16>([&](auto q) {
-    mfma_start(F0, q);
-    fetch_f1(0, q);
-    __builtin_amdgcn_sched_barrier(0);
-  });
-  int kt = 0;
+  // 8 cycles each, 2000 of the tile's 30000 at k = 1024), so k-tile 0 stands before the loop.
+  ktile(0, std::true_type());
   int block_end = KBLOCKED ? g.ktiles_per_block : 0;
-  // The loop below starts 16 bytes past a multiple of 32.  Where it starts at one the same instructions take up to 4 % longer, in
-  // whole launches (stage 2 in the Strassen form, 16384 x 8192 x 12288, 24 moduli, ms, start modulo 64 = 0 / 16 / 32 / 48 / 56:
-  // 27.6 / 26.5 / 27.2 / 26.6 / 26.5; 8192 x 8192 x 12288, 18 moduli 9.78 / 9.51 / 9.72 / 9.50 / 9.52).  The 16 bytes are the
-  // instructions that the compiler puts between this statement and the loop.
-  asm volatile(".p2align 5");
-  while (kt + 1 < ktiles) {
-    step1(kt);
-    ++kt;
+  // Where the loop starts: the same instructions take up to 1 % longer at other places (first statement behind a multiple of 64, four
+  // bytes each: 0 / 4 / 8 / 12 instructions, 16384^3 51.76 / 51.23 / 51.67 / 51.20 ms, 4096^3 1084 / 1071 / 1078 / 1073 us).
+  asm volatile(
+      ".p2align 6\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop "
+      "0\n\ts_nop 0");
+  for (int kt = 1; kt < ktiles; ++kt) {
     if constexpr (KBLOCKED) {
       if (kt == block_end) {  // between k-blocks: bring the accumulators back near zero
         block_end += g.ktiles_per_block;
         settle_acc();
-        unrolled<16>([&](auto tile) {
+        unrolled<64>([&](auto tile) {
           constexpr int T = decltype(tile)::value;
           constexpr int start = RESIDUE_U8 ? (int)OZ2_ACC_START : 0;
-          unrolled<16>([&](auto e) {
+          unrolled<4>([&](auto e) {
             Acc<T>::write(decltype(e)::value, (unsigned)(reduce_mod((int)Acc<T>::read(decltype(e)::value) - start, fc.p, fc.inv_p) + start));
           });
         });
         settle_acc();
       }
     }
-    step0(kt);
+    ktile(kt, std::false_type());
   }
-  step1(kt);
 
   // ---- a next tile whose first copies were not fetched by the main loop above: they fly during the epilogue
   // below.  The barrier makes sure that every wave has left the main loop (all LDS reads of this tile issued) before
@@ -571,8 +549,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
     // accumulators for the next tile).  With the stores left to drain and the tile decoding on the scalar unit the
     // work between two main loops went from 13000 to 7500 cycles: GEMM of 18 moduli at 8192 x 8192 x 1024 1.31 -> 1.20 ms
     // (2.08 POP/s), of 16 at 4096^3 0.87 -> 0.85, of 14 at 2048^3 0.115 -> 0.108, of 26 at 8192^3 10.67 -> 10.50.
-    // the wave's corner of the tile (uniform over the wave) and the lane's own offset from it (column lane % 32,
-    // rows 16 half ..: below 2^32, m_pad is below 2^27)
+    // the wave's corner of the tile (uniform over the wave) and the lane's own offset from it (column lane % 16,
+    // rows 16 (lane / 16) ..: below 2^32, m_pad is below 2^27)
     uint8_t* const corner = reinterpret_cast<uint8_t*>(g.c) + (size_t)t * g.n_pad * g.m_pad +
                             ((size_t)tn * BN + wn * 128) * g.m_pad + (size_t)tm * BM + wm * 128;
     // (formed again for every tile from the lane number as the hardware counts it: a value kept across the main
@@ -580,46 +558,43 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
     unsigned start = 0u;
     asm volatile("" : "+s"(start));  // opaque zero: the count below is taken here, in every tile
     const unsigned lane_now = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, start));
-    const unsigned lane_off = (lane_now & 31u) * (unsigned)g.m_pad + 16u * (lane_now >> 5);
-    unrolled<4>([&](auto tjc) {
-      constexpr int tj = decltype(tjc)::value;
-      // w[ti][a]: rows ti*32 + 8a + 4*half + (0..3) of column j, one byte each
-      unsigned w[4][4];
-      unrolled<4>([&](auto tic) {
-        constexpr int ti = decltype(tic)::value;
-        // sixteen elements step by step: a byte dot product's result can only be read three instructions later
-        unsigned x[16];
-        unrolled<16>([&](auto e) { x[e] = Acc<4 * tj + ti>::fold_sum(decltype(e)::value, fv.kpack, fv.base); });
-        settle_sums(x);
+    const unsigned lane_off = (lane_now & 15u) * (unsigned)g.m_pad + 16u * (lane_now >> 4);
+    unrolled<8>([&](auto yc) {
+      constexpr int y = decltype(yc)::value;
+      v4i o[2];
+      unrolled<2>([&](auto hc) {
+        constexpr int x0 = 4 * decltype(hc)::value;
+        // w[x]: rows 16 (x0 + x) + 4 (lane / 16) + (0..3) of column lane % 16, one byte each; sixteen elements step by step: a
+        // byte dot product's result can only be read three instructions later
+        unsigned v[16], w[4];
+        unrolled<16>([&](auto e) { v[e] = Acc<8 * y + x0 + e / 4>::fold_sum(decltype(e)::value % 4, fv.kpack, fv.base); });
+        settle_sums(v);
 #pragma unroll
-        for (int a = 0; a < 4; ++a) w[ti][a] = oz2_fold_residues4(x + 4 * a, fv);
+        for (int x = 0; x < 4; ++x) w[x] = oz2_fold_residues4(v + 4 * x, fv);
+        // The four groups of sixteen lanes hold interleaved quarters of the same four tiles.  Transposed, group q holds the sixteen
+        // consecutive rows of tile x0 + q: one 16-byte store per lane, 64 bytes of a column side by side.
+        const auto s02 = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
+        const auto s13 = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+        const auto lo = __builtin_amdgcn_permlane16_swap(s02[0], s13[0], false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(s02[1], s13[1], false, false);
+        o[decltype(hc)::value] = v4i{(int)lo[0], (int)lo[1], (int)hi[0], (int)hi[1]};
         __builtin_amdgcn_sched_barrier(0);
       });
-      // Lanes l and l + 32 hold the two interleaved halves of the same 32 rows.  Swapping the upper half
-      // of w[ti][a] with the lower half of w[ti][a+2] leaves lane l with rows 0..15 and lane l + 32 with
-      // rows 16..31 of the 32-row group, 16 contiguous bytes each: one 16-byte store per lane and group,
-      // issued together so that the cache lines of the column are complete at once.
-      uint8_t* cj = corner + (size_t)(tj * 32) * g.m_pad;  // uniform; + ti*32 + lane_off below
-#pragma unroll
-      for (int ti = 0; ti < 4; ++ti) {
-        const auto s0 = __builtin_amdgcn_permlane32_swap(w[ti][0], w[ti][2], false, false);
-        const auto s1 = __builtin_amdgcn_permlane32_swap(w[ti][1], w[ti][3], false, false);
-        v4i o = {(int)s0[0], (int)s0[1], (int)s1[0], (int)s1[1]};
-        *reinterpret_cast<v4i*>(cj + ti * 32 + lane_off) = o;
-      }
+      // both halves of a column together, so that its cache lines are complete at once
+      uint8_t* cj = corner + (size_t)(y * 16) * g.m_pad;  // uniform; + 64 h + lane_off below
+      *reinterpret_cast<v4i*>(cj + lane_off) = o[0];
+      *reinterpret_cast<v4i*>(cj + 64 + lane_off) = o[1];
       __builtin_amdgcn_sched_barrier(0);
     });
   } else {
-    // lane holds row i = lane % 32 of a 32 x 32 tile, register e column 8 (e / 4) + 4 (lane / 32) + e % 4
-    const size_t row = (size_t)tm * BM + wm * 128 + (lane & 31);       // + ti*32
-    const size_t col0 = (size_t)tn * BN + wn * 128 + 4 * half;         // + tj*32 + 8*(e/4) + e%4
-    int* plane = g.c + (size_t)t * g.n_pad * g.m_pad + row;
-    unrolled<4>([&](auto tjc) {
-      unrolled<4>([&](auto tic) {
-        unrolled<16>([&](auto ec) {
-          constexpr int tj = decltype(tjc)::value, ti = decltype(tic)::value, e = decltype(ec)::value;
-          plane[(col0 + tj * 32 + 8 * (e >> 2) + (e & 3)) * g.m_pad + ti * 32] = (int)Acc<4 * tj + ti>::read(e);
-        });
+    // lane holds rows 4 (lane / 16) .. + 3 of column lane % 16 of a tile: one 16-byte store
+    int* plane = g.c + ((size_t)t * g.n_pad + (size_t)tn * BN + wn * 128 + (lane & 15)) * g.m_pad + (size_t)tm * BM + wm * 128 + 4 * (lane >> 4);
+    unrolled<8>([&](auto yc) {
+      unrolled<8>([&](auto xc) {
+        constexpr int x = decltype(xc)::value, y = decltype(yc)::value;
+        typedef Acc<8 * y + x> A;
+        *reinterpret_cast<v4i*>(plane + (size_t)(y * 16) * g.m_pad + x * 16) =
+            v4i{(int)A::read(0), (int)A::read(1), (int)A::read(2), (int)A::read(3)};
       });
     });
   }
