@@ -56,7 +56,8 @@ def named_register_faults(assembly):
         code = line.split(";")[0].split("//")[0].strip()
         if not code or code.startswith("."):
             continue
-        if code.startswith(("scratch_", "buffer_load", "buffer_store")):
+        # M0 holds the target of the copies into LDS between statements of the source
+        if code.startswith(("scratch_", "buffer_load", "buffer_store")) or (not inside and re.search(r"\bm0\b", code)):
             faults.append((kernel, code))
         for found in re.finditer(r"\b([va])(?:(\d+)\b|\[(0x[0-9a-f]+|\d+)(\+\d+)?(?::(0x[0-9a-f]+|\d+))?\])", code):
             kind, single, low, offset, high = found.groups()

@@ -19,6 +19,15 @@ __device__ __forceinline__ void load_to_lds_16(const int8_t* base, unsigned voff
       : "memory", "m0");
 }
 
+// The same in two steps, for several loads to one place: M0 once, then loads whose OFFSET counts for the source and for the target.
+// Nothing else in the kernel may use M0 between them (build.py looks).
+__device__ __forceinline__ void set_lds_target(unsigned lds_addr) { asm volatile("s_mov_b32 m0, %0" : : "s"(lds_addr) : "m0"); }
+template <int OFFSET>
+__device__ __forceinline__ void load_to_lds_target(const int8_t* base, unsigned voff) {
+  static_assert(0 <= OFFSET && OFFSET < 4096, "twelve bits");
+  asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" : : "v"(voff), "s"(base), "n"(OFFSET) : "memory");
+}
+
 // s_waitcnt vmcnt(N) only (gfx9 encoding: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8)
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {

@@ -26,7 +26,9 @@
 // read again for the next k-tile after its last product.  During the first half rows 4-7 and the last column arrive; at
 // the start of the second one vmcnt wait + barrier makes the NEXT k-tile visible to all waves; during the rest its rows 0-3 and columns
 // 0-6 are read and the 8 direct loads that refill the stage freed by the barrier are issued, spread out so that no queue
-// fills up and stalls MFMA issue.
+// fills up.  A product occupies the matrix core for 16 cycles and any other instruction the issue of the one wave for four or five, so
+// not more than two or three stand between two products: 130 instructions per k-tile, one M0 for four direct loads, scalar arithmetic in
+// the first half (175, six of them around every direct load, before: 8192^3 7.36 -> 6.90 ms a call, 16384^3 50.5 -> 47.5, 4096^3 1.073 -> 1.039).
 //
 // INT32 accumulation is exact for fewer than 2^17 terms (Section 3.1).  For longer inner dimensions the
 // accumulators are reduced modulo p_t every `kblock` bytes of k (kblock <= 65536, UINT8 residues: 61440), which keeps them below
@@ -68,6 +70,7 @@ constexpr int kThreads = 256;
 constexpr int NS = 4;                            // LDS stages
 constexpr int kStageBytes = (BM + BN) * BK;      // 32 KiB: A tile then B tile
 constexpr int kLdsBytes = NS * kStageBytes;
+static_assert((kLdsBytes & (kLdsBytes - 1)) == 0, "the ring of stages wraps by a mask");
 constexpr int kLoads = 8;                        // direct loads per wave per k-tile
 constexpr int kGroupM = 8;
 // The product behind which the barrier stands: the first ones of the second half cover the arrival of the last fragments.
@@ -362,9 +365,10 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
 
   // ---- LDS -> fragments: lane reads row (lane & 15) of a 16-row group, k-chunk lane / 16
   const int frag_off = (lane & 15) * BK + (((lane >> 4) ^ ((lane >> 2) & 3)) << 4);
-  const int a_off = wm * 128 * BK + frag_off, b_off = BM * BK + wn * 128 * BK + frag_off;
-  auto rd_a = [&](Frag& F, const char* base, int x) { F.a[x] = *reinterpret_cast<const v4i*>(base + a_off + x * 16 * BK); };
-  auto rd_b = [&](Frag& F, const char* base, int y) { F.b[y] = *reinterpret_cast<const v4i*>(base + b_off + y * 16 * BK); };
+  const unsigned a_base = lds_base + wm * 128 * BK + frag_off, b_base = lds_base + BM * BK + wn * 128 * BK + frag_off;
+  typedef const __attribute__((address_space(3))) v4i* LdsFrag;
+  auto rd_a = [&](Frag& F, unsigned at, int x) { F.a[x] = *(LdsFrag)(at + x * 16 * BK); };
+  auto rd_b = [&](Frag& F, unsigned at, int y) { F.b[y] = *(LdsFrag)(at + y * 16 * BK); };
 
   // Operand roles of v_mfma_i32_16x16x64_i8: the rows of the first operand run over the result registers
   // (lane l, register e: row 4 (l / 16) + e), the rows of the second over the lanes (row l % 16).  First = A', second = B': the
@@ -387,7 +391,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
   }
   bool first = true;
   int round = 0;
-  int stage = 0;  // stage that holds k-tile 0 of the current tile
+  unsigned soff = 0;  // first byte of the stage that holds k-tile 0 of the current tile
   const int xcd = blockIdx.x % kXcds;
   for (;;) {
   const int ktiles = cur.ktiles;
@@ -444,30 +448,55 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
   // One set of fragments: each is read again for the next k-tile after its last product and, two hundred cycles or more, before its
   // first one there.  Rows 4-7 and the last column of a k-tile arrive during its own first half.
   Frag F;
+  unsigned ra = a_base + soff, rb = b_base + soff;  // where this lane's fragments of the current k-tile start
 #pragma unroll
-  for (int x = 0; x < 4; ++x) rd_a(F, lds + stage * kStageBytes, x);
+  for (int x = 0; x < 4; ++x) rd_a(F, ra, x);
 #pragma unroll
-  for (int y = 0; y < 7; ++y) rd_b(F, lds + stage * kStageBytes, y);
+  for (int y = 0; y < 7; ++y) rd_b(F, rb, y);
 
-  // fa, fb: where the next fetch reads (k-tile kt + NS - 1 of this tile while that exists)
+  // fa, fb: where the next fetch reads (k-tile kt + NS - 1 of this tile while that exists), and its step from k-tile to k-tile
   const int8_t* fa = NS - 1 < ktiles ? cur.a_wave + (size_t)(NS - 1) * (BM * BK) : cur.a_wave;
   const int8_t* fb = NS - 1 < ktiles ? cur.b_wave + (size_t)(NS - 1) * (BN * BK) : cur.b_wave;
-  // k-tile kt: its products; the fragments of k-tile kt + 1; the loads of k-tile kt + NS - 1
+  const unsigned over_step = across ? BM * BK : 0;
+  unsigned fstep = NS - 1 < ktiles ? BM * BK : over_step;
+  // k-tile kt: its products; the fragments of k-tile kt + 1; the loads of k-tile kt + NS - 1.  A product takes the matrix core 16
+  // cycles and every other instruction four or five of issue, so that not more than two stand between products.
   auto ktile = [&](int kt, auto first) {
-    const char* base = lds + stage * kStageBytes;
-    const int nstage = stage + 1 == NS ? 0 : stage + 1;
-    const char* nbase = lds + nstage * kStageBytes;
-    const int lstage = stage == 0 ? NS - 1 : stage - 1;  // stage of tile kt-1 == stage of tile kt+NS-1
+    unsigned noff, na, nb, fill;
     unrolled<64>([&](auto qc) {
       constexpr int q = decltype(qc)::value;
       mfma(F, qc, first);
-      if constexpr (q == 1) rd_b(F, base, 7);
-      if constexpr (q >= 4 && q < 20 && q % 4 == 0) rd_a(F, base, 4 + (q - 4) / 4);
-      if constexpr (q == 22) {
-        if (kt + NS - 1 == ktiles) {  // the fetches run past the end of this tile from here on
-          fa = over_a;
-          fb = over_b;
-        }
+      if constexpr (q == 1) rd_b(F, rb, 7);
+      if constexpr (q >= 4 && q < 20 && q % 4 == 0) rd_a(F, ra, 4 + (q - 4) / 4);
+      // (each statement pinned to its place: the compiler would collect them in one)
+      if constexpr (q == 18) {
+        noff = (soff + kStageBytes) & (kLdsBytes - 1);
+        asm volatile("" : "+s"(noff));
+      }
+      if constexpr (q == 20) {
+        na = a_base + noff;
+        asm volatile("" : "+v"(na));
+      }
+      if constexpr (q == 21) {
+        nb = b_base + noff;
+        asm volatile("" : "+v"(nb));
+      }
+      if constexpr (q == 23) {
+        fill = lds_wave + ((soff + (NS - 1) * kStageBytes) & (kLdsBytes - 1));  // k-tile kt - 1's stage
+        asm volatile("" : "+s"(fill));
+      }
+      // from k-tile ktiles - NS + 1 on the fetches run past the end of this tile
+      if constexpr (q == 25) {
+        fa = kt + NS - 1 == ktiles ? over_a : fa;
+        asm volatile("" : "+s"(fa));
+      }
+      if constexpr (q == 27) {
+        fb = kt + NS - 1 == ktiles ? over_b : fb;
+        asm volatile("" : "+s"(fb));
+      }
+      if constexpr (q == 29) {
+        fstep = kt + NS - 1 == ktiles ? over_step : fstep;
+        asm volatile("" : "+s"(fstep));
       }
       if constexpr (q == kSyncAt) {
         // k-tile kt+1 must be complete in LDS for every wave before anyone reads it; passing this barrier
@@ -476,22 +505,31 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
         wait_vmcnt_unless_below<(NS - 3) * kLoads, (NS - 3) * kLoads + kStores>(kt, store_window);
         __syncthreads();
       }
-      if constexpr (q > kSyncAt) {
-        constexpr int d = q - kSyncAt;  // 1 .. 30
-        // row r of the next k-tile's first half at 2, 4, 6, 8, column c (last used at product 35 + 4 c) at 10, 13 .. 28
-        if constexpr (d % 2 == 0 && d <= 8) rd_a(F, nbase, d / 2 - 1);
-        if constexpr (d >= 10 && (d - 10) % 3 == 0 && d <= 28) rd_b(F, nbase, (d - 10) / 3);
-        if constexpr (d % 3 == 0 && d <= 24) gl(fa, fb, lstage, d / 3 - 1);
-      }
+      // rows of the next k-tile's first half, then its columns (c is used for the last time at product 35 + 4 c)
+      if constexpr (q == 35) rd_a(F, na, 0);
+      if constexpr (q == 37) rd_a(F, na, 1);
+      if constexpr (q == 40) rd_a(F, na, 2);
+      if constexpr (q == 43) rd_a(F, na, 3);
+      if constexpr (q == 44) rd_b(F, nb, 0);
+      if constexpr (q == 47) rd_b(F, nb, 1);
+      if constexpr (q == 50) rd_b(F, nb, 2);
+      if constexpr (q == 53) rd_b(F, nb, 3);
+      if constexpr (q == 55) rd_b(F, nb, 4);
+      if constexpr (q == 58) rd_b(F, nb, 5);
+      if constexpr (q == 60) rd_b(F, nb, 6);
+      if constexpr (q == 34) set_lds_target(fill);
+      if constexpr (q == 46) set_lds_target(fill + BM * BK);
+      if constexpr (q >= 36 && q <= 45 && q % 3 == 0) load_to_lds_target<(q - 36) / 3 * 1024>(fa, voff);
+      if constexpr (q >= 48 && q <= 57 && q % 3 == 0) load_to_lds_target<(q - 48) / 3 * 1024>(fb, voff);
+      if constexpr (q == 61) fa += fstep;
+      if constexpr (q == 62) fb += fstep;
       if constexpr (q == 63) {
-        if (kt + NS - 1 < ktiles || across) {
-          fa += BM * BK;
-          fb += BN * BK;
-        }
+        soff = noff;
+        ra = na;
+        rb = nb;
       }
       __builtin_amdgcn_sched_barrier(0);
     });
-    stage = nstage;
   };
 
   const Oz2FoldConsts& fc = g.fold[t / g.per_modulus];
@@ -525,11 +563,11 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
 
   // ---- a next tile whose first copies were not fetched by the main loop above: they fly during the epilogue
   // below.  The barrier makes sure that every wave has left the main loop (all LDS reads of this tile issued) before
-  // stages refill.  `stage` is by now the stage after this tile's last k-tile, where the next tile starts.
+  // stages refill.  `soff` is by now the stage after this tile's last k-tile, where the next tile starts.
   if (nxt.valid) {
     if (!across) {
       __syncthreads();
-      prologue_loads(nxt, stage);
+      prologue_loads(nxt, (int)(soff / kStageBytes));
     }
     if constexpr (EARLY_ARRIVAL) {
       // count in for the next round now: the others then wait for this workgroup's main loop only, not for its
