@@ -581,7 +581,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
   settle_acc();
   if (RESIDUE_U8) {
     // Algorithm 1 line 7 here: c'' = c' mod p in [0, p), four residues per 32-bit word.  Lane holds column
-    // j = lane % 32 of a 32 x 32 tile, each group of four registers four consecutive rows i.
+    // j = lane % 16 of a 16 x 16 tile, its four registers four consecutive rows i.
     // Bound by instruction issue, one wave per SIMD: 3.25 instructions of 5 cycles per element, and the 8-cycle move for
     // the half that sits in accumulation registers (before: seven, the move for all, and 2000 cycles to clear the
     // accumulators for the next tile).  With the stores left to drain and the tile decoding on the scalar unit the
