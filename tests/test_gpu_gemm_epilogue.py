@@ -12,6 +12,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 import paper_2504_08009_amd as oz
+from oracle import oracle as orc
 
 N = 26
 
@@ -121,4 +122,30 @@ def test_thin_products_of_the_longest_sums(first):
     got = dC.cpu().numpy()
     ref = np.array([[float(k * x * y) for x in va] for y in vb])
     assert np.array_equal(got if first else got.T, ref)
+    del ws
+
+
+@pytest.mark.parametrize("int32", [True, False])
+@pytest.mark.parametrize("k", [1, 64, 65, 130, 193, 257, 321, 400, 513])
+def test_large_tiles_with_few_k_tiles_several_per_workgroup(k, int32):
+    """The main loop of the large tiles fetches across the ends of tiles that are shorter than its ring of stages, as long, and longer:
+    inner dimensions of one k-tile to nine, more tiles than compute units, both result formats, ragged last tiles."""
+    m, n, N = 2299, 2227, 12
+    rng = np.random.default_rng(k)
+    print("large tiles: k=%d int32=%s" % (k, int32), flush=True)
+    A = np.asfortranarray(rng.standard_normal((m, k)))
+    B = np.asfortranarray(rng.standard_normal((k, n)))
+    dA = torch.from_numpy(np.ascontiguousarray(A.T)).cuda().t()
+    dB = torch.from_numpy(np.ascontiguousarray(B.T)).cuda().t()
+    dC = torch.zeros((n, m), dtype=torch.float64, device="cuda")
+    oz.oz2_set_product_format(oz.OZ2_PRODUCT_INT32 if int32 else oz.OZ2_PRODUCT_RESIDUE_U8)
+    try:
+        ws = oz.Workspace(m, n, k, N)
+        oz.oz2_dgemm(m, n, k, dA.data_ptr(), m, dB.data_ptr(), k, dC.data_ptr(), m, N)
+        torch.cuda.synchronize()
+    finally:
+        oz.oz2_set_product_format(oz.OZ2_PRODUCT_RESIDUE_U8)
+    rows = [0, 15, 16, 127, 128, 255, 256, 1111, 2047, 2048, m - 1]
+    got = dC.t()[rows].cpu().numpy()
+    assert np.array_equal(got, orc.dgemm(A, B, N, rows=rows).C)
     del ws
