@@ -97,8 +97,10 @@ void oz2_make_layout(int64_t m, int64_t n, int64_t k, int N, int c_elem_bytes, O
 // 256 and 64), and each plane region holds 7 N planes of a quarter of the padded area.
 void oz2_make_layout_strassen(int64_t m, int64_t n, int64_t k, int N, Oz2Layout* lay);
 
-// Reports of a stage 1 that found its maxima without atomics: one word per workgroup, nonzero where it saw an infinity or
-// a NaN.  A workgroup of the next launch turns them into the 32 flag words (finish_scan).
+// Reports of a stage 1 that found its maxima without atomics: one word per workgroup (or, where the norm bounds of the
+// Cauchy-Schwarz mode carry them, per vector), kBadReport where it saw an infinity or a NaN, below 2^63 otherwise.  A workgroup of
+// the next launch turns them into the 32 flag words (finish_scan).
+constexpr unsigned long long kBadReport = ~0ull;
 struct Oz2ScanFinish {
   const unsigned long long* slots;  // null: nothing to do
   unsigned count;

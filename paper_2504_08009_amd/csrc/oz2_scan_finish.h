@@ -1,13 +1,13 @@
-// Shared by the kernels that follow a stage 1 without atomics (oz2_stage1.hip): each of its workgroups reports in a slot
-// of its own whether it saw an infinity or a NaN, and one workgroup of the next launch forms the flag word (1 when any
-// slot is set) and clears the counters of the GEMM's round synchronisation.  The other workgroups of that launch cannot
+// Shared by the kernels that follow a stage 1 without atomics (oz2_stage1.hip): it reports in words of its own (see
+// Oz2ScanFinish) whether it saw an infinity or a NaN, and one workgroup of the next launch forms the flag word (1 when any
+// report is bad) and clears the counters of the GEMM's round synchronisation.  The other workgroups of that launch cannot
 // look at the flag word yet; where it pays (oz2_stage2.hip) they look at the slots.
 #ifndef OZ2_SCAN_FINISH_H
 #define OZ2_SCAN_FINISH_H
 
 #include "oz2_internal.h"
 
-// all threads of the workgroup: is any slot set?
+// all threads of the workgroup: is any report bad (its highest bit set)?
 __device__ __forceinline__ int scan_found(const Oz2ScanFinish& f) {
   unsigned long long any = 0ull;
   unsigned i = threadIdx.x;
@@ -18,7 +18,7 @@ __device__ __forceinline__ int scan_found(const Oz2ScanFinish& f) {
     any |= v[0] | v[1] | v[2] | v[3];
   }
   for (; i < f.count; i += blockDim.x) any |= f.slots[i];
-  return __syncthreads_or(any != 0ull);
+  return __syncthreads_or((long long)any < 0);
 }
 
 // all threads of the workgroup

@@ -375,7 +375,7 @@ __global__ void __launch_bounds__(kScanThreads) vector_scan_kernel(const ScanJob
     bad = mx >= kInfBits;
   }
   const int any = __syncthreads_or(bad ? 1 : 0);
-  if (threadIdx.x == 0) slots[blockIdx.x] = any ? 1ull : 0ull;
+  if (threadIdx.x == 0) slots[blockIdx.x] = any ? kBadReport : 0ull;
 }
 
 __device__ __forceinline__ unsigned pack4(int r0, int r1, int r2, int r3) {
@@ -621,6 +621,7 @@ struct ShortJob {
   const double* X;
   int64_t ld, nvec, nvec_pad, k, k_pad;
   unsigned long long* vmax;
+  unsigned long long* vnorm;  // norm bounds (mode 1), which are the reports too
   int* shifts;
   int8_t* planes;
   int param;  // as in ShiftJob
@@ -628,7 +629,8 @@ struct ShortJob {
   unsigned nblk;   // workgroups
   unsigned chunk;  // workgroups per die: nblk / 8, there are 256 / V or a multiple of that
 };
-// KIND 0, 1: residue planes as in the conversion above; 2: the plane of 6-bit bounds.  mode: as shift_of counts them (0 or 1)
+// KIND 0, 1: residue planes as in the conversion above; 2: the plane of 6-bit bounds.  mode: as shift_of counts them (0 or 1).
+// slot: this workgroup's report (mode 0; in mode 1 a vector with an infinity or a NaN has kBadReport for its norm bound)
 template <int KIND, int V>
 __device__ __forceinline__ void convert_short(const ShortJob& j, const Oz2ConvConsts& cc, const int mode, double* tile, unsigned id,
                                               unsigned long long* slot) {
@@ -731,11 +733,12 @@ __device__ __forceinline__ void convert_short(const ShortJob& j, const Oz2ConvCo
   const int shift = shift_of(mx, norm, KIND == 2 ? 0 : mode, j.param, 0);
   if (wv == 0 && side == 0 && (lane & 7) == 0) {
     j.vmax[v0 + v] = mx;
+    if (KIND != 2 && mode == 1) j.vnorm[v0 + v] = mx >= kInfBits ? kBadReport : norm;
     j.shifts[v0 + v] = shift;
   }
-  if (wv == 0) {
+  if (wv == 0 && (KIND == 2 || mode == 0)) {
     const bool any = __any(mx >= kInfBits);
-    if (lane == 0) *slot = any ? 1ull : 0ull;
+    if (lane == 0) *slot = any ? kBadReport : 0ull;
   }
   int8_t* const base = j.planes + (size_t)(v0 / kBlkRows) * kBlkRows * j.k_pad + ((v0 % kBlkRows) + v) * kBlkK + 8 * (lane & 7) +
                        (size_t)kt_begin * (kBlkRows * kBlkK);
@@ -997,15 +1000,15 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
     for (int x = 0; x < nops; ++x) {
       const Operand& o = ops[x];
       const unsigned nblk = (unsigned)(o.nvec_pad / short_vecs);
-      sj[x] = {o.X, o.ld, o.nvec, o.nvec_pad, o.k, o.k_pad, o.vmax, o.shifts, o.planes, param[x], o.tri,
+      sj[x] = {o.X, o.ld, o.nvec, o.nvec_pad, o.k, o.k_pad, o.vmax, o.vaux, o.shifts, o.planes, param[x], o.tri,
                o.strided ? 1 : 0, nblk, nblk / 8};
       groups += nblk;
     }
-    // The reports live in the auxiliary vectors (a word per two vectors or more), which nothing else needs when this launch ends
-    // stage 1; in the INT8-product mode in the product region until the next launch has folded them.
+    // The reports live in the auxiliary vectors: a word per two vectors or more, or, in the Cauchy-Schwarz mode, whose norm bounds
+    // belong there, a word per vector; in the INT8-product mode in the product region until the next launch has folded them.
     const bool bounds = shift_mode == OZ2_SHIFT_INT8_PRODUCT;
     unsigned long long* slots = bounds ? reinterpret_cast<unsigned long long*>(ws + lay.off_c) : ops[0].vaux;
-    fin = {slots, groups, flag};
+    fin = {slots, base_mode == 1 ? (unsigned)vectors : groups, flag};
     const dim3 grid(8 * (sj[0].chunk + sj[1].chunk)), thr(kShortThreads);
     const size_t lds = (size_t)short_vecs * (lay.k_pad + 4) * sizeof(double);
 #define OZ2_SHORT_V(KA, KB, V) \

@@ -118,6 +118,61 @@ def test_one_pass_conversion_of_a_triangular_operand(side, uplo, ta, mode, k, n)
     del ws
 
 
+def _norm_bounds(vectors):
+    """S of each row: with e = floor(log2 max |x|) and q_l = ceil(|x_l| 2^(19 - e)), the sum of q_l^2 (0 for a row of zeros)."""
+    x = np.abs(np.asarray(vectors))
+    e = np.frexp(x.max(axis=1))[1] - 1
+    q = np.ceil(np.ldexp(x, (19 - e)[:, None])).astype(np.int64)
+    return (q * q).sum(axis=1)
+
+
+@pytest.mark.parametrize("entry", ["dgemm", "dsyrk", "dtrmm"])
+@pytest.mark.parametrize("k", [300, 1500, 5000, 10300])
+def test_norm_bounds_that_whole_calls_leave_in_the_workspace(entry, k):
+    """Cauchy-Schwarz mode, inner dimensions on either side of what the one-pass conversion takes: the documented entries of the
+    workspace hold the norm bounds, zero in the padding; an infinity in one row changes no other row's."""
+    if entry == "dtrmm" and k > 1500:
+        k = 900
+    rng = np.random.default_rng(k)
+    m, n, N = {"dgemm": (70, 300, 9), "dsyrk": (130, 130, 9), "dtrmm": (k, 40, 9)}[entry]
+    A, B = _mat(rng, m, k), _mat(rng, k, n)
+    A[m // 2, : k - 1] = 0.0
+    print("norms: %s m=%d n=%d k=%d" % (entry, m, n, k), flush=True)
+    dC = torch.zeros((n, m), dtype=torch.float64, device="cuda")
+    ws = oz.Workspace(m, n, k, N)
+    lay = oz.workspace_layout(m, n, k, N)
+    flags = ws.view(lay["flags"], 1, torch.int64)
+
+    def norms(name, pad):
+        return ws.view(lay[name], lay[pad], torch.int64).cpu().numpy()
+
+    oz.oz2_set_shift_mode(oz.OZ2_SHIFT_CAUCHY_SCHWARZ)
+    try:
+        for bad in (False, True):
+            if bad:
+                A[3, 2] = np.inf
+            ws.buf.fill_(0x7f)
+            dA, dB = _dev(A), _dev(B)
+            if entry == "dgemm":
+                oz.oz2_dgemm(m, n, k, dA.data_ptr(), m, dB.data_ptr(), k, dC.data_ptr(), m, N)
+            elif entry == "dsyrk":
+                oz.oz2_dsyrk("L", "N", m, k, 1.0, dA.data_ptr(), m, 0.0, dC.data_ptr(), m, N)
+            else:
+                oz.oz2_dtrmm("L", "L", "N", "N", m, n, 1.0, dA.data_ptr(), m, dB.data_ptr(), m, N)
+            torch.cuda.synchronize()
+            assert int(flags.item()) == int(bad)
+            rows = np.where(np.arange(m) == 3, 0.0 if bad else 1.0, 1.0).astype(bool)
+            stored = np.tril(A) if entry == "dtrmm" else A
+            got = norms("rownorm", "m_pad")
+            assert np.array_equal(got[:m][rows], _norm_bounds(stored[rows])) and not got[m:].any()
+            if entry != "dsyrk":
+                got = norms("colnorm", "n_pad")
+                assert np.array_equal(got[:n], _norm_bounds(B.T)) and not got[n:].any()
+    finally:
+        oz.oz2_set_shift_mode(oz.OZ2_SHIFT_MAX)
+    del ws
+
+
 @pytest.mark.parametrize("delta", [30, -30])
 def test_one_operand_split_deeper_than_the_other(delta):
     """21 moduli and a bit split of 30: one operand needs the two-level split, the other does not."""
