@@ -358,7 +358,7 @@ int oz2_stage2_gemm(int64_t m, int64_t n, int64_t k, int num_moduli, void* strea
   // the counters of the round synchronisation must be zero at launch; in oz2_dgemm stage 1 has cleared them
   hipError_t e = oz2_launch_clear_sync(lay, s.ws, static_cast<hipStream_t>(stream));
   if (e == hipSuccess)
-    e = oz2_launch_products(*plan, lay, s.ws, m, n, s.kblock, s.product_format, 0, OZ2_KRANGE_ALL, 0, Oz2ScanFinish{nullptr, 0u, nullptr},
+    e = oz2_launch_products(*plan, lay, s.ws, m, n, s.kblock, s.product_format, 0, OZ2_KRANGE_ALL, 0, Oz2ScanFinish{nullptr, 0u, nullptr, 0},
                           static_cast<hipStream_t>(stream));
   return e == hipSuccess ? OZ2_OK : OZ2_ERR_HIP;
 }

@@ -105,11 +105,13 @@ struct Oz2ScanFinish {
   const unsigned long long* slots;  // null: nothing to do
   unsigned count;
   unsigned long long* flags;
+  int stops;  // 1: products are left out once a report is bad, however short they are
 };
 
 // Products that take this many nanoseconds or more wait for the flag word, so that inputs with an infinity or a NaN skip
 // them: one launch of 2 to 4 us (whole calls with 16 moduli, finite inputs, with / without it, us: dtrmm 1024 x 16384 523 / 518,
-// dsyrk of order 4000, inner dimension 1000 273 / 270; with an infinity 2296 / 2666 and 1762 / 1951).
+// dsyrk of order 4000, inner dimension 1000 273 / 270; with an infinity 2296 / 2666 and 1762 / 1951).  Shorter ones that are to be left
+// out too look at the reports in every workgroup, or wait as well where those are too many for that.
 #define OZ2_FINISH_FIRST_NS 100000
 
 // Kernel launchers.  Each returns hipSuccess or the launch error.
@@ -153,7 +155,7 @@ hipError_t oz2_launch_clear_sync(const Oz2Layout& lay, char* ws, hipStream_t st)
 // triangle: 0 = general product; 1 / 2 = symmetric product op(A) op(A)^T (B's planes are A's), only the tiles of
 // the lower / upper triangle are computed
 // fin: what stage 1 left to this launch (see Oz2ScanFinish).  With check_flag, short products are then formed whatever the
-// flag will be; long ones find out first.
+// flag will be, unless fin.stops; long ones find out first.
 hipError_t oz2_launch_stage2(const Oz2Plan& plan, const Oz2Layout& lay, char* ws, int64_t kblock, int residue_u8,
                              int triangle, int krange, int check_flag, const Oz2ScanFinish& fin, hipStream_t st);
 // The same for an m x n result with the tiles that fit its size (oz2_stage2_tiles.hip): the large kernel above, or one with

@@ -384,10 +384,15 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
   };
 
   named_accumulators();
+  if (g.fin_stops) fetch_reports(g.fin, lds_base + (NS - 1) * kStageBytes, wv, lane);  // into the stage that the main loop fills first
   prologue_loads(cur, 0);
-  if (g.fin_stops && scan_found(g.fin)) {  // (the reports arrive with the first copies)
-    wait_vmcnt<0>();
-    return;
+  if (g.fin_stops) {
+    wait_vmcnt<(NS - 2) * kLoads>();
+    __syncthreads();
+    if (fetched_report_bad(g.fin, lds + (NS - 1) * kStageBytes)) {
+      wait_vmcnt<0>();
+      return;
+    }
   }
   bool first = true;
   int round = 0;
@@ -656,6 +661,7 @@ namespace {
 // workgroup slot each).  Callers hold the library's lock.
 int g_cus = 0;
 int g_sync_spins = 4096;  // polls per wait of the round synchronisation (each followed by a short sleep); 0: off
+constexpr Oz2ScanFinish kNothing = {nullptr, 0u, nullptr, 0};
 hipError_t gemm_setup() {
   if (g_cus) return hipSuccess;
 #define OZ2_BOTH(U8, LIST, EARLY)                                              \
@@ -773,18 +779,19 @@ hipError_t launch_gemm(const Oz2Layout& lay, char* ws, int num_moduli, const int
   // is formed ahead of the launch.
   if (check_flag && fin.slots) {
     const int64_t each = 720 * (krange == OZ2_KRANGE_ALL ? g.ktiles : (g.ktiles + 1) / 2) + 4500;
-    if (grid <= (unsigned)g_cus && total > 4 * (int64_t)g_cus && fin.count <= 4096) {
+    const bool wait = (triangle && !g.folded ? total / 2 : total) / g_cus * each >= OZ2_FINISH_FIRST_NS;
+    if (((grid <= (unsigned)g_cus && total > 4 * (int64_t)g_cus) || (fin.stops && !wait)) && fin.count <= kStageBytes / 8) {
       g.fin_stops = 1;
-    } else if ((triangle && !g.folded ? total / 2 : total) / g_cus * each >= OZ2_FINISH_FIRST_NS) {
+    } else if (wait || fin.stops) {
       if ((e = oz2_launch_finish_scan(fin, st)) != hipSuccess) return e;
-      g.fin = {nullptr, 0u, nullptr};
+      g.fin = kNothing;
       g.skip_flag = reinterpret_cast<const unsigned long long*>(ws + lay.off_flags);
     }
   }
   // The round synchronisation needs its counters cleared before the launch, which comes with forming the flag word.
   if (g.xcd_sync != nullptr && g.fin.slots) {
     if ((e = oz2_launch_finish_scan(fin, st)) != hipSuccess) return e;
-    g.fin = {nullptr, 0u, nullptr};
+    g.fin = kNothing;
     g.fin_stops = 0;
     if (check_flag) g.skip_flag = reinterpret_cast<const unsigned long long*>(ws + lay.off_flags);
   }
@@ -819,8 +826,6 @@ hipError_t launch_gemm(const Oz2Layout& lay, char* ws, int num_moduli, const int
 hipError_t oz2_gemm_setup() { return gemm_setup(); }
 
 int oz2_gemm_cus() { return g_cus; }
-
-static constexpr Oz2ScanFinish kNothing = {nullptr, 0u, nullptr};
 
 void oz2_gemm_set_sync_spins(int spins) { g_sync_spins = spins; }
 

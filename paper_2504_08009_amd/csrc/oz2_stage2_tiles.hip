@@ -36,6 +36,7 @@ struct TileArgs {
   int ktiles, triangle, folded, krange;  // as in the large kernel
   const unsigned long long* skip_flag;
   Oz2ScanFinish fin;
+  int fin_stops;  // 1: every workgroup looks at the reports and stops when one is bad
   FastDiv div_plane, div_group, div_last;
   Oz2FoldConsts fold[OZ2_MAX_N];
 };
@@ -50,8 +51,7 @@ __global__ void __launch_bounds__(kThreads, WGS) gemm_i8_tile_kernel(const TileA
   warm_arguments(g);
 
   if (g.skip_flag != nullptr && *g.skip_flag != 0ull) return;
-  if (g.fin.slots != nullptr && blockIdx.x == 0) finish_scan(g.fin);
-
+  if (g.fin.slots != nullptr && !g.fin_stops && blockIdx.x == 0) finish_scan(g.fin);
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wv >> 1, wn = wv & 1;
@@ -107,9 +107,20 @@ __global__ void __launch_bounds__(kThreads, WGS) gemm_i8_tile_kernel(const TileA
     for (int y = 0; y < NI; ++y)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[x][y][e] = (int)OZ2_ACC_START;
+  if (g.fin_stops) fetch_reports(g.fin, lds_base + (NS - 1) * kStage, wv, lane);  // into the stage that the loop fills first
   // (beyond the last k-tile the first one is fetched again: every wait counts on the same number of copies in flight)
 #pragma unroll
   for (int p = 0; p < NS - 1; ++p) load(p < ktiles ? p : 0, p);
+  if (g.fin_stops) {
+    wait_vmcnt<(NS - 2) * kLoads>();
+    __syncthreads();
+    const int bad = fetched_report_bad(g.fin, lds + (NS - 1) * kStage);
+    if (blockIdx.x == 0) write_flags(g.fin, bad);
+    if (bad) {
+      wait_vmcnt<0>();
+      return;
+    }
+  }
   const Oz2FoldConsts fc = in_vector_registers(g.fold[t]);
   int stage = 0;
   for (int kt = 0; kt < ktiles; ++kt) {
@@ -190,10 +201,16 @@ hipError_t launch(TileArgs& g, int64_t m, int64_t n, int planes, const unsigned 
   g.skip_flag = g.fin.slots ? nullptr : flag;
   // (with reports still to be turned into the flag by this launch, nobody can look at the flag yet)
   const int64_t each = 270 * (g.krange == OZ2_KRANGE_ALL ? g.ktiles : (g.ktiles + 1) / 2) + 600;
-  if (flag && g.fin.slots && total / oz2_gemm_cus() * each >= OZ2_FINISH_FIRST_NS) {
-    if (hipError_t e = oz2_launch_finish_scan(g.fin, st); e != hipSuccess) return e;
-    g.fin = {nullptr, 0u, nullptr};
-    g.skip_flag = flag;
+  g.fin_stops = 0;
+  if (flag && g.fin.slots) {
+    const bool wait = total / oz2_gemm_cus() * each >= OZ2_FINISH_FIRST_NS;
+    if (g.fin.stops && !wait && g.fin.count <= (unsigned)(TM + TN) * BK / 8u) {
+      g.fin_stops = 1;
+    } else if (wait || g.fin.stops) {
+      if (hipError_t e = oz2_launch_finish_scan(g.fin, st); e != hipSuccess) return e;
+      g.fin = {nullptr, 0u, nullptr, 0};
+      g.skip_flag = flag;
+    }
   }
   hipLaunchKernelGGL((gemm_i8_tile_kernel<MI, NI, NS, WGS>), dim3((unsigned)g.chunk * 8), dim3(kThreads),
                      (kTileLds<MI, NI, NS, WGS>), st, g);

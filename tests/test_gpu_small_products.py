@@ -173,6 +173,48 @@ def test_norm_bounds_that_whole_calls_leave_in_the_workspace(entry, k):
     del ws
 
 
+@pytest.mark.parametrize("entry,m,n,k,mode", [
+    ("dgemm", 60, 50, 1100, 0), ("dgemm", 300, 300, 1500, 0), ("dgemm", 300, 200, 5000, 0), ("dgemm", 1000, 900, 1400, 0),
+    ("dgemm", 500, 500, 1500, 1), ("dgemm", 1000, 1000, 1088, 1), ("dgemm", 2040, 2048, 2048, 1), ("dgemm", 9000, 150, 1100, 1),
+    ("dgemm", 9000, 150, 1100, 0),
+    ("dgemm", 1000, 1000, 2000, 2), ("dgemm", 700, 700, 700, 2), ("dgemm", 1000, 1000, 7000, 0),
+    ("dsyrk", 500, 500, 3000, 0), ("dsyrk", 1500, 1500, 1500, 0), ("dsyrk", 700, 700, 1200, 1), ("dtrmm", 1500, 300, 1500, 0),
+    ("dtrmm", 1100, 1000, 1100, 1)])
+def test_products_are_left_out_of_calls_on_infinities(entry, m, n, k, mode):
+    """Vectors longer than 1024 (INT8-product mode: of any length): an infinity in the last row or column leaves the product planes as
+    they were (those that the fallback of an in-place product and the bound product do not use), and the next finite call fills them.
+    9000 x 150: more reports than a workgroup fetches."""
+    rng = np.random.default_rng(m + n + k)
+    N = 14
+    print("left out: %s m=%d n=%d k=%d mode=%d" % (entry, m, n, k, mode), flush=True)
+    dA = torch.from_numpy(rng.standard_normal((k, m))).cuda()
+    B = torch.from_numpy(rng.standard_normal((n, k))).cuda()
+    dC = torch.zeros((n, m), dtype=torch.float64, device="cuda")
+    ws = oz.Workspace(m, n, k, N)
+    lay = oz.workspace_layout(m, n, k, N)
+    flags = ws.view(lay["flags"], 1, torch.int64)
+    area = lay["m_pad"] * lay["n_pad"]
+    planes = ws.view(lay["c_planes"] + 8 * area, (N - 8) * area, torch.uint8)
+    oz.oz2_set_shift_mode(mode)
+    try:
+        for bad in (True, False):
+            dB = B.clone()
+            (dB if entry == "dgemm" else dA)[-1, -1] = float("inf") if bad else 1.0
+            ws.buf.fill_(0xff)  # no residue: all moduli but 256 are below it
+            if entry == "dgemm":
+                oz.oz2_dgemm(m, n, k, dA.data_ptr(), m, dB.data_ptr(), k, dC.data_ptr(), m, N)
+            elif entry == "dsyrk":
+                oz.oz2_dsyrk("L", "N", m, k, 1.0, dA.data_ptr(), m, 0.0, dC.data_ptr(), m, N)
+            else:
+                oz.oz2_dtrmm("L", "L", "N", "N", m, n, 1.0, dA.data_ptr(), m, dB.data_ptr(), m, N)
+            torch.cuda.synchronize()
+            assert int(flags.item()) == int(bad)
+            assert bool((planes == 0xff).all()) == bad
+    finally:
+        oz.oz2_set_shift_mode(0)
+    del ws
+
+
 @pytest.mark.parametrize("delta", [30, -30])
 def test_one_operand_split_deeper_than_the_other(delta):
     """21 moduli and a bit split of 30: one operand needs the two-level split, the other does not."""
