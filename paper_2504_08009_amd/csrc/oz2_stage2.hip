@@ -371,16 +371,20 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
   auto rd_b = [&](Frag& F, unsigned at, int y) { F.b[y] = *(LdsFrag)(at + y * 16 * BK); };
 
   // Operand roles of v_mfma_i32_16x16x64_i8: the rows of the first operand run over the result registers
-  // (lane l, register e: row 4 (l / 16) + e), the rows of the second over the lanes (row l % 16).  First = A', second = B': the
-  // four registers of a tile hold four consecutive rows i of one column.
+  // (lane l, register e: row 4 (l / 16) + e), the rows of the second over the lanes (row l % 16).
+  //   UINT8 export: first = A', second = B': the four registers of a tile hold four consecutive rows i of one column, the four
+  //   bytes of a word.
+  //   INT32 export: first = B', second = A': a register holds sixteen consecutive rows i of each of four columns.
   // The 64 products of a k-tile: rows of tiles 0-3 against all eight columns, then rows 4-7; within a column back and forth, so
   // that every product shares an operand with the one before it.
   auto mfma = [&](const Frag& F, auto qc, auto first) {
     constexpr int q = decltype(qc)::value, y = (q >> 2) & 7, x = (q >> 5) * 4 + ((y & 1) ? 3 - (q & 3) : q & 3);
+    const v4i& over_registers = RESIDUE_U8 ? F.a[x] : F.b[y];
+    const v4i& over_lanes = RESIDUE_U8 ? F.b[y] : F.a[x];
     if constexpr (decltype(first)::value)
-      Acc<8 * y + x>::template start<RESIDUE_U8>(F.a[x], F.b[y]);
+      Acc<8 * y + x>::template start<RESIDUE_U8>(over_registers, over_lanes);
     else
-      Acc<8 * y + x>::add(F.a[x], F.b[y]);
+      Acc<8 * y + x>::add(over_registers, over_lanes);
   };
 
   named_accumulators();
@@ -630,14 +634,20 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
       __builtin_amdgcn_sched_barrier(0);
     });
   } else {
-    // lane holds rows 4 (lane / 16) .. + 3 of column lane % 16 of a tile: one 16-byte store
-    int* plane = g.c + ((size_t)t * g.n_pad + (size_t)tn * BN + wn * 128 + (lane & 15)) * g.m_pad + (size_t)tm * BM + wm * 128 + 4 * (lane >> 4);
+    // Register e of tile (x, y) holds rows 16 x + lane % 16 of column 16 y + 4 (lane / 16) + e.  Exchanged between the groups of
+    // sixteen lanes of two tiles, a register has 32 consecutive rows of two columns: every store fills two cache lines.  (16 bytes
+    // per lane, 64 bytes of each of sixteen columns, meet in the same channels where the columns are a power of two apart: whole calls
+    // with 16 moduli, us, 8192 x 8192 x 1024 2610 -> 2412, 4096^3 1298 -> 1280, INT8-product mode 500^3 58.5 -> 54.4.)
+    int* plane = g.c + ((size_t)t * g.n_pad + (size_t)tn * BN + wn * 128 + 8 * (lane >> 5)) * g.m_pad + (size_t)tm * BM + wm * 128 + (lane & 31);
     unrolled<8>([&](auto yc) {
-      unrolled<8>([&](auto xc) {
-        constexpr int x = decltype(xc)::value, y = decltype(yc)::value;
-        typedef Acc<8 * y + x> A;
-        *reinterpret_cast<v4i*>(plane + (size_t)(y * 16) * g.m_pad + x * 16) =
-            v4i{(int)A::read(0), (int)A::read(1), (int)A::read(2), (int)A::read(3)};
+      unrolled<4>([&](auto xc) {
+        unrolled<4>([&](auto ec) {
+          constexpr int x = 2 * decltype(xc)::value, y = decltype(yc)::value, e = decltype(ec)::value;
+          const auto s = __builtin_amdgcn_permlane16_swap(Acc<8 * y + x>::read(e), Acc<8 * y + x + 1>::read(e), false, false);
+          int* p = plane + (size_t)(y * 16 + e) * g.m_pad + x * 16;
+          p[0] = (int)s[0];
+          p[4 * g.m_pad] = (int)s[1];
+        });
       });
     });
   }
