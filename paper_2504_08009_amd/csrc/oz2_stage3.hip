@@ -180,7 +180,10 @@ __global__ void __launch_bounds__(kThreads) crt_kernel(const void* __restrict__ 
 
 // Products below 2^24 elements, where every launch counts: the blocks of the FP64 fallback ride in the same launch, behind those of
 // the kernel above.  Which of the two sets works is decided by the flag of stage 1, the other returns at once.
-template <int L, int R>
+// kBatch: eight planes at a time, four where the last eight would be half repeats of the last plane or more (9 to 12 moduli, say), which
+// are fetched like any other (whole calls, us, always eight / this: 4 moduli 1629 x 3786 x 343 57.9 / 56.0, 10 moduli 2000 x 2000 x 300
+// 58.7 / 57.5, 9 moduli 2500 x 2500 x 200 with an update 80.3 / 79.1; always four / this: 15 moduli 3001 x 2777 x 300 131.6 / 129.4, 14 moduli 700^3 29.7 / 29.4).
+template <int L, int R, int kBatch>
 __global__ void __launch_bounds__(kThreads, 4) crt_or_fallback_kernel(const void* __restrict__ cplanes, int64_t m_pad,
                                                                    int64_t n_pad, const int* __restrict__ sa,
                                                                    const int* __restrict__ sb,
@@ -192,7 +195,7 @@ __global__ void __launch_bounds__(kThreads, 4) crt_or_fallback_kernel(const void
   if (blockIdx.x < crt_blocks) {
     const int g = (int)(blockIdx.x * kThreads + threadIdx.x), j = g / by_col;
     if (j >= f.n) return;
-    crt_rows<L, true, R, 8, true>(cplanes, m_pad, n_pad, sa, sb, f.C, f.ldc, f.m, f.n, f.alpha, f.beta, 0, cc, j,
+    crt_rows<L, true, R, kBatch, true>(cplanes, m_pad, n_pad, sa, sb, f.C, f.ldc, f.m, f.n, f.alpha, f.beta, 0, cc, j,
                             (int64_t)(g - j * per_col) * R, flag);
   } else if (*flag != 0ull) {
     oz2_fallback_tile<kFallbackSmallTile>(f, blockIdx.x - crt_blocks);
@@ -452,15 +455,21 @@ hipError_t oz2_launch_stage3_or_fallback(int transa, int transb, int64_t m, int6
   const FastDiv by_col = fast_div((unsigned)per_col);
   const Oz2FallbackArgs f = {transa, transb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, tiles_m, 0, 0, 0};
   const dim3 grid((unsigned)(crt_blocks + tiles_m * tiles_n));
+  const bool by_four = (plan.N - 1) % 8 < 4;
   switch (plan.crt.L) {
-#define OZ2_CASE(LL)                                                                                                     \
-  case LL:                                                                                                               \
-    if (rows == 2)                                                                                                       \
-      hipLaunchKernelGGL((crt_or_fallback_kernel<LL, 2>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa, \
-                         sb, flag, (unsigned)crt_blocks, (int)per_col, by_col, f, plan.crt);                             \
-    else                                                                                                                 \
-      hipLaunchKernelGGL((crt_or_fallback_kernel<LL, 4>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa, \
-                         sb, flag, (unsigned)crt_blocks, (int)per_col, by_col, f, plan.crt);                             \
+#define OZ2_LAUNCH(LL, R, BATCH)                                                                                           \
+  hipLaunchKernelGGL((crt_or_fallback_kernel<LL, R, BATCH>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa, \
+                     sb, flag, (unsigned)crt_blocks, (int)per_col, by_col, f, plan.crt)
+#define OZ2_CASE(LL)                \
+  case LL:                          \
+    if (rows == 2 && by_four)       \
+      OZ2_LAUNCH(LL, 2, 4);         \
+    else if (rows == 2)             \
+      OZ2_LAUNCH(LL, 2, 8);         \
+    else if (by_four)               \
+      OZ2_LAUNCH(LL, 4, 4);         \
+    else                            \
+      OZ2_LAUNCH(LL, 4, 8);         \
     break;
     OZ2_CASE(1)
     OZ2_CASE(2)
@@ -468,6 +477,7 @@ hipError_t oz2_launch_stage3_or_fallback(int transa, int transb, int64_t m, int6
     OZ2_CASE(4)
     OZ2_CASE(5)
 #undef OZ2_CASE
+#undef OZ2_LAUNCH
     default:
       return hipErrorInvalidValue;
   }

@@ -61,6 +61,17 @@ def test_one_pass_conversion_by_four_and_by_eight_vectors(m, n, N, k):
     assert flag == 0 and np.array_equal(got, ref)
 
 
+@pytest.mark.parametrize("N", range(2, 27))
+@pytest.mark.parametrize("m,n", [(45, 70), (601, 500)])
+def test_every_number_of_moduli(m, n, N):
+    """Stage 3 of small results takes the planes eight or four at a time, by the number of moduli, in pieces of two and of four rows."""
+    k = 40
+    rng = np.random.default_rng(m + N)
+    print("moduli: m=%d n=%d k=%d N=%d" % (m, n, k, N), flush=True)
+    got, ref, flag = _gemm("N", "N", _mat(rng, m, k), _mat(rng, k, n), N, beta=float(N % 2))
+    assert flag == 0 and np.array_equal(got, ref)
+
+
 @pytest.mark.parametrize("mode", [0, 1, 2])
 @pytest.mark.parametrize("m,n,k,N", [(60, 40, 1025, 3), (300, 200, 1999, 14), (700, 500, 2496, 9), (1200, 100, 2497, 5), (40, 700, 3393, 15),
                                      (2000, 100, 4992, 4), (70, 300, 4993, 16), (256, 130, 6209, 22), (30, 20, 9984, 21), (30, 20, 9985, 21)])
