@@ -784,10 +784,10 @@ __global__ void __launch_bounds__(kFinishThreads) finish_scan_kernel(const Oz2Sc
 
 template <int KA, int KB, int V>
 __global__ void __launch_bounds__(kShortThreads, KA == 1 || KB == 1 ? 4 : 6) short_convert_kernel(const ShortJob ja, const ShortJob jb,
-                                                                      const Oz2ConvConsts cc, const int mode,
+                                                                      const Oz2ConvConsts cc, const int mode, const int warm,
                                                                       unsigned long long* __restrict__ slots) {
   extern __shared__ __attribute__((aligned(16))) double short_tile[];
-  if (KA != 2) warm_arguments(cc);
+  if (KA != 2 && warm) warm_arguments(cc);
   // workgroup i of a launch runs on die i % 8: consecutive vectors for each die; of a triangular operand, whose vectors grow from one
   // end to the other, 16 at a time, the next 16 for the next die
   const unsigned x = blockIdx.x & 7u;
@@ -1012,9 +1012,12 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
     // cost up to 6 % of a finite call, Cauchy-Schwarz mode 500^3 22.2 -> 23.5 us.)
     fin = {slots, base_mode == 1 ? (unsigned)vectors : groups, flag, lay.k_pad > 1024};
     const dim3 grid(8 * (sj[0].chunk + sj[1].chunk)), thr(kShortThreads);
+    // Up to three workgroups on two compute units wait for the constants (700^3 29.8 -> 29.2 us a call); where there are more, the first
+    // have fetched them for the others and the loads only cost (9 moduli 71 x 5081 x 184 22.5 -> 23.1, 900 x 700 x 300 22.7 -> 23.1).
+    const int warm = 2 * (int64_t)groups <= 3 * oz2_gemm_cus();
     const size_t lds = (size_t)short_vecs * (lay.k_pad + 4) * sizeof(double);
 #define OZ2_SHORT_V(KA, KB, V) \
-  hipLaunchKernelGGL((short_convert_kernel<KA, KB, V>), grid, thr, lds, st, sj[0], sj[1], conv, base_mode, slots)
+  hipLaunchKernelGGL((short_convert_kernel<KA, KB, V>), grid, thr, lds, st, sj[0], sj[1], conv, base_mode, warm, slots)
 #define OZ2_SHORT(KA, KB)        \
   do {                           \
     if (short_vecs == 8)         \
