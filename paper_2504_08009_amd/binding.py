@@ -12,7 +12,7 @@ SYMBOLS = [
     "oz2_set_gemm_algorithm", "oz2_gemm_algorithm_for", "oz2_workspace_bytes_strassen", "oz2_workspace_bytes_preferred",
     "oz2_context_create", "oz2_context_destroy", "oz2_context_set_workspace", "oz2_context_set", "oz2_context_get",
     "oz2_context_workspace_bytes", "oz2_context_dgemm", "oz2_context_dsyrk", "oz2_context_dtrmm",
-    "oz2_set_kblock", "oz2_set_round_sync", "oz2_set_shift_mode", "oz2_set_product_format", "oz2_set_bit_split", "oz2_set_nonfinite_check", "oz2_set_stage_events", "oz2_calibrate_mfma", "oz2_host_crt_element", "oz2_host_crt_element_digits", "oz2_host_residues", "oz2_host_product_residues", "oz2_status_string",
+    "oz2_set_kblock", "oz2_set_round_sync", "oz2_set_shift_mode", "oz2_set_product_format", "oz2_set_bit_split", "oz2_set_nonfinite_check", "oz2_set_stage_events", "oz2_calibrate_mfma", "oz2_host_kernel_choice", "oz2_host_crt_element", "oz2_host_crt_element_digits", "oz2_host_residues", "oz2_host_product_residues", "oz2_status_string",
 ]
 
 
@@ -74,6 +74,7 @@ def lib():
         L.oz2_calibrate_mfma.argtypes = [ci, ci, ci, vp, vp, vp]
         L.oz2_host_crt_element.argtypes = [ci, vp, vp]
         L.oz2_host_crt_element_digits.argtypes = [ci, vp, vp]
+        L.oz2_host_kernel_choice.argtypes = [i64, i64, i64, ci, ci, vp]
         L.oz2_host_residues.argtypes = [ci, ci, ctypes.c_double, ci, vp]
         L.oz2_host_product_residues.argtypes = [ci, i64, vp, vp]
         L.oz2_status_string.restype = ctypes.c_char_p
@@ -261,6 +262,13 @@ def oz2_stage3_crt(m, n, k, C_ptr, ldc, num_moduli, stream=None):
 def oz2_calibrate_mfma(workgroups, iters, random_operands, sink_ptr, clocks_ptr, stream=None):
     _check(lib().oz2_calibrate_mfma(workgroups, iters, int(random_operands), sink_ptr, clocks_ptr,
                                     _stream_ptr(stream)), "oz2_calibrate_mfma")
+
+
+def host_kernel_choice(m, n, k, num_moduli, compute_units):
+    """(vectors of the one-pass conversion, side of a thin product, edge of the product tiles) of a general product."""
+    out = (ctypes.c_int * 3)()
+    _check(lib().oz2_host_kernel_choice(m, n, k, num_moduli, compute_units, out), "oz2_host_kernel_choice")
+    return tuple(out)
 
 
 def host_crt_element(num_moduli, cprod):

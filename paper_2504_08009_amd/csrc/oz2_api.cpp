@@ -437,7 +437,7 @@ int dgemm_ex_impl(bool static_ws, char transa, char transb, int64_t m, int64_t n
   auto mark = [&](int i) { return !s.ev_on || hipEventRecord(s.ev[i], st) == hipSuccess; };
   Oz2ScanFinish fin;
   const int thin =
-      !strassen && s.product_format == OZ2_PRODUCT_RESIDUE_U8 ? oz2_thin_applies(m, n, *plan, lay, s.kblock) : 0;
+      !strassen && s.product_format == OZ2_PRODUCT_RESIDUE_U8 ? oz2_thin_applies(m, n, *plan, lay, s.kblock, oz2_gemm_cus()) : 0;
   int two_level = 0;
   if (!mark(0)) return OZ2_ERR_HIP;
   if (oz2_launch_stage1(ta, tb, m, n, k, A, lda, B, ldb, 0, 0, *plan, s.shift_mode, s.bit_split, strassen ? 1 : 0, lay, ws,
@@ -712,6 +712,27 @@ int oz2_calibrate_mfma(int workgroups, int iters, int random_operands, int* sink
   hipError_t e = oz2_launch_mfma_calibration(workgroups, iters, random_operands, sink, clocks,
                                              static_cast<hipStream_t>(stream));
   return e == hipSuccess ? OZ2_OK : OZ2_ERR_HIP;
+}
+
+int oz2_host_kernel_choice(int64_t m, int64_t n, int64_t k, int num_moduli, int compute_units, int choice[3]) {
+  if (m < 1) return -1;
+  if (n < 1) return -2;
+  if (k < 1) return -3;
+  if (!dims_ok(m, n, k)) return -1;
+  if (!n_ok(num_moduli)) return -4;
+  if (compute_units < 1) return -5;
+  if (!choice) return -6;
+  State& s = state();
+  std::lock_guard<std::mutex> lock(s.mu);
+  const Oz2Plan* plan;
+  if (get_plan(s, num_moduli, k, &plan) < 0) return -4;
+  Oz2Layout lay;
+  const int u8 = s.product_format == OZ2_PRODUCT_RESIDUE_U8;
+  oz2_make_layout(m, n, k, num_moduli, u8 ? 1 : 4, &lay);
+  choice[1] = u8 ? oz2_thin_applies(m, n, *plan, lay, s.kblock, compute_units) : 0;
+  choice[0] = choice[1] ? 0 : oz2_one_pass_vectors(*plan, lay, 0, s.shift_mode, s.bit_split, compute_units);
+  choice[2] = choice[1] ? 0 : oz2_products_tile(*plan, lay, m, n, s.kblock, u8, 0, OZ2_KRANGE_ALL, compute_units);
+  return OZ2_OK;
 }
 
 int oz2_host_crt_element(int num_moduli, const int32_t* cprod, double* x_out) {

@@ -123,6 +123,8 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
                              const double* B, int64_t ldb, int tri_a, int tri_b, const Oz2Plan& plan, int shift_mode,
                              int bit_split, int strassen, const Oz2Layout& lay, char* ws, hipStream_t st,
                              int thin, int* large_two_level, Oz2ScanFinish* deferred);
+// Vectors that a workgroup of the one-pass conversion holds, on a device with that many compute units; 0: separate launches.
+int oz2_one_pass_vectors(const Oz2Plan& plan, const Oz2Layout& lay, int symmetric, int shift_mode, int bit_split, int64_t cus);
 // Strassen form of line 6 (oz2_strassen.hip, oz2_stage2.hip): operand planes, the 7 N products, CRT pass
 hipError_t oz2_launch_strassen_convert(int transa, int transb, int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
                                        const double* B, int64_t ldb, const Oz2Plan& plan, const int* kinds,
@@ -164,10 +166,13 @@ hipError_t oz2_gemm_tiles_setup();
 hipError_t oz2_launch_products(const Oz2Plan& plan, const Oz2Layout& lay, char* ws, int64_t m, int64_t n, int64_t kblock,
                                int residue_u8, int triangle, int krange, int check_flag, const Oz2ScanFinish& fin,
                                hipStream_t st);
+// Edge of the tiles it takes: 64, 128 or 256.
+int oz2_products_tile(const Oz2Plan& plan, const Oz2Layout& lay, int64_t m, int64_t n, int64_t kblock, int residue_u8, int triangle,
+                      int krange, int64_t cus);
 hipError_t oz2_thin_setup();
 // Thin general products (oz2_thin.hip): conversion of the large operand and products in one kernel.  oz2_thin_applies: 0 no,
 // 1 the first operand is the large one, 2 the second.
-int oz2_thin_applies(int64_t m, int64_t n, const Oz2Plan& plan, const Oz2Layout& lay, int64_t kblock);
+int oz2_thin_applies(int64_t m, int64_t n, const Oz2Plan& plan, const Oz2Layout& lay, int64_t kblock, int64_t cus);
 hipError_t oz2_launch_thin_products(int which, int strided, const double* X, int64_t ld, int64_t nvec, int64_t nthin, int64_t k,
                                     int two_level, const Oz2Plan& plan, const Oz2Layout& lay, char* ws, int check_flag,
                                     hipStream_t st);

@@ -904,14 +904,36 @@ hipError_t launch_convert(const Operand* ops, int nops, const int* kind, bool la
 // 229 / 213, 240, 16 moduli 4096^3 1169 / 1159, 1157, dtrmm of order 4096 with 2048 columns 522 / 525, 496.  Up to 9984: 300 x 300 x 5000
 // with 16 64.2, 96.6, 500 x 500 x 8000 103, 139, 1000 x 1000 x 8000 208, 214, 2000 x 2000 x 8000 628, 607.  Elements split two levels
 // deep, 22 moduli: 700 x 3000 x 4000 341 / 347, 345, 4096 x 4096 x 2048 892 / 889 / 882, 886.
-static int short_vectors(int64_t vectors, int64_t k_pad, bool two_level) {
-  const int64_t cus = oz2_gemm_cus(), elements = vectors * k_pad;
+static int short_vectors(int64_t vectors, int64_t k_pad, bool two_level, int64_t cus) {
+  const int64_t elements = vectors * k_pad;
   const auto fits = [&](int v) { return v * (k_pad + 4) * (int64_t)sizeof(double) <= kShortLds; };
   if (k_pad <= 1024) return vectors <= (k_pad <= 256 ? 4 : k_pad <= 512 ? 8 : 16) * cus ? 4 : 8;
   if (two_level && elements > (int64_t)3 << 22) return 0;
   if (fits(8)) return vectors <= 4 * cus ? 2 : 4;
   if (fits(4)) return elements > (int64_t)21 << 20 ? 0 : vectors <= 4 * cus || k_pad <= 3392 || two_level ? 2 : 4;
   return fits(2) && vectors <= 8 * cus ? 2 : 0;
+}
+
+// What the shifts are formed from: the budgets of the operands, or (INT8-product mode) first the exponents 5 - e of the
+// 6-bit bounds.  bit_split moves that many bits from the first operand to the second, which also gets the odd bit of the sum
+// (bit_split == 0: the equal split; the symmetric product always uses it).
+static void shift_params(const Oz2Plan& plan, int shift_mode, int bit_split, int param[2]) {
+  if (shift_mode == OZ2_SHIFT_INT8_PRODUCT) {
+    param[0] = param[1] = 6;
+  } else if (shift_mode == OZ2_SHIFT_CAUCHY_SCHWARZ) {
+    param[0] = plan.beta - bit_split;
+    param[1] = bit_split == 0 ? plan.beta : plan.budget2 - param[0];
+  } else {
+    param[0] = plan.kappa - bit_split;
+    param[1] = bit_split == 0 ? plan.kappa : plan.kappa_sum - param[0];
+  }
+}
+
+int oz2_one_pass_vectors(const Oz2Plan& plan, const Oz2Layout& lay, int symmetric, int shift_mode, int bit_split, int64_t cus) {
+  int param[2];
+  shift_params(plan, shift_mode, bit_split, param);
+  const int most = 75 - (shift_mode == OZ2_SHIFT_CAUCHY_SCHWARZ ? 1 : 0);
+  return short_vectors(lay.m_pad + (symmetric ? 0 : lay.n_pad), lay.k_pad, param[0] > most || param[1] > most, cus);
 }
 
 hipError_t oz2_launch_finish_scan(const Oz2ScanFinish& f, hipStream_t st) {
@@ -970,30 +992,18 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
     hipLaunchKernelGGL(shifts_kernel, dim3(blocks_of(ja.count + jb.count, kThreads)), thr, 0, st, ja, jb, mode);
   };
   Oz2ConvConsts conv = plan.conv;
-  // Budgets per operand: bit_split moves that many bits from the first operand to the second, which also gets
-  // the odd bit of the sum (bit_split == 0: the equal split; the symmetric product always uses it).
   const int d = bit_split;
   int xbits[2];  // |x'| < 2^xbits decides how deep the conversion kernels split an element
   Oz2ScanFinish fin = nothing;
   if (deferred) *deferred = nothing;
   const int64_t vectors = lay.m_pad + (nops == 2 ? lay.n_pad : 0);
-  // what the shifts are formed from: the budgets of the operands, or (INT8-product mode) first the exponents 5 - e of the
-  // 6-bit bounds
   int param[2];
-  if (shift_mode == OZ2_SHIFT_INT8_PRODUCT) {
-    param[0] = param[1] = 6;
-  } else if (shift_mode == OZ2_SHIFT_CAUCHY_SCHWARZ) {
-    param[0] = plan.beta - d;
-    param[1] = d == 0 ? plan.beta : plan.budget2 - param[0];
-  } else {
-    param[0] = plan.kappa - d;
-    param[1] = d == 0 ? plan.kappa : plan.kappa_sum - param[0];
-  }
+  shift_params(plan, shift_mode, d, param);
   const int base_mode = shift_mode == OZ2_SHIFT_CAUCHY_SCHWARZ ? 1 : 0;  // as shift_of counts them
   // Short vectors: everything in one launch (in the INT8-product mode: maxima and bound planes), whose reports the caller's
   // GEMM launch turns into the flag word (deferred != nullptr: the caller sees to that).
   const bool two_a = param[0] + base_mode > 75, two_b = param[1] + base_mode > 75;
-  const int short_vecs = deferred && !thin && !strassen ? short_vectors(vectors, lay.k_pad, two_a || two_b) : 0;
+  const int short_vecs = deferred && !thin && !strassen ? oz2_one_pass_vectors(plan, lay, nops == 1, shift_mode, d, oz2_gemm_cus()) : 0;
   if (short_vecs) {
     ShortJob sj[2] = {};
     unsigned groups = 0;

@@ -19,8 +19,8 @@
 //
 // Which matrix instruction: under the card's power cap the products of 16 x 16 x 64 run at 4.0 POP/s on random operands with no
 // memory traffic, those of 32 x 32 x 32 at 3.5 (the larger tile moves twice the accumulator bytes per operation through the
-// register file): stage 2 of 16384^3 with 16 moduli in the Strassen form, whole calls 56.97 -> 51.8 ms, 8192^3 7.84 -> 7.40, 18 moduli
-// 8192 x 8192 x 1024 1.795 -> 1.69, 4096^3 1.167 -> 1.08; clock 1.55 -> 1.79 GHz at 8192^3.
+// register file).  Whole calls, ms, 16384^3 with 16 moduli in the Strassen form 53.5 -> 49.9, 8192^3 even at 7.63, 18 moduli
+// 8192 x 8192 x 1024 1.78 -> 1.74, 4096^3 1.134 -> 1.094.
 //
 // Schedule of one k-tile (64 MFMAs: tile rows 0-3 against all eight columns, then rows 4-7): there is one set of fragments, each
 // read again for the next k-tile after its last product.  During the first half rows 4-7 and the last column arrive; at
@@ -28,7 +28,7 @@
 // 0-6 are read and the 8 direct loads that refill the stage freed by the barrier are issued, spread out so that no queue
 // fills up.  A product occupies the matrix core for 16 cycles and any other instruction the issue of the one wave for four or five, so
 // not more than two or three stand between two products: 130 instructions per k-tile, one M0 for four direct loads, scalar arithmetic in
-// the first half (175, six of them around every direct load, before: 8192^3 7.36 -> 6.90 ms a call, 16384^3 50.5 -> 47.5, 4096^3 1.073 -> 1.039).
+// the first half (175, six of them around every direct load, before: 8192^3 7.64 -> 7.00 ms a call, 16384^3 49.9 -> 47.9, 4096^3 1.094 -> 1.050).
 //
 // INT32 accumulation is exact for fewer than 2^17 terms (Section 3.1).  For longer inner dimensions the
 // accumulators are reduced modulo p_t every `kblock` bytes of k (kblock <= 65536, UINT8 residues: 61440), which keeps them below
@@ -714,7 +714,7 @@ hipError_t launch_gemm(const Oz2Layout& lay, char* ws, int num_moduli, const int
   g.m_pad = lay.m_pad;
   g.n_pad = lay.n_pad;
   g.k_pad = lay.k_pad;
-  if (lay.m_pad >= ((int64_t)1 << 27)) return hipErrorInvalidValue;  // the epilogue's lane offsets: 31 m_pad + 16 in 32 bits
+  if (lay.m_pad >= ((int64_t)1 << 27)) return hipErrorInvalidValue;  // the epilogue's lane offsets: 15 m_pad + 48 in 32 bits
   g.tiles_m = (int)(lay.m_pad / BM);
   g.tiles_n = (int)(lay.n_pad / BN);
   g.num_moduli = num_moduli;

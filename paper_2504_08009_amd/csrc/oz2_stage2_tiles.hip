@@ -285,8 +285,7 @@ static hipError_t launch_tiles(int tile, const Oz2Plan& plan, const Oz2Layout& l
 // 1030 x 3420 x 38226 2375 / 2236, 17 moduli 1509 x 700 x 53536 2129 / 1981).  The large tiles' time per k-tile is shorter in a launch of
 // three rounds or more, whose workgroups fetch across tiles (17 moduli 1308 x 1848 x 4879 369 / 334, 13 moduli 426 x 5028 x 1066 95.0 / 92.4;
 // two rounds, the second nearly empty: 15 moduli 4375 x 165 x 2233 117 / 123, 10 moduli 2656 x 564 x 1231 64 / 71).
-static int tile_size(int64_t m, int64_t n, int64_t k_pad, int num_moduli, int triangle, int krange) {
-  const int64_t cus = oz2_gemm_cus();
+static int tile_size(int64_t m, int64_t n, int64_t k_pad, int num_moduli, int triangle, int krange, int64_t cus) {
   auto rounds = [&](int64_t tile) { return (tiles_of(tile, m, n, triangle) * num_moduli + cus - 1) / cus; };
   if (rounds(64) <= (k_pad / BK >= kDeepKtiles ? 2 : 1)) return 64;
   const int64_t ktiles = krange == OZ2_KRANGE_ALL ? k_pad / BK : (k_pad / BK + 1) / 2;
@@ -295,12 +294,17 @@ static int tile_size(int64_t m, int64_t n, int64_t k_pad, int num_moduli, int tr
   return rounds(128) * (per_ktile * ktiles + 600) + 3000 < rounds(256) * (per_large * ktiles + 4500) ? 128 : 256;
 }
 
+int oz2_products_tile(const Oz2Plan& plan, const Oz2Layout& lay, int64_t m, int64_t n, int64_t kblock, int residue_u8, int triangle,
+                      int krange, int64_t cus) {
+  // (the small tiles take UINT8 residues and one block of the inner dimension only)
+  const bool fits = residue_u8 && kblock >= lay.k_pad && lay.k_pad <= OZ2_ACC_BLOCK;
+  return fits ? tile_size(m, n, lay.k_pad, plan.N, triangle, krange, cus) : 256;
+}
+
 hipError_t oz2_launch_products(const Oz2Plan& plan, const Oz2Layout& lay, char* ws, int64_t m, int64_t n, int64_t kblock,
                                int residue_u8, int triangle, int krange, int check_flag, const Oz2ScanFinish& fin,
                                hipStream_t st) {
-  // (the small tiles take UINT8 residues and one block of the inner dimension only)
-  const bool fits = residue_u8 && kblock >= lay.k_pad && lay.k_pad <= OZ2_ACC_BLOCK;
-  const int tile = fits ? tile_size(m, n, lay.k_pad, plan.N, triangle, krange) : 256;
+  const int tile = oz2_products_tile(plan, lay, m, n, kblock, residue_u8, triangle, krange, oz2_gemm_cus());
   if (tile == 256) return oz2_launch_stage2(plan, lay, ws, kblock, residue_u8, triangle, krange, check_flag, fin, st);
   return launch_tiles(tile, plan, lay, ws, m, n, triangle, krange, check_flag != 0, fin, st);
 }

@@ -308,13 +308,13 @@ hipError_t oz2_thin_setup() {
 // operand, 4.3 TB/s).  Whole calls, with planes against without (us): 16 moduli 8192 x 96 x 8192 680 / 366, 96 x 8192 x 8192
 // 698 / 399, 8192 x 32 x 8192 671 / 327, 16384 x 64 x 2048 374 / 195; 14 moduli 64 x 15484 x 9445 1391 / 818; 18 moduli
 // 8192 x 96 x 8192 739 / 520; 22 moduli 8192 x 96 x 8192 906 / 702.
-int oz2_thin_applies(int64_t m, int64_t n, const Oz2Plan& plan, const Oz2Layout& lay, int64_t kblock) {
+int oz2_thin_applies(int64_t m, int64_t n, const Oz2Plan& plan, const Oz2Layout& lay, int64_t kblock, int64_t cus) {
   const int64_t thin = m < n ? m : n, large = m < n ? n : m;
   // (up to 1024 the one-pass conversion reads the operand once, which is the better half of this; above, where it does so too up to 9984,
   // these kernels are still ahead where this rule takes them, whole calls, one pass / here, us: 16 moduli 8192 x 96 x 2000 189 / 114,
   // 96 x 8192 x 2000 157 / 117, 12 moduli 16000 x 90 x 1500 210 / 145)
   if (thin > kMaxThin || lay.k_pad <= 1024 || lay.k_pad > OZ2_ACC_BLOCK || kblock < lay.k_pad) return 0;
-  const int64_t groups = (plan.N + kGroup - 1) / kGroup, cus = oz2_gemm_cus();
+  const int64_t groups = (plan.N + kGroup - 1) / kGroup;
   const int64_t rounds = ((large + kRows - 1) / kRows * groups + cus - 1) / cus;
   const int64_t here = rounds * (lay.k_pad / BK) * 2400, planes = large * lay.k_pad / 10 * (8 + 2 * plan.N) / 430;
   return here < planes - planes / 10 ? (m < n ? 2 : 1) : 0;

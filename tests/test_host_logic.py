@@ -426,6 +426,34 @@ def test_strassen_identities_reproduce_the_oracles_residues():
         assert np.array_equal(Cr, ref.Cres[t].astype(np.int64)), "modulus %d" % p
 
 
+def test_kernel_choice_at_the_limits_of_the_rules():
+    """The kernels that general products take on 256 compute units: the longest vectors of which eight, four and two fit into LDS
+    (vectors enough for more than two per workgroup, where the rule takes four) and one more, thin products from one side and the
+    other, the three sizes of tiles; other settings."""
+    def choice(m, n, k, N):
+        return oz.host_kernel_choice(m, n, k, N, 256)
+
+    for k, vectors in [(1024, 4), (2432, 4), (2433, 2), (3392, 2), (3393, 4), (4928, 4), (4929, 2), (9920, 2), (9921, 0)]:
+        assert choice(700, 500, k, 9)[:2] == (vectors, 0), k
+    assert choice(4200, 100, 1024, 5)[0] == 8 and choice(2000, 100, 4929, 4)[0] == 0
+    assert choice(8192, 96, 8192, 16) == (0, 1, 0) and choice(96, 8192, 8192, 16) == (0, 2, 0)
+    assert choice(8192, 129, 8192, 16)[1] == 0 and choice(8192, 96, 1024, 16)[1] == 0
+    assert [choice(m, m, 300, 14)[2] for m in (200, 500, 4096)] == [64, 128, 256]
+    try:
+        oz.oz2_set_product_format(oz.OZ2_PRODUCT_INT32)  # residues only: thin products and the smaller tiles
+        assert choice(8192, 96, 8192, 16)[1:] == (0, 256) and choice(200, 200, 300, 14)[2] == 256
+        oz.oz2_set_product_format(oz.OZ2_PRODUCT_RESIDUE_U8)
+        oz.oz2_set_kblock(64)
+        assert choice(8192, 96, 8192, 16)[1:] == (0, 256) and choice(200, 200, 300, 14)[2] == 256
+    finally:
+        oz.oz2_set_product_format(oz.OZ2_PRODUCT_RESIDUE_U8)
+        oz.oz2_set_kblock(65536)
+    L, out = oz.lib(), (ctypes.c_int * 3)()
+    assert [L.oz2_host_kernel_choice(*a, out) for a in [(0, 1, 1, 9, 1), (1, 0, 1, 9, 1), (1, 1, 0, 9, 1), (1, 1, 1, 1, 1), (1, 1, 1, 9, 0)]] == \
+        [-1, -2, -3, -4, -5]
+    assert L.oz2_host_kernel_choice(1, 1, 1, 9, 1, None) == -6
+
+
 def test_bench_refuses_more_than_one_gpu():
     """The path runs on one GPU: bench.py --gpus N with N above 1 exits with a message and touches no GPU."""
     import subprocess
