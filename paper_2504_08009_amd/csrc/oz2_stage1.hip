@@ -897,8 +897,9 @@ hipError_t launch_convert(const Operand* ops, int nops, const int* kind, bool la
 // Vectors per workgroup of the one-pass conversion, or 0: the separate launches.  A workgroup's vectors have to fit its LDS, and
 // several workgroups should share a compute unit, so that some read while others convert; strided vectors ask for whole cache lines, i.e.
 // for many vectors.  Whole calls, us, two / four / eight vectors and separate launches, 14 moduli where not said: up to an inner dimension of
-// 1024, four / eight: 512^3 21.2 / 22.2, 700^3 29.9 / 30.6, 16 moduli 150 x 2500 x 900 41.2 / 42.9, 1000 x 1000 x 200 37.0 / 36.3, 12
-// moduli 2000 x 2000 x 100 57.3 / 54.5.  Up to 2496: 12 moduli 150 x 150 x 1100 20.1 / 21.2 / 23.3, 27.1 separately, 16 moduli
+// 1024, four / eight: 512^3 21.2 / 22.2, 700^3 29.9 / 30.6, 16 moduli 150 x 2500 x 900 40.2 / 42.3, 1000 x 1000 x 200 37.0 / 36.3, 12
+// moduli 1400 x 1400 x 1000 61.2 / 62.2, 2000 x 2000 x 100 57.3 / 54.5, 15 moduli 85 x 3412 x 643 35.3 / 31.9, 10 moduli
+// 1900 x 1900 x 600 70.3 / 67.9.  Up to 2496: 12 moduli 150 x 150 x 1100 20.1 / 21.2 / 23.3, 27.1 separately, 16 moduli
 // 1000 x 1000 x 1500 62.2 / 59.7 / 60.3, 73.9, 2048^3 183.7 / 181.0 / 182.6, 190.5, 8000 x 8000 x 2400 2390 / 2359 / 2383, 2406, dsyrk
 // 3000 x 2000 214 / 210 / 219, 231.  Up to 4992: 2000 x 200 x 3000 with 15 77.5 / 84.9, 88.3, 3000^3 482 / 482, 512, 1500 x 1500 x 4500
 // 229 / 213, 240, 16 moduli 4096^3 1169 / 1159, 1157, dtrmm of order 4096 with 2048 columns 522 / 525, 496.  Up to 9984: 300 x 300 x 5000
@@ -907,7 +908,7 @@ hipError_t launch_convert(const Operand* ops, int nops, const int* kind, bool la
 static int short_vectors(int64_t vectors, int64_t k_pad, bool two_level, int64_t cus) {
   const int64_t elements = vectors * k_pad;
   const auto fits = [&](int v) { return v * (k_pad + 4) * (int64_t)sizeof(double) <= kShortLds; };
-  if (k_pad <= 1024) return vectors <= (k_pad <= 256 ? 4 : k_pad <= 512 ? 8 : 16) * cus ? 4 : 8;
+  if (k_pad <= 1024) return vectors <= (k_pad <= 256 ? 4 : k_pad <= 512 ? 8 : 12) * cus ? 4 : 8;
   if (two_level && elements > (int64_t)3 << 22) return 0;
   if (fits(8)) return vectors <= 4 * cus ? 2 : 4;
   if (fits(4)) return elements > (int64_t)21 << 20 ? 0 : vectors <= 4 * cus || k_pad <= 3392 || two_level ? 2 : 4;

@@ -435,7 +435,10 @@ def test_kernel_choice_at_the_limits_of_the_rules():
 
     for k, vectors in [(1024, 4), (2432, 4), (2433, 2), (3392, 2), (3393, 4), (4928, 4), (4929, 2), (9920, 2), (9921, 0)]:
         assert choice(700, 500, k, 9)[:2] == (vectors, 0), k
-    assert choice(4200, 100, 1024, 5)[0] == 8 and choice(2000, 100, 4929, 4)[0] == 0
+    # up to 1024: four where a compute unit gets four, eight or twelve vectors, by their length, or fewer, eight where it gets more
+    for k, most in [(256, 1024), (512, 2048), (1024, 3072)]:
+        assert choice(most - 256, 100, k, 9)[0] == 4 and choice(most, 100, k, 9)[0] == 8, k
+    assert choice(85, 3412, 643, 15)[0] == 8 and choice(2000, 100, 4929, 4)[0] == 0
     assert choice(8192, 96, 8192, 16) == (0, 1, 0) and choice(96, 8192, 8192, 16) == (0, 2, 0)
     assert choice(8192, 129, 8192, 16)[1] == 0 and choice(8192, 96, 1024, 16)[1] == 0
     assert [choice(m, m, 300, 14)[2] for m in (200, 500, 4096)] == [64, 128, 256]
