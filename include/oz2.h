@@ -324,14 +324,15 @@ int oz2_set_kblock(int64_t kblock);
  * 0 <= spins <= 2^20.  Returns 0 or -1. */
 int oz2_set_round_sync(int spins);
 
-/* Which kernels oz2_dgemm / oz2_dgemm_ex take for a shape in the classical form, under the settings in force, on a device
- * with that many compute units: the rules that the launches follow, so that a test which aims at a kernel can tell that it
- * gets there.  No GPU is touched.
+/* Which kernels a call takes for a shape in the classical form, under the settings in force, on a device with that many
+ * compute units: the rules that the launches follow, so that a test which aims at a kernel can tell that it gets there.
+ * No GPU is touched.
+ *   call: 0: oz2_dgemm, oz2_dgemm_ex; 1: oz2_dsyrk (m == n); 2: oz2_dtrmm (k the order of A)
  *   choice[0]: vectors that a workgroup of the one-pass conversion holds (2, 4 or 8), 0: separate launches
  *   choice[1]: 1 / 2: thin product whose first / second operand is the large one, 0: not
  *   choice[2]: edge of the tiles of the products (64, 128 or 256), 0 for a thin product
  * m, n, k >= 1.  Returns 0 or a negative argument code. */
-int oz2_host_kernel_choice(int64_t m, int64_t n, int64_t k, int num_moduli, int compute_units, int choice[3]);
+int oz2_host_kernel_choice(int call, int64_t m, int64_t n, int64_t k, int num_moduli, int compute_units, int choice[3]);
 
 /* Host-side evaluation of the device routine for lines 7-10 and the final rounding (same source,
  * compiled for the host), for unit tests of the exact-arithmetic design: given the num_moduli INT32

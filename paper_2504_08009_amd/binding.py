@@ -74,7 +74,7 @@ def lib():
         L.oz2_calibrate_mfma.argtypes = [ci, ci, ci, vp, vp, vp]
         L.oz2_host_crt_element.argtypes = [ci, vp, vp]
         L.oz2_host_crt_element_digits.argtypes = [ci, vp, vp]
-        L.oz2_host_kernel_choice.argtypes = [i64, i64, i64, ci, ci, vp]
+        L.oz2_host_kernel_choice.argtypes = [ci, i64, i64, i64, ci, ci, vp]
         L.oz2_host_residues.argtypes = [ci, ci, ctypes.c_double, ci, vp]
         L.oz2_host_product_residues.argtypes = [ci, i64, vp, vp]
         L.oz2_status_string.restype = ctypes.c_char_p
@@ -264,10 +264,11 @@ def oz2_calibrate_mfma(workgroups, iters, random_operands, sink_ptr, clocks_ptr,
                                     _stream_ptr(stream)), "oz2_calibrate_mfma")
 
 
-def host_kernel_choice(m, n, k, num_moduli, compute_units):
-    """(vectors of the one-pass conversion, side of a thin product, edge of the product tiles) of a general product."""
+def host_kernel_choice(m, n, k, num_moduli, compute_units, call="dgemm"):
+    """(vectors of the one-pass conversion, side of a thin product, edge of the product tiles) of a call."""
     out = (ctypes.c_int * 3)()
-    _check(lib().oz2_host_kernel_choice(m, n, k, num_moduli, compute_units, out), "oz2_host_kernel_choice")
+    _check(lib().oz2_host_kernel_choice(("dgemm", "dsyrk", "dtrmm").index(call), m, n, k, num_moduli, compute_units, out),
+           "oz2_host_kernel_choice")
     return tuple(out)
 
 

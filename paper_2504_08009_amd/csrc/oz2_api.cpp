@@ -714,24 +714,26 @@ int oz2_calibrate_mfma(int workgroups, int iters, int random_operands, int* sink
   return e == hipSuccess ? OZ2_OK : OZ2_ERR_HIP;
 }
 
-int oz2_host_kernel_choice(int64_t m, int64_t n, int64_t k, int num_moduli, int compute_units, int choice[3]) {
-  if (m < 1) return -1;
-  if (n < 1) return -2;
-  if (k < 1) return -3;
-  if (!dims_ok(m, n, k)) return -1;
-  if (!n_ok(num_moduli)) return -4;
-  if (compute_units < 1) return -5;
-  if (!choice) return -6;
+int oz2_host_kernel_choice(int call, int64_t m, int64_t n, int64_t k, int num_moduli, int compute_units, int choice[3]) {
+  if (call < 0 || call > 2) return -1;
+  if (m < 1) return -2;
+  if (n < 1 || (call == 1 && n != m)) return -3;
+  if (k < 1 || (call == 2 && k != m && k != n)) return -4;
+  if (!dims_ok(m, n, k)) return -2;
+  if (!n_ok(num_moduli)) return -5;
+  if (compute_units < 1) return -6;
+  if (!choice) return -7;
   State& s = state();
   std::lock_guard<std::mutex> lock(s.mu);
   const Oz2Plan* plan;
-  if (get_plan(s, num_moduli, k, &plan) < 0) return -4;
+  if (get_plan(s, num_moduli, k, &plan) < 0) return -5;
   Oz2Layout lay;
   const int u8 = s.product_format == OZ2_PRODUCT_RESIDUE_U8;
   oz2_make_layout(m, n, k, num_moduli, u8 ? 1 : 4, &lay);
-  choice[1] = u8 ? oz2_thin_applies(m, n, *plan, lay, s.kblock, compute_units) : 0;
-  choice[0] = choice[1] ? 0 : oz2_one_pass_vectors(*plan, lay, 0, s.shift_mode, s.bit_split, compute_units);
-  choice[2] = choice[1] ? 0 : oz2_products_tile(*plan, lay, m, n, s.kblock, u8, 0, OZ2_KRANGE_ALL, compute_units);
+  const int krange = call == 2 ? OZ2_KRANGE_UPTO_ROW : OZ2_KRANGE_ALL;  // (the rules treat the four ranges alike)
+  choice[1] = u8 && call == 0 ? oz2_thin_applies(m, n, *plan, lay, s.kblock, compute_units) : 0;
+  choice[0] = choice[1] ? 0 : oz2_one_pass_vectors(*plan, lay, call == 1, s.shift_mode, call == 0 ? s.bit_split : 0, compute_units);
+  choice[2] = choice[1] ? 0 : oz2_products_tile(*plan, lay, m, n, s.kblock, u8, call == 1, krange, compute_units);
   return OZ2_OK;
 }
 

@@ -442,6 +442,9 @@ def test_kernel_choice_at_the_limits_of_the_rules():
     assert choice(8192, 96, 8192, 16) == (0, 1, 0) and choice(96, 8192, 8192, 16) == (0, 2, 0)
     assert choice(8192, 129, 8192, 16)[1] == 0 and choice(8192, 96, 1024, 16)[1] == 0
     assert [choice(m, m, 300, 14)[2] for m in (200, 500, 4096)] == [64, 128, 256]
+    assert [oz.host_kernel_choice(m, m, k, 14, 256, "dsyrk") for m, k in [(200, 300), (500, 300), (5000, 1024)]] == [(4, 0, 64), (4, 0, 128), (8, 0, 256)]
+    # triangular products have no workgroups that fetch across tiles, which large tiles would have to themselves
+    assert oz.host_kernel_choice(1000, 2700, 1000, 14, 256, "dtrmm") == (8, 0, 128)
     try:
         oz.oz2_set_product_format(oz.OZ2_PRODUCT_INT32)  # residues only: thin products and the smaller tiles
         assert choice(8192, 96, 8192, 16)[1:] == (0, 256) and choice(200, 200, 300, 14)[2] == 256
@@ -452,9 +455,9 @@ def test_kernel_choice_at_the_limits_of_the_rules():
         oz.oz2_set_product_format(oz.OZ2_PRODUCT_RESIDUE_U8)
         oz.oz2_set_kblock(65536)
     L, out = oz.lib(), (ctypes.c_int * 3)()
-    assert [L.oz2_host_kernel_choice(*a, out) for a in [(0, 1, 1, 9, 1), (1, 0, 1, 9, 1), (1, 1, 0, 9, 1), (1, 1, 1, 1, 1), (1, 1, 1, 9, 0)]] == \
-        [-1, -2, -3, -4, -5]
-    assert L.oz2_host_kernel_choice(1, 1, 1, 9, 1, None) == -6
+    assert [L.oz2_host_kernel_choice(*a, out) for a in [(3, 1, 1, 1, 9, 1), (0, 0, 1, 1, 9, 1), (1, 2, 1, 1, 9, 1), (2, 1, 1, 2, 9, 1),
+                                                     (0, 1, 1, 1, 1, 1), (0, 1, 1, 1, 9, 0)]] == [-1, -2, -3, -4, -5, -6]
+    assert L.oz2_host_kernel_choice(0, 1, 1, 1, 9, 1, None) == -7
 
 
 def test_bench_refuses_more_than_one_gpu():
