@@ -125,14 +125,15 @@ def test_thin_products_of_the_longest_sums(first):
     del ws
 
 
-@pytest.mark.parametrize("int32", [True, False])
-@pytest.mark.parametrize("k", [1, 64, 65, 130, 193, 257, 321, 400, 513])
-def test_large_tiles_with_few_k_tiles_several_per_workgroup(k, int32):
-    """The main loop of the large tiles fetches across the ends of tiles that are shorter than its ring of stages, as long, and longer:
-    inner dimensions of one k-tile to nine, more tiles than compute units, both result formats, ragged last tiles."""
-    m, n, N = 2299, 2227, 12
+@pytest.mark.parametrize("m,n,N,k,int32", [(2299, 2227, 12, k, True) for k in [1, 64, 65, 130, 193, 257, 321, 400, 513]] +
+                         [(2047, 2040, 4, k, False) for k in [1, 64]] + [(2047, 2040, 8, k, False) for k in [65, 128, 130, 192]] +
+                         [(2299, 2227, 12, k, False) for k in [193, 257, 321, 400, 513]])
+def test_large_tiles_with_few_k_tiles_several_per_workgroup(m, n, N, k, int32):
+    """The main loop of the large tiles, whose ring has four stages, on inner dimensions of one k-tile to nine, more tiles than compute
+    units, both result formats, ragged last tiles.  With UINT8 residues two or three k-tiles take the large tiles at two per workgroup, a
+    single one only where each workgroup has one tile."""
     rng = np.random.default_rng(k)
-    print("large tiles: k=%d int32=%s" % (k, int32), flush=True)
+    print("large tiles: m=%d n=%d k=%d N=%d int32=%s" % (m, n, k, N, int32), flush=True)
     A = np.asfortranarray(rng.standard_normal((m, k)))
     B = np.asfortranarray(rng.standard_normal((k, n)))
     dA = torch.from_numpy(np.ascontiguousarray(A.T)).cuda().t()
@@ -140,12 +141,13 @@ def test_large_tiles_with_few_k_tiles_several_per_workgroup(k, int32):
     dC = torch.zeros((n, m), dtype=torch.float64, device="cuda")
     oz.oz2_set_product_format(oz.OZ2_PRODUCT_INT32 if int32 else oz.OZ2_PRODUCT_RESIDUE_U8)
     try:
+        assert oz.host_kernel_choice(m, n, k, N, torch.cuda.get_device_properties(0).multi_processor_count)[2] == 256
         ws = oz.Workspace(m, n, k, N)
         oz.oz2_dgemm(m, n, k, dA.data_ptr(), m, dB.data_ptr(), k, dC.data_ptr(), m, N)
         torch.cuda.synchronize()
     finally:
         oz.oz2_set_product_format(oz.OZ2_PRODUCT_RESIDUE_U8)
-    rows = [0, 15, 16, 127, 128, 255, 256, 1111, 2047, 2048, m - 1]
+    rows = [r for r in [0, 15, 16, 127, 128, 255, 256, 1111, 1792, 2046, 2047, 2048, m - 1] if r < m]
     got = dC.t()[rows].cpu().numpy()
     assert np.array_equal(got, orc.dgemm(A, B, N, rows=rows).C)
     del ws

@@ -1,5 +1,5 @@
 """Small products against the oracle, every bit of C: sizes at the edges of the 64 x 64, 128 x 128 and 256 x 256 tiles of
-the products, inner dimensions at the edges of a k-tile and of the one-pass conversion (1024), both orientations of either
+the products, inner dimensions at the edges of a k-tile and of the one-pass conversion's forms, both orientations of either
 operand, operands split one and two levels deep, and infinities / NaNs in the last vector of the last workgroup."""
 import numpy as np
 import pytest
@@ -28,6 +28,10 @@ def _gemm(ta, tb, A, B, N, beta=0.0):
     torch.cuda.synchronize()
     flag = int(ws.view(oz.workspace_layout(m, n, k, N)["flags"], 1, torch.int64).item())
     return dC.cpu().numpy(), orc.dgemm_ex(ta, tb, 1.0, A, B, beta, C0, N), flag
+
+
+def _choice(m, n, k, N):
+    return oz.host_kernel_choice(m, n, k, N, torch.cuda.get_device_properties(0).multi_processor_count)
 
 
 def _mat(rng, r, c):
@@ -73,11 +77,13 @@ def test_every_number_of_moduli(m, n, N):
 
 
 @pytest.mark.parametrize("mode", [0, 1, 2])
-@pytest.mark.parametrize("m,n,k,N", [(60, 40, 1025, 3), (300, 200, 1999, 14), (700, 500, 2496, 9), (1200, 100, 2497, 5), (40, 700, 3393, 15),
-                                     (2000, 100, 4992, 4), (70, 300, 4993, 16), (256, 130, 6209, 22), (30, 20, 9984, 21), (30, 20, 9985, 21)])
-def test_one_pass_conversion_of_long_vectors(m, n, k, N, mode):
-    """Two, four and eight vectors per workgroup, the longest that fit and one more, in every shift mode; inner dimensions at which the
-    large tiles' round synchronisation needs its counters cleared ahead."""
+@pytest.mark.parametrize("m,n,k,N,vectors", [
+    (2000, 2300, 250, 6, 8), (4000, 300, 512, 7, 8), (4200, 100, 1024, 5, 8), (60, 40, 1025, 3, 2), (300, 200, 1999, 14, 2), (700, 500, 2432, 9, 4),
+    (700, 500, 2433, 9, 2), (1200, 100, 2433, 5, 2), (40, 700, 3393, 15, 2), (300, 800, 3393, 15, 4), (2000, 100, 4928, 4, 4), (700, 500, 4929, 6, 2),
+    (70, 300, 4929, 16, 2), (256, 130, 6209, 22, 2), (30, 20, 9920, 21, 2), (30, 20, 9921, 21, 0)])
+def test_one_pass_conversion_of_long_vectors(m, n, k, N, vectors, mode):
+    """Two, four and eight vectors per workgroup in every shift mode; four and two at the longest that fit into LDS (2432 is the last
+    inner dimension of eight, at which four are taken, 4928 that of four and 9920 that of two) and at one more."""
     rng = np.random.default_rng(3 * m + n + k)
     ta, tb = [("N", "N"), ("T", "T"), ("N", "T")][(k + mode) % 3]
     print("long: m=%d n=%d k=%d N=%d mode=%d op=%s%s" % (m, n, k, N, mode, ta, tb), flush=True)
@@ -90,6 +96,7 @@ def test_one_pass_conversion_of_long_vectors(m, n, k, N, mode):
     flags = ws.view(oz.workspace_layout(m, n, k, N)["flags"], 1, torch.int64)
     oz.oz2_set_shift_mode(mode)
     try:
+        assert _choice(m, n, k, N)[0] == vectors
         args = (ta, tb, m, n, k, 1.0, dA.data_ptr(), A.shape[0], dB.data_ptr(), B.shape[0], 0.0, dC.data_ptr(), m, N)
         oz.oz2_dgemm_ex(*args)
         torch.cuda.synchronize()
@@ -423,6 +430,7 @@ def test_thin_products_convert_the_large_operand_on_the_way(thin, ta, tb, first)
     large, k = 12337, 1101
     N = {1: 16, 32: 15, 33: 24, 97: 8, 128: 23}[thin]
     m, n = (large, thin) if first else (thin, large)
+    assert _choice(m, n, k, N)[1] == (1 if first else 2)
     rng = np.random.default_rng(thin)
     A = _mat(rng, *((m, k) if ta == "N" else (k, m)))
     B = _mat(rng, *((k, n) if tb == "N" else (n, k)))
@@ -482,6 +490,7 @@ def test_triangular_operand_of_which_only_the_used_half_is_converted(side, uplo,
 def test_thin_products_at_the_ends_of_the_inner_dimension(k, ta):
     """Even and odd numbers of k-tiles, the last one whole or not: the loop takes two at a time."""
     m, n, N = 12337, 40, 16
+    assert _choice(m, n, k, N)[1] == 1
     rng = np.random.default_rng(k)
     A = _mat(rng, *((m, k) if ta == "N" else (k, m)))
     B = _mat(rng, k, n)
@@ -498,12 +507,13 @@ def test_thin_products_at_the_ends_of_the_inner_dimension(k, ta):
 
 
 @pytest.mark.parametrize("k", [1025, 1089, 1153, 1217, 1281, 1344])
-@pytest.mark.parametrize("thin,N,first", [(20, 16, True), (32, 15, False), (96, 16, True), (70, 13, False), (31, 23, True), (90, 24, False)])
-def test_thin_products_two_k_tiles_at_a_time(thin, N, first, k):
+@pytest.mark.parametrize("large,thin,N,first", [(5003, 20, 16, True), (5003, 32, 15, False), (5003, 96, 16, True), (7003, 70, 13, False),
+                                                (5003, 31, 23, True), (5003, 90, 24, False)])
+def test_thin_products_two_k_tiles_at_a_time(large, thin, N, first, k):
     """One and three 32-vector tiles of the thin operand with at most one workgroup per compute unit, elements split one and two levels
     deep, every remainder of the number of k-tiles that the loop's rounds and its last fetches can meet."""
-    large = 5003
     m, n = (large, thin) if first else (thin, large)
+    assert _choice(m, n, k, N)[1] == (1 if first else 2)
     rng = np.random.default_rng(thin + k)
     A, B = _mat(rng, m, k), _mat(rng, k, n)
     print("thin pairs: m=%d n=%d k=%d N=%d" % (m, n, k, N), flush=True)
