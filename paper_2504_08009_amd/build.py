@@ -65,12 +65,11 @@ def named_register_faults(assembly):
             last = int(high, 0) if high else first
             if kind == "v" and last < NAMED_VGPR:
                 continue
-            # a statement of the source: a whole tile, as the result or the accumulator of a product, or one register counted from
-            # a tile's first
+            # a statement of the source: a whole tile of four registers, as the result or the accumulator of a product, or one
+            # register counted from a tile's first
             base = NAMED_VGPR if kind == "v" else NAMED_AGPR
-            count = last - first + 1
-            tile = count in (4, 16) and (first - base) % count == 0 and code[:found.start()].count(",") in (0, 3)
-            if inside and first >= base and (tile or (offset and (first - base) % 4 == 0)):
+            named = code[:found.start()].count(",") in (0, 3) if last == first + 3 else offset and int(offset) < 4
+            if inside and first >= base and (first - base) % 4 == 0 and named:
                 continue
             faults.append((kernel, code))
     if not kernels:

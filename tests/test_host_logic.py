@@ -477,8 +477,8 @@ def test_build_rejects_a_gemm_whose_accumulator_registers_the_compiler_uses():
 
     def faults(*lines):
         body = ["_ZN1_14gemm_i8_kernelILb1EEEv: ; @_ZN1_14gemm_i8_kernelILb1EEEv", "\tv_add_u32_e32 v75, v1, v111 ; v200 here is a comment",
-                "\t;;#ASMSTART", "\tv_mfma_i32_32x32x32_i8 v[112:127], v[4:7], v[32:35], 0", "", "\t;;#ASMEND",
-                "\t;;#ASMSTART", "\tv_accvgpr_read_b32 v7, a[240+15]", "\tv_dot4_u32_u8 v7, v7, v1, v2", "\t;;#ASMEND"]
+                "\t;;#ASMSTART", "\tv_mfma_i32_16x16x64_i8 v[112:115], v[4:7], v[32:35], 0", "", "\t;;#ASMEND",
+                "\t;;#ASMSTART", "\tv_accvgpr_read_b32 v7, a[240+3]", "\tv_dot4_u32_u8 v7, v7, v1, v2", "\t;;#ASMEND"]
         return len(b.named_register_faults("\n".join(body + list(lines) + [".Lfunc_end0:", "\tv_mov_b32_e32 v250, v1"])))
 
     assert faults() == 0
@@ -486,6 +486,9 @@ def test_build_rejects_a_gemm_whose_accumulator_registers_the_compiler_uses():
     assert faults("\tds_read_b128 v[110:113], v3") == 1                  # ... or reaching into one
     assert faults("\tglobal_load_dwordx4 a[0:3], v[4:5], off") == 1      # accumulation registers are not its to use
     assert faults("\tscratch_store_dwordx2 off, v[10:11], off") == 1
-    assert faults("\t;;#ASMSTART", "\tv_mfma_i32_32x32x32_i8 v[112:127], v[128:131], v[32:35], 0", "\t;;#ASMEND") == 1
+    assert faults("\t;;#ASMSTART", "\tv_mfma_i32_16x16x64_i8 v[112:115], v[128:131], v[32:35], 0", "\t;;#ASMEND") == 1
+    assert faults("\t;;#ASMSTART", "\tv_mfma_i32_32x32x32_i8 v[112:127], v[4:7], v[32:35], 0", "\t;;#ASMEND") == 1  # a tile has four
+    assert faults("\t;;#ASMSTART", "\tv_mfma_i32_16x16x64_i8 v[114:117], v[4:7], v[32:35], 0", "\t;;#ASMEND") == 1  # parts of two tiles
+    assert faults("\t;;#ASMSTART", "\tv_accvgpr_read_b32 v7, a[240+4]", "\t;;#ASMEND") == 1
     assert faults("\t;;#ASMSTART", "\tv_mov_b32 v120, v[112+3]", "\t;;#ASMEND") == 1
     assert len(b.named_register_faults("_ZN1_11other_kernelEv:\n\tv_mov_b32_e32 v250, v1\n")) == 1  # the kernels are not there
