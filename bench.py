@@ -430,7 +430,7 @@ def main():
             torch.cuda.synchronize()
             ms = e0.elapsed_time(e1)
             cyc, ref = [int(v) for v in clocks.cpu()]
-            out["context"]["mfma_only_%s_operands_TOPs" % label] = round(512 * 4 * iters * 8 * 65536.0 / (ms * 1e-3) / 1e12, 1)
+            out["context"]["mfma_only_%s_operands_TOPs" % label] = round(512 * 4 * iters * 16 * 32768.0 / (ms * 1e-3) / 1e12, 1)
             out["context"]["mfma_only_%s_operands_GHz" % label] = round(cyc / max(ref, 1) * 0.1, 3)
         # the GEMM against what the matrix cores of this card sustain on random INT8 operands with no memory
         # traffic at all (the card is power-capped well below the published peak)

@@ -295,9 +295,9 @@ int oz2_set_bit_split(int delta);
  * their order do not change.  events == NULL switches the hooks off.  Returns 0. */
 int oz2_set_stage_events(void* const events[4]);
 
-/* Measurement support: an MFMA-only kernel (v_mfma_i32_32x32x32_i8, no memory traffic) that shows what
+/* Measurement support: an MFMA-only kernel (v_mfma_i32_16x16x64_i8, as in the large GEMM, no memory traffic) that shows what
  * the matrix cores of the card sustain under its power cap.  `workgroups` x 256 threads each issue
- * iters x 8 MFMAs (65536 INT8 operations per wave and MFMA); random_operands: 0 fills the operand registers with a
+ * iters x 16 MFMAs (32768 INT8 operations per wave and MFMA); random_operands: 0 fills the operand registers with a
  * constant, 1 with random bytes (two fragments per operand, reused by every instruction), 2 with random bytes in
  * eight fragments per operand that meet in changing pairs, as the fragments of a product do (iters should then
  * be a multiple of 8).  sink: device buffer of workgroups*256 ints (written).

@@ -20,6 +20,7 @@ HIP_FLAGS = [
 # vector registers (otherwise every result is copied out of the accumulation registers, and the accumulator start copied
 # in, one instruction per register).
 EXTRA_FLAGS = {
+    "oz2_calibrate.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "oz2_stage3.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "oz2_stage2_tiles.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "oz2_thin.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
