@@ -1,7 +1,7 @@
 // Stage 1 of Ozaki scheme II on gfx950: Algorithm 1 lines 1-5.
 //   1a  per-row maximum of |A| and per-column maximum of |B| (bit patterns, 64-bit atomic max)
 //   1a' shifts  sa_i = kappa - 1 - floor(log2 max_l |a_il|),  sb_j likewise  (Section 3, D and E); or, in the
-//       modes of Section 4.1, from an integer bound of the 2-norms (one more pass over A and B) or from the
+//       modes of Section 4.1, from an integer bound of the 2-norms (one more pass over vectors that do not fit into LDS) or from the
 //       row / column maxima of an INT8 product of 6-bit upper bounds of |A| and |B| (bound planes, one GEMM
 //       launch, one pass over the product)
 //   1b  a' = trunc(a * 2^sa_i) and its symmetric residues modulo every p_t, written as INT8 planes in the
@@ -244,7 +244,7 @@ __global__ void __launch_bounds__(kThreads) shifts_kernel(const ShiftJob ja, con
   j.s[i] = shift_of(j.mx[i], mode == 0 ? 0ull : j.aux[i], mode, j.param, j.offset);
 }
 
-// ---- Operands whose vectors are too long for that: maxima, in the Cauchy-Schwarz mode the norm bounds, and shifts of both in ONE launch and
+// ---- Operands whose vectors are too long for the one-pass conversion (below): maxima, in the Cauchy-Schwarz mode the norm bounds, and shifts of both in ONE launch and
 // without atomics, so that nothing has to be cleared first: a workgroup owns 16 whole vectors, forms their maxima (and
 // from them, reading the vectors once more out of the caches, the sums of squares), writes them and the shifts, and reports
 // in a slot of its own whether it saw an infinity or a NaN.  The conversion launch that follows folds the slots into the
@@ -617,6 +617,8 @@ __global__ void __launch_bounds__(kThreads) operand_convert_kernel(const ConvJob
 // groups, which read the other parts of the same cache lines, are placed on the same die.
 constexpr int kShortThreads = 512;
 constexpr int kShortLds = 156 * 1024;  // of 160 KiB, what a workgroup's vectors may take
+constexpr int short_longest(int vectors) { return (kShortLds / (8 * vectors) - 4) / kBlkK * kBlkK; }  // padded inner dimension
+static_assert(short_longest(8) == 2432 && short_longest(4) == 4928 && short_longest(2) == 9920, "the lines of short_vectors");
 struct ShortJob {
   const double* X;
   int64_t ld, nvec, nvec_pad, k, k_pad;
@@ -899,15 +901,15 @@ hipError_t launch_convert(const Operand* ops, int nops, const int* kind, bool la
 // for many vectors.  Whole calls, us, two / four / eight vectors and separate launches, 14 moduli where not said: up to an inner dimension of
 // 1024, four / eight: 512^3 21.2 / 22.2, 700^3 29.9 / 30.6, 16 moduli 150 x 2500 x 900 40.2 / 42.3, 1000 x 1000 x 200 37.0 / 36.3, 12
 // moduli 1400 x 1400 x 1000 61.2 / 62.2, 2000 x 2000 x 100 57.3 / 54.5, 15 moduli 85 x 3412 x 643 35.3 / 31.9, 10 moduli
-// 1900 x 1900 x 600 70.3 / 67.9.  Up to 2496: 12 moduli 150 x 150 x 1100 20.1 / 21.2 / 23.3, 27.1 separately, 16 moduli
+// 1900 x 1900 x 600 70.3 / 67.9.  Up to 2432: 12 moduli 150 x 150 x 1100 20.1 / 21.2 / 23.3, 27.1 separately, 16 moduli
 // 1000 x 1000 x 1500 62.2 / 59.7 / 60.3, 73.9, 2048^3 183.7 / 181.0 / 182.6, 190.5, 8000 x 8000 x 2400 2390 / 2359 / 2383, 2406, dsyrk
-// 3000 x 2000 214 / 210 / 219, 231.  Up to 4992: 2000 x 200 x 3000 with 15 77.5 / 84.9, 88.3, 3000^3 482 / 482, 512, 1500 x 1500 x 4500
-// 229 / 213, 240, 16 moduli 4096^3 1169 / 1159, 1157, dtrmm of order 4096 with 2048 columns 522 / 525, 496.  Up to 9984: 300 x 300 x 5000
+// 3000 x 2000 214 / 210 / 219, 231.  Up to 4928: 2000 x 200 x 3000 with 15 77.5 / 84.9, 88.3, 3000^3 482 / 482, 512, 1500 x 1500 x 4500
+// 229 / 213, 240, 16 moduli 4096^3 1169 / 1159, 1157, dtrmm of order 4096 with 2048 columns 522 / 525, 496.  Up to 9920: 300 x 300 x 5000
 // with 16 64.2, 96.6, 500 x 500 x 8000 103, 139, 1000 x 1000 x 8000 208, 214, 2000 x 2000 x 8000 628, 607.  Elements split two levels
 // deep, 22 moduli: 700 x 3000 x 4000 341 / 347, 345, 4096 x 4096 x 2048 892 / 889 / 882, 886.
 static int short_vectors(int64_t vectors, int64_t k_pad, bool two_level, int64_t cus) {
   const int64_t elements = vectors * k_pad;
-  const auto fits = [&](int v) { return v * (k_pad + 4) * (int64_t)sizeof(double) <= kShortLds; };
+  const auto fits = [&](int v) { return k_pad <= short_longest(v); };
   if (k_pad <= 1024) return vectors <= (k_pad <= 256 ? 4 : k_pad <= 512 ? 8 : 12) * cus ? 4 : 8;
   if (two_level && elements > (int64_t)3 << 22) return 0;
   if (fits(8)) return vectors <= 4 * cus ? 2 : 4;

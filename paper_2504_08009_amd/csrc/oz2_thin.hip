@@ -310,7 +310,7 @@ hipError_t oz2_thin_setup() {
 // 8192 x 96 x 8192 739 / 520; 22 moduli 8192 x 96 x 8192 906 / 702.
 int oz2_thin_applies(int64_t m, int64_t n, const Oz2Plan& plan, const Oz2Layout& lay, int64_t kblock, int64_t cus) {
   const int64_t thin = m < n ? m : n, large = m < n ? n : m;
-  // (up to 1024 the one-pass conversion reads the operand once, which is the better half of this; above, where it does so too up to 9984,
+  // (up to 1024 the one-pass conversion reads the operand once, which is the better half of this; above, where it does so too up to 9920,
   // these kernels are still ahead where this rule takes them, whole calls, one pass / here, us: 16 moduli 8192 x 96 x 2000 189 / 114,
   // 96 x 8192 x 2000 157 / 117, 12 moduli 16000 x 90 x 1500 210 / 145)
   if (thin > kMaxThin || lay.k_pad <= 1024 || lay.k_pad > OZ2_ACC_BLOCK || kblock < lay.k_pad) return 0;
