@@ -37,7 +37,10 @@ constexpr int BK = OZ2_TILE_K;
 constexpr int kBlk = OZ2_TILE_M;        // plane layout: blocks of 256 rows x 64 bytes
 constexpr int kTileBytes = kRows * BK;  // one modulus in LDS
 constexpr int kMaxThin = 128;
-constexpr int thin_lds_bytes(bool paired) { return (paired ? 4 : 2) * kGroup * kTileBytes; }  // k-tiles in LDS
+template <int KIND, bool PAIRED>
+constexpr bool kArray = !PAIRED && KIND == 0;
+template <int KIND, bool PAIRED>
+constexpr int kThinLds = kArray<KIND, PAIRED> ? 0 : (PAIRED ? 4 : 2) * kGroup * kTileBytes;  // of the launch's own size
 constexpr int kMfmaSteps = 8;           // steps of a k-tile's conversion that carry its products
 
 struct ThinArgs {
@@ -60,8 +63,13 @@ struct ThinArgs {
 template <int KIND, int NI, bool BIG_A, bool PAIRED>
 __global__ void __launch_bounds__(kThreads) thin_products_kernel(const ThinArgs g) {
   constexpr bool TWO_LEVEL = KIND == 1;
+  // The k-tiles in LDS: of the launch's own size, or two in an array, for which the compiler makes another schedule: the better one for
+  // elements split one level deep (16 moduli 128 x 5824 x 14528 785 -> 766 us a call, 18 moduli 128 x 8195 x 9097 968 -> 929), not for
+  // two (22 moduli 8192 x 128 x 8192 788 -> 826).
+  constexpr bool ARRAY = kArray<KIND, PAIRED>;
   extern __shared__ __attribute__((aligned(1024))) char thin_lds[];
-  auto lds = reinterpret_cast<char(*)[kGroup][kTileBytes]>(thin_lds);
+  auto own = reinterpret_cast<char(*)[kGroup][kTileBytes]>(thin_lds);
+  __shared__ __attribute__((aligned(1024))) char two[ARRAY ? 2 : 1][ARRAY ? kGroup : 1][ARRAY ? kTileBytes : 16];
   if (g.skip_flag != nullptr && *g.skip_flag != 0ull) return;
   const int item = (int)(blockIdx.x & 7) * g.chunk + (int)(blockIdx.x >> 3);  // workgroup i of a launch runs on die i % 8
   if (item >= g.total) return;
@@ -116,7 +124,10 @@ __global__ void __launch_bounds__(kThreads) thin_products_kernel(const ThinArgs 
         for (int h = 0; h < 2; ++h)
           w[h] = oz2_pack_pairs(oz2_residue_pair<TWO_LEVEL>(xs[2 * h], mods[tt]),
                                 oz2_residue_pair<TWO_LEVEL>(xs[2 * h + 1], mods[tt]));
-        *reinterpret_cast<v2u*>(&lds[buf][tt][put]) = w;
+        if constexpr (ARRAY)
+          *reinterpret_cast<v2u*>(&two[buf][tt][put]) = w;
+        else
+          *reinterpret_cast<v2u*>(&own[buf][tt][put]) = w;
       }
       after(4 + tt);
     }
@@ -144,7 +155,11 @@ __global__ void __launch_bounds__(kThreads) thin_products_kernel(const ThinArgs 
       for (int e = 0; e < 16; ++e) acc[x][y][e] = (int)OZ2_ACC_START;
 
   auto fragments = [&](int slot, v4i (&fb)[2][2]) {
-    const char* base = lds[slot][works ? wv : 0] + (lane & 31) * BK;
+    const char* base;
+    if constexpr (ARRAY)
+      base = two[slot][works ? wv : 0] + (lane & 31) * BK;
+    else
+      base = own[slot][works ? wv : 0] + (lane & 31) * BK;
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
@@ -262,16 +277,16 @@ constexpr bool kSingles = NI == 4 || (NI == 1 && KIND == 0);
 template <int KIND, int NI, bool PAIRED>
 hipError_t set_thin_lds() {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(thin_products_kernel<KIND, NI, true, PAIRED>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, thin_lds_bytes(PAIRED));
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, kThinLds<KIND, PAIRED>);
   if (e != hipSuccess) return e;
   return hipFuncSetAttribute(reinterpret_cast<const void*>(thin_products_kernel<KIND, NI, false, PAIRED>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, thin_lds_bytes(PAIRED));
+                             hipFuncAttributeMaxDynamicSharedMemorySize, kThinLds<KIND, PAIRED>);
 }
 template <int KIND, int NI>
 hipError_t set_thin() {
   hipError_t e = hipSuccess;
   if constexpr (kPairs<KIND, NI>) e = set_thin_lds<KIND, NI, true>();
-  if constexpr (kSingles<KIND, NI>) e = e == hipSuccess ? set_thin_lds<KIND, NI, false>() : e;
+  if constexpr (kSingles<KIND, NI> && !kArray<KIND, false>) e = e == hipSuccess ? set_thin_lds<KIND, NI, false>() : e;
   return e;
 }
 template <int KIND>
@@ -288,11 +303,11 @@ void launch_thin(const ThinArgs& g, hipStream_t st) {
   const bool two_fit = g.total > oz2_gemm_cus();
   if constexpr (kPairs<KIND, NI> && kSingles<KIND, NI>) {
     if (two_fit) {
-      hipLaunchKernelGGL((thin_products_kernel<KIND, NI, BIG_A, false>), grid, thr, thin_lds_bytes(false), st, g);
+      hipLaunchKernelGGL((thin_products_kernel<KIND, NI, BIG_A, false>), grid, thr, (kThinLds<KIND, false>), st, g);
       return;
     }
   }
-  hipLaunchKernelGGL((thin_products_kernel<KIND, NI, BIG_A, kPairs<KIND, NI>>), grid, thr, thin_lds_bytes(kPairs<KIND, NI>), st, g);
+  hipLaunchKernelGGL((thin_products_kernel<KIND, NI, BIG_A, kPairs<KIND, NI>>), grid, thr, (kThinLds<KIND, kPairs<KIND, NI>>), st, g);
 }
 
 }  // namespace
