@@ -41,14 +41,14 @@ struct TileArgs {
   Oz2FoldConsts fold[OZ2_MAX_N];
 };
 
-// MI x NI MFMA tiles of 32 x 32 per wave, NS stages, WGS workgroups per compute unit
-template <int MI, int NI, int NS, int WGS>
+// MI x NI MFMA tiles of 32 x 32 per wave, NS stages, WGS workgroups per compute unit; WARM: a launch of few workgroups
+template <int MI, int NI, int NS, int WGS, bool WARM>
 __global__ void __launch_bounds__(kThreads, WGS) gemm_i8_tile_kernel(const TileArgs g) {
   constexpr int TM = 64 * MI, TN = 64 * NI;
   constexpr int kStage = (TM + TN) * BK;
   constexpr int kLoadsA = MI, kLoadsB = NI, kLoads = kLoadsA + kLoadsB;  // direct loads of 1 KiB per wave and k-tile
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  warm_arguments(g);
+  if constexpr (WARM) warm_arguments(g);
 
   if (g.skip_flag != nullptr && *g.skip_flag != 0ull) return;
   if (g.fin.slots != nullptr && !g.fin_stops && blockIdx.x == 0) finish_scan(g.fin);
@@ -170,17 +170,17 @@ __global__ void __launch_bounds__(kThreads, WGS) gemm_i8_tile_kernel(const TileA
   wait_vmcnt<0>();  // the copies fetched beyond the last k-tile must have landed before the LDS is given back
 }
 
-template <int MI, int NI, int NS, int WGS>
+template <int MI, int NI, int NS>
 constexpr int kTileLds = NS * 64 * (MI + NI) * BK;
 
-template <int MI, int NI, int NS, int WGS>
+template <int MI, int NI, int NS, int WGS, bool WARM>
 hipError_t set_lds() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_i8_tile_kernel<MI, NI, NS, WGS>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, kTileLds<MI, NI, NS, WGS>);
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_i8_tile_kernel<MI, NI, NS, WGS, WARM>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, kTileLds<MI, NI, NS>);
 }
 
 // flag: the flag word when the products are not needed once it is set, else null
-template <int MI, int NI, int NS, int WGS>
+template <int MI, int NI, int NS, int WGS, bool WARM>
 hipError_t launch(TileArgs& g, int64_t m, int64_t n, int planes, const unsigned long long* flag, hipStream_t st) {
   constexpr int TM = 64 * MI, TN = 64 * NI;
   g.tiles_m = (int)((m + TM - 1) / TM);
@@ -212,17 +212,18 @@ hipError_t launch(TileArgs& g, int64_t m, int64_t n, int planes, const unsigned 
       g.skip_flag = flag;
     }
   }
-  hipLaunchKernelGGL((gemm_i8_tile_kernel<MI, NI, NS, WGS>), dim3((unsigned)g.chunk * 8), dim3(kThreads),
-                     (kTileLds<MI, NI, NS, WGS>), st, g);
+  hipLaunchKernelGGL((gemm_i8_tile_kernel<MI, NI, NS, WGS, WARM>), dim3((unsigned)g.chunk * 8), dim3(kThreads),
+                     (kTileLds<MI, NI, NS>), st, g);
   return hipGetLastError();
 }
 
-#define OZ2_TILE_128 2, 2, 3, 3
-#define OZ2_TILE_64 1, 1, 4, 4
+#define OZ2_TILE_128 2, 2, 3, 3, true
+#define OZ2_TILE_128_MANY 2, 2, 3, 3, false
+#define OZ2_TILE_64 1, 1, 4, 4, true
 // few workgroups per compute unit, long inner dimensions (launch_tiles)
-#define OZ2_TILE_128_ONE 2, 2, 9, 1
-#define OZ2_TILE_64_ONE 1, 1, 16, 1
-#define OZ2_TILE_64_TWO 1, 1, 9, 2
+#define OZ2_TILE_128_ONE 2, 2, 9, 1, true
+#define OZ2_TILE_64_ONE 1, 1, 16, 1, true
+#define OZ2_TILE_64_TWO 1, 1, 9, 2, true
 constexpr int kDeepKtiles = 24;
 
 // tiles of a plane
@@ -235,6 +236,7 @@ int64_t tiles_of(int64_t tile, int64_t m, int64_t n, int triangle) {
 
 hipError_t oz2_gemm_tiles_setup() {
   hipError_t e = set_lds<OZ2_TILE_128>();
+  if (e == hipSuccess) e = set_lds<OZ2_TILE_128_MANY>();
   if (e == hipSuccess) e = set_lds<OZ2_TILE_64>();
   if (e == hipSuccess) e = set_lds<OZ2_TILE_64_ONE>();
   if (e == hipSuccess) e = set_lds<OZ2_TILE_64_TWO>();
@@ -270,7 +272,10 @@ static hipError_t launch_tiles(int tile, const Oz2Plan& plan, const Oz2Layout& l
     return launch<OZ2_TILE_64>(g, m, n, plan.N, flag, st);
   }
   if (deep && total <= cus) return launch<OZ2_TILE_128_ONE>(g, m, n, plan.N, flag, st);
-  return launch<OZ2_TILE_128>(g, m, n, plan.N, flag, st);
+  // With more than eight workgroups per compute unit the constants are fetched where they are needed: the registers of the fetch ahead
+  // cost more (whole calls, us, ahead / not: 17 moduli 13728 x 8516 x 167 1655 / 1635, 18 moduli 10028 x 12048 x 192 1821 / 1804; 10
+  // moduli 15610 x 64 x 64, five per compute unit, 31.5 / 32.0).
+  return total <= 8 * cus ? launch<OZ2_TILE_128>(g, m, n, plan.N, flag, st) : launch<OZ2_TILE_128_MANY>(g, m, n, plan.N, flag, st);
 }
 
 // Which kernel's tiles: 64 or 128 (this file) or 256 (oz2_stage2.hip).  64 x 64 when every tile gets a compute unit
