@@ -907,11 +907,17 @@ hipError_t launch_convert(const Operand* ops, int nops, const int* kind, bool la
 // 229 / 213, 240, 16 moduli 4096^3 1169 / 1159, 1157, dtrmm of order 4096 with 2048 columns 522 / 525, 496.  Up to 9920: 300 x 300 x 5000
 // with 16 64.2, 96.6, 500 x 500 x 8000 103, 139, 1000 x 1000 x 8000 208, 214, 2000 x 2000 x 8000 628, 607.  Elements split two levels
 // deep, 22 moduli: 700 x 3000 x 4000 341 / 347, 345, 4096 x 4096 x 2048 892 / 889 / 882, 886.
-static int short_vectors(int64_t vectors, int64_t k_pad, bool two_level, int64_t cus) {
+// Where most vectors are strided, and their elements many, the pieces of two or four vectors cost more than the second reading of whole
+// lines (one pass, separate launches): 18 moduli 14272 x 139 x 1797 345, 316, both strided 10560 x 576 x 2368 515, 488, 17 moduli
+// 352 x 4288 x 4224 311, 287, 16 moduli 1216 x 280 x 7424 181, 168; below the lines 12000 x 2000 x 1600 797, 802, 14 moduli both strided
+// 3000^3 478, 489, 16 moduli both strided 1216 x 280 x 5100 123, 138; half of them 14 moduli 8000 x 8000 x 2400 2227, 2263,
+// 1000 x 1000 x 8000 199, 204.
+static int short_vectors(int64_t vectors, int64_t strided, int64_t k_pad, bool two_level, int64_t cus) {
   const int64_t elements = vectors * k_pad;
   const auto fits = [&](int v) { return k_pad <= short_longest(v); };
   if (k_pad <= 1024) return vectors <= (k_pad <= 256 ? 4 : k_pad <= 512 ? 8 : 12) * cus ? 4 : 8;
   if (two_level && elements > (int64_t)3 << 22) return 0;
+  if (2 * strided > vectors && strided * k_pad > (int64_t)(fits(4) ? 19 : 9) << 20) return 0;
   if (fits(8)) return vectors <= 4 * cus ? 2 : 4;
   if (fits(4)) return elements > (int64_t)21 << 20 ? 0 : vectors <= 4 * cus || k_pad <= 3392 || two_level ? 2 : 4;
   return fits(2) && vectors <= 8 * cus ? 2 : 0;
@@ -932,11 +938,13 @@ static void shift_params(const Oz2Plan& plan, int shift_mode, int bit_split, int
   }
 }
 
-int oz2_one_pass_vectors(const Oz2Plan& plan, const Oz2Layout& lay, int symmetric, int shift_mode, int bit_split, int64_t cus) {
+int oz2_one_pass_vectors(const Oz2Plan& plan, const Oz2Layout& lay, int strided_a, int strided_b, int symmetric, int shift_mode, int bit_split,
+                         int64_t cus) {
   int param[2];
   shift_params(plan, shift_mode, bit_split, param);
   const int most = 75 - (shift_mode == OZ2_SHIFT_CAUCHY_SCHWARZ ? 1 : 0);
-  return short_vectors(lay.m_pad + (symmetric ? 0 : lay.n_pad), lay.k_pad, param[0] > most || param[1] > most, cus);
+  const int64_t second = symmetric ? 0 : lay.n_pad;
+  return short_vectors(lay.m_pad + second, (strided_a ? lay.m_pad : 0) + (strided_b ? second : 0), lay.k_pad, param[0] > most || param[1] > most, cus);
 }
 
 hipError_t oz2_launch_finish_scan(const Oz2ScanFinish& f, hipStream_t st) {
@@ -1006,7 +1014,7 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
   // Short vectors: everything in one launch (in the INT8-product mode: maxima and bound planes), whose reports the caller's
   // GEMM launch turns into the flag word (deferred != nullptr: the caller sees to that).
   const bool two_a = param[0] + base_mode > 75, two_b = param[1] + base_mode > 75;
-  const int short_vecs = deferred && !thin && !strassen ? oz2_one_pass_vectors(plan, lay, nops == 1, shift_mode, d, oz2_gemm_cus()) : 0;
+  const int short_vecs = deferred && !thin && !strassen ? oz2_one_pass_vectors(plan, lay, transa == 0, transb != 0, nops == 1, shift_mode, d, oz2_gemm_cus()) : 0;
   if (short_vecs) {
     ShortJob sj[2] = {};
     unsigned groups = 0;
