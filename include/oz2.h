@@ -328,7 +328,8 @@ int oz2_set_round_sync(int spins);
 /* Which kernels a call takes for a shape in the classical form, under the settings in force, on a device with that many
  * compute units: the rules that the launches follow, so that a test which aims at a kernel can tell that it gets there.
  * No GPU is touched.
- *   call: 0: oz2_dgemm; 1: oz2_dsyrk (m == n); 2: oz2_dtrmm (k the order of A); nothing transposed, A from the left
+ *   call: 0: oz2_dgemm; 1: oz2_dsyrk (m == n); 2: oz2_dtrmm (k the order of A); nothing transposed, A from the
+ *         left, its leading dimension m and its address a multiple of 128
  *   choice[0]: vectors that a workgroup of the one-pass conversion holds (2, 4 or 8), 0: separate launches
  *   choice[1]: 1 / 2: thin product whose first / second operand is the large one, 0: not
  *   choice[2]: edge of the tiles of the products (64, 128 or 256), 0 for a thin product

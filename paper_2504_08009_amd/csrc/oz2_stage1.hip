@@ -907,17 +907,18 @@ hipError_t launch_convert(const Operand* ops, int nops, const int* kind, bool la
 // 229 / 213, 240, 16 moduli 4096^3 1169 / 1159, 1157, dtrmm of order 4096 with 2048 columns 522 / 525, 496.  Up to 9920: 300 x 300 x 5000
 // with 16 64.2, 96.6, 500 x 500 x 8000 103, 139, 1000 x 1000 x 8000 208, 214, 2000 x 2000 x 8000 628, 607.  Elements split two levels
 // deep, 22 moduli: 700 x 3000 x 4000 341 / 347, 345, 4096 x 4096 x 2048 892 / 889 / 882, 886.
-// Where most vectors are strided, and their elements many, the pieces of two or four vectors cost more than the second reading of whole
-// lines (one pass, separate launches): 18 moduli 14272 x 139 x 1797 345, 316, both strided 10560 x 576 x 2368 515, 488, 17 moduli
-// 352 x 4288 x 4224 311, 287, 16 moduli 1216 x 280 x 7424 181, 168; below the lines 12000 x 2000 x 1600 797, 802, 14 moduli both strided
-// 3000^3 478, 489, 16 moduli both strided 1216 x 280 x 5100 123, 138; half of them 14 moduli 8000 x 8000 x 2400 2227, 2263,
-// 1000 x 1000 x 8000 199, 204.
-static int short_vectors(int64_t vectors, int64_t strided, int64_t k_pad, bool two_level, int64_t cus) {
+// in_lines: strided vectors of which the separate launches' sixteen are whole cache lines (lines_of_vectors).  Where they are most and their
+// elements many, pieces of two or four vectors cost more than the second reading (one pass, separate launches): 18 moduli
+// 14272 x 139 x 1797 339, 311, both strided 10560 x 576 x 2368 498, 473, 17 moduli 352 x 4288 x 4224 301, 281, 16 moduli
+// 1216 x 280 x 7424 177, 166; not in lines, 14273 vectors 347, 364, 14280 336, 354, 15 moduli both strided 3001 x 2777 x 3500 508, 536;
+// below the lines 12000 x 2000 x 1600 797, 802, 14 moduli 512 x 512 x 8000, both strided 96, 113; half of them 14 moduli
+// 8000 x 8000 x 2400 2227, 2263.  (Under the other shifts the separate launches take longer: 3001 x 2777 x 3500, INT8-product mode, 641, 655.)
+static int short_vectors(int64_t vectors, int64_t in_lines, int64_t k_pad, bool two_level, int64_t cus) {
   const int64_t elements = vectors * k_pad;
   const auto fits = [&](int v) { return k_pad <= short_longest(v); };
   if (k_pad <= 1024) return vectors <= (k_pad <= 256 ? 4 : k_pad <= 512 ? 8 : 12) * cus ? 4 : 8;
   if (two_level && elements > (int64_t)3 << 22) return 0;
-  if (2 * strided > vectors && strided * k_pad > (int64_t)(fits(4) ? 19 : 9) << 20) return 0;
+  if (2 * in_lines > vectors && in_lines * k_pad > (int64_t)(fits(4) ? 19 : 9) << 20) return 0;
   if (fits(8)) return vectors <= 4 * cus ? 2 : 4;
   if (fits(4)) return elements > (int64_t)21 << 20 ? 0 : vectors <= 4 * cus || k_pad <= 3392 || two_level ? 2 : 4;
   return fits(2) && vectors <= 8 * cus ? 2 : 0;
@@ -938,13 +939,19 @@ static void shift_params(const Oz2Plan& plan, int shift_mode, int bit_split, int
   }
 }
 
-int oz2_one_pass_vectors(const Oz2Plan& plan, const Oz2Layout& lay, int strided_a, int strided_b, int symmetric, int shift_mode, int bit_split,
+// Are sixteen neighbouring vectors of this operand whole cache lines?
+static bool lines_of_vectors(int strided, const double* X, int64_t ld) {
+  return strided && ld % 16 == 0 && reinterpret_cast<uintptr_t>(X) % 128 == 0;
+}
+
+int oz2_one_pass_vectors(const Oz2Plan& plan, const Oz2Layout& lay, int lines_a, int lines_b, int symmetric, int shift_mode, int bit_split,
                          int64_t cus) {
   int param[2];
   shift_params(plan, shift_mode, bit_split, param);
   const int most = 75 - (shift_mode == OZ2_SHIFT_CAUCHY_SCHWARZ ? 1 : 0);
   const int64_t second = symmetric ? 0 : lay.n_pad;
-  return short_vectors(lay.m_pad + second, (strided_a ? lay.m_pad : 0) + (strided_b ? second : 0), lay.k_pad, param[0] > most || param[1] > most, cus);
+  const int64_t in_lines = shift_mode != OZ2_SHIFT_MAX ? 0 : (lines_a ? lay.m_pad : 0) + (lines_b ? second : 0);
+  return short_vectors(lay.m_pad + second, in_lines, lay.k_pad, param[0] > most || param[1] > most, cus);
 }
 
 hipError_t oz2_launch_finish_scan(const Oz2ScanFinish& f, hipStream_t st) {
@@ -1014,7 +1021,10 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
   // Short vectors: everything in one launch (in the INT8-product mode: maxima and bound planes), whose reports the caller's
   // GEMM launch turns into the flag word (deferred != nullptr: the caller sees to that).
   const bool two_a = param[0] + base_mode > 75, two_b = param[1] + base_mode > 75;
-  const int short_vecs = deferred && !thin && !strassen ? oz2_one_pass_vectors(plan, lay, transa == 0, transb != 0, nops == 1, shift_mode, d, oz2_gemm_cus()) : 0;
+  const int short_vecs = deferred && !thin && !strassen
+                             ? oz2_one_pass_vectors(plan, lay, lines_of_vectors(ops[0].strided, A, lda), lines_of_vectors(ops[1].strided, B, ldb),
+                                                    nops == 1, shift_mode, d, oz2_gemm_cus())
+                             : 0;
   if (short_vecs) {
     ShortJob sj[2] = {};
     unsigned groups = 0;
@@ -1033,9 +1043,10 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
     // cost up to 6 % of a finite call, Cauchy-Schwarz mode 500^3 22.2 -> 23.5 us.)
     fin = {slots, base_mode == 1 ? (unsigned)vectors : groups, flag, lay.k_pad > 1024};
     const dim3 grid(8 * (sj[0].chunk + sj[1].chunk)), thr(kShortThreads);
-    // Up to three workgroups on two compute units wait for the constants (700^3 29.8 -> 29.2 us a call); where there are more, the first
-    // have fetched them for the others and the loads only cost (9 moduli 71 x 5081 x 184 22.5 -> 23.1, 900 x 700 x 300 22.7 -> 23.1).
-    const int warm = 2 * (int64_t)groups <= 3 * oz2_gemm_cus();
+    // Up to three workgroups on two compute units wait for the constants (700^3 29.8 -> 29.2 us a call), and those of vectors above 1024
+    // too (300 x 300 x 1500 29.1 -> 28.2, 2048 x 256 x 2000 59.3 -> 58.0); where more have short vectors, the first have fetched them for
+    // the others and the loads only cost (9 moduli 71 x 5081 x 184 22.5 -> 23.1, 900 x 700 x 300 22.7 -> 23.1).
+    const int warm = lay.k_pad > 1024 || 2 * (int64_t)groups <= 3 * oz2_gemm_cus();
     const size_t lds = (size_t)short_vecs * (lay.k_pad + 4) * sizeof(double);
 #define OZ2_SHORT_V(KA, KB, V) \
   hipLaunchKernelGGL((short_convert_kernel<KA, KB, V>), grid, thr, lds, st, sj[0], sj[1], conv, base_mode, warm, slots)

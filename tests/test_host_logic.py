@@ -439,8 +439,14 @@ def test_kernel_choice_at_the_limits_of_the_rules():
     for k, most in [(256, 1024), (512, 2048), (1024, 3072)]:
         assert choice(most - 256, 100, k, 9)[0] == 4 and choice(most, 100, k, 9)[0] == 8, k
     assert choice(85, 3412, 643, 15)[0] == 8 and choice(2000, 100, 4929, 4)[0] == 0
-    # many strided vectors, more than the others: 19 2^20 elements, above an inner dimension of 4928 9 2^20
+    # many strided vectors that are whole cache lines by sixteens, more than the others: 19 2^20 elements, above an inner dimension of 4928 9 2^20
     assert choice(11264, 300, 1728, 15)[0] == 4 and choice(11776, 300, 1728, 15)[0] == 0 and choice(11776, 11776, 1728, 15)[0] == 4
+    assert choice(11777, 300, 1728, 15)[0] == 4
+    try:
+        oz.oz2_set_shift_mode(oz.OZ2_SHIFT_INT8_PRODUCT)
+        assert choice(11776, 300, 1728, 15)[0] == 4
+    finally:
+        oz.oz2_set_shift_mode(oz.OZ2_SHIFT_MAX)
     assert choice(4352, 200, 4224, 17)[0] == 4 and choice(1024, 280, 7424, 16)[0] == 2 and choice(1280, 280, 7424, 16)[0] == 0
     assert choice(8192, 96, 8192, 16) == (0, 1, 0) and choice(96, 8192, 8192, 16) == (0, 2, 0)
     assert choice(8192, 129, 8192, 16)[1] == 0 and choice(8192, 96, 1024, 16)[1] == 0
