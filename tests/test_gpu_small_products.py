@@ -110,6 +110,29 @@ def test_one_pass_conversion_of_long_vectors(m, n, k, N, vectors, mode):
         oz.oz2_set_shift_mode(0)
 
 
+@pytest.mark.parametrize("lda,shift", [(1280, 0), (1281, 0), (1288, 0), (1296, 0), (1296, 1)])
+def test_many_strided_vectors_in_whole_lines_and_not(lda, shift):
+    """Rows of A that are whole cache lines by sixteens take the separate launches, others the one-pass conversion: leading dimensions that
+    are a multiple of 16 and not, and an array that starts inside a line."""
+    m, n, k, N = 1280, 140, 7424, 9
+    assert _choice(m, n, k, N) == (0, 0, 128)
+    rng = np.random.default_rng(lda + shift)
+    A, B = _mat(rng, m, k), _mat(rng, k, n)
+    print("lines: lda=%d shift=%d" % (lda, shift), flush=True)
+    buf = torch.full((k * lda + 16,), float("nan"), dtype=torch.float64, device="cuda")
+    assert buf.data_ptr() % 128 == 0
+    dA = buf[shift:shift + k * lda].view(k, lda)
+    dA[:, :m] = torch.from_numpy(np.ascontiguousarray(A.T)).cuda()
+    dB, dC = _dev(B), torch.zeros((n, m), dtype=torch.float64, device="cuda")
+    ws = oz.Workspace(m, n, k, N)
+    ws.buf.fill_(0x7f)
+    oz.oz2_dgemm(m, n, k, dA.data_ptr(), lda, dB.data_ptr(), k, dC.data_ptr(), m, N)
+    torch.cuda.synchronize()
+    rows = np.concatenate([np.arange(40), np.arange(m - 40, m)])
+    assert np.array_equal(dC.t()[rows].cpu().numpy(), orc.dgemm(A, B, N, rows=rows).C)
+    del ws
+
+
 @pytest.mark.parametrize("k,n", [(1100, 40), (2500, 30), (3500, 20)])
 @pytest.mark.parametrize("mode", [0, 1, 2])
 @pytest.mark.parametrize("side,uplo,ta", [("L", "L", "N"), ("L", "U", "T"), ("R", "U", "N"), ("R", "L", "T"), ("L", "U", "N")])
