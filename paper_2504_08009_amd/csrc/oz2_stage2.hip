@@ -14,8 +14,12 @@
 // 128 x 128 sub-tile = 8 x 8 MFMA tiles of 16 x 16 (256 accumulator registers).  The inner dimension is
 // walked in k-tiles of 64 bytes through a ring of four LDS stages (32 KiB each).  Both operands of a
 // k-tile are copied global -> LDS with 16-byte direct loads (no VGPR staging).  LDS rows are 64 bytes; the
-// 16-byte chunk index is XOR-swizzled with bits 2..3 of the row so that the 16 rows read together by a
-// ds_read_b128 fall on 16 different bank groups (measured: no bank conflicts).
+// 16-byte chunk index is XOR-swizzled with two bits of the row so that the 16 rows read together by a
+// ds_read_b128 fall on 16 different bank groups (measured: no bank conflicts): bits 2..3 for the columns of B', whose MFMA tiles
+// are sixteen neighbouring rows of the plane, bits 4..5 for A', whose tile x of a group of four is the rows 16 q + 4 x + (0..3),
+// q = 0..3, of 64.  A lane's words of four such tiles then are sixteen neighbouring rows of C', which it stores at once; with
+// neighbouring rows in a tile four exchanges between lanes per sixteen bytes did that (9 cycles each;
+// whole calls, us, 18 moduli 8192 x 8192 x 1024 1711 -> 1690, 16 moduli 4096^3 1044 -> 1041, dsyrk 5000 x 1024 344 -> 340).
 //
 // Which matrix instruction: under the card's power cap the products of 16 x 16 x 64 run at 4.0 POP/s on random operands with no
 // memory traffic, those of 32 x 32 x 32 at 3.5 (the larger tile moves twice the accumulator bytes per operation through the
@@ -338,7 +342,11 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
 
   // ---- global -> LDS copy: wave wv fills rows [64 wv, 64 wv + 64) of both tiles, 16 rows (1 KiB) per
   // load.  Lane l covers row (l >> 2) of the group and the chunk that the swizzle puts at position (l & 3).
+  constexpr bool kSpreadRows = RESIDUE_U8;  // A' tiles of spread rows: the UINT8 epilogue's stores want them
   const unsigned voff = (unsigned)((lane >> 2) * BK) + (((lane & 3) ^ (lane >> 4)) << 4);
+  unsigned voff_a[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) voff_a[q] = kSpreadRows ? (unsigned)((lane >> 2) * BK) + (((lane & 3) ^ q) << 4) : voff;
   const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)lds;
   const unsigned lds_wave = __builtin_amdgcn_readfirstlane(lds_base + wv * (64 * BK));
 
@@ -346,7 +354,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
   auto gl = [&](const int8_t* pa, const int8_t* pb, int stage, int q) {
     const unsigned sa = lds_wave + stage * kStageBytes;
     if (q < 4)
-      load_to_lds_16(pa + q * 1024, voff, sa + q * 1024);
+      load_to_lds_16(pa + q * 1024, voff_a[q & 3], sa + q * 1024);
     else
       load_to_lds_16(pb + (q - 4) * 1024, voff, sa + BM * BK + (q - 4) * 1024);
   };
@@ -365,9 +373,11 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
 
   // ---- LDS -> fragments: lane reads row (lane & 15) of a 16-row group, k-chunk lane / 16
   const int frag_off = (lane & 15) * BK + (((lane >> 4) ^ ((lane >> 2) & 3)) << 4);
-  const unsigned a_base = lds_base + wm * 128 * BK + frag_off, b_base = lds_base + BM * BK + wn * 128 * BK + frag_off;
+  // (A' of spread rows: row 16 ((lane & 15) / 4) + 4 (x % 4) + lane % 4 of the 64, the same position within it)
+  const int frag_off_a = kSpreadRows ? frag_off + (((lane & 12) << 2) + (lane & 3) - (lane & 15)) * BK : frag_off;
+  const unsigned a_base = lds_base + wm * 128 * BK + frag_off_a, b_base = lds_base + BM * BK + wn * 128 * BK + frag_off;
   typedef const __attribute__((address_space(3))) v4i* LdsFrag;
-  auto rd_a = [&](Frag& F, unsigned at, int x) { F.a[x] = *(LdsFrag)(at + x * 16 * BK); };
+  auto rd_a = [&](Frag& F, unsigned at, int x) { F.a[x] = *(LdsFrag)(at + (kSpreadRows ? (x & 4) * 16 + (x & 3) * 4 : x * 16) * BK); };
   auto rd_b = [&](Frag& F, unsigned at, int y) { F.b[y] = *(LdsFrag)(at + y * 16 * BK); };
 
   // Operand roles of v_mfma_i32_16x16x64_i8: the rows of the first operand run over the result registers
@@ -528,7 +538,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
       if constexpr (q == 60) rd_b(F, nb, 6);
       if constexpr (q == 34) set_lds_target(fill);
       if constexpr (q == 46) set_lds_target(fill + BM * BK);
-      if constexpr (q >= 36 && q <= 45 && q % 3 == 0) load_to_lds_target<(q - 36) / 3 * 1024>(fa, voff);
+      if constexpr (q >= 36 && q <= 45 && q % 3 == 0) load_to_lds_target<(q - 36) / 3 * 1024>(fa, voff_a[(q - 36) / 3]);
       if constexpr (q >= 48 && q <= 57 && q % 3 == 0) load_to_lds_target<(q - 48) / 3 * 1024>(fb, voff);
       if constexpr (q == 61) fa += fstep;
       if constexpr (q == 62) fb += fstep;
@@ -590,7 +600,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
   settle_acc();
   if (RESIDUE_U8) {
     // Algorithm 1 line 7 here: c'' = c' mod p in [0, p), four residues per 32-bit word.  Lane holds column
-    // j = lane % 16 of a 16 x 16 tile, its four registers four consecutive rows i.
+    // j = lane % 16 of an MFMA tile, its four registers four consecutive rows i, those of four tiles sixteen.
     // Bound by instruction issue, one wave per SIMD: 3.25 instructions of 5 cycles per element, and the 8-cycle move for
     // the half that sits in accumulation registers (before: seven, the move for all, and 2000 cycles to clear the
     // accumulators for the next tile).  With the stores left to drain and the tile decoding on the scalar unit the
@@ -611,20 +621,15 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
       v4i o[2];
       unrolled<2>([&](auto hc) {
         constexpr int x0 = 4 * decltype(hc)::value;
-        // w[x]: rows 16 (x0 + x) + 4 (lane / 16) + (0..3) of column lane % 16, one byte each; sixteen elements step by step: a
-        // byte dot product's result can only be read three instructions later
+        // w[x]: rows 16 (lane / 16) + 4 x + (0..3) of the 64 rows of four tiles, column lane % 16, one byte each; sixteen elements step
+        // by step: a byte dot product's result can only be read three instructions later
         unsigned v[16], w[4];
         unrolled<16>([&](auto e) { v[e] = Acc<8 * y + x0 + e / 4>::fold_sum(decltype(e)::value % 4, fv.kpack, fv.base); });
         settle_sums(v);
 #pragma unroll
         for (int x = 0; x < 4; ++x) w[x] = oz2_fold_residues4(v + 4 * x, fv);
-        // The four groups of sixteen lanes hold interleaved quarters of the same four tiles.  Transposed, group q holds the sixteen
-        // consecutive rows of tile x0 + q: one 16-byte store per lane, 64 bytes of a column side by side.
-        const auto s02 = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
-        const auto s13 = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
-        const auto lo = __builtin_amdgcn_permlane16_swap(s02[0], s13[0], false, false);
-        const auto hi = __builtin_amdgcn_permlane16_swap(s02[1], s13[1], false, false);
-        o[decltype(hc)::value] = v4i{(int)lo[0], (int)lo[1], (int)hi[0], (int)hi[1]};
+        // sixteen consecutive rows: one 16-byte store per lane, 64 bytes of a column side by side
+        o[decltype(hc)::value] = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
         __builtin_amdgcn_sched_barrier(0);
       });
       // both halves of a column together, so that its cache lines are complete at once
