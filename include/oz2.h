@@ -361,6 +361,9 @@ int oz2_host_residues(int num_moduli, int kappa, double a, int shift, int8_t* re
  * (|product| <= 61440 * 2^14).  No GPU is touched.  Returns 0 or a negative argument code. */
 int oz2_host_product_residues(int index, int64_t count, const int32_t* products, uint8_t* res_out);
 
+/* The same as the large tiles take it for inner dimensions up to 1024 (|product| <= 2^24). */
+int oz2_host_short_product_residues(int index, int64_t count, const int32_t* products, uint8_t* res_out);
+
 const char* oz2_status_string(int status);
 
 #ifdef __cplusplus

@@ -12,7 +12,7 @@ SYMBOLS = [
     "oz2_set_gemm_algorithm", "oz2_gemm_algorithm_for", "oz2_workspace_bytes_strassen", "oz2_workspace_bytes_preferred",
     "oz2_context_create", "oz2_context_destroy", "oz2_context_set_workspace", "oz2_context_set", "oz2_context_get",
     "oz2_context_workspace_bytes", "oz2_context_dgemm", "oz2_context_dsyrk", "oz2_context_dtrmm",
-    "oz2_set_kblock", "oz2_set_round_sync", "oz2_set_shift_mode", "oz2_set_product_format", "oz2_set_bit_split", "oz2_set_nonfinite_check", "oz2_set_stage_events", "oz2_calibrate_mfma", "oz2_host_kernel_choice", "oz2_host_crt_element", "oz2_host_crt_element_digits", "oz2_host_residues", "oz2_host_product_residues", "oz2_status_string",
+    "oz2_set_kblock", "oz2_set_round_sync", "oz2_set_shift_mode", "oz2_set_product_format", "oz2_set_bit_split", "oz2_set_nonfinite_check", "oz2_set_stage_events", "oz2_calibrate_mfma", "oz2_host_kernel_choice", "oz2_host_crt_element", "oz2_host_crt_element_digits", "oz2_host_residues", "oz2_host_product_residues", "oz2_host_short_product_residues", "oz2_status_string",
 ]
 
 
@@ -77,6 +77,7 @@ def lib():
         L.oz2_host_kernel_choice.argtypes = [ci, i64, i64, i64, ci, ci, vp]
         L.oz2_host_residues.argtypes = [ci, ci, ctypes.c_double, ci, vp]
         L.oz2_host_product_residues.argtypes = [ci, i64, vp, vp]
+        L.oz2_host_short_product_residues.argtypes = [ci, i64, vp, vp]
         L.oz2_status_string.restype = ctypes.c_char_p
         L.oz2_status_string.argtypes = [ci]
         _lib = L
@@ -292,13 +293,13 @@ def host_residues(num_moduli, kappa, a, shift):
     return list(out)
 
 
-def host_product_residues(index, products):
-    """products: contiguous int32 numpy array -> uint8 array of the same shape"""
+def host_product_residues(index, products, short=False):
+    """products: contiguous int32 numpy array -> uint8 array of the same shape; short: as for inner dimensions up to 1024"""
     import numpy as np
     assert products.dtype == np.int32 and products.flags.c_contiguous
     out = np.empty(products.shape, dtype=np.uint8)
-    _check(lib().oz2_host_product_residues(index, products.size, products.ctypes.data, out.ctypes.data),
-           "oz2_host_product_residues")
+    name = "oz2_host_short_product_residues" if short else "oz2_host_product_residues"
+    _check(getattr(lib(), name)(index, products.size, products.ctypes.data, out.ctypes.data), name)
     return out
 
 

@@ -769,7 +769,8 @@ int oz2_host_residues(int num_moduli, int kappa, double a, int shift, int8_t* re
   return oz2_host_residues_impl(plan.conv, a, shift, res_out) ? OZ2_OK : -6;
 }
 
-int oz2_host_product_residues(int index, int64_t count, const int32_t* products, uint8_t* res_out) {
+typedef void (*Oz2HostResidues)(int p, int64_t count, const int32_t* products, uint8_t* out);
+static int host_product_residues(int index, int64_t count, const int32_t* products, uint8_t* res_out, Oz2HostResidues impl) {
   if (index < 0 || index >= OZ2_MAX_N) return -1;
   if (count < 0) return -2;
   if (count == 0) return OZ2_OK;
@@ -777,8 +778,16 @@ int oz2_host_product_residues(int index, int64_t count, const int32_t* products,
   if (!res_out) return -4;
   int moduli[OZ2_MAX_N];
   oz2_table_moduli(OZ2_MAX_N, moduli);
-  oz2_host_product_residues_impl(moduli[index], count, products, res_out);
+  impl(moduli[index], count, products, res_out);
   return OZ2_OK;
+}
+
+int oz2_host_product_residues(int index, int64_t count, const int32_t* products, uint8_t* res_out) {
+  return host_product_residues(index, count, products, res_out, oz2_host_product_residues_impl);
+}
+
+int oz2_host_short_product_residues(int index, int64_t count, const int32_t* products, uint8_t* res_out) {
+  return host_product_residues(index, count, products, res_out, oz2_host_short_product_residues_impl);
 }
 
 const char* oz2_status_string(int status) {

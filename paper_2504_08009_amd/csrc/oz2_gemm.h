@@ -111,7 +111,26 @@ inline Oz2FoldConsts oz2_fold_consts(int p) {
   }
   c.base = 0x4b000000u + e + start;
   c.offset = (float)((1u << 23) - above - 1u + j);
+  c.recip = (unsigned)((((uint64_t)1 << 32) + u / 2u) / u);
+  c.half = (1u << 31) / u - OZ2_ACC_START * c.recip;
   return c;
+}
+
+// Sums of at most OZ2_SHORT_SUM terms: |c'| <= 2^24.  With M = 2^32 / p + e, |e| <= 1/2, the low word of c' M + 2^31 / p is 2^32 times the
+// fraction of c' / p + 1 / (2 p) + c' e / 2^32, and p times that fraction is the residue plus one half, moved by less than
+// 2^24 p / 2^33 <= 1/2 (p = 256 has e = 0, 255 below it 255/512) and p / 2^32 for the rounding of the half: the upper word of a product
+// with p is the residue.  Two instructions in the place of three, nine cycles of them for the 16-bit multiply-add on a lone wave, and none
+// of them a dot product, which waits for the matrix core.
+#define OZ2_SHORT_SUM 1024
+inline uint8_t oz2_host_short_residue(int32_t product, const Oz2FoldConsts& c) {
+  const unsigned low = ((unsigned)product + OZ2_ACC_START) * c.recip + c.half;
+  return (uint8_t)(((uint64_t)low * (unsigned)c.p) >> 32);
+}
+// Four low words -> four residues, one per byte.
+__device__ __forceinline__ unsigned oz2_short_residues4(const unsigned* low, unsigned p) {
+  const unsigned a = __builtin_amdgcn_perm(__umulhi(low[1], p), __umulhi(low[0], p), 0x0c0c0400u);
+  const unsigned b = __builtin_amdgcn_perm(__umulhi(low[3], p), __umulhi(low[2], p), 0x04000c0cu);
+  return a | b;
 }
 
 // The same for one value on the host, step by step (the 16-bit multiply-add of the device keeps the same low byte).
@@ -147,6 +166,9 @@ __device__ __forceinline__ Oz2FoldConsts in_vector_registers(const Oz2FoldConsts
   v.kpack = to_vector(c.kpack);
   v.base = to_vector(c.base);
   v.neg_p = to_vector(c.neg_p);
+  v.recip = to_vector(c.recip);
+  v.half = to_vector(c.half);
+  v.p = (int)to_vector((unsigned)c.p);
   v.inv_p = __uint_as_float(to_vector(__float_as_uint(c.inv_p)));
   v.offset = __uint_as_float(to_vector(__float_as_uint(c.offset)));
   return v;

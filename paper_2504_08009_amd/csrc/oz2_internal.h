@@ -68,6 +68,8 @@ struct Oz2FoldConsts {
   unsigned base;     // bits of the float 2^23, plus what the byte sums start from
   float offset;
   unsigned neg_p;    // 2^16 - p
+  unsigned recip;    // nearest integer to 2^32 / p
+  unsigned half;     // 2^31 / p, less OZ2_ACC_START times recip modulo 2^32
 };
 
 struct Oz2Plan {
@@ -210,6 +212,7 @@ hipError_t oz2_static_scratch(char** ptr, size_t* bytes);
 // Host instantiations of the device math (oz2_stage1.hip / oz2_stage3.hip), for unit tests.
 bool oz2_host_residues_impl(const Oz2ConvConsts& c, double a, int shift, int8_t* out);
 void oz2_host_product_residues_impl(int p, int64_t count, const int32_t* products, uint8_t* out);
+void oz2_host_short_product_residues_impl(int p, int64_t count, const int32_t* products, uint8_t* out);
 double oz2_host_crt_impl(const Oz2CrtConsts& c, const int32_t* cprod);
 // the same element by the digit route of the matrix-core CRT kernel (res: num_moduli residues in [0, p_t))
 double oz2_host_crt_digits_impl(const Oz2CrtConsts& c, const Oz2CrtDigits& d, const uint8_t* res);

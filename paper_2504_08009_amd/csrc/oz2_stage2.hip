@@ -174,6 +174,19 @@ struct Acc {
       asm volatile("v_accvgpr_read_b32 %0, a[%3+%4]\n\tv_dot4_u32_u8 %0, %0, %1, %2" : "=&v"(v) : "v"(kpack), "v"(base), "n"(kReg), "n"(e));
     return v;
   }
+  /* the low word of (acc) (recip) + half */
+  static __device__ __forceinline__ unsigned low_word(int e, unsigned recip, unsigned long long half) {
+    unsigned long long w;
+    if constexpr (kV) {
+      asm volatile("v_mad_u64_u32 %0, vcc, v[%3+%4], %1, %2" : "=v"(w) : "v"(recip), "v"(half), "n"(kReg), "n"(e) : "vcc");
+    } else {
+      // (one statement: the compiler puts an s_nop between two)
+      unsigned v;
+      asm volatile("v_accvgpr_read_b32 %1, a[%4+%5]\n\tv_mad_u64_u32 %0, vcc, %1, %2, %3"
+                   : "=&v"(w), "=&v"(v) : "v"(recip), "v"(half), "n"(kReg), "n"(e) : "vcc");
+    }
+    return (unsigned)w;
+  }
 };
 #define OZ2_TEN(R, N) R #N "0", R #N "1", R #N "2", R #N "3", R #N "4", R #N "5", R #N "6", R #N "7", R #N "8", R #N "9"
 __device__ __forceinline__ void named_accumulators() {
@@ -316,7 +329,8 @@ __device__ __forceinline__ Tile decode_tile(const GemmArgs& g, int slot, int wv)
 // accumulators between them (inner dimensions beyond the INT32 exactness bound, or a smaller block on request).
 // A kernel of its own: the reduction's 256 x 8 instructions need so many registers at once that the compiler parks
 // 48 accumulators in scratch memory around it, on the path of every tile, and the instantiation without it does not.
-template <bool RESIDUE_U8, bool LIST_ORDER, bool EARLY_ARRIVAL, bool KBLOCKED>
+// SHORT: the inner dimension is at most OZ2_SHORT_SUM.
+template <bool RESIDUE_U8, bool LIST_ORDER, bool EARLY_ARRIVAL, bool KBLOCKED, bool SHORT = false>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))) gemm_i8_kernel(const GemmArgs g) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
 
@@ -624,10 +638,16 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
         // w[x]: rows 16 (lane / 16) + 4 x + (0..3) of the 64 rows of four tiles, column lane % 16, one byte each; sixteen elements step
         // by step: a byte dot product's result can only be read three instructions later
         unsigned v[16], w[4];
-        unrolled<16>([&](auto e) { v[e] = Acc<8 * y + x0 + e / 4>::fold_sum(decltype(e)::value % 4, fv.kpack, fv.base); });
-        settle_sums(v);
+        if constexpr (SHORT) {
+          unrolled<16>([&](auto e) { v[e] = Acc<8 * y + x0 + e / 4>::low_word(decltype(e)::value % 4, fv.recip, fv.half); });
 #pragma unroll
-        for (int x = 0; x < 4; ++x) w[x] = oz2_fold_residues4(v + 4 * x, fv);
+          for (int x = 0; x < 4; ++x) w[x] = oz2_short_residues4(v + 4 * x, (unsigned)fv.p);
+        } else {
+          unrolled<16>([&](auto e) { v[e] = Acc<8 * y + x0 + e / 4>::fold_sum(decltype(e)::value % 4, fv.kpack, fv.base); });
+          settle_sums(v);
+#pragma unroll
+          for (int x = 0; x < 4; ++x) w[x] = oz2_fold_residues4(v + 4 * x, fv);
+        }
         // sixteen consecutive rows: one 16-byte store per lane, 64 bytes of a column side by side
         o[decltype(hc)::value] = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
         __builtin_amdgcn_sched_barrier(0);
@@ -682,11 +702,13 @@ hipError_t gemm_setup() {
 #define OZ2_BOTH(U8, LIST, EARLY)                                              \
   reinterpret_cast<const void*>(gemm_i8_kernel<U8, LIST, EARLY, false>),       \
       reinterpret_cast<const void*>(gemm_i8_kernel<U8, LIST, EARLY, true>)
-  const void* kernels[12] = {OZ2_BOTH(false, false, false), OZ2_BOTH(true, false, false), OZ2_BOTH(false, true, false),
+  const void* kernels[14] = {reinterpret_cast<const void*>(gemm_i8_kernel<true, false, false, false, true>),
+                             reinterpret_cast<const void*>(gemm_i8_kernel<true, true, false, false, true>),
+                             OZ2_BOTH(false, false, false), OZ2_BOTH(true, false, false), OZ2_BOTH(false, true, false),
                              OZ2_BOTH(true, true, false),   OZ2_BOTH(true, false, true),  OZ2_BOTH(true, true, true)};
 #undef OZ2_BOTH
   hipError_t e = hipSuccess;
-  for (int i = 0; i < 12 && e == hipSuccess; ++i)
+  for (int i = 0; i < 14 && e == hipSuccess; ++i)
     e = hipFuncSetAttribute(kernels[i], hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
   if (e != hipSuccess) return e;
   int dev = 0, n = 0;
@@ -820,7 +842,12 @@ hipError_t launch_gemm(const Oz2Layout& lay, char* ws, int num_moduli, const int
     else                                                                                            \
       hipLaunchKernelGGL((gemm_i8_kernel<U8, LIST, EARLY, false>), grd, thr, kLdsBytes, st, g);     \
   } while (0)
-  if (!residue_u8 && list_order)
+  const bool short_sums = residue_u8 && !kblocked && lay.k_pad <= OZ2_SHORT_SUM;  // (no round synchronisation: at most 16 k-tiles)
+  if (short_sums && list_order)
+    hipLaunchKernelGGL((gemm_i8_kernel<true, true, false, false, true>), grd, thr, kLdsBytes, st, g);
+  else if (short_sums)
+    hipLaunchKernelGGL((gemm_i8_kernel<true, false, false, false, true>), grd, thr, kLdsBytes, st, g);
+  else if (!residue_u8 && list_order)
     OZ2_GEMM(false, true, false);
   else if (!residue_u8)
     OZ2_GEMM(false, false, false);

@@ -319,3 +319,7 @@ void oz2_host_product_residues_impl(int p, int64_t count, const int32_t* product
   const Oz2FoldConsts c = oz2_fold_consts(p);
   for (int64_t i = 0; i < count; ++i) out[i] = oz2_host_fold_residue(products[i], c);
 }
+void oz2_host_short_product_residues_impl(int p, int64_t count, const int32_t* products, uint8_t* out) {
+  const Oz2FoldConsts c = oz2_fold_consts(p);
+  for (int64_t i = 0; i < count; ++i) out[i] = oz2_host_short_residue(products[i], c);
+}

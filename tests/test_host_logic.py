@@ -269,6 +269,22 @@ def test_host_product_residues_over_all_legal_sums(index):
     assert wrong.size == 0, (p, wrong.size, wrong[:5])
 
 
+@pytest.mark.parametrize("index", range(26))
+def test_host_short_product_residues(index):
+    """Sums of up to 1024 products of two INT8 values, |sum| <= 2^24, one form of which multiplies by 2^32 / p rounded: its error
+    grows with the sum, so both ends are taken whole, and what lies between at random."""
+    p = orc.moduli(26)[index]
+    limit = 1024 * 2**14
+    rng = np.random.default_rng(index)
+    near = np.arange(-70000, 70001)
+    c = np.concatenate([near, limit - 140000 + near + 70000, -limit + 140000 + near - 70000, rng.integers(-limit, limit + 1, 1 << 20)])
+    c = np.ascontiguousarray(c[np.abs(c) <= limit].astype(np.int32))
+    assert c.max() == limit and c.min() == -limit
+    got = oz.host_product_residues(index, c, short=True)
+    wrong = c[got != c.astype(np.int64) % p]
+    assert wrong.size == 0, (p, wrong.size, wrong[:5])
+
+
 # ----------------------------------------------------------------------------------------------
 # Algorithm 1 lines 7-11 on one element: residues of INT32 products -> double nearest to X
 # ----------------------------------------------------------------------------------------------
