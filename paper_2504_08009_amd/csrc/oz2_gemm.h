@@ -148,10 +148,11 @@ __device__ __forceinline__ unsigned oz2_fold_residues4(const unsigned* x, const 
   unsigned t[4], lo, hi;
 #pragma unroll
   for (int i = 0; i < 4; ++i) t[i] = __float_as_uint(fmaf(__uint_as_float(x[i]), c.inv_p, c.offset));
-  asm("v_mad_u16 %0, %1, %2, %3" : "=v"(lo) : "v"(t[0]), "v"(c.neg_p), "v"(x[0]));
-  asm("v_mad_u16 %0, %1, %2, %3" : "=v"(hi) : "v"(t[2]), "v"(c.neg_p), "v"(x[2]));
-  asm("v_mad_u16 %0, %1, %2, %3 op_sel:[0,0,0,1]" : "+v"(lo) : "v"(t[1]), "v"(c.neg_p), "v"(x[1]));
-  asm("v_mad_u16 %0, %1, %2, %3 op_sel:[0,0,0,1]" : "+v"(hi) : "v"(t[3]), "v"(c.neg_p), "v"(x[3]));
+  // (one statement: the compiler puts an s_nop between dependent ones; the last result can be read two instructions later, which it sees to)
+  asm("v_mad_u16 %0, %2, %6, %7\n\tv_mad_u16 %1, %4, %6, %9\n\t"
+      "v_mad_u16 %0, %3, %6, %8 op_sel:[0,0,0,1]\n\tv_mad_u16 %1, %5, %6, %10 op_sel:[0,0,0,1]"
+      : "=&v"(lo), "=&v"(hi)
+      : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(c.neg_p), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]));
   return __builtin_amdgcn_perm(hi, lo, 0x06040200u);
 }
 

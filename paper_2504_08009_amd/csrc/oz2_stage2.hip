@@ -102,6 +102,7 @@ struct GemmArgs {
   int fin_stops;                        // 1: every workgroup looks at the reports and stops when there is one
   unsigned long long* xcd_sync;         // one counter per XCD (zero at launch), or null: no round sync
   int full_rounds;                      // rounds in which every workgroup slot has a tile
+  int pass_by;                          // 1: residues are stored past the L2 (see the launcher)
   int sync_spins;                       // bound of one wait of the round synchronisation, in polls of the counter
   FastDiv per_modulus;                  // planes per modulus: plane u is reduced modulo number u / per_modulus
   FastDiv div_plane;                    // tiles, sub-blocks or super-blocks of a plane
@@ -174,18 +175,29 @@ struct Acc {
       asm volatile("v_accvgpr_read_b32 %0, a[%3+%4]\n\tv_dot4_u32_u8 %0, %0, %1, %2" : "=&v"(v) : "v"(kpack), "v"(base), "n"(kReg), "n"(e));
     return v;
   }
-  /* the low word of (acc) (recip) + half */
-  static __device__ __forceinline__ unsigned low_word(int e, unsigned recip, unsigned long long half) {
-    unsigned long long w;
+  /* the low words of (acc) (recip) + half, in one statement: the compiler puts an s_nop between several */
+  static __device__ __forceinline__ void low_words(unsigned* low, unsigned recip, unsigned long long half) {
+    unsigned long long w[4];
     if constexpr (kV) {
-      asm volatile("v_mad_u64_u32 %0, vcc, v[%3+%4], %1, %2" : "=v"(w) : "v"(recip), "v"(half), "n"(kReg), "n"(e) : "vcc");
+      asm volatile(
+          "v_mad_u64_u32 %0, vcc, v[%6+0], %4, %5\n\tv_mad_u64_u32 %1, vcc, v[%6+1], %4, %5\n\t"
+          "v_mad_u64_u32 %2, vcc, v[%6+2], %4, %5\n\tv_mad_u64_u32 %3, vcc, v[%6+3], %4, %5"
+          : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3])
+          : "v"(recip), "v"(half), "n"(kReg)
+          : "vcc");
     } else {
-      // (one statement: the compiler puts an s_nop between two)
-      unsigned v;
-      asm volatile("v_accvgpr_read_b32 %1, a[%4+%5]\n\tv_mad_u64_u32 %0, vcc, %1, %2, %3"
-                   : "=&v"(w), "=&v"(v) : "v"(recip), "v"(half), "n"(kReg), "n"(e) : "vcc");
+      unsigned t[4];
+      asm volatile(
+          "v_accvgpr_read_b32 %4, a[%10+0]\n\tv_accvgpr_read_b32 %5, a[%10+1]\n\t"
+          "v_accvgpr_read_b32 %6, a[%10+2]\n\tv_accvgpr_read_b32 %7, a[%10+3]\n\t"
+          "v_mad_u64_u32 %0, vcc, %4, %8, %9\n\tv_mad_u64_u32 %1, vcc, %5, %8, %9\n\t"
+          "v_mad_u64_u32 %2, vcc, %6, %8, %9\n\tv_mad_u64_u32 %3, vcc, %7, %8, %9"
+          : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]), "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3])
+          : "v"(recip), "v"(half), "n"(kReg)
+          : "vcc");
     }
-    return (unsigned)w;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) low[e] = (unsigned)w[e];
   }
 };
 #define OZ2_TEN(R, N) R #N "0", R #N "1", R #N "2", R #N "3", R #N "4", R #N "5", R #N "6", R #N "7", R #N "8", R #N "9"
@@ -425,6 +437,9 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
   bool first = true;
   int round = 0;
   unsigned soff = 0;  // first byte of the stage that holds k-tile 0 of the current tile
+  // One set of fragments: each is read again for the next k-tile after its last product and, two hundred cycles or more, before its
+  // first one there.  Rows 4-7 and the last column of a k-tile arrive during its own first half.
+  Frag F;
   const int xcd = blockIdx.x % kXcds;
   for (;;) {
   const int ktiles = cur.ktiles;
@@ -477,11 +492,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
   ++round;
   const int store_window = first ? 0 : NS - 2;
   first = false;
-  __syncthreads();
-  // One set of fragments: each is read again for the next k-tile after its last product and, two hundred cycles or more, before its
-  // first one there.  Rows 4-7 and the last column of a k-tile arrive during its own first half.
-  Frag F;
   unsigned ra = a_base + soff, rb = b_base + soff;  // where this lane's fragments of the current k-tile start
+  __syncthreads();
 #pragma unroll
   for (int x = 0; x < 4; ++x) rd_a(F, ra, x);
 #pragma unroll
@@ -612,6 +624,25 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
 
   // ---- epilogue
   settle_acc();
+  // Sixteen residues of column y of MFMA tiles, those of tiles 4 h .. 4 h + 3: rows 16 (lane / 16) + (0..15) of 64, column lane % 16, one
+  // byte each.
+  auto residues = [&](auto yc, auto hc) {
+    constexpr int T = 8 * decltype(yc)::value + 4 * decltype(hc)::value;
+    unsigned v[16], w[4];
+    if constexpr (SHORT) {
+      unrolled<4>([&](auto xc) { Acc<T + decltype(xc)::value>::low_words(v + 4 * decltype(xc)::value, fv.recip, fv.half); });
+#pragma unroll
+      for (int x = 0; x < 4; ++x) w[x] = oz2_short_residues4(v + 4 * x, (unsigned)fv.p);
+    } else {
+      // (step by step: a byte dot product's result can only be read three instructions later)
+      unrolled<16>([&](auto e) { v[e] = Acc<T + e / 4>::fold_sum(decltype(e)::value % 4, fv.kpack, fv.base); });
+      settle_sums(v);
+#pragma unroll
+      for (int x = 0; x < 4; ++x) w[x] = oz2_fold_residues4(v + 4 * x, fv);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    return v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
+  };
   if (RESIDUE_U8) {
     // Algorithm 1 line 7 here: c'' = c' mod p in [0, p), four residues per 32-bit word.  Lane holds column
     // j = lane % 16 of an MFMA tile, its four registers four consecutive rows i, those of four tiles sixteen.
@@ -632,30 +663,17 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
     const unsigned lane_off = (lane_now & 15u) * (unsigned)g.m_pad + 16u * (lane_now >> 4);
     unrolled<8>([&](auto yc) {
       constexpr int y = decltype(yc)::value;
-      v4i o[2];
-      unrolled<2>([&](auto hc) {
-        constexpr int x0 = 4 * decltype(hc)::value;
-        // w[x]: rows 16 (lane / 16) + 4 x + (0..3) of the 64 rows of four tiles, column lane % 16, one byte each; sixteen elements step
-        // by step: a byte dot product's result can only be read three instructions later
-        unsigned v[16], w[4];
-        if constexpr (SHORT) {
-          unrolled<16>([&](auto e) { v[e] = Acc<8 * y + x0 + e / 4>::low_word(decltype(e)::value % 4, fv.recip, fv.half); });
-#pragma unroll
-          for (int x = 0; x < 4; ++x) w[x] = oz2_short_residues4(v + 4 * x, (unsigned)fv.p);
-        } else {
-          unrolled<16>([&](auto e) { v[e] = Acc<8 * y + x0 + e / 4>::fold_sum(decltype(e)::value % 4, fv.kpack, fv.base); });
-          settle_sums(v);
-#pragma unroll
-          for (int x = 0; x < 4; ++x) w[x] = oz2_fold_residues4(v + 4 * x, fv);
-        }
-        // sixteen consecutive rows: one 16-byte store per lane, 64 bytes of a column side by side
-        o[decltype(hc)::value] = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-        __builtin_amdgcn_sched_barrier(0);
-      });
+      const v4i lo = residues(yc, std::integral_constant<int, 0>()), hi = residues(yc, std::integral_constant<int, 1>());
       // both halves of a column together, so that its cache lines are complete at once
       uint8_t* cj = corner + (size_t)(y * 16) * g.m_pad;  // uniform; + 64 h + lane_off below
-      *reinterpret_cast<v4i*>(cj + lane_off) = o[0];
-      *reinterpret_cast<v4i*>(cj + 64 + lane_off) = o[1];
+      v4i* const to = reinterpret_cast<v4i*>(cj + lane_off);
+      if (SHORT || g.pass_by) {
+        __builtin_nontemporal_store(lo, to);  // (SHORT: always, see the launcher)
+        __builtin_nontemporal_store(hi, to + 4);
+      } else {
+        to[0] = lo;
+        to[4] = hi;
+      }
       __builtin_amdgcn_sched_barrier(0);
     });
   } else {
@@ -782,6 +800,13 @@ hipError_t launch_gemm(const Oz2Layout& lay, char* ws, int num_moduli, const int
   // every workgroup walks the work indices of its slot in launch order.  Structured products have tiles of
   // unequal length (or none): there the hardware's dynamic placement of one workgroup per index balances better.
   unsigned grid = (unsigned)(g.chunk * 8);
+  // Residues stored past the L2 (evicted first): where the panels of a round of tiles are of the L2's size, the lines of C' push them out
+  // and the copies into LDS wait (cycles per k-tile at 8192 x 8192 x 1024 1510 -> 1240, inside the kernel), and planes beyond the last-level
+  // cache are not found there by stage 3 anyway; between the two they are better left in the caches.  Whole calls, us, through / past: 12
+  // moduli 8000 x 4000 x 300 381 / 337, 16 moduli 4000 x 4000 x 600 316 / 292, 18 moduli 8192 x 8192 x 1024 1629 / 1572, 14 moduli 2048^3
+  // 176.9 / 172.5, 16 moduli 8192 x 8192 x 2048 2210 / 2169, 12288 x 12288 x 4096 8325 / 8252; 4000 x 4000 x 2400 611 / 613, 6000 x 6000 x
+  // 3000 1692 / 1698, 5000 x 5000 x 4096 with 12 1275 / 1270, 2048 x 2048 x 8192 616 / 622.
+  g.pass_by = g.ktiles <= 32 || total * (BM * BN) > (int64_t)1 << 29;
   g.xcd_sync = nullptr;
   g.full_rounds = 0;
   g.sync_spins = g_sync_spins;
