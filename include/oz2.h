@@ -349,6 +349,9 @@ int oz2_host_crt_element(int num_moduli, const int32_t* cprod, double* x_out);
  * [0, p_t).  num_moduli <= 16.  Returns 0 or a negative argument code. */
 int oz2_host_crt_element_digits(int num_moduli, const uint8_t* residues, double* x_out);
 
+/* The same for 17 to 20 moduli (twenty digits). */
+int oz2_host_crt_element_wide_digits(int num_moduli, const uint8_t* residues, double* x_out);
+
 /* Host-side evaluation of the device routine for lines 2-5 on one element: residues of
  * trunc(a * 2^shift) for all moduli (int8, num_moduli entries).  kappa tells the routine which of its
  * two splitting depths to use, as the kernels do.  Returns 0, a negative argument code, or -6 when the forms in which the

@@ -747,8 +747,8 @@ int oz2_host_crt_element(int num_moduli, const int32_t* cprod, double* x_out) {
   return OZ2_OK;
 }
 
-int oz2_host_crt_element_digits(int num_moduli, const uint8_t* residues, double* x_out) {
-  if (!n_ok(num_moduli) || num_moduli > 16) return -1;
+static int host_crt_element_digits(int num_moduli, int fewest, int most, const uint8_t* residues, double* x_out) {
+  if (!n_ok(num_moduli) || num_moduli < fewest || num_moduli > most) return -1;
   if (!residues) return -2;
   if (!x_out) return -3;
   Oz2Plan plan;
@@ -757,6 +757,14 @@ int oz2_host_crt_element_digits(int num_moduli, const uint8_t* residues, double*
     if (residues[t] >= plan.moduli[t]) return -2;
   *x_out = oz2_host_crt_digits_impl(plan.crt, plan.digits, residues);
   return OZ2_OK;
+}
+
+int oz2_host_crt_element_digits(int num_moduli, const uint8_t* residues, double* x_out) {
+  return host_crt_element_digits(num_moduli, OZ2_MIN_N, 16, residues, x_out);
+}
+
+int oz2_host_crt_element_wide_digits(int num_moduli, const uint8_t* residues, double* x_out) {
+  return host_crt_element_digits(num_moduli, 17, OZ2_MFMA_N, residues, x_out);
 }
 
 int oz2_host_residues(int num_moduli, int kappa, double a, int shift, int8_t* res_out) {

@@ -47,16 +47,16 @@ struct Oz2CrtConsts {
   double rinv[OZ2_MAX_L];              // RN(2^(40 l) / M)
 };
 
-// Constants of the matrix-core form of lines 8-9 (at most 16 moduli, M < 2^128): the weights in the symmetric range,
-// Ws_t = W_t or W_t - M with |Ws_t| <= M/2, as sixteen balanced base-256 digits each,
+// Constants of the matrix-core form of lines 8-9 (at most OZ2_MFMA_N moduli, M < 2^160): the weights in the symmetric range,
+// Ws_t = W_t or W_t - M with |Ws_t| <= M/2, as balanced base-256 digits,
 //   Ws_t = sum_i dig[i][t] 256^i,  dig in [-128, 127],
-// so that one INT8 MFMA forms sum_t (c''_t - 128) dig[i][t] for all sixteen digits of 64 output elements at once;
-// init[i] = 128 sum_t dig[i][t] makes up for the 128: sum_t c''_t dig[i][t] = (MFMA result) + init[i].
+// so that INT8 MFMAs form sum_t (c''_t - 128) dig[i][t] for all digits of 64 output elements: sixteen digits in one for at most
+// 16 moduli (M < 2^128), twenty in two above.  128 sum_t dig[i][t] makes up for the 128.
+#define OZ2_MFMA_N 20
 struct Oz2CrtDigits {
-  int valid;            // 1 when the plan has them (N <= 16)
-  int init[16];
-  int8_t dig[16][16];   // [digit][modulus], zero beyond N
-  double sinit[4];      // sum_i init[i] 256^i as 40-bit limbs (digits 5 l .. 5 l + 4 in limb l, the rest in the top one
+  int valid;                              // 1 when the plan has them (N <= OZ2_MFMA_N)
+  int8_t dig[OZ2_MFMA_N][OZ2_MFMA_N];     // [digit][modulus], zero beyond N
+  double sinit[4];      // 128 sum_i sum_t dig[i][t] 256^i as 40-bit limbs (digits 5 l .. 5 l + 4 in limb l, the rest in the top one
                         // of the L in use): added after the MFMA, whose accumulator then starts at the inline zero
 };
 

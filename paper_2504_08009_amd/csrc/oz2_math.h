@@ -174,17 +174,17 @@ OZ2_HD void oz2_carry(double* T) {
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Digit route to the same S[l] (matrix-core CRT kernel): D[i] = sum_t c''_t dig[i][t] for the sixteen balanced
-// base-256 digits of the weights in the symmetric range, |D[i]| <= 16 * 255 * 128 < 2^20, so that
-//   Y' = sum_i D[i] 256^i  is congruent to  Y = sum_t c''_t W_t  modulo M,  |Y'| <= 2^11 M.
+// Digit route to the same S[l] (matrix-core CRT kernel): D[i] = sum_t c''_t dig[i][t] for the balanced base-256
+// digits of the weights in the symmetric range, sixteen, or twenty above 16 moduli, |D[i]| <= 20 * 255 * 128 < 2^20, so that
+//   Y' = sum_i D[i] 256^i  is congruent to  Y = sum_t c''_t W_t  modulo M,  |Y'| <= 2^12 M.
 // Limb l collects the digits 5 l .. 5 l + 4 (the top limb all that remain): integers below 2^53, exact.  In a
 // top limb with few digits in use the upper D[i] are zero (|Ws| <= M/2 < 2^(40 L - 1)).
 // ---------------------------------------------------------------------------------------------------
-template <int L>
+template <int L, int DIGITS>
 OZ2_HD void oz2_digits_to_limbs(const int* D, const double* start, double* S) {
 #pragma unroll
   for (int l = 0; l < L; ++l) {
-    const int first = 5 * l, last = l + 1 < L ? 5 * l + 4 : 15;
+    const int first = 5 * l, last = l + 1 < L ? 5 * l + 4 : DIGITS - 1;
     // (two digits at a time as an integer below 2^29: a shift and add in the place of a conversion and an FP64 instruction)
     double v = (last - first) % 2 == 0 ? (double)D[last] : (double)(D[last] * 256 + D[last - 1]);
 #pragma unroll

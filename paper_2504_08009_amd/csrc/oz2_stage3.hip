@@ -203,7 +203,7 @@ __global__ void __launch_bounds__(kThreads, 4) crt_or_fallback_kernel(const void
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Lines 8-11 on UINT8 residue planes with the accumulation of line 9 on the matrix cores (at most 16 moduli).
+// Lines 8-11 on UINT8 residue planes with the accumulation of line 9 on the matrix cores (at most OZ2_MFMA_N moduli).
 // Y = sum_t c''_t W_t is a product of the residues (elements x moduli, bytes) with the weights (moduli x digits,
 // bytes once the weights are written in balanced base-256 digits): one v_mfma_i32_32x32x32_i8 forms all sixteen
 // digit sums of 64 output elements.  Operand roles: the 32 "rows" of the first operand run over the result
@@ -214,6 +214,13 @@ __global__ void __launch_bounds__(kThreads, 4) crt_or_fallback_kernel(const void
 // itself and half in the lane 32 away (result register e of lane l is row 8 (e / 4) + 4 (l / 32) + e % 4); eight
 // v_permlane32_swap bring them together.  The residues enter as c'' - 128 (signed bytes); 128 sum_t dig, in limb
 // form, is added when the digits become the 40-bit limbs the exact tail works on.
+// WIDE, 17 to 20 moduli: twenty digits, on the rows of ten result registers of both halves (digit e or 10 + e), and two products, one for
+// the elements of lanes 0-31 and one for those of lanes 32-63, whose twenty residues are shared out between the halves: words 0 and 1 in
+// the lower one, 3 and 4 in the upper, brought there by two v_permlane32_swap for both products; word 2 stays where it is, against weights
+// that are zero in the other half.  (Four products, two more for digits 16-19 of either half, took 135 registers and were slower than
+// crt_kernel: 660 against 480 us for 18 moduli at 8192 x 8192; with products of 32 x 32 x 16, whose constants take fewer registers, 15 us
+// slower than this there.)  Whole calls, us, crt_kernel / this: 18 moduli 8192 x 8192 x 1024 1565 / 1505, x 200 1032 / 968, 20 moduli x 200
+// 1101 / 1050, 17 moduli 5000 x 7999 x 300 with an update 771 / 698.
 // A thread owns four consecutive rows (one 32-bit load per plane, transposed to four 16-byte operands with byte
 // permutes) of kCrtCols consecutive columns, so that the set-up of the constant operand is spread over 64 elements.
 // Residues, and C where it is updated, are fetched a column ahead of the arithmetic, the shifts once (C and shifts read where they are
@@ -229,7 +236,13 @@ constexpr int kCrtCols = 16;
 // 12-15 in lanes 32-63 (digits 8-15)
 __device__ __forceinline__ constexpr int digit_of_row(int rb) { return ((rb >> 2) & 1) * 8 + (rb >> 3) * 4 + (rb & 3); }
 
-template <int L>
+// WIDE: rows 0-3, 8-11, 16 and 17 of a product (registers 0 to 9 of lanes 0-31) and those four rows on (of lanes 32-63)
+__device__ __forceinline__ constexpr int wide_digit_of_row(int row) {
+  const int e = (row >> 3) * 4 + (row & 3);
+  return e < 10 ? ((row >> 2) & 1) * 10 + e : -1;
+}
+
+template <int L, bool WIDE>
 __global__ void __launch_bounds__(kThreads) crt_mfma_kernel(const uint8_t* __restrict__ planes, int64_t m_pad, int64_t n_pad,
                                                             const int* __restrict__ sa, const int* __restrict__ sb,
                                                             double* __restrict__ C, int64_t ldc, int64_t m, int64_t n,
@@ -246,25 +259,34 @@ __global__ void __launch_bounds__(kThreads) crt_mfma_kernel(const uint8_t* __res
   if ((triangle == 1 && i0 - 4 * lane + 255 < j0) || (triangle == 2 && i0 - 4 * lane > j0 + kCrtCols - 1)) return;
   const int N = cc.N;
 
+  constexpr int kWords = WIDE ? 5 : 4, kResidues = 4 * kWords;  // words of four residues
   // first operand: row lane % 32, inner positions 16 (lane / 32) .. + 15; nonzero where the row's block is the half
   const v16i_t zero16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   v4i_t wop = {0, 0, 0, 0};
+  int wop_upper = 0;  // WIDE: word 2 of the second product's, where the first one's has zero
   {
     const int row = lane & 31;
-    const int mine = (row >> 4) == half ? digit_of_row(row & 15) : -1;
+    const int mine = WIDE ? wide_digit_of_row(row) : (row >> 4) == half ? digit_of_row(row & 15) : -1;
 #pragma unroll
-    for (int d = 0; d < 16; ++d) {
+    for (int d = 0; d < kResidues; ++d) {
       const int* w = reinterpret_cast<const int*>(dg.dig[d]);
-      if (mine == d) wop = v4i_t{w[0], w[1], w[2], w[3]};
+      if (mine == d) {
+        if constexpr (WIDE) {
+          wop = half ? v4i_t{w[3], w[4], 0, 0} : v4i_t{w[0], w[1], w[2], 0};
+          wop_upper = half ? w[2] : 0;
+        } else {
+          wop = v4i_t{w[0], w[1], w[2], w[3]};
+        }
+      }
     }
   }
 
   const size_t plane_words = (size_t)n_pad * m_pad / 4;
   const unsigned* src = reinterpret_cast<const unsigned*>(planes) + ((size_t)j0 * m_pad + i0) / 4;
-  unsigned nx[16];
+  unsigned nx[kResidues];
   auto fetch = [&](int jj) {
 #pragma unroll
-    for (int t = 0; t < 16; ++t)
+    for (int t = 0; t < kResidues; ++t)
       nx[t] = (t < N && j0 + jj < n) ? __builtin_nontemporal_load(src + (size_t)t * plane_words + (size_t)jj * (m_pad / 4)) : 0x80808080u;
   };
   // the shifts of these rows and columns, and C where it is updated, one column ahead like the residues
@@ -289,24 +311,25 @@ __global__ void __launch_bounds__(kThreads) crt_mfma_kernel(const uint8_t* __res
     }
   };
   fetch(0);
-  fetch_c(0);
+  if (!WIDE) fetch_c(0);
   for (int jj = 0; jj < kCrtCols; ++jj) {
     const int64_t j = j0 + jj;
     if (j >= n) break;  // uniform
-    unsigned x[16];
+    unsigned x[kResidues];
 #pragma unroll
-    for (int t = 0; t < 16; ++t) x[t] = nx[t] ^ 0x80808080u;  // c'' - 128 as signed bytes
+    for (int t = 0; t < kResidues; ++t) x[t] = nx[t] ^ 0x80808080u;  // c'' - 128 as signed bytes
     double now[4];
+    if (WIDE) fetch_c(jj);  // (and the next residues between the rows: both a column ahead take 145 registers, this 133)
 #pragma unroll
     for (int r = 0; r < 4; ++r) now[r] = old[r];
-    if (jj + 1 < kCrtCols) {
+    if (!WIDE && jj + 1 < kCrtCols) {
       fetch(jj + 1);
       fetch_c(jj + 1);
     }
-    // 16 words [modulus](4 rows) -> 4 operands [row](16 moduli)
-    v4i_t y[4];
+    // words [modulus](4 rows) -> words [row][group of four moduli]
+    int y[4][kWords];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
+    for (int g = 0; g < kWords; ++g) {
       const unsigned a = __builtin_amdgcn_perm(x[4 * g + 1], x[4 * g], 0x05010400u);  // x0.b0 x1.b0 x0.b1 x1.b1
       const unsigned b = __builtin_amdgcn_perm(x[4 * g + 1], x[4 * g], 0x07030602u);  // x0.b2 x1.b2 x0.b3 x1.b3
       const unsigned c = __builtin_amdgcn_perm(x[4 * g + 3], x[4 * g + 2], 0x05010400u);
@@ -320,21 +343,39 @@ __global__ void __launch_bounds__(kThreads) crt_mfma_kernel(const uint8_t* __res
     double out[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const v16i_t acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wop, y[r], zero16, 0, 0, 0);
-      int D[16];
+      int D[kResidues];
+      if constexpr (WIDE) {
+        const auto s03 = __builtin_amdgcn_permlane32_swap((unsigned)y[r][0], (unsigned)y[r][3], false, false);
+        const auto s14 = __builtin_amdgcn_permlane32_swap((unsigned)y[r][1], (unsigned)y[r][4], false, false);
+        // (word 3 of the weights is zero)
+        const v16i_t lower = __builtin_amdgcn_mfma_i32_32x32x32_i8(wop, v4i_t{(int)s03[0], (int)s14[0], y[r][2], y[r][2]}, zero16, 0, 0, 0);
+        const v16i_t upper = __builtin_amdgcn_mfma_i32_32x32x32_i8(half ? v4i_t{wop[0], wop[1], wop_upper, 0} : v4i_t{wop[0], wop[1], 0, 0},
+                                                                   v4i_t{(int)s03[1], (int)s14[1], y[r][2], y[r][2]}, zero16, 0, 0, 0);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        // lanes 0-31 keep register e (digit e) and get the other half's register e (digit 8 + e) in the place of
-        // register 8 + e; lanes 32-63 the other way round
-        const auto sw = __builtin_amdgcn_permlane32_swap((unsigned)acc[e], (unsigned)acc[8 + e], false, false);
-        D[e] = (int)sw[0];
-        D[8 + e] = (int)sw[1];
+        for (int e = 0; e < 10; ++e) {
+          // lanes 0-31 keep register e of the first product (digit e) and get the other half's (digit 10 + e); lanes 32-63 have
+          // theirs from the second one
+          const auto sw = __builtin_amdgcn_permlane32_swap((unsigned)lower[e], (unsigned)upper[e], false, false);
+          D[e] = (int)sw[0];
+          D[10 + e] = (int)sw[1];
+        }
+      } else {
+        const v16i_t acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wop, v4i_t{y[r][0], y[r][1], y[r][2], y[r][3]}, zero16, 0, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          // lanes 0-31 keep register e (digit e) and get the other half's register e (digit 8 + e) in the place of
+          // register 8 + e; lanes 32-63 the other way round
+          const auto sw = __builtin_amdgcn_permlane32_swap((unsigned)acc[e], (unsigned)acc[8 + e], false, false);
+          D[e] = (int)sw[0];
+          D[8 + e] = (int)sw[1];
+        }
       }
       double S[L];
-      oz2_digits_to_limbs<L>(D, dg.sinit, S);
+      oz2_digits_to_limbs<L, kResidues>(D, dg.sinit, S);
       int e2;
       const double xv = oz2_crt_reduce<L>(S, cc, &e2);
       out[r] = ldexp(xv, e2 - row_shift[r] - sbj);
+      if (WIDE && r == 1 && jj + 1 < kCrtCols) fetch(jj + 1);
     }
     double* dst = C + i0 + j * ldc;
     if (alpha != 1.0 || beta != 0.0) {
@@ -387,13 +428,17 @@ hipError_t oz2_launch_stage3(int64_t m, int64_t n, double alpha, double beta, do
   const int* sb = triangle ? sa : reinterpret_cast<const int*>(ws + lay.off_sb);  // symmetric: columns are A's rows
   // (from 2^24 elements on: below, a thread's 64 elements leave too few threads for the chip and the other kernel wins)
   if (residue_u8 && plan.digits.valid && m * n >= ((int64_t)1 << 24)) {
-    // at most 16 moduli: the accumulation of line 9 on the matrix cores
+    // at most OZ2_MFMA_N moduli: the accumulation of line 9 on the matrix cores
     const uint8_t* p8 = static_cast<const uint8_t*>(cplanes);
     dim3 g2((unsigned)((n + kCrtCols - 1) / kCrtCols), (unsigned)((m + 1023) / 1024));
-    switch (plan.crt.L) {
+    switch (plan.N > 16 ? OZ2_MAX_L : plan.crt.L) {
+      case OZ2_MAX_L:  // 17 to 20 moduli: four limbs
+        hipLaunchKernelGGL((crt_mfma_kernel<4, true>), g2, dim3(kThreads), 0, st, p8, lay.m_pad, lay.n_pad, sa, sb, C, ldc, m, n, alpha,
+                           beta, skip, triangle, plan.crt, plan.digits);
+        break;
 #define OZ2_CASE(LL)                                                                                                  \
   case LL:                                                                                                            \
-    hipLaunchKernelGGL((crt_mfma_kernel<LL>), g2, dim3(kThreads), 0, st, p8, lay.m_pad, lay.n_pad, sa, sb, C, ldc, m, \
+    hipLaunchKernelGGL((crt_mfma_kernel<LL, false>), g2, dim3(kThreads), 0, st, p8, lay.m_pad, lay.n_pad, sa, sb, C, ldc, m, \
                        n, alpha, beta, skip, triangle, plan.crt, plan.digits);                                         \
     break;
       OZ2_CASE(1)
@@ -490,27 +535,28 @@ hipError_t oz2_launch_scale_c(int64_t m, int64_t n, double beta, double* C, int6
   return hipGetLastError();
 }
 
-template <int L>
+template <int L, int DIGITS>
 double host_crt_digits(const Oz2CrtConsts& cc, const Oz2CrtDigits& dg, const uint8_t* res) {
-  int D[16];
-  for (int i = 0; i < 16; ++i) {
+  int D[DIGITS];
+  for (int i = 0; i < DIGITS; ++i) {
     int acc = 0;  // what the matrix core computes: signed bytes c'' - 128 against the digits
     for (int t = 0; t < cc.N; ++t) acc += ((int)res[t] - 128) * (int)dg.dig[i][t];
     D[i] = acc;
   }
   double S[L];
-  oz2_digits_to_limbs<L>(D, dg.sinit, S);
+  oz2_digits_to_limbs<L, DIGITS>(D, dg.sinit, S);
   int e2;
   double x = oz2_crt_reduce<L>(S, cc, &e2);
   return ldexp(x, e2);
 }
 
 double oz2_host_crt_digits_impl(const Oz2CrtConsts& cc, const Oz2CrtDigits& dg, const uint8_t* res) {
+  if (cc.N > 16) return host_crt_digits<4, OZ2_MFMA_N>(cc, dg, res);
   switch (cc.L) {
-    case 1: return host_crt_digits<1>(cc, dg, res);
-    case 2: return host_crt_digits<2>(cc, dg, res);
-    case 3: return host_crt_digits<3>(cc, dg, res);
-    default: return host_crt_digits<4>(cc, dg, res);
+    case 1: return host_crt_digits<1, 16>(cc, dg, res);
+    case 2: return host_crt_digits<2, 16>(cc, dg, res);
+    case 3: return host_crt_digits<3, 16>(cc, dg, res);
+    default: return host_crt_digits<4, 16>(cc, dg, res);
   }
 }
 

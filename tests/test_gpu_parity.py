@@ -497,6 +497,30 @@ def test_matrix_core_crt_every_element_ragged(N, alpha, beta):
     assert not np.isnan(got).any()
 
 
+@pytest.mark.parametrize("N,alpha,beta", [(18, 1.0, 0.0), (20, -0.75, 2.0)])
+def test_matrix_core_crt_of_more_than_16_moduli_every_element(N, alpha, beta):
+    """Twenty digits in two products: a ragged shape, EVERY element against the call with INT32 planes, whose weights are added up in
+    FP64."""
+    m, n, k = 4357, 4099, 70
+    assert m * n >= 1 << 24
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    A, B, C0 = (torch.randn(s, dtype=torch.float64, device="cuda", generator=gen) for s in ((k, m), (n, k), (n, m)))
+    got = []
+    for fmt in (oz.OZ2_PRODUCT_INT32, oz.OZ2_PRODUCT_RESIDUE_U8):
+        C = C0.clone()
+        ws = oz.Workspace(m, n, k, N, product_format=fmt)
+        print("CRT of %d moduli, product format %d" % (N, fmt), flush=True)
+        oz.oz2_set_product_format(fmt)
+        try:
+            oz.oz2_dgemm_ex("N", "N", m, n, k, alpha, A.data_ptr(), m, B.data_ptr(), k, beta, C.data_ptr(), m, N)
+            torch.cuda.synchronize()
+        finally:
+            oz.oz2_set_product_format(oz.OZ2_PRODUCT_RESIDUE_U8)
+        got.append(C.view(torch.int64))
+        del ws
+    assert torch.equal(*got)
+
+
 _c3_oracle = {}
 
 

@@ -358,6 +358,20 @@ def test_host_crt_element_by_digits_is_correctly_rounded(N):
     assert oz.lib().oz2_host_crt_element_digits(17, None, None) == -1
 
 
+@pytest.mark.parametrize("N", [17, 18, 19, 20])
+def test_host_crt_element_by_twenty_digits_is_correctly_rounded(N):
+    """The same route with the twenty digits that 17 to 20 moduli take."""
+    rng = random.Random(177 + N)
+    mods, M, xs = _crt_cases(N, rng)
+    for x in xs:
+        got = oz.host_crt_element_digits(N, [x % p for p in mods])
+        assert got == float(x), (N, x, got, float(x))
+    for res in ([p - 1 for p in mods], [0] * N, [p - 1 if t % 2 else 0 for t, p in enumerate(mods)]):
+        y = sum(r * w for r, w in zip(res, orc.crt_constants(N)[1])) % M
+        assert oz.host_crt_element_digits(N, res) == float(y - M if y >= M - M // 2 else y)
+    assert oz.lib().oz2_host_crt_element_wide_digits(16, None, None) == oz.lib().oz2_host_crt_element_wide_digits(21, None, None) == -1
+
+
 def test_host_crt_extreme_int32_products():
     # products at the INT32 limits and negative values: floor-mod must stay in [0, p)
     N = 16
