@@ -456,8 +456,8 @@ int dgemm_ex_impl(bool static_ws, char transa, char transb, int64_t m, int64_t n
                     : oz2_launch_products(*plan, lay, ws, m, n, s.kblock, s.product_format, 0, OZ2_KRANGE_ALL,
                                           s.nonfinite_check, fin, st);
     if (e != hipSuccess || !mark(2)) return OZ2_ERR_HIP;
-    // below 2^24 elements of C (where the matrix-core kernel takes over) the blocks of the fallback ride in the launch of
-    // stage 3: one launch less (whole calls, us: 2200 x 2200 x 500 103 -> 98, 3000 x 3000 x 1000 224 -> 220, 18 moduli
+    // below 2^24 elements of C the blocks of the fallback ride in the launch of stage 3 (above, its registers cost more than the launch: 10
+    // moduli 4096 x 4096 x 300 164 us, apart 155): one launch less (whole calls, us: 2200 x 2200 x 500 103 -> 98, 3000 x 3000 x 1000 224 -> 220, 18 moduli
     // 3001 x 2777 x 3500 674 -> 667), and with its smaller tiles the fallback itself is the faster one (1024^3 612 -> 277,
     // 4000^3 7770 -> 5430)
     if (s.nonfinite_check && s.product_format == OZ2_PRODUCT_RESIDUE_U8 && m * n < ((int64_t)1 << 24)) {

@@ -15,7 +15,7 @@ constexpr int kThreads = 256;
 static_assert(kThreads == kFallbackThreads, "the small-problem kernel runs both bodies with one block size");
 
 // One plane's values for R consecutive rows: INT32 products (16-byte loads, R = 4) or UINT8 residues that
-// the GEMM epilogue already reduced (R bytes: 8, 4 or 2).
+// the GEMM epilogue already reduced (R bytes: 4 or 2).
 template <bool U8, int R>
 struct PlaneLoad;
 template <>
@@ -26,17 +26,6 @@ struct PlaneLoad<false, 4> {
     res[1] = oz2_floor_mod(c.y, p, ip, hip_);
     res[2] = oz2_floor_mod(c.z, p, ip, hip_);
     res[3] = oz2_floor_mod(c.w, p, ip, hip_);
-  }
-};
-template <>
-struct PlaneLoad<true, 8> {
-  typedef unsigned Raw __attribute__((ext_vector_type(2)));
-  static __device__ __forceinline__ void residues(const Raw& c, double, double, double, double* res) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      res[r] = (double)((c.x >> (8 * r)) & 0xffu);
-      res[4 + r] = (double)((c.y >> (8 * r)) & 0xffu);
-    }
   }
 };
 template <>
@@ -426,8 +415,11 @@ hipError_t oz2_launch_stage3(int64_t m, int64_t n, double alpha, double beta, do
   const unsigned long long* skip = check_flag ? reinterpret_cast<const unsigned long long*>(ws + lay.off_flags) : nullptr;
   const int* sa = reinterpret_cast<const int*>(ws + lay.off_sa);
   const int* sb = triangle ? sa : reinterpret_cast<const int*>(ws + lay.off_sb);  // symmetric: columns are A's rows
-  // (from 2^24 elements on: below, a thread's 64 elements leave too few threads for the chip and the other kernel wins)
-  if (residue_u8 && plan.digits.valid && m * n >= ((int64_t)1 << 24)) {
+  // (from 2^25 elements on, 3/2 of them of a symmetric product: below, a thread's 64 elements leave too few threads for the chip and the
+  // other kernel wins.  Whole calls with inner dimension 300, us, other / matrix cores: 18 moduli 4096^2 245 / 261, 10 moduli 155 / 159, 18
+  // moduli 5200 x 5100 455 / 470, 16 moduli 409 / 409, 5800 x 5900 524 / 514, 8192^2 860 / 846 with 200; dsyrk of order 5000 with 1024 and 10
+  // moduli 214 / 225, 6000 with 16 288 / 295, 7000 384 / 377, 8000 487 / 471.)
+  if (residue_u8 && plan.digits.valid && (triangle ? m * n / 3 * 2 : m * n) >= ((int64_t)1 << 25)) {
     // at most OZ2_MFMA_N moduli: the accumulation of line 9 on the matrix cores
     const uint8_t* p8 = static_cast<const uint8_t*>(cplanes);
     dim3 g2((unsigned)((n + kCrtCols - 1) / kCrtCols), (unsigned)((m + 1023) / 1024));
@@ -451,7 +443,10 @@ hipError_t oz2_launch_stage3(int64_t m, int64_t n, double alpha, double beta, do
     }
     return hipGetLastError();
   }
-  const int rows = residue_u8 ? 8 : 4;
+  // four rows per thread (eight of UINT8 planes, 64 bytes of C at once, leave few waves for a small result and no more bytes in flight:
+  // whole calls, us, eight / four: dtrmm 4096 x 2048 446 / 433, of order 1000 50.6 / 47.7; dsyrk of order 3000 with inner dimension 300
+  // 92.7 / 82.9, 4000 with 500 and 18 moduli 201 / 187; 22 moduli 5000 x 5000 x 200 510 / 499, 8192 x 8192 x 200 1220 / 1211)
+  constexpr int rows = 4;
   const int64_t per_col = (m + rows - 1) / rows;
   const FastDiv by_col = fast_div((unsigned)per_col);
   // the pieces of a launch are counted below 2^31: results of 2^33 elements and more take several
@@ -463,7 +458,7 @@ hipError_t oz2_launch_stage3(int64_t m, int64_t n, double alpha, double beta, do
 #define OZ2_CASE(LL)                                                                                                    \
     case LL:                                                                                                              \
       if (residue_u8)                                                                                                     \
-        hipLaunchKernelGGL((crt_kernel<LL, true, 8>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa, sb, \
+        hipLaunchKernelGGL((crt_kernel<LL, true, 4>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa, sb, \
                            C, ldc, m, j0, j1, alpha, beta, skip, triangle, (int)per_col, by_col, plan.crt);               \
       else                                                                                                                \
         hipLaunchKernelGGL((crt_kernel<LL, false, 4>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa,    \

@@ -521,6 +521,35 @@ def test_matrix_core_crt_of_more_than_16_moduli_every_element(N, alpha, beta):
     assert torch.equal(*got)
 
 
+@pytest.mark.parametrize("uplo,N", [("L", 12), ("U", 18)])
+def test_matrix_core_crt_of_a_triangle_every_element(uplo, N):
+    """The first orders of a symmetric update whose CRT runs on the matrix cores, and the last ones below: the written triangle against
+    the call with INT32 planes, the other one untouched."""
+    for n in (7100, 7090):
+        assert (n * n // 3 * 2 >= 1 << 25) == (n == 7100)
+        gen = torch.Generator(device="cuda").manual_seed(n)
+        A = torch.randn((40, n), dtype=torch.float64, device="cuda", generator=gen)
+        C0 = torch.randn((n, n), dtype=torch.float64, device="cuda", generator=gen)
+        got = []
+        for fmt in (oz.OZ2_PRODUCT_INT32, oz.OZ2_PRODUCT_RESIDUE_U8):
+            C = C0.clone()
+            ws = oz.Workspace(n, n, 40, N, product_format=fmt)
+            print("CRT of a triangle of order %d, product format %d" % (n, fmt), flush=True)
+            oz.oz2_set_product_format(fmt)
+            try:
+                oz.oz2_dsyrk(uplo, "N", n, 40, -0.5, A.data_ptr(), n, 1.25, C.data_ptr(), n, N)
+                torch.cuda.synchronize()
+            finally:
+                oz.oz2_set_product_format(oz.OZ2_PRODUCT_RESIDUE_U8)
+            got.append(C.view(torch.int64))
+            del ws
+        assert torch.equal(*got)
+        other = torch.ones((n, n), dtype=torch.bool, device="cuda").triu(1)  # C is column-major: row and column change places
+        other = other.t() if uplo == "L" else other
+        assert torch.equal(got[1][other], C0.view(torch.int64)[other]) and not torch.equal(got[1], C0.view(torch.int64))
+        del A, C0, C, got, other
+
+
 _c3_oracle = {}
 
 
