@@ -471,8 +471,8 @@ __device__ __forceinline__ oz2_u16x2 conversion_residues(const Oz2SplitPair<(KIN
 template <int KIND>
 __device__ __forceinline__ void convert_strided(const double* __restrict__ A, int64_t lda, int64_t m, int64_t k,
                                                 int64_t m_pad, int64_t k_pad, const int* __restrict__ sa,
-                                                int8_t* __restrict__ planes, const int tri, const Oz2ConvConsts& cc,
-                                                double* tile, unsigned bx, unsigned by) {
+                                                int8_t* __restrict__ planes, const int tri, const bool cached,
+                                                const Oz2ConvConsts& cc, double* tile, unsigned bx, unsigned by) {
   const int64_t r0 = (int64_t)bx * kConvARows;  // < m_pad
   const int64_t kb = by;
   if (KIND != 2 && !tile_used(r0, kb * kBlkK, kb * kBlkK + kBlkK, (tri & 3) == 1, tri)) return;
@@ -480,13 +480,19 @@ __device__ __forceinline__ void convert_strided(const double* __restrict__ A, in
   {
     const int64_t i = r0 + lane;
     const double* src = A + i;
+    auto read = [&](auto load) {
 #pragma unroll 4
-    for (int c = 0; c < kBlkK / 4; ++c) {
-      const int lc = c * 4 + wv;
-      const int64_t l = kb * kBlkK + lc;
-      double v = (i < m && l < k) ? tri_value(__builtin_nontemporal_load(src + l * lda), i, l, tri) : 0.0;
-      tile[lane * kConvAPitch + lc] = v;
-    }
+      for (int c = 0; c < kBlkK / 4; ++c) {
+        const int lc = c * 4 + wv;
+        const int64_t l = kb * kBlkK + lc;
+        double v = (i < m && l < k) ? tri_value(load(src + l * lda), i, l, tri) : 0.0;
+        tile[lane * kConvAPitch + lc] = v;
+      }
+    };
+    if (cached)
+      read([](const double* p) { return *p; });
+    else
+      read([](const double* p) { return __builtin_nontemporal_load(p); });
   }
   __syncthreads();
   const int row = wv * 16 + (lane >> 2);
@@ -527,20 +533,26 @@ constexpr int kConvBColPitch = 296; // doubles per column in LDS: 16 groups + 8 
 template <int KIND>
 __device__ __forceinline__ void convert_contig(const double* __restrict__ B, int64_t ldb, int64_t k, int64_t n,
                                                int64_t n_pad, int64_t k_pad, const int* __restrict__ sb,
-                                               int8_t* __restrict__ planes, const int tri, const Oz2ConvConsts& cc,
-                                               double* tile, unsigned bx, unsigned by) {
+                                               int8_t* __restrict__ planes, const int tri, const bool cached,
+                                               const Oz2ConvConsts& cc, double* tile, unsigned bx, unsigned by) {
   const int64_t j0 = (int64_t)bx * kConvBCols;  // < n_pad, multiple of 16
   const int64_t lbase = (int64_t)by * kConvBKC;
   if (KIND != 2 && !tile_used(j0, lbase, lbase + kConvBKC, (tri & 3) == 2, tri)) return;
   {
     const int64_t l = lbase + threadIdx.x;
     const int slot = (threadIdx.x >> 4) * kConvBGroup + (threadIdx.x & 15);
+    auto read = [&](auto load) {
 #pragma unroll 4
-    for (int c = 0; c < kConvBCols; ++c) {
-      const int64_t j = j0 + c;
-      double v = (j < n && l < k) ? tri_value(__builtin_nontemporal_load(B + l + j * ldb), l, j, tri) : 0.0;
-      tile[c * kConvBColPitch + slot] = v;
-    }
+      for (int c = 0; c < kConvBCols; ++c) {
+        const int64_t j = j0 + c;
+        double v = (j < n && l < k) ? tri_value(load(B + l + j * ldb), l, j, tri) : 0.0;
+        tile[c * kConvBColPitch + slot] = v;
+      }
+    };
+    if (cached)
+      read([](const double* p) { return *p; });
+    else
+      read([](const double* p) { return __builtin_nontemporal_load(p); });
   }
   __syncthreads();
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -574,12 +586,14 @@ __device__ __forceinline__ void convert_contig(const double* __restrict__ B, int
 
 // Both operands of a call in one launch (see operand_max_kernel).  KA / KB: what is written for the first /
 // second job (0, 1: residue planes with the one- / two-level split; 2: the bound plane).
+constexpr int64_t kCachedElements = (int64_t)190 << 17;
 struct ConvJob {
   const double* X;
   int64_t ld, nvec, k, nvec_pad, k_pad;
   const int* shifts;
   int8_t* planes;
   int tri, strided;
+  int cached;  // 1: the operands are of the last-level cache's size, which still holds them from the pass for the maxima
   unsigned gx, nblk;
 };
 constexpr int kConvTileDoubles =
@@ -592,16 +606,16 @@ __global__ void __launch_bounds__(kThreads) operand_convert_kernel(const ConvJob
   if (blockIdx.x < ja.nblk) {
     const unsigned bx = blockIdx.x % ja.gx, by = blockIdx.x / ja.gx;
     if (ja.strided)
-      convert_strided<KA>(ja.X, ja.ld, ja.nvec, ja.k, ja.nvec_pad, ja.k_pad, ja.shifts, ja.planes, ja.tri, cc, tile, bx, by);
+      convert_strided<KA>(ja.X, ja.ld, ja.nvec, ja.k, ja.nvec_pad, ja.k_pad, ja.shifts, ja.planes, ja.tri, ja.cached, cc, tile, bx, by);
     else
-      convert_contig<KA>(ja.X, ja.ld, ja.k, ja.nvec, ja.nvec_pad, ja.k_pad, ja.shifts, ja.planes, ja.tri, cc, tile, bx, by);
+      convert_contig<KA>(ja.X, ja.ld, ja.k, ja.nvec, ja.nvec_pad, ja.k_pad, ja.shifts, ja.planes, ja.tri, ja.cached, cc, tile, bx, by);
   } else {
     const unsigned id = blockIdx.x - ja.nblk;
     const unsigned bx = id % jb.gx, by = id / jb.gx;
     if (jb.strided)
-      convert_strided<KB>(jb.X, jb.ld, jb.nvec, jb.k, jb.nvec_pad, jb.k_pad, jb.shifts, jb.planes, jb.tri, cc, tile, bx, by);
+      convert_strided<KB>(jb.X, jb.ld, jb.nvec, jb.k, jb.nvec_pad, jb.k_pad, jb.shifts, jb.planes, jb.tri, jb.cached, cc, tile, bx, by);
     else
-      convert_contig<KB>(jb.X, jb.ld, jb.k, jb.nvec, jb.nvec_pad, jb.k_pad, jb.shifts, jb.planes, jb.tri, cc, tile, bx, by);
+      convert_contig<KB>(jb.X, jb.ld, jb.k, jb.nvec, jb.nvec_pad, jb.k_pad, jb.shifts, jb.planes, jb.tri, jb.cached, cc, tile, bx, by);
   }
 }
 
@@ -860,16 +874,21 @@ void launch_norm(const Operand& o, hipStream_t st) {
 hipError_t launch_convert(const Operand* ops, int nops, const int* kind, bool large, const Oz2ConvConsts& conv,
                           const Oz2ScanFinish& fin, hipStream_t st) {
   ConvJob job[2] = {};
-  int64_t total = 0;
+  int64_t total = 0, elements = 0;
   for (int x = 0; x < nops; ++x) {
     const Operand& o = ops[x];
     const int64_t gx = o.strided ? o.nvec_pad / kConvARows : o.nvec_pad / kConvBCols;
     const int64_t gy = o.strided ? o.k_pad / kBlkK : blocks_of(o.k_pad, kConvBKC);
     total += gx * gy;
     if (total >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-    job[x] = {o.X, o.ld, o.nvec, o.k, o.nvec_pad, o.k_pad, o.shifts, o.planes, o.tri, o.strided ? 1 : 0, (unsigned)gx,
+    elements += o.tri ? o.nvec * o.k / 2 : o.nvec * o.k;
+    job[x] = {o.X, o.ld, o.nvec, o.k, o.nvec_pad, o.k_pad, o.shifts, o.planes, o.tri, o.strided ? 1 : 0, 0, (unsigned)gx,
               (unsigned)(gx * gy)};
   }
+  // Up to 190 MB the last-level cache still has the operands from the pass for the maxima, and non-temporal loads do not find them there
+  // (whole calls, us, non-temporal / this: 16 moduli 300 x 300 x 20000 272 / 223, 14 moduli 500 x 500 x 12000 172 / 152, 2000 x 2000 x
+  // 5000 371 / 360, INT8-product mode 1500 x 1500 x 3000 221 / 206, 3001 x 2777 x 3500 with 15 630 / 604; above, 4096^3 1048 / 1063).
+  job[0].cached = job[1].cached = elements <= kCachedElements;
   const int ka = kind[0], kb = nops == 2 ? kind[1] : kind[0];
   if (nops == 1) job[1] = job[0], job[1].nblk = 0;
   const dim3 grid((unsigned)total), thr(kThreads);
