@@ -14,6 +14,9 @@
 #define OZ2_MAX_PLANES (7 * OZ2_MAX_N)  // planes of one GEMM launch: seven per modulus in the Strassen form
 #define OZ2_LIMB_BITS 40
 
+// Bytes of residue planes of a result up to which the last-level cache (256 MB) keeps them from stage 2 to stage 3.
+#define OZ2_CACHED_RESULT ((int64_t)160 << 20)
+
 // GEMM tiling (stage 2): workgroup tile TILE_M x TILE_N, k-tile TILE_K bytes.
 #define OZ2_TILE_M 256
 #define OZ2_TILE_N 256

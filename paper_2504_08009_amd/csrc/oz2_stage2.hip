@@ -102,7 +102,6 @@ struct GemmArgs {
   int fin_stops;                        // 1: every workgroup looks at the reports and stops when there is one
   unsigned long long* xcd_sync;         // one counter per XCD (zero at launch), or null: no round sync
   int full_rounds;                      // rounds in which every workgroup slot has a tile
-  int pass_by;                          // 1: residues are stored past the L2 (see the launcher)
   int sync_spins;                       // bound of one wait of the round synchronisation, in polls of the counter
   FastDiv per_modulus;                  // planes per modulus: plane u is reduced modulo number u / per_modulus
   FastDiv div_plane;                    // tiles, sub-blocks or super-blocks of a plane
@@ -341,8 +340,9 @@ __device__ __forceinline__ Tile decode_tile(const GemmArgs& g, int slot, int wv)
 // accumulators between them (inner dimensions beyond the INT32 exactness bound, or a smaller block on request).
 // A kernel of its own: the reduction's 256 x 8 instructions need so many registers at once that the compiler parks
 // 48 accumulators in scratch memory around it, on the path of every tile, and the instantiation without it does not.
-// SHORT: the inner dimension is at most OZ2_SHORT_SUM.
-template <bool RESIDUE_U8, bool LIST_ORDER, bool EARLY_ARRIVAL, bool KBLOCKED, bool SHORT = false>
+// SHORT: the inner dimension is at most OZ2_SHORT_SUM.  PASS_BY: residues are stored past the caches (see the launcher; as a branch around
+// the stores it cost 1 to 2 % of the whole call).
+template <bool RESIDUE_U8, bool LIST_ORDER, bool EARLY_ARRIVAL, bool KBLOCKED, bool SHORT = false, bool PASS_BY = false>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))) gemm_i8_kernel(const GemmArgs g) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
 
@@ -667,8 +667,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(112))
       // both halves of a column together, so that its cache lines are complete at once
       uint8_t* cj = corner + (size_t)(y * 16) * g.m_pad;  // uniform; + 64 h + lane_off below
       v4i* const to = reinterpret_cast<v4i*>(cj + lane_off);
-      if (SHORT || g.pass_by) {
-        __builtin_nontemporal_store(lo, to);  // (SHORT: always, see the launcher)
+      if constexpr (PASS_BY) {
+        __builtin_nontemporal_store(lo, to);
         __builtin_nontemporal_store(hi, to + 4);
       } else {
         to[0] = lo;
@@ -720,13 +720,16 @@ hipError_t gemm_setup() {
 #define OZ2_BOTH(U8, LIST, EARLY)                                              \
   reinterpret_cast<const void*>(gemm_i8_kernel<U8, LIST, EARLY, false>),       \
       reinterpret_cast<const void*>(gemm_i8_kernel<U8, LIST, EARLY, true>)
-  const void* kernels[14] = {reinterpret_cast<const void*>(gemm_i8_kernel<true, false, false, false, true>),
-                             reinterpret_cast<const void*>(gemm_i8_kernel<true, true, false, false, true>),
+#define OZ2_SHALLOW(SHORT, PASS_BY)                                                           \
+  reinterpret_cast<const void*>(gemm_i8_kernel<true, false, false, false, SHORT, PASS_BY>),   \
+      reinterpret_cast<const void*>(gemm_i8_kernel<true, true, false, false, SHORT, PASS_BY>)
+  const void* kernels[18] = {OZ2_SHALLOW(true, false), OZ2_SHALLOW(true, true), OZ2_SHALLOW(false, true),
                              OZ2_BOTH(false, false, false), OZ2_BOTH(true, false, false), OZ2_BOTH(false, true, false),
                              OZ2_BOTH(true, true, false),   OZ2_BOTH(true, false, true),  OZ2_BOTH(true, true, true)};
 #undef OZ2_BOTH
+#undef OZ2_SHALLOW
   hipError_t e = hipSuccess;
-  for (int i = 0; i < 14 && e == hipSuccess; ++i)
+  for (int i = 0; i < 18 && e == hipSuccess; ++i)
     e = hipFuncSetAttribute(kernels[i], hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
   if (e != hipSuccess) return e;
   int dev = 0, n = 0;
@@ -800,13 +803,6 @@ hipError_t launch_gemm(const Oz2Layout& lay, char* ws, int num_moduli, const int
   // every workgroup walks the work indices of its slot in launch order.  Structured products have tiles of
   // unequal length (or none): there the hardware's dynamic placement of one workgroup per index balances better.
   unsigned grid = (unsigned)(g.chunk * 8);
-  // Residues stored past the L2 (evicted first): where the panels of a round of tiles are of the L2's size, the lines of C' push them out
-  // and the copies into LDS wait (cycles per k-tile at 8192 x 8192 x 1024 1510 -> 1240, inside the kernel), and planes beyond the last-level
-  // cache are not found there by stage 3 anyway; between the two they are better left in the caches.  Whole calls, us, through / past: 12
-  // moduli 8000 x 4000 x 300 381 / 337, 16 moduli 4000 x 4000 x 600 316 / 292, 18 moduli 8192 x 8192 x 1024 1629 / 1572, 14 moduli 2048^3
-  // 176.9 / 172.5, 16 moduli 8192 x 8192 x 2048 2210 / 2169, 12288 x 12288 x 4096 8325 / 8252; 4000 x 4000 x 2400 611 / 613, 6000 x 6000 x
-  // 3000 1692 / 1698, 5000 x 5000 x 4096 with 12 1275 / 1270, 2048 x 2048 x 8192 616 / 622.
-  g.pass_by = g.ktiles <= 32 || total * (BM * BN) > (int64_t)1 << 29;
   g.xcd_sync = nullptr;
   g.full_rounds = 0;
   g.sync_spins = g_sync_spins;
@@ -867,11 +863,29 @@ hipError_t launch_gemm(const Oz2Layout& lay, char* ws, int num_moduli, const int
     else                                                                                            \
       hipLaunchKernelGGL((gemm_i8_kernel<U8, LIST, EARLY, false>), grd, thr, kLdsBytes, st, g);     \
   } while (0)
-  const bool short_sums = residue_u8 && !kblocked && lay.k_pad <= OZ2_SHORT_SUM;  // (no round synchronisation: at most 16 k-tiles)
-  if (short_sums && list_order)
-    hipLaunchKernelGGL((gemm_i8_kernel<true, true, false, false, true>), grd, thr, kLdsBytes, st, g);
-  else if (short_sums)
-    hipLaunchKernelGGL((gemm_i8_kernel<true, false, false, false, true>), grd, thr, kLdsBytes, st, g);
+  // Inner dimensions up to 2048: no round synchronisation, and residues stored past the caches.  Where the panels of a round of tiles are
+  // of the L2's size, the lines of C' push them out and the copies into LDS wait (cycles per k-tile at 8192 x 8192 x 1024 1510 -> 1240,
+  // inside the kernel).  Not where the last-level cache keeps them for stage 3, but for results that the L2s hold whole, which they
+  // would give back at the end of the launch, one line after the other.  Whole calls, us, through / past: 12 moduli 8000 x 4000 x 300 381
+  // / 337, 16 moduli 4000 x 4000 x 600 316 / 292, 18 moduli 8192 x 8192 x 1024 1629 / 1572, 16 moduli 8192 x 8192 x 2048 2210 / 2169, 14
+  // moduli 1024^3 38.2 / 36.9; 2000 x 2000 x 500 71.8 / 75.8, 2048^3 171.1 / 172.1, 15 moduli 3001 x 2777 x 1000 194 / 198; longer ones:
+  // 14 moduli 4000 x 4000 x 2400 611 / 613, 16 moduli 6000 x 6000 x 3000 1692 / 1698, 2048 x 2048 x 8192 616 / 622, 8192^3 7042 / 7076.
+  const int64_t result = total * (BM * BN);
+  const bool shallow = residue_u8 && !kblocked && g.ktiles <= 32 && g.xcd_sync == nullptr;
+  const bool short_sums = lay.k_pad <= OZ2_SHORT_SUM, pass_by = result > OZ2_CACHED_RESULT || result <= (int64_t)1 << 25;
+#define OZ2_GEMM_SHALLOW(SHORT, PASS_BY)                                                                            \
+  do {                                                                                                              \
+    if (list_order)                                                                                                 \
+      hipLaunchKernelGGL((gemm_i8_kernel<true, true, false, false, SHORT, PASS_BY>), grd, thr, kLdsBytes, st, g);   \
+    else                                                                                                            \
+      hipLaunchKernelGGL((gemm_i8_kernel<true, false, false, false, SHORT, PASS_BY>), grd, thr, kLdsBytes, st, g);  \
+  } while (0)
+  if (shallow && short_sums && pass_by)
+    OZ2_GEMM_SHALLOW(true, true);
+  else if (shallow && short_sums)
+    OZ2_GEMM_SHALLOW(true, false);
+  else if (shallow && pass_by)
+    OZ2_GEMM_SHALLOW(false, true);
   else if (!residue_u8 && list_order)
     OZ2_GEMM(false, true, false);
   else if (!residue_u8)
@@ -885,6 +899,7 @@ hipError_t launch_gemm(const Oz2Layout& lay, char* ws, int num_moduli, const int
   else
     OZ2_GEMM(true, false, false);
 #undef OZ2_GEMM
+#undef OZ2_GEMM_SHALLOW
   return hipGetLastError();
 }
 

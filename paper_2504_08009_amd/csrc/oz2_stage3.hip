@@ -49,7 +49,8 @@ struct PlaneLoad<true, 2> {
 // the arithmetic.  SMALL (a launch at its own latency): the shifts and C, where it is updated, are fetched with the first ones,
 // and so is *flag, which leaves C alone where it is set: one wait for memory in the place of four (256^3, inside the launch, 3.3
 // us before; in large launches the registers cost a wave per SIMD).
-template <int L, bool U8, int R, int kBatch, bool SMALL>
+// PASS_BY: planes larger than the last-level cache are read past the caches; smaller ones are found there.
+template <int L, bool U8, int R, int kBatch, bool SMALL, bool PASS_BY>
 __device__ __forceinline__ void crt_rows(const void* __restrict__ cplanes, int64_t m_pad, int64_t n_pad,
                                          const int* __restrict__ sa, const int* __restrict__ sb, double* __restrict__ C,
                                          int64_t ldc, int64_t m, int64_t n, const double alpha, const double beta,
@@ -70,12 +71,13 @@ __device__ __forceinline__ void crt_rows(const void* __restrict__ cplanes, int64
 #pragma unroll
     for (int l = 0; l < L; ++l) S[r][l] = 0.0;
 
-  // Planes are read once (non-temporal loads), a batch ahead of the arithmetic: kBatch loads per thread in flight keep enough bytes
+  // Planes are read once, a batch ahead of the arithmetic: kBatch loads per thread in flight keep enough bytes
   // moving per CU to cover the memory latency (one load ahead does not).
   const int N = cc.N;
   Raw nxt[kBatch];
+  auto read = [](const Raw* p) { return PASS_BY ? __builtin_nontemporal_load(p) : *p; };
 #pragma unroll
-  for (int d = 0; d < kBatch; ++d) nxt[d] = __builtin_nontemporal_load(src + (size_t)(d < N ? d : N - 1) * stride);
+  for (int d = 0; d < kBatch; ++d) nxt[d] = read(src + (size_t)(d < N ? d : N - 1) * stride);
   double* dst = C + i0 + j * ldc;
   int shift[R];
   double old[R];
@@ -97,7 +99,7 @@ __device__ __forceinline__ void crt_rows(const void* __restrict__ cplanes, int64
 #pragma unroll
       for (int d = 0; d < kBatch; ++d) {
         const int t = t0 + kBatch + d;
-        nxt[d] = __builtin_nontemporal_load(src + (size_t)(t < N ? t : N - 1) * stride);  // past the end: a harmless repeat of the last plane
+        nxt[d] = read(src + (size_t)(t < N ? t : N - 1) * stride);  // past the end: a harmless repeat of the last plane
       }
     }
 #pragma unroll
@@ -150,7 +152,7 @@ __device__ __forceinline__ void crt_rows(const void* __restrict__ cplanes, int64
 // The work of a launch is the columns' pieces of R rows, one after the other (per_col of them in a column), so that
 // short and ragged columns leave no lanes idle (a block per 2048 rows of a column before: one lane in eight worked at 256
 // rows, two thirds of them at 2777).  A launch takes the columns j0 .. n - 1.
-template <int L, bool U8, int R>
+template <int L, bool U8, int R, bool PASS_BY>
 __global__ void __launch_bounds__(kThreads) crt_kernel(const void* __restrict__ cplanes, int64_t m_pad, int64_t n_pad,
                                                        const int* __restrict__ sa, const int* __restrict__ sb,
                                                        double* __restrict__ C, int64_t ldc, int64_t m, int64_t j0,
@@ -163,7 +165,7 @@ __global__ void __launch_bounds__(kThreads) crt_kernel(const void* __restrict__ 
   const int g = (int)(blockIdx.x * kThreads + threadIdx.x), q = g / by_col;
   const int64_t j = j0 + q;
   if (j >= n) return;
-  crt_rows<L, U8, R, 4, false>(cplanes, m_pad, n_pad, sa, sb, C, ldc, m, n, alpha, beta, triangle, cc, j, (int64_t)(g - q * per_col) * R,
+  crt_rows<L, U8, R, 4, false, PASS_BY>(cplanes, m_pad, n_pad, sa, sb, C, ldc, m, n, alpha, beta, triangle, cc, j, (int64_t)(g - q * per_col) * R,
                         nullptr);
 }
 
@@ -172,7 +174,7 @@ __global__ void __launch_bounds__(kThreads) crt_kernel(const void* __restrict__ 
 // kBatch: eight planes at a time, four where the last eight would be half repeats of the last plane or more (9 to 12 moduli, say), which
 // are fetched like any other (whole calls, us, always eight / this: 4 moduli 1629 x 3786 x 343 57.9 / 56.0, 10 moduli 2000 x 2000 x 300
 // 58.7 / 57.5, 9 moduli 2500 x 2500 x 200 with an update 80.3 / 79.1; always four / this: 15 moduli 3001 x 2777 x 300 131.6 / 129.4, 14 moduli 700^3 29.7 / 29.4).
-template <int L, int R, int kBatch>
+template <int L, int R, int kBatch, bool PASS_BY>
 __global__ void __launch_bounds__(kThreads, 4) crt_or_fallback_kernel(const void* __restrict__ cplanes, int64_t m_pad,
                                                                    int64_t n_pad, const int* __restrict__ sa,
                                                                    const int* __restrict__ sb,
@@ -184,7 +186,7 @@ __global__ void __launch_bounds__(kThreads, 4) crt_or_fallback_kernel(const void
   if (blockIdx.x < crt_blocks) {
     const int g = (int)(blockIdx.x * kThreads + threadIdx.x), j = g / by_col;
     if (j >= f.n) return;
-    crt_rows<L, true, R, kBatch, true>(cplanes, m_pad, n_pad, sa, sb, f.C, f.ldc, f.m, f.n, f.alpha, f.beta, 0, cc, j,
+    crt_rows<L, true, R, kBatch, true, PASS_BY>(cplanes, m_pad, n_pad, sa, sb, f.C, f.ldc, f.m, f.n, f.alpha, f.beta, 0, cc, j,
                             (int64_t)(g - j * per_col) * R, flag);
   } else if (*flag != 0ull) {
     oz2_fallback_tile<kFallbackSmallTile>(f, blockIdx.x - crt_blocks);
@@ -393,6 +395,13 @@ __global__ void __launch_bounds__(kThreads) scale_c_kernel(double* __restrict__ 
   }
 }
 
+// Does the last-level cache hold the UINT8 planes of a result that the products have just written?  (Whole calls, us, read past it /
+// through it: 14 moduli 3001 x 2777 x 200 120 / 107, 1024^3 38.3 / 36.9, 12 moduli dsyrk of order 5000 with 200 152 / 142; 268 MB 16 moduli
+// 4000 x 4000 x 600 284 / 293, 210 MB dsyrk of order 5000 with 1024 315 / 323.)
+bool planes_cached(const Oz2Plan& plan, const Oz2Layout& lay, int triangle) {
+  return plan.N * lay.m_pad * lay.n_pad / (triangle ? 2 : 1) <= OZ2_CACHED_RESULT;
+}
+
 template <int L>
 double host_crt(const Oz2CrtConsts& cc, const int32_t* cprod) {
   double S[L];
@@ -449,6 +458,7 @@ hipError_t oz2_launch_stage3(int64_t m, int64_t n, double alpha, double beta, do
   constexpr int rows = 4;
   const int64_t per_col = (m + rows - 1) / rows;
   const FastDiv by_col = fast_div((unsigned)per_col);
+  const bool cached = planes_cached(plan, lay, triangle);
   // the pieces of a launch are counted below 2^31: results of 2^33 elements and more take several
   const int64_t cols = (((int64_t)1 << 31) - kThreads) / per_col;
   for (int64_t j0 = 0; j0 < n; j0 += cols) {
@@ -457,11 +467,14 @@ hipError_t oz2_launch_stage3(int64_t m, int64_t n, double alpha, double beta, do
     switch (plan.crt.L) {
 #define OZ2_CASE(LL)                                                                                                    \
     case LL:                                                                                                              \
-      if (residue_u8)                                                                                                     \
-        hipLaunchKernelGGL((crt_kernel<LL, true, 4>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa, sb, \
+      if (residue_u8 && cached)                                                                                           \
+        hipLaunchKernelGGL((crt_kernel<LL, true, 4, false>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa, sb, \
+                           C, ldc, m, j0, j1, alpha, beta, skip, triangle, (int)per_col, by_col, plan.crt);               \
+      else if (residue_u8)                                                                                                \
+        hipLaunchKernelGGL((crt_kernel<LL, true, 4, true>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa, sb, \
                            C, ldc, m, j0, j1, alpha, beta, skip, triangle, (int)per_col, by_col, plan.crt);               \
       else                                                                                                                \
-        hipLaunchKernelGGL((crt_kernel<LL, false, 4>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa,    \
+        hipLaunchKernelGGL((crt_kernel<LL, false, 4, true>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa,    \
                            sb, C, ldc, m, j0, j1, alpha, beta, skip, triangle, (int)per_col, by_col, plan.crt);           \
       break;
       OZ2_CASE(1)
@@ -495,21 +508,25 @@ hipError_t oz2_launch_stage3_or_fallback(int transa, int transb, int64_t m, int6
   const FastDiv by_col = fast_div((unsigned)per_col);
   const Oz2FallbackArgs f = {transa, transb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, tiles_m, 0, 0, 0};
   const dim3 grid((unsigned)(crt_blocks + tiles_m * tiles_n));
-  const bool by_four = (plan.N - 1) % 8 < 4;
+  const bool by_four = (plan.N - 1) % 8 < 4, cached = planes_cached(plan, lay, 0);
   switch (plan.crt.L) {
-#define OZ2_LAUNCH(LL, R, BATCH)                                                                                           \
-  hipLaunchKernelGGL((crt_or_fallback_kernel<LL, R, BATCH>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa, \
+#define OZ2_LAUNCH(LL, R, BATCH, PASS_BY)                                                                                  \
+  hipLaunchKernelGGL((crt_or_fallback_kernel<LL, R, BATCH, PASS_BY>), grid, dim3(kThreads), 0, st, cplanes, lay.m_pad, lay.n_pad, sa, \
                      sb, flag, (unsigned)crt_blocks, (int)per_col, by_col, f, plan.crt)
-#define OZ2_CASE(LL)                \
-  case LL:                          \
-    if (rows == 2 && by_four)       \
-      OZ2_LAUNCH(LL, 2, 4);         \
-    else if (rows == 2)             \
-      OZ2_LAUNCH(LL, 2, 8);         \
-    else if (by_four)               \
-      OZ2_LAUNCH(LL, 4, 4);         \
-    else                            \
-      OZ2_LAUNCH(LL, 4, 8);         \
+#define OZ2_CASE(LL)                     \
+  case LL:                               \
+    if (rows == 2 && by_four)            \
+      OZ2_LAUNCH(LL, 2, 4, false);       \
+    else if (rows == 2)                  \
+      OZ2_LAUNCH(LL, 2, 8, false);       \
+    else if (by_four && cached)          \
+      OZ2_LAUNCH(LL, 4, 4, false);       \
+    else if (by_four)                    \
+      OZ2_LAUNCH(LL, 4, 4, true);        \
+    else if (cached)                     \
+      OZ2_LAUNCH(LL, 4, 8, false);       \
+    else                                 \
+      OZ2_LAUNCH(LL, 4, 8, true);        \
     break;
     OZ2_CASE(1)
     OZ2_CASE(2)
