@@ -647,7 +647,8 @@ struct ShortJob {
 };
 // KIND 0, 1: residue planes as in the conversion above; 2: the plane of 6-bit bounds.  mode: as shift_of counts them (0 or 1).
 // slot: this workgroup's report (mode 0; in mode 1 a vector with an infinity or a NaN has kBadReport for its norm bound)
-template <int KIND, int V>
+// THROUGH: residues are stored through the caches (planes_through_caches).
+template <int KIND, int V, bool THROUGH>
 __device__ __forceinline__ void convert_short(const ShortJob& j, const Oz2ConvConsts& cc, const int mode, double* tile, unsigned id,
                                               unsigned long long* slot) {
   constexpr int kWaves = kShortThreads / 64;
@@ -787,7 +788,10 @@ __device__ __forceinline__ void convert_short(const ShortJob& j, const Oz2ConvCo
 #pragma unroll
         for (int h = 0; h < 2; ++h)
           w[h] = oz2_pack_pairs(oz2_residue_pair<TWO_LEVEL>(xs[2 * h], mod), oz2_residue_pair<TWO_LEVEL>(xs[2 * h + 1], mod));
-        __builtin_nontemporal_store(w, reinterpret_cast<v2u*>(dst));
+        if constexpr (THROUGH)
+          *reinterpret_cast<v2u*>(dst) = w;
+        else
+          __builtin_nontemporal_store(w, reinterpret_cast<v2u*>(dst));
         dst += plane_stride;
       }
     }
@@ -798,7 +802,7 @@ __device__ __forceinline__ void convert_short(const ShortJob& j, const Oz2ConvCo
 constexpr int kFinishThreads = 1024;
 __global__ void __launch_bounds__(kFinishThreads) finish_scan_kernel(const Oz2ScanFinish f) { finish_scan(f); }
 
-template <int KA, int KB, int V>
+template <int KA, int KB, int V, bool THROUGH>
 __global__ void __launch_bounds__(kShortThreads, KA == 1 || KB == 1 ? 4 : 6) short_convert_kernel(const ShortJob ja, const ShortJob jb,
                                                                       const Oz2ConvConsts cc, const int mode, const int warm,
                                                                       unsigned long long* __restrict__ slots) {
@@ -815,9 +819,9 @@ __global__ void __launch_bounds__(kShortThreads, KA == 1 || KB == 1 ? 4 : 6) sho
   const unsigned id = j.tri ? (y / kNear * 8 + x) * kNear + y % kNear : x * j.chunk + y;
   unsigned long long* slot = slots + (first ? id : ja.nblk + id);
   if (first)
-    convert_short<KA, V>(ja, cc, mode, short_tile, id, slot);
+    convert_short<KA, V, THROUGH>(ja, cc, mode, short_tile, id, slot);
   else
-    convert_short<KB, V>(jb, cc, mode, short_tile, id, slot);
+    convert_short<KB, V, THROUGH>(jb, cc, mode, short_tile, id, slot);
 }
 
 }  // namespace
@@ -943,6 +947,16 @@ static int short_vectors(int64_t vectors, int64_t in_lines, int64_t k_pad, bool 
   return fits(2) && vectors <= 8 * cus ? 2 : 0;
 }
 
+// Residue planes of the one-pass conversion stored through the caches: those that the last-level cache keeps for the products.  Not the
+// ones of a small result that the L2s hold whole, which they would give back at the end of the launch while nothing else runs.  Whole
+// calls, us, past the caches / through: 14 moduli 2000 x 2000 x 500 75.8 / 68.2, 3001 x 2777 x 200 107 / 99, 2048^3 172.1 / 166.5, 4000 x
+// 500 x 1000 72.8 / 68.7, 12 moduli 8000 x 4000 x 300 332 / 319, dsyrk of order 5000 with 200 142 / 136, with 1024 and 16 moduli 315 / 307;
+// 14 moduli 700^3 29.0 / 31.0, 1024^3 36.9 / 37.5; 302 MB 18 moduli 8192 x 8192 x 1024 1487 / 1507.
+static bool planes_through_caches(int num_moduli, const Oz2Layout& lay, bool symmetric) {
+  const int64_t bytes = num_moduli * (lay.m_pad + (symmetric ? 0 : lay.n_pad)) * lay.k_pad;
+  return bytes <= (int64_t)200 << 20 && (bytes > (int64_t)32 << 20 || lay.m_pad * lay.n_pad >= (int64_t)1 << 21);
+}
+
 // What the shifts are formed from: the budgets of the operands, or (INT8-product mode) first the exponents 5 - e of the
 // 6-bit bounds.  bit_split moves that many bits from the first operand to the second, which also gets the odd bit of the sum
 // (bit_split == 0: the equal split; the symmetric product always uses it).
@@ -980,13 +994,16 @@ hipError_t oz2_launch_finish_scan(const Oz2ScanFinish& f, hipStream_t st) {
 
 // Once per process, before any launch: the dynamic LDS limit of the one-pass conversion.
 hipError_t oz2_stage1_setup() {
-#define OZ2_ALL(KA, KB)                                           \
-  reinterpret_cast<const void*>(short_convert_kernel<KA, KB, 8>), \
-      reinterpret_cast<const void*>(short_convert_kernel<KA, KB, 4>), reinterpret_cast<const void*>(short_convert_kernel<KA, KB, 2>)
-  const void* kernels[15] = {OZ2_ALL(0, 0), OZ2_ALL(0, 1), OZ2_ALL(1, 0), OZ2_ALL(1, 1), OZ2_ALL(2, 2)};
+#define OZ2_ALL(KA, KB, THROUGH)                                           \
+  reinterpret_cast<const void*>(short_convert_kernel<KA, KB, 8, THROUGH>), \
+      reinterpret_cast<const void*>(short_convert_kernel<KA, KB, 4, THROUGH>), \
+      reinterpret_cast<const void*>(short_convert_kernel<KA, KB, 2, THROUGH>)
+#define OZ2_BOTH(KA, KB) OZ2_ALL(KA, KB, false), OZ2_ALL(KA, KB, true)
+  const void* kernels[27] = {OZ2_BOTH(0, 0), OZ2_BOTH(0, 1), OZ2_BOTH(1, 0), OZ2_BOTH(1, 1), OZ2_ALL(2, 2, false)};
+#undef OZ2_BOTH
 #undef OZ2_ALL
   hipError_t e = hipSuccess;
-  for (int i = 0; i < 15 && e == hipSuccess; ++i)
+  for (int i = 0; i < 27 && e == hipSuccess; ++i)
     e = hipFuncSetAttribute(kernels[i], hipFuncAttributeMaxDynamicSharedMemorySize, kShortLds);
   return e;
 }
@@ -1067,19 +1084,27 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
     // the others and the loads only cost (9 moduli 71 x 5081 x 184 22.5 -> 23.1, 900 x 700 x 300 22.7 -> 23.1).
     const int warm = lay.k_pad > 1024 || 2 * (int64_t)groups <= 3 * oz2_gemm_cus();
     const size_t lds = (size_t)short_vecs * (lay.k_pad + 4) * sizeof(double);
-#define OZ2_SHORT_V(KA, KB, V) \
-  hipLaunchKernelGGL((short_convert_kernel<KA, KB, V>), grid, thr, lds, st, sj[0], sj[1], conv, base_mode, warm, slots)
-#define OZ2_SHORT(KA, KB)        \
-  do {                           \
-    if (short_vecs == 8)         \
-      OZ2_SHORT_V(KA, KB, 8);    \
-    else if (short_vecs == 4)    \
-      OZ2_SHORT_V(KA, KB, 4);    \
-    else                         \
-      OZ2_SHORT_V(KA, KB, 2);    \
+    const bool through = planes_through_caches(plan.N, lay, B == nullptr);
+#define OZ2_SHORT_V(KA, KB, V, THROUGH) \
+  hipLaunchKernelGGL((short_convert_kernel<KA, KB, V, THROUGH>), grid, thr, lds, st, sj[0], sj[1], conv, base_mode, warm, slots)
+#define OZ2_SHORT_ALL(KA, KB, THROUGH)    \
+  do {                                    \
+    if (short_vecs == 8)                  \
+      OZ2_SHORT_V(KA, KB, 8, THROUGH);    \
+    else if (short_vecs == 4)             \
+      OZ2_SHORT_V(KA, KB, 4, THROUGH);    \
+    else                                  \
+      OZ2_SHORT_V(KA, KB, 2, THROUGH);    \
+  } while (0)
+#define OZ2_SHORT(KA, KB)                 \
+  do {                                    \
+    if (through)                          \
+      OZ2_SHORT_ALL(KA, KB, true);        \
+    else                                  \
+      OZ2_SHORT_ALL(KA, KB, false);       \
   } while (0)
     if (bounds)
-      OZ2_SHORT(2, 2);
+      OZ2_SHORT_ALL(2, 2, false);
     else if (two_a && two_b)
       OZ2_SHORT(1, 1);
     else if (two_a)
@@ -1089,6 +1114,7 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
     else
       OZ2_SHORT(0, 0);
 #undef OZ2_SHORT
+#undef OZ2_SHORT_ALL
 #undef OZ2_SHORT_V
     if (!bounds) {
       *deferred = fin;
