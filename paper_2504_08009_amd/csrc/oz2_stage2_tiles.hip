@@ -290,14 +290,18 @@ static hipError_t launch_tiles(int tile, const Oz2Plan& plan, const Oz2Layout& l
 // 1030 x 3420 x 38226 2375 / 2236, 17 moduli 1509 x 700 x 53536 2129 / 1981).  The large tiles' time per k-tile is shorter in a launch of
 // three rounds or more, whose workgroups fetch across tiles (17 moduli 1308 x 1848 x 4879 369 / 334, 13 moduli 426 x 5028 x 1066 95.0 / 92.4;
 // two rounds, the second nearly empty: 15 moduli 4375 x 165 x 2233 117 / 123, 10 moduli 2656 x 564 x 1231 64 / 71), but not of a triangular
-// operand's, which have a workgroup per tile (14 moduli, dtrmm of order 1000 with 2700 columns 86.4 / 93.0).
+// operand's, which have a workgroup per tile (14 moduli, dtrmm of order 1000 with 2700 columns 86.4 / 93.0).  The rest of their time is
+// shorter with the residues of short sums, in launches of five rounds or more, nine with one or two k-tiles (15 moduli 3512 x 2177 x 278 111.2 /
+// 100.0, 3122 x 4032 x 257 173 / 162, 12 moduli 3045 x 5324 x 121 164 / 157, 17 moduli 3483 x 1266 x 215 72.4 / 69.5; four rounds, 10 moduli
+// 887 x 4989 x 682 77.3 / 81.0, 14 moduli 706 x 5007 x 80 47.7 / 50.7, five 12 moduli 2410 x 2556 x 90 60.0 / 62.4).
 static int tile_size(int64_t m, int64_t n, int64_t k_pad, int num_moduli, int triangle, int krange, int64_t cus) {
   auto rounds = [&](int64_t tile) { return (tiles_of(tile, m, n, triangle) * num_moduli + cus - 1) / cus; };
   if (rounds(64) <= (k_pad / BK >= kDeepKtiles ? 2 : 1)) return 64;
   const int64_t ktiles = krange == OZ2_KRANGE_ALL ? k_pad / BK : (k_pad / BK + 1) / 2;
   const int64_t per_ktile = 270 + (ktiles < 200 ? 0 : ktiles > 445 ? 35 : (ktiles - 200) / 7);
   const int64_t per_large = krange == OZ2_KRANGE_ALL && rounds(256) > 2 ? 660 : 720;
-  return rounds(128) * (per_ktile * ktiles + 600) + 3000 < rounds(256) * (per_large * ktiles + 4500) ? 128 : 256;
+  const int64_t rest_large = krange == OZ2_KRANGE_ALL && rounds(256) > (ktiles > 2 ? 4 : 8) && k_pad <= OZ2_SHORT_SUM ? 3300 : 4500;
+  return rounds(128) * (per_ktile * ktiles + 600) + 3000 < rounds(256) * (per_large * ktiles + rest_large) ? 128 : 256;
 }
 
 int oz2_products_tile(const Oz2Plan& plan, const Oz2Layout& lay, int64_t m, int64_t n, int64_t kblock, int residue_u8, int triangle,
