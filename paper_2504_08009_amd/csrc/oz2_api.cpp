@@ -732,7 +732,7 @@ int oz2_host_kernel_choice(int call, int64_t m, int64_t n, int64_t k, int num_mo
   oz2_make_layout(m, n, k, num_moduli, u8 ? 1 : 4, &lay);
   const int krange = call == 2 ? OZ2_KRANGE_UPTO_ROW : OZ2_KRANGE_ALL;  // (the rules treat the four ranges alike)
   choice[1] = u8 && call == 0 ? oz2_thin_applies(m, n, *plan, lay, s.kblock, compute_units) : 0;
-  choice[0] = choice[1] ? 0 : oz2_one_pass_vectors(*plan, lay, m % 16 == 0, 0, call == 1, s.shift_mode, call == 0 ? s.bit_split : 0, compute_units);
+  choice[0] = choice[1] ? 0 : oz2_one_pass_vectors(*plan, lay, 1, 0, m % 16 == 0, 0, call == 1, s.shift_mode, call == 0 ? s.bit_split : 0, compute_units);
   choice[2] = choice[1] ? 0 : oz2_products_tile(*plan, lay, m, n, s.kblock, u8, call == 1, krange, compute_units);
   return OZ2_OK;
 }

@@ -129,9 +129,10 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
                              int bit_split, int strassen, const Oz2Layout& lay, char* ws, hipStream_t st,
                              int thin, int* large_two_level, Oz2ScanFinish* deferred);
 // Vectors that a workgroup of the one-pass conversion holds, on a device with that many compute units; 0: separate launches.
-// lines_a / lines_b: sixteen neighbouring vectors of that operand are whole cache lines.
-int oz2_one_pass_vectors(const Oz2Plan& plan, const Oz2Layout& lay, int lines_a, int lines_b, int symmetric, int shift_mode, int bit_split,
-                         int64_t cus);
+// strided_a / strided_b: the vectors of that operand are not contiguous; lines_a / lines_b: and sixteen neighbours of them are whole
+// cache lines.
+int oz2_one_pass_vectors(const Oz2Plan& plan, const Oz2Layout& lay, int strided_a, int strided_b, int lines_a, int lines_b, int symmetric,
+                         int shift_mode, int bit_split, int64_t cus);
 // Strassen form of line 6 (oz2_strassen.hip, oz2_stage2.hip): operand planes, the 7 N products, CRT pass
 hipError_t oz2_launch_strassen_convert(int transa, int transb, int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
                                        const double* B, int64_t ldb, const Oz2Plan& plan, const int* kinds,

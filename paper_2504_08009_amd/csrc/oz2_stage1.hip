@@ -936,15 +936,21 @@ hipError_t launch_convert(const Operand* ops, int nops, const int* kind, bool la
 // 1216 x 280 x 7424 177, 166; not in lines, 14273 vectors 347, 364, 14280 336, 354, 15 moduli both strided 3001 x 2777 x 3500 508, 536;
 // below the lines 12000 x 2000 x 1600 797, 802, 14 moduli 512 x 512 x 8000, both strided 96, 113; half of them 14 moduli
 // 8000 x 8000 x 2400 2227, 2263.  (Under the other shifts the separate launches take longer: 3001 x 2777 x 3500, INT8-product mode, 641, 655.)
-static int short_vectors(int64_t vectors, int64_t in_lines, int64_t k_pad, bool two_level, int64_t cus) {
+// (strided: all strided vectors.)  Where two thirds of the vectors or more are contiguous and the last-level cache does not keep the
+// operands between two readings, the one pass is the better one at every size that fits (first operand transposed where not said, one pass, separate launches): 16 moduli 4096^3 1024, 1049, 14 moduli 6000 x 6000 x 3000 1425, 1510, 16 moduli 8192^3 6743,
+// 6905, 14 moduli 16000 x 300 x 4000 688, 803, 3000 x 3000 x 9000 1153, 1221, 11 moduli 1198 x 3865 x 7761 538, 596; 14 moduli 1000 x 6000 x
+// 5000 as it is 531, 595, dsyrk 5000 x 8000 1324, 1373; half of them 2000 x 2000 x 5000 363, 360, 3000 x 3000 x 5000 682, 701; few 18 moduli
+// 2752 x 656 x 6880 450, 395; smaller, as it is, 13 moduli 597 x 1865 x 5895 222, 208.
+static int short_vectors(int64_t vectors, int64_t strided, int64_t in_lines, int64_t k_pad, bool two_level, int64_t cus) {
   const int64_t elements = vectors * k_pad;
+  const bool contiguous = 3 * strided <= vectors && elements > (int64_t)19 << 20;
   const auto fits = [&](int v) { return k_pad <= short_longest(v); };
   if (k_pad <= 1024) return vectors <= (k_pad <= 256 ? 4 : k_pad <= 512 ? 8 : 12) * cus ? 4 : 8;
   if (two_level && elements > (int64_t)3 << 22) return 0;
   if (2 * in_lines > vectors && in_lines * k_pad > (int64_t)(fits(4) ? 19 : 9) << 20) return 0;
   if (fits(8)) return vectors <= 4 * cus ? 2 : 4;
-  if (fits(4)) return elements > (int64_t)21 << 20 ? 0 : vectors <= 4 * cus || k_pad <= 3392 || two_level ? 2 : 4;
-  return fits(2) && vectors <= 8 * cus ? 2 : 0;
+  if (fits(4)) return elements > (int64_t)21 << 20 && !contiguous ? 0 : vectors <= 4 * cus || k_pad <= 3392 || two_level ? 2 : 4;
+  return fits(2) && (vectors <= 8 * cus || contiguous) ? 2 : 0;
 }
 
 // Residue planes of the one-pass conversion stored through the caches: those that the last-level cache keeps for the products.  Not the
@@ -977,14 +983,15 @@ static bool lines_of_vectors(int strided, const double* X, int64_t ld) {
   return strided && ld % 16 == 0 && reinterpret_cast<uintptr_t>(X) % 128 == 0;
 }
 
-int oz2_one_pass_vectors(const Oz2Plan& plan, const Oz2Layout& lay, int lines_a, int lines_b, int symmetric, int shift_mode, int bit_split,
-                         int64_t cus) {
+int oz2_one_pass_vectors(const Oz2Plan& plan, const Oz2Layout& lay, int strided_a, int strided_b, int lines_a, int lines_b, int symmetric,
+                         int shift_mode, int bit_split, int64_t cus) {
   int param[2];
   shift_params(plan, shift_mode, bit_split, param);
   const int most = 75 - (shift_mode == OZ2_SHIFT_CAUCHY_SCHWARZ ? 1 : 0);
   const int64_t second = symmetric ? 0 : lay.n_pad;
   const int64_t in_lines = shift_mode != OZ2_SHIFT_MAX ? 0 : (lines_a ? lay.m_pad : 0) + (lines_b ? second : 0);
-  return short_vectors(lay.m_pad + second, in_lines, lay.k_pad, param[0] > most || param[1] > most, cus);
+  const int64_t strided = (strided_a ? lay.m_pad : 0) + (strided_b ? second : 0);
+  return short_vectors(lay.m_pad + second, strided, in_lines, lay.k_pad, param[0] > most || param[1] > most, cus);
 }
 
 hipError_t oz2_launch_finish_scan(const Oz2ScanFinish& f, hipStream_t st) {
@@ -1058,8 +1065,8 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
   // GEMM launch turns into the flag word (deferred != nullptr: the caller sees to that).
   const bool two_a = param[0] + base_mode > 75, two_b = param[1] + base_mode > 75;
   const int short_vecs = deferred && !thin && !strassen
-                             ? oz2_one_pass_vectors(plan, lay, lines_of_vectors(ops[0].strided, A, lda), lines_of_vectors(ops[1].strided, B, ldb),
-                                                    nops == 1, shift_mode, d, oz2_gemm_cus())
+                             ? oz2_one_pass_vectors(plan, lay, ops[0].strided, ops[1].strided, lines_of_vectors(ops[0].strided, A, lda),
+                                                    lines_of_vectors(ops[1].strided, B, ldb), nops == 1, shift_mode, d, oz2_gemm_cus())
                              : 0;
   if (short_vecs) {
     ShortJob sj[2] = {};

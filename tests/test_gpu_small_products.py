@@ -598,3 +598,28 @@ def test_thin_products_under_the_other_settings(mode, delta, N, k, ta, tb, first
     # alpha is a power of two and beta doubles: fma(alpha, P, beta C) rounds alpha P + beta C once, as this sum does
     assert np.array_equal(got[np.ix_(rows, cols)], -0.5 * P + 2.0 * sub)
     del ws
+
+
+@pytest.mark.parametrize("mode,k", [(0, 2500), (0, 4928), (1, 4929), (0, 9920), (2, 9919)])
+def test_many_long_contiguous_vectors_in_one_pass(mode, k):
+    """More elements than the last-level cache keeps, in contiguous vectors: one pass.  The same operands stored the other way round take
+    the separate launches; every bit of C is the same, with an infinity too."""
+    m, N = 300, 4
+    n = ((19 << 20) // k // 256 + 1) * 256 - 3
+    gen = torch.Generator(device="cuda").manual_seed(k)
+    At = torch.randn((m, k), dtype=torch.float64, device="cuda", generator=gen)  # columns of the stored k x m matrix: rows of op(A)
+    B = torch.randn((n, k), dtype=torch.float64, device="cuda", generator=gen)
+    A, Bt = At.t().contiguous(), B.t().contiguous()
+    ctx = oz.Context()
+    ctx.set(oz.OZ2_OPT_SHIFT_MODE, mode)
+    ctx.allocate_workspace(m, n, k, N, device="cuda:0")
+    for infinity in (False, True):
+        print("one pass over long vectors: k=%d n=%d mode=%d infinity=%d" % (k, n, mode, infinity), flush=True)
+        if infinity:
+            B[7, k - 1] = Bt[k - 1, 7] = float("inf")
+        C1, C2 = (torch.zeros((n, m), dtype=torch.float64, device="cuda") for _ in range(2))
+        ctx.dgemm("T", "N", m, n, k, 1.0, At.data_ptr(), k, B.data_ptr(), k, 0.0, C1.data_ptr(), m, N)
+        ctx.dgemm("N", "T", m, n, k, 1.0, A.data_ptr(), m, Bt.data_ptr(), n, 0.0, C2.data_ptr(), m, N)
+        torch.cuda.synchronize()
+        assert bool(torch.isinf(C1).any()) == infinity
+        assert torch.equal(C1.view(torch.int64), C2.view(torch.int64))
