@@ -151,3 +151,30 @@ def test_large_tiles_with_few_k_tiles_several_per_workgroup(m, n, N, k, int32):
     got = dC.t()[rows].cpu().numpy()
     assert np.array_equal(got, orc.dgemm(A, B, N, rows=rows).C)
     del ws
+
+
+@pytest.mark.parametrize("m,n", [(1024, 1000), (2048, 2040)])
+@pytest.mark.parametrize("k", [64, 512, 1023, 1024, 1025])
+def test_residues_of_short_sums_in_large_tiles(m, n, k):
+    """Up to 1024 terms the large tiles take the residue from one product with 2^32 / p rounded, whose error grows with the sum: all
+    products of all residues, -128 * -128 included, stored through the caches and past them; the first longer sum too."""
+    mods, _ = oz.get_moduli(N)
+    print("short sums: m=%d n=%d k=%d" % (m, n, k), flush=True)
+    ws = oz.Workspace(m, n, k, N, product_format=oz.OZ2_PRODUCT_RESIDUE_U8)
+    lay = oz.workspace_layout(m, n, k, N)
+    if k >= 512:
+        assert oz.host_kernel_choice(m, n, k, N, torch.cuda.get_device_properties(0).multi_processor_count)[2] == 256
+    lo = np.array([-(p // 2) for p in mods])
+    hi = np.array([(p - 1) // 2 for p in mods])
+    a = np.clip((np.arange(lay["m_pad"]) % 256 - 128)[None, :], lo[:, None], hi[:, None]).astype(np.int8)
+    b = np.clip((np.arange(lay["n_pad"]) * 85 // 256 % 256 - 128)[None, :], lo[:, None], hi[:, None]).astype(np.int8)
+    b[:, :256] = np.clip((np.arange(256) - 128)[None, :], lo[:, None], hi[:, None])
+    _fill(ws, lay, "a_planes", lay["m_pad"], a, k)
+    _fill(ws, lay, "b_planes", lay["n_pad"], b, k)
+    oz.oz2_stage2_gemm(m, n, k, N)
+    torch.cuda.synchronize()
+    got = ws.view(lay["c_planes"], N * lay["n_pad"] * lay["m_pad"], torch.uint8).view(N, lay["n_pad"], lay["m_pad"])
+    for t, p in enumerate(mods):
+        at, bt = (torch.from_numpy(v[t].astype(np.int64)).cuda() for v in (a, b))
+        ref = torch.remainder(k * bt[:n, None] * at[None, :m], p).to(torch.uint8)
+        assert torch.equal(got[t, :n, :m], ref), "modulus %d" % p
