@@ -1145,8 +1145,38 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
   const bool few_and_long = shift_mode != OZ2_SHIFT_MAX && lay.k_pad > line && vectors <= few;
   const bool large = vectors * lay.k_pad > ((int64_t)1 << 25);
   const bool scan = !strassen && !large && !few_and_long;
+  // One operand of strided vectors, one of contiguous ones, more elements than the last-level cache keeps: the contiguous one in one
+  // pass (short_vectors), the scan and the conversion for the other alone, which folds both launches' reports.  Not where the vectors
+  // or the contiguous ones are few, nor with a triangular operand (whole calls, both in two passes / this, us: 14 moduli 3000 x 3000 x 5000
+  // 708 / 677, 6000 x 6000 x 3000 1510 / 1467, 16 moduli 8192 x 8192 x 4096 3749 / 3663, 10 moduli 2920 x 3916 x 3980 560 / 543, 16 moduli
+  // 4096^3 1037 / 1025; 15 moduli 1488 x 1744 x 8976 470 / 489, 10 moduli 1072 x 1040 x 9216 205 / 230, 18 moduli 2752 x 656 x 6880 392 / 402,
+  // dtrmm 4096 x 2048 443 / 461).
+  const int contiguous = nops == 2 && ops[0].strided != ops[1].strided ? (ops[0].strided ? 1 : 0) : -1;
+  const bool split = contiguous >= 0 && 3 * ops[contiguous].nvec_pad >= vectors && !tri_a && !tri_b && shift_mode == OZ2_SHIFT_MAX && !strassen && !thin && !short_vecs && !two_a &&
+                     !two_b && lay.k_pad > short_longest(8) && lay.k_pad <= short_longest(2) && vectors * lay.k_pad > kCachedElements && vectors >= 20 * oz2_gemm_cus();
   if (short_vecs) {
     // (the bound planes exist)
+  } else if (split) {
+    const Operand &c = ops[contiguous], &o = ops[1 - contiguous];
+    const int v = lay.k_pad > short_longest(4) || lay.k_pad <= 3392 || c.nvec_pad <= 4 * oz2_gemm_cus() ? 2 : 4;
+    const unsigned nblk = (unsigned)(c.nvec_pad / v), scans = (unsigned)(o.nvec_pad / kScanVecs);
+    unsigned long long* slots = reinterpret_cast<unsigned long long*>(ws + lay.off_c);
+    const ShortJob sj = {c.X, c.ld, c.nvec, c.nvec_pad, c.k, c.k_pad, c.vmax, c.vaux, c.shifts, c.planes, param[contiguous], 0, 0, nblk, nblk / 8};
+    ShortJob none = sj;
+    none.nblk = none.chunk = 0;
+    const size_t lds = (size_t)v * (lay.k_pad + 4) * sizeof(double);
+    if (v == 2)
+      hipLaunchKernelGGL((short_convert_kernel<0, 0, 2, false>), dim3(8 * sj.chunk), dim3(kShortThreads), lds, st, sj, none, conv, 0, 1, slots);
+    else
+      hipLaunchKernelGGL((short_convert_kernel<0, 0, 4, false>), dim3(8 * sj.chunk), dim3(kShortThreads), lds, st, sj, none, conv, 0, 1, slots);
+    const ScanJob job = {o.X, o.ld, o.nvec, o.nvec_pad, o.k, o.vmax, o.vaux, o.shifts, param[1 - contiguous], o.tri, o.strided ? 1 : 0, scans};
+    ScanJob no_job = job;
+    no_job.nblk = 0;
+    hipLaunchKernelGGL(vector_scan_kernel, dim3(scans), dim3(kScanThreads), 0, st, job, no_job, 0, slots + nblk);
+    fin = {slots, nblk + scans, flag, 0};
+    const int kind[1] = {0};
+    if (hipError_t e = launch_convert(&o, 1, kind, false, conv, fin, st); e != hipSuccess) return e;
+    return hipGetLastError();
   } else if (scan) {
     ScanJob sj[2] = {};
     unsigned total = 0;

@@ -623,3 +623,32 @@ def test_many_long_contiguous_vectors_in_one_pass(mode, k):
         torch.cuda.synchronize()
         assert bool(torch.isinf(C1).any()) == infinity
         assert torch.equal(C1.view(torch.int64), C2.view(torch.int64))
+
+
+@pytest.mark.parametrize("m,n,k", [(3200, 3000, 4928), (3000, 2900, 4929), (2600, 2500, 9920), (9000, 5000, 2500)])
+def test_one_operand_in_one_pass_and_the_other_in_two(m, n, k):
+    """Strided vectors of one operand, contiguous ones of the other, more elements than the last-level cache keeps: bit for bit what the
+    operands give stored the other way round, with an infinity in either of them too."""
+    N = 4
+    gen = torch.Generator(device="cuda").manual_seed(k)
+    A = torch.randn((k, m), dtype=torch.float64, device="cuda", generator=gen)
+    B = torch.randn((n, k), dtype=torch.float64, device="cuda", generator=gen)
+    assert (m + n) * k > 190 << 17 and m + n >= 20 * 250
+    ctx = oz.Context()
+    ctx.allocate_workspace(m, n, k, N, device="cuda:0")
+    for infinite in ("none", "A", "B"):
+        print("one operand in one pass: m=%d n=%d k=%d infinite=%s" % (m, n, k, infinite), flush=True)
+        X, Y = A.clone(), B.clone()
+        if infinite == "A":
+            X[k - 1, m - 1] = float("inf")
+        if infinite == "B":
+            Y[n - 1, 0] = float("-inf")
+        got = []
+        for ta, tb in (("N", "N"), ("T", "T"), ("T", "N")):
+            x, y = (X if ta == "N" else X.t().contiguous()), (Y if tb == "N" else Y.t().contiguous())
+            C = torch.zeros((n, m), dtype=torch.float64, device="cuda")
+            ctx.dgemm(ta, tb, m, n, k, 1.0, x.data_ptr(), x.shape[1], y.data_ptr(), y.shape[1], 0.0, C.data_ptr(), m, N)
+            torch.cuda.synchronize()
+            got.append(C)
+        assert bool(torch.isinf(got[0]).any()) == (infinite != "none")
+        assert all(torch.equal(got[0].view(torch.int64), c.view(torch.int64)) for c in got[1:])
