@@ -17,6 +17,7 @@
 #include <type_traits>
 
 #include "oz2_math.h"
+#include "oz2_bound.h"
 #include "oz2_scan_finish.h"
 #include "oz2_warm.h"
 
@@ -26,8 +27,7 @@ constexpr int kThreads = 256;
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
 
-__global__ void __launch_bounds__(kThreads) fill_u64_kernel(unsigned long long* p, int64_t count, const Oz2ScanFinish fin) {
-  if (fin.slots != nullptr && blockIdx.x == 0) finish_scan(fin);
+__global__ void __launch_bounds__(kThreads) fill_u64_kernel(unsigned long long* p, int64_t count) {
   int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (i < count) p[i] = 0ull;
 }
@@ -263,7 +263,7 @@ struct ScanJob {
   const double* X;
   int64_t ld, nvec, nvec_pad, k;
   unsigned long long* vmax;
-  unsigned long long* vnorm;  // norm bounds (mode 1)
+  unsigned long long* vnorm;  // norm bounds (mode 1), else cleared (the INT8-product mode gathers its maxima there)
   int* shifts;
   int param;  // as in ShiftJob
   int tri, strided;
@@ -369,7 +369,7 @@ __global__ void __launch_bounds__(kScanThreads) vector_scan_kernel(const ScanJob
     const int64_t v = v0 + threadIdx.x;
     if (v < j.nvec_pad) {
       j.vmax[v] = mx;
-      if (mode == 1) j.vnorm[v] = norm;
+      j.vnorm[v] = norm;
       j.shifts[v] = shift_of(mx, norm, mode, j.param, 0);
     }
     bad = mx >= kInfBits;
@@ -637,7 +637,7 @@ struct ShortJob {
   const double* X;
   int64_t ld, nvec, nvec_pad, k, k_pad;
   unsigned long long* vmax;
-  unsigned long long* vnorm;  // norm bounds (mode 1), which are the reports too
+  unsigned long long* vnorm;  // norm bounds (mode 1), which are the reports too; KIND 2: cleared
   int* shifts;
   int8_t* planes;
   int param;  // as in ShiftJob
@@ -750,6 +750,7 @@ __device__ __forceinline__ void convert_short(const ShortJob& j, const Oz2ConvCo
   const int shift = shift_of(mx, norm, KIND == 2 ? 0 : mode, j.param, 0);
   if (wv == 0 && side == 0 && (lane & 7) == 0) {
     j.vmax[v0 + v] = mx;
+    if (KIND == 2) j.vnorm[v0 + v] = 0ull;
     if (KIND != 2 && mode == 1) j.vnorm[v0 + v] = mx >= kInfBits ? kBadReport : norm;
     j.shifts[v0 + v] = shift;
   }
@@ -1044,8 +1045,8 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
   const int64_t n_max = nops == 2 ? lay.m_pad + 32 + lay.n_pad : lay.m_pad + 32;
   const int64_t n_aux = nops == 2 ? lay.m_pad + lay.n_pad : lay.m_pad;
   const Oz2ScanFinish nothing = {nullptr, 0u, nullptr, 0};
-  auto fill = [&](unsigned long long* p, int64_t count, const Oz2ScanFinish& f) {
-    hipLaunchKernelGGL(fill_u64_kernel, dim3(blocks_of(count, kThreads)), thr, 0, st, p, count, f);
+  auto fill = [&](unsigned long long* p, int64_t count) {
+    hipLaunchKernelGGL(fill_u64_kernel, dim3(blocks_of(count, kThreads)), thr, 0, st, p, count);
   };
   auto shifts = [&](int mode, int param_a, int param_b, int off_a, int off_b) {
     const ShiftJob ja = {ops[0].vmax, ops[0].vaux, ops[0].shifts, ops[0].nvec_pad, param_a, off_a};
@@ -1079,9 +1080,12 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
       groups += nblk;
     }
     // The reports live in the auxiliary vectors: a word per two vectors or more, or, in the Cauchy-Schwarz mode, whose norm bounds
-    // belong there, a word per vector; in the INT8-product mode in the product region until the next launch has folded them.
+    // belong there, a word per vector; in the INT8-product mode, whose auxiliary vectors are cleared for the product's maxima, in plane 1 of the
+    // operand with more vectors, which the launch after the bound product writes (at least 64 bytes per vector, two moduli at least).
     const bool bounds = shift_mode == OZ2_SHIFT_INT8_PRODUCT;
-    unsigned long long* slots = bounds ? reinterpret_cast<unsigned long long*>(ws + lay.off_c) : ops[0].vaux;
+    const Operand& most = ops[nops == 2 && lay.n_pad > lay.m_pad ? 1 : 0];
+    unsigned long long* slots =
+        bounds ? reinterpret_cast<unsigned long long*>(most.planes + (size_t)most.nvec_pad * most.k_pad) : ops[0].vaux;
     // (Inputs with an infinity or a NaN skip their products, except short ones of short vectors: there the look at the reports would
     // cost up to 6 % of a finite call, Cauchy-Schwarz mode 500^3 22.2 -> 23.5 us.)
     fin = {slots, base_mode == 1 ? (unsigned)vectors : groups, flag, lay.k_pad > 1024};
@@ -1192,10 +1196,10 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
     hipLaunchKernelGGL(vector_scan_kernel, dim3(total), dim3(kScanThreads), 0, st, sj[0], sj[1], base_mode, slots);
     fin = {slots, total, flag, 0};
   } else {
-    fill(ops[0].vmax, n_max, nothing);
+    fill(ops[0].vmax, n_max);
     if (hipError_t e = launch_max(ops, nops, st); e != hipSuccess) return e;
     if (base_mode == 1) {
-      fill(ops[0].vaux, n_aux, nothing);
+      fill(ops[0].vaux, n_aux);
       for (int x = 0; x < nops; ++x) launch_norm(ops[x], st);
     }
     shifts(base_mode, param[0], param[1], 0, 0);
@@ -1208,18 +1212,25 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
       const int bound[2] = {2, 2};
       if (hipError_t e = launch_convert(ops, nops, bound, false, conv, fin, st); e != hipSuccess) return e;
       fin = nothing;
+      if (!scan) fill(ops[0].vaux, n_aux);
     }
-    fill(ops[0].vaux, n_aux, fin);
-    fin = nothing;
-    hipError_t e = oz2_launch_bound_gemm(lay, ws, B == nullptr, st);
-    if (e != hipSuccess) return e;
-    const int64_t row_blocks = (lay.m_pad + kProdRows - 1) / kProdRows;
-    int cols = 8;  // as few as leave a row 128 atomic maxima or fewer
-    while (cols < 64 && (n + cols - 1) / cols > 128) cols *= 2;
-    const int64_t nblk = row_blocks * (int64_t)blocks_of(n, cols);
-    if (nblk >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(prodmax_kernel, dim3((unsigned)nblk), thr, 0, st, reinterpret_cast<const int*>(ws + lay.off_c),
-                       lay.m_pad, m, n, row_blocks, cols, ops[0].vaux, ops[1].vaux);
+    const int tile = oz2_bound_tile(lay, m, n, B == nullptr, oz2_gemm_cus());
+    if (tile != 256) {
+      if (hipError_t e = oz2_launch_bound_maxima(tile, lay, ws, m, n, B == nullptr, fin, st); e != hipSuccess) return e;
+      fin = nothing;
+    } else {
+      if (fin.slots)
+        if (hipError_t e = oz2_launch_finish_scan(fin, st); e != hipSuccess) return e;
+      fin = nothing;
+      if (hipError_t e = oz2_launch_bound_gemm(lay, ws, B == nullptr, st); e != hipSuccess) return e;
+      const int64_t row_blocks = (lay.m_pad + kProdRows - 1) / kProdRows;
+      int cols = 8;  // as few as leave a row 128 atomic maxima or fewer
+      while (cols < 64 && (n + cols - 1) / cols > 128) cols *= 2;
+      const int64_t nblk = row_blocks * (int64_t)blocks_of(n, cols);
+      if (nblk >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+      hipLaunchKernelGGL(prodmax_kernel, dim3((unsigned)nblk), thr, 0, st, reinterpret_cast<const int*>(ws + lay.off_c),
+                         lay.m_pad, m, n, row_blocks, cols, ops[0].vaux, ops[1].vaux);
+    }
     shifts(2, plan.budget2, plan.budget2, -d, d);
     xbits[0] = plan.budget2 / 2 + 7 - d;  // |x'| < 2^(e + 1 + sa) <= 2^(floor(b/2) + 6 -+ d)
     xbits[1] = plan.budget2 / 2 + 7 + d;

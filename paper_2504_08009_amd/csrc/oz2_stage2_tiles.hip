@@ -12,6 +12,7 @@
 // loads NS - 1 ahead; the other workgroups of the compute unit work while one waits for its first copies or stores its
 // residues.  256 registers per lane or less: the accumulators are ordinary registers (build.py builds this file with
 // -amdgpu-mfma-vgpr-form), so the epilogue reads them directly.
+#include "oz2_bound.h"
 #include "oz2_gemm.h"
 #include "oz2_scan_finish.h"
 #include "oz2_warm.h"
@@ -42,13 +43,16 @@ struct TileArgs {
 };
 
 // MI x NI MFMA tiles of 32 x 32 per wave, NS stages, WGS workgroups per compute unit; WARM: a launch of few workgroups
-template <int MI, int NI, int NS, int WGS, bool WARM>
+// MAXIMA: the one product of the bound planes of the INT8-product mode (Section 4.1).  Only its row and column maxima are wanted: they
+// are gathered here (c holds the words of the rows, then those of the columns, zero before the launch; the rows' for both where the
+// product is symmetric), and the INT32 product, 4 bytes an element written and read again, does not exist.
+template <int MI, int NI, int NS, int WGS, bool WARM, bool MAXIMA>
 __global__ void __launch_bounds__(kThreads, WGS) gemm_i8_tile_kernel(const TileArgs g) {
   constexpr int TM = 64 * MI, TN = 64 * NI;
   constexpr int kStage = (TM + TN) * BK;
   constexpr int kLoadsA = MI, kLoadsB = NI, kLoads = kLoadsA + kLoadsB;  // direct loads of 1 KiB per wave and k-tile
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  if constexpr (WARM) warm_arguments(g);
+  if constexpr (WARM && !MAXIMA) warm_arguments(g);
 
   if (g.skip_flag != nullptr && *g.skip_flag != 0ull) return;
   if (g.fin.slots != nullptr && !g.fin_stops && blockIdx.x == 0) finish_scan(g.fin);
@@ -106,7 +110,7 @@ __global__ void __launch_bounds__(kThreads, WGS) gemm_i8_tile_kernel(const TileA
 #pragma unroll
     for (int y = 0; y < NI; ++y)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[x][y][e] = (int)OZ2_ACC_START;
+      for (int e = 0; e < 16; ++e) acc[x][y][e] = MAXIMA ? 0 : (int)OZ2_ACC_START;
   if (g.fin_stops) fetch_reports(g.fin, lds_base + (NS - 1) * kStage, wv, lane);  // into the stage that the loop fills first
   // (beyond the last k-tile the first one is fetched again: every wait counts on the same number of copies in flight)
 #pragma unroll
@@ -146,6 +150,57 @@ __global__ void __launch_bounds__(kThreads, WGS) gemm_i8_tile_kernel(const TileA
     stage = stage + 1 == NS ? 0 : stage + 1;
   }
 
+  if constexpr (MAXIMA) {
+    wait_vmcnt<0>();
+    __syncthreads();  // the stages are free
+    int* const row_top = reinterpret_cast<int*>(lds);  // [wn][TM], [wm][TN]
+    int* const col_top = row_top + 2 * TM;
+#pragma unroll
+    for (int y = 0; y < NI; ++y) {
+      int top = 0;  // (bounds are not negative)
+#pragma unroll
+      for (int x = 0; x < MI; ++x)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) top = max(top, acc[x][y][e]);
+      top = max(top, __shfl_xor(top, 32, 64));
+      if (half == 0) col_top[wm * TN + wn * (TN / 2) + y * 32 + lane] = top;
+    }
+#pragma unroll
+    for (int x = 0; x < MI; ++x) {
+      int top[16];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        top[e] = acc[x][0][e];
+#pragma unroll
+        for (int y = 1; y < NI; ++y) top[e] = max(top[e], acc[x][y][e]);
+      }
+      // sixteen rows over 32 lanes: every step halves the rows that a lane keeps
+#pragma unroll
+      for (int keep = 8, bit = 1; keep >= 1; keep /= 2, bit *= 2)
+#pragma unroll
+        for (int q = 0; q < keep; ++q) {
+          const bool upper = (lane & bit) != 0;
+          const int mine = upper ? top[q + keep] : top[q], other = upper ? top[q] : top[q + keep];
+          top[q] = max(mine, __shfl_xor(other, bit, 64));
+        }
+      top[0] = max(top[0], __shfl_xor(top[0], 16, 64));
+      const int e = ((lane & 1) << 3) | ((lane & 2) << 1) | ((lane & 4) >> 1) | ((lane & 8) >> 3);
+      if ((lane & 16) == 0) row_top[wn * TM + wm * (TM / 2) + x * 32 + 8 * (e >> 2) + 4 * half + (e & 3)] = top[0];
+    }
+    __syncthreads();
+    unsigned long long* const tops = reinterpret_cast<unsigned long long*>(g.c);
+    static_assert(TM + TN <= kThreads, "a thread for every row and column");
+    const int q = (int)threadIdx.x - TM;
+    if (q < 0) {
+      const int top = max(row_top[threadIdx.x], row_top[TM + threadIdx.x]);
+      if (top > 0) atomicMax(tops + (size_t)tm * TM + threadIdx.x, (unsigned long long)top);
+    } else if (q < TN) {
+      const int top = max(col_top[q], col_top[TN + q]);
+      if (top > 0) atomicMax(tops + (g.triangle != 0 ? 0 : g.m_pad) + (size_t)tn * TN + q, (unsigned long long)top);
+    }
+    return;
+  }
+
   // Algorithm 1 line 7 (see the large kernel): four consecutive registers are four consecutive rows of a column
   uint8_t* const corner = g.c + ((size_t)t * g.n_pad + (size_t)tn * TN + wn * (TN / 2)) * g.m_pad + (size_t)tm * TM + wm * (TM / 2);
   const unsigned lane_off = (lane & 31u) * (unsigned)g.m_pad + 16u * (lane >> 5);
@@ -173,14 +228,14 @@ __global__ void __launch_bounds__(kThreads, WGS) gemm_i8_tile_kernel(const TileA
 template <int MI, int NI, int NS>
 constexpr int kTileLds = NS * 64 * (MI + NI) * BK;
 
-template <int MI, int NI, int NS, int WGS, bool WARM>
+template <int MI, int NI, int NS, int WGS, bool WARM, bool MAXIMA = false>
 hipError_t set_lds() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_i8_tile_kernel<MI, NI, NS, WGS, WARM>),
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_i8_tile_kernel<MI, NI, NS, WGS, WARM, MAXIMA>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, kTileLds<MI, NI, NS>);
 }
 
 // flag: the flag word when the products are not needed once it is set, else null
-template <int MI, int NI, int NS, int WGS, bool WARM>
+template <int MI, int NI, int NS, int WGS, bool WARM, bool MAXIMA = false>
 hipError_t launch(TileArgs& g, int64_t m, int64_t n, int planes, const unsigned long long* flag, hipStream_t st) {
   constexpr int TM = 64 * MI, TN = 64 * NI;
   g.tiles_m = (int)((m + TM - 1) / TM);
@@ -212,7 +267,7 @@ hipError_t launch(TileArgs& g, int64_t m, int64_t n, int planes, const unsigned 
       g.skip_flag = flag;
     }
   }
-  hipLaunchKernelGGL((gemm_i8_tile_kernel<MI, NI, NS, WGS, WARM>), dim3((unsigned)g.chunk * 8), dim3(kThreads),
+  hipLaunchKernelGGL((gemm_i8_tile_kernel<MI, NI, NS, WGS, WARM, MAXIMA>), dim3((unsigned)g.chunk * 8), dim3(kThreads),
                      (kTileLds<MI, NI, NS>), st, g);
   return hipGetLastError();
 }
@@ -240,7 +295,12 @@ hipError_t oz2_gemm_tiles_setup() {
   if (e == hipSuccess) e = set_lds<OZ2_TILE_64>();
   if (e == hipSuccess) e = set_lds<OZ2_TILE_64_ONE>();
   if (e == hipSuccess) e = set_lds<OZ2_TILE_64_TWO>();
-  return e == hipSuccess ? set_lds<OZ2_TILE_128_ONE>() : e;
+  if (e == hipSuccess) e = set_lds<OZ2_TILE_128_ONE>();
+  if (e == hipSuccess) e = set_lds<OZ2_TILE_128, true>();
+  if (e == hipSuccess) e = set_lds<OZ2_TILE_64, true>();
+  if (e == hipSuccess) e = set_lds<OZ2_TILE_64_ONE, true>();
+  if (e == hipSuccess) e = set_lds<OZ2_TILE_64_TWO, true>();
+  return e == hipSuccess ? set_lds<OZ2_TILE_128_ONE, true>() : e;
 }
 
 static hipError_t launch_tiles(int tile, const Oz2Plan& plan, const Oz2Layout& lay, char* ws, int64_t m, int64_t n, int triangle,
@@ -317,6 +377,44 @@ hipError_t oz2_launch_products(const Oz2Plan& plan, const Oz2Layout& lay, char* 
   const int tile = oz2_products_tile(plan, lay, m, n, kblock, residue_u8, triangle, krange, oz2_gemm_cus());
   if (tile == 256) return oz2_launch_stage2(plan, lay, ws, kblock, residue_u8, triangle, krange, check_flag, fin, st);
   return launch_tiles(tile, plan, lay, ws, m, n, triangle, krange, check_flag != 0, fin, st);
+}
+
+// The product of the bound planes, for its row and column maxima.  The smaller tiles wherever they are estimated to take no longer than
+// the large ones with their INT32 product, 8 bytes an element, and the launch that reads it
+// (15 moduli 3001 x 2777 x 3500 606 -> 580 us a call, where 132 large tiles left half of the chip idle).
+int oz2_bound_tile(const Oz2Layout& lay, int64_t m, int64_t n, bool symmetric, int64_t cus) {
+  if (lay.m_pad >= ((int64_t)1 << 27) || (symmetric && lay.m_pad != lay.n_pad)) return 256;
+  auto rounds = [&](int64_t tile, bool triangle) { return (tiles_of(tile, m, n, triangle) + cus - 1) / cus; };
+  const int64_t ktiles = lay.k_pad / BK;
+  if (rounds(64, symmetric) <= (ktiles >= kDeepKtiles ? 2 : 1)) return 64;
+  const int64_t per_ktile = 270 + (ktiles < 200 ? 0 : ktiles > 445 ? 35 : (ktiles - 200) / 7);
+  const int64_t small = rounds(128, symmetric) * (per_ktile * ktiles + 600) + 3000;
+  const int64_t large = rounds(256, false) * ((rounds(256, false) > 2 ? 660 : 720) * ktiles + 4500) + lay.m_pad * lay.n_pad / 500 + 5000;
+  return small < large ? 128 : 256;
+}
+
+hipError_t oz2_launch_bound_maxima(int tile, const Oz2Layout& lay, char* ws, int64_t m, int64_t n, bool symmetric,
+                                   const Oz2ScanFinish& fin, hipStream_t st) {
+  TileArgs g = {};
+  g.a = reinterpret_cast<const int8_t*>(ws + lay.off_a);
+  g.b = reinterpret_cast<const int8_t*>(ws + (symmetric ? lay.off_a : lay.off_b));
+  g.c = reinterpret_cast<uint8_t*>(ws + lay.off_rownorm);
+  g.m_pad = lay.m_pad;
+  g.n_pad = lay.n_pad;
+  g.k_pad = lay.k_pad;
+  g.ktiles = (int)(lay.k_pad / BK);
+  g.triangle = symmetric ? 1 : 0;
+  g.krange = OZ2_KRANGE_ALL;
+  g.fin = fin;
+  const int64_t total = tiles_of(tile, m, n, g.triangle), cus = oz2_gemm_cus();
+  const bool deep = g.ktiles >= kDeepKtiles;
+  if (tile == 64) {
+    if (deep && total <= cus) return launch<OZ2_TILE_64_ONE, true>(g, m, n, 1, nullptr, st);
+    if (deep && total <= 2 * cus) return launch<OZ2_TILE_64_TWO, true>(g, m, n, 1, nullptr, st);
+    return launch<OZ2_TILE_64, true>(g, m, n, 1, nullptr, st);
+  }
+  if (deep && total <= cus) return launch<OZ2_TILE_128_ONE, true>(g, m, n, 1, nullptr, st);
+  return launch<OZ2_TILE_128, true>(g, m, n, 1, nullptr, st);
 }
 
 void oz2_host_product_residues_impl(int p, int64_t count, const int32_t* products, uint8_t* out) {

@@ -658,6 +658,13 @@ def test_int8_product_mode_all_stages(m, n, k, N, phi):
     check_against_oracle(A, B, N, mode=2)
 
 
+@pytest.mark.parametrize("m,n,k,N", [(64, 64, 64, 3), (65, 129, 65, 2), (128, 193, 1600, 2), (300, 700, 40, 2), (1100, 1030, 70, 2)])
+def test_int8_product_maxima_at_the_edges_of_tiles(m, n, k, N):
+    """Row and column maxima gathered by tiles of 64 and 128, one to many of them: shifts and all that follows."""
+    rng = np.random.default_rng(m + n + k)
+    check_against_oracle(rng.standard_normal((m, k)), rng.standard_normal((k, n)), N, mode=2)
+
+
 def test_int8_product_mode_full_size_c3_sampled_and_transposed():
     # the shifts depend on all rows and columns; both operands are handed over transposed, so each is read
     # by the stage-1 kernels of the other orientation
