@@ -330,11 +330,22 @@ int oz2_set_round_sync(int spins);
  * No GPU is touched.
  *   call: 0: oz2_dgemm; 1: oz2_dsyrk (m == n); 2: oz2_dtrmm (k the order of A); nothing transposed, A from the
  *         left, its leading dimension m and its address a multiple of 128
- *   choice[0]: vectors that a workgroup of the one-pass conversion holds (2, 4 or 8), 0: separate launches
+ *   choice[0]: vectors that a workgroup of the one-pass conversion of both operands holds (2, 4 or 8), 0: separate launches for
+ *         one of them at least
  *   choice[1]: 1 / 2: thin product whose first / second operand is the large one, 0: not
  *   choice[2]: edge of the tiles of the products (64, 128 or 256), 0 for a thin product
  * m, n, k >= 1.  Returns 0 or a negative argument code. */
 int oz2_host_kernel_choice(int call, int64_t m, int64_t n, int64_t k, int num_moduli, int compute_units, int choice[3]);
+
+/* What oz2_host_kernel_choice does not tell, with the operands' orientations (transb is that of oz2_dgemm alone; leading dimensions
+ * as small as they can be, addresses multiples of 128; oz2_dtrmm has A on the left where k is m).
+ *   route[0]: operands converted in one pass: 0: none, 1: the first, 2: the second, 3: both
+ *   route[1]: 1: both, and their residues stored through the caches, 0: past them, or not in one pass
+ *   route[2]: edge of the tiles of the product of bounds of the INT8-product mode: 64 or 128, which gather its maxima, or 256, which store
+ *         the product for another launch to read; 0 in the other modes
+ *   route[3]: lines 8-11: 0: in one launch with the FP64 fallback, 1: in a launch of their own, 2: line 9 on the matrix cores
+ * Returns 0 or a negative argument code. */
+int oz2_host_route(int call, char transa, char transb, int64_t m, int64_t n, int64_t k, int num_moduli, int compute_units, int route[4]);
 
 /* Host-side evaluation of the device routine for lines 7-10 and the final rounding (same source,
  * compiled for the host), for unit tests of the exact-arithmetic design: given the num_moduli INT32

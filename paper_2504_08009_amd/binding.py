@@ -12,7 +12,7 @@ SYMBOLS = [
     "oz2_set_gemm_algorithm", "oz2_gemm_algorithm_for", "oz2_workspace_bytes_strassen", "oz2_workspace_bytes_preferred",
     "oz2_context_create", "oz2_context_destroy", "oz2_context_set_workspace", "oz2_context_set", "oz2_context_get",
     "oz2_context_workspace_bytes", "oz2_context_dgemm", "oz2_context_dsyrk", "oz2_context_dtrmm",
-    "oz2_set_kblock", "oz2_set_round_sync", "oz2_set_shift_mode", "oz2_set_product_format", "oz2_set_bit_split", "oz2_set_nonfinite_check", "oz2_set_stage_events", "oz2_calibrate_mfma", "oz2_host_kernel_choice", "oz2_host_crt_element", "oz2_host_crt_element_digits", "oz2_host_crt_element_wide_digits", "oz2_host_residues", "oz2_host_product_residues", "oz2_host_short_product_residues", "oz2_status_string",
+    "oz2_set_kblock", "oz2_set_round_sync", "oz2_set_shift_mode", "oz2_set_product_format", "oz2_set_bit_split", "oz2_set_nonfinite_check", "oz2_set_stage_events", "oz2_calibrate_mfma", "oz2_host_kernel_choice", "oz2_host_route", "oz2_host_crt_element", "oz2_host_crt_element_digits", "oz2_host_crt_element_wide_digits", "oz2_host_residues", "oz2_host_product_residues", "oz2_host_short_product_residues", "oz2_status_string",
 ]
 
 
@@ -76,6 +76,7 @@ def lib():
         L.oz2_host_crt_element_digits.argtypes = [ci, vp, vp]
         L.oz2_host_crt_element_wide_digits.argtypes = [ci, vp, vp]
         L.oz2_host_kernel_choice.argtypes = [ci, i64, i64, i64, ci, ci, vp]
+        L.oz2_host_route.argtypes = [ci, ctypes.c_char, ctypes.c_char, i64, i64, i64, ci, ci, vp]
         L.oz2_host_residues.argtypes = [ci, ci, ctypes.c_double, ci, vp]
         L.oz2_host_product_residues.argtypes = [ci, i64, vp, vp]
         L.oz2_host_short_product_residues.argtypes = [ci, i64, vp, vp]
@@ -271,6 +272,14 @@ def host_kernel_choice(m, n, k, num_moduli, compute_units, call="dgemm"):
     out = (ctypes.c_int * 3)()
     _check(lib().oz2_host_kernel_choice(("dgemm", "dsyrk", "dtrmm").index(call), m, n, k, num_moduli, compute_units, out),
            "oz2_host_kernel_choice")
+    return tuple(out)
+
+
+def host_route(m, n, k, num_moduli, compute_units, call="dgemm", ta="N", tb="N"):
+    """(operands in one pass, residues through the caches, edge of the bound tiles, kernel of lines 8-11) of a call."""
+    out = (ctypes.c_int * 4)()
+    _check(lib().oz2_host_route(("dgemm", "dsyrk", "dtrmm").index(call), ta.encode(), tb.encode(), m, n, k, num_moduli, compute_units, out),
+           "oz2_host_route")
     return tuple(out)
 
 

@@ -3,7 +3,9 @@
 #include <new>
 
 #include "../../include/oz2.h"
+#include "oz2_bound.h"
 #include "oz2_internal.h"
+#include "oz2_route.h"
 
 namespace {
 
@@ -395,6 +397,13 @@ int trans_code(char c) {
 }  // namespace
 
 namespace {
+// Below 2^24 elements of C the blocks of the fallback ride in the launch of stage 3 (above, its registers cost more than the launch: 10
+// moduli 4096 x 4096 x 300 164 us, apart 155): one launch less (whole calls, us: 2200 x 2200 x 500 103 -> 98, 3000 x 3000 x 1000 224 -> 220, 18
+// moduli 3001 x 2777 x 3500 674 -> 667), and with its smaller tiles the fallback itself is the faster one (1024^3 612 -> 277, 4000^3 7770 -> 5430).
+bool fallback_in_stage3(const State& s, int64_t m, int64_t n) {
+  return s.nonfinite_check && s.product_format == OZ2_PRODUCT_RESIDUE_U8 && m * n < ((int64_t)1 << 24);
+}
+
 // The general product on the registered workspace (static_ws == false) or on the library's static buffer.
 int dgemm_ex_impl(bool static_ws, char transa, char transb, int64_t m, int64_t n, int64_t k, double alpha, const double* A,
                   int64_t lda, const double* B, int64_t ldb, double beta, double* C, int64_t ldc, int num_moduli,
@@ -456,11 +465,7 @@ int dgemm_ex_impl(bool static_ws, char transa, char transb, int64_t m, int64_t n
                     : oz2_launch_products(*plan, lay, ws, m, n, s.kblock, s.product_format, 0, OZ2_KRANGE_ALL,
                                           s.nonfinite_check, fin, st);
     if (e != hipSuccess || !mark(2)) return OZ2_ERR_HIP;
-    // below 2^24 elements of C the blocks of the fallback ride in the launch of stage 3 (above, its registers cost more than the launch: 10
-    // moduli 4096 x 4096 x 300 164 us, apart 155): one launch less (whole calls, us: 2200 x 2200 x 500 103 -> 98, 3000 x 3000 x 1000 224 -> 220, 18 moduli
-    // 3001 x 2777 x 3500 674 -> 667), and with its smaller tiles the fallback itself is the faster one (1024^3 612 -> 277,
-    // 4000^3 7770 -> 5430)
-    if (s.nonfinite_check && s.product_format == OZ2_PRODUCT_RESIDUE_U8 && m * n < ((int64_t)1 << 24)) {
+    if (fallback_in_stage3(s, m, n)) {
       if (oz2_launch_stage3_or_fallback(ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, *plan, lay, ws, st) !=
               hipSuccess ||
           !mark(3))
@@ -714,7 +719,9 @@ int oz2_calibrate_mfma(int workgroups, int iters, int random_operands, int* sink
   return e == hipSuccess ? OZ2_OK : OZ2_ERR_HIP;
 }
 
-int oz2_host_kernel_choice(int call, int64_t m, int64_t n, int64_t k, int num_moduli, int compute_units, int choice[3]) {
+namespace {
+// What the two hooks below need of a call: the arguments checked, the plan and the layout.
+int host_call(State& s, int call, int64_t m, int64_t n, int64_t k, int num_moduli, int compute_units, const Oz2Plan** plan, Oz2Layout* lay) {
   if (call < 0 || call > 2) return -1;
   if (m < 1) return -2;
   if (n < 1 || (call == 1 && n != m)) return -3;
@@ -722,18 +729,50 @@ int oz2_host_kernel_choice(int call, int64_t m, int64_t n, int64_t k, int num_mo
   if (!dims_ok(m, n, k)) return -2;
   if (!n_ok(num_moduli)) return -5;
   if (compute_units < 1) return -6;
-  if (!choice) return -7;
+  if (get_plan(s, num_moduli, k, plan) < 0) return -5;
+  oz2_make_layout(m, n, k, num_moduli, s.product_format == OZ2_PRODUCT_RESIDUE_U8 ? 1 : 4, lay);
+  return OZ2_OK;
+}
+}  // namespace
+
+int oz2_host_kernel_choice(int call, int64_t m, int64_t n, int64_t k, int num_moduli, int compute_units, int choice[3]) {
   State& s = state();
   std::lock_guard<std::mutex> lock(s.mu);
   const Oz2Plan* plan;
-  if (get_plan(s, num_moduli, k, &plan) < 0) return -5;
   Oz2Layout lay;
+  if (const int rc = host_call(s, call, m, n, k, num_moduli, compute_units, &plan, &lay); rc != OZ2_OK) return rc;
+  if (!choice) return -7;
   const int u8 = s.product_format == OZ2_PRODUCT_RESIDUE_U8;
-  oz2_make_layout(m, n, k, num_moduli, u8 ? 1 : 4, &lay);
   const int krange = call == 2 ? OZ2_KRANGE_UPTO_ROW : OZ2_KRANGE_ALL;  // (the rules treat the four ranges alike)
   choice[1] = u8 && call == 0 ? oz2_thin_applies(m, n, *plan, lay, s.kblock, compute_units) : 0;
   choice[0] = choice[1] ? 0 : oz2_one_pass_vectors(*plan, lay, 1, 0, m % 16 == 0, 0, call == 1, s.shift_mode, call == 0 ? s.bit_split : 0, compute_units);
   choice[2] = choice[1] ? 0 : oz2_products_tile(*plan, lay, m, n, s.kblock, u8, call == 1, krange, compute_units);
+  return OZ2_OK;
+}
+
+int oz2_host_route(int call, char transa, char transb, int64_t m, int64_t n, int64_t k, int num_moduli, int compute_units, int route[4]) {
+  const int ta = trans_code(transa), tb = trans_code(transb);
+  if (ta < 0) return -2;
+  if (tb < 0) return -3;
+  State& s = state();
+  std::lock_guard<std::mutex> lock(s.mu);
+  const Oz2Plan* plan;
+  Oz2Layout lay;
+  const int rc = host_call(s, call, m, n, k, num_moduli, compute_units, &plan, &lay);
+  if (rc != OZ2_OK) return rc == -1 ? -1 : rc - 2;
+  if (!route) return -9;
+  // dtrmm: A from the left where k is m, else from the right, where it is the second operand
+  const bool right = call == 2 && k != m, symmetric = call == 1;
+  const int strided_a = right ? 1 : !ta, strided_b = right ? ta : call == 0 ? tb : 0;
+  const int lines_a = strided_a && m % 16 == 0, lines_b = strided_b && n % 16 == 0;
+  const int u8 = s.product_format == OZ2_PRODUCT_RESIDUE_U8, split = call == 0 ? s.bit_split : 0;
+  const int thin = u8 && call == 0 ? oz2_thin_applies(m, n, *plan, lay, s.kblock, compute_units) : 0;
+  const bool both = !thin && oz2_one_pass_vectors(*plan, lay, strided_a, strided_b, lines_a, lines_b, symmetric, s.shift_mode, split, compute_units);
+  const bool bounds = s.shift_mode == OZ2_SHIFT_INT8_PRODUCT;
+  route[0] = both ? 3 : thin ? 0 : oz2_one_pass_operand(*plan, lay, strided_a, strided_b, call == 2, symmetric, s.shift_mode, split, compute_units);
+  route[1] = both && !bounds && oz2_planes_through_caches(num_moduli, lay, symmetric);
+  route[2] = bounds ? oz2_bound_tile(lay, m, n, symmetric, compute_units) : 0;
+  route[3] = call == 0 && fallback_in_stage3(s, m, n) ? 0 : oz2_crt_on_matrix_cores(*plan, m, n, u8, symmetric) ? 2 : 1;
   return OZ2_OK;
 }
 

@@ -18,6 +18,7 @@
 
 #include "oz2_math.h"
 #include "oz2_bound.h"
+#include "oz2_route.h"
 #include "oz2_scan_finish.h"
 #include "oz2_warm.h"
 
@@ -959,7 +960,7 @@ static int short_vectors(int64_t vectors, int64_t strided, int64_t in_lines, int
 // calls, us, past the caches / through: 14 moduli 2000 x 2000 x 500 75.8 / 68.2, 3001 x 2777 x 200 107 / 99, 2048^3 172.1 / 166.5, 4000 x
 // 500 x 1000 72.8 / 68.7, 12 moduli 8000 x 4000 x 300 332 / 319, dsyrk of order 5000 with 200 142 / 136, with 1024 and 16 moduli 315 / 307;
 // 14 moduli 700^3 29.0 / 31.0, 1024^3 36.9 / 37.5; 302 MB 18 moduli 8192 x 8192 x 1024 1487 / 1507.
-static bool planes_through_caches(int num_moduli, const Oz2Layout& lay, bool symmetric) {
+bool oz2_planes_through_caches(int num_moduli, const Oz2Layout& lay, bool symmetric) {
   const int64_t bytes = num_moduli * (lay.m_pad + (symmetric ? 0 : lay.n_pad)) * lay.k_pad;
   return bytes <= (int64_t)200 << 20 && (bytes > (int64_t)32 << 20 || lay.m_pad * lay.n_pad >= (int64_t)1 << 21);
 }
@@ -993,6 +994,23 @@ int oz2_one_pass_vectors(const Oz2Plan& plan, const Oz2Layout& lay, int strided_
   const int64_t in_lines = shift_mode != OZ2_SHIFT_MAX ? 0 : (lines_a ? lay.m_pad : 0) + (lines_b ? second : 0);
   const int64_t strided = (strided_a ? lay.m_pad : 0) + (strided_b ? second : 0);
   return short_vectors(lay.m_pad + second, strided, in_lines, lay.k_pad, param[0] > most || param[1] > most, cus);
+}
+
+// One operand of strided vectors, one of contiguous ones, more elements than the last-level cache keeps: the contiguous one in one
+// pass (short_vectors), the scan and the conversion for the other alone, which folds both launches' reports.  Not where the vectors
+// or the contiguous ones are few, nor with a triangular operand (whole calls, both in two passes / this, us: 14 moduli 3000 x 3000 x 5000
+// 708 / 677, 6000 x 6000 x 3000 1510 / 1467, 16 moduli 8192 x 8192 x 4096 3749 / 3663, 10 moduli 2920 x 3916 x 3980 560 / 543, 16 moduli
+// 4096^3 1037 / 1025; 15 moduli 1488 x 1744 x 8976 470 / 489, 10 moduli 1072 x 1040 x 9216 205 / 230, 18 moduli 2752 x 656 x 6880 392 / 402,
+// dtrmm 4096 x 2048 443 / 461).
+int oz2_one_pass_operand(const Oz2Plan& plan, const Oz2Layout& lay, int strided_a, int strided_b, int triangular, int symmetric,
+                         int shift_mode, int bit_split, int64_t cus) {
+  int param[2];
+  shift_params(plan, shift_mode, bit_split, param);
+  if (symmetric || triangular || shift_mode != OZ2_SHIFT_MAX || !strided_a == !strided_b || param[0] > 75 || param[1] > 75) return 0;
+  const int64_t vectors = lay.m_pad + lay.n_pad, contiguous = strided_a ? lay.n_pad : lay.m_pad;
+  const bool fits = lay.k_pad > short_longest(8) && lay.k_pad <= short_longest(2);
+  if (!fits || 3 * contiguous < vectors || vectors * lay.k_pad <= kCachedElements || vectors < 20 * cus) return 0;
+  return strided_a ? 2 : 1;
 }
 
 hipError_t oz2_launch_finish_scan(const Oz2ScanFinish& f, hipStream_t st) {
@@ -1095,7 +1113,7 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
     // the others and the loads only cost (9 moduli 71 x 5081 x 184 22.5 -> 23.1, 900 x 700 x 300 22.7 -> 23.1).
     const int warm = lay.k_pad > 1024 || 2 * (int64_t)groups <= 3 * oz2_gemm_cus();
     const size_t lds = (size_t)short_vecs * (lay.k_pad + 4) * sizeof(double);
-    const bool through = planes_through_caches(plan.N, lay, B == nullptr);
+    const bool through = oz2_planes_through_caches(plan.N, lay, B == nullptr);
 #define OZ2_SHORT_V(KA, KB, V, THROUGH) \
   hipLaunchKernelGGL((short_convert_kernel<KA, KB, V, THROUGH>), grid, thr, lds, st, sj[0], sj[1], conv, base_mode, warm, slots)
 #define OZ2_SHORT_ALL(KA, KB, THROUGH)    \
@@ -1149,23 +1167,17 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
   const bool few_and_long = shift_mode != OZ2_SHIFT_MAX && lay.k_pad > line && vectors <= few;
   const bool large = vectors * lay.k_pad > ((int64_t)1 << 25);
   const bool scan = !strassen && !large && !few_and_long;
-  // One operand of strided vectors, one of contiguous ones, more elements than the last-level cache keeps: the contiguous one in one
-  // pass (short_vectors), the scan and the conversion for the other alone, which folds both launches' reports.  Not where the vectors
-  // or the contiguous ones are few, nor with a triangular operand (whole calls, both in two passes / this, us: 14 moduli 3000 x 3000 x 5000
-  // 708 / 677, 6000 x 6000 x 3000 1510 / 1467, 16 moduli 8192 x 8192 x 4096 3749 / 3663, 10 moduli 2920 x 3916 x 3980 560 / 543, 16 moduli
-  // 4096^3 1037 / 1025; 15 moduli 1488 x 1744 x 8976 470 / 489, 10 moduli 1072 x 1040 x 9216 205 / 230, 18 moduli 2752 x 656 x 6880 392 / 402,
-  // dtrmm 4096 x 2048 443 / 461).
-  const int contiguous = nops == 2 && ops[0].strided != ops[1].strided ? (ops[0].strided ? 1 : 0) : -1;
-  const bool split = contiguous >= 0 && 3 * ops[contiguous].nvec_pad >= vectors && !tri_a && !tri_b && shift_mode == OZ2_SHIFT_MAX && !strassen && !thin && !short_vecs && !two_a &&
-                     !two_b && lay.k_pad > short_longest(8) && lay.k_pad <= short_longest(2) && vectors * lay.k_pad > kCachedElements && vectors >= 20 * oz2_gemm_cus();
+  const int alone = !strassen && !thin && !short_vecs ? oz2_one_pass_operand(plan, lay, ops[0].strided, ops[1].strided, tri_a || tri_b, nops == 1,
+                                                                             shift_mode, d, oz2_gemm_cus())
+                                                      : 0;
   if (short_vecs) {
     // (the bound planes exist)
-  } else if (split) {
-    const Operand &c = ops[contiguous], &o = ops[1 - contiguous];
+  } else if (alone) {
+    const Operand &c = ops[alone - 1], &o = ops[2 - alone];
     const int v = lay.k_pad > short_longest(4) || lay.k_pad <= 3392 || c.nvec_pad <= 4 * oz2_gemm_cus() ? 2 : 4;
     const unsigned nblk = (unsigned)(c.nvec_pad / v), scans = (unsigned)(o.nvec_pad / kScanVecs);
     unsigned long long* slots = reinterpret_cast<unsigned long long*>(ws + lay.off_c);
-    const ShortJob sj = {c.X, c.ld, c.nvec, c.nvec_pad, c.k, c.k_pad, c.vmax, c.vaux, c.shifts, c.planes, param[contiguous], 0, 0, nblk, nblk / 8};
+    const ShortJob sj = {c.X, c.ld, c.nvec, c.nvec_pad, c.k, c.k_pad, c.vmax, c.vaux, c.shifts, c.planes, param[alone - 1], 0, 0, nblk, nblk / 8};
     ShortJob none = sj;
     none.nblk = none.chunk = 0;
     const size_t lds = (size_t)v * (lay.k_pad + 4) * sizeof(double);
@@ -1173,7 +1185,7 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
       hipLaunchKernelGGL((short_convert_kernel<0, 0, 2, false>), dim3(8 * sj.chunk), dim3(kShortThreads), lds, st, sj, none, conv, 0, 1, slots);
     else
       hipLaunchKernelGGL((short_convert_kernel<0, 0, 4, false>), dim3(8 * sj.chunk), dim3(kShortThreads), lds, st, sj, none, conv, 0, 1, slots);
-    const ScanJob job = {o.X, o.ld, o.nvec, o.nvec_pad, o.k, o.vmax, o.vaux, o.shifts, param[1 - contiguous], o.tri, o.strided ? 1 : 0, scans};
+    const ScanJob job = {o.X, o.ld, o.nvec, o.nvec_pad, o.k, o.vmax, o.vaux, o.shifts, param[2 - alone], o.tri, o.strided ? 1 : 0, scans};
     ScanJob no_job = job;
     no_job.nblk = 0;
     hipLaunchKernelGGL(vector_scan_kernel, dim3(scans), dim3(kScanThreads), 0, st, job, no_job, 0, slots + nblk);

@@ -7,6 +7,7 @@
 #include "oz2_fallback_tile.h"
 #include "oz2_fast_div.h"
 #include "oz2_math.h"
+#include "oz2_route.h"
 #include "oz2_warm.h"
 
 namespace {
@@ -430,6 +431,14 @@ double host_crt(const Oz2CrtConsts& cc, const int32_t* cprod) {
 
 }  // namespace
 
+// From 2^25 elements on, 3/2 of them of a symmetric product: below, a thread's 64 elements leave too few threads for the chip and the
+// other kernel wins.  Whole calls with inner dimension 300, us, other / matrix cores: 18 moduli 4096^2 245 / 261, 10 moduli 155 / 159, 18
+// moduli 5200 x 5100 455 / 470, 16 moduli 409 / 409, 5800 x 5900 524 / 514, 8192^2 860 / 846 with 200; dsyrk of order 5000 with 1024 and 10
+// moduli 214 / 225, 6000 with 16 288 / 295, 7000 384 / 377, 8000 487 / 471.
+bool oz2_crt_on_matrix_cores(const Oz2Plan& plan, int64_t m, int64_t n, int residue_u8, int triangle) {
+  return residue_u8 && plan.digits.valid && (triangle ? m * n / 3 * 2 : m * n) >= ((int64_t)1 << 25);
+}
+
 hipError_t oz2_launch_stage3(int64_t m, int64_t n, double alpha, double beta, double* C, int64_t ldc,
                              const Oz2Plan& plan, const Oz2Layout& lay, char* ws, int residue_u8, int check_flag,
                              int triangle, hipStream_t st) {
@@ -437,11 +446,7 @@ hipError_t oz2_launch_stage3(int64_t m, int64_t n, double alpha, double beta, do
   const unsigned long long* skip = check_flag ? reinterpret_cast<const unsigned long long*>(ws + lay.off_flags) : nullptr;
   const int* sa = reinterpret_cast<const int*>(ws + lay.off_sa);
   const int* sb = triangle ? sa : reinterpret_cast<const int*>(ws + lay.off_sb);  // symmetric: columns are A's rows
-  // (from 2^25 elements on, 3/2 of them of a symmetric product: below, a thread's 64 elements leave too few threads for the chip and the
-  // other kernel wins.  Whole calls with inner dimension 300, us, other / matrix cores: 18 moduli 4096^2 245 / 261, 10 moduli 155 / 159, 18
-  // moduli 5200 x 5100 455 / 470, 16 moduli 409 / 409, 5800 x 5900 524 / 514, 8192^2 860 / 846 with 200; dsyrk of order 5000 with 1024 and 10
-  // moduli 214 / 225, 6000 with 16 288 / 295, 7000 384 / 377, 8000 487 / 471.)
-  if (residue_u8 && plan.digits.valid && (triangle ? m * n / 3 * 2 : m * n) >= ((int64_t)1 << 25)) {
+  if (oz2_crt_on_matrix_cores(plan, m, n, residue_u8, triangle)) {
     // at most OZ2_MFMA_N moduli: the accumulation of line 9 on the matrix cores
     const uint8_t* p8 = static_cast<const uint8_t*>(cplanes);
     dim3 g2((unsigned)((n + kCrtCols - 1) / kCrtCols), (unsigned)((m + 1023) / 1024));

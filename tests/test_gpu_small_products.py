@@ -34,6 +34,10 @@ def _choice(m, n, k, N):
     return oz.host_kernel_choice(m, n, k, N, torch.cuda.get_device_properties(0).multi_processor_count)
 
 
+def _route(m, n, k, N, ta="N", tb="N", call="dgemm"):
+    return oz.host_route(m, n, k, N, torch.cuda.get_device_properties(0).multi_processor_count, call, ta, tb)
+
+
 def _mat(rng, r, c):
     return np.asfortranarray((rng.random((r, c)) - 0.5) * np.exp(rng.standard_normal((r, c))))
 
@@ -613,6 +617,11 @@ def test_many_long_contiguous_vectors_in_one_pass(mode, k):
     ctx = oz.Context()
     ctx.set(oz.OZ2_OPT_SHIFT_MODE, mode)
     ctx.allocate_workspace(m, n, k, N, device="cuda:0")
+    oz.oz2_set_shift_mode(mode)  # (the default context's, which the routes are told for)
+    try:
+        assert _route(m, n, k, N, "T", "N")[0] == 3 and _route(m, n, k, N, "N", "T")[0] == 0
+    finally:
+        oz.oz2_set_shift_mode(oz.OZ2_SHIFT_MAX)
     for infinity in (False, True):
         print("one pass over long vectors: k=%d n=%d mode=%d infinity=%d" % (k, n, mode, infinity), flush=True)
         if infinity:
@@ -633,7 +642,7 @@ def test_one_operand_in_one_pass_and_the_other_in_two(m, n, k):
     gen = torch.Generator(device="cuda").manual_seed(k)
     A = torch.randn((k, m), dtype=torch.float64, device="cuda", generator=gen)
     B = torch.randn((n, k), dtype=torch.float64, device="cuda", generator=gen)
-    assert (m + n) * k > 190 << 17 and m + n >= 20 * 250
+    assert [_route(m, n, k, N, ta, tb)[0] for ta, tb in (("N", "N"), ("T", "T"), ("T", "N"))] == [2, 1, 3]
     ctx = oz.Context()
     ctx.allocate_workspace(m, n, k, N, device="cuda:0")
     for infinite in ("none", "A", "B"):

@@ -499,6 +499,37 @@ def test_kernel_choice_at_the_limits_of_the_rules():
     assert L.oz2_host_kernel_choice(0, 1, 1, 1, 9, 1, None) == -7
 
 
+def test_route_at_the_limits_of_the_rules():
+    """What oz2_host_route tells on 256 compute units: operands in one pass (both, one of them, none) by their orientations, the tiles of the
+    product of bounds, the kernel of lines 8-11."""
+    def route(m, n, k, N, ta="N", tb="N", call="dgemm"):
+        return oz.host_route(m, n, k, N, 256, call, ta, tb)
+
+    # strided and contiguous vectors of a large product; what fits into LDS no longer (9921), and few elements
+    assert [route(4096, 4096, 4096, 16, ta, tb)[0] for ta in "NT" for tb in "NT"] == [2, 0, 3, 1]
+    assert [route(2600, 2500, k, 4)[0] for k in (9920, 9921)] == [2, 0] and route(2300, 2300, 9920, 4)[0] == 0
+    assert route(4096, 4096, 4096, 22)[0] == 0 and route(4096, 4096, 4096, 16, call="dtrmm")[0] == 0
+    assert route(256, 256, 256, 14) == (3, 0, 0, 0) and route(8192, 96, 8192, 16)[0] == 0
+    # the lines of the two kernels of stage 3
+    assert [route(4096, n, 300, 16)[3] for n in (4095, 4096, 8191, 8192)] == [0, 1, 1, 2]
+    assert [route(8192, 8192, 300, N)[3] for N in (16, 17, 20, 21, 26)] == [2, 2, 2, 1, 1]
+    assert [route(n, n, 40, 12, call="dsyrk")[3] for n in (600, 7090, 7100)] == [1, 1, 2]
+    assert [route(16384, n, n, 12, call="dtrmm")[3] for n in (100, 2047, 2048)] == [1, 1, 2]
+    assert route(4096, 4096, 300, 16)[2] == 0
+    try:
+        oz.oz2_set_shift_mode(oz.OZ2_SHIFT_INT8_PRODUCT)
+        assert [route(m, m, k, 2)[2] for m, k in [(200, 200), (1000, 1600), (4096, 4096), (3584, 8192), (16384, 16384)]] == [64, 64, 128, 256, 256]
+        assert [route(4000, 4000, k, 2, call="dsyrk")[2] for k in (1000, 30000)] == [128, 256]
+        assert route(4096, 4096, 4096, 16)[0] == 0 and route(4096, 4096, 4096, 16, "T")[0] == 3
+    finally:
+        oz.oz2_set_shift_mode(oz.OZ2_SHIFT_MAX)
+    L, out = oz.lib(), (ctypes.c_int * 4)()
+    assert [L.oz2_host_route(*a, out) for a in [(3, b"N", b"N", 1, 1, 1, 9, 1), (0, b"X", b"N", 1, 1, 1, 9, 1), (0, b"N", b"X", 1, 1, 1, 9, 1),
+                                                (0, b"N", b"N", 0, 1, 1, 9, 1), (1, b"N", b"N", 1, 2, 1, 9, 1), (2, b"N", b"N", 1, 1, 2, 9, 1),
+                                                (0, b"N", b"N", 1, 1, 1, 1, 1), (0, b"N", b"N", 1, 1, 1, 9, 0)]] == [-1, -2, -3, -4, -5, -6, -7, -8]
+    assert L.oz2_host_route(0, b"N", b"N", 1, 1, 1, 9, 1, None) == -9
+
+
 def test_bench_refuses_more_than_one_gpu():
     """The path runs on one GPU: bench.py --gpus N with N above 1 exits with a message and touches no GPU."""
     import subprocess
