@@ -9,7 +9,7 @@
 int oz2_one_pass_operand(const Oz2Plan& plan, const Oz2Layout& lay, int strided_a, int strided_b, int triangular, int symmetric,
                          int shift_mode, int bit_split, int64_t cus);
 // Are the residue planes of a one-pass conversion of both operands stored through the caches?
-bool oz2_planes_through_caches(int num_moduli, const Oz2Layout& lay, bool symmetric);
+bool oz2_planes_through_caches(int num_moduli, const Oz2Layout& lay, int64_t m, int64_t n, bool symmetric);
 // Is line 9 formed on the matrix cores?  triangle: 0, 1 or 2, as oz2_launch_stage3 takes it.
 bool oz2_crt_on_matrix_cores(const Oz2Plan& plan, int64_t m, int64_t n, int residue_u8, int triangle);
 

@@ -960,9 +960,19 @@ static int short_vectors(int64_t vectors, int64_t strided, int64_t in_lines, int
 // calls, us, past the caches / through: 14 moduli 2000 x 2000 x 500 75.8 / 68.2, 3001 x 2777 x 200 107 / 99, 2048^3 172.1 / 166.5, 4000 x
 // 500 x 1000 72.8 / 68.7, 12 moduli 8000 x 4000 x 300 332 / 319, dsyrk of order 5000 with 200 142 / 136, with 1024 and 16 moduli 315 / 307;
 // 14 moduli 700^3 29.0 / 31.0, 1024^3 36.9 / 37.5; 302 MB 18 moduli 8192 x 8192 x 1024 1487 / 1507.
-bool oz2_planes_through_caches(int num_moduli, const Oz2Layout& lay, bool symmetric) {
-  const int64_t bytes = num_moduli * (lay.m_pad + (symmetric ? 0 : lay.n_pad)) * lay.k_pad;
-  return bytes <= (int64_t)200 << 20 && (bytes > (int64_t)32 << 20 || lay.m_pad * lay.n_pad >= (int64_t)1 << 21);
+// Some 390 calls with up to 200 MB of planes and either more than 32 MB or 2^21 elements of C gain 2.6 % (geometric mean; operands that the
+// last-level cache does not hold yet: 4.0).  Left out are the kinds that lose in both ways: results of one tile (14 moduli 117 x 90 x 5412 40.4 /
+// 42.5; two tiles, 16 moduli 171 x 342 x 3113 40.4 / 40.1, operands elsewhere 47.6 / 43.1), up to 20 MB with less than 2^20 elements written
+// (10 moduli 64 x 8852 x 160 27.1 / 28.8; 21 MB 12 moduli 106 x 9009 x 152 31.0 / 30.7), and long vectors that are more than 300 MB together with their
+// planes (9 moduli 271 x 3981 x 4490 212 / 227; 297 MB 14 moduli 718 x 663 x 9180 186 / 184, operands elsewhere 201 / 186).  Single calls of the rest
+// are slower still, most of them with planes of 32 to 48 MB (15 moduli 2085 x 178 x 1270 52.0 / 54.9, 13 moduli 16192 x 384 x 732 189 / 203; but
+// 10 moduli 2095 x 154 x 1774 49.6 / 43.7).
+bool oz2_planes_through_caches(int num_moduli, const Oz2Layout& lay, int64_t m, int64_t n, bool symmetric) {
+  constexpr int64_t kMB = 1 << 20;
+  const int64_t elements = (lay.m_pad + (symmetric ? 0 : lay.n_pad)) * lay.k_pad, bytes = num_moduli * elements, result = lay.m_pad * lay.n_pad;
+  if (bytes > 200 * kMB || result <= (int64_t)OZ2_TILE_M * OZ2_TILE_N) return false;
+  if (bytes > 32 * kMB) return lay.k_pad <= short_longest(8) || bytes + 8 * elements <= 300 * kMB;
+  return result >= 1 << 21 && (bytes > 20 * kMB || (symmetric ? m * n / 2 : m * n) >= 1 << 20);
 }
 
 // What the shifts are formed from: the budgets of the operands, or (INT8-product mode) first the exponents 5 - e of the
@@ -1113,7 +1123,7 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
     // the others and the loads only cost (9 moduli 71 x 5081 x 184 22.5 -> 23.1, 900 x 700 x 300 22.7 -> 23.1).
     const int warm = lay.k_pad > 1024 || 2 * (int64_t)groups <= 3 * oz2_gemm_cus();
     const size_t lds = (size_t)short_vecs * (lay.k_pad + 4) * sizeof(double);
-    const bool through = oz2_planes_through_caches(plan.N, lay, B == nullptr);
+    const bool through = oz2_planes_through_caches(plan.N, lay, m, n, B == nullptr);
 #define OZ2_SHORT_V(KA, KB, V, THROUGH) \
   hipLaunchKernelGGL((short_convert_kernel<KA, KB, V, THROUGH>), grid, thr, lds, st, sj[0], sj[1], conv, base_mode, warm, slots)
 #define OZ2_SHORT_ALL(KA, KB, THROUGH)    \

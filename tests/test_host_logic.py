@@ -510,6 +510,14 @@ def test_route_at_the_limits_of_the_rules():
     assert [route(2600, 2500, k, 4)[0] for k in (9920, 9921)] == [2, 0] and route(2300, 2300, 9920, 4)[0] == 0
     assert route(4096, 4096, 4096, 22)[0] == 0 and route(4096, 4096, 4096, 16, call="dtrmm")[0] == 0
     assert route(256, 256, 256, 14) == (3, 0, 0, 0) and route(8192, 96, 8192, 16)[0] == 0
+    # residues of a one-pass conversion through the caches
+    assert [route(*a)[1] for a in [(2000, 2000, 500, 14), (4000, 500, 1000, 14), (2048, 2048, 2048, 14), (3001, 2777, 200, 14)]] == [1, 1, 1, 1]
+    assert [route(8192, 8192, k, 12)[1] for k in (1024, 1088)] == [1, 0] and route(5000, 5000, 1024, 16, call="dsyrk")[1] == 1
+    # not for one tile of C, nor for small planes and few elements of it, nor for long vectors and planes that fill the last-level cache
+    assert [route(m, 90, 5412, 14)[1] for m in (117, 256, 257)] == [0, 0, 1]
+    assert [route(64, n, 160, 10)[1] for n in (8852, 10496, 10497)] == [0, 0, 1] and route(64, 16300, 64, 10)[1] == 0
+    assert [route(n, n, 64, 15, call="dsyrk")[1] for n in (1440, 1460)] == [0, 1] and route(1440, 1440, 64, 15)[1] == 1
+    assert route(271, 3981, 4490, 9, "T", "N")[:2] == (3, 0) and route(718, 663, 9180, 14, "T", "T")[:2] == (3, 1)
     # the lines of the two kernels of stage 3
     assert [route(4096, n, 300, 16)[3] for n in (4095, 4096, 8191, 8192)] == [0, 1, 1, 2]
     assert [route(8192, 8192, 300, N)[3] for N in (16, 17, 20, 21, 26)] == [2, 2, 2, 1, 1]
