@@ -769,7 +769,8 @@ int oz2_host_route(int call, char transa, char transb, int64_t m, int64_t n, int
   const int thin = u8 && call == 0 ? oz2_thin_applies(m, n, *plan, lay, s.kblock, compute_units) : 0;
   const bool both = !thin && oz2_one_pass_vectors(*plan, lay, strided_a, strided_b, lines_a, lines_b, symmetric, s.shift_mode, split, compute_units);
   const bool bounds = s.shift_mode == OZ2_SHIFT_INT8_PRODUCT;
-  route[0] = both ? 3 : thin ? 0 : oz2_one_pass_operand(*plan, lay, strided_a, strided_b, call == 2, symmetric, s.shift_mode, split, compute_units);
+  route[0] = both ? 3 : thin ? 0 : oz2_one_pass_operand(*plan, lay, strided_a, strided_b, lines_a, lines_b, call == 2, symmetric, s.shift_mode,
+                                                             split, compute_units);
   route[1] = both && !bounds && oz2_planes_through_caches(num_moduli, lay, m, n, symmetric);
   route[2] = bounds ? oz2_bound_tile(lay, m, n, symmetric, compute_units) : 0;
   route[3] = call == 0 && fallback_in_stage3(s, m, n) ? 0 : oz2_crt_on_matrix_cores(*plan, m, n, u8, symmetric) ? 2 : 1;

@@ -1011,15 +1011,19 @@ int oz2_one_pass_vectors(const Oz2Plan& plan, const Oz2Layout& lay, int strided_
 // or the contiguous ones are few, nor with a triangular operand (whole calls, both in two passes / this, us: 14 moduli 3000 x 3000 x 5000
 // 708 / 677, 6000 x 6000 x 3000 1510 / 1467, 16 moduli 8192 x 8192 x 4096 3749 / 3663, 10 moduli 2920 x 3916 x 3980 560 / 543, 16 moduli
 // 4096^3 1037 / 1025; 15 moduli 1488 x 1744 x 8976 470 / 489, 10 moduli 1072 x 1040 x 9216 205 / 230, 18 moduli 2752 x 656 x 6880 392 / 402,
-// dtrmm 4096 x 2048 443 / 461).
-int oz2_one_pass_operand(const Oz2Plan& plan, const Oz2Layout& lay, int strided_a, int strided_b, int triangular, int symmetric,
-                         int shift_mode, int bit_split, int64_t cus) {
+// dtrmm 4096 x 2048 443 / 461).  Vectors above 4928 are taken two at a time, which gains less, and strided ones that are not whole cache lines by
+// sixteens cost the scan half of what it reads: not where those are more than the 2^25 elements up to which it is the better way for two
+// operands (14 moduli, transposed, 4675 x 9173 x 9354 5016 / 5128, 16 moduli 5395 x 4159 x 7289 2504 / 2552, 10 moduli 5153 x 2649 x 6871 1123 /
+// 1140; fewer 9 moduli 3674 x 3987 x 7080 1095 / 1069, in lines 17 moduli 5952 x 2880 x 5140 1.6 % faster).
+int oz2_one_pass_operand(const Oz2Plan& plan, const Oz2Layout& lay, int strided_a, int strided_b, int lines_a, int lines_b, int triangular,
+                         int symmetric, int shift_mode, int bit_split, int64_t cus) {
   int param[2];
   shift_params(plan, shift_mode, bit_split, param);
   if (symmetric || triangular || shift_mode != OZ2_SHIFT_MAX || !strided_a == !strided_b || param[0] > 75 || param[1] > 75) return 0;
   const int64_t vectors = lay.m_pad + lay.n_pad, contiguous = strided_a ? lay.n_pad : lay.m_pad;
   const bool fits = lay.k_pad > short_longest(8) && lay.k_pad <= short_longest(2);
   if (!fits || 3 * contiguous < vectors || vectors * lay.k_pad <= kCachedElements || vectors < 20 * cus) return 0;
+  if (lay.k_pad > short_longest(4) && !(strided_a ? lines_a : lines_b) && (vectors - contiguous) * lay.k_pad > (int64_t)1 << 25) return 0;
   return strided_a ? 2 : 1;
 }
 
@@ -1093,10 +1097,10 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
   // Short vectors: everything in one launch (in the INT8-product mode: maxima and bound planes), whose reports the caller's
   // GEMM launch turns into the flag word (deferred != nullptr: the caller sees to that).
   const bool two_a = param[0] + base_mode > 75, two_b = param[1] + base_mode > 75;
-  const int short_vecs = deferred && !thin && !strassen
-                             ? oz2_one_pass_vectors(plan, lay, ops[0].strided, ops[1].strided, lines_of_vectors(ops[0].strided, A, lda),
-                                                    lines_of_vectors(ops[1].strided, B, ldb), nops == 1, shift_mode, d, oz2_gemm_cus())
-                             : 0;
+  const bool lines_a = lines_of_vectors(ops[0].strided, A, lda), lines_b = lines_of_vectors(ops[1].strided, B, ldb);
+  const int short_vecs = deferred && !thin && !strassen ? oz2_one_pass_vectors(plan, lay, ops[0].strided, ops[1].strided, lines_a, lines_b,
+                                                                               nops == 1, shift_mode, d, oz2_gemm_cus())
+                                                        : 0;
   if (short_vecs) {
     ShortJob sj[2] = {};
     unsigned groups = 0;
@@ -1177,9 +1181,10 @@ hipError_t oz2_launch_stage1(int transa, int transb, int64_t m, int64_t n, int64
   const bool few_and_long = shift_mode != OZ2_SHIFT_MAX && lay.k_pad > line && vectors <= few;
   const bool large = vectors * lay.k_pad > ((int64_t)1 << 25);
   const bool scan = !strassen && !large && !few_and_long;
-  const int alone = !strassen && !thin && !short_vecs ? oz2_one_pass_operand(plan, lay, ops[0].strided, ops[1].strided, tri_a || tri_b, nops == 1,
-                                                                             shift_mode, d, oz2_gemm_cus())
-                                                      : 0;
+  const int alone = !strassen && !thin && !short_vecs
+                        ? oz2_one_pass_operand(plan, lay, ops[0].strided, ops[1].strided, lines_a, lines_b, tri_a || tri_b, nops == 1, shift_mode, d,
+                                               oz2_gemm_cus())
+                        : 0;
   if (short_vecs) {
     // (the bound planes exist)
   } else if (alone) {

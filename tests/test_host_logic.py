@@ -508,6 +508,9 @@ def test_route_at_the_limits_of_the_rules():
     # strided and contiguous vectors of a large product; what fits into LDS no longer (9921), and few elements
     assert [route(4096, 4096, 4096, 16, ta, tb)[0] for ta in "NT" for tb in "NT"] == [2, 0, 3, 1]
     assert [route(2600, 2500, k, 4)[0] for k in (9920, 9921)] == [2, 0] and route(2300, 2300, 9920, 4)[0] == 0
+    # strided vectors that are not whole cache lines by sixteens, beside contiguous ones taken two at a time
+    assert [route(m, 3000, 6871, 10)[0] for m in (5152, 5153, 3500, 3501)] == [2, 0, 2, 2] and route(5153, 3000, 4928, 10)[0] == 2
+    assert [route(3000, n, 6871, 10, "T", "T")[0] for n in (5152, 5153)] == [1, 0]
     assert route(4096, 4096, 4096, 22)[0] == 0 and route(4096, 4096, 4096, 16, call="dtrmm")[0] == 0
     assert route(256, 256, 256, 14) == (3, 0, 0, 0) and route(8192, 96, 8192, 16)[0] == 0
     # residues of a one-pass conversion through the caches
