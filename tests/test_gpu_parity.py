@@ -642,7 +642,7 @@ def test_cauchy_schwarz_mode_full_size_c4_sampled():
     (300, 200, 333, 5, 0.5),
     (64, 40, 1000, 20, 4.0),
     (33, 17, 50, 26, 4.0),        # 2^(b/2 + 7) > 2^75: two-level split
-    (530, 70, 130, 16, 1.0),      # three row blocks and two column chunks of the product-maximum kernel
+    (530, 70, 130, 16, 1.0),      # nine rows and two columns of 64 x 64 tiles of the product of bounds
     (1, 1, 1, 2, 0.5),
 ])
 def test_int8_product_mode_all_stages(m, n, k, N, phi):
@@ -663,6 +663,127 @@ def test_int8_product_maxima_at_the_edges_of_tiles(m, n, k, N):
     """Row and column maxima gathered by tiles of 64 and 128, one to many of them: shifts and all that follows."""
     rng = np.random.default_rng(m + n + k)
     check_against_oracle(rng.standard_normal((m, k)), rng.standard_normal((k, n)), N, mode=2)
+
+
+def _agrees_with_the_oracle_in_mode_2(A, B, N, sa, sb, C):
+    """All shifts, and the elements of C in sampled rows and in sampled columns (the first and last ones among them)."""
+    m, n = C.shape
+    rng = np.random.default_rng(m + n)
+    for rows, cols in ((None, np.unique(np.concatenate([[0, n - 1], rng.choice(n, 24, replace=False)]))),
+                       (np.unique(np.concatenate([[0, m - 1], rng.choice(m, 24, replace=False)])), None)):
+        ref = orc.dgemm(A, B, N, mode=2, rows=rows, cols=cols, want=("C", "shifts"))
+        rows, cols = np.arange(m) if rows is None else rows, np.arange(n) if cols is None else cols
+        if not (np.array_equal(sa[rows], ref.sa) and np.array_equal(sb[cols], ref.sb) and np.array_equal(C[np.ix_(rows, cols)], ref.C)):
+            return False
+    return True
+
+
+def _bound_tile(m, n, k, N, call="dgemm", ta="N", tb="N"):
+    """Edge of the tiles that the product of bounds of a call takes, and how many of them a compute unit gets."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    oz.oz2_set_shift_mode(oz.OZ2_SHIFT_INT8_PRODUCT)
+    try:
+        route = oz.host_route(m, n, k, N, cus, call, ta, tb)
+    finally:
+        oz.oz2_set_shift_mode(oz.OZ2_SHIFT_MAX)
+    tm, tn = -(-m // route[2]), -(-n // route[2])
+    return route[0], route[2], (tm * (tm + 1) // 2 if call == "dsyrk" else tm * tn) / cus
+
+
+@pytest.mark.parametrize("m,n,k,tile,most", [(1100, 1200, 1600, 64, 2), (1090, 1000, 1535, 64, 2), (2000, 1990, 1600, 128, 1), (2300, 2400, 1600, 128, 2),
+                                             (2100, 2200, 100, 128, 2)])
+@pytest.mark.parametrize("ta,tb", [("N", "N"), ("T", "T")])
+def test_int8_product_maxima_of_few_and_many_tiles(m, n, k, tile, most, ta, tb):
+    """Every form of the tiles that gather the maxima, in whole calls: one or two workgroups per compute unit with a long inner dimension, more
+    of them, a short one; and an infinity, whose report the launch of the product turns into the flag."""
+    N = 5
+    one_pass, edge, share = _bound_tile(m, n, k, N, ta=ta, tb=tb)
+    assert (one_pass, edge) == (3, tile) and most - 1 < share <= most
+    rng = np.random.default_rng(m + k)
+    A, B = np.asfortranarray(rng.standard_normal((m, k))), np.asfortranarray(rng.standard_normal((k, n)))
+    dA, dB = _dev(A.T if ta == "T" else A), _dev(B.T if tb == "T" else B)
+    dC = torch.full((n, m), float("nan"), dtype=torch.float64, device="cuda").t()
+    ws = oz.Workspace(m, n, k, N)
+    ws.buf.fill_(0x7f)
+    lay = oz.workspace_layout(m, n, k, N)
+    flags = ws.view(lay["flags"], 1, torch.int64)
+    oz.oz2_set_shift_mode(oz.OZ2_SHIFT_INT8_PRODUCT)
+    try:
+        print("bound product: m=%d n=%d k=%d op=%s%s" % (m, n, k, ta, tb), flush=True)
+        args = (ta, tb, m, n, k, 1.0, dA.data_ptr(), k if ta == "T" else m, dB.data_ptr(), n if tb == "T" else k, 0.0, dC.data_ptr(), m, N)
+        oz.oz2_dgemm_ex(*args)
+        torch.cuda.synchronize()
+        shifts = [ws.view(lay[x], count, torch.int32).cpu().numpy() for x, count in (("sa", m), ("sb", n))]
+        assert int(flags.item()) == 0 and _agrees_with_the_oracle_in_mode_2(A, B, N, *shifts, dC.cpu().numpy())
+        dB[-1, -1] = float("inf")
+        oz.oz2_dgemm_ex(*args)
+        torch.cuda.synchronize()
+        assert int(flags.item()) == 1 and not torch.isfinite(dC[:, n - 1]).any()
+    finally:
+        oz.oz2_set_shift_mode(oz.OZ2_SHIFT_MAX)
+    del ws
+
+
+@pytest.mark.parametrize("ta,tb,one_pass", [("T", "N", 3), ("N", "T", 0)])
+def test_int8_product_stored_for_a_launch_of_its_own_that_finds_the_maxima(ta, tb, one_pass):
+    """A product of bounds that large tiles form the faster way: its INT32 values are stored and read again (several row blocks and column
+    chunks).  Behind the one-pass conversion, whose reports lie in a residue plane until a launch before the product folds them, and behind
+    the separate launches; and an infinity."""
+    m, n, k, N = 4411, 2749, 6140, 4
+    assert _bound_tile(m, n, k, N, ta=ta, tb=tb)[:2] == (one_pass, 256)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    dA = torch.randn((k, m) if ta == "N" else (m, k), dtype=torch.float64, device="cuda", generator=gen)
+    dB = torch.randn((n, k) if tb == "N" else (k, n), dtype=torch.float64, device="cuda", generator=gen)
+    dC = torch.full((n, m), float("nan"), dtype=torch.float64, device="cuda")
+    A, B = ((x.t() if t == "N" else x).cpu().numpy() for x, t in ((dA, ta), (dB, tb)))
+    ws = oz.Workspace(m, n, k, N)
+    ws.buf.fill_(0x7f)
+    lay = oz.workspace_layout(m, n, k, N)
+    oz.oz2_set_shift_mode(oz.OZ2_SHIFT_INT8_PRODUCT)
+    try:
+        print("stored bound product: op=%s%s" % (ta, tb), flush=True)
+        args = (ta, tb, m, n, k, 1.0, dA.data_ptr(), dA.shape[1], dB.data_ptr(), dB.shape[1], 0.0, dC.data_ptr(), m, N)
+        oz.oz2_dgemm_ex(*args)
+        torch.cuda.synchronize()
+        shifts = [ws.view(lay[x], count, torch.int32).cpu().numpy() for x, count in (("sa", m), ("sb", n))]
+        assert _agrees_with_the_oracle_in_mode_2(np.asfortranarray(A), np.asfortranarray(B), N, *shifts, dC.t().cpu().numpy())
+        dA[-1, -1] = float("-inf")
+        oz.oz2_dgemm_ex(*args)
+        torch.cuda.synchronize()
+        assert int(ws.view(lay["flags"], 1, torch.int64).item()) == 1 and not torch.isfinite(dC[:, m - 1]).any()
+    finally:
+        oz.oz2_set_shift_mode(oz.OZ2_SHIFT_MAX)
+    del ws
+
+
+@pytest.mark.parametrize("n,k,tile,most", [(1700, 300, 128, 1), (1700, 1600, 64, 2), (2500, 1600, 128, 1), (3100, 1600, 128, 2), (4032, 24000, 256, 3)])
+@pytest.mark.parametrize("uplo,trans", [("L", "N"), ("U", "T")])
+def test_int8_product_mode_dsyrk_by_the_tiles_of_its_bounds(n, k, tile, most, uplo, trans):
+    """Maxima from tiles of one triangle, by 64 and 128, and from the stored product; sampled rows and columns, the diagonal among them."""
+    N = 4
+    _, edge, share = _bound_tile(n, n, k, N, "dsyrk", trans)
+    assert edge == tile and (tile == 256 or most - 1 < share <= most)
+    gen = torch.Generator(device="cuda").manual_seed(n + k)
+    dA = torch.randn((k, n) if trans == "N" else (n, k), dtype=torch.float64, device="cuda", generator=gen)
+    dC = torch.full((n, n), 7.0, dtype=torch.float64, device="cuda")
+    ws = oz.Workspace(n, n, k, N)
+    ws.buf.fill_(0x7f)
+    oz.oz2_set_shift_mode(oz.OZ2_SHIFT_INT8_PRODUCT)
+    try:
+        print("bound product of one triangle: n=%d k=%d %s%s" % (n, k, uplo, trans), flush=True)
+        oz.oz2_dsyrk(uplo, trans, n, k, 1.0, dA.data_ptr(), dA.shape[1], 0.0, dC.data_ptr(), n, N)
+        torch.cuda.synchronize()
+    finally:
+        oz.oz2_set_shift_mode(oz.OZ2_SHIFT_MAX)
+    sa = ws.view(oz.workspace_layout(n, n, k, N)["sa"], n, torch.int32).cpu().numpy()
+    del ws
+    A = np.asfortranarray((dA.t() if trans == "N" else dA).cpu().numpy())
+    pick = np.unique(np.concatenate([[0, 127, 128, n - 1], np.random.default_rng(n).choice(n, 60, replace=False)]))
+    ref = orc.dgemm(A, np.asfortranarray(A.T), N, mode=2, rows=pick, cols=pick, want=("C", "shifts"))
+    assert np.array_equal(sa[pick], ref.sa)
+    got = dC.t()[torch.from_numpy(pick).cuda()][:, torch.from_numpy(pick).cuda()].cpu().numpy()
+    mine = pick[:, None] >= pick[None, :] if uplo == "L" else pick[:, None] <= pick[None, :]
+    assert np.array_equal(got[mine], ref.C[mine]) and np.all(got[~mine] == 7.0)
 
 
 def test_int8_product_mode_full_size_c3_sampled_and_transposed():
