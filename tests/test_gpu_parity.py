@@ -304,12 +304,12 @@ def test_full_size_configs_on_sampled_outputs(name, kblock, algorithm, N):
     del ws
 
 
-@pytest.mark.parametrize("N,algorithm", [(8, 0), (17, 0), (8, 1)])
+@pytest.mark.parametrize("N,algorithm", [(8, 0), (17, 0), (21, 0), (8, 1)])
 def test_more_than_2_to_the_32_elements_of_c(N, algorithm):
     """A product whose C (and, in the classical form, every residue plane) has more than 2^32 elements, so that an
-    element index does not fit 32 bits: 66000 x 65600 with a short inner dimension, 8 moduli (matrix-core CRT
-    kernel) and 17 (FP64 accumulation) in the classical form, 8 moduli with the Strassen form forced (56 planes of
-    2^30 elements).  Every element is written (C starts as NaN), and a sample of rows and columns including the last
+    element index does not fit 32 bits: 66000 x 65600 with a short inner dimension, 8 and 17 moduli (line 9 on the
+    matrix cores, in sixteen and in twenty digits) and 21 (FP64 accumulation) in the classical form, 8 moduli with the
+    Strassen form forced (56 planes of 2^30 elements).  Every element is written (C starts as NaN), and a sample of rows and columns including the last
     ones is compared with the oracle."""
     m, n, k, phi = 66000, 65600, 64 if algorithm == 0 else 128, 0.5
     assert m * n > 1 << 32
@@ -323,8 +323,9 @@ def test_more_than_2_to_the_32_elements_of_c(N, algorithm):
     dC = torch.full((n, m), float("nan"), dtype=torch.float64, device="cuda").t()
     oz.oz2_set_gemm_algorithm(algorithm)
     try:
-        ws = oz.Workspace(m, n, k, N, product_format=oz.OZ2_PRODUCT_RESIDUE_U8)   # 8, 17 or 14 bytes per element of C
+        ws = oz.Workspace(m, n, k, N, product_format=oz.OZ2_PRODUCT_RESIDUE_U8)   # 8, 17, 21 or 14 bytes per element of C
         assert (oz.oz2_gemm_algorithm_for(m, n, k, N) == oz.OZ2_GEMM_STRASSEN) == (algorithm == 1)
+        assert oz.host_route(m, n, k, N, torch.cuda.get_device_properties(0).multi_processor_count)[3] == (2 if N <= 20 else 1)
         print("C of %d x %d = %.2f * 2^32 elements, N=%d, form %d" % (m, n, m * n / 2.0**32, N, algorithm), flush=True)
         oz.oz2_dgemm(m, n, k, dA.data_ptr(), m, dB.data_ptr(), k, dC.data_ptr(), m, N)
         torch.cuda.synchronize()
@@ -466,15 +467,20 @@ def test_round_synchronisation_bound_and_switch(spins):
     del ws
 
 
+def _crt_kernel(m, n, k, N, call="dgemm"):
+    """0: with the fallback in one launch, 1: a launch of its own, 2: line 9 on the matrix cores"""
+    return oz.host_route(m, n, k, N, torch.cuda.get_device_properties(0).multi_processor_count, call)[3]
+
+
 @pytest.mark.parametrize("N,alpha,beta", [(16, 1.0, 0.0), (13, 1.0, 0.0), (9, 1.0, 0.0), (4, 1.0, 0.0), (16, -0.75, 2.0),
-                                          (17, 1.0, 0.0)])
+                                          (17, 1.0, 0.0), (20, 1.0, 0.0), (21, 1.0, 0.0)])
 def test_matrix_core_crt_every_element_ragged(N, alpha, beta):
-    """Alg. 1 line 9 on the matrix cores (the kernel taken from 2^24 elements of C on, classical form, up to 16
+    """Alg. 1 line 9 on the matrix cores (the kernel taken from 2^25 elements of C on, classical form, up to 20
     moduli): a ragged shape above that size with a short inner dimension, EVERY element of C compared with the
     oracle, for moduli counts whose product needs one, two, three and four 40-bit limbs, as the update with alpha
-    and beta, and with 17 moduli (the first count that stays with the FP64 accumulation at this size)."""
+    and beta, with 17 and 20 moduli (twenty digits), and with 21 (the first count that stays with the FP64 accumulation)."""
     m, n, k, phi = 5801, 5791, 40, 1.0
-    assert m * n >= 1 << 25
+    assert _crt_kernel(m, n, k, N) == (2 if N <= 20 else 1)
     A = inputs.block(77, 0, m, k, phi)
     B = inputs.block(77, 1, k, n, phi)
     C0 = inputs.block(77, 2, m, n, 0.5)
@@ -484,7 +490,7 @@ def test_matrix_core_crt_every_element_ragged(N, alpha, beta):
     oz.oz2_set_gemm_algorithm(oz.OZ2_GEMM_CLASSICAL)
     try:
         ws = oz.Workspace(m, n, k, N)
-        print("matrix-core CRT, every element of %d x %d, N=%d alpha=%g beta=%g" % (m, n, N, alpha, beta), flush=True)
+        print("CRT, every element of %d x %d, N=%d alpha=%g beta=%g" % (m, n, N, alpha, beta), flush=True)
         oz.oz2_dgemm_ex("N", "N", m, n, k, alpha, dA.data_ptr(), m, dB.data_ptr(), k, beta, dC.data_ptr(), m, N)
         torch.cuda.synchronize()
     finally:
@@ -497,12 +503,13 @@ def test_matrix_core_crt_every_element_ragged(N, alpha, beta):
     assert not np.isnan(got).any()
 
 
-@pytest.mark.parametrize("N,alpha,beta", [(18, 1.0, 0.0), (20, -0.75, 2.0)])
-def test_matrix_core_crt_of_more_than_16_moduli_every_element(N, alpha, beta):
-    """Twenty digits in two products: a ragged shape, EVERY element against the call with INT32 planes, whose weights are added up in
-    FP64."""
-    m, n, k = 4357, 4099, 70
-    assert m * n >= 1 << 24
+@pytest.mark.parametrize("m,n,kernel", [(5801, 5791, 2), (4357, 4099, 1)])
+@pytest.mark.parametrize("N,alpha,beta", [(18, 1.0, 0.0), (18, -0.75, 2.0), (19, 1.0, 0.0), (19, -0.75, 2.0), (20, 1.0, 0.0), (20, -0.75, 2.0)])
+def test_matrix_core_crt_of_more_than_16_moduli_every_element(N, alpha, beta, m, n, kernel):
+    """Twenty digits in two products, and the smaller results that do not take them: ragged shapes, EVERY element against the call with
+    INT32 planes, whose weights are added up in FP64."""
+    k = 70
+    assert _crt_kernel(m, n, k, N) == kernel
     gen = torch.Generator(device="cuda").manual_seed(N)
     A, B, C0 = (torch.randn(s, dtype=torch.float64, device="cuda", generator=gen) for s in ((k, m), (n, k), (n, m)))
     got = []
@@ -526,7 +533,7 @@ def test_matrix_core_crt_of_a_triangle_every_element(uplo, N):
     """The first orders of a symmetric update whose CRT runs on the matrix cores, and the last ones below: the written triangle against
     the call with INT32 planes, the other one untouched."""
     for n in (7100, 7090):
-        assert (n * n // 3 * 2 >= 1 << 25) == (n == 7100)
+        assert _crt_kernel(n, n, 40, N, "dsyrk") == (2 if n == 7100 else 1)
         gen = torch.Generator(device="cuda").manual_seed(n)
         A = torch.randn((40, n), dtype=torch.float64, device="cuda", generator=gen)
         C0 = torch.randn((n, n), dtype=torch.float64, device="cuda", generator=gen)
@@ -1092,17 +1099,17 @@ def test_dsyrk_matches_the_oracle_and_leaves_the_other_triangle(uplo, trans, mod
 
 @pytest.mark.parametrize("uplo", ["L", "U"])
 def test_dsyrk_every_element_where_the_crt_runs_on_the_matrix_cores(uplo):
-    """A symmetric update with more than 2^24 elements of C and 12 moduli: stages 3 and 4 run in the matrix-core
+    """A symmetric update with more than 3/2 2^25 elements of C and 12 moduli: stages 3 and 4 run in the matrix-core
     kernel, which has to keep to the triangle (rows of a thread's four on both sides of the diagonal, ragged last
     rows); every element of the triangle against the oracle, the other triangle untouched."""
     rng = np.random.default_rng(33)
-    n, k, N = 4100, 48, 12
-    assert n * n >= 1 << 24
+    n, k, N = 7110, 48, 12
+    assert _crt_kernel(n, n, k, N, "dsyrk") == 2
     A = np.asfortranarray((rng.random((n, k)) - 0.5) * np.exp(rng.standard_normal((n, k))))
     alpha, beta = -0.5, 1.25
     C0 = np.asfortranarray(rng.standard_normal((n, n)))
-    ii, jj = np.meshgrid(np.arange(n), np.arange(n), indexing="ij")
-    outside = (ii < jj) if uplo == "L" else (ii > jj)
+    ii = np.arange(n)
+    outside = (ii[:, None] < ii[None, :]) if uplo == "L" else (ii[:, None] > ii[None, :])
     C0[outside] = np.nan            # never read, never written
     dA = _dev(A)
     dC = torch.from_numpy(np.ascontiguousarray(C0.T)).cuda().t()
@@ -1252,11 +1259,11 @@ def test_dtrmm_matches_the_oracle_in_place(side, uplo, transa, diag, mode):
 
 
 def test_dtrmm_every_element_where_the_crt_runs_on_the_matrix_cores():
-    """A triangular product with more than 2^24 elements of B and 12 moduli (stages 3 and 4 in the matrix-core
-    kernel, written into the staging buffer of the in-place product): every element against the oracle."""
+    """A triangular product with more than 2^25 elements of B and 12 moduli (stages 3 and 4 in the matrix-core
+    kernel, over the operand that stage 1 has read): every element against the oracle."""
     rng = np.random.default_rng(52)
-    m, n, N = 16390, 1030, 12       # B := alpha * B * op(A), A of order 1030
-    assert m * n >= 1 << 24
+    m, n, N = 112001, 300, 12       # B := alpha * B * op(A), A of order 300
+    assert _crt_kernel(m, n, n, N, "dtrmm") == 2
     A = (rng.random((n, n)) - 0.5) * np.exp(rng.standard_normal((n, n)))
     B = np.asfortranarray((rng.random((m, n)) - 0.5) * np.exp(rng.standard_normal((m, n))))
     G = _garbage_outside(A, "L", "N")

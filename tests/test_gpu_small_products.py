@@ -357,12 +357,13 @@ def test_long_products_are_not_formed_for_nonfinite_inputs(call, m, n, k):
     del ws
 
 
-@pytest.mark.parametrize("n,k", [(4200, 64), (4200, 520), (4400, 520)])
+@pytest.mark.parametrize("n,k,kernel", [(4200, 64, 1), (4200, 520, 1), (4400, 520, 1), (7110, 64, 2), (7110, 520, 2), (7300, 520, 2)])
 @pytest.mark.parametrize("uplo", ["L", "U"])
-def test_symmetric_update_with_more_than_2_24_elements(uplo, n, k):
-    """The matrix-core kernel of stage 3 skips what lies in the other triangle: rows and columns around its 256 x 16 blocks;
-    with the longer inner dimension the products take 256 x 256 tiles, 17 or 18 rows of them, of one triangle only."""
+def test_symmetric_update_with_more_than_2_24_elements(uplo, n, k, kernel):
+    """Both kernels of stage 3 skip what lies in the other triangle: rows and columns around the 256 x 16 blocks of the one on the matrix
+    cores; with the longer inner dimension the products take 256 x 256 tiles, odd and even numbers of rows of them, of one triangle only."""
     N = 6
+    assert _route(n, n, k, N, call="dsyrk")[3] == kernel
     rng = np.random.default_rng(3)
     A = _mat(rng, n, k)
     dA = _dev(A)
