@@ -272,17 +272,15 @@ def test_host_product_residues_over_all_legal_sums(index):
 @pytest.mark.parametrize("index", range(26))
 def test_host_short_product_residues(index):
     """Sums of up to 1024 products of two INT8 values, |sum| <= 2^24, one form of which multiplies by 2^32 / p rounded: its error
-    grows with the sum, so both ends are taken whole, and what lies between at random."""
+    grows with the sum and comes close to the distance of two residues.  Every such sum."""
     p = orc.moduli(26)[index]
-    limit = 1024 * 2**14
-    rng = np.random.default_rng(index)
-    near = np.arange(-70000, 70001)
-    c = np.concatenate([near, limit - 140000 + near + 70000, -limit + 140000 + near - 70000, rng.integers(-limit, limit + 1, 1 << 20)])
-    c = np.ascontiguousarray(c[np.abs(c) <= limit].astype(np.int32))
-    assert c.max() == limit and c.min() == -limit
-    got = oz.host_product_residues(index, c, short=True)
-    wrong = c[got != c.astype(np.int64) % p]
-    assert wrong.size == 0, (p, wrong.size, wrong[:5])
+    limit, chunk = 1024 * 2**14, 1 << 22
+    for first in range(-limit, limit + 1, chunk):
+        c = np.arange(first, min(first + chunk, limit + 1), dtype=np.int32)
+        got = oz.host_product_residues(index, c, short=True)
+        wrong = c[got != np.resize((np.arange(p) + first) % p, c.size).astype(np.uint8)]
+        assert wrong.size == 0, (p, wrong.size, wrong[:5])
+    assert c[-1] == limit
 
 
 # ----------------------------------------------------------------------------------------------
