@@ -274,8 +274,8 @@ size_t oz2_workspace_bytes_preferred(int64_t m, int64_t n, int64_t k, int num_mo
  *     B''_lj = ceil(|b_lj| 2^(5-f_j)) in [0, 64] (e_i, f_j = floor(log2) of the row / column maximum), P = A''B''
  *     on the matrix cores, R_i = max_j P_ij, C_j = max_i P_ij, t = min{t : 2^t >= R_i (C_j)}, b = max{b : 2^b <=
  *     M/2 - 1}, sa_i = floor((b - t_i)/2) - (e_i - 5), sb_j likewise; then (|A'||B'|)_ij <= 2^b.  One more pass
- *     over A and B (to form A'' and B''), one more INT8 product and a pass over P; needs k (rounded up to 64) below 2^19, else calls
- *     return OZ2_ERR_BUDGET.
+ *     over A and B (to form A'' and B'') and one more INT8 product, whose maxima are gathered where it is formed or, for the largest,
+ *     in a pass over P; needs k (rounded up to 64) below 2^19, else calls return OZ2_ERR_BUDGET.
  * Returns 0 or -1. */
 int oz2_set_shift_mode(int mode);
 

@@ -587,6 +587,9 @@ __device__ __forceinline__ void convert_contig(const double* __restrict__ B, int
 
 // Both operands of a call in one launch (see operand_max_kernel).  KA / KB: what is written for the first /
 // second job (0, 1: residue planes with the one- / two-level split; 2: the bound plane).
+// FP64 operands that the last-level cache (256 MB) still holds when they are read a second time, nothing written in between: 190 MB.
+// (Residue planes have their own lines, with what lies beside them there: OZ2_CACHED_RESULT those of a result, which stage 3 reads while it
+// writes C; oz2_planes_through_caches those of the operands, which the products read.)
 constexpr int64_t kCachedElements = (int64_t)190 << 17;
 struct ConvJob {
   const double* X;

@@ -17,7 +17,8 @@ static_assert(kThreads == kFallbackThreads, "the small-problem kernel runs both 
 
 // Two elements of C, past the caches: what this launch writes is not read by it again, and left in the L2s it would be given back at the
 // end of the launch, while nothing else runs (whole calls, us, through / past: 14 moduli 2048^3 177.3 / 169.2, 1000 x 1000 x 300 31.2 /
-// 29.3, 1024^3 37.9 / 37.3, 12 moduli dsyrk of order 5000 with 200 139.5 / 135.8, 18 moduli 8192 x 8192 x 1024 1502 / 1483).
+// 29.3, 1024^3 37.9 / 37.3, 12 moduli dsyrk of order 5000 with 200 139.5 / 135.8, 18 moduli 8192 x 8192 x 1024 1502 / 1483; dtrmm 9024 x 1696 2.6 %
+// faster, 3000^3 1.5 %, but 6000 x 2500 1.7 % slower, 4096 x 2048 0.7 %).
 __device__ __forceinline__ void store_past(double* dst, double lo, double hi) {
   typedef double v2d __attribute__((ext_vector_type(2)));
   __builtin_nontemporal_store(v2d{lo, hi}, reinterpret_cast<v2d*>(dst));
