@@ -353,14 +353,19 @@ static hipError_t launch_tiles(int tile, const Oz2Plan& plan, const Oz2Layout& l
 // operand's, which have a workgroup per tile (14 moduli, dtrmm of order 1000 with 2700 columns 86.4 / 93.0).  The rest of their time is
 // shorter with the residues of short sums, in launches of five rounds or more, nine with one or two k-tiles (15 moduli 3512 x 2177 x 278 111.2 /
 // 100.0, 3122 x 4032 x 257 173 / 162, 12 moduli 3045 x 5324 x 121 164 / 157, 17 moduli 3483 x 1266 x 215 72.4 / 69.5; four rounds, 10 moduli
-// 887 x 4989 x 682 77.3 / 81.0, 14 moduli 706 x 5007 x 80 47.7 / 50.7, five 12 moduli 2410 x 2556 x 90 60.0 / 62.4).
+// 887 x 4989 x 682 77.3 / 81.0, 14 moduli 706 x 5007 x 80 47.7 / 50.7, five 12 moduli 2410 x 2556 x 90 60.0 / 62.4).  Not in a symmetric
+// product whose residues' columns are a multiple of 4096 bytes apart, so that the sixteen of a store meet in the same channels (15 moduli,
+// order 3996, inner dimension 200, 106.1 / 131.5, 12 moduli 8192 x 161 323 / 367, 12096 x 161 697 / 755; 10240 x 161 496 / 454, general products in
+// their other order 13 moduli 12288 x 4096 x 200 552 / 485).
 static int tile_size(int64_t m, int64_t n, int64_t k_pad, int num_moduli, int triangle, int krange, int64_t cus) {
   auto rounds = [&](int64_t tile) { return (tiles_of(tile, m, n, triangle) * num_moduli + cus - 1) / cus; };
   if (rounds(64) <= (k_pad / BK >= kDeepKtiles ? 2 : 1)) return 64;
   const int64_t ktiles = krange == OZ2_KRANGE_ALL ? k_pad / BK : (k_pad / BK + 1) / 2;
   const int64_t per_ktile = 270 + (ktiles < 200 ? 0 : ktiles > 445 ? 35 : (ktiles - 200) / 7);
   const int64_t per_large = krange == OZ2_KRANGE_ALL && rounds(256) > 2 ? 660 : 720;
-  const int64_t rest_large = krange == OZ2_KRANGE_ALL && rounds(256) > (ktiles > 2 ? 4 : 8) && k_pad <= OZ2_SHORT_SUM ? 3300 : 4500;
+  const bool same_channels = triangle != 0 && (m + 255) / 256 % 16 == 0;
+  const bool shorter = krange == OZ2_KRANGE_ALL && rounds(256) > (ktiles > 2 ? 4 : 8) && k_pad <= OZ2_SHORT_SUM && !same_channels;
+  const int64_t rest_large = shorter ? 3300 : 4500;
   return rounds(128) * (per_ktile * ktiles + 600) + 3000 < rounds(256) * (per_large * ktiles + rest_large) ? 128 : 256;
 }
 

@@ -480,6 +480,9 @@ def test_kernel_choice_at_the_limits_of_the_rules():
     assert choice(8192, 129, 8192, 16)[1] == 0 and choice(8192, 96, 1024, 16)[1] == 0
     assert [choice(m, m, 300, 14)[2] for m in (200, 500, 4096)] == [64, 128, 256]
     assert [oz.host_kernel_choice(m, m, k, 14, 256, "dsyrk") for m, k in [(200, 300), (500, 300), (5000, 1024)]] == [(4, 0, 64), (4, 0, 128), (8, 0, 256)]
+    # symmetric products of a pitch that is a multiple of 4096: short inner dimensions by small tiles
+    assert [oz.host_kernel_choice(n, n, k, 12, 256, "dsyrk")[2] for n, k in [(12096, 161), (12000, 161), (8192, 300), (8448, 300), (8192, 500)]] == [128, 256, 128, 256, 256]
+    assert choice(12288, 4096, 161, 12)[2] == 256
     # triangular products have no workgroups that fetch across tiles, which large tiles would have to themselves
     assert oz.host_kernel_choice(1000, 2700, 1000, 14, 256, "dtrmm") == (8, 0, 128)
     try:
