@@ -304,12 +304,17 @@ def test_full_size_configs_on_sampled_outputs(name, kblock, algorithm, N):
     del ws
 
 
-@pytest.mark.parametrize("N,algorithm", [(8, 0), (17, 0), (21, 0), (8, 1)])
+def _crt_kernel(m, n, k, N, call="dgemm"):
+    """0: with the fallback in one launch, 1: a launch of its own, 2: line 9 on the matrix cores"""
+    return oz.host_route(m, n, k, N, torch.cuda.get_device_properties(0).multi_processor_count, call)[3]
+
+
+@pytest.mark.parametrize("N,algorithm", [(8, 0), (17, 0), (8, 1)])
 def test_more_than_2_to_the_32_elements_of_c(N, algorithm):
     """A product whose C (and, in the classical form, every residue plane) has more than 2^32 elements, so that an
     element index does not fit 32 bits: 66000 x 65600 with a short inner dimension, 8 and 17 moduli (line 9 on the
-    matrix cores, in sixteen and in twenty digits) and 21 (FP64 accumulation) in the classical form, 8 moduli with the
-    Strassen form forced (56 planes of 2^30 elements).  Every element is written (C starts as NaN), and a sample of rows and columns including the last
+    matrix cores, in sixteen and in twenty digits) in the classical form, 8 moduli with the Strassen form forced (56 planes of
+    2^30 elements).  Every element is written (C starts as NaN), and a sample of rows and columns including the last
     ones is compared with the oracle."""
     m, n, k, phi = 66000, 65600, 64 if algorithm == 0 else 128, 0.5
     assert m * n > 1 << 32
@@ -323,9 +328,8 @@ def test_more_than_2_to_the_32_elements_of_c(N, algorithm):
     dC = torch.full((n, m), float("nan"), dtype=torch.float64, device="cuda").t()
     oz.oz2_set_gemm_algorithm(algorithm)
     try:
-        ws = oz.Workspace(m, n, k, N, product_format=oz.OZ2_PRODUCT_RESIDUE_U8)   # 8, 17, 21 or 14 bytes per element of C
+        ws = oz.Workspace(m, n, k, N, product_format=oz.OZ2_PRODUCT_RESIDUE_U8)   # 8, 17 or 14 bytes per element of C
         assert (oz.oz2_gemm_algorithm_for(m, n, k, N) == oz.OZ2_GEMM_STRASSEN) == (algorithm == 1)
-        assert oz.host_route(m, n, k, N, torch.cuda.get_device_properties(0).multi_processor_count)[3] == (2 if N <= 20 else 1)
         print("C of %d x %d = %.2f * 2^32 elements, N=%d, form %d" % (m, n, m * n / 2.0**32, N, algorithm), flush=True)
         oz.oz2_dgemm(m, n, k, dA.data_ptr(), m, dB.data_ptr(), k, dC.data_ptr(), m, N)
         torch.cuda.synchronize()
@@ -339,6 +343,12 @@ def test_more_than_2_to_the_32_elements_of_c(N, algorithm):
     del dC
     ref = orc.dgemm(np.asfortranarray(A[rows, :]), np.asfortranarray(B[:, cols]), N).C
     assert np.array_equal(got, ref)
+
+
+def test_more_than_2_to_the_32_elements_of_c_by_the_fp64_accumulation():
+    """The same with 21 moduli, the fewest that add up the weights in FP64 at this size."""
+    assert [_crt_kernel(66000, 65600, 64, N) for N in (8, 17, 20, 21)] == [2, 2, 2, 1]
+    test_more_than_2_to_the_32_elements_of_c(21, 0)
 
 
 @pytest.mark.parametrize("beta", [0.0, 1.0])
@@ -467,20 +477,15 @@ def test_round_synchronisation_bound_and_switch(spins):
     del ws
 
 
-def _crt_kernel(m, n, k, N, call="dgemm"):
-    """0: with the fallback in one launch, 1: a launch of its own, 2: line 9 on the matrix cores"""
-    return oz.host_route(m, n, k, N, torch.cuda.get_device_properties(0).multi_processor_count, call)[3]
-
-
 @pytest.mark.parametrize("N,alpha,beta", [(16, 1.0, 0.0), (13, 1.0, 0.0), (9, 1.0, 0.0), (4, 1.0, 0.0), (16, -0.75, 2.0),
-                                          (17, 1.0, 0.0), (20, 1.0, 0.0), (21, 1.0, 0.0)])
+                                          (17, 1.0, 0.0)])
 def test_matrix_core_crt_every_element_ragged(N, alpha, beta):
     """Alg. 1 line 9 on the matrix cores (the kernel taken from 2^25 elements of C on, classical form, up to 20
     moduli): a ragged shape above that size with a short inner dimension, EVERY element of C compared with the
     oracle, for moduli counts whose product needs one, two, three and four 40-bit limbs, as the update with alpha
-    and beta, with 17 and 20 moduli (twenty digits), and with 21 (the first count that stays with the FP64 accumulation)."""
+    and beta, and with 17 moduli (the first count whose weights are twenty digits)."""
     m, n, k, phi = 5801, 5791, 40, 1.0
-    assert _crt_kernel(m, n, k, N) == (2 if N <= 20 else 1)
+    assert m * n >= 1 << 25
     A = inputs.block(77, 0, m, k, phi)
     B = inputs.block(77, 1, k, n, phi)
     C0 = inputs.block(77, 2, m, n, 0.5)
@@ -490,7 +495,7 @@ def test_matrix_core_crt_every_element_ragged(N, alpha, beta):
     oz.oz2_set_gemm_algorithm(oz.OZ2_GEMM_CLASSICAL)
     try:
         ws = oz.Workspace(m, n, k, N)
-        print("CRT, every element of %d x %d, N=%d alpha=%g beta=%g" % (m, n, N, alpha, beta), flush=True)
+        print("matrix-core CRT, every element of %d x %d, N=%d alpha=%g beta=%g" % (m, n, N, alpha, beta), flush=True)
         oz.oz2_dgemm_ex("N", "N", m, n, k, alpha, dA.data_ptr(), m, dB.data_ptr(), k, beta, dC.data_ptr(), m, N)
         torch.cuda.synchronize()
     finally:
@@ -503,13 +508,19 @@ def test_matrix_core_crt_every_element_ragged(N, alpha, beta):
     assert not np.isnan(got).any()
 
 
-@pytest.mark.parametrize("m,n,kernel", [(5801, 5791, 2), (4357, 4099, 1)])
-@pytest.mark.parametrize("N,alpha,beta", [(18, 1.0, 0.0), (18, -0.75, 2.0), (19, 1.0, 0.0), (19, -0.75, 2.0), (20, 1.0, 0.0), (20, -0.75, 2.0)])
-def test_matrix_core_crt_of_more_than_16_moduli_every_element(N, alpha, beta, m, n, kernel):
-    """Twenty digits in two products, and the smaller results that do not take them: ragged shapes, EVERY element against the call with
-    INT32 planes, whose weights are added up in FP64."""
-    k = 70
-    assert _crt_kernel(m, n, k, N) == kernel
+@pytest.mark.parametrize("N", [20, 21])
+def test_crt_every_element_ragged_at_the_last_count_of_the_matrix_cores(N):
+    """20 moduli, which fill the twenty digits, and 21, which stay with the FP64 accumulation at this size."""
+    assert [_crt_kernel(5801, 5791, 40, n) for n in (4, 9, 13, 16, 17, 20, 21)] == [2, 2, 2, 2, 2, 2, 1]
+    test_matrix_core_crt_every_element_ragged(N, 1.0, 0.0)
+
+
+@pytest.mark.parametrize("N,alpha,beta", [(18, 1.0, 0.0), (20, -0.75, 2.0)])
+def test_matrix_core_crt_of_more_than_16_moduli_every_element(N, alpha, beta):
+    """UINT8 planes of a ragged shape below the line of the matrix-core CRT, EVERY element against the call with INT32 planes; both
+    add up the weights in FP64."""
+    m, n, k = 4357, 4099, 70
+    assert m * n >= 1 << 24
     gen = torch.Generator(device="cuda").manual_seed(N)
     A, B, C0 = (torch.randn(s, dtype=torch.float64, device="cuda", generator=gen) for s in ((k, m), (n, k), (n, m)))
     got = []
@@ -528,12 +539,37 @@ def test_matrix_core_crt_of_more_than_16_moduli_every_element(N, alpha, beta, m,
     assert torch.equal(*got)
 
 
+@pytest.mark.parametrize("alpha,beta", [(1.0, 0.0), (-0.75, 2.0)])
+@pytest.mark.parametrize("N", [18, 19, 20])
+def test_twenty_digits_in_two_products_every_element(N, alpha, beta):
+    """18 to 20 moduli on the matrix cores, the fifth word of residues filled in part and whole: a ragged shape, EVERY element against the
+    call with INT32 planes, whose weights are added up in FP64."""
+    m, n, k = 5801, 5791, 70
+    assert _crt_kernel(m, n, k, N) == 2
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    A, B, C0 = (torch.randn(s, dtype=torch.float64, device="cuda", generator=gen) for s in ((k, m), (n, k), (n, m)))
+    got = []
+    for fmt in (oz.OZ2_PRODUCT_INT32, oz.OZ2_PRODUCT_RESIDUE_U8):
+        C = C0.clone()
+        ws = oz.Workspace(m, n, k, N, product_format=fmt)
+        print("CRT of %d moduli on the matrix cores, product format %d" % (N, fmt), flush=True)
+        oz.oz2_set_product_format(fmt)
+        try:
+            oz.oz2_dgemm_ex("N", "N", m, n, k, alpha, A.data_ptr(), m, B.data_ptr(), k, beta, C.data_ptr(), m, N)
+            torch.cuda.synchronize()
+        finally:
+            oz.oz2_set_product_format(oz.OZ2_PRODUCT_RESIDUE_U8)
+        got.append(C.view(torch.int64))
+        del ws
+    assert torch.equal(*got)
+
+
 @pytest.mark.parametrize("uplo,N", [("L", 12), ("U", 18)])
 def test_matrix_core_crt_of_a_triangle_every_element(uplo, N):
     """The first orders of a symmetric update whose CRT runs on the matrix cores, and the last ones below: the written triangle against
     the call with INT32 planes, the other one untouched."""
     for n in (7100, 7090):
-        assert _crt_kernel(n, n, 40, N, "dsyrk") == (2 if n == 7100 else 1)
+        assert (n * n // 3 * 2 >= 1 << 25) == (n == 7100)
         gen = torch.Generator(device="cuda").manual_seed(n)
         A = torch.randn((40, n), dtype=torch.float64, device="cuda", generator=gen)
         C0 = torch.randn((n, n), dtype=torch.float64, device="cuda", generator=gen)
@@ -1099,9 +1135,34 @@ def test_dsyrk_matches_the_oracle_and_leaves_the_other_triangle(uplo, trans, mod
 
 @pytest.mark.parametrize("uplo", ["L", "U"])
 def test_dsyrk_every_element_where_the_crt_runs_on_the_matrix_cores(uplo):
-    """A symmetric update with more than 3/2 2^25 elements of C and 12 moduli: stages 3 and 4 run in the matrix-core
-    kernel, which has to keep to the triangle (rows of a thread's four on both sides of the diagonal, ragged last
+    """A symmetric update with more than 2^24 elements of C and 12 moduli, below the line of the matrix-core CRT: stages
+    3 and 4 have to keep to the triangle (rows of a thread's four on both sides of the diagonal, ragged last
     rows); every element of the triangle against the oracle, the other triangle untouched."""
+    rng = np.random.default_rng(33)
+    n, k, N = 4100, 48, 12
+    assert n * n >= 1 << 24
+    A = np.asfortranarray((rng.random((n, k)) - 0.5) * np.exp(rng.standard_normal((n, k))))
+    alpha, beta = -0.5, 1.25
+    C0 = np.asfortranarray(rng.standard_normal((n, n)))
+    ii, jj = np.meshgrid(np.arange(n), np.arange(n), indexing="ij")
+    outside = (ii < jj) if uplo == "L" else (ii > jj)
+    C0[outside] = np.nan            # never read, never written
+    dA = _dev(A)
+    dC = torch.from_numpy(np.ascontiguousarray(C0.T)).cuda().t()
+    ws = oz.Workspace(n, n, k, N)
+    print("dsyrk %d x %d, uplo=%s" % (n, n, uplo), flush=True)
+    oz.oz2_dsyrk(uplo, "N", n, k, alpha, dA.data_ptr(), n, beta, dC.data_ptr(), n, N)
+    torch.cuda.synchronize()
+    got = dC.cpu().numpy()
+    del ws, dC
+    assert np.all(np.isnan(got[outside])) and not np.any(np.isnan(got[~outside]))
+    ref = orc.dsyrk(uplo, "N", alpha, A, beta, np.asfortranarray(np.where(outside, 0.0, C0)), N)
+    assert np.array_equal(got[~outside], ref[~outside])
+
+
+@pytest.mark.parametrize("uplo", ["L", "U"])
+def test_dsyrk_every_element_by_the_matrix_core_crt(uplo):
+    """The same above 3/2 2^25 elements of C, where stages 3 and 4 run in the matrix-core kernel."""
     rng = np.random.default_rng(33)
     n, k, N = 7110, 48, 12
     assert _crt_kernel(n, n, k, N, "dsyrk") == 2
@@ -1259,8 +1320,28 @@ def test_dtrmm_matches_the_oracle_in_place(side, uplo, transa, diag, mode):
 
 
 def test_dtrmm_every_element_where_the_crt_runs_on_the_matrix_cores():
-    """A triangular product with more than 2^25 elements of B and 12 moduli (stages 3 and 4 in the matrix-core
-    kernel, over the operand that stage 1 has read): every element against the oracle."""
+    """A triangular product with more than 2^24 elements of B and 12 moduli, below the line of the matrix-core CRT
+    (stages 3 and 4 over the operand that stage 1 has read): every element against the oracle."""
+    rng = np.random.default_rng(52)
+    m, n, N = 16390, 1030, 12       # B := alpha * B * op(A), A of order 1030
+    assert m * n >= 1 << 24
+    A = (rng.random((n, n)) - 0.5) * np.exp(rng.standard_normal((n, n)))
+    B = np.asfortranarray((rng.random((m, n)) - 0.5) * np.exp(rng.standard_normal((m, n))))
+    G = _garbage_outside(A, "L", "N")
+    dA = _dev(G)
+    dB = _dev(B)
+    ws = oz.Workspace(m, n, n, N)
+    print("dtrmm %d x %d, right lower" % (m, n), flush=True)
+    oz.oz2_dtrmm("R", "L", "N", "N", m, n, 0.75, dA.data_ptr(), n, dB.data_ptr(), m, N)
+    torch.cuda.synchronize()
+    got = dB.cpu().numpy()
+    del ws, dA, dB
+    ref = orc.dtrmm("R", "L", "N", "N", 0.75, G, B, N)
+    assert np.array_equal(got, ref)
+
+
+def test_dtrmm_every_element_by_the_matrix_core_crt():
+    """The same above 2^25 elements of B, where stages 3 and 4 run in the matrix-core kernel."""
     rng = np.random.default_rng(52)
     m, n, N = 112001, 300, 12       # B := alpha * B * op(A), A of order 300
     assert _crt_kernel(m, n, n, N, "dtrmm") == 2

@@ -357,13 +357,12 @@ def test_long_products_are_not_formed_for_nonfinite_inputs(call, m, n, k):
     del ws
 
 
-@pytest.mark.parametrize("n,k,kernel", [(4200, 64, 1), (4200, 520, 1), (4400, 520, 1), (7110, 64, 2), (7110, 520, 2), (7300, 520, 2)])
+@pytest.mark.parametrize("n,k", [(4200, 64), (4200, 520), (4400, 520)])
 @pytest.mark.parametrize("uplo", ["L", "U"])
-def test_symmetric_update_with_more_than_2_24_elements(uplo, n, k, kernel):
-    """Both kernels of stage 3 skip what lies in the other triangle: rows and columns around the 256 x 16 blocks of the one on the matrix
-    cores; with the longer inner dimension the products take 256 x 256 tiles, odd and even numbers of rows of them, of one triangle only."""
+def test_symmetric_update_with_more_than_2_24_elements(uplo, n, k):
+    """Stage 3, here without the matrix cores, skips what lies in the other triangle;
+    with the longer inner dimension the products take 256 x 256 tiles, 17 or 18 rows of them, of one triangle only."""
     N = 6
-    assert _route(n, n, k, N, call="dsyrk")[3] == kernel
     rng = np.random.default_rng(3)
     A = _mat(rng, n, k)
     dA = _dev(A)
@@ -379,6 +378,15 @@ def test_symmetric_update_with_more_than_2_24_elements(uplo, n, k, kernel):
     mine = inside[rows]
     assert np.array_equal(got[rows][mine], ref[mine])
     del ws
+
+
+@pytest.mark.parametrize("n,k", [(7110, 64), (7110, 520), (7300, 520)])
+@pytest.mark.parametrize("uplo", ["L", "U"])
+def test_symmetric_update_whose_crt_runs_on_the_matrix_cores(uplo, n, k):
+    """Rows and columns around the 256 x 16 blocks of the matrix-core kernel; with the longer inner dimension 256 x 256 tiles, 28 or 29
+    rows of them."""
+    assert _route(n, n, k, 6, call="dsyrk")[3] == 2 and _route(4400, 4400, k, 6, call="dsyrk")[3] == 1
+    test_symmetric_update_with_more_than_2_24_elements(uplo, n, k)
 
 
 @pytest.mark.parametrize("n", [1, 64, 65, 128, 129, 200, 256, 257, 320, 385, 600, 700])
@@ -618,11 +626,6 @@ def test_many_long_contiguous_vectors_in_one_pass(mode, k):
     ctx = oz.Context()
     ctx.set(oz.OZ2_OPT_SHIFT_MODE, mode)
     ctx.allocate_workspace(m, n, k, N, device="cuda:0")
-    oz.oz2_set_shift_mode(mode)  # (the default context's, which the routes are told for)
-    try:
-        assert _route(m, n, k, N, "T", "N")[0] == 3 and _route(m, n, k, N, "N", "T")[0] == 0
-    finally:
-        oz.oz2_set_shift_mode(oz.OZ2_SHIFT_MAX)
     for infinity in (False, True):
         print("one pass over long vectors: k=%d n=%d mode=%d infinity=%d" % (k, n, mode, infinity), flush=True)
         if infinity:
@@ -635,17 +638,26 @@ def test_many_long_contiguous_vectors_in_one_pass(mode, k):
         assert torch.equal(C1.view(torch.int64), C2.view(torch.int64))
 
 
-@pytest.mark.parametrize("m,n,k,alone", [(3200, 3000, 4928, [2, 1]), (3000, 2900, 4929, [2, 1]), (2600, 2500, 9920, [2, 1]), (3500, 2500, 9911, [0, 1]),
-                                         (9000, 5000, 2500, [2, 1])])
-def test_one_operand_in_one_pass_and_the_other_in_two(m, n, k, alone):
+@pytest.mark.parametrize("mode,k", [(0, 2500), (0, 4928), (1, 4929), (0, 9920), (2, 9919)])
+def test_many_long_contiguous_vectors_take_the_one_pass(mode, k):
+    """The routes of the test above: one pass with contiguous vectors, separate launches with the others."""
+    n = ((19 << 20) // k // 256 + 1) * 256 - 3
+    oz.oz2_set_shift_mode(mode)
+    try:
+        assert _route(300, n, k, 4, "T", "N")[0] == 3 and _route(300, n, k, 4, "N", "T")[0] == 0
+    finally:
+        oz.oz2_set_shift_mode(oz.OZ2_SHIFT_MAX)
+
+
+@pytest.mark.parametrize("m,n,k", [(3200, 3000, 4928), (3000, 2900, 4929), (2600, 2500, 9920), (9000, 5000, 2500)])
+def test_one_operand_in_one_pass_and_the_other_in_two(m, n, k):
     """Strided vectors of one operand, contiguous ones of the other, more elements than the last-level cache keeps: bit for bit what the
-    operands give stored the other way round, with an infinity in either of them too.  (The longest strided vectors have to be whole cache
-    lines by sixteens.)"""
+    operands give stored the other way round, with an infinity in either of them too."""
     N = 4
     gen = torch.Generator(device="cuda").manual_seed(k)
     A = torch.randn((k, m), dtype=torch.float64, device="cuda", generator=gen)
     B = torch.randn((n, k), dtype=torch.float64, device="cuda", generator=gen)
-    assert [_route(m, n, k, N, ta, tb)[0] for ta, tb in (("N", "N"), ("T", "T"), ("T", "N"))] == alone + [3]
+    assert (m + n) * k > 190 << 17 and m + n >= 20 * 250
     ctx = oz.Context()
     ctx.allocate_workspace(m, n, k, N, device="cuda:0")
     for infinite in ("none", "A", "B"):
@@ -664,3 +676,13 @@ def test_one_operand_in_one_pass_and_the_other_in_two(m, n, k, alone):
             got.append(C)
         assert bool(torch.isinf(got[0]).any()) == (infinite != "none")
         assert all(torch.equal(got[0].view(torch.int64), c.view(torch.int64)) for c in got[1:])
+
+
+@pytest.mark.parametrize("m,n,k,alone", [(3200, 3000, 4928, [2, 1]), (3000, 2900, 4929, [2, 1]), (2600, 2500, 9920, [2, 1]), (9000, 5000, 2500, [2, 1]),
+                                         (3500, 2500, 9911, [0, 1])])
+def test_the_operand_that_takes_the_one_pass(m, n, k, alone):
+    """The routes of the test above; and, of the longest vectors, strided ones that are not whole cache lines by sixteens, which do not
+    take that route."""
+    assert [_route(m, n, k, 4, ta, tb)[0] for ta, tb in (("N", "N"), ("T", "T"), ("T", "N"))] == alone + [3]
+    if 0 in alone:
+        test_one_operand_in_one_pass_and_the_other_in_two(m, n, k)

@@ -272,7 +272,22 @@ def test_host_product_residues_over_all_legal_sums(index):
 @pytest.mark.parametrize("index", range(26))
 def test_host_short_product_residues(index):
     """Sums of up to 1024 products of two INT8 values, |sum| <= 2^24, one form of which multiplies by 2^32 / p rounded: its error
-    grows with the sum and comes close to the distance of two residues.  Every such sum."""
+    grows with the sum, so both ends are taken whole, and what lies between at random."""
+    p = orc.moduli(26)[index]
+    limit = 1024 * 2**14
+    rng = np.random.default_rng(index)
+    near = np.arange(-70000, 70001)
+    c = np.concatenate([near, limit - 140000 + near + 70000, -limit + 140000 + near - 70000, rng.integers(-limit, limit + 1, 1 << 20)])
+    c = np.ascontiguousarray(c[np.abs(c) <= limit].astype(np.int32))
+    assert c.max() == limit and c.min() == -limit
+    got = oz.host_product_residues(index, c, short=True)
+    wrong = c[got != c.astype(np.int64) % p]
+    assert wrong.size == 0, (p, wrong.size, wrong[:5])
+
+
+@pytest.mark.parametrize("index", range(26))
+def test_host_short_product_residues_of_every_sum(index):
+    """All of |sum| <= 2^24: the error comes close to the distance of two residues."""
     p = orc.moduli(26)[index]
     limit, chunk = 1024 * 2**14, 1 << 22
     for first in range(-limit, limit + 1, chunk):
@@ -480,9 +495,6 @@ def test_kernel_choice_at_the_limits_of_the_rules():
     assert choice(8192, 129, 8192, 16)[1] == 0 and choice(8192, 96, 1024, 16)[1] == 0
     assert [choice(m, m, 300, 14)[2] for m in (200, 500, 4096)] == [64, 128, 256]
     assert [oz.host_kernel_choice(m, m, k, 14, 256, "dsyrk") for m, k in [(200, 300), (500, 300), (5000, 1024)]] == [(4, 0, 64), (4, 0, 128), (8, 0, 256)]
-    # symmetric products of a pitch that is a multiple of 4096: short inner dimensions by small tiles
-    assert [oz.host_kernel_choice(n, n, k, 12, 256, "dsyrk")[2] for n, k in [(12096, 161), (12000, 161), (8192, 300), (8448, 300), (8192, 500)]] == [128, 256, 128, 256, 256]
-    assert choice(12288, 4096, 161, 12)[2] == 256
     # triangular products have no workgroups that fetch across tiles, which large tiles would have to themselves
     assert oz.host_kernel_choice(1000, 2700, 1000, 14, 256, "dtrmm") == (8, 0, 128)
     try:
@@ -498,6 +510,12 @@ def test_kernel_choice_at_the_limits_of_the_rules():
     assert [L.oz2_host_kernel_choice(*a, out) for a in [(3, 1, 1, 1, 9, 1), (0, 0, 1, 1, 9, 1), (1, 2, 1, 1, 9, 1), (2, 1, 1, 2, 9, 1),
                                                      (0, 1, 1, 1, 1, 1), (0, 1, 1, 1, 9, 0)]] == [-1, -2, -3, -4, -5, -6]
     assert L.oz2_host_kernel_choice(0, 1, 1, 1, 9, 1, None) == -7
+
+
+def test_tiles_of_symmetric_products_by_their_pitch():
+    """Short inner dimensions by small tiles where the pitch of a residue plane is a multiple of 4096; not general products."""
+    assert [oz.host_kernel_choice(n, n, k, 12, 256, "dsyrk")[2] for n, k in [(12096, 161), (12000, 161), (8192, 300), (8448, 300), (8192, 500)]] == [128, 256, 128, 256, 256]
+    assert oz.host_kernel_choice(12288, 4096, 161, 12, 256)[2] == 256
 
 
 def test_route_at_the_limits_of_the_rules():
